@@ -4,13 +4,18 @@
 // ADERF and SDERF), as the statistics kernels leave them.  Output: one theta block per group (layout in
 // favorsharp.h) and one status word per group.
 //
-// The symmetric eigenproblems (M1, M2, and N = M1 + mu4 mu5^T + mu5 mu4^T + M2) are solved by the two-sided Jacobi
-// iteration, the singular value problem of the ADERF matrix Lambda1^(1/2) Q1^T Q2 Lambda2^(1/2) by the one-sided
-// (Hestenes) iteration on its columns, whose normalised columns are the left singular vectors.  Both use the
-// round-robin ordering: a round rotates d/2 disjoint index pairs at once, a few lanes per pair, one or two barriers
-// per round.  The matrix lives in LDS during the iteration, and so do the accumulated rotations when both fit
-// (d <= 96).
+// The symmetric eigenproblems (M1, M2, and N = M1 + mu4 mu5^T + mu5 mu4^T + M2) are reduced to tridiagonal form by
+// Householder reflections with the matrix in registers; eigenvalues by bisection on Sturm sequences, all of them side
+// by side; eigenvectors of the tridiagonal matrix from twisted factorisations (Fernando; Parlett and Dhillon), one lane
+// per vector; the reflections are then applied to them (`eig_tridiagonal`).  Matrices with (nearly) equal eigenvalues,
+// for which such vectors are not orthogonal by themselves, are decomposed by the two-sided Jacobi iteration instead.
+// The singular value problem of the ADERF matrix Lambda1^(1/2) Q1^T Q2 Lambda2^(1/2) is solved by the one-sided
+// (Hestenes) iteration on its columns, whose normalised columns are the left singular vectors.  Both iterations use
+// the round-robin ordering: a round rotates d/2 disjoint index pairs at once, a few lanes per pair, one or two barriers
+// per round.  Their matrix lives in LDS, and so do the accumulated rotations when both fit (d <= 96).
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "kernels.h"
 
@@ -44,7 +49,9 @@ struct FitShared {
   double nrm[3][FIT_DMAX];   // column norms after an iteration (eigenvalues / singular values, unsorted)
   double sgn[3][FIT_DMAX];   // sign that makes the largest component of an eigenvector positive
   int ord[3][FIT_DMAX];      // ord[k] = column with the k-th largest norm
+  double red_row[FIT_DMAX];  // per-row scale factors of the results
   double red[8];             // scalars shared by the workgroup
+  int twist[FIT_DMAX];
   int flag;
 };
 
@@ -344,6 +351,451 @@ __device__ __forceinline__ void decompose(double* g, double* v, int n, int k, bo
   __syncthreads();
 }
 
+// ---------------------------------------------------------------------------------------------------
+// Symmetric eigenproblem by reduction to tridiagonal form, one workgroup, everything in fp64.
+//
+// What bounds it is latency (one workgroup per matrix, a few matrices per call), so the design counts dependent steps:
+// the reduction has two barriers per column against two barriers per rotation round of the Jacobi iteration, which
+// needs (n - 1) x 6 - 8 rounds; everything after the reduction has no barrier per step at all.  Measured (8 matrices of
+// 64: k_fit_device 686 -> 108 us; 16 matrices of 128: 7290 -> 325 us).
+// ---------------------------------------------------------------------------------------------------
+
+// Gap between neighbouring eigenvalues (in units of the trace) below which the vectors of `eig_tridiagonal` are not
+// used: their inner product is about 1e-18 / gap (measured on matrices of 2 .. 128), 1e-8 here, below the rounding of
+// the fp32 results.
+constexpr double kMinGap = 1e-10;
+
+__device__ __forceinline__ double rcp64(double x) {        // hardware estimate and two Newton steps
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
+__device__ __forceinline__ double rsqrt64(double x) {
+  double r = __builtin_amdgcn_rsq(x);
+  r = fma(fma(-x * r, r, 1.0), 0.5 * r, r);
+  return fma(fma(-x * r, r, 1.0), 0.5 * r, r);
+}
+
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kMirror8 = 0x141, kMirror16 = 0x140;      // DPP controls
+template <int CTRL>
+__device__ __forceinline__ double dpp64(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+// Exchanges the odd 16-lane rows of x with the even rows of y and adds: rows 0, 2 of the result are the sums of x over
+// the row pairs (0, 1), (2, 3), rows 1, 3 those of y.
+__device__ __forceinline__ double add_rows16(double x, double y) {
+  const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(x), (unsigned)__double2loint(y), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(y), false, false);
+  return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+__device__ __forceinline__ double add_halves32(double x, double y) {     // the same with the two halves of the wave
+  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(x), (unsigned)__double2loint(y), false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(x), (unsigned)__double2hiint(y), false, false);
+  return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+__device__ __forceinline__ double sum8(double v) {         // over aligned groups of 8 lanes
+  v += dpp64<kXor1>(v);
+  v += dpp64<kXor2>(v);
+  return v + dpp64<kMirror8>(v);
+}
+__device__ __forceinline__ double sum64(double v) {        // over the wave
+  v = sum8(v);
+  v += dpp64<kMirror16>(v);
+  v = add_rows16(v, v);
+  return add_halves32(v, v);
+}
+
+// LDS of `eig_tridiagonal` (doubles; NP = 32 RJ): reflectors [NP][NP], two vectors of NP, (diagonal, e^2) pairs, e,
+// eigenvalues, partial norms, partial minima with their rows (one per thread); for NP = 64 also the multipliers of the
+// twisted factorisations [2][NP][NP].
+constexpr size_t tri_lds_doubles(int NP) { return (size_t)(NP == 64 ? 3 : 1) * NP * NP + 8 * (size_t)NP + FIT_NT + FIT_NT / 2; }
+
+// a: the matrix, entry (ti + 4 RJ ii, tj + 32 jj) in a[ii][jj] of thread (ti = t / 32, tj = t % 32) < 128 RJ, zero
+// outside n x n (destroyed).  `scale`: its trace (positive semidefinite: no eigenvalue is larger).  On success the
+// eigenvalues go to slot k of the shared block with their order and signs (as rank_columns leaves them) and eigenvector
+// j to column j of v (global, column-major with stride n).  scr: 2 n n doubles of global scratch (NP = 128).  Returns
+// false, with nothing written outside LDS and scr, when two eigenvalues are closer than kMinGap.
+template <int RJ>
+__device__ __forceinline__ bool eig_tridiagonal(double (&a)[8][RJ], int n, double scale, double* v, double* scr, int k_slot,
+                                                FitShared& sh, double* lds) {
+  constexpr int NP = 32 * RJ, RI = 8, HT = 128 * RJ, RS = 4 * RJ;      // HT threads hold the matrix, rows RS apart
+  auto IB = [](int jc) constexpr { return 32 * jc / RS; };             // first register row of column block jc
+  constexpr bool kInLds = NP == 64;
+  double* refl = lds;                                // reflector k: refl[k * NP + i], zero for i <= k
+  double* col = refl + (size_t)NP * NP;
+  double* pv = col + NP;
+  f64x2* de = (f64x2*)(pv + NP);                     // (d_i, e_{i-1}^2)
+  double* es = (double*)(de + NP);
+  double* lam = es + NP;
+  double* nsq = lam + NP;                            // [2][NP]
+  double* part_val = nsq + 2 * NP;
+  int* part_arg = (int*)(part_val + FIT_NT);
+  double* mul = part_val + FIT_NT + FIT_NT / 2;      // NP = 64: [2][n][n]
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, ti = t >> 5, tj = t & 31;
+
+  // ---- Householder reduction: A <- H A H with H = I - u u^T, |u|^2 = 2, column by column: u from column k (every wave
+  // forms it by itself: no barrier), p = A u, w = p - (u^T p / 2) u, A <- A - u w^T - w u^T.  The loop over blocks of 32
+  // columns is unrolled so that registers of finished rows and columns are skipped at compile time.  A wave issues one
+  // instruction per 6 cycles, two waves of a SIMD one fp64 instruction each per 8: with n <= 64 half the waves hold the
+  // whole matrix (2360 -> 2060 cycles per column on 4 instead of 8 waves), the others only meet the barriers.
+#pragma unroll
+  for (int jc = 0; jc < RJ; ++jc) {
+    for (int kk = 0; kk < 32; ++kk) {
+      const int k = 32 * jc + kk;
+      if (k > n - 3) break;
+      if (t < HT && tj == kk) {
+#pragma unroll
+        for (int ii = 0; ii < RI; ++ii) {
+          const int i = ti + RS * ii;
+          col[i] = i > k ? a[ii][jc] : 0.0;
+          if (i == k) de[k].x = a[ii][jc];
+        }
+      }
+      __syncthreads();
+      double xl[NP / 64], ui[RI], uj[RJ];
+      if (t < HT) {      // u = (x - beta e_0) / sqrt(|x| (|x| + |x_0|))
+        const double x0 = col[k + 1];
+        double n2 = 0.0;
+#pragma unroll
+        for (int q = 0; q < NP / 64; ++q) { xl[q] = col[lane + 64 * q]; n2 += xl[q] * xl[q]; }
+#pragma unroll
+        for (int ii = IB(jc); ii < RI; ++ii) ui[ii] = col[ti + RS * ii];
+#pragma unroll
+        for (int jj = jc; jj < RJ; ++jj) uj[jj] = col[tj + 32 * jj];
+        n2 = sum64(n2);
+        double beta = 0.0, f = 0.0;
+        if (n2 > 1e-290) {
+          const double nrm = n2 * rsqrt64(n2);
+          beta = -copysign(nrm, x0);
+          f = rsqrt64(nrm * (nrm + fabs(x0)));
+        }
+        const double fb = f * beta;
+#pragma unroll
+        for (int ii = IB(jc); ii < RI; ++ii) ui[ii] = ui[ii] * f - (ti + RS * ii == k + 1 ? fb : 0.0);
+#pragma unroll
+        for (int jj = jc; jj < RJ; ++jj) uj[jj] = uj[jj] * f - (tj + 32 * jj == k + 1 ? fb : 0.0);
+#pragma unroll
+        for (int q = 0; q < NP / 64; ++q) xl[q] = xl[q] * f - (lane + 64 * q == k + 1 ? fb : 0.0);
+        if (wave == 0) {
+#pragma unroll
+          for (int q = 0; q < NP / 64; ++q) refl[(size_t)k * NP + lane + 64 * q] = xl[q];
+          if (lane == 0) es[k] = beta;
+        }
+        // p = A u: partial sums of a row over the 32 lanes of its half wave, folded so that every lane ends with one row
+        double s[RI];
+#pragma unroll
+        for (int ii = 0; ii < RI; ++ii) {
+          s[ii] = 0.0;
+          if (ii >= IB(jc)) {
+#pragma unroll
+            for (int jj = jc; jj < RJ; ++jj) s[ii] += a[ii][jj] * uj[jj];
+          }
+        }
+        const bool b3 = lane & 8, b2 = lane & 4;
+        double q4[4], q2[2];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) q4[q] = add_rows16(s[2 * q], s[2 * q + 1]);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) q2[q] = (b3 ? q4[2 * q + 1] : q4[2 * q]) + dpp64<kMirror16>(b3 ? q4[2 * q] : q4[2 * q + 1]);
+        double r = (b2 ? q2[1] : q2[0]) + dpp64<kMirror8>(b2 ? q2[0] : q2[1]);
+        r += dpp64<kXor2>(r);
+        r += dpp64<kXor1>(r);
+        if ((lane & 3) == 0) pv[ti + RS * (4 * (b2 ? 1 : 0) + 2 * (b3 ? 1 : 0) + ((lane >> 4) & 1))] = r;
+      }
+      __syncthreads();
+      if (t < HT) {
+        double up = 0.0;
+#pragma unroll
+        for (int q = 0; q < NP / 64; ++q) up += xl[q] * pv[lane + 64 * q];
+        double wi[RI], wj[RJ];
+#pragma unroll
+        for (int ii = IB(jc); ii < RI; ++ii) wi[ii] = pv[ti + RS * ii];
+#pragma unroll
+        for (int jj = jc; jj < RJ; ++jj) wj[jj] = pv[tj + 32 * jj];
+        const double K = 0.5 * sum64(up);
+#pragma unroll
+        for (int ii = IB(jc); ii < RI; ++ii) wi[ii] -= K * ui[ii];
+#pragma unroll
+        for (int jj = jc; jj < RJ; ++jj) wj[jj] -= K * uj[jj];
+#pragma unroll
+        for (int ii = IB(jc); ii < RI; ++ii)
+#pragma unroll
+          for (int jj = jc; jj < RJ; ++jj) a[ii][jj] -= ui[ii] * wj[jj] + wi[ii] * uj[jj];
+      }
+    }
+  }
+#pragma unroll
+  for (int ii = 0; ii < RI; ++ii)
+#pragma unroll
+    for (int jj = 0; jj < RJ; ++jj) {
+      const int i = ti + RS * ii, j = tj + 32 * jj;
+      if (t >= HT) continue;
+      if (i == j && i < n && i >= n - 2) de[i].x = a[ii][jj];
+      if (i == n - 1 && j == n - 2) es[n - 2] = a[ii][jj];
+    }
+  __syncthreads();
+  // in units of the trace; off-diagonal entries at least 1e-17 (far below the rounding of the reduction), so that no
+  // Sturm sequence and no factorisation meets an exact split; entries behind the matrix keep the sign of a sequence
+  {
+    const double inv = 1.0 / scale;
+    double dd = 2.0, e2 = 1e-34;
+    if (t < NP) {
+      if (t < n) dd = de[t].x * inv;
+      if (t >= 1 && t < n) { const double e = fmax(fabs(es[t - 1] * inv), 1e-17); e2 = e * e; }
+    }
+    double ee = 0.0;
+    if (t < n - 1) { ee = es[t] * inv; if (fabs(ee) < 1e-17) ee = 1e-17; }
+    __syncthreads();
+    if (t < NP) { de[t] = f64x2{dd, e2}; es[t] = ee; }
+    __syncthreads();
+  }
+
+  // ---- eigenvalues: 256 / NP lanes per eigenvalue split its interval into as many parts + 1.  The sequence of leading
+  // minors in its three-term form: one dependent multiply-add per row, rescaled every 16 rows (a factor of at least
+  // 1e-34 per two rows: no underflow before).  One wave per SIMD: with twice the lanes (and a quarter fewer steps) the
+  // waves share the fp64 issue slots (50 k -> 60 k cycles at n = 64).
+  if (t < 256) {
+    constexpr int S = 256 / NP;
+    const int j = t / S, sec = t % S;
+    const double frac = (double)(sec + 1) / (double)(S + 1);
+    double lo = -1e-9, hi = 1.0 + 1e-9;
+    const int steps = S == 4 ? 24 : 35;              // 5^24, 3^35 > 2^55
+    for (int it = 0; it < steps; ++it) {
+      const double x = fma(hi - lo, frac, lo);
+      double p1 = 1.0, p2 = 0.0;
+      unsigned bits = 0;
+      int cnt = 0;
+      for (int i0 = 0; i0 < n; i0 += 16) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const f64x2 c = de[i0 + i];
+          const double p = fma(c.x - x, p1, -(c.y * p2));
+          p2 = p1;
+          p1 = p;
+          bits = __builtin_amdgcn_alignbit(bits, (unsigned)__double2hiint(p), 31);     // shift the sign in
+        }
+        cnt += __popc((bits ^ (bits >> 1)) & 0xffffu);
+        const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(p1), fabs(p2)));
+        p1 = ldexp(p1, -ex);
+        p2 = ldexp(p2, -ex);
+      }
+      double nlo = cnt <= j ? x : lo, nhi = cnt <= j ? hi : x;
+      nlo = fmax(nlo, dpp64<kXor1>(nlo));
+      nhi = fmin(nhi, dpp64<kXor1>(nhi));
+      if constexpr (S == 4) {
+        nlo = fmax(nlo, dpp64<kXor2>(nlo));
+        nhi = fmin(nhi, dpp64<kXor2>(nhi));
+      }
+      lo = nlo;
+      hi = nhi;
+    }
+    if (sec == 0) lam[j] = 0.5 * (lo + hi);
+  }
+  if (t == 0) sh.flag = 0;
+  __syncthreads();
+  if (t < n - 1 && !(lam[t + 1] - lam[t] > kMinGap)) sh.flag = 1;
+  __syncthreads();
+  if (sh.flag) return false;
+
+  // ---- eigenvectors of the tridiagonal matrix.  Forward and backward factorisations of T - lambda_j, a lane per j:
+  // l_i = e_i / D+_i and u_i = e_i / D-_{i+1}; the twist index r minimises |gamma_i| (largest component of the vector).
+  // The pivots are quotients of successive minors, so that the chain from row to row is the minors' recurrence and the
+  // divisions run beside it.
+  double* fl = kInLds ? mul : scr;                   // l_i of vector j at fl[i * n + j], later its component i (i < r)
+  double* bu = fl + (size_t)n * n;                   // u_i, later component i + 1 (i >= r)
+  constexpr int NW = NP / 64;                        // waves per direction
+  constexpr double kTiny = 1e-30;                    // smallest pivot (far below the error of the eigenvalue)
+  const int vj = min(t & (NP - 1), n - 1);
+  const bool mine = (t & (NP - 1)) < n, fwd = wave < NW, bwd = wave >= NW && wave < 2 * NW;
+  const double lj = lam[vj];
+  if (fwd || bwd) {
+    const int r0 = fwd ? 0 : n - 1, step = fwd ? 1 : -1, eoff = fwd ? 0 : -1;
+    double* out = (fwd ? fl : bu) + vj;
+    double p1 = 1.0, p2 = 0.0, e2 = 0.0;
+    auto row = [&](int i) {
+      const double e = es[i + eoff];
+      double p = fma(de[i].x - lj, p1, -(e2 * p2));
+      p = copysign(fmax(fabs(p), kTiny * fabs(p1)), p);
+      out[(i + eoff) * n] = e * p1 * rcp64(p);       // (lanes past the last vector repeat it)
+      e2 = e * e;
+      p2 = p1;
+      p1 = p;
+    };
+    int i0 = 0;
+    for (; i0 + 8 <= n - 1; i0 += 8) {
+#pragma unroll
+      for (int m = 0; m < 8; ++m) row(r0 + step * (i0 + m));
+      const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(p1), fabs(p2)));
+      p1 = ldexp(p1, -ex);
+      p2 = ldexp(p2, -ex);
+    }
+    for (; i0 < n - 1; ++i0) row(r0 + step * i0);
+  }
+  __syncthreads();
+  {   // gamma_i = d_i - lambda - u_i e_i - l_{i-1} e_{i-1}: NT / NP threads per vector, a range of rows each
+    constexpr int NC = FIT_NT / NP;
+    const int c = t / NP, len = (n + NC - 1) / NC;
+    double best = 1e300;
+    int arg = 0;
+    for (int i0 = c * len; i0 < min(n, (c + 1) * len); i0 += 16) {
+      double ub[16], lb[16];             // (sixteen rows' loads in flight; clamped, as es is zero past the last row)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        ub[q] = bu[(size_t)min(i0 + q, max(n - 2, 0)) * n + vj];
+        lb[q] = fl[(size_t)min(max(i0 + q - 1, 0), max(n - 2, 0)) * n + vj];
+      }
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const int i = i0 + q;
+        if (i < min(n, (c + 1) * len)) {
+          double g = de[i].x - lj;
+          if (i < n - 1) g -= ub[q] * es[i];
+          if (i > 0) g -= lb[q] * es[i - 1];
+          if (fabs(g) < best) { best = fabs(g); arg = i; }
+        }
+      }
+    }
+    part_val[t] = best;
+    part_arg[t] = arg;
+  }
+  __syncthreads();
+  int rtw = part_arg[t & (NP - 1)];
+  {
+    double best = part_val[t & (NP - 1)];
+#pragma unroll
+    for (int i = (t & (NP - 1)) + NP; i < FIT_NT; i += NP)
+      if (part_val[i] < best) { best = part_val[i]; rtw = part_arg[i]; }
+  }
+  if (fwd && mine) {
+    double z = 1.0, q = 0.0;
+    for (int i0 = n - 2; i0 >= 0; i0 -= 16) {
+      double l[16];
+#pragma unroll
+      for (int m = 0; m < 16; ++m) l[m] = fl[(size_t)max(i0 - m, 0) * n + vj];
+#pragma unroll
+      for (int m = 0; m < 16; ++m)
+        if (i0 - m >= 0 && i0 - m < rtw) {
+          z *= -l[m];
+          q += z * z;
+          fl[(size_t)(i0 - m) * n + vj] = z;
+        }
+    }
+    nsq[vj] = q;
+  } else if (bwd && mine) {
+    double z = 1.0, q = 0.0;
+    for (int i0 = 0; i0 < n - 1; i0 += 16) {
+      double u[16];
+#pragma unroll
+      for (int m = 0; m < 16; ++m) u[m] = bu[(size_t)min(i0 + m, n - 2) * n + vj];
+#pragma unroll
+      for (int m = 0; m < 16; ++m)
+        if (i0 + m < n - 1 && i0 + m >= rtw) {
+          z *= -u[m];
+          q += z * z;
+          bu[(size_t)(i0 + m) * n + vj] = z;
+        }
+    }
+    nsq[NP + vj] = q;
+  }
+  if (t < NP) sh.twist[t] = rtw;
+  __syncthreads();
+
+  // ---- the reflections applied to the vectors: eight lanes per RC vectors, a lane holds rows 2 part + 16 q + {0, 1}.
+  constexpr int RC = NP / 64, NQ = NP / 16;
+  const int part = t & 7, grp = t >> 3;
+  double z[RC][2 * NQ];
+#pragma unroll
+  for (int c = 0; c < RC; ++c) {
+    const int j = grp + 64 * c, jc = min(j, n - 1), rt = sh.twist[jc];
+    const double sc = j < n ? rsqrt64(1.0 + nsq[jc] + nsq[NP + jc]) : 0.0;
+#pragma unroll
+    for (int q = 0; q < 2 * NQ; ++q) {
+      const int i = 2 * part + 16 * (q >> 1) + (q & 1);
+      double x = 0.0;
+      if (i < n) x = i == rt ? 1.0 : (i < rt ? fl[(size_t)i * n + jc] : bu[(size_t)(i - 1) * n + jc]);
+      z[c][q] = x * sc;
+    }
+  }
+  // (sixteen reflectors per block, so that the rows above them are skipped at compile time; the next reflector is
+  // requested while the current one is used)
+#pragma unroll
+  for (int jb = NQ - 1; jb >= 0; --jb) {
+    const int ktop = min(n - 3, 16 * jb + 15);
+    if (ktop < 16 * jb) continue;
+    const f64x2* up = (const f64x2*)(refl + (size_t)ktop * NP) + part;
+    f64x2 u[NQ];
+#pragma unroll
+    for (int q = jb; q < NQ; ++q) u[q] = up[8 * q];
+    for (int k = ktop; k >= 16 * jb; --k) {
+      up -= k > 0 ? NP / 2 : 0;
+      f64x2 un[NQ];
+#pragma unroll
+      for (int q = jb; q < NQ; ++q) un[q] = up[8 * q];
+#pragma unroll
+      for (int c = 0; c < RC; ++c) {
+        double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+        for (int q = jb; q < NQ; ++q) { s0 += u[q].x * z[c][2 * q]; s1 += u[q].y * z[c][2 * q + 1]; }
+        const double sm = sum8(s0 + s1);
+#pragma unroll
+        for (int q = jb; q < NQ; ++q) { z[c][2 * q] -= u[q].x * sm; z[c][2 * q + 1] -= u[q].y * sm; }
+      }
+#pragma unroll
+      for (int q = jb; q < NQ; ++q) u[q] = un[q];
+    }
+  }
+  // results: vectors, and per vector the sign that makes its largest component positive (lowest index on ties)
+#pragma unroll
+  for (int c = 0; c < RC; ++c) {
+    const int j = grp + 64 * c;
+    double big = 0.0;
+    int at = 0;
+#pragma unroll
+    for (int q = 0; q < 2 * NQ; ++q) {
+      const int i = 2 * part + 16 * (q >> 1) + (q & 1);
+      if (j < n && i < n) v[(size_t)j * n + i] = z[c][q];
+      if (fabs(z[c][q]) > fabs(big)) { big = z[c][q]; at = i; }
+    }
+    for (int m = 1; m < 8; m <<= 1) {
+      const double ob = __shfl_xor(big, m, 64);
+      const int oa = __shfl_xor(at, m, 64);
+      if (fabs(ob) > fabs(big) || (fabs(ob) == fabs(big) && oa < at)) { big = ob; at = oa; }
+    }
+    if (part == 0 && j < n) {
+      sh.sgn[k_slot][j] = big < 0.0 ? -1.0 : 1.0;
+      sh.nrm[k_slot][j] = lam[j] * scale;
+      sh.ord[k_slot][n - 1 - j] = j;                 // eigenvalues came out in ascending order
+    }
+  }
+  __syncthreads();
+  return true;
+}
+
+// Eigen-decomposition of the symmetric positive semidefinite matrix entry(i, j) with trace `tr`: into slot k and v as
+// above; g: n x n doubles (the Jacobi form's matrix), scr: 2 n n doubles, both global.
+template <int RJ, class Entry>
+__device__ __forceinline__ void decompose_symmetric(Entry entry, double tr, double* g, double* v, double* scr, int n, int k,
+                                                    FitShared& sh, double* lds) {
+  const int t = threadIdx.x, ti = t >> 5, tj = t & 31;
+  if (n > 1 && tr > 1e-280 && tr < 1e280) {
+    double a[8][RJ];
+#pragma unroll
+    for (int ii = 0; ii < 8; ++ii)
+#pragma unroll
+      for (int jj = 0; jj < RJ; ++jj) {
+        const int i = ti + 4 * RJ * ii, j = tj + 32 * jj;
+        a[ii][jj] = t < 128 * RJ && i < n && j < n ? entry(i, j) : 0.0;
+      }
+    if (eig_tridiagonal<RJ>(a, n, tr, v, scr, k, sh, lds)) return;
+  }
+  for (int e = t; e < n * n; e += FIT_NT) g[e] = entry(e / n, e % n);
+  __syncthreads();
+  decompose(g, v, n, k, true, sh, lds);
+}
+
 __device__ void write_header(float* th, double logD, double lbar, int flags, int variant) {
   th[0] = (float)logD;
   th[1] = (float)lbar;
@@ -353,6 +805,8 @@ __device__ void write_header(float* th, double logD, double lbar, int flags, int
 }
 
 // grid (groups), block FIT_NT.  stats: per group [M1 d*d, mu4 d][M2 d*d, mu5 d]; ws: per group 7 d*d doubles.
+// RJ: d <= 32 RJ (the columns of a matrix per thread of eig_tridiagonal).
+template <int RJ>
 __global__ void __launch_bounds__(FIT_NT) k_fit_device(int variant, int d, const double* stats, double ridge, double* ws,
                                                        float* theta, int* status, size_t theta_floats) {
   extern __shared__ __align__(16) unsigned char fit_lds[];
@@ -373,9 +827,16 @@ __global__ void __launch_bounds__(FIT_NT) k_fit_device(int variant, int d, const
   double* lds = (double*)fit_lds;
   const double nan = __builtin_nan("");
 
-  // traces and mu4 . mu5 (every thread computes them: d <= 128 terms)
+  // traces and mu4 . mu5 (every wave sums them for itself: d <= 128 terms)
   double tr1 = 0.0, tr2 = 0.0, dot = 0.0;
-  for (int l = 0; l < d; ++l) { tr1 += M1[(size_t)l * d + l]; tr2 += M2[(size_t)l * d + l]; dot += mu4[l] * mu5[l]; }
+  for (int l = t & 63; l < d; l += 64) {
+    tr1 += M1[(size_t)l * d + l];
+    tr2 += M2[(size_t)l * d + l];
+    dot += mu4[l] * mu5[l];
+  }
+  tr1 = sum64(tr1);
+  tr2 = sum64(tr2);
+  dot = sum64(dot);
 
   if (variant <= 2) {                                   // PosRF, GERF, SADERF: A = a I, diagonal B and C
     // psi_l = (M2_ll / M1_ll)^(1/4) for SADERF, 1 otherwise
@@ -419,20 +880,20 @@ __global__ void __launch_bounds__(FIT_NT) k_fit_device(int variant, int d, const
   if (variant == 4) {                                   // SDERF: one eigendecomposition of N
     double* N = w;
     double* V = w + nn;
-    for (int e = t; e < nn; e += FIT_NT) {
-      const int r = e / d, c = e % d;
-      N[e] = M1[e] + mu4[r] * mu5[c] + mu5[r] * mu4[c] + M2[e];
-    }
+    decompose_symmetric<RJ>([=](int r, int c) {
+      const size_t e = (size_t)r * d + c;
+      return M1[e] + mu4[r] * mu5[c] + mu5[r] * mu4[c] + M2[e];
+    }, tr1 + tr2 + 2.0 * dot, N, V, w + 4 * (size_t)nn, n, 0, sh, lds);
+    // row scales: sqrt(1 - 4a), with the sign of the eigenvector
+    if (t < d) sh.red_row[t] = sqrt(1.0 - 4.0 * a_star(fmax(sh.nrm[0][t], 0.0))) * sh.sgn[0][t];
     __syncthreads();
-    decompose(N, V, n, 0, true, sh, lds);
     for (int e = t; e < nn; e += FIT_NT) {              // B = (I - 4A)^(1/2) Q3^T: row l is the scaled eigenvector l
       const int l = e / d, c = e % d, src = sh.ord[0][l];
-      const double a = a_star(fmax(sh.nrm[0][src], 0.0));
-      const float bv = (float)(sqrt(1.0 - 4.0 * a) * sh.sgn[0][src] * V[(size_t)src * d + c]);
+      const float bv = (float)(sh.red_row[src] * V[(size_t)src * d + c]);
       B1[e] = bv;
       B2[e] = bv;
       C1[e] = C2[e] = l == c ? -0.5f : 0.f;
-      if (c == 0) A[l] = (float)a;
+      if (c == 0) A[l] = (float)a_star(fmax(sh.nrm[0][src], 0.0));
     }
     // the per-eigenvalue terms of log D and of the objective in parallel (the logarithms are the expensive part),
     // their sums in eigenvalue order by one thread
@@ -459,14 +920,11 @@ __global__ void __launch_bounds__(FIT_NT) k_fit_device(int variant, int d, const
   double* Z = w + 4 * (size_t)nn;      // column-major
   double* b1 = w + 5 * (size_t)nn;     // row-major
   double* b2 = w + 6 * (size_t)nn;
-  for (int e = t; e < nn; e += FIT_NT) {
-    const double rd = (e / d == e % d) ? ridge : 0.0;
-    G1[e] = M1[e] + rd;
-    G2[e] = M2[e] + rd;
-  }
-  __syncthreads();
-  decompose(G1, V1, n, 0, true, sh, lds);
-  decompose(G2, V2, n, 1, true, sh, lds);
+  // (Z, b1 and b2 are not yet in use: scratch)
+  decompose_symmetric<RJ>([=](int r, int c) { return M1[(size_t)r * d + c] + (r == c ? ridge : 0.0); }, tr1 + d * ridge, G1,
+                          V1, Z, n, 0, sh, lds);
+  decompose_symmetric<RJ>([=](int r, int c) { return M2[(size_t)r * d + c] + (r == c ? ridge : 0.0); }, tr2 + d * ridge, G2,
+                          V2, Z, n, 1, sh, lds);
   {
     const double l1max = sh.nrm[0][sh.ord[0][0]], l1min = sh.nrm[0][sh.ord[0][d - 1]];
     const double l2max = sh.nrm[1][sh.ord[1][0]], l2min = sh.nrm[1][sh.ord[1][d - 1]];
@@ -541,13 +999,15 @@ size_t fit_device_workspace_doubles(int d, int groups) { return (size_t)groups *
 int launch_fit_device(int variant, int d, int groups, const double* stats, double ridge, double* ws, float* theta,
                       int* status, size_t theta_floats, hipStream_t st) {
   if (d < 1 || d > FIT_DMAX) return 2;
-  const size_t lds = (size_t)(d <= 96 ? 2 : 1) * d * (d + 1) * sizeof(double);
-  if (lds > 0 && hipFuncSetAttribute((const void*)k_fit_device, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
+  // the Jacobi form's matrix (and rotations), or what the tridiagonal form keeps there
+  const size_t jacobi = (size_t)(d <= kLdsBoth ? 2 : 1) * d * (d + 1);
+  const size_t lds = (d <= 64 ? std::max(jacobi, tri_lds_doubles(64)) : std::max(jacobi, tri_lds_doubles(128))) * sizeof(double);
+  auto kernel = d <= 64 ? k_fit_device<2> : k_fit_device<4>;
+  if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
     (void)hipGetLastError();
     return 2;
   }
-  hipLaunchKernelGGL(k_fit_device, dim3(groups), dim3(FIT_NT), lds, st, variant, d, stats, ridge, ws, theta, status,
-                     theta_floats);
+  hipLaunchKernelGGL(kernel, dim3(groups), dim3(FIT_NT), lds, st, variant, d, stats, ridge, ws, theta, status, theta_floats);
   if (hipGetLastError() != hipSuccess) return 5;
   return 0;
 }

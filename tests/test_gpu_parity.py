@@ -331,6 +331,31 @@ def test_device_fit_dense_families_at_other_sizes(fs, variant, d):
     np.testing.assert_allclose(got.B1.T @ got.B2, host.B1.T @ host.B2, atol=3e-4)
 
 
+@pytest.mark.parametrize("spectrum", ["distinct", "equal"])
+@pytest.mark.parametrize("d", [1, 2, 3, 31, 33, 64, 65, 96, 127, 128])
+def test_device_fit_eigensolver_sizes(fs, d, spectrum):
+    """The eigensolver of the device-resident fit (tridiagonal form) at the edges of its register blocks and of its two
+    instantiations, and on matrices whose eigenvalues coincide (rows in a subspace of two dimensions: all others are
+    zero), which the Jacobi iteration takes over.  Invariants of the SDERF fit against the oracle; the statistics are
+    sums of 400 fp32 products, relative error up to 400 * 2^-24 = 2.4e-5."""
+    import torch
+    rng = np.random.default_rng(900 + d)
+    L, dpad = 400, (d + 3) // 4 * 4
+    U, _ = np.linalg.qr(rng.standard_normal((d, d)))
+    spec = np.linspace(1.2, 0.3, d) if spectrum == "distinct" else (np.arange(d) < 2) * np.array([1.1, *([0.7] * (d - 1))])
+    Q, K = np.zeros((1, 1, L, dpad), np.float32), np.zeros((1, 1, L, dpad), np.float32)
+    Q[..., :d] = (rng.standard_normal((L, d)) * spec) @ U.T
+    K[..., :d] = (rng.standard_normal((L, d)) * spec) @ U.T
+    s = d ** -0.25
+    theta = _fit(fs, "device", "sderf", torch.from_numpy(Q).cuda()[..., :d], torch.from_numpy(K).cuda()[..., :d], s, 1)
+    ref = orc.fit("sderf", s * Q[0, 0, :, :d].astype(np.float64), s * K[0, 0, :, :d].astype(np.float64))
+    got = util.oracle_theta_from_vec(theta[0], d)
+    np.testing.assert_allclose(got.A, np.sort(ref.A), atol=2.4e-5)
+    assert got.logD == pytest.approx(ref.logD, abs=2.4e-5 * max(1.0, d * abs(ref.A).max()))
+    np.testing.assert_allclose(got.B1.T @ got.B1, ref.B1.T @ ref.B1, atol=1e-4)       # 4 |A| error
+    np.testing.assert_allclose(got.B1 @ got.B1.T, np.diag(1.0 - 4.0 * got.A), atol=2e-6)   # orthogonal rows, fp32 storage
+
+
 @pytest.mark.parametrize("entry", ["host", "device"])
 @pytest.mark.parametrize("d", [64, 128])
 def test_fit_on_bf16_rows_scanned_by_the_mfma_statistics_kernels(fs, d, entry):
