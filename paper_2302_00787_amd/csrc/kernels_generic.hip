@@ -27,63 +27,133 @@ __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-// dst[r][c] = scale * T[row0 + r][c] for r < 32; zero outside [0, nrows) x [0, ncols); columns up to ncols_pad written.
-__device__ void load_rows(float* dst, int ld, const TensorDev& t, long long base, int row0, int nrows,
-                          int ncols, int ncols_pad, float scale) {
-  for (int idx = threadIdx.x; idx < TR * ncols_pad; idx += NT) {
-    const int r = idx / ncols_pad, c = idx - r * ncols_pad;
-    float v = 0.f;
-    if (row0 + r < nrows && c < ncols) v = scale * load_elem(t, base + (long long)(row0 + r) * t.sl + c);
-    dst[r * ld + c] = v;
+// acc += sum over k < n (a multiple of 4) of A[.][k] B[k][.]: ap and bp point at this lane's k = lane / 16 elements,
+// sa and sb are the distances of consecutive k.  Eight steps' operands are read from LDS together: read one step at a
+// time, each matrix instruction waits for an LDS latency of its own.
+__device__ __forceinline__ f32x4 mfma_chain(const float* ap, int sa, const float* bp, int sb, int n, f32x4 acc) {
+  int k = 0;
+  for (; k + 32 <= n; k += 32) {
+    float a[8], b[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      a[i] = ap[(k + 4 * i) * sa];
+      b[i] = bp[(k + 4 * i) * sb];
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc = mfma4(a[i], b[i], acc);
   }
+  for (; k < n; k += 4) acc = mfma4(ap[k * sa], bp[k * sb], acc);
+  return acc;
+}
+
+// A tile of 32 rows and up to 32 NI columns travelling global -> registers -> LDS: thread t carries rows t/32 + 8j,
+// columns t%32 + 32i.  All loads of a tile are in flight together, and between fetch and put a kernel may compute.  A
+// loop that stores each element to LDS as it arrives is a chain of 16 - 18 memory latencies per tile, with one
+// workgroup per CU (LDS) to hide them; together with mfma_chain and the state update from the LDS copy this took
+// causal attention B2 H4 L4096 d64 M256 f32 from 704 to 405 us and the causal backward pass B1 H16 L4096 d128 M512
+// from 15.2 to 5.9 ms, bit for bit the same.  Addresses outside the tile are clamped into it, so that no load is
+// conditional; the put writes zeros there.  The registers hold the raw bits (f32, or bf16 zero-extended).
+template <int NI> struct Tile { uint32_t v[4][NI]; };
+template <int NI>
+__device__ __forceinline__ void tile_fetch(Tile<NI>& t, const void* ptr, int dtype, long long base, long long stride,
+                                           int live, int ncols) {
+  const int r0 = threadIdx.x >> 5, c0 = threadIdx.x & 31;
+  if (dtype == 0) {
+    const uint32_t* p = (const uint32_t*)ptr + base;
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+      if (32 * i < ncols) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) t.v[j][i] = p[(long long)min(r0 + 8 * j, live - 1) * stride + min(c0 + 32 * i, ncols - 1)];
+      }
+  } else {
+    const uint16_t* p = (const uint16_t*)ptr + base;
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+      if (32 * i < ncols) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) t.v[j][i] = p[(long long)min(r0 + 8 * j, live - 1) * stride + min(c0 + 32 * i, ncols - 1)];
+      }
+  }
+}
+// dst[r][c] = scale * tile for r < live, c < ncols, `fill` at column ncols of the live rows, 0 elsewhere up to ncols_pad.
+template <int NI>
+__device__ __forceinline__ void tile_put(const Tile<NI>& t, int dtype, float* dst, int ld, int live, int ncols,
+                                         int ncols_pad, float scale, float fill) {
+  const int r0 = threadIdx.x >> 5, c0 = threadIdx.x & 31, shift = dtype == 0 ? 0 : 16;
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int c = c0 + 32 * i;
+    if (c < ncols_pad) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int r = r0 + 8 * j;
+        float v = 0.f;
+        if (r < live) v = c < ncols ? scale * __uint_as_float(t.v[j][i] << shift) : (c == ncols ? fill : 0.f);
+        dst[r * ld + c] = v;
+      }
+    }
+  }
+}
+
+// Rows of a side (at most 128 columns) and of values (at most 144, with the column of ones that is the normaliser).
+typedef Tile<4> RowTile;
+typedef Tile<5> ValTile;
+static_assert(TR == 32 && MB == 32 && NT == 256, "tiles are carried by 8 x 32 threads, four rows each");
+__device__ __forceinline__ void rows_fetch(RowTile& x, const TensorDev& t, long long base, int row0, int nrows, int ncols) {
+  tile_fetch(x, t.ptr, t.dtype, base + (long long)row0 * t.sl, t.sl, nrows - row0, ncols);
+}
+__device__ __forceinline__ void rows_put(const RowTile& x, const TensorDev& t, float* dst, int ld, int row0, int nrows,
+                                         int ncols, int ncols_pad, float scale) {
+  tile_put(x, t.dtype, dst, ld, nrows - row0, ncols, ncols_pad, scale, 0.f);
+}
+__device__ __forceinline__ void values_fetch(ValTile& x, const TensorDev& t, long long base, int row0, int nrows, int ncols) {
+  tile_fetch(x, t.ptr, t.dtype, base + (long long)row0 * t.sl, t.sl, nrows - row0, ncols);
+}
+__device__ __forceinline__ void values_put(const ValTile& x, const TensorDev& t, float* dst, int ld, int row0, int nrows,
+                                           int ncols, int ncols_pad, int append_ones) {
+  tile_put(x, t.dtype, dst, ld, nrows - row0, ncols, ncols_pad, 1.f, append_ones ? 1.f : 0.f);
+}
+
+// dst[r][c] = scale * T[row0 + r][c] for r < 32; zero outside [0, nrows) x [0, ncols); columns up to ncols_pad written.
+__device__ __forceinline__ void load_rows(float* dst, int ld, const TensorDev& t, long long base, int row0, int nrows,
+                                          int ncols, int ncols_pad, float scale) {
+  RowTile x;
+  rows_fetch(x, t, base, row0, nrows, ncols);
+  rows_put(x, t, dst, ld, row0, nrows, ncols, ncols_pad, scale);
 }
 
 // Value tile with an optional column of ones at index ncols (the normaliser column of attention).
-__device__ void load_values(float* dst, int ld, const TensorDev& t, long long base, int row0, int nrows,
-                            int ncols, int ncols_pad, int append_ones) {
-  for (int idx = threadIdx.x; idx < TR * ncols_pad; idx += NT) {
-    const int r = idx / ncols_pad, c = idx - r * ncols_pad;
-    float v = 0.f;
-    if (row0 + r < nrows) {
-      if (c < ncols) v = load_elem(t, base + (long long)(row0 + r) * t.sl + c);
-      else if (c == ncols && append_ones) v = 1.f;
-    }
-    dst[r * ld + c] = v;
-  }
+__device__ __forceinline__ void load_values(float* dst, int ld, const TensorDev& t, long long base, int row0, int nrows,
+                                            int ncols, int ncols_pad, int append_ones) {
+  ValTile x;
+  values_fetch(x, t, base, row0, nrows, ncols);
+  values_put(x, t, dst, ld, row0, nrows, ncols, ncols_pad, append_ones);
 }
 
-// Ws[f][c] = W[m0 + f][c] (zero rows past M), bias_s[f] = bias[m0 + f].
-__device__ void load_wblock(float* Ws, float* bias_s, int ld, const float* W, const float* bias, int m0, int M,
-                            int d, int dpad) {
-  for (int idx = threadIdx.x; idx < MB * dpad; idx += NT) {
-    const int f = idx / dpad, c = idx - f * dpad;
-    Ws[f * ld + c] = (m0 + f < M && c < d) ? W[(long long)(m0 + f) * d + c] : 0.f;
-  }
-  if (threadIdx.x < MB) bias_s[threadIdx.x] = (m0 + threadIdx.x < M) ? bias[m0 + threadIdx.x] : 0.f;
+// Ws[f][c] = W[m0 + f][c] (zero rows past M), bias_s[f] = bias[m0 + f], in two halves.
+struct WRegs { RowTile w; float b; };
+__device__ __forceinline__ void wblock_fetch(WRegs& r, const float* W, const float* bias, int m0, int M, int d) {
+  tile_fetch(r.w, W, 0, (long long)m0 * d, d, M - m0, d);
+  r.b = bias[min(m0 + (int)(threadIdx.x & (MB - 1)), M - 1)];
+}
+__device__ __forceinline__ void wblock_put(const WRegs& r, float* Ws, float* bias_s, int ld, int m0, int M, int d, int dpad) {
+  tile_put(r.w, 0, Ws, ld, M - m0, d, dpad, 1.f, 0.f);
+  if (threadIdx.x < MB) bias_s[threadIdx.x] = m0 + (int)threadIdx.x < M ? r.b : 0.f;
+}
+__device__ __forceinline__ void load_wblock(float* Ws, float* bias_s, int ld, const float* W, const float* bias, int m0,
+                                            int M, int d, int dpad) {
+  WRegs r;
+  wblock_fetch(r, W, bias, m0, M, d);
+  wblock_put(r, Ws, bias_s, ld, m0, M, d, dpad);
 }
 
-// The same block travelling global -> registers -> LDS, so that the load of the next block is in flight while the
-// current one is used: thread t carries row f = t/8 of the block, columns t%8 + 8i (dpad <= 128: at most 16).
-struct WRegs { float w[16]; float b; };
-__device__ __forceinline__ void wblock_fetch(WRegs& r, const float* W, const float* bias, int m0, int M, int d, int dpad) {
-  const int f = threadIdx.x >> 3, c0 = threadIdx.x & 7;
-  const float* row = W + (long long)(m0 + f) * d;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int c = c0 + 8 * i;
-    r.w[i] = 0.f;
-    if (8 * i < dpad && m0 + f < M && c < d) r.w[i] = row[c];
-  }
-  r.b = (threadIdx.x < MB && m0 + threadIdx.x < M) ? bias[m0 + threadIdx.x] : 0.f;
+// The block of a state that belongs to features m0 .. m0 + 31 (rows of ldt floats; zero rows past M).
+__device__ __forceinline__ void sblock_fetch(ValTile& t, const float* T, int m0, int M, int ldt) {
+  tile_fetch(t, T, 0, (long long)m0 * ldt, ldt, M - m0, ldt);
 }
-__device__ __forceinline__ void wblock_put(const WRegs& r, float* Ws, float* bias_s, int ld, int dpad) {
-  const int f = threadIdx.x >> 3, c0 = threadIdx.x & 7;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int c = c0 + 8 * i;
-    if (8 * i < dpad && c < dpad) Ws[f * ld + c] = r.w[i];
-  }
-  if (threadIdx.x < MB) bias_s[threadIdx.x] = r.b;
+__device__ __forceinline__ void sblock_put(const ValTile& t, float* Ts, int ld, int m0, int M, int ldt) {
+  tile_put(t, 0, Ts, ld, M - m0, ldt, ldt, 1.f, 0.f);
 }
 
 // ((C + C^T) x)[c] for a dense C (four partial sums and several loads in flight: a plain loop is a chain of cache
@@ -151,7 +221,7 @@ __device__ __forceinline__ f32x4 proj_tile(const float* Xs, const float* Ws, int
   const float* ap = Xs + ((w >> 1) * 16 + (lane & 15)) * ld + (lane >> 4);
   const float* bp = Ws + ((w & 1) * 16 + (lane & 15)) * ld + (lane >> 4);
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int k = 0; k < dpad; k += 4) acc = mfma4(ap[k], bp[k], acc);
+  acc = mfma_chain(ap, 1, bp, 1, dpad, acc);
   return acc;
 }
 
@@ -175,12 +245,12 @@ __device__ void rowmax_pass(uint32_t* rowmax_u, const float* Xs, float* Ws, floa
   if (threadIdx.x < TR) rowmax_u[threadIdx.x] = 0u;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   WRegs wr;
-  wblock_fetch(wr, W, bias, 0, M, d, dpad);
+  wblock_fetch(wr, W, bias, 0, M, d);
   for (int m0 = 0; m0 < M; m0 += MB) {
     __syncthreads();
-    wblock_put(wr, Ws, bias_s, ld, dpad);
+    wblock_put(wr, Ws, bias_s, ld, m0, M, d, dpad);
     __syncthreads();
-    if (m0 + MB < M) wblock_fetch(wr, W, bias, m0 + MB, M, d, dpad);
+    if (m0 + MB < M) wblock_fetch(wr, W, bias, m0 + MB, M, d);
     const f32x4 acc = proj_tile(Xs, Ws, ld, dpad);
     const int f = (w & 1) * 16 + (lane & 15);
     float e[4];
@@ -334,11 +404,21 @@ __global__ void __launch_bounds__(NT) k_gen_state(GenSide ks, TensorDev V, int L
   for (int t = 0; t < ACC_PER_WAVE; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   const int row_end = min(Lk, (seg + 1) * rows_per_seg);
+  const long long xbase = b * ks.X.sb + h * ks.X.sh, vbase = b * V.sb + h * V.sh;
+  // (the rows and values of the next step are fetched while the current one computes)
+  RowTile xr;
+  ValTile vr;
+  rows_fetch(xr, ks.X, xbase, seg * rows_per_seg, row_end, d);
+  values_fetch(vr, V, vbase, seg * rows_per_seg, row_end, nv);
   for (int row0 = seg * rows_per_seg; row0 < row_end; row0 += TR) {
     __syncthreads();
-    load_rows(Xs, ld, ks.X, b * ks.X.sb + h * ks.X.sh, row0, row_end, d, dpad, ks.scale);
-    load_values(Vs, ldv, V, b * V.sb + h * V.sh, row0, row_end, nv, ldt, append_ones);
+    rows_put(xr, ks.X, Xs, ld, row0, row_end, d, dpad, ks.scale);
+    values_put(vr, V, Vs, ldv, row0, row_end, nv, ldt, append_ones);
     __syncthreads();
+    if (row0 + TR < row_end) {
+      rows_fetch(xr, ks.X, xbase, row0 + TR, row_end, d);
+      values_fetch(vr, V, vbase, row0 + TR, row_end, nv);
+    }
     if (row_shift == nullptr) row_terms_of(rterm, ks, bh, Lk, row0, row_end, Xs, ld, d, Cmat, ks.alpha);
     else if (threadIdx.x < TR) rterm[threadIdx.x] = row0 + threadIdx.x < row_end ? -row_shift[(size_t)bh * Lk + row0 + threadIdx.x] : 0.f;
     __syncthreads();
@@ -357,7 +437,7 @@ __global__ void __launch_bounds__(NT) k_gen_state(GenSide ks, TensorDev V, int L
         const int mt = t & 1, vt = t >> 1;
         const float* ap = Ss + (lane >> 4) * lds + mt * 16 + (lane & 15);      // A[i=m][k=j] = Ss[j][m]
         const float* bp = Vs + (lane >> 4) * ldv + vt * 16 + (lane & 15);      // B[k=j][n=v] = Vs[j][v]
-        for (int k = 0; k < TR; k += 4) acc[tl] = mfma4(ap[k * lds], bp[k * ldv], acc[tl]);
+        acc[tl] = mfma_chain(ap, lds, bp, ldv, TR, acc[tl]);
       }
     }
   }
@@ -470,34 +550,19 @@ __global__ void __launch_bounds__(NT) k_gen_apply(GenSide qs, int Lq, int H, int
   f32x4 acc[ACC_PER_WAVE];
 #pragma unroll
   for (int t = 0; t < ACC_PER_WAVE; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // the projection block and the state block of the next step are fetched while the current step computes: thread
-  // t carries row t/8 of the state block, columns t%8 + 8i (ldt <= 144: at most 18)
+  // the projection block and the state block of the next step are fetched while the current step computes
   WRegs wr;
-  float tr[18];
-  auto fetch_t = [&](int m0) {
-    const int f = threadIdx.x >> 3, c0 = threadIdx.x & 7;
-    const float* row = Tb + (size_t)(m0 + f) * ldt;
-#pragma unroll
-    for (int i = 0; i < 18; ++i) {
-      tr[i] = 0.f;
-      if (8 * i < ldt && m0 + f < M) tr[i] = row[c0 + 8 * i];
-    }
-  };
-  wblock_fetch(wr, W, bias, 0, M, d, dpad);
-  fetch_t(0);
+  ValTile tr;
+  wblock_fetch(wr, W, bias, 0, M, d);
+  sblock_fetch(tr, Tb, 0, M, ldt);
   for (int m0 = 0; m0 < M; m0 += MB) {
     __syncthreads();
-    wblock_put(wr, Ws, bias_s, ld, dpad);
-    {
-      const int f = threadIdx.x >> 3, c0 = threadIdx.x & 7;
-#pragma unroll
-      for (int i = 0; i < 18; ++i)
-        if (8 * i < ldt) Ts[f * ldts + c0 + 8 * i] = tr[i];
-    }
+    wblock_put(wr, Ws, bias_s, ld, m0, M, d, dpad);
+    sblock_put(tr, Ts, ldts, m0, M, ldt);
     __syncthreads();
     if (m0 + MB < M) {
-      wblock_fetch(wr, W, bias, m0 + MB, M, d, dpad);
-      fetch_t(m0 + MB);
+      wblock_fetch(wr, W, bias, m0 + MB, M, d);
+      sblock_fetch(tr, Tb, m0 + MB, M, ldt);
     }
     const f32x4 e = proj_tile(Xs, Ws, ld, dpad);
     const int f = (w & 1) * 16 + (lane & 15);
@@ -514,7 +579,7 @@ __global__ void __launch_bounds__(NT) k_gen_apply(GenSide qs, int Lq, int H, int
         const int rt = t & 1, vt = t >> 1;
         const float* ap = Ps + (rt * 16 + (lane & 15)) * lds + (lane >> 4);    // A[i][k=m] = Ps[i][m]
         const float* bp = Ts + (lane >> 4) * ldts + vt * 16 + (lane & 15);     // B[k=m][n=v] = Ts[m][v]
-        for (int k = 0; k < MB; k += 4) acc[tl] = mfma4(ap[k], bp[k * ldts], acc[tl]);
+        acc[tl] = mfma_chain(ap, 1, bp, ldts, MB, acc[tl]);
       }
     }
   }
@@ -588,15 +653,23 @@ __global__ void __launch_bounds__(NT) k_gen_causal(GenSide qs, GenSide ks, Tenso
 #pragma unroll
     for (int t = 0; t < ACC_PER_WAVE; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     f32x4 sc = {0.f, 0.f, 0.f, 0.f};          // scores tile (query tile w>>1, key tile w&1)
+    // the three blocks of the next step are fetched while the current one computes (rows of the state that this step
+    // writes are not among them)
+    WRegs wa, wb;
+    ValTile tr;
+    wblock_fetch(wa, W1, bias1, 0, M, d);
+    sblock_fetch(tr, Tg, 0, M, ldt);
+    wblock_fetch(wb, W2, bias2, 0, M, d);
     for (int m0 = 0; m0 < M; m0 += MB) {
       const int f = (w & 1) * 16 + (lane & 15);
       __syncthreads();
-      load_wblock(Ws, bias_s, ld, W1, bias1, m0, M, d, dpad);
-      for (int idx = threadIdx.x; idx < MB * ldt; idx += NT) {
-        const int ff = idx / ldt, cc = idx - ff * ldt;
-        Ts[ff * ldv + cc] = (m0 + ff < M) ? Tg[(size_t)(m0 + ff) * ldt + cc] : 0.f;
-      }
+      wblock_put(wa, Ws, bias_s, ld, m0, M, d, dpad);
+      sblock_put(tr, Ts, ldv, m0, M, ldt);
       __syncthreads();
+      if (m0 + MB < M) {
+        wblock_fetch(wa, W1, bias1, m0 + MB, M, d);
+        sblock_fetch(tr, Tg, m0 + MB, M, ldt);
+      }
       {
         const f32x4 e = proj_tile(Qs, Ws, ld, dpad);
 #pragma unroll
@@ -606,8 +679,9 @@ __global__ void __launch_bounds__(NT) k_gen_causal(GenSide qs, GenSide ks, Tenso
         }
       }
       __syncthreads();
-      load_wblock(Ws, bias_s, ld, W2, bias2, m0, M, d, dpad);
+      wblock_put(wb, Ws, bias_s, ld, m0, M, d, dpad);
       __syncthreads();
+      if (m0 + MB < M) wblock_fetch(wb, W2, bias2, m0 + MB, M, d);
       {
         const f32x4 e = proj_tile(Ks, Ws, ld, dpad);
 #pragma unroll
@@ -620,7 +694,7 @@ __global__ void __launch_bounds__(NT) k_gen_causal(GenSide qs, GenSide ks, Tenso
       {   // scores: A[i][k=m] = Ps[i][m], B[k=m][n=j] = Ss[j][m]
         const float* ap = Ps + ((w >> 1) * 16 + (lane & 15)) * lds + (lane >> 4);
         const float* bp = Ss + ((w & 1) * 16 + (lane & 15)) * lds + (lane >> 4);
-        for (int k = 0; k < MB; k += 4) sc = mfma4(ap[k], bp[k], sc);
+        sc = mfma_chain(ap, 1, bp, 1, MB, sc);
       }
 #pragma unroll
       for (int tl = 0; tl < ACC_PER_WAVE; ++tl) {
@@ -630,17 +704,17 @@ __global__ void __launch_bounds__(NT) k_gen_causal(GenSide qs, GenSide ks, Tenso
           {   // inter-chunk term with the state before this step
             const float* ap = Ps + (rt * 16 + (lane & 15)) * lds + (lane >> 4);
             const float* bp = Ts + (lane >> 4) * ldv + vt * 16 + (lane & 15);
-            for (int k = 0; k < MB; k += 4) acc[tl] = mfma4(ap[k], bp[k * ldv], acc[tl]);
+            acc[tl] = mfma_chain(ap, 1, bp, ldv, MB, acc[tl]);
           }
           {   // state update for feature tile rt: T[m][v] += sum_j Ss[j][m] Vs[j][v]
             f32x4 up = {0.f, 0.f, 0.f, 0.f};
             const float* ap = Ss + (lane >> 4) * lds + rt * 16 + (lane & 15);
             const float* bp = Vs + (lane >> 4) * ldv + vt * 16 + (lane & 15);
-            for (int k = 0; k < TR; k += 4) up = mfma4(ap[k * lds], bp[k * ldv], up);
+            up = mfma_chain(ap, lds, bp, ldv, TR, up);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-              const int m = m0 + rt * 16 + 4 * (lane >> 4) + r;
-              if (m < M) Tg[(size_t)m * ldt + vt * 16 + (lane & 15)] += up[r];
+              const int mb = rt * 16 + 4 * (lane >> 4) + r;
+              if (m0 + mb < M) Tg[(size_t)(m0 + mb) * ldt + vt * 16 + (lane & 15)] = Ts[mb * ldv + vt * 16 + (lane & 15)] + up[r];
             }
           }
         }
@@ -660,7 +734,7 @@ __global__ void __launch_bounds__(NT) k_gen_causal(GenSide qs, GenSide ks, Tenso
         const int rt = t & 1, vt = t >> 1;
         const float* ap = As + (rt * 16 + (lane & 15)) * lds + (lane >> 4);
         const float* bp = Vs + (lane >> 4) * ldv + vt * 16 + (lane & 15);
-        for (int k = 0; k < TR; k += 4) acc[tl] = mfma4(ap[k], bp[k * ldv], acc[tl]);
+        acc[tl] = mfma_chain(ap, 1, bp, ldv, TR, acc[tl]);
       }
     }
     __syncthreads();
@@ -844,14 +918,19 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_side(GenSide sd, int side, Tenso
   for (int t = 0; t < 4; ++t) acc_g[t] = f32x4{0.f, 0.f, 0.f, 0.f};
   float rs_part = 0.f;               // thread (row = tid / 8, part = tid % 8): its share of rowsum(dE)
 
+  WRegs wr;                          // the next step's blocks, fetched while the current one computes
+  ValTile tr;
+  wblock_fetch(wr, W, bias, 0, M, d);
+  sblock_fetch(tr, Sb, 0, M, ldt);
   for (int m0 = 0; m0 < M; m0 += MB) {
     __syncthreads();
-    load_wblock(Ws, bias_s, ld, W, bias, m0, M, d, dpad);
-    for (int idx = threadIdx.x; idx < MB * ldt; idx += NT) {
-      const int f = idx / ldt, c = idx - f * ldt;
-      Sts[f * ldts + c] = (m0 + f < M) ? Sb[(size_t)(m0 + f) * ldt + c] : 0.f;
-    }
+    wblock_put(wr, Ws, bias_s, ld, m0, M, d, dpad);
+    sblock_put(tr, Sts, ldts, m0, M, ldt);
     __syncthreads();
+    if (m0 + MB < M) {
+      wblock_fetch(wr, W, bias, m0 + MB, M, d);
+      sblock_fetch(tr, Sb, m0 + MB, M, ldt);
+    }
     const f32x4 e = proj_tile(Xs, Ws, ld, dpad);
     const int f = (w & 1) * 16 + (lane & 15);
     float fv[4];
@@ -866,7 +945,7 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_side(GenSide sd, int side, Tenso
       const float* ap = As + ((w >> 1) * 16 + (lane & 15)) * ldts + (lane >> 4);
       const float* bp = Sts + ((w & 1) * 16 + (lane & 15)) * ldts + (lane >> 4);
       f32x4 df = {0.f, 0.f, 0.f, 0.f};
-      for (int k = 0; k < ldt; k += 4) df = mfma4(ap[k], bp[k], df);
+      df = mfma_chain(ap, 1, bp, 1, ldt, df);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int row = (w >> 1) * 16 + 4 * (lane >> 4) + r;
@@ -882,7 +961,7 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_side(GenSide sd, int side, Tenso
           const int rt = t & 1, vt = t >> 1;
           const float* ap = Fs + (rt * 16 + (lane & 15)) * lds + (lane >> 4);     // A[i][k=m] = Fs[i][m]
           const float* bp = Sts + (lane >> 4) * ldts + vt * 16 + (lane & 15);     // B[k=m][n=v] = Sts[m][v]
-          for (int k = 0; k < MB; k += 4) acc_o[tl] = mfma4(ap[k], bp[k * ldts], acc_o[tl]);
+          acc_o[tl] = mfma_chain(ap, 1, bp, ldts, MB, acc_o[tl]);
         }
       }
     }
@@ -892,10 +971,8 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_side(GenSide sd, int side, Tenso
       if (t < ngt) {
         const int rt = t & 1, ct = t >> 1;
         const float* ap = dEs + (rt * 16 + (lane & 15)) * lds + (lane >> 4);      // A[i][k=m] = dEs[i][m]
-        const float* bp = Ws + (lane >> 4) * ld + ct * 16 + (lane & 15);          // B[k=m][n=c] = Ws[m][c]
-        f32x4 a = acc_g[tl];
-        for (int k = 0; k < MB; k += 4) a = mfma4(ap[k], (ct * 16 + (lane & 15) < dpad) ? bp[k * ld] : 0.f, a);
-        acc_g[tl] = a;
+        const float* bp = Ws + (lane >> 4) * ld + min(ct * 16 + (lane & 15), dpad - 1);   // B[k=m][n=c] = Ws[m][c]; columns past dpad are dropped below
+        acc_g[tl] = mfma_chain(ap, 1, bp, ld, MB, acc_g[tl]);
       }
     }
     {
@@ -994,7 +1071,7 @@ __device__ __forceinline__ void bwd_causal_amat(float* As, const float* Gs, cons
   const float* ap = Gs + ((w >> 1) * 16 + (lane & 15)) * ldv + (lane >> 4);   // A[i][k=v] = Gs[i][v]
   const float* bp = Vs + ((w & 1) * 16 + (lane & 15)) * ldv + (lane >> 4);    // B[k=v][n=j] = Vs[j][v]
   f32x4 a = {0.f, 0.f, 0.f, 0.f};
-  for (int k = 0; k < ldt; k += 4) a = mfma4(ap[k], bp[k], a);
+  a = mfma_chain(ap, 1, bp, 1, ldt, a);
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int i = (w >> 1) * 16 + 4 * (lane >> 4) + r, j = (w & 1) * 16 + (lane & 15);
@@ -1057,15 +1134,23 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_causal_q(GenSide qs, GenSide ks,
 #pragma unroll
     for (int t = 0; t < 4; ++t) acc_g[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     float rs_part = 0.f;
+    // the three blocks of the next step are fetched while the current one computes (rows of the state that this step
+    // writes are not among them)
+    WRegs wa, wb;
+    ValTile tr;
+    wblock_fetch(wa, W2, bias2, 0, M, d);
+    sblock_fetch(tr, Tg, 0, M, ldt);
+    wblock_fetch(wb, W1, bias1, 0, M, d);
     for (int m0 = 0; m0 < M; m0 += MB) {
       const int f = (w & 1) * 16 + (lane & 15);
       __syncthreads();
-      load_wblock(m.Ws, m.bias_s, ld, W2, bias2, m0, M, d, dpad);
-      for (int idx = threadIdx.x; idx < MB * ldt; idx += NT) {
-        const int ff = idx / ldt, cc = idx - ff * ldt;
-        m.Ts[ff * ldv + cc] = (m0 + ff < M) ? Tg[(size_t)(m0 + ff) * ldt + cc] : 0.f;
-      }
+      wblock_put(wa, m.Ws, m.bias_s, ld, m0, M, d, dpad);
+      sblock_put(tr, m.Ts, ldv, m0, M, ldt);
       __syncthreads();
+      if (m0 + MB < M) {
+        wblock_fetch(wa, W2, bias2, m0 + MB, M, d);
+        sblock_fetch(tr, Tg, m0 + MB, M, ldt);
+      }
       {
         const f32x4 e = proj_tile(m.Ks, m.Ws, ld, dpad);
 #pragma unroll
@@ -1075,8 +1160,9 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_causal_q(GenSide qs, GenSide ks,
         }
       }
       __syncthreads();
-      load_wblock(m.Ws, m.bias_s, ld, W1, bias1, m0, M, d, dpad);
+      wblock_put(wb, m.Ws, m.bias_s, ld, m0, M, d, dpad);
       __syncthreads();
+      if (m0 + MB < M) wblock_fetch(wb, W1, bias1, m0 + MB, M, d);
       {
         const f32x4 e = proj_tile(m.Qs, m.Ws, ld, dpad);
         float fv[4];
@@ -1090,12 +1176,12 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_causal_q(GenSide qs, GenSide ks,
         {
           const float* ap = m.Gs + ((w >> 1) * 16 + (lane & 15)) * ldv + (lane >> 4);   // A[i][k=v] = Gs[i][v]
           const float* bp = m.Ts + ((w & 1) * 16 + (lane & 15)) * ldv + (lane >> 4);    // B[k=v][n=m] = Ts[m][v]
-          for (int k = 0; k < ldt; k += 4) df = mfma4(ap[k], bp[k], df);
+          df = mfma_chain(ap, 1, bp, 1, ldt, df);
         }
         {
           const float* ap = m.As + ((w >> 1) * 16 + (lane & 15)) * lds + (lane >> 4);   // A[i][k=j] = As[i][j]
           const float* bp = m.Ss + (lane >> 4) * lds + (w & 1) * 16 + (lane & 15);      // B[k=j][n=m] = Ss[j][m]
-          for (int k = 0; k < TR; k += 4) df = mfma4(ap[k], bp[k * lds], df);
+          df = mfma_chain(ap, 1, bp, lds, TR, df);
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -1110,11 +1196,8 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_causal_q(GenSide qs, GenSide ks,
         if (t < ngt) {
           const int rt = t & 1, ct = t >> 1;
           const float* ap = m.dEs + (rt * 16 + (lane & 15)) * lds + (lane >> 4);        // A[i][k=m] = dEs[i][m]
-          const float* bp = m.Ws + (lane >> 4) * ld + ct * 16 + (lane & 15);            // B[k=m][n=c] = Ws[m][c]
-          const bool in = ct * 16 + (lane & 15) < dpad;
-          f32x4 a = acc_g[tl];
-          for (int k = 0; k < MB; k += 4) a = mfma4(ap[k], in ? bp[k * ld] : 0.f, a);
-          acc_g[tl] = a;
+          const float* bp = m.Ws + (lane >> 4) * ld + min(ct * 16 + (lane & 15), dpad - 1);   // (columns past dpad are dropped below)
+          acc_g[tl] = mfma_chain(ap, 1, bp, ld, MB, acc_g[tl]);
         }
       }
       {
@@ -1131,11 +1214,11 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_causal_q(GenSide qs, GenSide ks,
           f32x4 up = {0.f, 0.f, 0.f, 0.f};
           const float* ap = m.Ss + (lane >> 4) * lds + rt * 16 + (lane & 15);
           const float* bp = m.Vs + (lane >> 4) * ldv + vt * 16 + (lane & 15);
-          for (int k = 0; k < TR; k += 4) up = mfma4(ap[k * lds], bp[k * ldv], up);
+          up = mfma_chain(ap, lds, bp, ldv, TR, up);
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            const int mm = m0 + rt * 16 + 4 * (lane >> 4) + r;
-            if (mm < M) Tg[(size_t)mm * ldt + vt * 16 + (lane & 15)] += up[r];
+            const int mb = rt * 16 + 4 * (lane >> 4) + r;
+            if (m0 + mb < M) Tg[(size_t)(m0 + mb) * ldt + vt * 16 + (lane & 15)] = m.Ts[mb * ldv + vt * 16 + (lane & 15)] + up[r];
           }
         }
       }
@@ -1204,15 +1287,23 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_causal_k(GenSide qs, GenSide ks,
     for (int t = 0; t < 4; ++t) acc_g[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     f32x4 sc = {0.f, 0.f, 0.f, 0.f};      // scores tile (query tile w>>1, key tile w&1)
     float rs_part = 0.f;
+    // the three blocks of the next step are fetched while the current one computes (rows of the state that this step
+    // writes are not among them)
+    WRegs wa, wb;
+    ValTile tr;
+    wblock_fetch(wa, W1, bias1, 0, M, d);
+    sblock_fetch(tr, Rg, 0, M, ldt);
+    wblock_fetch(wb, W2, bias2, 0, M, d);
     for (int m0 = 0; m0 < M; m0 += MB) {
       const int f = (w & 1) * 16 + (lane & 15);
       __syncthreads();
-      load_wblock(m.Ws, m.bias_s, ld, W1, bias1, m0, M, d, dpad);
-      for (int idx = threadIdx.x; idx < MB * ldt; idx += NT) {
-        const int ff = idx / ldt, cc = idx - ff * ldt;
-        m.Ts[ff * ldv + cc] = (m0 + ff < M) ? Rg[(size_t)(m0 + ff) * ldt + cc] : 0.f;
-      }
+      wblock_put(wa, m.Ws, m.bias_s, ld, m0, M, d, dpad);
+      sblock_put(tr, m.Ts, ldv, m0, M, ldt);
       __syncthreads();
+      if (m0 + MB < M) {
+        wblock_fetch(wa, W1, bias1, m0 + MB, M, d);
+        sblock_fetch(tr, Rg, m0 + MB, M, ldt);
+      }
       {
         const f32x4 e = proj_tile(m.Qs, m.Ws, ld, dpad);
 #pragma unroll
@@ -1222,8 +1313,9 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_causal_k(GenSide qs, GenSide ks,
         }
       }
       __syncthreads();
-      load_wblock(m.Ws, m.bias_s, ld, W2, bias2, m0, M, d, dpad);
+      wblock_put(wb, m.Ws, m.bias_s, ld, m0, M, d, dpad);
       __syncthreads();
+      if (m0 + MB < M) wblock_fetch(wb, W2, bias2, m0 + MB, M, d);
       {
         const f32x4 e = proj_tile(m.Ks, m.Ws, ld, dpad);
         float fv[4];
@@ -1238,12 +1330,12 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_causal_k(GenSide qs, GenSide ks,
         {
           const float* ap = m.Vs + ((w >> 1) * 16 + (lane & 15)) * ldv + (lane >> 4);   // A[j][k=v] = Vs[j][v]
           const float* bp = m.Ts + ((w & 1) * 16 + (lane & 15)) * ldv + (lane >> 4);    // B[k=v][n=m] = Rs[m][v]
-          for (int k = 0; k < ldt; k += 4) ds = mfma4(ap[k], bp[k], ds);
+          ds = mfma_chain(ap, 1, bp, 1, ldt, ds);
         }
         {
           const float* ap = m.As + (lane >> 4) * lds + (w >> 1) * 16 + (lane & 15);     // A[j][k=i] = As[i][j]
           const float* bp = m.Ps + (lane >> 4) * lds + (w & 1) * 16 + (lane & 15);      // B[k=i][n=m] = Ps[i][m]
-          for (int k = 0; k < TR; k += 4) ds = mfma4(ap[k * lds], bp[k * lds], ds);
+          ds = mfma_chain(ap, lds, bp, lds, TR, ds);
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -1255,7 +1347,7 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_causal_k(GenSide qs, GenSide ks,
       {   // scores: A[i][k=m] = Ps[i][m], B[k=m][n=j] = Ss[j][m]
         const float* ap = m.Ps + ((w >> 1) * 16 + (lane & 15)) * lds + (lane >> 4);
         const float* bp = m.Ss + ((w & 1) * 16 + (lane & 15)) * lds + (lane >> 4);
-        for (int k = 0; k < MB; k += 4) sc = mfma4(ap[k], bp[k], sc);
+        sc = mfma_chain(ap, 1, bp, 1, MB, sc);
       }
 #pragma unroll
       for (int tl = 0; tl < ACC_PER_WAVE; ++tl) {
@@ -1265,17 +1357,17 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_causal_k(GenSide qs, GenSide ks,
           {   // dV1 += S R_next: A[j][k=m] = Ss[j][m], B[k=m][n=v] = Rs[m][v]
             const float* ap = m.Ss + (rt * 16 + (lane & 15)) * lds + (lane >> 4);
             const float* bp = m.Ts + (lane >> 4) * ldv + vt * 16 + (lane & 15);
-            for (int k = 0; k < MB; k += 4) acc_o[tl] = mfma4(ap[k], bp[k * ldv], acc_o[tl]);
+            acc_o[tl] = mfma_chain(ap, 1, bp, ldv, MB, acc_o[tl]);
           }
           {   // the suffix sum takes this chunk's queries (after its last use): R[m][v] += sum_i Ps[i][m] Gs[i][v]
             f32x4 up = {0.f, 0.f, 0.f, 0.f};
             const float* ap = m.Ps + (lane >> 4) * lds + rt * 16 + (lane & 15);
             const float* bp = m.Gs + (lane >> 4) * ldv + vt * 16 + (lane & 15);
-            for (int k = 0; k < TR; k += 4) up = mfma4(ap[k * lds], bp[k * ldv], up);
+            up = mfma_chain(ap, lds, bp, ldv, TR, up);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-              const int mm = m0 + rt * 16 + 4 * (lane >> 4) + r;
-              if (mm < M) Rg[(size_t)mm * ldt + vt * 16 + (lane & 15)] += up[r];
+              const int mb = rt * 16 + 4 * (lane >> 4) + r;
+              if (m0 + mb < M) Rg[(size_t)(m0 + mb) * ldt + vt * 16 + (lane & 15)] = m.Ts[mb * ldv + vt * 16 + (lane & 15)] + up[r];
             }
           }
         }
@@ -1286,11 +1378,8 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_causal_k(GenSide qs, GenSide ks,
         if (t < ngt) {
           const int rt = t & 1, ct = t >> 1;
           const float* ap = m.dEs + (rt * 16 + (lane & 15)) * lds + (lane >> 4);
-          const float* bp = m.Ws + (lane >> 4) * ld + ct * 16 + (lane & 15);
-          const bool in = ct * 16 + (lane & 15) < dpad;
-          f32x4 a = acc_g[tl];
-          for (int k = 0; k < MB; k += 4) a = mfma4(ap[k], in ? bp[k * ld] : 0.f, a);
-          acc_g[tl] = a;
+          const float* bp = m.Ws + (lane >> 4) * ld + min(ct * 16 + (lane & 15), dpad - 1);   // (columns past dpad are dropped below)
+          acc_g[tl] = mfma_chain(ap, 1, bp, ld, MB, acc_g[tl]);
         }
       }
       {
@@ -1313,7 +1402,7 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_causal_k(GenSide qs, GenSide ks,
         const int rt = t & 1, vt = t >> 1;
         const float* ap = m.Bs + (lane >> 4) * lds + rt * 16 + (lane & 15);
         const float* bp = m.Gs + (lane >> 4) * ldv + vt * 16 + (lane & 15);
-        for (int k = 0; k < TR; k += 4) acc_o[tl] = mfma4(ap[k * lds], bp[k * ldv], acc_o[tl]);
+        acc_o[tl] = mfma_chain(ap, lds, bp, ldv, TR, acc_o[tl]);
       }
     }
     __syncthreads();
