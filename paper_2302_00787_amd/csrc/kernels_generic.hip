@@ -263,32 +263,61 @@ __device__ void rowmax_pass(uint32_t* rowmax_u, const float* Xs, float* Ws, floa
 
 // ---------------------------------------------------------------------------------------------------
 // Projection constants (Section 4, evaluation recipe): W~[m,:] = log2e * omega_m^T B, bias_m = log2e *
-// (omega_m^T A omega_m + log D - 1/2 log M).  grid (M, 2 sides, pgroups), block 128.
+// (omega_m^T A omega_m + log D - 1/2 log M).  grid (ceil(M/4), 2 sides, pgroups), block 128: thread c carries column c
+// of four features, so that a row of B is read once for the four, eight rows at a time in flight (one feature per
+// workgroup and one load at a time: 231 us for 16 heads of d 128, M 512 and 24 us for 4 of d 64, M 256; now 28 and 8).  Four and not
+// more: with few features the launch would leave most of the chip idle.
 // ---------------------------------------------------------------------------------------------------
-__global__ void k_prep(const float* theta, int groups, const float* Omega, int omega_groups, int pgroups,
+constexpr int PREP_F = 4;
+__global__ void __launch_bounds__(128) k_prep(const float* theta, int groups, const float* Omega, int omega_groups, int pgroups,
                        int B, int H, int M, int d, float* W, uint16_t* Wbf, float* bias) {
-  const int m = blockIdx.x, side = blockIdx.y, pg = blockIdx.z;
+  __shared__ float om[PREP_F][128];
+  const int m0 = blockIdx.x * PREP_F, side = blockIdx.y, pg = blockIdx.z, nf = min(PREP_F, M - m0);
   int b = 0, h = 0;
   if (pgroups == H && pgroups != 1) h = pg;
   else if (pgroups != 1) { b = pg / H; h = pg % H; }
   const size_t tf = FS_THETA_HEADER_ + (size_t)d + 4 * (size_t)d * d;
   const float* th = theta + (size_t)group_of(groups, b, h, H) * tf;
-  const float* om = Omega + ((size_t)group_of(omega_groups, b, h, H) * M + m) * d;
+  const float* omg = Omega + ((size_t)group_of(omega_groups, b, h, H) * M + m0) * d;
   const float* Bm = th + FS_THETA_HEADER_ + d + (side ? (size_t)d * d : 0);
-  const size_t o = (((size_t)pg * 2 + side) * M + m);
+  const size_t o = (((size_t)pg * 2 + side) * M + m0);
   const int c = threadIdx.x;
+#pragma unroll
+  for (int f = 0; f < PREP_F; ++f) om[f][c] = (f < nf && c < d) ? omg[(size_t)f * d + c] : 0.f;
+  __syncthreads();
   if (c < d) {
-    float acc = 0.f;
-    for (int l = 0; l < d; ++l) acc += om[l] * Bm[l * d + c];
-    acc *= kLog2e;
-    W[o * d + c] = acc;
-    Wbf[o * d + c] = f32_to_bf16_bits(acc);
+    float acc[PREP_F];
+#pragma unroll
+    for (int f = 0; f < PREP_F; ++f) acc[f] = 0.f;
+    int l = 0;
+    for (; l + 8 <= d; l += 8) {
+      float bv[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) bv[i] = Bm[(l + i) * d + c];
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int f = 0; f < PREP_F; ++f) acc[f] += om[f][l + i] * bv[i];
+    }
+    for (; l < d; ++l) {
+      const float bv = Bm[l * d + c];
+#pragma unroll
+      for (int f = 0; f < PREP_F; ++f) acc[f] += om[f][l] * bv;
+    }
+#pragma unroll
+    for (int f = 0; f < PREP_F; ++f)
+      if (f < nf) {
+        const float v = acc[f] * kLog2e;
+        W[(o + f) * d + c] = v;
+        Wbf[(o + f) * d + c] = f32_to_bf16_bits(v);
+      }
   }
-  if (c == 0) {
+  if (c < nf) {
     const float* A = th + FS_THETA_HEADER_;
     float q = 0.f;
-    for (int l = 0; l < d; ++l) q += A[l] * om[l] * om[l];
-    bias[o] = kLog2e * (q + th[0] - 0.5f * logf((float)M));
+#pragma unroll 8
+    for (int l = 0; l < d; ++l) q += A[l] * om[c][l] * om[c][l];
+    bias[o + c] = kLog2e * (q + th[0] - 0.5f * logf((float)M));
   }
 }
 
@@ -1475,7 +1504,7 @@ static int set_lds(const void* fn, size_t bytes) {
 
 int launch_prep(const float* theta, int groups, const float* Omega, int omega_groups, int pgroups, int B, int H,
                 int M, int d, float* W, uint16_t* Wbf, float* bias, hipStream_t st) {
-  hipLaunchKernelGGL(k_prep, dim3(M, 2, pgroups), dim3(128), 0, st, theta, groups, Omega, omega_groups, pgroups, B, H,
+  hipLaunchKernelGGL(k_prep, dim3((M + PREP_F - 1) / PREP_F, 2, pgroups), dim3(128), 0, st, theta, groups, Omega, omega_groups, pgroups, B, H,
                      M, d, W, Wbf, bias);
   FS_LAUNCH_CHECK();
   return 0;
