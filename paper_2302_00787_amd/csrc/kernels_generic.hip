@@ -13,9 +13,15 @@ namespace fs {
 
 constexpr int TR = 32;     // rows per tile
 constexpr int MB = 32;     // features per block
-constexpr int NT = 256;    // threads per workgroup
+constexpr int NT = 256;    // threads per workgroup (causal kernels: NTC)
+// The causal kernels keep so much in LDS that one or two workgroups fit a CU: eight waves each, two per SIMD or more.
+// Four of them work on the query side while the other four work on the key side, both projection blocks in LDS (two
+// barriers fewer per block).  Against four waves: causal attention B2 H4 L4096 d64 M256 f32 388 -> 320 us, causal
+// backward pass B1 H16 L4096 d128 M512 5.63 -> 4.64 ms.
+constexpr int NTC = 512;
 
 constexpr int ACC_PER_WAVE = 5;   // ceil(2 * MAXVT / 4)
+constexpr int ACC_PER_WAVE_C = 3; // ceil(2 * MAXVT / 8)
 
 // This side's C matrix, or nullptr when the parameter set says C = -I/2 (flag bit 0 of the theta header).
 __device__ __forceinline__ const float* side_cmat(const GenSide& s, int b, int h, int H) {
@@ -46,25 +52,28 @@ __device__ __forceinline__ f32x4 mfma_chain(const float* ap, int sa, const float
   return acc;
 }
 
-// A tile of 32 rows and up to 32 NI columns travelling global -> registers -> LDS: thread t carries rows t/32 + 8j,
+// A tile of 32 rows and up to 32 NI columns travelling global -> registers -> LDS: thread t carries rows t/32 + (TH/32) j,
 // columns t%32 + 32i.  All loads of a tile are in flight together, and between fetch and put a kernel may compute.  A
 // loop that stores each element to LDS as it arrives is a chain of 16 - 18 memory latencies per tile, with one
 // workgroup per CU (LDS) to hide them; together with mfma_chain and the state update from the LDS copy this took
 // causal attention B2 H4 L4096 d64 M256 f32 from 704 to 405 us and the causal backward pass B1 H16 L4096 d128 M512
 // from 15.2 to 5.9 ms, bit for bit the same.  Addresses outside the tile are clamped into it, so that no load is
 // conditional; the put writes zeros there.  The registers hold the raw bits (f32, or bf16 zero-extended).
-template <int NI> struct Tile { uint32_t v[4][NI]; };
-template <int NI>
-__device__ __forceinline__ void tile_fetch(Tile<NI>& t, const void* ptr, int dtype, long long base, long long stride,
+template <int NI, int TH> struct Tile { uint32_t v[TR * 32 / TH][NI]; };
+template <int NI, int TH>
+__device__ __forceinline__ void tile_fetch(Tile<NI, TH>& t, const void* ptr, int dtype, long long base, long long stride,
                                            int live, int ncols) {
-  const int r0 = threadIdx.x >> 5, c0 = threadIdx.x & 31;
+  int tid = threadIdx.x;
+  // (causal kernels: offsets are computed at each fetch; hoisted out of the loops they take more than 100 registers)
+  if constexpr (TH == NTC) asm volatile("" : "+v"(tid));
+  const int r0 = tid >> 5, c0 = tid & 31;
   if (dtype == 0) {
     const uint32_t* p = (const uint32_t*)ptr + base;
 #pragma unroll
     for (int i = 0; i < NI; ++i)
       if (32 * i < ncols) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) t.v[j][i] = p[(long long)min(r0 + 8 * j, live - 1) * stride + min(c0 + 32 * i, ncols - 1)];
+        for (int j = 0; j < TR * 32 / TH; ++j) t.v[j][i] = p[(long long)min(r0 + (TH / 32) * j, live - 1) * stride + min(c0 + 32 * i, ncols - 1)];
       }
   } else {
     const uint16_t* p = (const uint16_t*)ptr + base;
@@ -72,13 +81,13 @@ __device__ __forceinline__ void tile_fetch(Tile<NI>& t, const void* ptr, int dty
     for (int i = 0; i < NI; ++i)
       if (32 * i < ncols) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) t.v[j][i] = p[(long long)min(r0 + 8 * j, live - 1) * stride + min(c0 + 32 * i, ncols - 1)];
+        for (int j = 0; j < TR * 32 / TH; ++j) t.v[j][i] = p[(long long)min(r0 + (TH / 32) * j, live - 1) * stride + min(c0 + 32 * i, ncols - 1)];
       }
   }
 }
 // dst[r][c] = scale * tile for r < live, c < ncols, `fill` at column ncols of the live rows, 0 elsewhere up to ncols_pad.
-template <int NI>
-__device__ __forceinline__ void tile_put(const Tile<NI>& t, int dtype, float* dst, int ld, int live, int ncols,
+template <int NI, int TH>
+__device__ __forceinline__ void tile_put(const Tile<NI, TH>& t, int dtype, float* dst, int ld, int live, int ncols,
                                          int ncols_pad, float scale, float fill) {
   const int r0 = threadIdx.x >> 5, c0 = threadIdx.x & 31, shift = dtype == 0 ? 0 : 16;
 #pragma unroll
@@ -86,8 +95,8 @@ __device__ __forceinline__ void tile_put(const Tile<NI>& t, int dtype, float* ds
     const int c = c0 + 32 * i;
     if (c < ncols_pad) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int r = r0 + 8 * j;
+      for (int j = 0; j < TR * 32 / TH; ++j) {
+        const int r = r0 + (TH / 32) * j;
         float v = 0.f;
         if (r < live) v = c < ncols ? scale * __uint_as_float(t.v[j][i] << shift) : (c == ncols ? fill : 0.f);
         dst[r * ld + c] = v;
@@ -97,62 +106,72 @@ __device__ __forceinline__ void tile_put(const Tile<NI>& t, int dtype, float* ds
 }
 
 // Rows of a side (at most 128 columns) and of values (at most 144, with the column of ones that is the normaliser).
-typedef Tile<4> RowTile;
-typedef Tile<5> ValTile;
-static_assert(TR == 32 && MB == 32 && NT == 256, "tiles are carried by 8 x 32 threads, four rows each");
-__device__ __forceinline__ void rows_fetch(RowTile& x, const TensorDev& t, long long base, int row0, int nrows, int ncols) {
+template <int TH> using RowTile = Tile<4, TH>;
+template <int TH> using ValTile = Tile<5, TH>;
+static_assert(TR == 32 && MB == 32, "32 threads carry a row of a tile");
+template <int TH>
+__device__ __forceinline__ void rows_fetch(RowTile<TH>& x, const TensorDev& t, long long base, int row0, int nrows, int ncols) {
   tile_fetch(x, t.ptr, t.dtype, base + (long long)row0 * t.sl, t.sl, nrows - row0, ncols);
 }
-__device__ __forceinline__ void rows_put(const RowTile& x, const TensorDev& t, float* dst, int ld, int row0, int nrows,
+template <int TH>
+__device__ __forceinline__ void rows_put(const RowTile<TH>& x, const TensorDev& t, float* dst, int ld, int row0, int nrows,
                                          int ncols, int ncols_pad, float scale) {
   tile_put(x, t.dtype, dst, ld, nrows - row0, ncols, ncols_pad, scale, 0.f);
 }
-__device__ __forceinline__ void values_fetch(ValTile& x, const TensorDev& t, long long base, int row0, int nrows, int ncols) {
+template <int TH>
+__device__ __forceinline__ void values_fetch(ValTile<TH>& x, const TensorDev& t, long long base, int row0, int nrows, int ncols) {
   tile_fetch(x, t.ptr, t.dtype, base + (long long)row0 * t.sl, t.sl, nrows - row0, ncols);
 }
-__device__ __forceinline__ void values_put(const ValTile& x, const TensorDev& t, float* dst, int ld, int row0, int nrows,
+template <int TH>
+__device__ __forceinline__ void values_put(const ValTile<TH>& x, const TensorDev& t, float* dst, int ld, int row0, int nrows,
                                            int ncols, int ncols_pad, int append_ones) {
   tile_put(x, t.dtype, dst, ld, nrows - row0, ncols, ncols_pad, 1.f, append_ones ? 1.f : 0.f);
 }
 
 // dst[r][c] = scale * T[row0 + r][c] for r < 32; zero outside [0, nrows) x [0, ncols); columns up to ncols_pad written.
+template <int TH = NT>
 __device__ __forceinline__ void load_rows(float* dst, int ld, const TensorDev& t, long long base, int row0, int nrows,
                                           int ncols, int ncols_pad, float scale) {
-  RowTile x;
+  RowTile<TH> x;
   rows_fetch(x, t, base, row0, nrows, ncols);
   rows_put(x, t, dst, ld, row0, nrows, ncols, ncols_pad, scale);
 }
 
 // Value tile with an optional column of ones at index ncols (the normaliser column of attention).
+template <int TH = NT>
 __device__ __forceinline__ void load_values(float* dst, int ld, const TensorDev& t, long long base, int row0, int nrows,
                                             int ncols, int ncols_pad, int append_ones) {
-  ValTile x;
+  ValTile<TH> x;
   values_fetch(x, t, base, row0, nrows, ncols);
   values_put(x, t, dst, ld, row0, nrows, ncols, ncols_pad, append_ones);
 }
 
 // Ws[f][c] = W[m0 + f][c] (zero rows past M), bias_s[f] = bias[m0 + f], in two halves.
-struct WRegs { RowTile w; float b; };
-__device__ __forceinline__ void wblock_fetch(WRegs& r, const float* W, const float* bias, int m0, int M, int d) {
+template <int TH> struct WRegs { RowTile<TH> w; float b; };
+template <int TH>
+__device__ __forceinline__ void wblock_fetch(WRegs<TH>& r, const float* W, const float* bias, int m0, int M, int d) {
   tile_fetch(r.w, W, 0, (long long)m0 * d, d, M - m0, d);
   r.b = bias[min(m0 + (int)(threadIdx.x & (MB - 1)), M - 1)];
 }
-__device__ __forceinline__ void wblock_put(const WRegs& r, float* Ws, float* bias_s, int ld, int m0, int M, int d, int dpad) {
+template <int TH>
+__device__ __forceinline__ void wblock_put(const WRegs<TH>& r, float* Ws, float* bias_s, int ld, int m0, int M, int d, int dpad) {
   tile_put(r.w, 0, Ws, ld, M - m0, d, dpad, 1.f, 0.f);
   if (threadIdx.x < MB) bias_s[threadIdx.x] = m0 + (int)threadIdx.x < M ? r.b : 0.f;
 }
 __device__ __forceinline__ void load_wblock(float* Ws, float* bias_s, int ld, const float* W, const float* bias, int m0,
                                             int M, int d, int dpad) {
-  WRegs r;
+  WRegs<NT> r;
   wblock_fetch(r, W, bias, m0, M, d);
   wblock_put(r, Ws, bias_s, ld, m0, M, d, dpad);
 }
 
 // The block of a state that belongs to features m0 .. m0 + 31 (rows of ldt floats; zero rows past M).
-__device__ __forceinline__ void sblock_fetch(ValTile& t, const float* T, int m0, int M, int ldt) {
+template <int TH>
+__device__ __forceinline__ void sblock_fetch(ValTile<TH>& t, const float* T, int m0, int M, int ldt) {
   tile_fetch(t, T, 0, (long long)m0 * ldt, ldt, M - m0, ldt);
 }
-__device__ __forceinline__ void sblock_put(const ValTile& t, float* Ts, int ld, int m0, int M, int ldt) {
+template <int TH>
+__device__ __forceinline__ void sblock_put(const ValTile<TH>& t, float* Ts, int ld, int m0, int M, int ldt) {
   tile_put(t, 0, Ts, ld, M - m0, ldt, ldt, 1.f, 0.f);
 }
 
@@ -176,6 +195,7 @@ __device__ __forceinline__ float sym_row_dot(const float* Cmat, int d, int c, co
 
 // rterm[r] = log2e * (x_r^T C x_r + alpha |x_r|^2); Cmat == nullptr means C = -I/2.
 __device__ void row_terms(float* rterm, const float* Xs, int ld, int d, const float* Cmat, float alpha) {
+  if (threadIdx.x >= 8 * TR) return;         // eight threads a row
   const int r = threadIdx.x >> 3, part = threadIdx.x & 7;
   const float* x = Xs + r * ld;
   float acc = 0.f;
@@ -215,9 +235,9 @@ __device__ void row_terms_of(float* rterm, const GenSide& sd, int bh, int L, int
   }
 }
 
-// Wave w computes the 16x16 tile (row tile w>>1, feature tile w&1) of Xs * Ws^T.
+// Wave w (of four) computes the 16x16 tile (row tile w>>1, feature tile w&1) of Xs * Ws^T.
 __device__ __forceinline__ f32x4 proj_tile(const float* Xs, const float* Ws, int ld, int dpad) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = (threadIdx.x >> 6) & 3;
   const float* ap = Xs + ((w >> 1) * 16 + (lane & 15)) * ld + (lane >> 4);
   const float* bp = Ws + ((w & 1) * 16 + (lane & 15)) * ld + (lane >> 4);
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -227,7 +247,7 @@ __device__ __forceinline__ f32x4 proj_tile(const float* Xs, const float* Ws, int
 
 // Max of e[0..3] over the 16 lanes that share lane>>4, combined into LDS (ordered-uint image) per row.
 __device__ __forceinline__ void rowmax_update(uint32_t* rowmax_u, const float e[4]) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = (threadIdx.x >> 6) & 3;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     float v = e[r];
@@ -244,7 +264,7 @@ __device__ void rowmax_pass(uint32_t* rowmax_u, const float* Xs, float* Ws, floa
                             const float* bias, int M, int d, int dpad) {
   if (threadIdx.x < TR) rowmax_u[threadIdx.x] = 0u;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  WRegs wr;
+  WRegs<NT> wr;
   wblock_fetch(wr, W, bias, 0, M, d);
   for (int m0 = 0; m0 < M; m0 += MB) {
     __syncthreads();
@@ -257,6 +277,34 @@ __device__ void rowmax_pass(uint32_t* rowmax_u, const float* Xs, float* Ws, floa
 #pragma unroll
     for (int r = 0; r < 4; ++r) e[r] = (m0 + f < M) ? acc[r] + bias_s[f] : -INFINITY;
     rowmax_update(rowmax_u, e);
+  }
+  __syncthreads();
+}
+
+// The same with eight waves: two feature blocks per step, four waves each.
+__device__ void rowmax_pass2(uint32_t* rowmax_u, const float* Xs, float* Ws, float* Ws2, float* bias_s, float* bias2_s,
+                             int ld, const float* W, const float* bias, int M, int d, int dpad) {
+  if (threadIdx.x < TR) rowmax_u[threadIdx.x] = 0u;
+  const int lane = threadIdx.x & 63, w = (threadIdx.x >> 6) & 3, half = threadIdx.x >> 8;
+  WRegs<NTC> wa, wb;
+  wblock_fetch(wa, W, bias, 0, M, d);
+  if (MB < M) wblock_fetch(wb, W, bias, MB, M, d);
+  for (int m0 = 0; m0 < M; m0 += 2 * MB) {
+    __syncthreads();
+    wblock_put(wa, Ws, bias_s, ld, m0, M, d, dpad);
+    if (m0 + MB < M) wblock_put(wb, Ws2, bias2_s, ld, m0 + MB, M, d, dpad);
+    __syncthreads();
+    if (m0 + 2 * MB < M) wblock_fetch(wa, W, bias, m0 + 2 * MB, M, d);
+    if (m0 + 3 * MB < M) wblock_fetch(wb, W, bias, m0 + 3 * MB, M, d);
+    const int mb = m0 + half * MB;
+    if (mb < M) {
+      const f32x4 acc = proj_tile(Xs, half ? Ws2 : Ws, ld, dpad);
+      const int f = (w & 1) * 16 + (lane & 15);
+      float e[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) e[r] = (mb + f < M) ? acc[r] + (half ? bias2_s : bias_s)[f] : -INFINITY;
+      rowmax_update(rowmax_u, e);
+    }
   }
   __syncthreads();
 }
@@ -435,8 +483,8 @@ __global__ void __launch_bounds__(NT) k_gen_state(GenSide ks, TensorDev V, int L
   const int row_end = min(Lk, (seg + 1) * rows_per_seg);
   const long long xbase = b * ks.X.sb + h * ks.X.sh, vbase = b * V.sb + h * V.sh;
   // (the rows and values of the next step are fetched while the current one computes)
-  RowTile xr;
-  ValTile vr;
+  RowTile<NT> xr;
+  ValTile<NT> vr;
   rows_fetch(xr, ks.X, xbase, seg * rows_per_seg, row_end, d);
   values_fetch(vr, V, vbase, seg * rows_per_seg, row_end, nv);
   for (int row0 = seg * rows_per_seg; row0 < row_end; row0 += TR) {
@@ -523,9 +571,10 @@ __global__ void __launch_bounds__(256) k_gen_reduce(float* Tpart, int nseg, size
 
 // Normalise (attention) or rescale (operator) an accumulated 32 x ldt tile held in LDS and store it.  Attention
 // rows whose normaliser is not positive are written as zeros and, with a counter, counted (once per row).
+template <int TH = NT>
 __device__ void store_result(const float* Os, int ldo, const TensorDev& Y, long long ybase, int row0, int nrows,
                              int nv, int matvec, const float* row_log2scale, unsigned* flushed = nullptr) {
-  for (int idx = threadIdx.x; idx < TR * nv; idx += NT) {
+  for (int idx = threadIdx.x; idx < TR * nv; idx += TH) {
     const int r = idx / nv, c = idx - r * nv;
     if (row0 + r >= nrows) continue;
     float v = Os[r * ldo + c];
@@ -580,8 +629,8 @@ __global__ void __launch_bounds__(NT) k_gen_apply(GenSide qs, int Lq, int H, int
 #pragma unroll
   for (int t = 0; t < ACC_PER_WAVE; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
   // the projection block and the state block of the next step are fetched while the current step computes
-  WRegs wr;
-  ValTile tr;
+  WRegs<NT> wr;
+  ValTile<NT> tr;
   wblock_fetch(wr, W, bias, 0, M, d);
   sblock_fetch(tr, Tb, 0, M, ldt);
   for (int m0 = 0; m0 < M; m0 += MB) {
@@ -638,7 +687,7 @@ __global__ void __launch_bounds__(NT) k_gen_apply(GenSide qs, int Lq, int H, int
 //   Y_c = (tril(P_c S_c^T) [V_c 1] + P_c T_prev) normalised by its last column;  T += S_c^T [V_c 1].
 // grid (nseg, B*H).
 // ---------------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(NT) k_gen_causal(GenSide qs, GenSide ks, TensorDev V, int L, int H, int M, int d,
+__global__ void __launch_bounds__(NTC) k_gen_causal(GenSide qs, GenSide ks, TensorDev V, int L, int H, int M, int d,
                                                    int nv, int ldt, int rows_per_seg, int nseg,
                                                    const uint32_t* kmax_u, float* Tstate, TensorDev Y, float* den_out,
                                                    float* shift_out, unsigned* flushed) {
@@ -647,16 +696,18 @@ __global__ void __launch_bounds__(NT) k_gen_causal(GenSide qs, GenSide ks, Tenso
   float* Qs = smem;
   float* Ks = Qs + TR * ld;
   float* Ws = Ks + TR * ld;
-  float* Vs = Ws + MB * ld;
+  float* Ws2 = Ws + MB * ld;          // Ws, bias_s: query side, Ws2, bias2_s: key side
+  float* Vs = Ws2 + MB * ld;
   float* Ts = Vs + TR * ldv;          // state block, later the output tile
   float* Ps = Ts + MB * ldv;
   float* Ss = Ps + TR * lds;
   float* As = Ss + TR * lds;
   float* bias_s = As + TR * lds;
-  float* rterm = bias_s + MB;
+  float* bias2_s = bias_s + MB;
+  float* rterm = bias2_s + MB;
   uint32_t* rowmax_u = (uint32_t*)(rterm + TR);
   const int seg = blockIdx.x, bh = blockIdx.y, b = bh / H, h = bh % H;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, w4 = w & 3, half = w >> 2;
   const int pgq = group_of(qs.pgroups, b, h, H);
   const float* W1 = qs.W + ((size_t)pgq * 2) * M * d;
   const float* bias1 = qs.bias + ((size_t)pgq * 2) * M;
@@ -671,63 +722,61 @@ __global__ void __launch_bounds__(NT) k_gen_causal(GenSide qs, GenSide ks, Tenso
   const int row_end = min(L, (seg + 1) * rows_per_seg);
   for (int row0 = seg * rows_per_seg; row0 < row_end; row0 += TR) {
     __syncthreads();
-    load_rows(Qs, ld, qs.X, qbase, row0, row_end, d, dpad, qs.scale);
-    load_rows(Ks, ld, ks.X, kbase, row0, row_end, d, dpad, ks.scale);
-    load_values(Vs, ldv, V, b * V.sb + h * V.sh, row0, row_end, nv, ldt, 1);
+    load_rows<NTC>(Qs, ld, qs.X, qbase, row0, row_end, d, dpad, qs.scale);
+    load_rows<NTC>(Ks, ld, ks.X, kbase, row0, row_end, d, dpad, ks.scale);
+    load_values<NTC>(Vs, ldv, V, b * V.sb + h * V.sh, row0, row_end, nv, ldt, 1);
     __syncthreads();
     row_terms_of(rterm, ks, bh, L, row0, row_end, Ks, ld, d, Cmat2, 0.f);
-    rowmax_pass(rowmax_u, Qs, Ws, bias_s, ld, W1, bias1, M, d, dpad);
+    rowmax_pass2(rowmax_u, Qs, Ws, Ws2, bias_s, bias2_s, ld, W1, bias1, M, d, dpad);
 
-    f32x4 acc[ACC_PER_WAVE];
+    f32x4 acc[ACC_PER_WAVE_C];
 #pragma unroll
-    for (int t = 0; t < ACC_PER_WAVE; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < ACC_PER_WAVE_C; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     f32x4 sc = {0.f, 0.f, 0.f, 0.f};          // scores tile (query tile w>>1, key tile w&1)
     // the three blocks of the next step are fetched while the current one computes (rows of the state that this step
     // writes are not among them)
-    WRegs wa, wb;
-    ValTile tr;
+    WRegs<NTC> wa, wb;
+    ValTile<NTC> tr;
     wblock_fetch(wa, W1, bias1, 0, M, d);
     sblock_fetch(tr, Tg, 0, M, ldt);
     wblock_fetch(wb, W2, bias2, 0, M, d);
     for (int m0 = 0; m0 < M; m0 += MB) {
-      const int f = (w & 1) * 16 + (lane & 15);
+      const int f = (w4 & 1) * 16 + (lane & 15);
       __syncthreads();
       wblock_put(wa, Ws, bias_s, ld, m0, M, d, dpad);
+      wblock_put(wb, Ws2, bias2_s, ld, m0, M, d, dpad);
       sblock_put(tr, Ts, ldv, m0, M, ldt);
       __syncthreads();
       if (m0 + MB < M) {
         wblock_fetch(wa, W1, bias1, m0 + MB, M, d);
+        wblock_fetch(wb, W2, bias2, m0 + MB, M, d);
         sblock_fetch(tr, Tg, m0 + MB, M, ldt);
       }
-      {
+      if (half == 0) {
         const f32x4 e = proj_tile(Qs, Ws, ld, dpad);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int row = (w >> 1) * 16 + 4 * (lane >> 4) + r;
+          const int row = (w4 >> 1) * 16 + 4 * (lane >> 4) + r;
           Ps[row * lds + f] = (m0 + f < M) ? fast_exp2(e[r] + bias_s[f] - ordered_to_float(rowmax_u[row])) : 0.f;
         }
       }
-      __syncthreads();
-      wblock_put(wb, Ws, bias_s, ld, m0, M, d, dpad);
-      __syncthreads();
-      if (m0 + MB < M) wblock_fetch(wb, W2, bias2, m0 + MB, M, d);
-      {
-        const f32x4 e = proj_tile(Ks, Ws, ld, dpad);
+      else {
+        const f32x4 e = proj_tile(Ks, Ws2, ld, dpad);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int row = (w >> 1) * 16 + 4 * (lane >> 4) + r;
-          Ss[row * lds + f] = (m0 + f < M) ? fast_exp2(e[r] + bias_s[f] + rterm[row] - c) : 0.f;
+          const int row = (w4 >> 1) * 16 + 4 * (lane >> 4) + r;
+          Ss[row * lds + f] = (m0 + f < M) ? fast_exp2(e[r] + bias2_s[f] + rterm[row] - c) : 0.f;
         }
       }
       __syncthreads();
-      {   // scores: A[i][k=m] = Ps[i][m], B[k=m][n=j] = Ss[j][m]
-        const float* ap = Ps + ((w >> 1) * 16 + (lane & 15)) * lds + (lane >> 4);
-        const float* bp = Ss + ((w & 1) * 16 + (lane & 15)) * lds + (lane >> 4);
+      if (half == 1) {   // scores: A[i][k=m] = Ps[i][m], B[k=m][n=j] = Ss[j][m]
+        const float* ap = Ps + ((w4 >> 1) * 16 + (lane & 15)) * lds + (lane >> 4);
+        const float* bp = Ss + ((w4 & 1) * 16 + (lane & 15)) * lds + (lane >> 4);
         sc = mfma_chain(ap, 1, bp, 1, MB, sc);
       }
 #pragma unroll
-      for (int tl = 0; tl < ACC_PER_WAVE; ++tl) {
-        const int t = w + 4 * tl;
+      for (int tl = 0; tl < ACC_PER_WAVE_C; ++tl) {
+        const int t = w + 8 * tl;
         if (t < ntiles) {
           const int rt = t & 1, vt = t >> 1;
           {   // inter-chunk term with the state before this step
@@ -750,15 +799,16 @@ __global__ void __launch_bounds__(NT) k_gen_causal(GenSide qs, GenSide ks, Tenso
       }
     }
     // causal mask inside the step (key j <= query i), then the intra-chunk product
+    if (half == 1)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int i = (w >> 1) * 16 + 4 * (lane >> 4) + r, j = (w & 1) * 16 + (lane & 15);
+      const int i = (w4 >> 1) * 16 + 4 * (lane >> 4) + r, j = (w4 & 1) * 16 + (lane & 15);
       As[i * lds + j] = (j <= i) ? sc[r] : 0.f;
     }
     __syncthreads();
 #pragma unroll
-    for (int tl = 0; tl < ACC_PER_WAVE; ++tl) {
-      const int t = w + 4 * tl;
+    for (int tl = 0; tl < ACC_PER_WAVE_C; ++tl) {
+      const int t = w + 8 * tl;
       if (t < ntiles) {
         const int rt = t & 1, vt = t >> 1;
         const float* ap = As + (rt * 16 + (lane & 15)) * lds + (lane >> 4);
@@ -769,8 +819,8 @@ __global__ void __launch_bounds__(NT) k_gen_causal(GenSide qs, GenSide ks, Tenso
     __syncthreads();
     float* Os = Ts;
 #pragma unroll
-    for (int tl = 0; tl < ACC_PER_WAVE; ++tl) {
-      const int t = w + 4 * tl;
+    for (int tl = 0; tl < ACC_PER_WAVE_C; ++tl) {
+      const int t = w + 8 * tl;
       if (t < ntiles) {
         const int rt = t & 1, vt = t >> 1;
 #pragma unroll
@@ -778,7 +828,7 @@ __global__ void __launch_bounds__(NT) k_gen_causal(GenSide qs, GenSide ks, Tenso
       }
     }
     __syncthreads();
-    store_result(Os, ldv, Y, b * Y.sb + h * Y.sh, row0, row_end, nv, 0, nullptr, flushed);
+    store_result<NTC>(Os, ldv, Y, b * Y.sb + h * Y.sh, row0, row_end, nv, 0, nullptr, flushed);
     if (den_out != nullptr && threadIdx.x < TR && row0 + threadIdx.x < row_end) {   // for the backward pass
       den_out[(size_t)bh * L + row0 + threadIdx.x] = Os[threadIdx.x * ldv + nv];
       shift_out[(size_t)bh * L + row0 + threadIdx.x] = ordered_to_float(rowmax_u[threadIdx.x]);
@@ -947,8 +997,8 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_side(GenSide sd, int side, Tenso
   for (int t = 0; t < 4; ++t) acc_g[t] = f32x4{0.f, 0.f, 0.f, 0.f};
   float rs_part = 0.f;               // thread (row = tid / 8, part = tid % 8): its share of rowsum(dE)
 
-  WRegs wr;                          // the next step's blocks, fetched while the current one computes
-  ValTile tr;
+  WRegs<NT> wr;                          // the next step's blocks, fetched while the current one computes
+  ValTile<NT> tr;
   wblock_fetch(wr, W, bias, 0, M, d);
   sblock_fetch(tr, Sb, 0, M, ldt);
   for (int m0 = 0; m0 < M; m0 += MB) {
@@ -1072,14 +1122,15 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_side(GenSide sd, int side, Tenso
 // grid (nseg, B*H) both.
 // ---------------------------------------------------------------------------------------------------
 struct BwdCausalSmem {
-  float *Qs, *Ks, *Ws, *Vs, *Gs, *Ts, *Ps, *Ss, *dEs, *As, *Bs, *bias_s, *rterm, *qsh, *rsum;
+  float *Qs, *Ks, *Ws, *Ws2, *Vs, *Gs, *Ts, *Ps, *Ss, *dEs, *As, *Bs, *bias_s, *bias2_s, *rterm, *qsh, *rsum;
 };
 __device__ __forceinline__ BwdCausalSmem bwd_causal_carve(float* smem, int ld, int ldv, int lds) {
   BwdCausalSmem m;
   m.Qs = smem;
   m.Ks = m.Qs + TR * ld;
   m.Ws = m.Ks + TR * ld;
-  m.Vs = m.Ws + MB * ld;
+  m.Ws2 = m.Ws + MB * ld;              // Ws, bias_s: query side, Ws2, bias2_s: key side
+  m.Vs = m.Ws2 + MB * ld;
   m.Gs = m.Vs + TR * ldv;
   m.Ts = m.Gs + TR * ldv;
   m.Ps = m.Ts + MB * ldv;
@@ -1088,7 +1139,8 @@ __device__ __forceinline__ BwdCausalSmem bwd_causal_carve(float* smem, int ld, i
   m.As = m.dEs + TR * lds;
   m.Bs = m.As + TR * lds;
   m.bias_s = m.Bs + TR * lds;
-  m.rterm = m.bias_s + MB;
+  m.bias2_s = m.bias_s + MB;
+  m.rterm = m.bias2_s + MB;
   m.qsh = m.rterm + TR;
   m.rsum = m.qsh + TR;
   return m;
@@ -1097,6 +1149,7 @@ __device__ __forceinline__ BwdCausalSmem bwd_causal_carve(float* smem, int ld, i
 // As[i][j] = (j <= i) ? G1_i . V1_j : 0 for the chunk's 32 x 32 (query, key) pairs; wave w owns tile (w>>1, w&1).
 __device__ __forceinline__ void bwd_causal_amat(float* As, const float* Gs, const float* Vs, int ldv, int lds, int ldt) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  if (w >= 4) return;
   const float* ap = Gs + ((w >> 1) * 16 + (lane & 15)) * ldv + (lane >> 4);   // A[i][k=v] = Gs[i][v]
   const float* bp = Vs + ((w & 1) * 16 + (lane & 15)) * ldv + (lane >> 4);    // B[k=v][n=j] = Vs[j][v]
   f32x4 a = {0.f, 0.f, 0.f, 0.f};
@@ -1112,7 +1165,7 @@ __device__ __forceinline__ void bwd_causal_amat(float* As, const float* Gs, cons
 __device__ __forceinline__ void bwd_store_grad(const TensorDev& grad, long long base, int row0, int row_end, int d, int ld,
                                                const float* Gsrc, const float* rsum, const float* Xs, const float* Cmat,
                                                float scale, float alpha) {
-  for (int idx = threadIdx.x; idx < TR * d; idx += NT) {
+  for (int idx = threadIdx.x; idx < TR * d; idx += NTC) {
     const int r = idx / d, c = idx - r * d;
     if (row0 + r >= row_end) continue;
     float cx;
@@ -1125,7 +1178,7 @@ __device__ __forceinline__ void bwd_store_grad(const TensorDev& grad, long long 
   }
 }
 
-__global__ void __launch_bounds__(NT) k_gen_bwd_causal_q(GenSide qs, GenSide ks, TensorDev V, const float* ghat, int L,
+__global__ void __launch_bounds__(NTC) k_gen_bwd_causal_q(GenSide qs, GenSide ks, TensorDev V, const float* ghat, int L,
                                                          int H, int M, int d, int nv, int ldt, int rows_per_seg, int nseg,
                                                          const uint32_t* kmax_u, const float* row_shift, float* Tstate,
                                                          TensorDev dQ) {
@@ -1133,7 +1186,7 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_causal_q(GenSide qs, GenSide ks,
   const int dpad = (d + 3) & ~3, ld = dpad + 1, ldv = ldt + 1, lds = MB + 1;
   const BwdCausalSmem m = bwd_causal_carve(smem, ld, ldv, lds);
   const int seg = blockIdx.x, bh = blockIdx.y, b = bh / H, h = bh % H;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, w4 = w & 3, half = w >> 2;
   const int pg = group_of(qs.pgroups, b, h, H);
   const float* W1 = qs.W + ((size_t)pg * 2) * M * d;
   const float* bias1 = qs.bias + ((size_t)pg * 2) * M;
@@ -1150,78 +1203,75 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_causal_q(GenSide qs, GenSide ks,
   const int row_end = min(L, (seg + 1) * rows_per_seg);
   for (int row0 = seg * rows_per_seg; row0 < row_end; row0 += TR) {
     __syncthreads();
-    load_rows(m.Qs, ld, qs.X, qbase, row0, row_end, d, dpad, qs.scale);
-    load_rows(m.Ks, ld, ks.X, kbase, row0, row_end, d, dpad, ks.scale);
-    load_values(m.Vs, ldv, V, b * V.sb + h * V.sh, row0, row_end, nv, ldt, 1);
-    load_values(m.Gs, ldv, G, b * G.sb + h * G.sh, row0, row_end, ldt, ldt, 0);
+    load_rows<NTC>(m.Qs, ld, qs.X, qbase, row0, row_end, d, dpad, qs.scale);
+    load_rows<NTC>(m.Ks, ld, ks.X, kbase, row0, row_end, d, dpad, ks.scale);
+    load_values<NTC>(m.Vs, ldv, V, b * V.sb + h * V.sh, row0, row_end, nv, ldt, 1);
+    load_values<NTC>(m.Gs, ldv, G, b * G.sb + h * G.sh, row0, row_end, ldt, ldt, 0);
     if (threadIdx.x < TR) m.qsh[threadIdx.x] = row0 + threadIdx.x < row_end ? -row_shift[(size_t)bh * L + row0 + threadIdx.x] : 0.f;
     __syncthreads();
     row_terms_of(m.rterm, ks, bh, L, row0, row_end, m.Ks, ld, d, Cmat2, 0.f);
     bwd_causal_amat(m.As, m.Gs, m.Vs, ldv, lds, ldt);
 
-    f32x4 acc_g[4];
+    f32x4 acc_g[2];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) acc_g[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < 2; ++t) acc_g[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     float rs_part = 0.f;
     // the three blocks of the next step are fetched while the current one computes (rows of the state that this step
     // writes are not among them)
-    WRegs wa, wb;
-    ValTile tr;
+    WRegs<NTC> wa, wb;
+    ValTile<NTC> tr;
     wblock_fetch(wa, W2, bias2, 0, M, d);
     sblock_fetch(tr, Tg, 0, M, ldt);
     wblock_fetch(wb, W1, bias1, 0, M, d);
     for (int m0 = 0; m0 < M; m0 += MB) {
-      const int f = (w & 1) * 16 + (lane & 15);
+      const int f = (w4 & 1) * 16 + (lane & 15);
       __syncthreads();
-      wblock_put(wa, m.Ws, m.bias_s, ld, m0, M, d, dpad);
+      wblock_put(wa, m.Ws2, m.bias2_s, ld, m0, M, d, dpad);
+      wblock_put(wb, m.Ws, m.bias_s, ld, m0, M, d, dpad);
       sblock_put(tr, m.Ts, ldv, m0, M, ldt);
       __syncthreads();
       if (m0 + MB < M) {
         wblock_fetch(wa, W2, bias2, m0 + MB, M, d);
+        wblock_fetch(wb, W1, bias1, m0 + MB, M, d);
         sblock_fetch(tr, Tg, m0 + MB, M, ldt);
       }
-      {
-        const f32x4 e = proj_tile(m.Ks, m.Ws, ld, dpad);
+      // waves 0 - 3: features and dP tile (rows (w4>>1)*16.., features (w4&1)*16..) = G1 T_prev^T + A S of the queries;
+      // waves 4 - 7: features of the keys
+      float fv[4];
+      f32x4 df = {0.f, 0.f, 0.f, 0.f};
+      if (half == 0) {
+        const f32x4 e = proj_tile(m.Qs, m.Ws, ld, dpad);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int row = (w >> 1) * 16 + 4 * (lane >> 4) + r;
-          m.Ss[row * lds + f] = (m0 + f < M && row0 + row < row_end) ? fast_exp2(e[r] + m.bias_s[f] + m.rterm[row] - c) : 0.f;
+          const int row = (w4 >> 1) * 16 + 4 * (lane >> 4) + r;
+          fv[r] = (m0 + f < M && row0 + row < row_end) ? fast_exp2(e[r] + m.bias_s[f] + m.qsh[row]) : 0.f;
+        }
+        const float* ap = m.Gs + ((w4 >> 1) * 16 + (lane & 15)) * ldv + (lane >> 4);   // A[i][k=v] = Gs[i][v]
+        const float* bp = m.Ts + ((w4 & 1) * 16 + (lane & 15)) * ldv + (lane >> 4);    // B[k=v][n=m] = Ts[m][v]
+        df = mfma_chain(ap, 1, bp, 1, ldt, df);
+      } else {
+        const f32x4 e = proj_tile(m.Ks, m.Ws2, ld, dpad);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = (w4 >> 1) * 16 + 4 * (lane >> 4) + r;
+          m.Ss[row * lds + f] = (m0 + f < M && row0 + row < row_end) ? fast_exp2(e[r] + m.bias2_s[f] + m.rterm[row] - c) : 0.f;
         }
       }
       __syncthreads();
-      wblock_put(wb, m.Ws, m.bias_s, ld, m0, M, d, dpad);
-      __syncthreads();
-      if (m0 + MB < M) wblock_fetch(wb, W1, bias1, m0 + MB, M, d);
-      {
-        const f32x4 e = proj_tile(m.Qs, m.Ws, ld, dpad);
-        float fv[4];
+      if (half == 0) {
+        const float* ap = m.As + ((w4 >> 1) * 16 + (lane & 15)) * lds + (lane >> 4);   // A[i][k=j] = As[i][j]
+        const float* bp = m.Ss + (lane >> 4) * lds + (w4 & 1) * 16 + (lane & 15);      // B[k=j][n=m] = Ss[j][m]
+        df = mfma_chain(ap, 1, bp, lds, TR, df);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int row = (w >> 1) * 16 + 4 * (lane >> 4) + r;
-          fv[r] = (m0 + f < M && row0 + row < row_end) ? fast_exp2(e[r] + m.bias_s[f] + m.qsh[row]) : 0.f;
-        }
-        // dP tile (rows (w>>1)*16.., features (w&1)*16..) = G1 T_prev^T + A S
-        f32x4 df = {0.f, 0.f, 0.f, 0.f};
-        {
-          const float* ap = m.Gs + ((w >> 1) * 16 + (lane & 15)) * ldv + (lane >> 4);   // A[i][k=v] = Gs[i][v]
-          const float* bp = m.Ts + ((w & 1) * 16 + (lane & 15)) * ldv + (lane >> 4);    // B[k=v][n=m] = Ts[m][v]
-          df = mfma_chain(ap, 1, bp, 1, ldt, df);
-        }
-        {
-          const float* ap = m.As + ((w >> 1) * 16 + (lane & 15)) * lds + (lane >> 4);   // A[i][k=j] = As[i][j]
-          const float* bp = m.Ss + (lane >> 4) * lds + (w & 1) * 16 + (lane & 15);      // B[k=j][n=m] = Ss[j][m]
-          df = mfma_chain(ap, 1, bp, lds, TR, df);
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int row = (w >> 1) * 16 + 4 * (lane >> 4) + r;
+          const int row = (w4 >> 1) * 16 + 4 * (lane >> 4) + r;
           m.dEs[row * lds + f] = fv[r] * df[r];
         }
       }
       __syncthreads();
 #pragma unroll
-      for (int tl = 0; tl < 4; ++tl) {
-        const int t = w + 4 * tl;
+      for (int tl = 0; tl < 2; ++tl) {
+        const int t = w + 8 * tl;
         if (t < ngt) {
           const int rt = t & 1, ct = t >> 1;
           const float* ap = m.dEs + (rt * 16 + (lane & 15)) * lds + (lane >> 4);        // A[i][k=m] = dEs[i][m]
@@ -1229,15 +1279,15 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_causal_q(GenSide qs, GenSide ks,
           acc_g[tl] = mfma_chain(ap, 1, bp, ld, MB, acc_g[tl]);
         }
       }
-      {
+      if (half == 0) {
         const int row = threadIdx.x >> 3, part = threadIdx.x & 7;
 #pragma unroll
         for (int q = 0; q < 4; ++q) rs_part += m.dEs[row * lds + part * 4 + q];
       }
       // the state takes this chunk's keys (after its last use above): T[m][v] += sum_j Ss[j][m] Vs[j][v]
 #pragma unroll
-      for (int tl = 0; tl < ACC_PER_WAVE; ++tl) {
-        const int t = w + 4 * tl;
+      for (int tl = 0; tl < ACC_PER_WAVE_C; ++tl) {
+        const int t = w + 8 * tl;
         if (t < ntiles) {
           const int rt = t & 1, vt = t >> 1;
           f32x4 up = {0.f, 0.f, 0.f, 0.f};
@@ -1255,8 +1305,8 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_causal_q(GenSide qs, GenSide ks,
     __syncthreads();
     float* Gd = m.Ws;
 #pragma unroll
-    for (int tl = 0; tl < 4; ++tl) {
-      const int t = w + 4 * tl;
+    for (int tl = 0; tl < 2; ++tl) {
+      const int t = w + 8 * tl;
       if (t < ngt) {
         const int rt = t & 1, ct = t >> 1, col = ct * 16 + (lane & 15);
         if (col < dpad) {
@@ -1268,13 +1318,13 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_causal_q(GenSide qs, GenSide ks,
     rs_part += __shfl_xor(rs_part, 1);
     rs_part += __shfl_xor(rs_part, 2);
     rs_part += __shfl_xor(rs_part, 4);
-    if ((threadIdx.x & 7) == 0) m.rsum[threadIdx.x >> 3] = rs_part;
+    if (half == 0 && (threadIdx.x & 7) == 0) m.rsum[threadIdx.x >> 3] = rs_part;
     __syncthreads();
     bwd_store_grad(dQ, b * dQ.sb + h * dQ.sh, row0, row_end, d, ld, Gd, m.rsum, m.Qs, Cmat1, qs.scale, 0.f);
   }
 }
 
-__global__ void __launch_bounds__(NT) k_gen_bwd_causal_k(GenSide qs, GenSide ks, TensorDev V, const float* ghat, int L,
+__global__ void __launch_bounds__(NTC) k_gen_bwd_causal_k(GenSide qs, GenSide ks, TensorDev V, const float* ghat, int L,
                                                          int H, int M, int d, int nv, int ldt, int rows_per_seg, int nseg,
                                                          const uint32_t* kmax_u, const float* row_shift, float* Rstate,
                                                          TensorDev dK, TensorDev dV) {
@@ -1282,7 +1332,7 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_causal_k(GenSide qs, GenSide ks,
   const int dpad = (d + 3) & ~3, ld = dpad + 1, ldv = ldt + 1, lds = MB + 1;
   const BwdCausalSmem m = bwd_causal_carve(smem, ld, ldv, lds);
   const int seg = blockIdx.x, bh = blockIdx.y, b = bh / H, h = bh % H;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, w4 = w & 3, half = w >> 2;
   const int pg = group_of(qs.pgroups, b, h, H);
   const float* W1 = qs.W + ((size_t)pg * 2) * M * d;
   const float* bias1 = qs.bias + ((size_t)pg * 2) * M;
@@ -1300,87 +1350,83 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_causal_k(GenSide qs, GenSide ks,
   for (int ch = nchunk - 1; ch >= 0; --ch) {
     const int row0 = row_beg + ch * TR;
     __syncthreads();
-    load_rows(m.Qs, ld, qs.X, qbase, row0, row_end, d, dpad, qs.scale);
-    load_rows(m.Ks, ld, ks.X, kbase, row0, row_end, d, dpad, ks.scale);
-    load_values(m.Vs, ldv, V, b * V.sb + h * V.sh, row0, row_end, nv, ldt, 1);
-    load_values(m.Gs, ldv, G, b * G.sb + h * G.sh, row0, row_end, ldt, ldt, 0);
+    load_rows<NTC>(m.Qs, ld, qs.X, qbase, row0, row_end, d, dpad, qs.scale);
+    load_rows<NTC>(m.Ks, ld, ks.X, kbase, row0, row_end, d, dpad, ks.scale);
+    load_values<NTC>(m.Vs, ldv, V, b * V.sb + h * V.sh, row0, row_end, nv, ldt, 1);
+    load_values<NTC>(m.Gs, ldv, G, b * G.sb + h * G.sh, row0, row_end, ldt, ldt, 0);
     if (threadIdx.x < TR) m.qsh[threadIdx.x] = row0 + threadIdx.x < row_end ? -row_shift[(size_t)bh * L + row0 + threadIdx.x] : 0.f;
     __syncthreads();
     row_terms_of(m.rterm, ks, bh, L, row0, row_end, m.Ks, ld, d, Cmat2, 0.f);
     bwd_causal_amat(m.As, m.Gs, m.Vs, ldv, lds, ldt);
 
-    f32x4 acc_o[ACC_PER_WAVE], acc_g[4];
+    f32x4 acc_o[ACC_PER_WAVE_C], acc_g[2];
 #pragma unroll
-    for (int t = 0; t < ACC_PER_WAVE; ++t) acc_o[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < ACC_PER_WAVE_C; ++t) acc_o[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int t = 0; t < 4; ++t) acc_g[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < 2; ++t) acc_g[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     f32x4 sc = {0.f, 0.f, 0.f, 0.f};      // scores tile (query tile w>>1, key tile w&1)
     float rs_part = 0.f;
     // the three blocks of the next step are fetched while the current one computes (rows of the state that this step
     // writes are not among them)
-    WRegs wa, wb;
-    ValTile tr;
+    WRegs<NTC> wa, wb;
+    ValTile<NTC> tr;
     wblock_fetch(wa, W1, bias1, 0, M, d);
     sblock_fetch(tr, Rg, 0, M, ldt);
     wblock_fetch(wb, W2, bias2, 0, M, d);
     for (int m0 = 0; m0 < M; m0 += MB) {
-      const int f = (w & 1) * 16 + (lane & 15);
+      const int f = (w4 & 1) * 16 + (lane & 15);
       __syncthreads();
       wblock_put(wa, m.Ws, m.bias_s, ld, m0, M, d, dpad);
+      wblock_put(wb, m.Ws2, m.bias2_s, ld, m0, M, d, dpad);
       sblock_put(tr, m.Ts, ldv, m0, M, ldt);
       __syncthreads();
       if (m0 + MB < M) {
         wblock_fetch(wa, W1, bias1, m0 + MB, M, d);
+        wblock_fetch(wb, W2, bias2, m0 + MB, M, d);
         sblock_fetch(tr, Rg, m0 + MB, M, ldt);
       }
-      {
+      // waves 0 - 3: features of the queries, then scores; waves 4 - 7: features and dS tile (keys (w4>>1)*16..,
+      // features (w4&1)*16..) = V1 R_next^T + A^T P of the keys
+      float fv[4];
+      f32x4 ds = {0.f, 0.f, 0.f, 0.f};
+      if (half == 0) {
         const f32x4 e = proj_tile(m.Qs, m.Ws, ld, dpad);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int row = (w >> 1) * 16 + 4 * (lane >> 4) + r;
+          const int row = (w4 >> 1) * 16 + 4 * (lane >> 4) + r;
           m.Ps[row * lds + f] = (m0 + f < M && row0 + row < row_end) ? fast_exp2(e[r] + m.bias_s[f] + m.qsh[row]) : 0.f;
         }
-      }
-      __syncthreads();
-      wblock_put(wb, m.Ws, m.bias_s, ld, m0, M, d, dpad);
-      __syncthreads();
-      if (m0 + MB < M) wblock_fetch(wb, W2, bias2, m0 + MB, M, d);
-      {
-        const f32x4 e = proj_tile(m.Ks, m.Ws, ld, dpad);
-        float fv[4];
+      } else {
+        const f32x4 e = proj_tile(m.Ks, m.Ws2, ld, dpad);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int row = (w >> 1) * 16 + 4 * (lane >> 4) + r;
-          fv[r] = (m0 + f < M && row0 + row < row_end) ? fast_exp2(e[r] + m.bias_s[f] + m.rterm[row] - c) : 0.f;
+          const int row = (w4 >> 1) * 16 + 4 * (lane >> 4) + r;
+          fv[r] = (m0 + f < M && row0 + row < row_end) ? fast_exp2(e[r] + m.bias2_s[f] + m.rterm[row] - c) : 0.f;
           m.Ss[row * lds + f] = fv[r];
         }
-        // dS tile (keys (w>>1)*16.., features (w&1)*16..) = V1 R_next^T + A^T P
-        f32x4 ds = {0.f, 0.f, 0.f, 0.f};
-        {
-          const float* ap = m.Vs + ((w >> 1) * 16 + (lane & 15)) * ldv + (lane >> 4);   // A[j][k=v] = Vs[j][v]
-          const float* bp = m.Ts + ((w & 1) * 16 + (lane & 15)) * ldv + (lane >> 4);    // B[k=v][n=m] = Rs[m][v]
-          ds = mfma_chain(ap, 1, bp, 1, ldt, ds);
-        }
-        {
-          const float* ap = m.As + (lane >> 4) * lds + (w >> 1) * 16 + (lane & 15);     // A[j][k=i] = As[i][j]
-          const float* bp = m.Ps + (lane >> 4) * lds + (w & 1) * 16 + (lane & 15);      // B[k=i][n=m] = Ps[i][m]
-          ds = mfma_chain(ap, lds, bp, lds, TR, ds);
-        }
+        const float* ap = m.Vs + ((w4 >> 1) * 16 + (lane & 15)) * ldv + (lane >> 4);   // A[j][k=v] = Vs[j][v]
+        const float* bp = m.Ts + ((w4 & 1) * 16 + (lane & 15)) * ldv + (lane >> 4);    // B[k=v][n=m] = Rs[m][v]
+        ds = mfma_chain(ap, 1, bp, 1, ldt, ds);
+      }
+      __syncthreads();
+      if (half == 0) {   // scores: A[i][k=m] = Ps[i][m], B[k=m][n=j] = Ss[j][m]
+        const float* ap = m.Ps + ((w4 >> 1) * 16 + (lane & 15)) * lds + (lane >> 4);
+        const float* bp = m.Ss + ((w4 & 1) * 16 + (lane & 15)) * lds + (lane >> 4);
+        sc = mfma_chain(ap, 1, bp, 1, MB, sc);
+      } else {
+        const float* ap = m.As + (lane >> 4) * lds + (w4 >> 1) * 16 + (lane & 15);     // A[j][k=i] = As[i][j]
+        const float* bp = m.Ps + (lane >> 4) * lds + (w4 & 1) * 16 + (lane & 15);      // B[k=i][n=m] = Ps[i][m]
+        ds = mfma_chain(ap, lds, bp, lds, TR, ds);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int row = (w >> 1) * 16 + 4 * (lane >> 4) + r;
+          const int row = (w4 >> 1) * 16 + 4 * (lane >> 4) + r;
           m.dEs[row * lds + f] = fv[r] * ds[r];
         }
       }
       __syncthreads();
-      {   // scores: A[i][k=m] = Ps[i][m], B[k=m][n=j] = Ss[j][m]
-        const float* ap = m.Ps + ((w >> 1) * 16 + (lane & 15)) * lds + (lane >> 4);
-        const float* bp = m.Ss + ((w & 1) * 16 + (lane & 15)) * lds + (lane >> 4);
-        sc = mfma_chain(ap, 1, bp, 1, MB, sc);
-      }
 #pragma unroll
-      for (int tl = 0; tl < ACC_PER_WAVE; ++tl) {
-        const int t = w + 4 * tl;
+      for (int tl = 0; tl < ACC_PER_WAVE_C; ++tl) {
+        const int t = w + 8 * tl;
         if (t < ntiles) {
           const int rt = t & 1, vt = t >> 1;
           {   // dV1 += S R_next: A[j][k=m] = Ss[j][m], B[k=m][n=v] = Rs[m][v]
@@ -1402,31 +1448,32 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_causal_k(GenSide qs, GenSide ks,
         }
       }
 #pragma unroll
-      for (int tl = 0; tl < 4; ++tl) {
-        const int t = w + 4 * tl;
+      for (int tl = 0; tl < 2; ++tl) {
+        const int t = w + 8 * tl;
         if (t < ngt) {
           const int rt = t & 1, ct = t >> 1;
           const float* ap = m.dEs + (rt * 16 + (lane & 15)) * lds + (lane >> 4);
-          const float* bp = m.Ws + (lane >> 4) * ld + min(ct * 16 + (lane & 15), dpad - 1);   // (columns past dpad are dropped below)
+          const float* bp = m.Ws2 + (lane >> 4) * ld + min(ct * 16 + (lane & 15), dpad - 1);   // (columns past dpad are dropped below)
           acc_g[tl] = mfma_chain(ap, 1, bp, ld, MB, acc_g[tl]);
         }
       }
-      {
+      if (half == 0) {
         const int row = threadIdx.x >> 3, part = threadIdx.x & 7;
 #pragma unroll
         for (int q = 0; q < 4; ++q) rs_part += m.dEs[row * lds + part * 4 + q];
       }
     }
     // B = tril(P S^T); dV1 += B^T G1: A[j][k=i] = Bs[i][j], B[k=i][n=v] = Gs[i][v]
+    if (half == 0)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int i = (w >> 1) * 16 + 4 * (lane >> 4) + r, j = (w & 1) * 16 + (lane & 15);
+      const int i = (w4 >> 1) * 16 + 4 * (lane >> 4) + r, j = (w4 & 1) * 16 + (lane & 15);
       m.Bs[i * lds + j] = (j <= i) ? sc[r] : 0.f;
     }
     __syncthreads();
 #pragma unroll
-    for (int tl = 0; tl < ACC_PER_WAVE; ++tl) {
-      const int t = w + 4 * tl;
+    for (int tl = 0; tl < ACC_PER_WAVE_C; ++tl) {
+      const int t = w + 8 * tl;
       if (t < ntiles) {
         const int rt = t & 1, vt = t >> 1;
         const float* ap = m.Bs + (lane >> 4) * lds + rt * 16 + (lane & 15);
@@ -1438,8 +1485,8 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_causal_k(GenSide qs, GenSide ks,
     float* Gd = m.Ws;
     float* Os = m.Ts;
 #pragma unroll
-    for (int tl = 0; tl < 4; ++tl) {
-      const int t = w + 4 * tl;
+    for (int tl = 0; tl < 2; ++tl) {
+      const int t = w + 8 * tl;
       if (t < ngt) {
         const int rt = t & 1, ct = t >> 1, col = ct * 16 + (lane & 15);
         if (col < dpad) {
@@ -1449,8 +1496,8 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_causal_k(GenSide qs, GenSide ks,
       }
     }
 #pragma unroll
-    for (int tl = 0; tl < ACC_PER_WAVE; ++tl) {
-      const int t = w + 4 * tl;
+    for (int tl = 0; tl < ACC_PER_WAVE_C; ++tl) {
+      const int t = w + 8 * tl;
       if (t < ntiles) {
         const int rt = t & 1, vt = t >> 1;
 #pragma unroll
@@ -1460,10 +1507,10 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_causal_k(GenSide qs, GenSide ks,
     rs_part += __shfl_xor(rs_part, 1);
     rs_part += __shfl_xor(rs_part, 2);
     rs_part += __shfl_xor(rs_part, 4);
-    if ((threadIdx.x & 7) == 0) m.rsum[threadIdx.x >> 3] = rs_part;
+    if (half == 0 && (threadIdx.x & 7) == 0) m.rsum[threadIdx.x >> 3] = rs_part;
     __syncthreads();
     bwd_store_grad(dK, b * dK.sb + h * dK.sh, row0, row_end, d, ld, Gd, m.rsum, m.Ks, Cmat2, ks.scale, 0.f);
-    for (int idx = threadIdx.x; idx < TR * nv; idx += NT) {
+    for (int idx = threadIdx.x; idx < TR * nv; idx += NTC) {
       const int r = idx / nv, cc = idx - r * nv;
       if (row0 + r < row_end) store_elem(dV, b * dV.sb + h * dV.sh + (long long)(row0 + r) * dV.sl + cc, Os[r * ldv + cc]);
     }
@@ -1486,7 +1533,7 @@ size_t gen_lds_apply(int d, int ldt) {
 }
 size_t gen_lds_causal(int d, int ldt) {
   const int ld = ((d + 3) & ~3) + 1;
-  return ((size_t)(2 * TR + MB) * ld + (size_t)(TR + MB) * (ldt + 1) + (size_t)3 * TR * (MB + 1) + MB + 2 * TR) * 4;
+  return ((size_t)2 * (TR + MB) * ld + (size_t)(TR + MB) * (ldt + 1) + (size_t)3 * TR * (MB + 1) + 2 * MB + 2 * TR) * 4;
 }
 size_t gen_lds_stats(int d) { return (size_t)TR * (((d + 15) & ~15) + 1) * 4; }
 
@@ -1593,7 +1640,7 @@ int launch_gen_bwd_side(const GenSide& sd, int side, const TensorDev& A, int a_c
 
 size_t gen_lds_bwd_causal(int d, int ldt) {
   const int ld = ((d + 3) & ~3) + 1;
-  return ((size_t)(2 * TR + MB) * ld + (size_t)(2 * TR + MB) * (ldt + 1) + (size_t)5 * TR * (MB + 1) + MB + 3 * TR) * 4;
+  return ((size_t)2 * (TR + MB) * ld + (size_t)(2 * TR + MB) * (ldt + 1) + (size_t)5 * TR * (MB + 1) + 2 * MB + 3 * TR) * 4;
 }
 
 int launch_gen_bwd_causal(const GenSide& qs, const GenSide& ks, const TensorDev& V, const float* ghat, int L, int BH, int H,
@@ -1603,10 +1650,10 @@ int launch_gen_bwd_causal(const GenSide& qs, const GenSide& ks, const TensorDev&
   const size_t lds = gen_lds_bwd_causal(d, ldt);
   if (int rc = set_lds((const void*)k_gen_bwd_causal_q, lds)) return rc;
   if (int rc = set_lds((const void*)k_gen_bwd_causal_k, lds)) return rc;
-  hipLaunchKernelGGL(k_gen_bwd_causal_q, dim3(nseg, BH), dim3(NT), lds, st, qs, ks, V, ghat, L, H, M, d, nv, ldt,
+  hipLaunchKernelGGL(k_gen_bwd_causal_q, dim3(nseg, BH), dim3(NTC), lds, st, qs, ks, V, ghat, L, H, M, d, nv, ldt,
                      rows_per_seg, nseg, kmax_u, row_shift, Tstate, dQ);
   FS_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_gen_bwd_causal_k, dim3(nseg, BH), dim3(NT), lds, st, qs, ks, V, ghat, L, H, M, d, nv, ldt,
+  hipLaunchKernelGGL(k_gen_bwd_causal_k, dim3(nseg, BH), dim3(NTC), lds, st, qs, ks, V, ghat, L, H, M, d, nv, ldt,
                      rows_per_seg, nseg, kmax_u, row_shift, Rstate, dK, dV);
   FS_LAUNCH_CHECK();
   return 0;
@@ -1617,7 +1664,7 @@ int launch_gen_causal(const GenSide& qs, const GenSide& ks, const TensorDev& V, 
                       const TensorDev& Y, float* den_out, float* shift_out, hipStream_t st, unsigned* flushed) {
   const size_t lds = gen_lds_causal(d, ldt);
   if (int rc = set_lds((const void*)k_gen_causal, lds)) return rc;
-  hipLaunchKernelGGL(k_gen_causal, dim3(nseg, BH), dim3(NT), lds, st, qs, ks, V, L, H, M, d, nv, ldt, rows_per_seg,
+  hipLaunchKernelGGL(k_gen_causal, dim3(nseg, BH), dim3(NTC), lds, st, qs, ks, V, L, H, M, d, nv, ldt, rows_per_seg,
                      nseg, kmax_u, Tstate, Y, den_out, shift_out, flushed);
   FS_LAUNCH_CHECK();
   return 0;

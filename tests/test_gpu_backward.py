@@ -585,3 +585,34 @@ def test_backward_error_paths(fs):
     with pytest.raises(fs.FavorSharpError) as err:          # causal needs as many queries as keys
         fs.attention_backward(th, Q, K, K, Q, 1.0, Om, causal=True)
     assert err.value.status in (2, 4)       # unsupported (the workspace query already says so with 0 bytes)
+
+
+@pytest.mark.parametrize("variant", ["sderf", "saderf"])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("L,d,dv,M", [
+    (1, 8, 8, 1),              # one row, one feature: everything but element 0 of each tile is padding
+    (33, 32, 16, 32),          # one row past a tile; exactly one block of features (the second of a pair is absent)
+    (65, 40, 128, 33),         # one feature past a block; the widest values (a state of 144 columns)
+    (96, 128, 96, 100),        # the widest rows; values whose normaliser column opens a new tile of 16; three of four blocks full
+])
+def test_backward_causal_general_path_at_tile_edges(fs, L, d, dv, M, dtype, variant):
+    rng = np.random.default_rng(7 * L + d)
+    B, H = 1, 2
+    Q, K = ((0.6 * rng.standard_normal((B, H, L, d))).astype(np.float32) for _ in range(2))
+    V, dY = (rng.standard_normal((B, H, L, dv)).astype(np.float32) for _ in range(2))
+    Om = rng.standard_normal((H, M, d)).astype(np.float32)
+    if dtype == "bf16":
+        Q, K, V, dY = (synth.round_to_bf16(x) for x in (Q, K, V, dY))
+    # parameters are fitted to more rows than the call has, so that their statistics have full rank
+    fit_rows = np.concatenate([Q, (0.6 * rng.standard_normal((B, H, 4 * d, d))).astype(np.float32)], axis=2)
+    import torch
+    scale = d ** -0.25
+    theta = _theta_block(variant, fit_rows, fit_rows[:, :, ::-1], scale)
+    grads = fs.attention_backward(torch.from_numpy(theta).cuda(), *(util.to_device(x, dtype) for x in (Q, K, V, dY)), scale,
+                                  torch.from_numpy(Om).cuda(), causal=True, grad_dtype=torch.float32)
+    grads = [util.to_host(g) for g in grads]
+    for h in range(H):
+        th = util.oracle_theta_from_vec(theta[h], d)
+        ref = orc.attention_backward(th, Om[h], Q[0, h], K[0, h], V[0, h], dY[0, h], scale, True)
+        # the bar of this file (3e-4); gradients that are zero by construction (one row) against the scale of dY
+        _assert_grads([g[0, h] for g in grads], ref, 3e-4, (h, L, d, dv, M), 1e-3 * float(np.linalg.norm(dY[0, h])))
