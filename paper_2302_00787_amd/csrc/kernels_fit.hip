@@ -360,7 +360,7 @@ __device__ __forceinline__ void decompose(double* g, double* v, int n, int k, bo
 // 64: k_fit_device 686 -> 108 us; 16 matrices of 128: 7290 -> 325 us).
 // ---------------------------------------------------------------------------------------------------
 
-// Gap between neighbouring eigenvalues (in units of the trace) below which the vectors of `eig_tridiagonal` are not
+// Gap between neighbouring eigenvalues (in units of the norm) below which the vectors of `eig_tridiagonal` are not
 // used: their inner product is about 1e-18 / gap (measured on matrices of 2 .. 128), 1e-8 here, below the rounding of
 // the fp32 results.
 constexpr double kMinGap = 1e-10;
@@ -407,6 +407,10 @@ __device__ __forceinline__ double sum64(double v) {        // over the wave
   v = add_rows16(v, v);
   return add_halves32(v, v);
 }
+__device__ __forceinline__ double max64(double v) {        // over the wave
+  for (int m = 1; m < 64; m <<= 1) v = fmax(v, __shfl_xor(v, m, 64));
+  return v;
+}
 
 // LDS of `eig_tridiagonal` (doubles; NP = 32 RJ): reflectors [NP][NP], two vectors of NP, (diagonal, e^2) pairs, e,
 // eigenvalues, partial norms, partial minima with their rows (one per thread); for NP = 64 also the multipliers of the
@@ -414,13 +418,14 @@ __device__ __forceinline__ double sum64(double v) {        // over the wave
 constexpr size_t tri_lds_doubles(int NP) { return (size_t)(NP == 64 ? 3 : 1) * NP * NP + 8 * (size_t)NP + FIT_NT + FIT_NT / 2; }
 
 // a: the matrix, entry (ti + 4 RJ ii, tj + 32 jj) in a[ii][jj] of thread (ti = t / 32, tj = t % 32) < 128 RJ, zero
-// outside n x n (destroyed).  `scale`: its trace (positive semidefinite: no eigenvalue is larger).  On success the
-// eigenvalues go to slot k of the shared block with their order and signs (as rank_columns leaves them) and eigenvector
+// outside n x n (destroyed).  Any symmetric matrix: the statistics' matrices are positive semidefinite only up to the
+// rounding of their fp32 sums, and where large means cancel that rounding is all there is.  On success the eigenvalues go to slot k of the shared block with their order and signs (as rank_columns leaves them) and eigenvector
 // j to column j of v (global, column-major with stride n).  scr: 2 n n doubles of global scratch (NP = 128).  Returns
-// false, with nothing written outside LDS and scr, when two eigenvalues are closer than kMinGap.
+// false, with nothing written outside LDS and scr, when two eigenvalues are closer than kMinGap or the matrix is zero or
+// not finite.
 template <int RJ>
-__device__ __forceinline__ bool eig_tridiagonal(double (&a)[8][RJ], int n, double scale, double* v, double* scr, int k_slot,
-                                                FitShared& sh, double* lds) {
+__device__ __forceinline__ bool eig_tridiagonal(double (&a)[8][RJ], int n, double* v, double* scr, int k_slot, FitShared& sh,
+                                                double* lds) {
   constexpr int NP = 32 * RJ, RI = 8, HT = 128 * RJ, RS = 4 * RJ;      // HT threads hold the matrix, rows RS apart
   auto IB = [](int jc) constexpr { return 32 * jc / RS; };             // first register row of column block jc
   constexpr bool kInLds = NP == 64;
@@ -537,8 +542,20 @@ __device__ __forceinline__ bool eig_tridiagonal(double (&a)[8][RJ], int n, doubl
       if (i == n - 1 && j == n - 2) es[n - 2] = a[ii][jj];
     }
   __syncthreads();
-  // in units of the trace; off-diagonal entries at least 1e-17 (far below the rounding of the reduction), so that no
-  // Sturm sequence and no factorisation meets an exact split; entries behind the matrix keep the sign of a sequence
+  // in units of the largest Gershgorin radius about zero (every wave finds it for itself), which no eigenvalue exceeds
+  // in size; off-diagonal entries at least 1e-17 (far below the rounding of the reduction), so that no Sturm sequence and
+  // no factorisation meets an exact split; entries behind the matrix keep the sign of a sequence
+  double scale = 0.0;
+#pragma unroll
+  for (int q = 0; q < NP / 64; ++q) {
+    const int i = lane + 64 * q;
+    if (i < n) {
+      const double r = fabs(de[i].x) + (i > 0 ? fabs(es[i - 1]) : 0.0) + (i < n - 1 ? fabs(es[i]) : 0.0);
+      scale = fmax(scale, r < 1e120 ? r : 1e300);
+    }
+  }
+  scale = max64(scale);
+  if (!(scale > 1e-120 && scale < 1e120)) return false;
   {
     const double inv = 1.0 / scale;
     double dd = 2.0, e2 = 1e-34;
@@ -561,7 +578,7 @@ __device__ __forceinline__ bool eig_tridiagonal(double (&a)[8][RJ], int n, doubl
     constexpr int S = 256 / NP;
     const int j = t / S, sec = t % S;
     const double frac = (double)(sec + 1) / (double)(S + 1);
-    double lo = -1e-9, hi = 1.0 + 1e-9;
+    double lo = -1.0 - 1e-9, hi = 1.0 + 1e-9;
     const int steps = S == 4 ? 24 : 35;              // 5^24, 3^35 > 2^55
     for (int it = 0; it < steps; ++it) {
       const double x = fma(hi - lo, frac, lo);
@@ -774,13 +791,13 @@ __device__ __forceinline__ bool eig_tridiagonal(double (&a)[8][RJ], int n, doubl
   return true;
 }
 
-// Eigen-decomposition of the symmetric positive semidefinite matrix entry(i, j) with trace `tr`: into slot k and v as
-// above; g: n x n doubles (the Jacobi form's matrix), scr: 2 n n doubles, both global.
+// Eigen-decomposition of the symmetric matrix entry(i, j): into slot k and v as above; g: n x n doubles (the Jacobi
+// form's matrix), scr: 2 n n doubles, both global.
 template <int RJ, class Entry>
-__device__ __forceinline__ void decompose_symmetric(Entry entry, double tr, double* g, double* v, double* scr, int n, int k,
-                                                    FitShared& sh, double* lds) {
+__device__ __forceinline__ void decompose_symmetric(Entry entry, double* g, double* v, double* scr, int n, int k, FitShared& sh,
+                                                    double* lds) {
   const int t = threadIdx.x, ti = t >> 5, tj = t & 31;
-  if (n > 1 && tr > 1e-280 && tr < 1e280) {
+  if (n > 1) {
     double a[8][RJ];
 #pragma unroll
     for (int ii = 0; ii < 8; ++ii)
@@ -789,7 +806,7 @@ __device__ __forceinline__ void decompose_symmetric(Entry entry, double tr, doub
         const int i = ti + 4 * RJ * ii, j = tj + 32 * jj;
         a[ii][jj] = t < 128 * RJ && i < n && j < n ? entry(i, j) : 0.0;
       }
-    if (eig_tridiagonal<RJ>(a, n, tr, v, scr, k, sh, lds)) return;
+    if (eig_tridiagonal<RJ>(a, n, v, scr, k, sh, lds)) return;
   }
   for (int e = t; e < n * n; e += FIT_NT) g[e] = entry(e / n, e % n);
   __syncthreads();
@@ -883,7 +900,7 @@ __global__ void __launch_bounds__(FIT_NT) k_fit_device(int variant, int d, const
     decompose_symmetric<RJ>([=](int r, int c) {
       const size_t e = (size_t)r * d + c;
       return M1[e] + mu4[r] * mu5[c] + mu5[r] * mu4[c] + M2[e];
-    }, tr1 + tr2 + 2.0 * dot, N, V, w + 4 * (size_t)nn, n, 0, sh, lds);
+    }, N, V, w + 4 * (size_t)nn, n, 0, sh, lds);
     // row scales: sqrt(1 - 4a), with the sign of the eigenvector
     if (t < d) sh.red_row[t] = sqrt(1.0 - 4.0 * a_star(fmax(sh.nrm[0][t], 0.0))) * sh.sgn[0][t];
     __syncthreads();
@@ -921,10 +938,10 @@ __global__ void __launch_bounds__(FIT_NT) k_fit_device(int variant, int d, const
   double* b1 = w + 5 * (size_t)nn;     // row-major
   double* b2 = w + 6 * (size_t)nn;
   // (Z, b1 and b2 are not yet in use: scratch)
-  decompose_symmetric<RJ>([=](int r, int c) { return M1[(size_t)r * d + c] + (r == c ? ridge : 0.0); }, tr1 + d * ridge, G1,
-                          V1, Z, n, 0, sh, lds);
-  decompose_symmetric<RJ>([=](int r, int c) { return M2[(size_t)r * d + c] + (r == c ? ridge : 0.0); }, tr2 + d * ridge, G2,
-                          V2, Z, n, 1, sh, lds);
+  decompose_symmetric<RJ>([=](int r, int c) { return M1[(size_t)r * d + c] + (r == c ? ridge : 0.0); }, G1, V1, Z, n, 0,
+                          sh, lds);
+  decompose_symmetric<RJ>([=](int r, int c) { return M2[(size_t)r * d + c] + (r == c ? ridge : 0.0); }, G2, V2, Z, n, 1,
+                          sh, lds);
   {
     const double l1max = sh.nrm[0][sh.ord[0][0]], l1min = sh.nrm[0][sh.ord[0][d - 1]];
     const double l2max = sh.nrm[1][sh.ord[1][0]], l2min = sh.nrm[1][sh.ord[1][d - 1]];

@@ -356,6 +356,40 @@ def test_device_fit_eigensolver_sizes(fs, d, spectrum):
     np.testing.assert_allclose(got.B1 @ got.B1.T, np.diag(1.0 - 4.0 * got.A), atol=2e-6)   # orthogonal rows, fp32 storage
 
 
+def _row_defect(theta, d):
+    """Largest |cosine| between two rows of B1 (SDERF: scaled eigenvectors, so rows must be orthogonal)."""
+    B = util.oracle_theta_from_vec(theta, d).B1
+    R = B / np.linalg.norm(B, axis=1, keepdims=True)
+    return np.abs(R @ R.T - np.eye(d)).max()
+
+
+@pytest.mark.parametrize("kind", ["opposite means", "few rows", "rank d-1", "rank d-2", "rank d-4"])
+@pytest.mark.parametrize("d", [16, 32, 64, 128])
+def test_device_fit_of_statistics_with_negative_eigenvalues(fs, d, kind):
+    """N = E(x + y)(x + y)^T is positive semidefinite only up to the rounding of its fp32 sums.  Where it is singular
+    (fewer rows than dimensions, rows in a subspace), or where large opposite means cancel, eigenvalues come out
+    negative; the rows of B must be orthogonal all the same.  Twelve draws, one per head.  fp32 storage of two rows
+    leaves a cosine of up to 2 * 2^-24 = 1.2e-7."""
+    import torch
+    rng = np.random.default_rng(1200 + d)
+    H, L = 12, max(2, d // 2 - 1) if kind == "few rows" else 1024
+    Q, K = rng.standard_normal((2, 1, H, L, d))
+    if kind == "opposite means":       # on the hyperplane of zero sum, means of norm 100
+        m = rng.standard_normal((H, 1, d))
+        m -= m.mean(-1, keepdims=True)
+        m *= 100.0 / np.linalg.norm(m, axis=-1, keepdims=True)
+        Q, K = ((x * 0.5 ** (np.arange(d) / 8)) for x in (Q, K))
+        Q, K = Q - Q.mean(-1, keepdims=True) + m, K - K.mean(-1, keepdims=True) - m
+    elif kind.startswith("rank"):
+        r = d + int(kind[6:])
+        P = np.linalg.qr(rng.standard_normal((H, d, d)))[0][:, :r]
+        Q, K = Q[..., :r] @ P, K[..., :r] @ P
+    Qd, Kd = (torch.from_numpy(x.astype(np.float32)).cuda() for x in (Q, K))
+    theta = _fit(fs, "device", "sderf", Qd, Kd, d ** -0.25, H)
+    worst = max(_row_defect(theta[h], d) for h in range(H))
+    assert worst <= 2.5e-7, worst
+
+
 @pytest.mark.parametrize("entry", ["host", "device"])
 @pytest.mark.parametrize("d", [64, 128])
 def test_fit_on_bf16_rows_scanned_by_the_mfma_statistics_kernels(fs, d, entry):
