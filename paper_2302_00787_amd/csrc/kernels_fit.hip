@@ -361,9 +361,10 @@ __device__ __forceinline__ void decompose(double* g, double* v, int n, int k, bo
 // ---------------------------------------------------------------------------------------------------
 
 // Gap between neighbouring eigenvalues (in units of the norm) below which the vectors of `eig_tridiagonal` are not
-// used: their inner product is about 1e-18 / gap (measured on matrices of 2 .. 128), 1e-8 here, below the rounding of
-// the fp32 results.
-constexpr double kMinGap = 1e-10;
+// used.  The eigenvalues carry an ulp or two of the norm, so the inner product of two vectors is about that over their
+// gap: up to 2.5e-16 / gap on matrices of 2 .. 128 with pairs 1e-10 .. 1e-7 apart.  2.5e-8 at this limit, below the
+// rounding of the fp32 results (6e-8); at a limit of 1e-10 it was up to 2e-6.
+constexpr double kMinGap = 1e-8;
 
 __device__ __forceinline__ double rcp64(double x) {        // hardware estimate and two Newton steps
   double r = __builtin_amdgcn_rcp(x);

@@ -390,6 +390,29 @@ def test_device_fit_of_statistics_with_negative_eigenvalues(fs, d, kind):
     assert worst <= 2.5e-7, worst
 
 
+@pytest.mark.parametrize("rel", [1e-9, 4e-9])
+@pytest.mark.parametrize("d", [2, 4, 8, 16])
+def test_device_fit_of_statistics_with_nearly_equal_eigenvalues(fs, d, rel):
+    """Pairs of eigenvalues about `rel` of the largest one apart.  The first 32 rows, small whole numbers
+    ([3u, 4u] and [-4u, 3u]), give every eigenvalue twice without any rounding; the rows behind them, a statistics chunk
+    of their own, split the pairs.  Rows of B orthogonal: fp32 storage leaves 2 * 2^-24 = 1.2e-7, the eigensolver 2.5e-8."""
+    import torch
+    rng = np.random.default_rng(1300 + d)
+    H = 16
+    u = rng.integers(-6, 7, (H, 8, d // 2)).astype(np.float64)
+    a, b = np.concatenate([3 * u, 4 * u], -1), np.concatenate([-4 * u, 3 * u], -1)
+    main = np.concatenate([a, -a, b, -b], 1)
+    top = np.linalg.eigvalsh(np.swapaxes(main, 1, 2) @ main)[:, -1]
+    w = rng.standard_normal((H, 1, d))
+    w *= (np.sqrt(rel * top) / np.linalg.norm(w[:, 0], axis=-1))[:, None, None]
+    X = np.zeros((1, H, 64, (d + 3) // 4 * 4), np.float32)
+    X[0, :, :, :d] = np.concatenate([main, w, -w, np.zeros((H, 30, d))], 1)
+    Xd = torch.from_numpy(X).cuda()[..., :d]
+    theta = _fit(fs, "device", "sderf", Xd, Xd, 1.0, H)
+    worst = max(_row_defect(theta[h], d) for h in range(H))
+    assert worst <= 1.5e-7, worst
+
+
 @pytest.mark.parametrize("entry", ["host", "device"])
 @pytest.mark.parametrize("d", [64, 128])
 def test_fit_on_bf16_rows_scanned_by_the_mfma_statistics_kernels(fs, d, entry):
