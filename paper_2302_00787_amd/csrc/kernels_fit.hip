@@ -285,6 +285,22 @@ __device__ __forceinline__ void jacobi_any(double* a, double* v, int n, int lda,
   }
 }
 
+// Place of v[t] in the descending order of v[0 .. n), ties by index.  The bits are compared, not the values: a total
+// order, so that the places are a permutation (they become column indices) whatever the statistics were, NaN included.
+__device__ __forceinline__ int descending_place(const double* v, int n, int t) {
+  auto key = [](double x) {
+    const long long b = __double_as_longlong(x + 0.0);       // (-0 counts as 0)
+    return b < 0 ? b ^ 0x7fffffffffffffffll : b;
+  };
+  const long long mine = key(v[t]);
+  int place = 0;
+  for (int i = 0; i < n; ++i) {
+    const long long k = key(v[i]);
+    place += (k > mine || (k == mine && i < t)) ? 1 : 0;
+  }
+  return place;
+}
+
 // Column norms (one-sided iteration) or diagonal entries (two-sided), their non-ascending order and (with v) the
 // eigenvector signs into slot k of the shared block.
 __device__ __forceinline__ void rank_columns(const double* wg, const double* wv, int n, int ldg, int ldv, int k, bool symmetric, FitShared& sh) {
@@ -305,12 +321,7 @@ __device__ __forceinline__ void rank_columns(const double* wg, const double* wv,
     }
   }
   __syncthreads();
-  if (t < n) {
-    int rank = 0;
-    const double mine = sh.nrm[k][t];
-    for (int i = 0; i < n; ++i) rank += (sh.nrm[k][i] > mine || (sh.nrm[k][i] == mine && i < t)) ? 1 : 0;
-    sh.ord[k][rank] = t;
-  }
+  if (t < n) sh.ord[k][descending_place(sh.nrm[k], n, t)] = t;
   __syncthreads();
 }
 

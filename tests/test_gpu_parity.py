@@ -413,6 +413,26 @@ def test_device_fit_of_statistics_with_nearly_equal_eigenvalues(fs, d, rel):
     assert worst <= 1.5e-7, worst
 
 
+@pytest.mark.parametrize("variant", ["sderf", "aderf"])
+@pytest.mark.parametrize("d", [16, 64, 128])
+def test_device_fit_with_a_nan_in_one_head(fs, d, variant):
+    """Statistics that are not finite stay in their own group: eigenvalues that compare with nothing still get places
+    inside the matrix, the other heads' parameters are the same bits as without the NaN, ADERF reports the head."""
+    import torch
+    rng = np.random.default_rng(1400 + d)
+    Q, K = (torch.from_numpy(rng.standard_normal((1, 3, 600, d)).astype(np.float32)).cuda() for _ in range(2))
+    clean, _ = fs.fit_params_device(variant, Q, K, d ** -0.25, groups=3)
+    for rows in (slice(5, 6), slice(0, 600)):
+        Qn = Q.clone()
+        Qn[0, 1, rows, : 1 if rows.start else d] = float("nan")
+        theta, status = fs.fit_params_device(variant, Qn, K, d ** -0.25, groups=3)
+        st = util.to_host(status).tolist()
+        assert st[0] == st[2] == 0
+        if variant == "aderf":
+            assert st[1] == 3
+        assert torch.equal(theta[0], clean[0]) and torch.equal(theta[2], clean[2])
+
+
 @pytest.mark.parametrize("entry", ["host", "device"])
 @pytest.mark.parametrize("d", [64, 128])
 def test_fit_on_bf16_rows_scanned_by_the_mfma_statistics_kernels(fs, d, entry):
