@@ -7,15 +7,15 @@
 // The symmetric eigenproblems (M1, M2, and N = M1 + mu4 mu5^T + mu5 mu4^T + M2) are reduced to tridiagonal form by
 // Householder reflections with the matrix in registers; eigenvalues by bisection on Sturm sequences, all of them side
 // by side; eigenvectors of the tridiagonal matrix from twisted factorisations (Fernando; Parlett and Dhillon), one lane
-// per vector; the reflections are then applied to them (`eig_tridiagonal`).  Matrices with (nearly) equal eigenvalues,
-// for which such vectors are not orthogonal by themselves, are decomposed by the two-sided Jacobi iteration instead.
+// per vector; the reflections are then applied to them (`eig_tridiagonal`).  Where eigenvalues (nearly) coincide such
+// vectors are not orthogonal by themselves: there the tridiagonal matrix is finished by implicit QR steps instead.
 // The singular value problem of the ADERF matrix Lambda1^(1/2) Q1^T Q2 Lambda2^(1/2) is solved by the one-sided
-// (Hestenes) iteration on its columns, whose normalised columns are the left singular vectors.  Both iterations use
-// the round-robin ordering: a round rotates d/2 disjoint index pairs at once, a few lanes per pair, one or two barriers
-// per round.  Their matrix lives in LDS, and so do the accumulated rotations when both fit (d <= 96).
+// (Hestenes) Jacobi iteration on its columns, whose normalised columns are the left singular vectors, in the
+// round-robin ordering: a round rotates d/2 disjoint index pairs at once, a few lanes per pair, one barrier per round,
+// the matrix in LDS.
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
+#include <type_traits>
 
 #include "kernels.h"
 
@@ -52,6 +52,7 @@ struct FitShared {
   double red_row[FIT_DMAX];  // per-row scale factors of the results
   double red[8];             // scalars shared by the workgroup
   int twist[FIT_DMAX];
+  int row[FIT_DMAX];         // rows of the matrix in the order of the eigenproblem: those with off-diagonal entries first
   int flag;
 };
 
@@ -75,37 +76,35 @@ __device__ __forceinline__ double rotation_cosine(double t) {
   return c;
 }
 
-// Batched access to a pair of strided vectors for the sizes where every lane of a pair handles exactly NI elements
+// Batched access to a pair of columns for the sizes where every lane of a pair handles exactly NI elements
 // (n = NI x lanes per pair: 32, 64, 128 with 512 threads).  Every request is issued before the first use, so a pair
 // costs one memory latency, not one per element as in the general loops (whose stores may alias the next loads).
 template <int NI>
-__device__ __forceinline__ void fetch_pair(const double* xp, const double* xq, int stride, int r0, int tpp,
-                                           double (&x)[NI], double (&y)[NI]) {
+__device__ __forceinline__ void fetch_pair(const double* xp, const double* xq, int r0, int tpp, double (&x)[NI], double (&y)[NI]) {
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
-    const size_t r = (size_t)(r0 + i * tpp) * stride;
+    const int r = r0 + i * tpp;
     x[i] = xp[r];
     y[i] = xq[r];
   }
 }
 // (xp, xq) <- (c xp - s xq, s xp + c xq) on those elements.
 template <int NI>
-__device__ __forceinline__ void store_rotated(double* xp, double* xq, int stride, int r0, int tpp, const double (&x)[NI],
-                                              const double (&y)[NI], double c, double s) {
+__device__ __forceinline__ void store_rotated(double* xp, double* xq, int r0, int tpp, const double (&x)[NI], const double (&y)[NI],
+                                              double c, double s) {
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
-    const size_t r = (size_t)(r0 + i * tpp) * stride;
+    const int r = r0 + i * tpp;
     xp[r] = c * x[i] - s * y[i];
     xq[r] = s * x[i] + c * y[i];
   }
 }
 
-// One-sided Jacobi on the columns of g (n x n, column c at g + c * ldg): g <- g R with mutually orthogonal columns,
-// v <- v R if v != nullptr (column c at v + c * ldv).  All FIT_NT threads must call; n <= FIT_DMAX.  The function is
-// inlined at each call site so that the address spaces of g and v (LDS or global) are known to the compiler.
+// One-sided Jacobi on the columns of g (n x n, column c at g + c * ldg): g <- g R with mutually orthogonal columns.
+// All FIT_NT threads must call; n <= FIT_DMAX.  Inlined at each call site so that the compiler knows g to be in LDS.
 // NI > 0: n = NI x (lanes per pair), batched accesses; NI = 0: any n.
 template <int NI>
-__device__ __forceinline__ void jacobi_columns(double* g, double* v, int n, int ldg, int ldv, FitShared& sh) {
+__device__ __forceinline__ void jacobi_columns(double* g, int n, int ldg, FitShared& sh) {
   const int np = (n + 1) / 2;        // pairs per round
   const int m = 2 * np;              // players of the tournament (player n is a bye when n is odd)
   int tpp = 64;                      // lanes per pair
@@ -129,7 +128,7 @@ __device__ __forceinline__ void jacobi_columns(double* g, double* v, int n, int 
           double al = 0.0, be = 0.0, ga = 0.0;
           double x[NA], y[NA];
           if constexpr (NI > 0) {
-            fetch_pair<NA>(gp, gq, 1, r0, tpp, x, y);
+            fetch_pair<NA>(gp, gq, r0, tpp, x, y);
 #pragma unroll
             for (int i = 0; i < NA; ++i) { al += x[i] * x[i]; be += y[i] * y[i]; ga += x[i] * y[i]; }
           } else {
@@ -145,24 +144,12 @@ __device__ __forceinline__ void jacobi_columns(double* g, double* v, int n, int 
             const double tn = (double)tn32;
             const double c = rotation_cosine(tn), s = c * tn;
             if constexpr (NI > 0) {
-              double vx[NA], vy[NA];
-              if (v != nullptr) fetch_pair<NA>(v + (size_t)p * ldv, v + (size_t)q * ldv, 1, r0, tpp, vx, vy);
-              store_rotated<NA>(gp, gq, 1, r0, tpp, x, y, c, s);
-              if (v != nullptr) store_rotated<NA>(v + (size_t)p * ldv, v + (size_t)q * ldv, 1, r0, tpp, vx, vy, c, s);
+              store_rotated<NA>(gp, gq, r0, tpp, x, y, c, s);
             } else {
               for (int r = r0; r < n; r += tpp) {
                 const double a = gp[r], b = gq[r];
                 gp[r] = c * a - s * b;
                 gq[r] = s * a + c * b;
-              }
-              if (v != nullptr) {
-                double* vp = v + (size_t)p * ldv;
-                double* vq = v + (size_t)q * ldv;
-                for (int r = r0; r < n; r += tpp) {
-                  const double a = vp[r], b = vq[r];
-                  vp[r] = c * a - s * b;
-                  vq[r] = s * a + c * b;
-                }
               }
             }
             if (r0 == 0 && ga * ga > kJacobiAgain * kJacobiAgain * al * be) sh.flag = 1;
@@ -176,112 +163,6 @@ __device__ __forceinline__ void jacobi_columns(double* g, double* v, int n, int 
     const int again = sh.flag;
     __syncthreads();
     if (!again) break;
-  }
-}
-
-// Two-sided Jacobi for a symmetric matrix a (n x n in column-major with stride lda): a <- J^T a J until the
-// off-diagonal part vanishes, v <- v J.  The rotation of pair (p, q) is fixed by the 2 x 2 block (a_pp, a_pq, a_qq),
-// which no other pair of the round touches; the round applies all column rotations, a barrier, all row rotations.
-// No inner products and no cross-lane sums are needed, and the sweep count follows the conditioning of a itself
-// (the one-sided iteration on a symmetric matrix works on its square).  `scale`: largest |a_ii| at the start.
-// NI as above; with NI > 0 the columns of a and of v are requested together with the 2 x 2 block, before the
-// rotation is known, so that a round is a chain of two memory latencies and two barriers.
-template <int NI>
-__device__ __forceinline__ void jacobi_symmetric(double* a, double* v, int n, int lda, int ldv, double scale, FitShared& sh) {
-  const int np = (n + 1) / 2;
-  const int m = 2 * np;
-  int tpp = 64;
-  while (tpp * np > FIT_NT) tpp >>= 1;
-  const int t = threadIdx.x, pair = t / tpp, r0 = t % tpp;
-  constexpr int NA = NI > 0 ? NI : 1;
-  for (int sweep = 0; sweep < 40; ++sweep) {
-    if (t == 0) sh.flag = 0;
-    __syncthreads();
-    int pa = pair % (m - 1), pb = (m - 1 - pair) % (m - 1);
-    for (int round = 0; round < m - 1; ++round) {
-      bool rot = false, big = false;
-      double c = 1.0, s = 0.0;
-      int p = 0, q = 0;
-      double x[NA], y[NA], vx[NA], vy[NA];
-      if (pair < np) {
-        p = pair == 0 ? m - 1 : pa;
-        q = pair == 0 ? round : pb;
-        if (p > q) { const int w = p; p = q; q = w; }
-        if (q < n) {
-          if constexpr (NI > 0) {
-            fetch_pair<NA>(a + (size_t)p * lda, a + (size_t)q * lda, 1, r0, tpp, x, y);
-            if (v != nullptr) fetch_pair<NA>(v + (size_t)p * ldv, v + (size_t)q * ldv, 1, r0, tpp, vx, vy);
-          }
-          const double app = a[(size_t)p * lda + p], aqq = a[(size_t)q * lda + q], apq = a[(size_t)q * lda + p];
-          const float tn32 = rotation_tangent((float)(aqq - app), (float)apq);
-          if (apq * apq > kJacobiEps * kJacobiEps * fabs(app * aqq) && fabs(apq) > 1e-18 * scale && tn32 != 0.f && isfinite(tn32)) {
-            const double tn = (double)tn32;
-            c = rotation_cosine(tn);
-            s = c * tn;
-            rot = true;
-            big = apq * apq > kJacobiAgain * kJacobiAgain * fabs(app * aqq);
-          }
-        }
-      }
-      if (rot) {
-        double* ap = a + (size_t)p * lda;
-        double* aq = a + (size_t)q * lda;
-        if constexpr (NI > 0) {
-          store_rotated<NA>(ap, aq, 1, r0, tpp, x, y, c, s);
-          if (v != nullptr) store_rotated<NA>(v + (size_t)p * ldv, v + (size_t)q * ldv, 1, r0, tpp, vx, vy, c, s);
-        } else {
-          for (int r = r0; r < n; r += tpp) {
-            const double xx = ap[r], yy = aq[r];
-            ap[r] = c * xx - s * yy;
-            aq[r] = s * xx + c * yy;
-          }
-          if (v != nullptr) {
-            double* vp = v + (size_t)p * ldv;
-            double* vq = v + (size_t)q * ldv;
-            for (int r = r0; r < n; r += tpp) {
-              const double xx = vp[r], yy = vq[r];
-              vp[r] = c * xx - s * yy;
-              vq[r] = s * xx + c * yy;
-            }
-          }
-        }
-      }
-      __syncthreads();
-      if (rot) {
-        if constexpr (NI > 0) {
-          fetch_pair<NA>(a + p, a + q, lda, r0, tpp, x, y);
-          store_rotated<NA>(a + p, a + q, lda, r0, tpp, x, y, c, s);
-        } else {
-          for (int k = r0; k < n; k += tpp) {
-            const double xx = a[(size_t)k * lda + p], yy = a[(size_t)k * lda + q];
-            a[(size_t)k * lda + p] = c * xx - s * yy;
-            a[(size_t)k * lda + q] = s * xx + c * yy;
-          }
-        }
-        if (r0 == 0 && big) sh.flag = 1;
-      }
-      pa = pa + 1 == m - 1 ? 0 : pa + 1;
-      pb = pb + 1 == m - 1 ? 0 : pb + 1;
-      __syncthreads();
-    }
-    const int again = sh.flag;
-    __syncthreads();
-    if (!again) break;
-  }
-}
-
-// The iteration for the sizes with a batched form (n = 64: 4 elements per lane, n = 128: 16), else the general one.
-__device__ __forceinline__ void jacobi_any(double* a, double* v, int n, int lda, int ldv, bool symmetric, double scale,
-                                           FitShared& sh) {
-  if (n == 64) {
-    if (symmetric) jacobi_symmetric<4>(a, v, n, lda, ldv, scale, sh);
-    else jacobi_columns<4>(a, v, n, lda, ldv, sh);
-  } else if (n == 128) {
-    if (symmetric) jacobi_symmetric<16>(a, v, n, lda, ldv, scale, sh);
-    else jacobi_columns<16>(a, v, n, lda, ldv, sh);
-  } else {
-    if (symmetric) jacobi_symmetric<0>(a, v, n, lda, ldv, scale, sh);
-    else jacobi_columns<0>(a, v, n, lda, ldv, sh);
   }
 }
 
@@ -301,64 +182,25 @@ __device__ __forceinline__ int descending_place(const double* v, int n, int t) {
   return place;
 }
 
-// Column norms (one-sided iteration) or diagonal entries (two-sided), their non-ascending order and (with v) the
-// eigenvector signs into slot k of the shared block.
-__device__ __forceinline__ void rank_columns(const double* wg, const double* wv, int n, int ldg, int ldv, int k, bool symmetric, FitShared& sh) {
-  const int t = threadIdx.x;
+// Singular values and left singular vectors of an n x n matrix in global memory (g, column-major with stride n): g <- g R
+// with orthogonal columns; their norms, the singular values, and the norms' order go to slot k.  The matrix is copied to
+// LDS for the iteration (column stride n + 1: columns start in different banks) and back afterwards.
+__device__ __forceinline__ void decompose_columns(double* g, int n, int k, FitShared& sh, double* lds) {
+  const int t = threadIdx.x, nn = n * n, ld = n + 1;
+  for (int e = t; e < nn; e += FIT_NT) lds[(e / n) * ld + e % n] = g[e];
+  __syncthreads();
+  // (the sizes with a batched form: n = 64, 4 elements per lane, n = 128, 16; else the general one)
+  if (n == 64) jacobi_columns<4>(lds, n, ld, sh);
+  else if (n == 128) jacobi_columns<16>(lds, n, ld, sh);
+  else jacobi_columns<0>(lds, n, ld, sh);
   if (t < n) {
-    if (symmetric) {
-      sh.nrm[k][t] = wg[(size_t)t * ldg + t];
-    } else {
-      double s2 = 0.0;
-      for (int r = 0; r < n; ++r) s2 += wg[(size_t)t * ldg + r] * wg[(size_t)t * ldg + r];
-      sh.nrm[k][t] = sqrt(s2);
-    }
-    if (wv != nullptr) {
-      int big = 0;
-      for (int r = 1; r < n; ++r)
-        if (fabs(wv[(size_t)t * ldv + r]) > fabs(wv[(size_t)t * ldv + big])) big = r;
-      sh.sgn[k][t] = wv[(size_t)t * ldv + big] < 0.0 ? -1.0 : 1.0;
-    }
+    double s2 = 0.0;
+    for (int r = 0; r < n; ++r) s2 += lds[(size_t)t * ld + r] * lds[(size_t)t * ld + r];
+    sh.nrm[k][t] = sqrt(s2);
   }
   __syncthreads();
   if (t < n) sh.ord[k][descending_place(sh.nrm[k], n, t)] = t;
-  __syncthreads();
-}
-
-// Decomposes a d x d matrix held in global memory (g, column-major with stride n, overwritten): the two-sided
-// iteration when `symmetric` (eigenvalues = final diagonal), else the one-sided one (singular values = final column
-// norms, left singular vectors = normalised columns); v (overwritten; nullptr: none) accumulates the rotations.
-// Values, order and signs go to slot k.  The matrix is copied to LDS for the iteration (column stride n + 1: columns
-// start in different banks) and back afterwards; the rotations join it there when both fit (n <= kLdsBoth), else
-// they stay in global memory.
-constexpr int kLdsBoth = 96;
-__device__ __forceinline__ void decompose(double* g, double* v, int n, int k, bool symmetric, FitShared& sh, double* lds) {
-  const int t = threadIdx.x, nn = n * n, ld = n + 1;
-  double* wg = lds;
-  for (int e = t; e < nn; e += FIT_NT) wg[(e / n) * ld + e % n] = g[e];
-  if (t == 0 && symmetric) {
-    double sc = 0.0;
-    for (int l = 0; l < n; ++l) sc = fmax(sc, fabs(g[(size_t)l * n + l]));
-    sh.red[1] = sc;
-  }
-  if (v == nullptr) {
-    __syncthreads();
-    jacobi_any(wg, nullptr, n, ld, 0, symmetric, sh.red[1], sh);
-    rank_columns(wg, nullptr, n, ld, 0, k, symmetric, sh);
-  } else if (n <= kLdsBoth) {
-    double* wv = lds + (size_t)n * ld;
-    for (int e = t; e < nn; e += FIT_NT) wv[(e / n) * ld + e % n] = (e / n == e % n) ? 1.0 : 0.0;
-    __syncthreads();
-    jacobi_any(wg, wv, n, ld, ld, symmetric, sh.red[1], sh);
-    rank_columns(wg, wv, n, ld, ld, k, symmetric, sh);
-    for (int e = t; e < nn; e += FIT_NT) v[e] = wv[(e / n) * ld + e % n];
-  } else {
-    for (int e = t; e < nn; e += FIT_NT) v[e] = (e / n == e % n) ? 1.0 : 0.0;
-    __syncthreads();
-    jacobi_any(wg, v, n, ld, n, symmetric, sh.red[1], sh);
-    rank_columns(wg, v, n, ld, n, k, symmetric, sh);
-  }
-  for (int e = t; e < nn; e += FIT_NT) g[e] = wg[(e / n) * ld + e % n];
+  for (int e = t; e < nn; e += FIT_NT) g[e] = lds[(e / n) * ld + e % n];
   __syncthreads();
 }
 
@@ -366,26 +208,27 @@ __device__ __forceinline__ void decompose(double* g, double* v, int n, int k, bo
 // Symmetric eigenproblem by reduction to tridiagonal form, one workgroup, everything in fp64.
 //
 // What bounds it is latency (one workgroup per matrix, a few matrices per call), so the design counts dependent steps:
-// the reduction has two barriers per column against two barriers per rotation round of the Jacobi iteration, which
-// needs (n - 1) x 6 - 8 rounds; everything after the reduction has no barrier per step at all.  Measured (8 matrices of
-// 64: k_fit_device 686 -> 108 us; 16 matrices of 128: 7290 -> 325 us).
+// the reduction has two barriers per column against two barriers per rotation round of a Jacobi iteration, which
+// needs (n - 1) x 6 - 8 rounds; everything after the reduction has no barrier per step at all.  Measured against a
+// two-sided Jacobi iteration (8 matrices of 64: k_fit_device 686 -> 108 us; 16 matrices of 128: 7290 -> 325 us).
 // ---------------------------------------------------------------------------------------------------
 
-// Gap between neighbouring eigenvalues (in units of the norm) below which the vectors of `eig_tridiagonal` are not
+// Gap between neighbouring eigenvalues (in units of the norm) below which vectors from twisted factorisations are not
 // used.  The eigenvalues carry an ulp or two of the norm, so the inner product of two vectors is about that over their
 // gap: up to 2.5e-16 / gap on matrices of 2 .. 128 with pairs 1e-10 .. 1e-7 apart.  2.5e-8 at this limit, below the
 // rounding of the fp32 results (6e-8); at a limit of 1e-10 it was up to 2e-6.
 constexpr double kMinGap = 1e-8;
+// Off-diagonal entries (in units of the norm) that the QR steps take for zero: below the rounding of the reduction.
+constexpr double kQrTiny = 1e-16;
 
 __device__ __forceinline__ double rcp64(double x) {        // hardware estimate and two Newton steps
   double r = __builtin_amdgcn_rcp(x);
   r = fma(fma(-x, r, 1.0), r, r);
   return fma(fma(-x, r, 1.0), r, r);
 }
-__device__ __forceinline__ double rsqrt64(double x) {
-  double r = __builtin_amdgcn_rsq(x);
-  r = fma(fma(-x * r, r, 1.0), 0.5 * r, r);
-  return fma(fma(-x * r, r, 1.0), 0.5 * r, r);
+__device__ __forceinline__ double rsqrt64(double x) {      // the estimate and one step of third order
+  const double r = __builtin_amdgcn_rsq(x), h = fma(-x * r, r, 1.0);
+  return fma(fma(h, 0.375, 0.5), h * r, r);
 }
 
 typedef double f64x2 __attribute__((ext_vector_type(2)));
@@ -420,24 +263,105 @@ __device__ __forceinline__ double sum64(double v) {        // over the wave
   return add_halves32(v, v);
 }
 __device__ __forceinline__ double max64(double v) {        // over the wave
-  for (int m = 1; m < 64; m <<= 1) v = fmax(v, __shfl_xor(v, m, 64));
-  return v;
+  v = fmax(v, dpp64<kXor1>(v));
+  v = fmax(v, dpp64<kXor2>(v));
+  v = fmax(v, dpp64<kMirror8>(v));
+  v = fmax(v, dpp64<kMirror16>(v));
+  auto pair = [](const auto& lo, const auto& hi) {
+    return fmax(__hiloint2double((int)hi[0], (int)lo[0]), __hiloint2double((int)hi[1], (int)lo[1]));
+  };
+  unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+  v = pair(__builtin_amdgcn_permlane16_swap(lo, lo, false, false), __builtin_amdgcn_permlane16_swap(hi, hi, false, false));
+  lo = (unsigned)__double2loint(v);
+  hi = (unsigned)__double2hiint(v);
+  return pair(__builtin_amdgcn_permlane32_swap(lo, lo, false, false), __builtin_amdgcn_permlane32_swap(hi, hi, false, false));
+}
+
+// Eigenvalues and vectors of a tridiagonal matrix by implicit QR steps with Wilkinson shifts (Golub and Van Loan, section
+// 8.3), for matrices with (nearly) equal eigenvalues: a product of rotations is orthogonal whatever the gaps are.
+// (diagonal, .) pairs `de`, off-diagonal `es`, both of NP, at most 2 in size.  NP / 64 waves call it, a lane per component:
+// lane i of them carries row i of the vectors (component i of vector j at Z[j NP + i], the identity at the start) through
+// every rotation; the rotations themselves are a serial chain, which each wave computes on a copy of the matrix of its own
+// (`mine`, 2 NP doubles): no barrier, no exchange.  The chain bounds it: about 1.1 n^2 rotations (fewer where blocks
+// split off), each 14 dependent fp64 operations, 110 - 150 ns.  Measured against a two-sided Jacobi iteration on the
+// original matrix, which is as orthogonal: fits of rank-2 rows, 8 heads, d 16 / 64 / 128 174 / 932 / 6933 -> 114 / 685 /
+// 2303 us.  The eigenvalues, in no order, stay in mine[0 .. n).
+template <int NP>
+__device__ __forceinline__ void tridiagonal_qr(const f64x2* de, const double* es, int n, double* Z, double* mine) {
+  const int lane = threadIdx.x & 63;
+  double *dg = mine, *of = mine + NP, *zr = Z + (threadIdx.x & (NP - 1));
+#pragma unroll
+  for (int h = 0; h < NP / 64; ++h) {
+    dg[lane + 64 * h] = de[lane + 64 * h].x;
+    of[lane + 64 * h] = es[lane + 64 * h];
+  }
+  int q = n - 1;
+  for (int left = 30 * n; left > 0; --left) {
+    // what the lanes stored in the last step is read by all of them in this one
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    unsigned long long zero[2] = {0, 0};             // bit i: entry i is negligible (or NaN: the iteration ends)
+#pragma unroll
+    for (int h = 0; h < NP / 64; ++h) zero[h] = __ballot(!(fabs(of[lane + 64 * h]) > kQrTiny));
+    auto below = [](const unsigned long long (&m)[2], int i) {      // highest set bit under bit i, or -1
+      if (NP > 64 && i > 64) {
+        const unsigned long long hi = m[1] << (128 - i);
+        if (hi) return i - 1 - __clzll(hi);
+      }
+      const unsigned long long lo = i > 0 ? m[0] << (64 - min(i, 64)) : 0;
+      return lo ? min(i, 64) - 1 - __clzll(lo) : -1;
+    };
+    const unsigned long long live[2] = {~zero[0], ~zero[1]};
+    q = below(live, q) + 1;                          // the last unreduced block: p .. q
+    if (q == 0) break;
+    const int p = below(zero, q) + 1;
+    const double dq = dg[q], b = of[q - 1], dl = 0.5 * (dg[q - 1] - dq);
+    const double h2 = dl * dl + b * b;
+    const double mu = dq - b * b * rcp64(dl + copysign(h2 * rsqrt64(h2), dl));
+    double a = dg[p], e = of[p], g = dg[p + 1], en = of[p + 1], x = a - mu, w = e, y0 = zr[p * NP], y1 = zr[(p + 1) * NP];
+    for (int k = p; k < q; ++k) {                    // rotate rows and columns k, k + 1: (x, w) -> (r, 0)
+      const int kn = min(k + 2, q);
+      const double gn = dg[kn], en2 = of[kn], yn = zr[kn * NP];
+      const double r2 = x * x + w * w;
+      double c = 1.0, s = 0.0, r = 0.0;
+      if (r2 > 1e-290) {
+        const double ir = rsqrt64(r2);
+        c = x * ir;
+        s = w * ir;
+        r = r2 * ir;
+      }
+      if (k > p) of[k - 1] = r;
+      const double u0 = c * a + s * e, u1 = c * e + s * g, v0 = c * e - s * a, v1 = c * g - s * e;
+      dg[k] = c * u0 + s * u1;
+      x = c * v0 + s * v1;                           // the entry (k, k + 1), and beyond it the bulge
+      a = c * v1 - s * v0;
+      w = s * en;
+      e = c * en;
+      zr[k * NP] = c * y0 + s * y1;
+      y0 = c * y1 - s * y0;
+      g = gn;
+      en = en2;
+      y1 = yn;
+    }
+    dg[q] = a;
+    of[q - 1] = x;
+    zr[q * NP] = y0;
+  }
 }
 
 // LDS of `eig_tridiagonal` (doubles; NP = 32 RJ): reflectors [NP][NP], two vectors of NP, (diagonal, e^2) pairs, e,
-// eigenvalues, partial norms, partial minima with their rows (one per thread); for NP = 64 also the multipliers of the
-// twisted factorisations [2][NP][NP].
+// eigenvalues, partial norms, partial minima with their rows (one per thread; the QR steps' matrices); for NP = 64 also the
+// multipliers of the twisted factorisations [2][NP][NP] (the QR steps' vectors; NP = 128: in place of the reflectors).
 constexpr size_t tri_lds_doubles(int NP) { return (size_t)(NP == 64 ? 3 : 1) * NP * NP + 8 * (size_t)NP + FIT_NT + FIT_NT / 2; }
 
 // a: the matrix, entry (ti + 4 RJ ii, tj + 32 jj) in a[ii][jj] of thread (ti = t / 32, tj = t % 32) < 128 RJ, zero
 // outside n x n (destroyed).  Any symmetric matrix: the statistics' matrices are positive semidefinite only up to the
-// rounding of their fp32 sums, and where large means cancel that rounding is all there is.  On success the eigenvalues go to slot k of the shared block with their order and signs (as rank_columns leaves them) and eigenvector
-// j to column j of v (global, column-major with stride n).  scr: 2 n n doubles of global scratch (NP = 128).  Returns
-// false, with nothing written outside LDS and scr, when two eigenvalues are closer than kMinGap or the matrix is zero or
-// not finite.
+// rounding of their fp32 sums, and where large means cancel that rounding is all there is.  Eigenvalues go to slot k of
+// the shared block with their order and the signs of the vectors, eigenvector j to column j of v (global, column-major
+// with stride ldv, component i in row sh.row[i]).  scr: 2 n n doubles of global scratch (NP = 128).  Statistics that are
+// not finite give parameters that are not finite.
 template <int RJ>
-__device__ __forceinline__ bool eig_tridiagonal(double (&a)[8][RJ], int n, double* v, double* scr, int k_slot, FitShared& sh,
-                                                double* lds) {
+__device__ __forceinline__ void eig_tridiagonal(double (&a)[8][RJ], int n, double* v, int ldv, double* scr, int k_slot,
+                                                FitShared& sh, double* lds) {
   constexpr int NP = 32 * RJ, RI = 8, HT = 128 * RJ, RS = 4 * RJ;      // HT threads hold the matrix, rows RS apart
   auto IB = [](int jc) constexpr { return 32 * jc / RS; };             // first register row of column block jc
   constexpr bool kInLds = NP == 64;
@@ -567,9 +491,9 @@ __device__ __forceinline__ bool eig_tridiagonal(double (&a)[8][RJ], int n, doubl
     }
   }
   scale = max64(scale);
-  if (!(scale > 1e-120 && scale < 1e120)) return false;
+  if (!(scale > 1e-120 && scale < 1e120)) scale = 1.0;     // a matrix of zeros, or one that is not finite
   {
-    const double inv = 1.0 / scale;
+    const double inv = rcp64(scale);
     double dd = 2.0, e2 = 1e-34;
     if (t < NP) {
       if (t < n) dd = de[t].x * inv;
@@ -627,127 +551,158 @@ __device__ __forceinline__ bool eig_tridiagonal(double (&a)[8][RJ], int n, doubl
   __syncthreads();
   if (t < n - 1 && !(lam[t + 1] - lam[t] > kMinGap)) sh.flag = 1;
   __syncthreads();
-  if (sh.flag) return false;
+  const bool close = sh.flag;
 
-  // ---- eigenvectors of the tridiagonal matrix.  Forward and backward factorisations of T - lambda_j, a lane per j:
-  // l_i = e_i / D+_i and u_i = e_i / D-_{i+1}; the twist index r minimises |gamma_i| (largest component of the vector).
-  // The pivots are quotients of successive minors, so that the chain from row to row is the minors' recurrence and the
-  // divisions run beside it.
-  double* fl = kInLds ? mul : scr;                   // l_i of vector j at fl[i * n + j], later its component i (i < r)
-  double* bu = fl + (size_t)n * n;                   // u_i, later component i + 1 (i >= r)
-  constexpr int NW = NP / 64;                        // waves per direction
-  constexpr double kTiny = 1e-30;                    // smallest pivot (far below the error of the eigenvalue)
-  const int vj = min(t & (NP - 1), n - 1);
-  const bool mine = (t & (NP - 1)) < n, fwd = wave < NW, bwd = wave >= NW && wave < 2 * NW;
-  const double lj = lam[vj];
-  if (fwd || bwd) {
-    const int r0 = fwd ? 0 : n - 1, step = fwd ? 1 : -1, eoff = fwd ? 0 : -1;
-    double* out = (fwd ? fl : bu) + vj;
-    double p1 = 1.0, p2 = 0.0, e2 = 0.0;
-    auto row = [&](int i) {
-      const double e = es[i + eoff];
-      double p = fma(de[i].x - lj, p1, -(e2 * p2));
-      p = copysign(fmax(fabs(p), kTiny * fabs(p1)), p);
-      out[(i + eoff) * n] = e * p1 * rcp64(p);       // (lanes past the last vector repeat it)
-      e2 = e * e;
-      p2 = p1;
-      p1 = p;
-    };
-    int i0 = 0;
-    for (; i0 + 8 <= n - 1; i0 += 8) {
-#pragma unroll
-      for (int m = 0; m < 8; ++m) row(r0 + step * (i0 + m));
-      const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(p1), fabs(p2)));
-      p1 = ldexp(p1, -ex);
-      p2 = ldexp(p2, -ex);
-    }
-    for (; i0 < n - 1; ++i0) row(r0 + step * i0);
-  }
-  __syncthreads();
-  {   // gamma_i = d_i - lambda - u_i e_i - l_{i-1} e_{i-1}: NT / NP threads per vector, a range of rows each
-    constexpr int NC = FIT_NT / NP;
-    const int c = t / NP, len = (n + NC - 1) / NC;
-    double best = 1e300;
-    int arg = 0;
-    for (int i0 = c * len; i0 < min(n, (c + 1) * len); i0 += 16) {
-      double ub[16], lb[16];             // (sixteen rows' loads in flight; clamped, as es is zero past the last row)
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        ub[q] = bu[(size_t)min(i0 + q, max(n - 2, 0)) * n + vj];
-        lb[q] = fl[(size_t)min(max(i0 + q - 1, 0), max(n - 2, 0)) * n + vj];
-      }
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int i = i0 + q;
-        if (i < min(n, (c + 1) * len)) {
-          double g = de[i].x - lj;
-          if (i < n - 1) g -= ub[q] * es[i];
-          if (i > 0) g -= lb[q] * es[i - 1];
-          if (fabs(g) < best) { best = fabs(g); arg = i; }
-        }
-      }
-    }
-    part_val[t] = best;
-    part_arg[t] = arg;
-  }
-  __syncthreads();
-  int rtw = part_arg[t & (NP - 1)];
-  {
-    double best = part_val[t & (NP - 1)];
-#pragma unroll
-    for (int i = (t & (NP - 1)) + NP; i < FIT_NT; i += NP)
-      if (part_val[i] < best) { best = part_val[i]; rtw = part_arg[i]; }
-  }
-  if (fwd && mine) {
-    double z = 1.0, q = 0.0;
-    for (int i0 = n - 2; i0 >= 0; i0 -= 16) {
-      double l[16];
-#pragma unroll
-      for (int m = 0; m < 16; ++m) l[m] = fl[(size_t)max(i0 - m, 0) * n + vj];
-#pragma unroll
-      for (int m = 0; m < 16; ++m)
-        if (i0 - m >= 0 && i0 - m < rtw) {
-          z *= -l[m];
-          q += z * z;
-          fl[(size_t)(i0 - m) * n + vj] = z;
-        }
-    }
-    nsq[vj] = q;
-  } else if (bwd && mine) {
-    double z = 1.0, q = 0.0;
-    for (int i0 = 0; i0 < n - 1; i0 += 16) {
-      double u[16];
-#pragma unroll
-      for (int m = 0; m < 16; ++m) u[m] = bu[(size_t)min(i0 + m, n - 2) * n + vj];
-#pragma unroll
-      for (int m = 0; m < 16; ++m)
-        if (i0 + m < n - 1 && i0 + m >= rtw) {
-          z *= -u[m];
-          q += z * z;
-          bu[(size_t)(i0 + m) * n + vj] = z;
-        }
-    }
-    nsq[NP + vj] = q;
-  }
-  if (t < NP) sh.twist[t] = rtw;
-  __syncthreads();
-
-  // ---- the reflections applied to the vectors: eight lanes per RC vectors, a lane holds rows 2 part + 16 q + {0, 1}.
+  // what the last stage starts from: the components of the vectors that a thread holds there, eight lanes per RC vectors, a
+  // lane with rows 2 part + 16 q + {0, 1}
   constexpr int RC = NP / 64, NQ = NP / 16;
   const int part = t & 7, grp = t >> 3;
   double z[RC][2 * NQ];
+  if (close) {
+    double* Z = kInLds ? mul : refl;
+    if (!kInLds) {                                   // (the reflectors wait in global memory)
+      for (int e = t; e < n * n; e += FIT_NT) scr[e] = refl[(size_t)(e / n) * NP + e % n];
+      __syncthreads();
+    }
+    for (int e = t; e < NP * NP; e += FIT_NT) Z[e] = e / NP == e % NP ? 1.0 : 0.0;
+    __syncthreads();
+    if (t < NP) {
+      double* mine = part_val + wave * 2 * NP;
+      tridiagonal_qr<NP>(de, es, n, Z, mine);
+      if (wave == 0) {
 #pragma unroll
-  for (int c = 0; c < RC; ++c) {
-    const int j = grp + 64 * c, jc = min(j, n - 1), rt = sh.twist[jc];
-    const double sc = j < n ? rsqrt64(1.0 + nsq[jc] + nsq[NP + jc]) : 0.0;
+        for (int h = 0; h < NP / 64; ++h) lam[lane + 64 * h] = mine[lane + 64 * h];
+      }
+    }
+    __syncthreads();
+    if (t < n) sh.twist[t] = descending_place(lam, n, t);
 #pragma unroll
-    for (int q = 0; q < 2 * NQ; ++q) {
-      const int i = 2 * part + 16 * (q >> 1) + (q & 1);
-      double x = 0.0;
-      if (i < n) x = i == rt ? 1.0 : (i < rt ? fl[(size_t)i * n + jc] : bu[(size_t)(i - 1) * n + jc]);
-      z[c][q] = x * sc;
+    for (int c = 0; c < RC; ++c)
+#pragma unroll
+      for (int q = 0; q < 2 * NQ; ++q) z[c][q] = Z[(grp + 64 * c) * NP + 2 * part + 16 * (q >> 1) + (q & 1)];
+    __syncthreads();
+    if (!kInLds) {
+      for (int e = t; e < n * NP; e += FIT_NT) refl[e] = e % NP < n ? scr[(size_t)(e / NP) * n + e % NP] : 0.0;
+      __syncthreads();
+    }
+  } else {
+    // ---- eigenvectors of the tridiagonal matrix.  Forward and backward factorisations of T - lambda_j, a lane per j:
+    // l_i = e_i / D+_i and u_i = e_i / D-_{i+1}; the twist index r minimises |gamma_i| (largest component of the vector).
+    // The pivots are quotients of successive minors, so that the chain from row to row is the minors' recurrence and the
+    // divisions run beside it.
+    double* fl = kInLds ? mul : scr;                   // l_i of vector j at fl[i * n + j], later its component i (i < r)
+    double* bu = fl + (size_t)n * n;                   // u_i, later component i + 1 (i >= r)
+    constexpr int NW = NP / 64;                        // waves per direction
+    constexpr double kTiny = 1e-30;                    // smallest pivot (far below the error of the eigenvalue)
+    const int vj = min(t & (NP - 1), n - 1);
+    const bool mine = (t & (NP - 1)) < n, fwd = wave < NW, bwd = wave >= NW && wave < 2 * NW;
+    const double lj = lam[vj];
+    if (fwd || bwd) {
+      const int r0 = fwd ? 0 : n - 1, step = fwd ? 1 : -1, eoff = fwd ? 0 : -1;
+      double* out = (fwd ? fl : bu) + vj;
+      double p1 = 1.0, p2 = 0.0, e2 = 0.0;
+      auto row = [&](int i) {
+        const double e = es[i + eoff];
+        double p = fma(de[i].x - lj, p1, -(e2 * p2));
+        p = copysign(fmax(fabs(p), kTiny * fabs(p1)), p);
+        out[(i + eoff) * n] = e * p1 * rcp64(p);       // (lanes past the last vector repeat it)
+        e2 = e * e;
+        p2 = p1;
+        p1 = p;
+      };
+      int i0 = 0;
+      for (; i0 + 8 <= n - 1; i0 += 8) {
+#pragma unroll
+        for (int m = 0; m < 8; ++m) row(r0 + step * (i0 + m));
+        const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(p1), fabs(p2)));
+        p1 = ldexp(p1, -ex);
+        p2 = ldexp(p2, -ex);
+      }
+      for (; i0 < n - 1; ++i0) row(r0 + step * i0);
+    }
+    __syncthreads();
+    {   // gamma_i = d_i - lambda - u_i e_i - l_{i-1} e_{i-1}: NT / NP threads per vector, a range of rows each
+      constexpr int NC = FIT_NT / NP;
+      const int c = t / NP, len = (n + NC - 1) / NC;
+      double best = 1e300;
+      int arg = 0;
+      for (int i0 = c * len; i0 < min(n, (c + 1) * len); i0 += 16) {
+        double ub[16], lb[16];             // (sixteen rows' loads in flight; clamped, as es is zero past the last row)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+          ub[q] = bu[(size_t)min(i0 + q, max(n - 2, 0)) * n + vj];
+          lb[q] = fl[(size_t)min(max(i0 + q - 1, 0), max(n - 2, 0)) * n + vj];
+        }
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+          const int i = i0 + q;
+          if (i < min(n, (c + 1) * len)) {
+            double g = de[i].x - lj;
+            if (i < n - 1) g -= ub[q] * es[i];
+            if (i > 0) g -= lb[q] * es[i - 1];
+            if (fabs(g) < best) { best = fabs(g); arg = i; }
+          }
+        }
+      }
+      part_val[t] = best;
+      part_arg[t] = arg;
+    }
+    __syncthreads();
+    int rtw = part_arg[t & (NP - 1)];
+    {
+      double best = part_val[t & (NP - 1)];
+#pragma unroll
+      for (int i = (t & (NP - 1)) + NP; i < FIT_NT; i += NP)
+        if (part_val[i] < best) { best = part_val[i]; rtw = part_arg[i]; }
+    }
+    if (fwd && mine) {
+      double z = 1.0, q = 0.0;
+      for (int i0 = n - 2; i0 >= 0; i0 -= 16) {
+        double l[16];
+#pragma unroll
+        for (int m = 0; m < 16; ++m) l[m] = fl[(size_t)max(i0 - m, 0) * n + vj];
+#pragma unroll
+        for (int m = 0; m < 16; ++m)
+          if (i0 - m >= 0 && i0 - m < rtw) {
+            z *= -l[m];
+            q += z * z;
+            fl[(size_t)(i0 - m) * n + vj] = z;
+          }
+      }
+      nsq[vj] = q;
+    } else if (bwd && mine) {
+      double z = 1.0, q = 0.0;
+      for (int i0 = 0; i0 < n - 1; i0 += 16) {
+        double u[16];
+#pragma unroll
+        for (int m = 0; m < 16; ++m) u[m] = bu[(size_t)min(i0 + m, n - 2) * n + vj];
+#pragma unroll
+        for (int m = 0; m < 16; ++m)
+          if (i0 + m < n - 1 && i0 + m >= rtw) {
+            z *= -u[m];
+            q += z * z;
+            bu[(size_t)(i0 + m) * n + vj] = z;
+          }
+      }
+      nsq[NP + vj] = q;
+    }
+    if (t < NP) sh.twist[t] = rtw;
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < RC; ++c) {
+      const int j = grp + 64 * c, jc = min(j, n - 1), rt = sh.twist[jc];
+      const double sc = j < n ? rsqrt64(1.0 + nsq[jc] + nsq[NP + jc]) : 0.0;
+#pragma unroll
+      for (int q = 0; q < 2 * NQ; ++q) {
+        const int i = 2 * part + 16 * (q >> 1) + (q & 1);
+        double x = 0.0;
+        if (i < n) x = i == rt ? 1.0 : (i < rt ? fl[(size_t)i * n + jc] : bu[(size_t)(i - 1) * n + jc]);
+        z[c][q] = x * sc;
+      }
     }
   }
+
+  // ---- the reflections applied to the vectors.
   // (sixteen reflectors per block, so that the rows above them are skipped at compile time; the next reflector is
   // requested while the current one is used)
 #pragma unroll
@@ -785,7 +740,7 @@ __device__ __forceinline__ bool eig_tridiagonal(double (&a)[8][RJ], int n, doubl
 #pragma unroll
     for (int q = 0; q < 2 * NQ; ++q) {
       const int i = 2 * part + 16 * (q >> 1) + (q & 1);
-      if (j < n && i < n) v[(size_t)j * n + i] = z[c][q];
+      if (j < n && i < n) v[(size_t)j * ldv + sh.row[i]] = z[c][q];
       if (fabs(z[c][q]) > fabs(big)) { big = z[c][q]; at = i; }
     }
     for (int m = 1; m < 8; m <<= 1) {
@@ -796,33 +751,92 @@ __device__ __forceinline__ bool eig_tridiagonal(double (&a)[8][RJ], int n, doubl
     if (part == 0 && j < n) {
       sh.sgn[k_slot][j] = big < 0.0 ? -1.0 : 1.0;
       sh.nrm[k_slot][j] = lam[j] * scale;
-      sh.ord[k_slot][n - 1 - j] = j;                 // eigenvalues came out in ascending order
+      sh.ord[k_slot][close ? sh.twist[j] : n - 1 - j] = j;      // (bisection: in ascending order)
     }
   }
   __syncthreads();
-  return true;
 }
 
-// Eigen-decomposition of the symmetric matrix entry(i, j): into slot k and v as above; g: n x n doubles (the Jacobi
-// form's matrix), scr: 2 n n doubles, both global.
+// Eigen-decomposition of the symmetric matrix entry(i, j): into slot k and v (stride n) as above.  A row without
+// off-diagonal entries (zero-padded dimensions) is left out of the eigenproblem: its diagonal entry is an eigenvalue, its
+// unit vector the eigenvector.  Several such rows would have equal eigenvalues and send the whole matrix through the QR
+// steps: fits with a quarter of the coordinates zero, 8 heads, d 16 / 64 / 128 take 78 / 145 / 378 us, with them 121 /
+// 723 / 2504.
 template <int RJ, class Entry>
-__device__ __forceinline__ void decompose_symmetric(Entry entry, double* g, double* v, double* scr, int n, int k, FitShared& sh,
-                                                    double* lds) {
-  const int t = threadIdx.x, ti = t >> 5, tj = t & 31;
-  if (n > 1) {
-    double a[8][RJ];
+__device__ __forceinline__ void decompose_symmetric(Entry entry, double* v, double* scr, int n, int k, FitShared& sh, double* lds) {
+  const int t = threadIdx.x, lane = t & 63, ti = t >> 5, tj = t & 31;
+  double a[8][RJ];
+  // an m x m matrix; indices are clamped, not conditional, so that all loads are in flight (at n = 64 12 k -> 4 k cycles)
+  auto load = [&](int m, auto row_of) {
+    auto part = [&](auto II, auto JJ) {
+#pragma unroll
+      for (int ii = 0; ii < II; ++ii)
+#pragma unroll
+        for (int jj = 0; jj < JJ; ++jj) a[ii][jj] = entry(row_of(min(ti + 4 * RJ * ii, m - 1)), row_of(min(tj + 32 * jj, m - 1)));
+    };
+    if (RJ == 4 || t < 128 * RJ) {
+      if (RJ == 4 || m > 16 * RJ) part(std::integral_constant<int, 8>(), std::integral_constant<int, RJ>());
+      else part(std::integral_constant<int, 4>(), std::integral_constant<int, RJ / 2>());
+    }
 #pragma unroll
     for (int ii = 0; ii < 8; ++ii)
 #pragma unroll
-      for (int jj = 0; jj < RJ; ++jj) {
-        const int i = ti + 4 * RJ * ii, j = tj + 32 * jj;
-        a[ii][jj] = t < 128 * RJ && i < n && j < n ? entry(i, j) : 0.0;
-      }
-    if (eig_tridiagonal<RJ>(a, n, v, scr, k, sh, lds)) return;
+      for (int jj = 0; jj < RJ; ++jj)
+        if (t >= 128 * RJ || ti + 4 * RJ * ii >= m || tj + 32 * jj >= m) a[ii][jj] = 0.0;
+  };
+  load(n, [](int i) { return i; });
+  unsigned rows = 0;                                 // bit ii: row ii of this thread has an off-diagonal entry
+#pragma unroll
+  for (int ii = 0; ii < 8; ++ii) {
+    unsigned bits = 0;
+#pragma unroll
+    for (int jj = 0; jj < RJ; ++jj) {
+      const unsigned b = ((unsigned)__double2hiint(a[ii][jj]) << 1) | (unsigned)__double2loint(a[ii][jj]);
+      bits |= ti + 4 * RJ * ii == tj + 32 * jj ? 0u : b;
+    }
+    rows |= bits != 0u ? 1u << ii : 0u;
   }
-  for (int e = t; e < n * n; e += FIT_NT) g[e] = entry(e / n, e % n);
+  // over the 32 lanes that share the rows
+  rows |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)rows, kXor1, 0xf, 0xf, true);
+  rows |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)rows, kXor2, 0xf, 0xf, true);
+  rows |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)rows, kMirror8, 0xf, 0xf, true);
+  rows |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)rows, kMirror16, 0xf, 0xf, true);
+  const auto halves = __builtin_amdgcn_permlane16_swap(rows, rows, false, false);
+  rows = halves[0] | halves[1];
+  if (t < 128 * RJ && tj < 8) sh.twist[ti + 4 * RJ * tj] = (rows >> tj) & 1;
+  if (t < n) sh.row[t] = t;
   __syncthreads();
-  decompose(g, v, n, k, true, sh, lds);
+  unsigned long long off[RJ / 2];
+  int coupled = 0;
+#pragma unroll
+  for (int h = 0; h < RJ / 2; ++h) {
+    off[h] = __ballot(lane + 64 * h < n && sh.twist[lane + 64 * h] != 0);
+    coupled += __popcll(off[h]);
+  }
+  if (coupled < n) {
+    if (t < n) {
+      int before = __popcll(off[RJ / 2 - 1] & ((1ull << lane) - 1));
+      if (t < 64) before = __popcll(off[0] & ((1ull << lane) - 1));
+      else before += __popcll(off[0]);
+      sh.row[sh.twist[t] ? before : coupled + t - before] = t;
+    }
+    __syncthreads();
+    if (coupled > 0) load(coupled, [&](int i) { return sh.row[i]; });
+  }
+  if (coupled > 0) eig_tridiagonal<RJ>(a, coupled, v, n, scr, k, sh, lds);
+  if (coupled < n) {
+    for (int e = t; e < n * n; e += FIT_NT) {
+      const int j = e / n, i = e % n;
+      if (j >= coupled || i >= coupled) v[(size_t)j * n + sh.row[i]] = i == j ? 1.0 : 0.0;
+    }
+    if (t >= coupled && t < n) {
+      sh.nrm[k][t] = entry(sh.row[t], sh.row[t]);
+      sh.sgn[k][t] = 1.0;
+    }
+    __syncthreads();
+    if (t < n) sh.ord[k][descending_place(sh.nrm[k], n, t)] = t;
+    __syncthreads();
+  }
 }
 
 __device__ void write_header(float* th, double logD, double lbar, int flags, int variant) {
@@ -833,7 +847,7 @@ __device__ void write_header(float* th, double logD, double lbar, int flags, int
   th[4] = th[5] = th[6] = th[7] = 0.f;
 }
 
-// grid (groups), block FIT_NT.  stats: per group [M1 d*d, mu4 d][M2 d*d, mu5 d]; ws: per group 7 d*d doubles.
+// grid (groups), block FIT_NT.  stats: per group [M1 d*d, mu4 d][M2 d*d, mu5 d]; ws: per group 5 d*d doubles.
 // RJ: d <= 32 RJ (the columns of a matrix per thread of eig_tridiagonal).
 template <int RJ>
 __global__ void __launch_bounds__(FIT_NT) k_fit_device(int variant, int d, const double* stats, double ridge, double* ws,
@@ -852,7 +866,7 @@ __global__ void __launch_bounds__(FIT_NT) k_fit_device(int variant, int d, const
   float* B2 = B1 + nn;
   float* C1 = B2 + nn;
   float* C2 = C1 + nn;
-  double* w = ws + (size_t)grp * 7 * nn;
+  double* w = ws + (size_t)grp * 5 * nn;
   double* lds = (double*)fit_lds;
   const double nan = __builtin_nan("");
 
@@ -907,12 +921,11 @@ __global__ void __launch_bounds__(FIT_NT) k_fit_device(int variant, int d, const
   }
 
   if (variant == 4) {                                   // SDERF: one eigendecomposition of N
-    double* N = w;
-    double* V = w + nn;
+    double* V = w;
     decompose_symmetric<RJ>([=](int r, int c) {
       const size_t e = (size_t)r * d + c;
       return M1[e] + mu4[r] * mu5[c] + mu5[r] * mu4[c] + M2[e];
-    }, N, V, w + 4 * (size_t)nn, n, 0, sh, lds);
+    }, V, w + nn, n, 0, sh, lds);
     // row scales: sqrt(1 - 4a), with the sign of the eigenvector
     if (t < d) sh.red_row[t] = sqrt(1.0 - 4.0 * a_star(fmax(sh.nrm[0][t], 0.0))) * sh.sgn[0][t];
     __syncthreads();
@@ -942,18 +955,16 @@ __global__ void __launch_bounds__(FIT_NT) k_fit_device(int variant, int d, const
   }
 
   // ADERF: eig M1, eig M2, SVD of Z = L1^(1/2) Q1^T Q2 L2^(1/2)
-  double* G1 = w;
-  double* V1 = w + nn;
-  double* G2 = w + 2 * (size_t)nn;
-  double* V2 = w + 3 * (size_t)nn;
-  double* Z = w + 4 * (size_t)nn;      // column-major
-  double* b1 = w + 5 * (size_t)nn;     // row-major
-  double* b2 = w + 6 * (size_t)nn;
+  double* V1 = w;
+  double* V2 = w + nn;
+  double* Z = w + 2 * (size_t)nn;      // column-major
+  double* b1 = w + 3 * (size_t)nn;     // row-major
+  double* b2 = w + 4 * (size_t)nn;
   // (Z, b1 and b2 are not yet in use: scratch)
-  decompose_symmetric<RJ>([=](int r, int c) { return M1[(size_t)r * d + c] + (r == c ? ridge : 0.0); }, G1, V1, Z, n, 0,
-                          sh, lds);
-  decompose_symmetric<RJ>([=](int r, int c) { return M2[(size_t)r * d + c] + (r == c ? ridge : 0.0); }, G2, V2, Z, n, 1,
-                          sh, lds);
+  decompose_symmetric<RJ>([=](int r, int c) { return M1[(size_t)r * d + c] + (r == c ? ridge : 0.0); }, V1, Z, n, 0, sh,
+                          lds);
+  decompose_symmetric<RJ>([=](int r, int c) { return M2[(size_t)r * d + c] + (r == c ? ridge : 0.0); }, V2, Z, n, 1, sh,
+                          lds);
   {
     const double l1max = sh.nrm[0][sh.ord[0][0]], l1min = sh.nrm[0][sh.ord[0][d - 1]];
     const double l2max = sh.nrm[1][sh.ord[1][0]], l2min = sh.nrm[1][sh.ord[1][d - 1]];
@@ -970,7 +981,7 @@ __global__ void __launch_bounds__(FIT_NT) k_fit_device(int variant, int d, const
     Z[e] = sqrt(sh.nrm[0][s1]) * sh.sgn[0][s1] * acc * sh.sgn[1][s2] * sqrt(sh.nrm[1][s2]);
   }
   __syncthreads();
-  decompose(Z, nullptr, n, 2, false, sh, lds);
+  decompose_columns(Z, n, 2, sh, lds);
   if (t == 0) {
     double trs = 0.0;
     for (int l = 0; l < d; ++l) trs += sh.nrm[2][l];
@@ -1023,14 +1034,14 @@ __global__ void __launch_bounds__(FIT_NT) k_fit_device(int variant, int d, const
 
 }  // namespace
 
-size_t fit_device_workspace_doubles(int d, int groups) { return (size_t)groups * 7 * d * d; }
+size_t fit_device_workspace_doubles(int d, int groups) { return (size_t)groups * 5 * d * d; }
 
 int launch_fit_device(int variant, int d, int groups, const double* stats, double ridge, double* ws, float* theta,
                       int* status, size_t theta_floats, hipStream_t st) {
   if (d < 1 || d > FIT_DMAX) return 2;
-  // the Jacobi form's matrix (and rotations), or what the tridiagonal form keeps there
-  const size_t jacobi = (size_t)(d <= kLdsBoth ? 2 : 1) * d * (d + 1);
-  const size_t lds = (d <= 64 ? std::max(jacobi, tri_lds_doubles(64)) : std::max(jacobi, tri_lds_doubles(128))) * sizeof(double);
+  // what the tridiagonal form keeps there; more than the matrix of the one-sided iteration
+  static_assert(64 * 65 <= tri_lds_doubles(64) && 128 * 129 <= tri_lds_doubles(128), "");
+  const size_t lds = tri_lds_doubles(d <= 64 ? 64 : 128) * sizeof(double);
   auto kernel = d <= 64 ? k_fit_device<2> : k_fit_device<4>;
   if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
     (void)hipGetLastError();

@@ -336,7 +336,7 @@ def test_device_fit_dense_families_at_other_sizes(fs, variant, d):
 def test_device_fit_eigensolver_sizes(fs, d, spectrum):
     """The eigensolver of the device-resident fit (tridiagonal form) at the edges of its register blocks and of its two
     instantiations, and on matrices whose eigenvalues coincide (rows in a subspace of two dimensions: all others are
-    zero), which the Jacobi iteration takes over.  Invariants of the SDERF fit against the oracle; the statistics are
+    zero), which take the QR steps.  Invariants of the SDERF fit against the oracle; the statistics are
     sums of 400 fp32 products, relative error up to 400 * 2^-24 = 2.4e-5."""
     import torch
     rng = np.random.default_rng(900 + d)
@@ -411,6 +411,38 @@ def test_device_fit_of_statistics_with_nearly_equal_eigenvalues(fs, d, rel):
     theta = _fit(fs, "device", "sderf", Xd, Xd, 1.0, H)
     worst = max(_row_defect(theta[h], d) for h in range(H))
     assert worst <= 1.5e-7, worst
+
+
+@pytest.mark.parametrize("variant", ["sderf", "aderf"])
+@pytest.mark.parametrize("alone", ["one", "every other", "all but two", "all"])
+@pytest.mark.parametrize("d", [2, 31, 64, 65, 128])
+def test_device_fit_with_uncorrelated_coordinates(fs, d, alone, variant):
+    """Coordinates uncorrelated with every other one (zero-padded dimensions are the usual case, left zero here for SDERF
+    where there are others) leave the eigenproblem as eigenvectors of their own, whatever their places; equal ones among
+    them give equal eigenvalues.  Invariants against the oracle; the sums are of 4 d + 400 fp32 products (as above)."""
+    import torch
+    rng = np.random.default_rng(1500 + d)
+    lone = {"one": np.arange(d) == d // 2, "every other": np.arange(d) % 2 == 1, "all but two": np.arange(d) >= min(2, d - 1),
+            "all": np.ones(d, bool)}[alone]
+    X = []
+    for _ in range(2):
+        x = rng.standard_normal((200, d)) * np.linspace(1.2, 0.3, d)
+        x[:, lone] = 0.0
+        e = 4.0 * np.eye(d)[lone] * (0.0 if variant == "sderf" and alone != "all" else 1.0)
+        X.append(np.concatenate([x, -x, e, -e]))
+    s = d ** -0.25
+    dev = np.zeros((2, 1, 1, len(X[0]), (d + 3) // 4 * 4), np.float32)
+    dev[:, 0, 0, :, :d] = X
+    Qd, Kd = (torch.from_numpy(v).cuda()[..., :d] for v in dev)
+    theta = _fit(fs, "device", variant, Qd, Kd, s, 1)
+    ref = orc.fit(variant, *(s * v[0, 0, :, :d].astype(np.float64) for v in dev))
+    got = util.oracle_theta_from_vec(theta[0], d)
+    tol = (4 * d + 400) * 2.0 ** -24
+    np.testing.assert_allclose(np.sort(got.A), np.sort(ref.A), atol=tol)
+    np.testing.assert_allclose(got.B1.T @ got.B1, ref.B1.T @ ref.B1, atol=6 * tol)
+    np.testing.assert_allclose(got.B1.T @ got.B2, ref.B1.T @ ref.B2, atol=6 * tol)
+    if variant == "sderf":
+        assert _row_defect(theta[0], d) <= 1.5e-7
 
 
 @pytest.mark.parametrize("variant", ["sderf", "aderf"])
