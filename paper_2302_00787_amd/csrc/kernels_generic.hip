@@ -193,8 +193,8 @@ __device__ __forceinline__ float sym_row_dot(const float* Cmat, int d, int c, co
   return (t0 + t1) + (t2 + t3);
 }
 
-// rterm[r] = log2e * (x_r^T C x_r + alpha |x_r|^2); Cmat == nullptr means C = -I/2.
-__device__ void row_terms(float* rterm, const float* Xs, int ld, int d, const float* Cmat, float alpha) {
+// rterm[r] = log2e * (x_r^T C x_r + alpha |x_r|^2), -inf for r >= live; Cmat == nullptr means C = -I/2.
+__device__ void row_terms(float* rterm, const float* Xs, int ld, int d, const float* Cmat, float alpha, int live = TR) {
   if (threadIdx.x >= 8 * TR) return;         // eight threads a row
   const int r = threadIdx.x >> 3, part = threadIdx.x & 7;
   const float* x = Xs + r * ld;
@@ -222,16 +222,18 @@ __device__ void row_terms(float* rterm, const float* Xs, int ld, int d, const fl
   acc += __shfl_xor(acc, 1);
   acc += __shfl_xor(acc, 2);
   acc += __shfl_xor(acc, 4);
-  if (part == 0) rterm[r] = kLog2e * acc;
+  if (part == 0) rterm[r] = r < live ? kLog2e * acc : -INFINITY;
 }
 
-// Row terms of the 32-row tile at row0 of (b,h): from the side's table when the call keeps one, else computed.
+// Row terms of the 32-row tile at row0 of (b,h): from the side's table when the call keeps one, else computed.  Rows of
+// padding get -inf, so that their features are exactly zero: with 0 the exponent of a feature is its bias less the
+// sequence's key shift, which overflows where all keys are long.
 __device__ void row_terms_of(float* rterm, const GenSide& sd, int bh, int L, int row0, int row_end, const float* Xs,
                              int ld, int d, const float* Cmat, float alpha) {
   if (sd.rk != nullptr) {
-    if (threadIdx.x < TR) rterm[threadIdx.x] = row0 + (int)threadIdx.x < row_end ? sd.rk[(size_t)bh * L + row0 + threadIdx.x] : 0.f;
+    if (threadIdx.x < TR) rterm[threadIdx.x] = row0 + (int)threadIdx.x < row_end ? sd.rk[(size_t)bh * L + row0 + threadIdx.x] : -INFINITY;
   } else {
-    row_terms(rterm, Xs, ld, d, Cmat, alpha);
+    row_terms(rterm, Xs, ld, d, Cmat, alpha, row_end - row0);
   }
 }
 
@@ -497,7 +499,7 @@ __global__ void __launch_bounds__(NT) k_gen_state(GenSide ks, TensorDev V, int L
       values_fetch(vr, V, vbase, row0 + TR, row_end, nv);
     }
     if (row_shift == nullptr) row_terms_of(rterm, ks, bh, Lk, row0, row_end, Xs, ld, d, Cmat, ks.alpha);
-    else if (threadIdx.x < TR) rterm[threadIdx.x] = row0 + threadIdx.x < row_end ? -row_shift[(size_t)bh * Lk + row0 + threadIdx.x] : 0.f;
+    else if (threadIdx.x < TR) rterm[threadIdx.x] = row0 + threadIdx.x < row_end ? -row_shift[(size_t)bh * Lk + row0 + threadIdx.x] : -INFINITY;
     __syncthreads();
     const f32x4 e = proj_tile(Xs, Ws, ld, dpad);
     const int f = (w & 1) * 16 + (lane & 15);

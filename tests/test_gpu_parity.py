@@ -59,6 +59,41 @@ def _check_attention(fs, Q, K, V, Omega, scale, causal, variant, dtype, chunk=0,
     return worst
 
 
+@pytest.mark.parametrize("what", ["attention", "backward", "operator"])
+@pytest.mark.parametrize("L", [31, 33, 64])
+def test_ragged_tiles_of_long_keys(fs, what, L):
+    """Keys that are all long: every exponent of a real key lies far below the bias of a feature, which is all the
+    exponent a row of padding has, and exp2 of the difference overflows (L = 31 and 33 pad the last tile, 64 does not).
+    Features of padding must be zero themselves: infinity times a value of zero is not.  Exponents of up to 700 binary
+    orders carry 700 * 2^-24 * ln 2 = 3e-5 per rounding, of which each has three (row term, projection, sum)."""
+    import torch
+    rng = np.random.default_rng(60 + L)
+    d, M, s = 64, 96, 64 ** -0.25
+    Q = rng.standard_normal((1, 1, L, d)).astype(np.float32)
+    K = rng.standard_normal((1, 1, L, d))
+    K = (64.0 * K / np.linalg.norm(K, axis=-1, keepdims=True) * (1 + 1e-3 * rng.random((1, 1, L, 1)))).astype(np.float32)
+    V, dY = rng.standard_normal((2, 1, 1, L, d)).astype(np.float32)
+    Om = rng.standard_normal((1, M, d)).astype(np.float32)
+    th = orc.fit_posrf(d)
+    theta = torch.from_numpy(util.theta_vec_from_oracle(th)[None]).cuda()
+    Qd, Kd, Vd, dYd, Omd = (torch.from_numpy(x).cuda() for x in (Q, K, V, dY, Om))
+    if what == "attention":
+        got, ref = fs.attention(theta, Qd, Kd, Vd, s, Omd), orc.attention(th, Om[0], Q[0, 0], K[0, 0], V[0, 0], s)
+    elif what == "backward":
+        got = torch.stack(fs.attention_backward(theta, Qd, Kd, Vd, dYd, s, Omd))
+        ref = np.stack(orc.attention_backward(th, Om[0], Q[0, 0], K[0, 0], V[0, 0], dY[0, 0], s))
+    else:       # forty right-hand sides: the general kernels; true values below 1e-70 are zero in fp32
+        C = rng.standard_normal((L, 40)).astype(np.float32)
+        got = fs.kernel_matvec(theta[0], Qd[0, 0], Kd[0, 0], s, 0.0, Omd[0], torch.from_numpy(C).cuda())
+        assert torch.equal(got, torch.zeros_like(got))
+        return
+    got = util.to_host(got).reshape(ref.shape)
+    # (where one key takes every query the gradients of Q and K cancel: measured against the output gradient then)
+    for g, r in zip(got, ref) if what == "backward" else ((got, ref),):
+        size = max(np.linalg.norm(r), np.linalg.norm(dY) if what == "backward" else 0.0)
+        assert np.linalg.norm(g - r) <= 3e-4 * size, np.linalg.norm(g - r) / size
+
+
 # ----------------------------------------------------------------------------- features
 @pytest.mark.parametrize("variant", ["posrf", "gerf", "saderf", "aderf", "sderf"])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
