@@ -6,6 +6,8 @@
 // Tile shape everywhere: 32 rows (tokens) x 32 features per step, 256 threads = 4 waves.
 // MFMA 16x16x4 f32 operand layout used below: lane l supplies A[l%16][l/16] and B[l/16][l%16];
 // accumulator register r of lane l is D[4*(l/16) + r][l%16].
+#include <type_traits>
+
 #include "fs_common.h"
 #include "kernels.h"
 
@@ -14,14 +16,20 @@ namespace fs {
 constexpr int TR = 32;     // rows per tile
 constexpr int MB = 32;     // features per block
 constexpr int NT = 256;    // threads per workgroup (causal kernels: NTC)
-// The causal kernels keep so much in LDS that one or two workgroups fit a CU: eight waves each, two per SIMD or more.
-// Four of them work on the query side while the other four work on the key side, both projection blocks in LDS (two
-// barriers fewer per block).  Against four waves: causal attention B2 H4 L4096 d64 M256 f32 388 -> 320 us, causal
-// backward pass B1 H16 L4096 d128 M512 5.63 -> 4.64 ms.
+// The causal kernels have eight waves, two per SIMD: with 164 to 256 registers (d > 32) one workgroup fills a CU, and at
+// d = 128 it needs most of its LDS as well.  Four waves work on the query side while the other four work on the key
+// side, both projection blocks in LDS (two barriers fewer per block).  Against four waves: causal attention B2 H4 L4096
+// d64 M256 f32 388 -> 320 us, causal backward pass B1 H16 L4096 d128 M512 5.63 -> 4.64 ms.
 constexpr int NTC = 512;
 
-constexpr int ACC_PER_WAVE = 5;   // ceil(2 * MAXVT / 4)
-constexpr int ACC_PER_WAVE_C = 3; // ceil(2 * MAXVT / 8)
+// Every kernel comes in three widths W: rows of at most 32 W columns and values of at most 32 NV (W = 1: 64, 2: 96,
+// 4: 144).  Registers of a tile and accumulators are counted for the width: with those of W = 4 for every d, two or three
+// waves of k_gen_state, k_gen_apply and k_gen_bwd_side fitted a SIMD, now four or five at d <= 32 and three or four at
+// d <= 64.  f32, M = 32 / 256: causal attention of 2048 sequences of 128 at d 8 302 -> 173 us, B2 H4 L4096 d64 311 ->
+// 278; backward pass of the 2048 sequences 426 -> 284 us non-causal, 874 -> 714 causal.
+template <int W> constexpr int NV = W == 4 ? 5 : W + 1;
+template <int W, int WAVES> constexpr int ACC_V = (4 * NV<W> + WAVES - 1) / WAVES;   // 16 x 16 tiles of 32 rows of values, per wave
+template <int W, int WAVES> constexpr int ACC_D = (4 * W + WAVES - 1) / WAVES;       // of 32 rows of a side
 
 // This side's C matrix, or nullptr when the parameter set says C = -I/2 (flag bit 0 of the theta header).
 __device__ __forceinline__ const float* side_cmat(const GenSide& s, int b, int h, int H) {
@@ -105,73 +113,74 @@ __device__ __forceinline__ void tile_put(const Tile<NI, TH>& t, int dtype, float
   }
 }
 
-// Rows of a side (at most 128 columns) and of values (at most 144, with the column of ones that is the normaliser).
-template <int TH> using RowTile = Tile<4, TH>;
-template <int TH> using ValTile = Tile<5, TH>;
+// Rows of a side, and of values with the column of ones that is the normaliser.
+template <int W, int TH> using RowTile = Tile<W, TH>;
+template <int W, int TH> using ValTile = Tile<NV<W>, TH>;
 static_assert(TR == 32 && MB == 32, "32 threads carry a row of a tile");
-template <int TH>
-__device__ __forceinline__ void rows_fetch(RowTile<TH>& x, const TensorDev& t, long long base, int row0, int nrows, int ncols) {
+template <int N, int TH>
+__device__ __forceinline__ void rows_fetch(Tile<N, TH>& x, const TensorDev& t, long long base, int row0, int nrows, int ncols) {
   tile_fetch(x, t.ptr, t.dtype, base + (long long)row0 * t.sl, t.sl, nrows - row0, ncols);
 }
-template <int TH>
-__device__ __forceinline__ void rows_put(const RowTile<TH>& x, const TensorDev& t, float* dst, int ld, int row0, int nrows,
+template <int N, int TH>
+__device__ __forceinline__ void rows_put(const Tile<N, TH>& x, const TensorDev& t, float* dst, int ld, int row0, int nrows,
                                          int ncols, int ncols_pad, float scale) {
   tile_put(x, t.dtype, dst, ld, nrows - row0, ncols, ncols_pad, scale, 0.f);
 }
-template <int TH>
-__device__ __forceinline__ void values_fetch(ValTile<TH>& x, const TensorDev& t, long long base, int row0, int nrows, int ncols) {
+template <int N, int TH>
+__device__ __forceinline__ void values_fetch(Tile<N, TH>& x, const TensorDev& t, long long base, int row0, int nrows, int ncols) {
   tile_fetch(x, t.ptr, t.dtype, base + (long long)row0 * t.sl, t.sl, nrows - row0, ncols);
 }
-template <int TH>
-__device__ __forceinline__ void values_put(const ValTile<TH>& x, const TensorDev& t, float* dst, int ld, int row0, int nrows,
+template <int N, int TH>
+__device__ __forceinline__ void values_put(const Tile<N, TH>& x, const TensorDev& t, float* dst, int ld, int row0, int nrows,
                                            int ncols, int ncols_pad, int append_ones) {
   tile_put(x, t.dtype, dst, ld, nrows - row0, ncols, ncols_pad, 1.f, append_ones ? 1.f : 0.f);
 }
 
 // dst[r][c] = scale * T[row0 + r][c] for r < 32; zero outside [0, nrows) x [0, ncols); columns up to ncols_pad written.
-template <int TH = NT>
+template <int W, int TH = NT>
 __device__ __forceinline__ void load_rows(float* dst, int ld, const TensorDev& t, long long base, int row0, int nrows,
                                           int ncols, int ncols_pad, float scale) {
-  RowTile<TH> x;
+  RowTile<W, TH> x;
   rows_fetch(x, t, base, row0, nrows, ncols);
   rows_put(x, t, dst, ld, row0, nrows, ncols, ncols_pad, scale);
 }
 
 // Value tile with an optional column of ones at index ncols (the normaliser column of attention).
-template <int TH = NT>
+template <int W, int TH = NT>
 __device__ __forceinline__ void load_values(float* dst, int ld, const TensorDev& t, long long base, int row0, int nrows,
                                             int ncols, int ncols_pad, int append_ones) {
-  ValTile<TH> x;
+  ValTile<W, TH> x;
   values_fetch(x, t, base, row0, nrows, ncols);
   values_put(x, t, dst, ld, row0, nrows, ncols, ncols_pad, append_ones);
 }
 
 // Ws[f][c] = W[m0 + f][c] (zero rows past M), bias_s[f] = bias[m0 + f], in two halves.
-template <int TH> struct WRegs { RowTile<TH> w; float b; };
-template <int TH>
-__device__ __forceinline__ void wblock_fetch(WRegs<TH>& r, const float* W, const float* bias, int m0, int M, int d) {
+template <int W, int TH> struct WRegs { RowTile<W, TH> w; float b; };
+template <int N, int TH>
+__device__ __forceinline__ void wblock_fetch(WRegs<N, TH>& r, const float* W, const float* bias, int m0, int M, int d) {
   tile_fetch(r.w, W, 0, (long long)m0 * d, d, M - m0, d);
   r.b = bias[min(m0 + (int)(threadIdx.x & (MB - 1)), M - 1)];
 }
-template <int TH>
-__device__ __forceinline__ void wblock_put(const WRegs<TH>& r, float* Ws, float* bias_s, int ld, int m0, int M, int d, int dpad) {
+template <int N, int TH>
+__device__ __forceinline__ void wblock_put(const WRegs<N, TH>& r, float* Ws, float* bias_s, int ld, int m0, int M, int d, int dpad) {
   tile_put(r.w, 0, Ws, ld, M - m0, d, dpad, 1.f, 0.f);
   if (threadIdx.x < MB) bias_s[threadIdx.x] = m0 + (int)threadIdx.x < M ? r.b : 0.f;
 }
+template <int WD>
 __device__ __forceinline__ void load_wblock(float* Ws, float* bias_s, int ld, const float* W, const float* bias, int m0,
                                             int M, int d, int dpad) {
-  WRegs<NT> r;
+  WRegs<WD, NT> r;
   wblock_fetch(r, W, bias, m0, M, d);
   wblock_put(r, Ws, bias_s, ld, m0, M, d, dpad);
 }
 
 // The block of a state that belongs to features m0 .. m0 + 31 (rows of ldt floats; zero rows past M).
-template <int TH>
-__device__ __forceinline__ void sblock_fetch(ValTile<TH>& t, const float* T, int m0, int M, int ldt) {
+template <int N, int TH>
+__device__ __forceinline__ void sblock_fetch(Tile<N, TH>& t, const float* T, int m0, int M, int ldt) {
   tile_fetch(t, T, 0, (long long)m0 * ldt, ldt, M - m0, ldt);
 }
-template <int TH>
-__device__ __forceinline__ void sblock_put(const ValTile<TH>& t, float* Ts, int ld, int m0, int M, int ldt) {
+template <int N, int TH>
+__device__ __forceinline__ void sblock_put(const Tile<N, TH>& t, float* Ts, int ld, int m0, int M, int ldt) {
   tile_put(t, 0, Ts, ld, M - m0, ldt, ldt, 1.f, 0.f);
 }
 
@@ -262,11 +271,12 @@ __device__ __forceinline__ void rowmax_update(uint32_t* rowmax_u, const float e[
 }
 
 // One pass over all feature blocks computing, per row, max_m (W_m . x + bias_m) (+ rterm is added by the caller).
+template <int WD>
 __device__ void rowmax_pass(uint32_t* rowmax_u, const float* Xs, float* Ws, float* bias_s, int ld, const float* W,
                             const float* bias, int M, int d, int dpad) {
   if (threadIdx.x < TR) rowmax_u[threadIdx.x] = 0u;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  WRegs<NT> wr;
+  WRegs<WD, NT> wr;
   wblock_fetch(wr, W, bias, 0, M, d);
   for (int m0 = 0; m0 < M; m0 += MB) {
     __syncthreads();
@@ -284,11 +294,12 @@ __device__ void rowmax_pass(uint32_t* rowmax_u, const float* Xs, float* Ws, floa
 }
 
 // The same with eight waves: two feature blocks per step, four waves each.
+template <int WD>
 __device__ void rowmax_pass2(uint32_t* rowmax_u, const float* Xs, float* Ws, float* Ws2, float* bias_s, float* bias2_s,
                              int ld, const float* W, const float* bias, int M, int d, int dpad) {
   if (threadIdx.x < TR) rowmax_u[threadIdx.x] = 0u;
   const int lane = threadIdx.x & 63, w = (threadIdx.x >> 6) & 3, half = threadIdx.x >> 8;
-  WRegs<NTC> wa, wb;
+  WRegs<WD, NTC> wa, wb;
   wblock_fetch(wa, W, bias, 0, M, d);
   if (MB < M) wblock_fetch(wb, W, bias, MB, M, d);
   for (int m0 = 0; m0 < M; m0 += 2 * MB) {
@@ -379,6 +390,7 @@ __global__ void k_fill_u32(uint32_t* p, uint32_t v, size_t n) {
 // ---------------------------------------------------------------------------------------------------
 // Materialised features (Section 2.1, rows of P or S).  grid (ceil(n/32)), dynamic LDS.
 // ---------------------------------------------------------------------------------------------------
+template <int WD>
 __global__ void __launch_bounds__(NT) k_gen_features(TensorDev X, int n, int d, float scale, float alpha,
                                                      const float* W, const float* bias, const float* theta,
                                                      long long c_offset, int M, float* out, float* row_logscale) {
@@ -393,18 +405,18 @@ __global__ void __launch_bounds__(NT) k_gen_features(TensorDev X, int n, int d, 
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const float* Cmat = (((int)theta[2]) & 1) ? nullptr : theta + c_offset;
 
-  load_rows(Xs, ld, X, 0, row0, n, d, dpad, scale);
+  load_rows<WD>(Xs, ld, X, 0, row0, n, d, dpad, scale);
   __syncthreads();
   row_terms(rterm, Xs, ld, d, Cmat, alpha);
   __syncthreads();
   if (row_logscale != nullptr) {
-    rowmax_pass(rowmax_u, Xs, Ws, bias_s, ld, W, bias, M, d, dpad);
+    rowmax_pass<WD>(rowmax_u, Xs, Ws, bias_s, ld, W, bias, M, d, dpad);
     if (threadIdx.x < TR && row0 + threadIdx.x < n)
       row_logscale[row0 + threadIdx.x] = (ordered_to_float(rowmax_u[threadIdx.x]) + rterm[threadIdx.x]) * kLn2;
   }
   for (int m0 = 0; m0 < M; m0 += MB) {
     __syncthreads();
-    load_wblock(Ws, bias_s, ld, W, bias, m0, M, d, dpad);
+    load_wblock<WD>(Ws, bias_s, ld, W, bias, m0, M, d, dpad);
     __syncthreads();
     const f32x4 acc = proj_tile(Xs, Ws, ld, dpad);
     const int f = (w & 1) * 16 + (lane & 15);
@@ -422,6 +434,7 @@ __global__ void __launch_bounds__(NT) k_gen_features(TensorDev X, int n, int d, 
 // Key-side maximum of the exponent per (b, h): kmax[bh] = max_{j,m} E2[j,m] (ordered-uint image, atomicMax).
 // grid (ceil(Lk/32), B*H).
 // ---------------------------------------------------------------------------------------------------
+template <int WD>
 __global__ void __launch_bounds__(NT) k_gen_kmax(GenSide ks, int Lk, int H, int M, int d, uint32_t* kmax_u) {
   extern __shared__ float smem[];
   const int dpad = (d + 3) & ~3, ld = dpad + 1;
@@ -437,10 +450,10 @@ __global__ void __launch_bounds__(NT) k_gen_kmax(GenSide ks, int Lk, int H, int 
   const float* bias = ks.bias + ((size_t)pg * 2 + 1) * M;
   const float* Cmat = side_cmat(ks, b, h, H);
 
-  load_rows(Xs, ld, ks.X, b * ks.X.sb + h * ks.X.sh, row0, Lk, d, dpad, ks.scale);
+  load_rows<WD>(Xs, ld, ks.X, b * ks.X.sb + h * ks.X.sh, row0, Lk, d, dpad, ks.scale);
   __syncthreads();
   row_terms(rterm, Xs, ld, d, Cmat, ks.alpha);
-  rowmax_pass(rowmax_u, Xs, Ws, bias_s, ld, W, bias, M, d, dpad);
+  rowmax_pass<WD>(rowmax_u, Xs, Ws, bias_s, ld, W, bias, M, d, dpad);
   if (threadIdx.x < 64) {
     float v = (threadIdx.x < TR && row0 + threadIdx.x < Lk)
                   ? ordered_to_float(rowmax_u[threadIdx.x]) + rterm[threadIdx.x] : -INFINITY;
@@ -456,6 +469,7 @@ __global__ void __launch_bounds__(NT) k_gen_kmax(GenSide ks, int Lk, int H, int 
 // ---------------------------------------------------------------------------------------------------
 // With row_shift != nullptr the kernel serves the backward pass on the query side: features of side 1 with the
 // per-row shifts the forward pass used (no row term in the exponent), "values" = the rows of the output gradient.
+template <int WD>
 __global__ void __launch_bounds__(NT) k_gen_state(GenSide ks, TensorDev V, int Lk, int H, int M, int d, int nv,
                                                   int append_ones, int ldt, int rows_per_seg, int nseg,
                                                   const uint32_t* kmax_u, const float* row_shift, float* Tpart) {
@@ -477,16 +491,16 @@ __global__ void __launch_bounds__(NT) k_gen_state(GenSide ks, TensorDev V, int L
   const float c = row_shift == nullptr ? ordered_to_float(kmax_u[bh]) : 0.f;
   const int nvt = ldt / 16, ntiles = 2 * nvt;
 
-  load_wblock(Ws, bias_s, ld, W, bias, m0, M, d, dpad);
-  f32x4 acc[ACC_PER_WAVE];
+  load_wblock<WD>(Ws, bias_s, ld, W, bias, m0, M, d, dpad);
+  f32x4 acc[ACC_V<WD, 4>];
 #pragma unroll
-  for (int t = 0; t < ACC_PER_WAVE; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int t = 0; t < ACC_V<WD, 4>; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   const int row_end = min(Lk, (seg + 1) * rows_per_seg);
   const long long xbase = b * ks.X.sb + h * ks.X.sh, vbase = b * V.sb + h * V.sh;
   // (the rows and values of the next step are fetched while the current one computes)
-  RowTile<NT> xr;
-  ValTile<NT> vr;
+  RowTile<WD, NT> xr;
+  ValTile<WD, NT> vr;
   rows_fetch(xr, ks.X, xbase, seg * rows_per_seg, row_end, d);
   values_fetch(vr, V, vbase, seg * rows_per_seg, row_end, nv);
   for (int row0 = seg * rows_per_seg; row0 < row_end; row0 += TR) {
@@ -510,7 +524,7 @@ __global__ void __launch_bounds__(NT) k_gen_state(GenSide ks, TensorDev V, int L
     }
     __syncthreads();
 #pragma unroll
-    for (int tl = 0; tl < ACC_PER_WAVE; ++tl) {
+    for (int tl = 0; tl < ACC_V<WD, 4>; ++tl) {
       const int t = w + 4 * tl;
       if (t < ntiles) {
         const int mt = t & 1, vt = t >> 1;
@@ -522,7 +536,7 @@ __global__ void __launch_bounds__(NT) k_gen_state(GenSide ks, TensorDev V, int L
   }
   float* out = Tpart + (((size_t)bh * nseg + seg) * M) * ldt;
 #pragma unroll
-  for (int tl = 0; tl < ACC_PER_WAVE; ++tl) {
+  for (int tl = 0; tl < ACC_V<WD, 4>; ++tl) {
     const int t = w + 4 * tl;
     if (t < ntiles) {
       const int mt = t & 1, vt = t >> 1;
@@ -594,6 +608,7 @@ __device__ void store_result(const float* Os, int ldo, const TensorDev& Y, long 
 // Query side of the non-causal contraction (Section 2.1, P (S^T C); Section 2.2 for the row normalisation).
 // grid (ceil(Lq/32), B*H).  T: [bh][M][ldt] with stride state_stride between (b,h).
 // ---------------------------------------------------------------------------------------------------
+template <int WD>
 __global__ void __launch_bounds__(NT) k_gen_apply(GenSide qs, int Lq, int H, int M, int d, int nv, int ldt,
                                                   const float* T, size_t state_stride, const uint32_t* kmax_u,
                                                   int matvec, TensorDev Y, float* den_out, float* shift_out,
@@ -617,22 +632,22 @@ __global__ void __launch_bounds__(NT) k_gen_apply(GenSide qs, int Lq, int H, int
   const float* Tb = T + (size_t)bh * state_stride;
   const int nvt = ldt / 16, ntiles = 2 * nvt;
 
-  load_rows(Xs, ld, qs.X, b * qs.X.sb + h * qs.X.sh, row0, Lq, d, dpad, qs.scale);
+  load_rows<WD>(Xs, ld, qs.X, b * qs.X.sb + h * qs.X.sh, row0, Lq, d, dpad, qs.scale);
   __syncthreads();
   // (the query row terms matter in operator mode only: in attention they cancel in the normalisation)
   if (matvec) row_terms(rterm, Xs, ld, d, Cmat, qs.alpha);
   else if (threadIdx.x < TR) rterm[threadIdx.x] = 0.f;
-  rowmax_pass(rowmax_u, Xs, Ws, bias_s, ld, W, bias, M, d, dpad);
+  rowmax_pass<WD>(rowmax_u, Xs, Ws, bias_s, ld, W, bias, M, d, dpad);
   // operator mode multiplies the shifts back: exp2(rowmax + rterm + kmax)
   if (threadIdx.x < TR)
     rscale[threadIdx.x] = ordered_to_float(rowmax_u[threadIdx.x]) + rterm[threadIdx.x] + ordered_to_float(kmax_u[bh]);
 
-  f32x4 acc[ACC_PER_WAVE];
+  f32x4 acc[ACC_V<WD, 4>];
 #pragma unroll
-  for (int t = 0; t < ACC_PER_WAVE; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int t = 0; t < ACC_V<WD, 4>; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
   // the projection block and the state block of the next step are fetched while the current step computes
-  WRegs<NT> wr;
-  ValTile<NT> tr;
+  WRegs<WD, NT> wr;
+  ValTile<WD, NT> tr;
   wblock_fetch(wr, W, bias, 0, M, d);
   sblock_fetch(tr, Tb, 0, M, ldt);
   for (int m0 = 0; m0 < M; m0 += MB) {
@@ -653,7 +668,7 @@ __global__ void __launch_bounds__(NT) k_gen_apply(GenSide qs, int Lq, int H, int
     }
     __syncthreads();
 #pragma unroll
-    for (int tl = 0; tl < ACC_PER_WAVE; ++tl) {
+    for (int tl = 0; tl < ACC_V<WD, 4>; ++tl) {
       const int t = w + 4 * tl;
       if (t < ntiles) {
         const int rt = t & 1, vt = t >> 1;
@@ -666,7 +681,7 @@ __global__ void __launch_bounds__(NT) k_gen_apply(GenSide qs, int Lq, int H, int
   __syncthreads();
   float* Os = Ts;
 #pragma unroll
-  for (int tl = 0; tl < ACC_PER_WAVE; ++tl) {
+  for (int tl = 0; tl < ACC_V<WD, 4>; ++tl) {
     const int t = w + 4 * tl;
     if (t < ntiles) {
       const int rt = t & 1, vt = t >> 1;
@@ -689,7 +704,10 @@ __global__ void __launch_bounds__(NT) k_gen_apply(GenSide qs, int Lq, int H, int
 //   Y_c = (tril(P_c S_c^T) [V_c 1] + P_c T_prev) normalised by its last column;  T += S_c^T [V_c 1].
 // grid (nseg, B*H).
 // ---------------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(NTC) k_gen_causal(GenSide qs, GenSide ks, TensorDev V, int L, int H, int M, int d,
+// (WD = 1: 129 registers by the compiler's own choice, one too many for two workgroups per CU; held to 128 without spills,
+// 2048 sequences of 128 at d 8 248 -> 173 us.  The backward kernels would spill 41 and 62 and get slower.)
+template <int WD>
+__global__ void __launch_bounds__(NTC, WD == 1 ? 4 : 2) k_gen_causal(GenSide qs, GenSide ks, TensorDev V, int L, int H, int M, int d,
                                                    int nv, int ldt, int rows_per_seg, int nseg,
                                                    const uint32_t* kmax_u, float* Tstate, TensorDev Y, float* den_out,
                                                    float* shift_out, unsigned* flushed) {
@@ -724,21 +742,21 @@ __global__ void __launch_bounds__(NTC) k_gen_causal(GenSide qs, GenSide ks, Tens
   const int row_end = min(L, (seg + 1) * rows_per_seg);
   for (int row0 = seg * rows_per_seg; row0 < row_end; row0 += TR) {
     __syncthreads();
-    load_rows<NTC>(Qs, ld, qs.X, qbase, row0, row_end, d, dpad, qs.scale);
-    load_rows<NTC>(Ks, ld, ks.X, kbase, row0, row_end, d, dpad, ks.scale);
-    load_values<NTC>(Vs, ldv, V, b * V.sb + h * V.sh, row0, row_end, nv, ldt, 1);
+    load_rows<WD, NTC>(Qs, ld, qs.X, qbase, row0, row_end, d, dpad, qs.scale);
+    load_rows<WD, NTC>(Ks, ld, ks.X, kbase, row0, row_end, d, dpad, ks.scale);
+    load_values<WD, NTC>(Vs, ldv, V, b * V.sb + h * V.sh, row0, row_end, nv, ldt, 1);
     __syncthreads();
     row_terms_of(rterm, ks, bh, L, row0, row_end, Ks, ld, d, Cmat2, 0.f);
-    rowmax_pass2(rowmax_u, Qs, Ws, Ws2, bias_s, bias2_s, ld, W1, bias1, M, d, dpad);
+    rowmax_pass2<WD>(rowmax_u, Qs, Ws, Ws2, bias_s, bias2_s, ld, W1, bias1, M, d, dpad);
 
-    f32x4 acc[ACC_PER_WAVE_C];
+    f32x4 acc[ACC_V<WD, 8>];
 #pragma unroll
-    for (int t = 0; t < ACC_PER_WAVE_C; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < ACC_V<WD, 8>; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     f32x4 sc = {0.f, 0.f, 0.f, 0.f};          // scores tile (query tile w>>1, key tile w&1)
     // the three blocks of the next step are fetched while the current one computes (rows of the state that this step
     // writes are not among them)
-    WRegs<NTC> wa, wb;
-    ValTile<NTC> tr;
+    WRegs<WD, NTC> wa, wb;
+    ValTile<WD, NTC> tr;
     wblock_fetch(wa, W1, bias1, 0, M, d);
     sblock_fetch(tr, Tg, 0, M, ldt);
     wblock_fetch(wb, W2, bias2, 0, M, d);
@@ -777,7 +795,7 @@ __global__ void __launch_bounds__(NTC) k_gen_causal(GenSide qs, GenSide ks, Tens
         sc = mfma_chain(ap, 1, bp, 1, MB, sc);
       }
 #pragma unroll
-      for (int tl = 0; tl < ACC_PER_WAVE_C; ++tl) {
+      for (int tl = 0; tl < ACC_V<WD, 8>; ++tl) {
         const int t = w + 8 * tl;
         if (t < ntiles) {
           const int rt = t & 1, vt = t >> 1;
@@ -809,7 +827,7 @@ __global__ void __launch_bounds__(NTC) k_gen_causal(GenSide qs, GenSide ks, Tens
     }
     __syncthreads();
 #pragma unroll
-    for (int tl = 0; tl < ACC_PER_WAVE_C; ++tl) {
+    for (int tl = 0; tl < ACC_V<WD, 8>; ++tl) {
       const int t = w + 8 * tl;
       if (t < ntiles) {
         const int rt = t & 1, vt = t >> 1;
@@ -821,7 +839,7 @@ __global__ void __launch_bounds__(NTC) k_gen_causal(GenSide qs, GenSide ks, Tens
     __syncthreads();
     float* Os = Ts;
 #pragma unroll
-    for (int tl = 0; tl < ACC_PER_WAVE_C; ++tl) {
+    for (int tl = 0; tl < ACC_V<WD, 8>; ++tl) {
       const int t = w + 8 * tl;
       if (t < ntiles) {
         const int rt = t & 1, vt = t >> 1;
@@ -843,6 +861,7 @@ __global__ void __launch_bounds__(NTC) k_gen_causal(GenSide qs, GenSide ks, Tens
 // fp32 partials), then a second kernel adds the partials of all (b,h) of a group in fp64.
 // grid (nchunks, B*H, 2 tensors).  part: [2][B*H][nchunks][d*d + d].
 // ---------------------------------------------------------------------------------------------------
+template <int WD>
 __global__ void __launch_bounds__(NT) k_stats_partial(TensorDev X, TensorDev Yt, int Lx, int Ly, int H, int d,
                                                       float scale, int rows_per_chunk, int nchunks, float* part) {
   extern __shared__ float smem[];
@@ -852,20 +871,20 @@ __global__ void __launch_bounds__(NT) k_stats_partial(TensorDev X, TensorDev Yt,
   const TensorDev& T = which ? Yt : X;
   const int L = which ? Ly : Lx;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int nt = dpad / 16, ntiles = nt * nt;      // <= 64 tiles, 16 per wave
-  f32x4 acc[16];
+  const int nt = dpad / 16, ntiles = nt * nt;      // <= 4 WD^2 tiles
+  f32x4 acc[WD * WD];
 #pragma unroll
-  for (int t = 0; t < 16; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int t = 0; t < WD * WD; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
   float colsum = 0.f;
   const int row_end = min(L, (chunk + 1) * rows_per_chunk);
   for (int row0 = chunk * rows_per_chunk; row0 < row_end; row0 += TR) {
     __syncthreads();
-    load_rows(Xs, ld, T, b * T.sb + h * T.sh, row0, row_end, d, dpad, scale);
+    load_rows<WD>(Xs, ld, T, b * T.sb + h * T.sh, row0, row_end, d, dpad, scale);
     __syncthreads();
     if (threadIdx.x < d)
       for (int r = 0; r < TR; ++r) colsum += Xs[r * ld + threadIdx.x];
 #pragma unroll
-    for (int tl = 0; tl < 16; ++tl) {
+    for (int tl = 0; tl < WD * WD; ++tl) {
       const int t = w + 4 * tl;
       if (t < ntiles) {
         const int at = t / nt, bt = t - at * nt;
@@ -877,7 +896,7 @@ __global__ void __launch_bounds__(NT) k_stats_partial(TensorDev X, TensorDev Yt,
   }
   float* out = part + (((size_t)which * gridDim.y + bh) * nchunks + chunk) * ((size_t)d * d + d);
 #pragma unroll
-  for (int tl = 0; tl < 16; ++tl) {
+  for (int tl = 0; tl < WD * WD; ++tl) {
     const int t = w + 4 * tl;
     if (t < ntiles) {
       const int at = t / nt, bt = t - at * nt;
@@ -957,6 +976,7 @@ __global__ void k_bwd_ghat(TensorDev dY, float* buf, const float* den, int L, in
 //   out1 = F St          (key side only: its first nv columns are dV)
 //   dF   = A St^T,  dE = F * dF,  grad = scale (dE W / log2e + rowsum(dE) (C + C^T) x)
 // grid (ceil(L/32), B*H).
+template <int WD>
 __global__ void __launch_bounds__(NT) k_gen_bwd_side(GenSide sd, int side, TensorDev A, int a_cols, int append_ones, int L,
                                                      int H, int M, int d, int nv, int ldt, const float* St,
                                                      size_t state_stride, const uint32_t* kmax_u, const float* row_shift,
@@ -981,8 +1001,8 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_side(GenSide sd, int side, Tenso
   const float* Sb = St + (size_t)bh * state_stride;
   const int nvt = ldt / 16, ntiles = 2 * nvt, nct = dpad / 16 + ((dpad & 15) ? 1 : 0), ngt = 2 * nct;
 
-  load_rows(Xs, ld, sd.X, b * sd.X.sb + h * sd.X.sh, row0, L, d, dpad, sd.scale);
-  load_values(As, ldts, A, b * A.sb + h * A.sh, row0, L, a_cols, ldt, append_ones);
+  load_rows<WD>(Xs, ld, sd.X, b * sd.X.sb + h * sd.X.sh, row0, L, d, dpad, sd.scale);
+  load_values<WD>(As, ldts, A, b * A.sb + h * A.sh, row0, L, a_cols, ldt, append_ones);
   __syncthreads();
   if (side == 1) {
     row_terms_of(rterm, sd, bh, L, row0, L, Xs, ld, d, Cmat, sd.alpha);
@@ -992,15 +1012,15 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_side(GenSide sd, int side, Tenso
     rterm[threadIdx.x] = row0 + threadIdx.x < L ? -row_shift[(size_t)bh * L + row0 + threadIdx.x] : 0.f;
   }
 
-  f32x4 acc_o[ACC_PER_WAVE], acc_g[4];
+  f32x4 acc_o[ACC_V<WD, 4>], acc_g[ACC_D<WD, 4>];
 #pragma unroll
-  for (int t = 0; t < ACC_PER_WAVE; ++t) acc_o[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int t = 0; t < ACC_V<WD, 4>; ++t) acc_o[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int t = 0; t < 4; ++t) acc_g[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int t = 0; t < ACC_D<WD, 4>; ++t) acc_g[t] = f32x4{0.f, 0.f, 0.f, 0.f};
   float rs_part = 0.f;               // thread (row = tid / 8, part = tid % 8): its share of rowsum(dE)
 
-  WRegs<NT> wr;                          // the next step's blocks, fetched while the current one computes
-  ValTile<NT> tr;
+  WRegs<WD, NT> wr;                          // the next step's blocks, fetched while the current one computes
+  ValTile<WD, NT> tr;
   wblock_fetch(wr, W, bias, 0, M, d);
   sblock_fetch(tr, Sb, 0, M, ldt);
   for (int m0 = 0; m0 < M; m0 += MB) {
@@ -1036,7 +1056,7 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_side(GenSide sd, int side, Tenso
     __syncthreads();
     if (want_out1) {
 #pragma unroll
-      for (int tl = 0; tl < ACC_PER_WAVE; ++tl) {
+      for (int tl = 0; tl < ACC_V<WD, 4>; ++tl) {
         const int t = w + 4 * tl;
         if (t < ntiles) {
           const int rt = t & 1, vt = t >> 1;
@@ -1047,7 +1067,7 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_side(GenSide sd, int side, Tenso
       }
     }
 #pragma unroll
-    for (int tl = 0; tl < 4; ++tl) {
+    for (int tl = 0; tl < ACC_D<WD, 4>; ++tl) {
       const int t = w + 4 * tl;
       if (t < ngt) {
         const int rt = t & 1, ct = t >> 1;
@@ -1067,7 +1087,7 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_side(GenSide sd, int side, Tenso
   float* Gs = Ws;
   float* Os = Sts;
 #pragma unroll
-  for (int tl = 0; tl < 4; ++tl) {
+  for (int tl = 0; tl < ACC_D<WD, 4>; ++tl) {
     const int t = w + 4 * tl;
     if (t < ngt) {
       const int rt = t & 1, ct = t >> 1, col = ct * 16 + (lane & 15);
@@ -1079,7 +1099,7 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_side(GenSide sd, int side, Tenso
   }
   if (want_out1) {
 #pragma unroll
-    for (int tl = 0; tl < ACC_PER_WAVE; ++tl) {
+    for (int tl = 0; tl < ACC_V<WD, 4>; ++tl) {
       const int t = w + 4 * tl;
       if (t < ntiles) {
         const int rt = t & 1, vt = t >> 1;
@@ -1180,6 +1200,7 @@ __device__ __forceinline__ void bwd_store_grad(const TensorDev& grad, long long 
   }
 }
 
+template <int WD>
 __global__ void __launch_bounds__(NTC) k_gen_bwd_causal_q(GenSide qs, GenSide ks, TensorDev V, const float* ghat, int L,
                                                          int H, int M, int d, int nv, int ldt, int rows_per_seg, int nseg,
                                                          const uint32_t* kmax_u, const float* row_shift, float* Tstate,
@@ -1205,23 +1226,23 @@ __global__ void __launch_bounds__(NTC) k_gen_bwd_causal_q(GenSide qs, GenSide ks
   const int row_end = min(L, (seg + 1) * rows_per_seg);
   for (int row0 = seg * rows_per_seg; row0 < row_end; row0 += TR) {
     __syncthreads();
-    load_rows<NTC>(m.Qs, ld, qs.X, qbase, row0, row_end, d, dpad, qs.scale);
-    load_rows<NTC>(m.Ks, ld, ks.X, kbase, row0, row_end, d, dpad, ks.scale);
-    load_values<NTC>(m.Vs, ldv, V, b * V.sb + h * V.sh, row0, row_end, nv, ldt, 1);
-    load_values<NTC>(m.Gs, ldv, G, b * G.sb + h * G.sh, row0, row_end, ldt, ldt, 0);
+    load_rows<WD, NTC>(m.Qs, ld, qs.X, qbase, row0, row_end, d, dpad, qs.scale);
+    load_rows<WD, NTC>(m.Ks, ld, ks.X, kbase, row0, row_end, d, dpad, ks.scale);
+    load_values<WD, NTC>(m.Vs, ldv, V, b * V.sb + h * V.sh, row0, row_end, nv, ldt, 1);
+    load_values<WD, NTC>(m.Gs, ldv, G, b * G.sb + h * G.sh, row0, row_end, ldt, ldt, 0);
     if (threadIdx.x < TR) m.qsh[threadIdx.x] = row0 + threadIdx.x < row_end ? -row_shift[(size_t)bh * L + row0 + threadIdx.x] : 0.f;
     __syncthreads();
     row_terms_of(m.rterm, ks, bh, L, row0, row_end, m.Ks, ld, d, Cmat2, 0.f);
     bwd_causal_amat(m.As, m.Gs, m.Vs, ldv, lds, ldt);
 
-    f32x4 acc_g[2];
+    f32x4 acc_g[ACC_D<WD, 8>];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) acc_g[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < ACC_D<WD, 8>; ++t) acc_g[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     float rs_part = 0.f;
     // the three blocks of the next step are fetched while the current one computes (rows of the state that this step
     // writes are not among them)
-    WRegs<NTC> wa, wb;
-    ValTile<NTC> tr;
+    WRegs<WD, NTC> wa, wb;
+    ValTile<WD, NTC> tr;
     wblock_fetch(wa, W2, bias2, 0, M, d);
     sblock_fetch(tr, Tg, 0, M, ldt);
     wblock_fetch(wb, W1, bias1, 0, M, d);
@@ -1272,7 +1293,7 @@ __global__ void __launch_bounds__(NTC) k_gen_bwd_causal_q(GenSide qs, GenSide ks
       }
       __syncthreads();
 #pragma unroll
-      for (int tl = 0; tl < 2; ++tl) {
+      for (int tl = 0; tl < ACC_D<WD, 8>; ++tl) {
         const int t = w + 8 * tl;
         if (t < ngt) {
           const int rt = t & 1, ct = t >> 1;
@@ -1288,7 +1309,7 @@ __global__ void __launch_bounds__(NTC) k_gen_bwd_causal_q(GenSide qs, GenSide ks
       }
       // the state takes this chunk's keys (after its last use above): T[m][v] += sum_j Ss[j][m] Vs[j][v]
 #pragma unroll
-      for (int tl = 0; tl < ACC_PER_WAVE_C; ++tl) {
+      for (int tl = 0; tl < ACC_V<WD, 8>; ++tl) {
         const int t = w + 8 * tl;
         if (t < ntiles) {
           const int rt = t & 1, vt = t >> 1;
@@ -1307,7 +1328,7 @@ __global__ void __launch_bounds__(NTC) k_gen_bwd_causal_q(GenSide qs, GenSide ks
     __syncthreads();
     float* Gd = m.Ws;
 #pragma unroll
-    for (int tl = 0; tl < 2; ++tl) {
+    for (int tl = 0; tl < ACC_D<WD, 8>; ++tl) {
       const int t = w + 8 * tl;
       if (t < ngt) {
         const int rt = t & 1, ct = t >> 1, col = ct * 16 + (lane & 15);
@@ -1326,6 +1347,7 @@ __global__ void __launch_bounds__(NTC) k_gen_bwd_causal_q(GenSide qs, GenSide ks
   }
 }
 
+template <int WD>
 __global__ void __launch_bounds__(NTC) k_gen_bwd_causal_k(GenSide qs, GenSide ks, TensorDev V, const float* ghat, int L,
                                                          int H, int M, int d, int nv, int ldt, int rows_per_seg, int nseg,
                                                          const uint32_t* kmax_u, const float* row_shift, float* Rstate,
@@ -1352,26 +1374,26 @@ __global__ void __launch_bounds__(NTC) k_gen_bwd_causal_k(GenSide qs, GenSide ks
   for (int ch = nchunk - 1; ch >= 0; --ch) {
     const int row0 = row_beg + ch * TR;
     __syncthreads();
-    load_rows<NTC>(m.Qs, ld, qs.X, qbase, row0, row_end, d, dpad, qs.scale);
-    load_rows<NTC>(m.Ks, ld, ks.X, kbase, row0, row_end, d, dpad, ks.scale);
-    load_values<NTC>(m.Vs, ldv, V, b * V.sb + h * V.sh, row0, row_end, nv, ldt, 1);
-    load_values<NTC>(m.Gs, ldv, G, b * G.sb + h * G.sh, row0, row_end, ldt, ldt, 0);
+    load_rows<WD, NTC>(m.Qs, ld, qs.X, qbase, row0, row_end, d, dpad, qs.scale);
+    load_rows<WD, NTC>(m.Ks, ld, ks.X, kbase, row0, row_end, d, dpad, ks.scale);
+    load_values<WD, NTC>(m.Vs, ldv, V, b * V.sb + h * V.sh, row0, row_end, nv, ldt, 1);
+    load_values<WD, NTC>(m.Gs, ldv, G, b * G.sb + h * G.sh, row0, row_end, ldt, ldt, 0);
     if (threadIdx.x < TR) m.qsh[threadIdx.x] = row0 + threadIdx.x < row_end ? -row_shift[(size_t)bh * L + row0 + threadIdx.x] : 0.f;
     __syncthreads();
     row_terms_of(m.rterm, ks, bh, L, row0, row_end, m.Ks, ld, d, Cmat2, 0.f);
     bwd_causal_amat(m.As, m.Gs, m.Vs, ldv, lds, ldt);
 
-    f32x4 acc_o[ACC_PER_WAVE_C], acc_g[2];
+    f32x4 acc_o[ACC_V<WD, 8>], acc_g[ACC_D<WD, 8>];
 #pragma unroll
-    for (int t = 0; t < ACC_PER_WAVE_C; ++t) acc_o[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < ACC_V<WD, 8>; ++t) acc_o[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int t = 0; t < 2; ++t) acc_g[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < ACC_D<WD, 8>; ++t) acc_g[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     f32x4 sc = {0.f, 0.f, 0.f, 0.f};      // scores tile (query tile w>>1, key tile w&1)
     float rs_part = 0.f;
     // the three blocks of the next step are fetched while the current one computes (rows of the state that this step
     // writes are not among them)
-    WRegs<NTC> wa, wb;
-    ValTile<NTC> tr;
+    WRegs<WD, NTC> wa, wb;
+    ValTile<WD, NTC> tr;
     wblock_fetch(wa, W1, bias1, 0, M, d);
     sblock_fetch(tr, Rg, 0, M, ldt);
     wblock_fetch(wb, W2, bias2, 0, M, d);
@@ -1427,7 +1449,7 @@ __global__ void __launch_bounds__(NTC) k_gen_bwd_causal_k(GenSide qs, GenSide ks
       }
       __syncthreads();
 #pragma unroll
-      for (int tl = 0; tl < ACC_PER_WAVE_C; ++tl) {
+      for (int tl = 0; tl < ACC_V<WD, 8>; ++tl) {
         const int t = w + 8 * tl;
         if (t < ntiles) {
           const int rt = t & 1, vt = t >> 1;
@@ -1450,7 +1472,7 @@ __global__ void __launch_bounds__(NTC) k_gen_bwd_causal_k(GenSide qs, GenSide ks
         }
       }
 #pragma unroll
-      for (int tl = 0; tl < 2; ++tl) {
+      for (int tl = 0; tl < ACC_D<WD, 8>; ++tl) {
         const int t = w + 8 * tl;
         if (t < ngt) {
           const int rt = t & 1, ct = t >> 1;
@@ -1474,7 +1496,7 @@ __global__ void __launch_bounds__(NTC) k_gen_bwd_causal_k(GenSide qs, GenSide ks
     }
     __syncthreads();
 #pragma unroll
-    for (int tl = 0; tl < ACC_PER_WAVE_C; ++tl) {
+    for (int tl = 0; tl < ACC_V<WD, 8>; ++tl) {
       const int t = w + 8 * tl;
       if (t < ntiles) {
         const int rt = t & 1, vt = t >> 1;
@@ -1487,7 +1509,7 @@ __global__ void __launch_bounds__(NTC) k_gen_bwd_causal_k(GenSide qs, GenSide ks
     float* Gd = m.Ws;
     float* Os = m.Ts;
 #pragma unroll
-    for (int tl = 0; tl < 2; ++tl) {
+    for (int tl = 0; tl < ACC_D<WD, 8>; ++tl) {
       const int t = w + 8 * tl;
       if (t < ngt) {
         const int rt = t & 1, ct = t >> 1, col = ct * 16 + (lane & 15);
@@ -1498,7 +1520,7 @@ __global__ void __launch_bounds__(NTC) k_gen_bwd_causal_k(GenSide qs, GenSide ks
       }
     }
 #pragma unroll
-    for (int tl = 0; tl < ACC_PER_WAVE_C; ++tl) {
+    for (int tl = 0; tl < ACC_V<WD, 8>; ++tl) {
       const int t = w + 8 * tl;
       if (t < ntiles) {
         const int rt = t & 1, vt = t >> 1;
@@ -1551,6 +1573,14 @@ static int set_lds(const void* fn, size_t bytes) {
   return 0;
 }
 
+// The kernels' width for rows of d and values of ldt columns: the narrowest that holds both.
+template <class F>
+static int by_width(int d, int ldt, F launch) {
+  if (d <= 32 && ldt <= 64) return launch(std::integral_constant<int, 1>());
+  if (d <= 64 && ldt <= 96) return launch(std::integral_constant<int, 2>());
+  return launch(std::integral_constant<int, 4>());
+}
+
 int launch_prep(const float* theta, int groups, const float* Omega, int omega_groups, int pgroups, int B, int H,
                 int M, int d, float* W, uint16_t* Wbf, float* bias, hipStream_t st) {
   hipLaunchKernelGGL(k_prep, dim3((M + PREP_F - 1) / PREP_F, 2, pgroups), dim3(128), 0, st, theta, groups, Omega, omega_groups, pgroups, B, H,
@@ -1569,31 +1599,40 @@ int launch_fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t st) {
 int launch_gen_features(const TensorDev& X, int n, int d, float scale, float alpha, const float* W, const float* bias,
                         const float* theta, long long c_offset, int M, float* out, float* row_logscale,
                         hipStream_t st) {
-  const size_t lds = gen_lds_features(d);
-  if (int rc = set_lds((const void*)k_gen_features, lds)) return rc;
-  hipLaunchKernelGGL(k_gen_features, dim3((n + TR - 1) / TR), dim3(NT), lds, st, X, n, d, scale, alpha, W, bias, theta,
-                     c_offset, M, out, row_logscale);
-  FS_LAUNCH_CHECK();
-  return 0;
+  return by_width(d, 0, [&](auto width) -> int {
+    constexpr int WD = width();
+    const size_t lds = gen_lds_features(d);
+    if (int rc = set_lds((const void*)k_gen_features<WD>, lds)) return rc;
+    hipLaunchKernelGGL((k_gen_features<WD>), dim3((n + TR - 1) / TR), dim3(NT), lds, st, X, n, d, scale, alpha, W, bias, theta,
+                       c_offset, M, out, row_logscale);
+    FS_LAUNCH_CHECK();
+    return 0;
+  });
 }
 
 int launch_gen_kmax(const GenSide& ks, int Lk, int BH, int H, int M, int d, uint32_t* kmax_u, hipStream_t st) {
-  const size_t lds = gen_lds_features(d);
-  if (int rc = set_lds((const void*)k_gen_kmax, lds)) return rc;
-  hipLaunchKernelGGL(k_gen_kmax, dim3((Lk + TR - 1) / TR, BH), dim3(NT), lds, st, ks, Lk, H, M, d, kmax_u);
-  FS_LAUNCH_CHECK();
-  return 0;
+  return by_width(d, 0, [&](auto width) -> int {
+    constexpr int WD = width();
+    const size_t lds = gen_lds_features(d);
+    if (int rc = set_lds((const void*)k_gen_kmax<WD>, lds)) return rc;
+    hipLaunchKernelGGL((k_gen_kmax<WD>), dim3((Lk + TR - 1) / TR, BH), dim3(NT), lds, st, ks, Lk, H, M, d, kmax_u);
+    FS_LAUNCH_CHECK();
+    return 0;
+  });
 }
 
 int launch_gen_state(const GenSide& ks, const TensorDev& V, int Lk, int BH, int H, int M, int d, int nv,
                      int append_ones, int ldt, int rows_per_seg, int nseg, const uint32_t* kmax_u,
                      const float* row_shift, float* Tpart, hipStream_t st) {
-  const size_t lds = gen_lds_state(d, ldt);
-  if (int rc = set_lds((const void*)k_gen_state, lds)) return rc;
-  hipLaunchKernelGGL(k_gen_state, dim3(nseg, (M + MB - 1) / MB, BH), dim3(NT), lds, st, ks, V, Lk, H, M, d, nv,
-                     append_ones, ldt, rows_per_seg, nseg, kmax_u, row_shift, Tpart);
-  FS_LAUNCH_CHECK();
-  return 0;
+  return by_width(d, ldt, [&](auto width) -> int {
+    constexpr int WD = width();
+    const size_t lds = gen_lds_state(d, ldt);
+    if (int rc = set_lds((const void*)k_gen_state<WD>, lds)) return rc;
+    hipLaunchKernelGGL((k_gen_state<WD>), dim3(nseg, (M + MB - 1) / MB, BH), dim3(NT), lds, st, ks, V, Lk, H, M, d, nv,
+                       append_ones, ldt, rows_per_seg, nseg, kmax_u, row_shift, Tpart);
+    FS_LAUNCH_CHECK();
+    return 0;
+  });
 }
 
 int launch_gen_reduce(float* Tpart, int BH, int nseg, size_t per_state, int prefix, hipStream_t st) {
@@ -1607,12 +1646,15 @@ int launch_gen_reduce(float* Tpart, int BH, int nseg, size_t per_state, int pref
 int launch_gen_apply(const GenSide& qs, int Lq, int BH, int H, int M, int d, int nv, int ldt, const float* T,
                      size_t state_stride, const uint32_t* kmax_u, int matvec, const TensorDev& Y, float* den_out,
                      float* shift_out, hipStream_t st, unsigned* flushed) {
-  const size_t lds = gen_lds_apply(d, ldt);
-  if (int rc = set_lds((const void*)k_gen_apply, lds)) return rc;
-  hipLaunchKernelGGL(k_gen_apply, dim3((Lq + TR - 1) / TR, BH), dim3(NT), lds, st, qs, Lq, H, M, d, nv, ldt, T,
-                     state_stride, kmax_u, matvec, Y, den_out, shift_out, flushed);
-  FS_LAUNCH_CHECK();
-  return 0;
+  return by_width(d, ldt, [&](auto width) -> int {
+    constexpr int WD = width();
+    const size_t lds = gen_lds_apply(d, ldt);
+    if (int rc = set_lds((const void*)k_gen_apply<WD>, lds)) return rc;
+    hipLaunchKernelGGL((k_gen_apply<WD>), dim3((Lq + TR - 1) / TR, BH), dim3(NT), lds, st, qs, Lq, H, M, d, nv, ldt, T,
+                       state_stride, kmax_u, matvec, Y, den_out, shift_out, flushed);
+    FS_LAUNCH_CHECK();
+    return 0;
+  });
 }
 
 size_t gen_lds_bwd_side(int d, int ldt) {
@@ -1632,12 +1674,15 @@ int launch_gen_bwd_side(const GenSide& sd, int side, const TensorDev& A, int a_c
                         int H, int M, int d, int nv, int ldt, const float* St, size_t state_stride,
                         const uint32_t* kmax_u, const float* row_shift, const TensorDev& out1, int want_out1,
                         const TensorDev& grad, hipStream_t st) {
-  const size_t lds = gen_lds_bwd_side(d, ldt);
-  if (int rc = set_lds((const void*)k_gen_bwd_side, lds)) return rc;
-  hipLaunchKernelGGL(k_gen_bwd_side, dim3((L + TR - 1) / TR, BH), dim3(NT), lds, st, sd, side, A, a_cols, append_ones, L,
-                     H, M, d, nv, ldt, St, state_stride, kmax_u, row_shift, out1, want_out1, grad);
-  FS_LAUNCH_CHECK();
-  return 0;
+  return by_width(d, ldt, [&](auto width) -> int {
+    constexpr int WD = width();
+    const size_t lds = gen_lds_bwd_side(d, ldt);
+    if (int rc = set_lds((const void*)k_gen_bwd_side<WD>, lds)) return rc;
+    hipLaunchKernelGGL((k_gen_bwd_side<WD>), dim3((L + TR - 1) / TR, BH), dim3(NT), lds, st, sd, side, A, a_cols, append_ones, L,
+                       H, M, d, nv, ldt, St, state_stride, kmax_u, row_shift, out1, want_out1, grad);
+    FS_LAUNCH_CHECK();
+    return 0;
+  });
 }
 
 size_t gen_lds_bwd_causal(int d, int ldt) {
@@ -1649,27 +1694,33 @@ int launch_gen_bwd_causal(const GenSide& qs, const GenSide& ks, const TensorDev&
                           int M, int d, int nv, int ldt, int rows_per_seg, int nseg, const uint32_t* kmax_u,
                           const float* row_shift, float* Tstate, float* Rstate, const TensorDev& dQ, const TensorDev& dK,
                           const TensorDev& dV, hipStream_t st) {
-  const size_t lds = gen_lds_bwd_causal(d, ldt);
-  if (int rc = set_lds((const void*)k_gen_bwd_causal_q, lds)) return rc;
-  if (int rc = set_lds((const void*)k_gen_bwd_causal_k, lds)) return rc;
-  hipLaunchKernelGGL(k_gen_bwd_causal_q, dim3(nseg, BH), dim3(NTC), lds, st, qs, ks, V, ghat, L, H, M, d, nv, ldt,
-                     rows_per_seg, nseg, kmax_u, row_shift, Tstate, dQ);
-  FS_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_gen_bwd_causal_k, dim3(nseg, BH), dim3(NTC), lds, st, qs, ks, V, ghat, L, H, M, d, nv, ldt,
-                     rows_per_seg, nseg, kmax_u, row_shift, Rstate, dK, dV);
-  FS_LAUNCH_CHECK();
-  return 0;
+  return by_width(d, ldt, [&](auto width) -> int {
+    constexpr int WD = width();
+    const size_t lds = gen_lds_bwd_causal(d, ldt);
+    if (int rc = set_lds((const void*)k_gen_bwd_causal_q<WD>, lds)) return rc;
+    if (int rc = set_lds((const void*)k_gen_bwd_causal_k<WD>, lds)) return rc;
+    hipLaunchKernelGGL((k_gen_bwd_causal_q<WD>), dim3(nseg, BH), dim3(NTC), lds, st, qs, ks, V, ghat, L, H, M, d, nv, ldt,
+                       rows_per_seg, nseg, kmax_u, row_shift, Tstate, dQ);
+    FS_LAUNCH_CHECK();
+    hipLaunchKernelGGL((k_gen_bwd_causal_k<WD>), dim3(nseg, BH), dim3(NTC), lds, st, qs, ks, V, ghat, L, H, M, d, nv, ldt,
+                       rows_per_seg, nseg, kmax_u, row_shift, Rstate, dK, dV);
+    FS_LAUNCH_CHECK();
+    return 0;
+  });
 }
 
 int launch_gen_causal(const GenSide& qs, const GenSide& ks, const TensorDev& V, int L, int BH, int H, int M, int d,
                       int nv, int ldt, int rows_per_seg, int nseg, const uint32_t* kmax_u, float* Tstate,
                       const TensorDev& Y, float* den_out, float* shift_out, hipStream_t st, unsigned* flushed) {
-  const size_t lds = gen_lds_causal(d, ldt);
-  if (int rc = set_lds((const void*)k_gen_causal, lds)) return rc;
-  hipLaunchKernelGGL(k_gen_causal, dim3(nseg, BH), dim3(NTC), lds, st, qs, ks, V, L, H, M, d, nv, ldt, rows_per_seg,
-                     nseg, kmax_u, Tstate, Y, den_out, shift_out, flushed);
-  FS_LAUNCH_CHECK();
-  return 0;
+  return by_width(d, ldt, [&](auto width) -> int {
+    constexpr int WD = width();
+    const size_t lds = gen_lds_causal(d, ldt);
+    if (int rc = set_lds((const void*)k_gen_causal<WD>, lds)) return rc;
+    hipLaunchKernelGGL((k_gen_causal<WD>), dim3(nseg, BH), dim3(NTC), lds, st, qs, ks, V, L, H, M, d, nv, ldt, rows_per_seg,
+                       nseg, kmax_u, Tstate, Y, den_out, shift_out, flushed);
+    FS_LAUNCH_CHECK();
+    return 0;
+  });
 }
 
 int launch_stats(const TensorDev& X, const TensorDev& Y, int B, int H, int Lx, int Ly, int d, float scale, int groups,
@@ -1679,11 +1730,16 @@ int launch_stats(const TensorDev& X, const TensorDev& Y, int B, int H, int Lx, i
   } else if (stats_wide_supported(X, Y, d)) {
     if (int rc = launch_stats_wide(X, Y, B * H, H, Lx, Ly, scale, rows_per_chunk, nchunks, part, st)) return rc;
   } else {
-    const size_t lds = gen_lds_stats(d);
-    if (int rc = set_lds((const void*)k_stats_partial, lds)) return rc;
-    hipLaunchKernelGGL(k_stats_partial, dim3(nchunks, B * H, 2), dim3(NT), lds, st, X, Y, Lx, Ly, H, d, scale,
-                       rows_per_chunk, nchunks, part);
-    FS_LAUNCH_CHECK();
+    const int rc = by_width(d, 0, [&](auto width) -> int {
+      constexpr int WD = width();
+      const size_t lds = gen_lds_stats(d);
+      if (int rc = set_lds((const void*)k_stats_partial<WD>, lds)) return rc;
+      hipLaunchKernelGGL((k_stats_partial<WD>), dim3(nchunks, B * H, 2), dim3(NT), lds, st, X, Y, Lx, Ly, H, d, scale,
+                         rows_per_chunk, nchunks, part);
+      FS_LAUNCH_CHECK();
+      return 0;
+    });
+    if (rc) return rc;
   }
   const size_t total = (size_t)groups * 2 * ((size_t)d * d + d);
   hipLaunchKernelGGL(k_stats_final, dim3((unsigned)((total + 127) / 128)), dim3(128), 0, st, part, B, H, nchunks, d,

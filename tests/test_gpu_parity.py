@@ -59,6 +59,40 @@ def _check_attention(fs, Q, K, V, Omega, scale, causal, variant, dtype, chunk=0,
     return worst
 
 
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d,dv,M,L", [(32, 63, 1, 33), (32, 64, 32, 64), (33, 16, 33, 31), (64, 95, 64, 65), (64, 96, 65, 96),
+                                      (65, 32, 96, 1), (8, 128, 97, 40), (5, 3, 100, 129), (128, 128, 31, 70)])
+def test_general_path_at_edges_of_widths_and_feature_blocks(fs, d, dv, M, L, causal):
+    """The general kernels at the sizes where their width changes (d 32 | 33 and 64 | 65, values with the normaliser
+    column of 64 | 80 and 96 | 112 columns) and around whole feature blocks: the causal kernel finds row maxima two
+    blocks of 32 at a time, so M = 1, 31 - 33, 64, 65, 96, 97, 100 end in every way.  Forward and backward."""
+    import torch
+    rng = np.random.default_rng(d + 3 * dv + 7 * M)
+    dp, vp = (d + 3) // 4 * 4, (dv + 3) // 4 * 4
+    Q, K = 0.6 * rng.standard_normal((2, 1, 2, L, dp)).astype(np.float32)
+    V, dY = rng.standard_normal((2, 1, 2, L, vp)).astype(np.float32)
+    Om = rng.standard_normal((2, M, d)).astype(np.float32)
+    th = orc.fit_gerf(0.5 * rng.standard_normal((64, d)), 0.5 * rng.standard_normal((64, d)))
+    theta = torch.from_numpy(np.stack([util.theta_vec_from_oracle(th)] * 2)).cuda()
+    th = util.oracle_theta_from_vec(util.theta_vec_from_oracle(th), d)
+    s, Omd = d ** -0.25, torch.from_numpy(Om).cuda()
+    Qd, Kd, Vd, dYd = (torch.from_numpy(x).cuda()[..., :n] for x, n in ((Q, d), (K, d), (V, dv), (dY, dv)))
+    out = torch.empty((1, 2, L, vp), device="cuda")[..., :dv]
+    Y = util.to_host(fs.attention(theta, Qd, Kd, Vd, s, Omd, causal=causal, out=out))
+    gr = tuple(torch.empty((1, 2, L, n), device="cuda")[..., :m] for n, m in ((dp, d), (dp, d), (vp, dv)))
+    gr = [util.to_host(g) for g in fs.attention_backward(theta, Qd, Kd, Vd, dYd, s, Omd, causal=causal, grads=gr)]
+    for h in range(2):
+        args = (th, Om[h], Q[0, h, :, :d], K[0, h, :, :d], V[0, h, :, :dv])
+        fro, row = util.attention_errors(Y[0, h], orc.attention(*args, s, causal), V[0, h, :, :dv].astype(np.float64))
+        assert fro <= TOL["f32"] and row <= 4 * TOL["f32"], (h, fro, row)
+        ref = orc.attention_backward(*args, dY[0, h, :, :dv], s, causal)
+        # (the bar of the backward tests.  Gradients that are zero by construction, of Q with one feature, of Q and K with
+        # one key, are differences of dY . V and dY . Y: their rounding is measured against |dY| |V|)
+        floor = 1e-3 * float(np.linalg.norm(dY[0, h]) * np.linalg.norm(V[0, h, :, :dv], axis=1).max())
+        errs = [util.gradient_errors(g[0, h], r, floor) for g, r in zip(gr, ref)]
+        assert max(e[0] for e in errs) <= 3e-4 and max(e[1] for e in errs) <= 1.2e-3, (h, errs)
+
+
 @pytest.mark.parametrize("what", ["attention", "backward", "operator"])
 @pytest.mark.parametrize("L", [31, 33, 64])
 def test_ragged_tiles_of_long_keys(fs, what, L):
