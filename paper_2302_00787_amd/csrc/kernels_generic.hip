@@ -25,8 +25,8 @@ constexpr int NTC = 512;
 // Every kernel comes in three widths W: rows of at most 32 W columns and values of at most 32 NV (W = 1: 64, 2: 96,
 // 4: 144).  Registers of a tile and accumulators are counted for the width: with those of W = 4 for every d, two or three
 // waves of k_gen_state, k_gen_apply and k_gen_bwd_side fitted a SIMD, now four or five at d <= 32 and three or four at
-// d <= 64.  f32, M = 32 / 256: causal attention of 2048 sequences of 128 at d 8 302 -> 173 us, B2 H4 L4096 d64 311 ->
-// 278; backward pass of the 2048 sequences 426 -> 284 us non-causal, 874 -> 714 causal.
+// d <= 64.  f32: 2048 sequences of 128, d 8, M 32, attention 152 -> 106 us, causal 302 -> 175, their backward passes 425 ->
+// 258 and 873 -> 638; causal attention B2 H4 L4096 d64 M256 311 -> 278.
 template <int W> constexpr int NV = W == 4 ? 5 : W + 1;
 template <int W, int WAVES> constexpr int ACC_V = (4 * NV<W> + WAVES - 1) / WAVES;   // 16 x 16 tiles of 32 rows of values, per wave
 template <int W, int WAVES> constexpr int ACC_D = (4 * W + WAVES - 1) / WAVES;       // of 32 rows of a side
@@ -705,7 +705,7 @@ __global__ void __launch_bounds__(NT) k_gen_apply(GenSide qs, int Lq, int H, int
 // grid (nseg, B*H).
 // ---------------------------------------------------------------------------------------------------
 // (WD = 1: 129 registers by the compiler's own choice, one too many for two workgroups per CU; held to 128 without spills,
-// 2048 sequences of 128 at d 8 248 -> 173 us.  The backward kernels would spill 41 and 62 and get slower.)
+// 2048 sequences of 128 at d 8 248 -> 175 us.  The backward kernels would spill 41 and 62 and get slower.)
 template <int WD>
 __global__ void __launch_bounds__(NTC, WD == 1 ? 4 : 2) k_gen_causal(GenSide qs, GenSide ks, TensorDev V, int L, int H, int M, int d,
                                                    int nv, int ldt, int rows_per_seg, int nseg,
