@@ -111,7 +111,8 @@ int favorsharp_fit_params(int variant, const fs_tensor* X, const fs_tensor* Y,
  * The same fit without a host round trip (the paper names the eigendecomposition on accelerators as the
  * practical obstacle of the dense families, Section 4.3 and the discussion of limitations): the statistics scan and
  * the closed forms of the Theorems on ADERF / SDERF and of Sections 2.3, 3.1, 4.3 all run on the device, the
- * d x d decompositions as one-sided Jacobi iterations in fp64, one workgroup per group.
+ * d x d decompositions in fp64 (eigenproblems by tridiagonal reduction, the ADERF singular value problem by a one-sided
+ * Jacobi iteration), one workgroup per group.
  * Arguments as favorsharp_fit_params, plus
  *   status: device, `groups` int32 values, overwritten: FS_OK, or FS_ERR_NOT_PD for a group whose statistics are
  *           singular where ADERF / SADERF need them nonsingular (that group's theta is then left unwritten).

@@ -210,7 +210,7 @@ __device__ __forceinline__ void decompose_columns(double* g, int n, int k, FitSh
 // What bounds it is latency (one workgroup per matrix, a few matrices per call), so the design counts dependent steps:
 // the reduction has two barriers per column against two barriers per rotation round of a Jacobi iteration, which
 // needs (n - 1) x 6 - 8 rounds; everything after the reduction has no barrier per step at all.  Measured against a
-// two-sided Jacobi iteration (8 matrices of 64: k_fit_device 686 -> 108 us; 16 matrices of 128: 7290 -> 325 us).
+// two-sided Jacobi iteration (8 matrices of 64: k_fit_device 686 -> 107 us; 16 matrices of 128: 7290 -> 319 us).
 // ---------------------------------------------------------------------------------------------------
 
 // Gap between neighbouring eigenvalues (in units of the norm) below which vectors from twisted factorisations are not
@@ -284,7 +284,7 @@ __device__ __forceinline__ double max64(double v) {        // over the wave
 // every rotation; the rotations themselves are a serial chain, which each wave computes on a copy of the matrix of its own
 // (`mine`, 2 NP doubles): no barrier, no exchange.  The chain bounds it: about 1.1 n^2 rotations (fewer where blocks
 // split off), each 14 dependent fp64 operations, 110 - 150 ns.  Measured against a two-sided Jacobi iteration on the
-// original matrix, which is as orthogonal: fits of rank-2 rows, 8 heads, d 16 / 64 / 128 174 / 932 / 6933 -> 114 / 685 /
+// original matrix, which is as orthogonal: fits of rank-2 rows, 8 heads, d 16 / 64 / 128 155 / 874 / 6796 -> 114 / 685 /
 // 2303 us.  The eigenvalues, in no order, stay in mine[0 .. n).
 template <int NP>
 __device__ __forceinline__ void tridiagonal_qr(const f64x2* de, const double* es, int n, double* Z, double* mine) {

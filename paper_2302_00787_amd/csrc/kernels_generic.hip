@@ -65,7 +65,7 @@ __device__ __forceinline__ f32x4 mfma_chain(const float* ap, int sa, const float
 // loop that stores each element to LDS as it arrives is a chain of 16 - 18 memory latencies per tile, with one
 // workgroup per CU (LDS) to hide them; together with mfma_chain and the state update from the LDS copy this took
 // causal attention B2 H4 L4096 d64 M256 f32 from 704 to 405 us and the causal backward pass B1 H16 L4096 d128 M512
-// from 15.2 to 5.9 ms, bit for bit the same.  Addresses outside the tile are clamped into it, so that no load is
+// from 15.2 to 5.9 ms (388 us and 5.6 ms once k_prep was faster too), bit for bit the same.  Addresses outside the tile are clamped into it, so that no load is
 // conditional; the put writes zeros there.  The registers hold the raw bits (f32, or bf16 zero-extended).
 template <int NI, int TH> struct Tile { uint32_t v[TR * 32 / TH][NI]; };
 template <int NI, int TH>
