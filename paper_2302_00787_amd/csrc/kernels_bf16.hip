@@ -8,6 +8,7 @@
 #include <cstddef>
 
 #include "fast_pc.h"
+#include "fast_rows.h"
 #include "fast_state.h"
 
 namespace fs {
@@ -291,6 +292,41 @@ __global__ void k_fast_reduce(float* Tpart, const float* cpart, float* cstar, in
   if (!prefix) *(f32x4*)p = run;
 }
 
+// The sum of the slots of a (b,h) on their largest shift as the operand image that the non-causal query kernel holds in
+// LDS: a thread takes the eight numbers of lane l for the tiles (2 fb, vt) and (2 fb + 1, vt) (accumulator images of
+// 16 features x 16 columns) and writes them as bf16 in the place of slot 0's first four, which nobody else reads.  The
+// state a query workgroup fetches is 40 kB that way instead of 80.  grid (ceil(M*DVP/2048), B*H), block 256.
+__global__ void __launch_bounds__(256) k_fast_total(float* Tpart, const float* cpart, int nslot, int nvalid, unsigned* flushed) {
+  const int bh = blockIdx.y;
+  if (flushed != nullptr && (blockIdx.x | blockIdx.y | threadIdx.x) == 0) *flushed = 0u;
+  constexpr size_t per = (size_t)M * DVP;
+  const int piece = blockIdx.x * 256 + threadIdx.x, l = piece & 63, vt = (piece >> 6) % NVT, fb = piece / (64 * NVT);
+  const float* cp = cpart + (size_t)bh * nslot;
+  float cs = -INFINITY;
+  for (int s = 0; s < nvalid; ++s) cs = fmaxf(cs, cp[s]);
+  if (piece >= (M / 32) * NVT * 64) return;
+  float* p = Tpart + (size_t)bh * nslot * per + (size_t)(2 * fb * NVT + vt) * 256 + 4 * l;
+  f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
+  constexpr int NB = 4;
+  for (int s0 = 0; s0 < nvalid; s0 += NB) {
+    f32x4 v[NB], u[NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const int s = min(s0 + i, nvalid - 1);
+      v[i] = *(const f32x4*)(p + (size_t)s * per);
+      u[i] = *(const f32x4*)(p + (size_t)s * per + NVT * 256);
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+      if (s0 + i < nvalid) {
+        const float f = fast_exp2(cp[s0 + i] - cs);
+        lo += v[i] * f;
+        hi += u[i] * f;
+      }
+  }
+  *(bf16x8*)p = pack8(lo, hi);
+}
+
 // The same reduction for few sequences with many slots (one sequence of 262144 rows has 512 of them, and twenty
 // workgroups walking them one after the other take longer than the two kernels around them): the slots are cut into
 // ranges of R, one workgroup row per range.
@@ -373,119 +409,61 @@ __global__ void k_fast_reduce_walk(float* Tpart, const float* cpart, float* csta
 
 // ---------------------------------------------------------------------------------------------------
 // Query side of the non-causal contraction: Y = (P T) normalised by its last column (Sections 2.1, 2.2) for a block
-// of query rows; T = total state of the (b,h) (slot 0 of Tpart).  Four waves of 64 features; the partial output
-// tiles cross the waves as bf16 and are summed on the MFMA pipe.  The kernel needs a third of the LDS of the
-// key-side kernels and at most 256 registers, so two workgroups share a CU (two waves per SIMD: one's exp2 and
-// convert work beside the other's MFMAs and memory waits).  grid (nblk, B*H), block 256.
+// of query rows; T = total state of the (b,h) (slot 0 of Tpart).  All features in LDS, every wave takes its own rows
+// through them (fast_rows.h).  grid (nblk, B*H), block 512, one workgroup per CU.
 // ---------------------------------------------------------------------------------------------------
-// Rows [row_beg, row_end) of the queries of one (b,h) against the state image tb (T^T as A operand: row v = 16 vt + c,
-// k <-> features 64w + 32 mb + 16 (e/4) + 4g + e%4).  Returns the number of rows this wave finished with a zero
-// normaliser.
-__device__ __forceinline__ int apply_rows(const FastArgs& a, SmemApply& sm, int bh, const bf16x8 (&tb)[NVT][2], int row_beg,
-                                          int row_end) {
-  const int b = bh / a.H, h = bh % a.H;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = lane >> 4, c = lane & 15;
-  const int pg = group_of(a.pgroups, b, h, a.H);
+constexpr int NTA = 512;
+template <int NTT>
+__global__ void __launch_bounds__(NTA) k_fast_apply(FastArgs a, int Lq, int rows_per_blk, int nblk) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  rows::SmemOps& sm = *reinterpret_cast<rows::SmemOps*>(smem_raw);
+  const int id = rows::xcd_contiguous(blockIdx.x, gridDim.x), bh = id / nblk, blk = id - bh * nblk;
+  const int pg = group_of(a.pgroups, bh / a.H, bh % a.H, a.H);
   const float wmax = max256(a.wnorm + ((size_t)pg * 2) * M), amax = max256(a.bias + ((size_t)pg * 2) * M);
-  const uint16_t* Qb = (const uint16_t*)a.Q.ptr + b * a.Q.sb + h * a.Q.sh;
-  const long long ybase = b * a.Y.sb + h * a.Y.sh;
-  WSlice wq;
-  load_wslice(wq, a.Wbf + ((size_t)pg * 2) * M * D);
-  QBias qb;
-  load_qbias(qb, a.bias + ((size_t)pg * 2) * M, amax);
-  RowRegs qr;
-  load_rows_g(qr, Qb, a.Q.sl, row_beg, row_end);
-  store_query_rows(qr, sm, 0, wmax);
+  const int row_beg = blk * rows_per_blk, row_end = min(Lq, row_beg + rows_per_blk);
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // everything the first step needs is requested at once
+  rows::load_t_image<NTA>(sm, a.Tpart + (size_t)bh * a.nslot * M * DVP);
+  uint16_t* buf = (uint16_t*)(smem_raw + sizeof(rows::SmemOps)) + (size_t)w * (16 * NTT * D);
+  const int row0 = row_beg + 16 * NTT * w;
+  if (row0 < row_end)
+    rows::dma_rows<NTT>(buf, (const uint16_t*)a.Q.ptr + (bh / a.H) * a.Q.sb + (bh % a.H) * a.Q.sh + (long long)row0 * a.Q.sl, a.Q.sl,
+                        row_end - row0, lane);
+  rows::load_w_image<NTA>(sm, a.Wbf + ((size_t)pg * 2) * M * D, a.bias + ((size_t)pg * 2) * M, amax);
+  rows::dma_wait<0>();
   __syncthreads();
-  int buf = 0, nzero = 0;
-  for (int row0 = row_beg; row0 < row_end; row0 += TC, buf ^= 1) {
-    const bool more = row0 + TC < row_end;
-    if (more) load_rows_g(qr, Qb, a.Q.sl, row0 + TC, row_end);
-#pragma unroll
-    for (int it = 0; it < 4; ++it) {
-      bf16x8 p[2];
-      feature_tile<true>(wq, &qb, sm.q[buf], it, sm.qadd[buf][16 * it + c], p);
-      f32x4 y[NVT];
-#pragma unroll
-      for (int vt = 0; vt < NVT; ++vt) {
-        y[vt] = mfma(tb[vt][0], p[0], f32x4{0.f, 0.f, 0.f, 0.f});
-        y[vt] = mfma(tb[vt][1], p[1], y[vt]);
-      }
-      exchange_put_bf16(sm, y, it, w, lane);
-    }
-    __syncthreads();
-    // wave w sums the four partial tiles of token tile w, normalises and stores
-    {
-      f32x4 fs[4] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-      finish_tiles(fs, sm, w, 0, lane);
-      finish_tiles(fs, sm, w, 2, lane);
-      unsigned zt;
-      finish_norm(fs, sm, w, lane, &zt);
-      nzero += count_zero_tokens(zt, w, row_end - row0);
-      const int token = row0 + 16 * w + c;
-      if (token < row_end) {
-        if (a.Y.dtype == 1) {
-          uint16_t* yp = (uint16_t*)a.Y.ptr + ybase + (long long)token * a.Y.sl + 4 * g;
-#pragma unroll
-          for (int vt = 0; vt < 4; ++vt) *(bf16x4*)(yp + 16 * vt) = __builtin_convertvector(fs[vt], bf16x4);
-        } else {
-          float* yp = (float*)a.Y.ptr + ybase + (long long)token * a.Y.sl + 4 * g;
-#pragma unroll
-          for (int vt = 0; vt < 4; ++vt) *(f32x4*)(yp + 16 * vt) = fs[vt];
-        }
-      }
-    }
-    if (more) store_query_rows(qr, sm, buf ^ 1, wmax);
-    __syncthreads();
-  }
-  return nzero;
-}
-
-__global__ void __launch_bounds__(NT, 2) k_fast_apply(FastArgs a, int Lq, int rows_per_blk) {
-  __shared__ SmemApply sm;
-  const int blk = blockIdx.x, bh = blockIdx.y;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  bf16x8 tb[NVT][2];
-  const float* Tg = a.Tpart + (size_t)bh * a.nslot * M * DVP;
-#pragma unroll
-  for (int vt = 0; vt < NVT; ++vt)
-#pragma unroll
-    for (int mb = 0; mb < 2; ++mb) {
-      // accumulator images of tiles (2 mb, vt) and (2 mb + 1, vt) of wave w (the forward state pass writes images)
-      const f32x4 lo = *(const f32x4*)(Tg + (size_t)((w * 4 + 2 * mb) * NVT + vt) * 256 + 4 * lane);
-      const f32x4 hi = *(const f32x4*)(Tg + (size_t)((w * 4 + 2 * mb + 1) * NVT + vt) * 256 + 4 * lane);
-      tb[vt][mb] = pack8(lo, hi);
-    }
-  const int row_beg = blk * rows_per_blk;
-  const int nzero = apply_rows(a, sm, bh, tb, row_beg, min(Lq, row_beg + rows_per_blk));
-  report_zero_rows(a.flushed, nzero, lane);
+  const int nzero = rows::apply_rows<NTT, NTA / 64, true>(a, sm, buf, wmax, bh, row_beg, row_end);
+  report_zero_rows(a.flushed, nzero, threadIdx.x & 63);
 }
 
 // ---------------------------------------------------------------------------------------------------
 // Non-causal call, one workgroup per (b,h): the state of all keys, then all query rows against it, the state never
-// leaving the registers (with many short sequences the states' way through memory, 80 kB each written and read
+// leaving the chip (with many short sequences the states' way through memory, 80 kB each written and read
 // again, outweighs the rows themselves: a sequence of 128 tokens is 64 kB of Q, K, V, Y).  The shift of the state
 // cancels in the normalised rows.  grid (B*H), block 256, two workgroups per CU.
 // ---------------------------------------------------------------------------------------------------
 union SmemWhole {
   SmemState s;
-  SmemApply q;
+  rows::SmemOps q;
 };
 
+template <int NTT>
 __global__ void __launch_bounds__(NT, 2) k_fast_whole(FastArgs a, int Lq) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const int bh = blockIdx.x, lane = threadIdx.x & 63;
-  bf16x8 tb[NVT][2];
+  const int bh = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int pg = group_of(a.pgroups, bh / a.H, bh % a.H, a.H);
+  rows::SmemOps& sm = *reinterpret_cast<rows::SmemOps*>(smem_raw);
   {
     f32x4 T[4][NVT];
     float dk;
     state_rows(a, *reinterpret_cast<SmemState*>(smem_raw), bh, 0, a.L, T, dk);
-#pragma unroll
-    for (int vt = 0; vt < NVT; ++vt)
-#pragma unroll
-      for (int mb = 0; mb < 2; ++mb) tb[vt][mb] = pack8(T[2 * mb][vt], T[2 * mb + 1][vt]);
+    rows::put_t_image(sm, T, w, lane);
   }
-  const int nzero = apply_rows(a, *reinterpret_cast<SmemApply*>(smem_raw), bh, tb, 0, Lq);
+  const float wmax = max256(a.wnorm + ((size_t)pg * 2) * M), amax = max256(a.bias + ((size_t)pg * 2) * M);
+  rows::load_w_image<NT>(sm, a.Wbf + ((size_t)pg * 2) * M * D, a.bias + ((size_t)pg * 2) * M, amax);
+  rows::dma_wait<0>();
+  __syncthreads();
+  const int nzero = rows::apply_rows<NTT, NT / 64, false>(a, sm, nullptr, wmax, bh, 0, Lq);
   report_zero_rows(a.flushed, nzero, lane);
 }
 
@@ -494,8 +472,16 @@ __global__ void __launch_bounds__(NT, 2) k_fast_whole(FastArgs a, int Lq) {
 // ---------------------------------------------------------------------------------------------------
 #define FS_LAUNCH_CHECK() do { if (hipGetLastError() != hipSuccess) return 5; } while (0)
 
-// Largest dynamic / static LDS request of the forward kernels of this path (the causal kernel's is the largest).
-size_t fast_lds_bytes() { return std::max({sizeof(SmemState), sizeof(SmemApply), fast_causal_lds_bytes()}); }
+static int allow_lds(const void* kernel, size_t bytes) {
+  if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess) return 0;
+  (void)hipGetLastError();
+  return 2;
+}
+
+// k_fast_apply: the operand images and 16 ntt rows per wave.
+static size_t apply_lds_bytes(int ntt) { return sizeof(rows::SmemOps) + (size_t)(NTA / 64) * 16 * ntt * D * sizeof(uint16_t); }
+// Largest dynamic LDS request of the forward kernels of this path.
+size_t fast_lds_bytes() { return std::max({sizeof(SmemState), sizeof(SmemWhole), apply_lds_bytes(4), fast_causal_lds_bytes()}); }
 
 bool fast_supported(int dtype, int d, int dv, int M_) { return dtype == 1 && d == D && dv == D && M_ == M; }
 
@@ -632,7 +618,8 @@ static int launch_fast_state_pass(const FastLaunch& f, FastArgs& a, hipStream_t 
     FS_LAUNCH_CHECK();
     if (prefix == 0) {
       // the sum of everything ends in range 0 of the scratch buffer: the query-side kernel reads it there
-      hipLaunchKernelGGL(k_fast_reduce, dim3(nblk, BH), dim3(256), 0, st, f.rscr, f.cscr, f.cstar, Z, Zvalid, 0, 1, f.flushed);
+      if (images) hipLaunchKernelGGL(k_fast_total, dim3((M * DVP / 8 + 255) / 256, BH), dim3(256), 0, st, f.rscr, f.cscr, Z, Zvalid, f.flushed);
+      else hipLaunchKernelGGL(k_fast_reduce, dim3(nblk, BH), dim3(256), 0, st, f.rscr, f.cscr, f.cstar, Z, Zvalid, 0, 1, f.flushed);
       FS_LAUNCH_CHECK();
       a.Tpart = f.rscr;
       a.nslot = Z;
@@ -646,8 +633,11 @@ static int launch_fast_state_pass(const FastLaunch& f, FastArgs& a, hipStream_t 
     }
     return 0;
   }
-  hipLaunchKernelGGL(k_fast_reduce, dim3(nblk, BH), dim3(256), 0, st, f.Tpart, f.cpart, f.cstar, a.nslot, nstate, prefix,
-                     every_slot ? 1 : f.sub, f.flushed);
+  if (images && prefix == 0)
+    hipLaunchKernelGGL(k_fast_total, dim3((M * DVP / 8 + 255) / 256, BH), dim3(256), 0, st, f.Tpart, f.cpart, a.nslot, nstate, f.flushed);
+  else
+    hipLaunchKernelGGL(k_fast_reduce, dim3(nblk, BH), dim3(256), 0, st, f.Tpart, f.cpart, f.cstar, a.nslot, nstate, prefix,
+                       every_slot ? 1 : f.sub, f.flushed);
   FS_LAUNCH_CHECK();
   return 0;
 }
@@ -686,12 +676,15 @@ int launch_fast_attention(const FastLaunch& f, hipStream_t st, hipEvent_t ev_beg
   FastArgs a;
   const int BH = f.B * f.H;
   if (!f.causal && fast_whole_sequences(BH, f.Lq, f.Lk)) {
-    static_assert(sizeof(SmemWhole) <= 65536, "k_fast_whole: two workgroups per CU");
+    static_assert(2 * sizeof(SmemWhole) <= 160 * 1024, "k_fast_whole: two workgroups per CU");
     if (int rc = launch_fast_constants(f, a, st, false)) return rc;
     if (f.flushed != nullptr)
       if (int rc = launch_fill_u32((uint32_t*)f.flushed, 0u, 1, st)) return rc;
-    if (ev_begin || ev_end) hipExtLaunchKernelGGL(k_fast_whole, dim3(BH), dim3(NT), sizeof(SmemWhole), st, ev_begin, ev_end, 0, a, f.Lq);
-    else hipLaunchKernelGGL(k_fast_whole, dim3(BH), dim3(NT), sizeof(SmemWhole), st, a, f.Lq);
+    // four waves: two row tiles each as long as one step takes the whole sequence, else four
+    auto kernel = f.Lq <= 128 ? k_fast_whole<2> : k_fast_whole<4>;
+    if (int rc = allow_lds((const void*)kernel, sizeof(SmemWhole))) return rc;
+    if (ev_begin || ev_end) hipExtLaunchKernelGGL(kernel, dim3(BH), dim3(NT), sizeof(SmemWhole), st, ev_begin, ev_end, 0, a, f.Lq);
+    else hipLaunchKernelGGL(kernel, dim3(BH), dim3(NT), sizeof(SmemWhole), st, a, f.Lq);
     FS_LAUNCH_CHECK();
     return 0;
   }
@@ -700,12 +693,19 @@ int launch_fast_attention(const FastLaunch& f, hipStream_t st, hipEvent_t ev_beg
   if (f.causal) {
     if (int rc = launch_fast_causal_kernel(a, BH, st, ev_begin, ev_end)) return rc;
   } else {
-    // two workgroups per CU: about 512 blocks in all, whole chunks each
-    const int want = std::max(1, std::min((512 + BH - 1) / BH, (f.Lq + TC - 1) / TC));
-    const int rows_per_blk = (((f.Lq + want - 1) / want) + TC - 1) / TC * TC;
+    // row tiles of 16 per wave: as many as leave the chip's 2048 waves a step each (few rows: latency counts, and the LDS
+    // rate that narrow steps need is there); one workgroup per CU, whole steps each
+    const long long tiles = (long long)BH * ((f.Lq + 15) / 16);
+    const int ntt = tiles >= 4 * 2048 ? 4 : tiles >= 2 * 2048 ? 2 : 1;
+    auto kernel = ntt == 4 ? k_fast_apply<4> : ntt == 2 ? k_fast_apply<2> : k_fast_apply<1>;
+    const int step = 16 * ntt * (NTA / 64) / 2;      // at least four of the eight waves have a step
+    const int want = std::max(1, std::min((256 + BH - 1) / BH, (f.Lq + step - 1) / step));
+    const int rows_per_blk = (((f.Lq + want - 1) / want) + step - 1) / step * step;
     const int nblk = (f.Lq + rows_per_blk - 1) / rows_per_blk;
-    if (ev_begin || ev_end) hipExtLaunchKernelGGL(k_fast_apply, dim3(nblk, BH), dim3(NT), 0, st, ev_begin, ev_end, 0, a, f.Lq, rows_per_blk);
-    else hipLaunchKernelGGL(k_fast_apply, dim3(nblk, BH), dim3(NT), 0, st, a, f.Lq, rows_per_blk);
+    const size_t lds = apply_lds_bytes(ntt);
+    if (int rc = allow_lds((const void*)kernel, lds)) return rc;
+    if (ev_begin || ev_end) hipExtLaunchKernelGGL(kernel, dim3(nblk * BH), dim3(NTA), lds, st, ev_begin, ev_end, 0, a, f.Lq, rows_per_blk, nblk);
+    else hipLaunchKernelGGL(kernel, dim3(nblk * BH), dim3(NTA), lds, st, a, f.Lq, rows_per_blk, nblk);
     FS_LAUNCH_CHECK();
   }
   return 0;

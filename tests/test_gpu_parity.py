@@ -712,6 +712,37 @@ def test_bf16_path_non_causal_whole_sequences_per_workgroup(fs, variant, B, H, L
           f"worst row {worst[1]:.2e}")
 
 
+@pytest.mark.parametrize("H,Lq,Lk", [(1, 1, 65), (3, 15, 700), (1, 17, 300), (2, 129, 1000), (1, 4097, 129),      # one row tile per wave
+                                     (33, 1999, 130), (70, 1121, 1030),                                          # two
+                                     (130, 1037, 193), (40, 4099, 100),                                          # four
+                                     (385, 128, 31), (385, 129, 70), (388, 1, 1)])                               # whole sequences
+def test_bf16_path_non_causal_row_tiles(fs, H, Lq, Lk):
+    """The query side in each of its row-tile widths, with remainders of tiles, steps and workgroups; a few query rows
+    are so long that their waves take the shifted form of the features.  Reference: float64 on the same bf16 inputs and
+    the kernels' bf16 projection matrices (an exponent of 40 carries their rounding as 0.1: conditioning, not error)."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(H + Lq + Lk)
+    Q, K, V = (torch.randn((1, H, L, 64), generator=gen, device="cuda") for L in (Lq, Lk, Lk))
+    Q[:, :, 5::131] *= 4.0
+    Q, K, V = (x.bfloat16() for x in (Q, K, V))
+    Om = torch.randn((1, 256, 64), generator=gen, device="cuda")
+    th = orc.fit_gerf(0.35 * np.random.default_rng(1).standard_normal((64, 64)), 0.35 * np.random.default_rng(2).standard_normal((64, 64)))
+    vec = util.theta_vec_from_oracle(th)
+    th, s = util.oracle_theta_from_vec(vec, 64), 64 ** -0.25
+    Y = fs.attention(torch.from_numpy(vec[None]).cuda(), Q, K, V, s, Om)
+    assert torch.isfinite(Y.float()).all()
+    log2e = float(np.log2(np.e))
+    W1, W2 = ((log2e * s * (Om[0] @ torch.from_numpy(Bm).float().cuda())).bfloat16().double() for Bm in (th.B1, th.B2))
+    bias = (Om[0].double() ** 2) @ torch.from_numpy(th.A).cuda()
+    for h in sorted({0, H // 2, H - 1}):
+        q, k, v = Q[0, h].double(), K[0, h].double(), V[0, h].double()
+        E1, E2 = q @ W1.T + log2e * bias, k @ W2.T + log2e * (bias - 0.5 * s * s * (k * k).sum(1, keepdim=True))
+        P, S = torch.exp2(E1 - E1.max(1, keepdim=True).values), torch.exp2(E2 - E2.max())
+        den = P @ S.sum(0)
+        fro, row = util.attention_errors(Y[0, h].double().cpu().numpy(), ((P @ (S.T @ v)) / den[:, None]).cpu().numpy(), v.cpu().numpy())
+        assert fro <= TOL["bf16"] and row <= 4 * TOL["bf16"], (h, fro, row)
+
+
 @pytest.mark.parametrize("variant,L", [("sderf", 128), ("aderf", 100), ("gerf", 333)])
 def test_bf16_path_causal_many_short_sequences(fs, variant, L):
     """Causal calls with 256 sequences or more are one segment per sequence: no state pass and no reduction run, the
