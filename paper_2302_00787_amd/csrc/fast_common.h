@@ -165,8 +165,8 @@ __device__ __forceinline__ bf16x8 load_vop_tr(const uint16_t (*v)[LDV], int jp, 
 }
 
 // The constant columns 64 .. 79 of `rows` value rows: a one, then zeros (the staging writes columns 0 .. 63 only).
-__device__ __forceinline__ void init_value_pad(uint16_t (*v)[LDV], int rows, int nthreads) {
-  for (int idx = threadIdx.x; idx < rows * (LDV - D); idx += nthreads) {
+__device__ __forceinline__ void init_value_pad(uint16_t (*v)[LDV], int rows, int nthreads, int tid = threadIdx.x) {
+  for (int idx = tid; idx < rows * (LDV - D); idx += nthreads) {
     const int row = idx / (LDV - D), col = idx % (LDV - D);
     v[row][D + col] = col == 0 ? 0x3f80 : 0;
   }
@@ -269,8 +269,8 @@ struct QBias {
   f32x4 b[4];          // 2 (bias - largest bias) of features 64w + 16mt + 4g + r
 };
 
-__device__ __forceinline__ void load_wslice(WSlice& ws, const uint16_t* Wbf) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = lane >> 4, c = lane & 15;
+__device__ __forceinline__ void load_wslice(WSlice& ws, const uint16_t* Wbf, int w = threadIdx.x >> 6) {
+  const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
 #pragma unroll
   for (int mt = 0; mt < 4; ++mt)
 #pragma unroll

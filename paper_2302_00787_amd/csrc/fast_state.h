@@ -21,7 +21,10 @@ using namespace fast;
 // contracts chunk c, and stores the value rows of chunk c+1 and the key rows of chunk c+2.  The largest bound of a
 // chunk is gathered with an LDS float maximum, so the chunk starts with one broadcast read instead of a reduction.
 // A wave executes in order, so every LDS read of a chunk is issued at the top of the iteration, ahead of the MFMA
-// and exp2 streams that consume them.
+// and exp2 streams that consume them.  What bounds the loop is the sum of both streams: 74 MFMAs of 16 cycles and about
+// 1050 cycles of vector work per wave and chunk, of which little overlaps between the two waves of a SIMD (4750 cycles
+// per chunk for both, measured).  B8 H8 L4096: state and reduction 40 -> 29 us with the interleaving, the loads ahead of
+// the constants and one state per two groups of waves (k_fast_state2).
 // ---------------------------------------------------------------------------------------------------
 struct SmemState {
   uint16_t k[3][TC][LDR];                                   // key rows of three consecutive chunks
@@ -34,31 +37,19 @@ struct SmemState {
 // (wave w: features 64w .. 64w+63 x 80 columns) on the shift dk.  Ends behind a barrier: the caller may reuse the LDS.
 // BOUND_ONLY: nothing but dk, the largest bound of the rows (the shift such a state would have): no projections, no
 // values, T untouched.
+// A workgroup of 512 threads calls it with two row ranges, one per group of four waves, each group with an LDS struct of
+// its own and both with the same `niter`, the number of chunks of the longer range (the barriers are the workgroup's).
 template <bool BOUND_ONLY = false>
-__device__ __forceinline__ void state_rows(const FastArgs& a, SmemState& sm, int bh, int row_beg, int row_end,
+__device__ __forceinline__ void state_rows(const FastArgs& a, SmemState& sm, int bh, int row_beg, int row_end, int niter,
                                            f32x4 (&T)[4][NVT], float& dk) {
   const int b = bh / a.H, h = bh % a.H;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, g = lane >> 4, c = lane & 15;
+  const int tid = threadIdx.x & (NT - 1), lane = tid & 63, w = tid >> 6, g = lane >> 4, c = lane & 15;
   const int pg = group_of(a.pgroups, b, h, a.H);
   const float* th = a.theta + (size_t)group_of(a.groups, b, h, a.H) * (FS_THETA_HEADER_ + (size_t)D + 4 * (size_t)D * D);
-  const bool isoC = ((int)th[2]) & 1;
-  const float wmax = max256(a.wnorm + ((size_t)pg * 2 + 1) * M);
   const uint16_t* Kb = (const uint16_t*)a.K.ptr + b * a.K.sb + h * a.K.sh + (long long)row_beg * a.K.sl;
   const uint16_t* Vb = (const uint16_t*)a.V.ptr + b * a.V.sb + h * a.V.sh + (long long)row_beg * a.V.sl;
   const float* rkb = a.rk + (size_t)bh * a.L + row_beg;
   const int nrows = row_end - row_beg;
-
-  WSlice wk;
-  if (!BOUND_ONLY) {
-    load_wslice(wk, a.Wbf + ((size_t)pg * 2 + 1) * M * D);
-    init_value_pad(sm.v[0], 2 * TC, NT);
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-      for (int vt = 0; vt < NVT; ++vt) T[mt][vt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
-  if (tid < 3) sm.kmax[tid] = -INFINITY;
-  dk = -INFINITY;
 
   // staging: thread -> rows tid/8 and tid/8 + 32 of a chunk, bytes 16 (tid%8); rows past the end read as zero
   // (a fresh descriptor per chunk: uniform base = the chunk's first row, 32-bit offsets inside the chunk)
@@ -84,6 +75,26 @@ __device__ __forceinline__ void state_rows(const FastArgs& a, SmemState& sm, int
 #pragma unroll
     for (int i = 0; i < 2; ++i) *(u32x4*)(&sm.v[vb][srow + 32 * i][spc * 8]) = vr[i];
   };
+  // the first two chunks' key rows and the first chunk's value rows are requested ahead of everything else: the constants
+  // arrive meanwhile (one memory latency at the start of the kernel instead of three in a row)
+  load_k(0);
+  load_v(0);
+  const u32x4 k0[2] = {kr[0], kr[1]};
+  load_k(TC);
+  WSlice wk;
+  if (!BOUND_ONLY) {
+    load_wslice(wk, a.Wbf + ((size_t)pg * 2 + 1) * M * D, w);
+    init_value_pad(sm.v[0], 2 * TC, NT, tid);
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+      for (int vt = 0; vt < NVT; ++vt) T[mt][vt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  const float wmax = max256(a.wnorm + ((size_t)pg * 2 + 1) * M);
+  const bool isoC = ((int)th[2]) & 1;
+  if (tid < 3) sm.kmax[tid] = -INFINITY;
+  dk = -INFINITY;
+
   // Per-token constants of token tile w of a chunk (first row r0 of the slot) from the squared norms n2 of its rows
   // (valid in the lanes (g, c) = (c / 4, c)): row terms to kadd[cb], the largest bound into kmax[mb].
   // (`rkv`: the token's row term from memory, for parameter sets with a dense C2: requested by the caller ahead of time)
@@ -105,25 +116,30 @@ __device__ __forceinline__ void state_rows(const FastArgs& a, SmemState& sm, int
   };
   auto tile_op = [&](int kb, int jt, int ks) { return *(const bf16x8*)(&sm.k[kb][16 * jt + c][32 * ks + 8 * g]); };
 
-  // the first two chunks' key rows and the first chunk's value rows in one round trip
-  {
-    load_k(0);
-    load_v(0);
-    const u32x4 k0[2] = {kr[0], kr[1]};
-    load_k(TC);
-    store_k(1);
-    kr[0] = k0[0]; kr[1] = k0[1];
-    store_k(0);
-    store_v(0);
-  }
+  store_k(1);
+  kr[0] = k0[0]; kr[1] = k0[1];
+  store_k(0);
+  store_v(0);
   __syncthreads();
   constants(tile_row_norms(tile_op(0, w, 0), tile_op(0, w, 1), lane), row_term_of(0), 0, 0, 0);
   load_v(TC);
   load_k(2 * TC);
   __syncthreads();
 
+  // The second half of a chunk's state update is left for the next iteration, where its matrix instructions cover the
+  // LDS reads behind the barrier; the exponentials of a token pair are interleaved with the matrix instructions beside
+  // them (a wave issues in order: left to the compiler they came in runs of 32 and more).
+  // (Zero operands ahead of the first chunk: a test for it would make the compiler peel the loop, with registers for both.)
+  const bf16x8 zero8 = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
+  bf16x8 st1[4] = {zero8, zero8, zero8, zero8}, vop1[NVT] = {zero8, zero8, zero8, zero8, zero8};
+  auto update1 = [&]() {
+#pragma unroll
+    for (int vt = 0; vt < NVT; ++vt)
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt) T[mt][vt] = mfma(st1[mt], vop1[vt], T[mt][vt]);
+  };
   int kcur = 0, knext = 1, kfree = 2;
-  for (int r0 = 0, ci = 0; r0 < nrows; r0 += TC, ++ci) {
+  for (int r0 = 0, ci = 0; ci < niter; r0 += TC, ++ci) {
     const int cb = ci & 1;
     if constexpr (BOUND_ONLY) {
       // the constants of the next chunk and the running maximum only
@@ -140,62 +156,74 @@ __device__ __forceinline__ void state_rows(const FastArgs& a, SmemState& sm, int
       const int t = kcur; kcur = knext; knext = kfree; kfree = t;
       continue;
     }
-    // ---- every LDS read of the chunk, up front
-    const float dnew = sm.kmax[kcur];
-    bf16x8 x[4][KS];
-    f32x4 kadd4[4];
-#pragma unroll
-    for (int jt = 0; jt < 4; ++jt) {
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) x[jt][ks] = tile_op(kcur, jt, ks);
-      kadd4[jt] = *(const f32x4*)(&sm.kadd[cb][16 * jt + 4 * g]);
-    }
-    const bf16x8 xn0 = tile_op(knext, w, 0), xn1 = tile_op(knext, w, 1);     // token tile w of the next chunk
+    float n2 = 0.f;
     const float rk_next = row_term_of(r0 + TC);      // (dense C2) requested here, used at the end of the iteration
-    // ---- running key shift: the state is rebased when the chunk's largest bound exceeds the current shift
-    if (dnew > dk) {
-      const float f = fast_exp2(dk - dnew);
+    if (r0 < nrows) {          // (always, but for the last chunk of the shorter of two ranges)
+      // ---- every LDS read of the projections, up front
+      const float dnew = sm.kmax[kcur];
+      bf16x8 x[4][KS];
+      f32x4 kadd4[4];
 #pragma unroll
-      for (int mt = 0; mt < 4; ++mt)
+      for (int jt = 0; jt < 4; ++jt) {
+        kadd4[jt] = *(const f32x4*)(&sm.kadd[cb][16 * jt + 4 * g]);
 #pragma unroll
-        for (int vt = 0; vt < NVT; ++vt) T[mt][vt] *= f;
-      dk = dnew;
-    }
-    // ---- projections of both token pairs (32 MFMAs); the value operands are requested behind them, the exp2 /
-    // convert stream of a pair runs beside the MFMAs of the other one
-    f32x4 acc[2][4][2];            // [pair][feature tile][tile of the pair]
-    bf16x8 vop[2][NVT];
-#pragma unroll
-    for (int jp = 0; jp < 2; ++jp) {
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj) {
-          acc[jp][mt][jj] = mfma(x[2 * jp + jj][0], wk.w[mt][0], kadd4[2 * jp + jj] - dk);
-#pragma unroll
-          for (int ks = 1; ks < KS; ++ks) acc[jp][mt][jj] = mfma(x[2 * jp + jj][ks], wk.w[mt][ks], acc[jp][mt][jj]);
-        }
-      if (jp == 0) {
-#pragma unroll
-        for (int vt = 0; vt < NVT; ++vt) vop[0][vt] = load_vop_tr(sm.v[cb], 0, vt, lane);
+        for (int ks = 0; ks < KS; ++ks) x[jt][ks] = tile_op(kcur, jt, ks);
       }
-    }
-    const float n2 = tile_row_norms(xn0, xn1, lane);
-    if (tid == 0) sm.kmax[kfree] = -INFINITY;    // last read in the previous iteration, gathered again in the next one
+      const bf16x8 xn0 = tile_op(knext, w, 0), xn1 = tile_op(knext, w, 1);     // token tile w of the next chunk
+      __builtin_amdgcn_sched_barrier(0);
+      update1();
+      __builtin_amdgcn_sched_barrier(0);
+      // ---- running key shift: the state is rebased when the chunk's largest bound exceeds the current shift
+      if (dnew > dk) {
+        const float f = fast_exp2(dk - dnew);
 #pragma unroll
-    for (int jp = 0; jp < 2; ++jp) {
-      bf16x8 st[4];
+        for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-      for (int mt = 0; mt < 4; ++mt) st[mt] = pack8(exp2v(acc[jp][mt][0]), exp2v(acc[jp][mt][1]));
-      if (jp == 0) {
-#pragma unroll
-        for (int vt = 0; vt < NVT; ++vt) vop[1][vt] = load_vop_tr(sm.v[cb], 1, vt, lane);
+          for (int vt = 0; vt < NVT; ++vt) T[mt][vt] *= f;
+        dk = dnew;
       }
+      f32x4 acc[2][4][2];            // [pair][feature tile][tile of the pair]
+      auto project = [&](int jp) {
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+          for (int jj = 0; jj < 2; ++jj) {
+            acc[jp][mt][jj] = mfma(x[2 * jp + jj][0], wk.w[mt][0], kadd4[2 * jp + jj] - dk);
+#pragma unroll
+            for (int ks = 1; ks < KS; ++ks) acc[jp][mt][jj] = mfma(x[2 * jp + jj][ks], wk.w[mt][ks], acc[jp][mt][jj]);
+          }
+      };
+      bf16x8 st0[4], vop0[NVT];
+      project(0);
+      n2 = tile_row_norms(xn0, xn1, lane);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int vt = 0; vt < NVT; ++vt) vop0[vt] = load_vop_tr(sm.v[cb], 0, vt, lane);
+      project(1);
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt) st0[mt] = pack8(exp2v(acc[0][mt][0]), exp2v(acc[0][mt][1]));
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x2, 3, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int vt = 0; vt < NVT; ++vt) vop1[vt] = load_vop_tr(sm.v[cb], 1, vt, lane);
 #pragma unroll
       for (int vt = 0; vt < NVT; ++vt)
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) T[mt][vt] = mfma(st[mt], vop[jp][vt], T[mt][vt]);
+        for (int mt = 0; mt < 4; ++mt) T[mt][vt] = mfma(st0[mt], vop0[vt], T[mt][vt]);
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt) st1[mt] = pack8(exp2v(acc[1][mt][0]), exp2v(acc[1][mt][1]));
+#pragma unroll
+      for (int i = 0; i < 20; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x2, 3, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
+    if (tid == 0) sm.kmax[kfree] = -INFINITY;    // last read in the previous iteration, gathered again in the next one
     constants(n2, rk_next, cb ^ 1, knext, r0 + TC);
     store_v(cb ^ 1);
     store_k(kfree);
@@ -204,6 +232,7 @@ __device__ __forceinline__ void state_rows(const FastArgs& a, SmemState& sm, int
     __syncthreads();
     const int t = kcur; kcur = knext; knext = kfree; kfree = t;
   }
+  if (!BOUND_ONLY) update1();
 }
 
 }  // namespace fs

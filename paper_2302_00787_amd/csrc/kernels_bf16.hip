@@ -179,17 +179,20 @@ int launch_key_row_terms(const float* theta, int groups, const TensorDev& K, int
   return 0;
 }
 
+__device__ __forceinline__ int chunks_of(int rows) { return (rows + TC - 1) / TC; }
+
 // Key-side state of one slot (fast_state.h: state_rows), written to Tpart with its shift in cpart.  grid (nslot, B*H),
-// block 256, two workgroups per CU.
+// block 256, two workgroups per CU: the slots of the causal backward pass, which needs the state of every half segment, and
+// segments of one chunk.
 __global__ void __launch_bounds__(NT, 2) k_fast_state(FastArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int slot = blockIdx.x, bh = blockIdx.y;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = lane >> 4, c = lane & 15;
   const int rows_per_slot = a.rows_per_seg / a.sub;
-  const int row_beg = slot * rows_per_slot;
+  const int row_beg = slot * rows_per_slot, row_end = min(a.L, row_beg + rows_per_slot);
   f32x4 T[4][NVT];
   float dk;
-  state_rows(a, *reinterpret_cast<SmemState*>(smem_raw), bh, row_beg, min(a.L, row_beg + rows_per_slot), T, dk);
+  state_rows(a, *reinterpret_cast<SmemState*>(smem_raw), bh, row_beg, row_end, chunks_of(row_end - row_beg), T, dk);
   float* out = a.Tpart + ((size_t)bh * a.nslot + slot) * M * DVP;
 #pragma unroll
   for (int mt = 0; mt < 4; ++mt)
@@ -205,6 +208,65 @@ __global__ void __launch_bounds__(NT, 2) k_fast_state(FastArgs a) {
   if (threadIdx.x == 0) a.cpart[(size_t)bh * a.nslot + slot] = dk;
 }
 
+// The same for one whole segment by two groups of four waves, each with half of the chunks, whose states meet in LDS:
+// one state per CU and launch goes to memory instead of two, and one is read by the reduction behind it (B8 H8 L4096:
+// 21 MB each way instead of 42, which at 5 TB/s is what the two kernels spent a third of their time on).  Group 0
+// finishes feature tiles 0 and 1 of every wave, group 1 tiles 2 and 3.  grid (nseg, B*H), block 512, one workgroup per CU.
+struct SmemState2 {
+  SmemState s[2];
+};
+union SmemState2X {
+  SmemState2 s;
+  f32x4 x[2][NW][2][NVT][64];      // [sender][wave of the group][its two tiles][value tile][lane]
+};
+static_assert(sizeof(SmemState2X) + 2 * sizeof(float) <= 160 * 1024, "k_fast_state2: one workgroup per CU");
+constexpr size_t kState2Lds = sizeof(SmemState2X) + 16;
+
+__global__ void __launch_bounds__(2 * NT) k_fast_state2(FastArgs a) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  SmemState2X& sm = *reinterpret_cast<SmemState2X*>(smem_raw);
+  float* dks = (float*)(smem_raw + sizeof(SmemState2X));
+  const int slot = blockIdx.x, bh = blockIdx.y;
+  const int grp = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), lane = threadIdx.x & 63, w = (threadIdx.x >> 6) & 3;
+  const int row_beg = slot * a.rows_per_seg, row_end = min(a.L, row_beg + a.rows_per_seg);
+  const int half = (chunks_of(row_end - row_beg) + 1) / 2, mid = min(row_end, row_beg + half * TC);
+  f32x4 T[4][NVT];
+  float dk;
+  state_rows(a, sm.s.s[grp], bh, grp ? mid : row_beg, grp ? row_end : mid, half, T, dk);
+  // (state_rows ends behind a barrier: its LDS is free)
+  if ((threadIdx.x & (NT - 1)) == 0) dks[grp] = dk;
+  auto put = [&](int t0) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int vt = 0; vt < NVT; ++vt) sm.x[grp][w][i][vt][lane] = T[t0 + i][vt];
+  };
+  if (grp) put(0);
+  else put(2);
+  __syncthreads();
+  const float dm = fmaxf(dks[0], dks[1]), other = dks[grp ^ 1];
+  // (a group without rows has a zero state and a shift of -inf)
+  const float f = dk == dm ? 1.f : fast_exp2(dk - dm), fo = other == dm ? 1.f : fast_exp2(other - dm);
+  float* out = a.Tpart + ((size_t)bh * a.nslot + slot) * M * DVP;
+  auto finish = [&](int t0) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int vt = 0; vt < NVT; ++vt) {
+        const f32x4 v = T[t0 + i][vt] * f + sm.x[grp ^ 1][w][i][vt][lane] * fo;
+        if (a.timg) {
+          *(f32x4*)(out + (size_t)((w * 4 + t0 + i) * NVT + vt) * 256 + 4 * lane) = v;
+        } else {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) out[(size_t)(64 * w + 16 * (t0 + i) + 4 * (lane >> 4) + r) * DVP + 16 * vt + (lane & 15)] = v[r];
+        }
+      }
+  };
+  if (grp) finish(2);
+  else finish(0);
+  if (threadIdx.x == 0) a.cpart[(size_t)bh * a.nslot + slot] = dm;
+}
+
 // The key shift of every sequence without the states (causal backward pass with one slot per sequence: its kernels
 // start from nothing and need the shift only): cstar[bh] = the largest bound of the sequence's keys, as the state
 // kernel would have left it.  Also puts the call's counter of flushed rows back to zero.  grid (B*H), block 256.
@@ -213,7 +275,7 @@ __global__ void __launch_bounds__(NT, 2) k_fast_bound(FastArgs a) {
   const int bh = blockIdx.x;
   f32x4 T[4][NVT];
   float dk;
-  state_rows<true>(a, *reinterpret_cast<SmemState*>(smem_raw), bh, 0, a.L, T, dk);
+  state_rows<true>(a, *reinterpret_cast<SmemState*>(smem_raw), bh, 0, a.L, chunks_of(a.L), T, dk);
   if (threadIdx.x == 0) {
     a.cstar[bh] = dk;
     if (bh == 0 && a.flushed != nullptr) *a.flushed = 0u;
@@ -226,7 +288,7 @@ __global__ void __launch_bounds__(NT, 2) k_fast_bound(FastArgs a) {
 // per-sequence shifts, at cstar[B*H + bh * nseg + s]; -inf and a zero state for slot 0), so that keys late in the
 // sequence cannot push the states the earlier rows need out of the fp32 range.  grid (ceil(M*DVP/1024), B*H).
 __global__ void k_fast_reduce(float* Tpart, const float* cpart, float* cstar, int nseg, int nseg_valid, int prefix,
-                              int sub, unsigned* flushed) {
+                              unsigned* flushed) {
   const int bh = blockIdx.y;
   // the query-side kernel of the call counts into this word: it starts every call at zero
   if (flushed != nullptr && (blockIdx.x | blockIdx.y | threadIdx.x) == 0) *flushed = 0u;
@@ -257,7 +319,7 @@ __global__ void k_fast_reduce(float* Tpart, const float* cpart, float* cstar, in
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
         const int s = s0 + i;
-        if (s < nseg && s % sub == 0) {            // only the slots that open a segment are read back
+        if (s < nseg) {
           if (e == 0) cpre[s] = cr;
           if (e < per) *(f32x4*)(p + (size_t)s * per) = run;
         }
@@ -276,17 +338,19 @@ __global__ void k_fast_reduce(float* Tpart, const float* cpart, float* cstar, in
   if (e >= per) return;
   for (int s0 = 0; s0 < nseg; s0 += NB) {
     f32x4 v[NB];
+    float c[NB];
+    // (no load is conditional: slots past the last are read again and left out)
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
-      const int s = s0 + i;
-      v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (s < nseg_valid) v[i] = *(const f32x4*)(p + (size_t)s * per) * fast_exp2(cpart[(size_t)bh * nseg + s] - cs);
+      const int s = max(0, min(s0 + i, nseg_valid - 1));
+      v[i] = *(const f32x4*)(p + (size_t)s * per);
+      c[i] = cpart[(size_t)bh * nseg + s];
     }
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
       const int s = s0 + i;
-      if (prefix && s < nseg && s % sub == 0) *(f32x4*)(p + (size_t)s * per) = run;    // only the slots that open a segment are read back
-      run += v[i];
+      if (prefix && s < nseg) *(f32x4*)(p + (size_t)s * per) = run;
+      if (s < nseg_valid) run += v[i] * fast_exp2(c[i] - cs);
     }
   }
   if (!prefix) *(f32x4*)p = run;
@@ -366,7 +430,7 @@ __global__ void k_fast_reduce_totals(const float* Tpart, const float* cpart, flo
 // `base` = scr after the scan (exclusive prefix of range z), `cbase` = the scan's shifts (largest shift of the ranges
 // before z at cbase[B*H + bh * Z + z]).
 __global__ void k_fast_reduce_walk(float* Tpart, const float* cpart, float* cstar, const float* base, const float* cbase,
-                                   int nseg, int nseg_valid, int sub, int R, unsigned* flushed) {
+                                   int nseg, int nseg_valid, int R, unsigned* flushed) {
   const int bh = blockIdx.y, z = blockIdx.z, Z = gridDim.z;
   if (flushed != nullptr && (blockIdx.x | blockIdx.y | blockIdx.z | threadIdx.x) == 0) *flushed = 0u;
   constexpr size_t per = (size_t)M * DVP;
@@ -394,7 +458,7 @@ __global__ void k_fast_reduce_walk(float* Tpart, const float* cpart, float* csta
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
       const int s = s0 + i;
-      if (s < s_end && s % sub == 0) {
+      if (s < s_end) {
         if (e == 0) cpre[s] = cr;
         if (e < per) *(f32x4*)(p + (size_t)s * per) = run;
       }
@@ -456,7 +520,7 @@ __global__ void __launch_bounds__(NT, 2) k_fast_whole(FastArgs a, int Lq) {
   {
     f32x4 T[4][NVT];
     float dk;
-    state_rows(a, *reinterpret_cast<SmemState*>(smem_raw), bh, 0, a.L, T, dk);
+    state_rows(a, *reinterpret_cast<SmemState*>(smem_raw), bh, 0, a.L, chunks_of(a.L), T, dk);
     rows::put_t_image(sm, T, w, lane);
   }
   const float wmax = max256(a.wnorm + ((size_t)pg * 2) * M), amax = max256(a.bias + ((size_t)pg * 2) * M);
@@ -481,7 +545,7 @@ static int allow_lds(const void* kernel, size_t bytes) {
 // k_fast_apply: the operand images and 16 ntt rows per wave.
 static size_t apply_lds_bytes(int ntt) { return sizeof(rows::SmemOps) + (size_t)(NTA / 64) * 16 * ntt * D * sizeof(uint16_t); }
 // Largest dynamic LDS request of the forward kernels of this path.
-size_t fast_lds_bytes() { return std::max({sizeof(SmemState), sizeof(SmemWhole), apply_lds_bytes(4), fast_causal_lds_bytes()}); }
+size_t fast_lds_bytes() { return std::max({kState2Lds, sizeof(SmemWhole), apply_lds_bytes(4), fast_causal_lds_bytes()}); }
 
 bool fast_supported(int dtype, int d, int dv, int M_) { return dtype == 1 && d == D && dv == D && M_ == M; }
 
@@ -594,10 +658,20 @@ static int launch_fast_constants(const FastLaunch& f, FastArgs& a, hipStream_t s
 static int launch_fast_state_pass(const FastLaunch& f, FastArgs& a, hipStream_t st, bool every_slot = false, bool images = false) {
   if (int rc = launch_fast_constants(f, a, st, images)) return rc;
   const int BH = f.B * f.H;
+  // whole segments, but for the causal backward pass, whose kernels run on the half segments
+  const int sub = every_slot ? f.sub : 1;
+  a.sub = sub;
+  a.nslot = f.nseg * sub;
   // the last segment's states are never needed by the causal pass
-  const int nstate = (f.causal && !every_slot ? f.nseg - 1 : f.nseg) * f.sub;
+  const int nstate = (f.causal && !every_slot ? f.nseg - 1 : f.nseg) * sub;
   if (nstate > 0) {
-    hipLaunchKernelGGL(k_fast_state, dim3(nstate, BH), dim3(NT), sizeof(SmemState), st, a);
+    // two groups of waves need two chunks (sequences in segments of one: 1 x 4096 25.4 us with one group, 27.9 with two)
+    if (every_slot || f.rows_per_seg <= TC) {
+      hipLaunchKernelGGL(k_fast_state, dim3(nstate, BH), dim3(NT), sizeof(SmemState), st, a);
+    } else {
+      if (int rc = allow_lds((const void*)k_fast_state2, kState2Lds)) return rc;
+      hipLaunchKernelGGL(k_fast_state2, dim3(nstate, BH), dim3(2 * NT), kState2Lds, st, a);
+    }
     FS_LAUNCH_CHECK();
   }
   const int prefix = f.causal ? (every_slot ? 1 : 2) : 0, nblk = (M * DVP / 4 + 255) / 256;
@@ -619,16 +693,16 @@ static int launch_fast_state_pass(const FastLaunch& f, FastArgs& a, hipStream_t 
     if (prefix == 0) {
       // the sum of everything ends in range 0 of the scratch buffer: the query-side kernel reads it there
       if (images) hipLaunchKernelGGL(k_fast_total, dim3((M * DVP / 8 + 255) / 256, BH), dim3(256), 0, st, f.rscr, f.cscr, Z, Zvalid, f.flushed);
-      else hipLaunchKernelGGL(k_fast_reduce, dim3(nblk, BH), dim3(256), 0, st, f.rscr, f.cscr, f.cstar, Z, Zvalid, 0, 1, f.flushed);
+      else hipLaunchKernelGGL(k_fast_reduce, dim3(nblk, BH), dim3(256), 0, st, f.rscr, f.cscr, f.cstar, Z, Zvalid, 0, f.flushed);
       FS_LAUNCH_CHECK();
       a.Tpart = f.rscr;
       a.nslot = Z;
     } else {
-      hipLaunchKernelGGL(k_fast_reduce, dim3(nblk, BH), dim3(256), 0, st, f.rscr, f.cscr, cscan, Z, Zvalid, 2, 1,
+      hipLaunchKernelGGL(k_fast_reduce, dim3(nblk, BH), dim3(256), 0, st, f.rscr, f.cscr, cscan, Z, Zvalid, 2,
                          (unsigned*)nullptr);
       FS_LAUNCH_CHECK();
       hipLaunchKernelGGL(k_fast_reduce_walk, dim3(nblk, BH, Z), dim3(256), 0, st, f.Tpart, f.cpart, f.cstar, f.rscr, cscan,
-                         a.nslot, nstate, every_slot ? 1 : f.sub, R, f.flushed);
+                         a.nslot, nstate, R, f.flushed);
       FS_LAUNCH_CHECK();
     }
     return 0;
@@ -637,7 +711,7 @@ static int launch_fast_state_pass(const FastLaunch& f, FastArgs& a, hipStream_t 
     hipLaunchKernelGGL(k_fast_total, dim3((M * DVP / 8 + 255) / 256, BH), dim3(256), 0, st, f.Tpart, f.cpart, a.nslot, nstate, f.flushed);
   else
     hipLaunchKernelGGL(k_fast_reduce, dim3(nblk, BH), dim3(256), 0, st, f.Tpart, f.cpart, f.cstar, a.nslot, nstate, prefix,
-                       every_slot ? 1 : f.sub, f.flushed);
+                       f.flushed);
   FS_LAUNCH_CHECK();
   return 0;
 }
@@ -652,7 +726,7 @@ int launch_fast_prepare(const float* theta, int groups, const float* Omega, int 
 
 // Sum of `nslot` segment states per (b,h) into slot 0 (the reduction kernel of the forward pass on another buffer).
 void launch_fast_reduce_sum(float* part, const float* cpart, float* cstar, int nslot, int BH, hipStream_t st) {
-  hipLaunchKernelGGL(k_fast_reduce, dim3((M * DVP / 4 + 255) / 256, BH), dim3(256), 0, st, part, cpart, cstar, nslot, nslot, 0, 1,
+  hipLaunchKernelGGL(k_fast_reduce, dim3((M * DVP / 4 + 255) / 256, BH), dim3(256), 0, st, part, cpart, cstar, nslot, nslot, 0,
                      (unsigned*)nullptr);
 }
 

@@ -568,7 +568,7 @@ __global__ void __launch_bounds__(NT, 2) k_bwd_whole(BwdArgs ba) {
   float cs;
   {
     f32x4 T[4][NVT];
-    state_rows(a, sm.s, bh, 0, ba.Lk, T, cs);
+    state_rows(a, sm.s, bh, 0, ba.Lk, (ba.Lk + TC - 1) / TC, T, cs);
     pack_state(T, tb);
   }
   const int nzero = apply_rows_b<1>(ba, sm.q, bh, tb, cs, 0, ba.Lq);
