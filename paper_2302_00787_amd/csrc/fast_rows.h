@@ -132,16 +132,18 @@ __device__ __forceinline__ void read_rows(bf16x8 (&x)[NTT][KS], const uint16_t* 
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the buffer may be filled again
 }
 
-// Exponents of the 32 features of block fb: bias + W~ x.
-template <int NTT>
-__device__ __forceinline__ void project(f32x4 (&acc)[2][NTT], const SmemOps& sm, int fb, const bf16x8 (&x)[NTT][KS], int lane) {
+// Exponents of the 32 features of block fb: W~ x + bias (BIAS), or + what is added to the exponents of the lane's row.
+template <int NTT, bool BIAS>
+__device__ __forceinline__ void project(f32x4 (&acc)[2][NTT], const SmemOps& sm, int fb, const bf16x8 (&x)[NTT][KS], const f32x4* add,
+                                        int lane) {
   const int g = lane >> 4;
 #pragma unroll
   for (int mt = 0; mt < 2; ++mt) {
     const bf16x8 w0 = *(const bf16x8*)(&sm.w[2 * fb + mt][0][lane][0]), w1 = *(const bf16x8*)(&sm.w[2 * fb + mt][1][lane][0]);
-    const f32x4 b = *(const f32x4*)(&sm.bias[32 * fb + 16 * mt + 4 * g]);
+    f32x4 b;
+    if (BIAS) b = *(const f32x4*)(&sm.bias[32 * fb + 16 * mt + 4 * g]);
 #pragma unroll
-    for (int t = 0; t < NTT; ++t) acc[mt][t] = mfma(w0, x[t][0], b);
+    for (int t = 0; t < NTT; ++t) acc[mt][t] = mfma(w0, x[t][0], BIAS ? b : add[t]);
 #pragma unroll
     for (int t = 0; t < NTT; ++t) acc[mt][t] = mfma(w1, x[t][1], acc[mt][t]);
   }
@@ -149,25 +151,28 @@ __device__ __forceinline__ void project(f32x4 (&acc)[2][NTT], const SmemOps& sm,
 
 // y[vt][t] = (state^T x features^T): rows = columns 16 vt + 4 g + r of the state, lane <-> row 16 t + c of the chunk;
 // y[NVT - 1][t][0] is the row's normaliser in every lane.  SHIFT: add[t] is added to the exponents of the lane's row.
+// KEEP: the features stay with the caller, keep[fb][t] (k <-> feature 32 fb + 16 (e/4) + 4 g + e%4 of the lane's row).
 // A wave issues in order, so the exponentials of block fb + 1 are interleaved with the contraction of block fb, one
 // matrix instruction to three of the others (left to the compiler they come in runs: encoder call 64.4 against 63.4 us).
-template <int NTT, bool SHIFT>
+template <int NTT, bool SHIFT, bool KEEP = false>
 __device__ __forceinline__ void contract_rows(f32x4 (&y)[NVT][NTT], const SmemOps& sm, const bf16x8 (&x)[NTT][KS],
-                                              const float (&add)[NTT], int lane) {
+                                              const float (&add)[NTT], int lane, bf16x8 (*keep)[NTT] = nullptr) {
   f32x4 acc[2][NTT];
-  project(acc, sm, 0, x, lane);
   bf16x8 p[NTT];
+  auto features = [&](bf16x8 (&f)[NTT]) {
 #pragma unroll
-  for (int t = 0; t < NTT; ++t)
-    p[t] = SHIFT ? pack8(exp2v(acc[0][t] + add[t]), exp2v(acc[1][t] + add[t])) : pack8(exp2v(acc[0][t]), exp2v(acc[1][t]));
-  project(acc, sm, 1, x, lane);
+    for (int t = 0; t < NTT; ++t)
+      f[t] = SHIFT ? pack8(exp2v(acc[0][t] + add[t]), exp2v(acc[1][t] + add[t])) : pack8(exp2v(acc[0][t]), exp2v(acc[1][t]));
+  };
+  project<NTT, true>(acc, sm, 0, x, nullptr, lane);
+  features(p);
+  project<NTT, true>(acc, sm, 1, x, nullptr, lane);
 #pragma unroll
   for (int vt = 0; vt < NVT; ++vt)
 #pragma unroll
     for (int t = 0; t < NTT; ++t) y[vt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int fb = 0; fb < M / 32; ++fb) {
-    // contraction of block fb beside the exponentials of block fb + 1, then the projections of block fb + 2
     __builtin_amdgcn_sched_barrier(0);
     bf16x8 pn[NTT];
 #pragma unroll
@@ -177,9 +182,7 @@ __device__ __forceinline__ void contract_rows(f32x4 (&y)[NVT][NTT], const SmemOp
       for (int t = 0; t < NTT; ++t) y[vt][t] = mfma(s, p[t], y[vt][t]);
     }
     if (fb + 1 < M / 32) {
-#pragma unroll
-      for (int t = 0; t < NTT; ++t)
-        pn[t] = SHIFT ? pack8(exp2v(acc[0][t] + add[t]), exp2v(acc[1][t] + add[t])) : pack8(exp2v(acc[0][t]), exp2v(acc[1][t]));
+      features(pn);
 #pragma unroll
       for (int i = 0; i < NVT * NTT; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
@@ -187,9 +190,12 @@ __device__ __forceinline__ void contract_rows(f32x4 (&y)[NVT][NTT], const SmemOp
       }
     }
     __builtin_amdgcn_sched_barrier(0);
-    if (fb + 2 < M / 32) project(acc, sm, fb + 2, x, lane);
+    if (fb + 2 < M / 32) project<NTT, true>(acc, sm, fb + 2, x, nullptr, lane);
 #pragma unroll
-    for (int t = 0; t < NTT; ++t) p[t] = pn[t];
+    for (int t = 0; t < NTT; ++t) {
+      if (KEEP) keep[fb][t] = p[t];
+      p[t] = pn[t];
+    }
   }
 }
 

@@ -35,18 +35,24 @@ struct SmemState {
 
 // The state of the key rows [row_beg, row_end) of one (b,h), left in the registers of the workgroup's four waves
 // (wave w: features 64w .. 64w+63 x 80 columns) on the shift dk.  Ends behind a barrier: the caller may reuse the LDS.
-// BOUND_ONLY: nothing but dk, the largest bound of the rows (the shift such a state would have): no projections, no
+// STATE_BOUND: nothing but dk, the largest bound of the rows (the shift such a state would have): no projections, no
 // values, T untouched.
+// STATE_QUERIES: the query-side twin R = sum_i P_i G1_i^T of the backward pass: Q's rows with their own shifts and the
+// biases, a.V = the G1 rows of 80 numbers; dk = 0.
 // A workgroup of 512 threads calls it with two row ranges, one per group of four waves, each group with an LDS struct of
 // its own and both with the same `niter`, the number of chunks of the longer range (the barriers are the workgroup's).
-template <bool BOUND_ONLY = false>
+enum { STATE_KEYS, STATE_BOUND, STATE_QUERIES };
+template <int MODE = STATE_KEYS>
 __device__ __forceinline__ void state_rows(const FastArgs& a, SmemState& sm, int bh, int row_beg, int row_end, int niter,
                                            f32x4 (&T)[4][NVT], float& dk) {
+  constexpr bool BOUND_ONLY = MODE == STATE_BOUND, QUERIES = MODE == STATE_QUERIES;
+  constexpr int side = QUERIES ? 0 : 1;
+  const TensorDev& X = QUERIES ? a.Q : a.K;
   const int b = bh / a.H, h = bh % a.H;
   const int tid = threadIdx.x & (NT - 1), lane = tid & 63, w = tid >> 6, g = lane >> 4, c = lane & 15;
   const int pg = group_of(a.pgroups, b, h, a.H);
   const float* th = a.theta + (size_t)group_of(a.groups, b, h, a.H) * (FS_THETA_HEADER_ + (size_t)D + 4 * (size_t)D * D);
-  const uint16_t* Kb = (const uint16_t*)a.K.ptr + b * a.K.sb + h * a.K.sh + (long long)row_beg * a.K.sl;
+  const uint16_t* Kb = (const uint16_t*)X.ptr + b * X.sb + h * X.sh + (long long)row_beg * X.sl;
   const uint16_t* Vb = (const uint16_t*)a.V.ptr + b * a.V.sb + h * a.V.sh + (long long)row_beg * a.V.sl;
   const float* rkb = a.rk + (size_t)bh * a.L + row_beg;
   const int nrows = row_end - row_beg;
@@ -54,15 +60,20 @@ __device__ __forceinline__ void state_rows(const FastArgs& a, SmemState& sm, int
   // staging: thread -> rows tid/8 and tid/8 + 32 of a chunk, bytes 16 (tid%8); rows past the end read as zero
   // (a fresh descriptor per chunk: uniform base = the chunk's first row, 32-bit offsets inside the chunk)
   const int srow = tid >> 3, spc = tid & 7;
-  u32x4 kr[2], vr[2];
+  u32x4 kr[2], vr[QUERIES ? 3 : 2];
   auto load_k = [&](int r0) {
-    const __amdgpu_buffer_rsrc_t rk_ = pc::chunk_rsrc(Kb + (long long)r0 * a.K.sl, 2 * (int)a.K.sl, nrows - r0, 2 * D);
+    const __amdgpu_buffer_rsrc_t rk_ = pc::chunk_rsrc(Kb + (long long)r0 * X.sl, 2 * (int)X.sl, nrows - r0, 2 * D);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) kr[i] = __builtin_amdgcn_raw_buffer_load_b128(rk_, 2 * ((srow + 32 * i) * (int)a.K.sl + spc * 8), 0, 0);
+    for (int i = 0; i < 2; ++i) kr[i] = __builtin_amdgcn_raw_buffer_load_b128(rk_, 2 * ((srow + 32 * i) * (int)X.sl + spc * 8), 0, 0);
   };
   auto load_v = [&](int r0) {
     if (BOUND_ONLY) return;
-    const __amdgpu_buffer_rsrc_t rv_ = pc::chunk_rsrc(Vb + (long long)r0 * a.V.sl, 2 * (int)a.V.sl, nrows - r0, 2 * D);
+    const __amdgpu_buffer_rsrc_t rv_ = pc::chunk_rsrc(Vb + (long long)r0 * a.V.sl, 2 * (int)a.V.sl, nrows - r0, QUERIES ? 2 * DVP : 2 * D);
+    if (QUERIES) {             // G1 rows: 160 bytes one after the other, a chunk is 640 pieces in a row
+#pragma unroll
+      for (int i = 0; i < (QUERIES ? 3 : 2); ++i) vr[i] = __builtin_amdgcn_raw_buffer_load_b128(rv_, 16 * (tid + NT * i), 0, 0);
+      return;
+    }
 #pragma unroll
     for (int i = 0; i < 2; ++i) vr[i] = __builtin_amdgcn_raw_buffer_load_b128(rv_, 2 * ((srow + 32 * i) * (int)a.V.sl + spc * 8), 0, 0);
   };
@@ -72,6 +83,12 @@ __device__ __forceinline__ void state_rows(const FastArgs& a, SmemState& sm, int
   };
   auto store_v = [&](int vb) {
     if (BOUND_ONLY) return;
+    if (QUERIES) {
+#pragma unroll
+      for (int i = 0; i < (QUERIES ? 3 : 2); ++i)
+        if (tid + NT * i < TC * (LDV / 8)) *(u32x4*)(&sm.v[vb][0][0] + 8 * (tid + NT * i)) = vr[i];
+      return;
+    }
 #pragma unroll
     for (int i = 0; i < 2; ++i) *(u32x4*)(&sm.v[vb][srow + 32 * i][spc * 8]) = vr[i];
   };
@@ -83,17 +100,24 @@ __device__ __forceinline__ void state_rows(const FastArgs& a, SmemState& sm, int
   load_k(TC);
   WSlice wk;
   if (!BOUND_ONLY) {
-    load_wslice(wk, a.Wbf + ((size_t)pg * 2 + 1) * M * D, w);
-    init_value_pad(sm.v[0], 2 * TC, NT, tid);
+    load_wslice(wk, a.Wbf + ((size_t)pg * 2 + side) * M * D, w);
+    if (!QUERIES) init_value_pad(sm.v[0], 2 * TC, NT, tid);
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
       for (int vt = 0; vt < NVT; ++vt) T[mt][vt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  const float wmax = max256(a.wnorm + ((size_t)pg * 2 + 1) * M);
-  const bool isoC = ((int)th[2]) & 1;
+  float bcol[4] = {0.f, 0.f, 0.f, 0.f};           // (queries) 2 (bias - largest bias) of feature 64 w + 16 mt + c
+  if (QUERIES) {
+    const float* bias = a.bias + ((size_t)pg * 2) * M;
+    const float amax = max256(bias);
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) bcol[mt] = 2.f * (bias[64 * w + 16 * mt + c] - amax);
+  }
+  const float wmax = max256(a.wnorm + ((size_t)pg * 2 + side) * M);
+  const bool isoC = QUERIES || (((int)th[2]) & 1);
   if (tid < 3) sm.kmax[tid] = -INFINITY;
-  dk = -INFINITY;
+  dk = QUERIES ? 0.f : -INFINITY;
 
   // Per-token constants of token tile w of a chunk (first row r0 of the slot) from the squared norms n2 of its rows
   // (valid in the lanes (g, c) = (c / 4, c)): row terms to kadd[cb], the largest bound into kmax[mb].
@@ -107,6 +131,10 @@ __device__ __forceinline__ void state_rows(const FastArgs& a, SmemState& sm, int
     if (g == (c >> 2)) {
       const int t = 16 * w + c;
       const bool valid = r0 + t < nrows;
+      if (QUERIES) {
+        sm.kadd[cb][t] = valid ? -row_shift(n2, wmax) : -INFINITY;
+        return;
+      }
       float rt = -0.5f * kLog2e * a.scale * a.scale * n2;
       if (!isoC) rt = valid ? rkv : 0.f;
       // rows past the end get -inf: their features are exactly zero whatever the key shift is
@@ -174,7 +202,7 @@ __device__ __forceinline__ void state_rows(const FastArgs& a, SmemState& sm, int
       update1();
       __builtin_amdgcn_sched_barrier(0);
       // ---- running key shift: the state is rebased when the chunk's largest bound exceeds the current shift
-      if (dnew > dk) {
+      if (!QUERIES && dnew > dk) {
         const float f = fast_exp2(dk - dnew);
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt)
@@ -188,7 +216,7 @@ __device__ __forceinline__ void state_rows(const FastArgs& a, SmemState& sm, int
         for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
           for (int jj = 0; jj < 2; ++jj) {
-            acc[jp][mt][jj] = mfma(x[2 * jp + jj][0], wk.w[mt][0], kadd4[2 * jp + jj] - dk);
+            acc[jp][mt][jj] = mfma(x[2 * jp + jj][0], wk.w[mt][0], kadd4[2 * jp + jj] + (QUERIES ? bcol[mt] : -dk));
 #pragma unroll
             for (int ks = 1; ks < KS; ++ks) acc[jp][mt][jj] = mfma(x[2 * jp + jj][ks], wk.w[mt][ks], acc[jp][mt][jj]);
           }
@@ -233,6 +261,62 @@ __device__ __forceinline__ void state_rows(const FastArgs& a, SmemState& sm, int
     const int t = kcur; kcur = knext; knext = kfree; kfree = t;
   }
   if (!BOUND_ONLY) update1();
+}
+
+// The state of the rows [row_beg, row_end) by two groups of four waves, whose states meet in LDS: one state per CU and launch goes
+// to memory instead of two, and one is read by the reduction behind it (B8 H8 L4096: 21 MB each way instead of 42, which at
+// 5 TB/s is what the two kernels spent a third of their time on).  Each group takes half of the chunks; group 0 finishes
+// feature tiles 0 and 1 of every wave, group 1 tiles 2 and 3.  For 512 threads and kState2Lds bytes of LDS.
+__device__ __forceinline__ int chunks_of(int rows) { return (rows + TC - 1) / TC; }
+
+union SmemState2 {
+  SmemState s[2];
+  f32x4 x[2][NW][2][NVT][64];      // [sender][wave of the group][its two tiles][value tile][lane]
+};
+constexpr size_t kState2Lds = sizeof(SmemState2) + 16;
+static_assert(kState2Lds <= 160 * 1024, "one workgroup per CU");
+
+template <int MODE>
+__device__ __forceinline__ void state_two_groups(const FastArgs& a, unsigned char* smem_raw, int bh, int row_beg, int row_end,
+                                                 bool image, float* out, float* shift_out) {
+  SmemState2& sm = *reinterpret_cast<SmemState2*>(smem_raw);
+  float* dks = (float*)(smem_raw + sizeof(SmemState2));
+  const int grp = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), lane = threadIdx.x & 63, w = (threadIdx.x >> 6) & 3;
+  const int half = (chunks_of(row_end - row_beg) + 1) / 2, mid = min(row_end, row_beg + half * TC);
+  f32x4 T[4][NVT];
+  float dk;
+  state_rows<MODE>(a, sm.s[grp], bh, grp ? mid : row_beg, grp ? row_end : mid, half, T, dk);
+  // (state_rows ends behind a barrier: its LDS is free)
+  if ((threadIdx.x & (NT - 1)) == 0) dks[grp] = dk;
+  auto put = [&](int t0) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int vt = 0; vt < NVT; ++vt) sm.x[grp][w][i][vt][lane] = T[t0 + i][vt];
+  };
+  if (grp) put(0);
+  else put(2);
+  __syncthreads();
+  const float dm = fmaxf(dks[0], dks[1]), other = dks[grp ^ 1];
+  // (a group without rows has a zero state and a shift of -inf)
+  const float f = dk == dm ? 1.f : fast_exp2(dk - dm), fo = other == dm ? 1.f : fast_exp2(other - dm);
+  auto finish = [&](int t0) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int vt = 0; vt < NVT; ++vt) {
+        const f32x4 v = T[t0 + i][vt] * f + sm.x[grp ^ 1][w][i][vt][lane] * fo;
+        if (image) {
+          *(f32x4*)(out + (size_t)((w * 4 + t0 + i) * NVT + vt) * 256 + 4 * lane) = v;
+        } else {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) out[(size_t)(64 * w + 16 * (t0 + i) + 4 * (lane >> 4) + r) * DVP + 16 * vt + (lane & 15)] = v[r];
+        }
+      }
+  };
+  if (grp) finish(2);
+  else finish(0);
+  if (threadIdx.x == 0) *shift_out = dm;
 }
 
 }  // namespace fs

@@ -622,20 +622,20 @@ namespace {
 struct FastBwdPlan {
   FastPlan f;
   int rslots, rows_per_rslot;
-  size_t off_gh, off_rpart, off_rcpart, off_rcstar, total;
+  size_t off_gh, off_rpart, off_rcpart, total;
 };
 
-void plan_fast_backward(int BH, int pgroups, int Lq, int Lk, FastBwdPlan* p) {
+void plan_fast_backward(int BH, int pgroups, int Lq, int Lk, int causal, FastBwdPlan* p) {
   plan_fast(BH, pgroups, Lk, &p->f);
   int nseg, rows_per_seg, sub;
   fast_plan(BH, Lq, &nseg, &rows_per_seg, &sub);
+  if (!causal) sub = 1;        // (half segments: the walks of the causal kernels)
   p->rslots = nseg * sub;
   p->rows_per_rslot = rows_per_seg / sub;
   size_t off = p->f.total;
   p->off_gh = off;     off = align_up(off + (size_t)BH * Lq * 80 * sizeof(uint16_t));
   p->off_rpart = off;  off = align_up(off + (size_t)BH * p->rslots * 256 * 80 * sizeof(float));
   p->off_rcpart = off; off = align_up(off + (size_t)BH * p->rslots * sizeof(float));
-  p->off_rcstar = off; off = align_up(off + (size_t)BH * sizeof(float));
   p->total = off;
 }
 }  // namespace
@@ -650,7 +650,7 @@ size_t favorsharp_attention_backward_workspace_bytes(int B, int H, int Lq, int L
   size_t total = p.total;
   if (fast_supported(FS_BF16, d, dv, M)) {      // the query does not know the dtype: cover both paths
     FastBwdPlan fp;
-    plan_fast_backward(B * H, std::max(groups, omega_groups), Lq, Lk, &fp);
+    plan_fast_backward(B * H, std::max(groups, omega_groups), Lq, Lk, causal, &fp);
     total = std::max(total, fp.total);
   }
   return total;
@@ -682,7 +682,7 @@ int attention_backward_impl(const float* theta, int groups, const fs_tensor* Q, 
       dV->stride_l < max_sl &&
       (int)std::max({fast_lds_bytes(), fast_bwd_lds_bytes(), fast_bwd_causal_lds_bytes()}) <= device_lds_limit()) {
     FastBwdPlan fp;
-    plan_fast_backward(BH, pgroups, Lq, Lk, &fp);
+    plan_fast_backward(BH, pgroups, Lq, Lk, causal, &fp);
     char* w8 = (char*)workspace;
     FastLaunch f;
     f.Q = dev(Q); f.K = dev(K); f.V = dev(V); f.Y = dev(dV);     // no forward output is written on this path
@@ -702,8 +702,7 @@ int attention_backward_impl(const float* theta, int groups, const fs_tensor* Q, 
       f.pre_mode = dense_c2 ? 1 : 2;
     }
     return launch_fast_attention_backward(f, dev(dY), dev(dQ), dev(dK), dev(dV), (uint16_t*)(w8 + fp.off_gh),
-                                          (float*)(w8 + fp.off_rpart), (float*)(w8 + fp.off_rcpart),
-                                          (float*)(w8 + fp.off_rcstar), fp.rslots, fp.rows_per_rslot, (hipStream_t)stream);
+                                          (float*)(w8 + fp.off_rpart), (float*)(w8 + fp.off_rcpart), fp.rslots, fp.rows_per_rslot, (hipStream_t)stream);
   }
   BwdPlan p;
   plan_backward(BH, pgroups, Lq, Lk, d, dv, M, causal, &p);

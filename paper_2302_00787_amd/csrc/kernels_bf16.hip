@@ -179,8 +179,6 @@ int launch_key_row_terms(const float* theta, int groups, const TensorDev& K, int
   return 0;
 }
 
-__device__ __forceinline__ int chunks_of(int rows) { return (rows + TC - 1) / TC; }
-
 // Key-side state of one slot (fast_state.h: state_rows), written to Tpart with its shift in cpart.  grid (nslot, B*H),
 // block 256, two workgroups per CU: the slots of the causal backward pass, which needs the state of every half segment, and
 // segments of one chunk.
@@ -208,63 +206,13 @@ __global__ void __launch_bounds__(NT, 2) k_fast_state(FastArgs a) {
   if (threadIdx.x == 0) a.cpart[(size_t)bh * a.nslot + slot] = dk;
 }
 
-// The same for one whole segment by two groups of four waves, each with half of the chunks, whose states meet in LDS:
-// one state per CU and launch goes to memory instead of two, and one is read by the reduction behind it (B8 H8 L4096:
-// 21 MB each way instead of 42, which at 5 TB/s is what the two kernels spent a third of their time on).  Group 0
-// finishes feature tiles 0 and 1 of every wave, group 1 tiles 2 and 3.  grid (nseg, B*H), block 512, one workgroup per CU.
-struct SmemState2 {
-  SmemState s[2];
-};
-union SmemState2X {
-  SmemState2 s;
-  f32x4 x[2][NW][2][NVT][64];      // [sender][wave of the group][its two tiles][value tile][lane]
-};
-static_assert(sizeof(SmemState2X) + 2 * sizeof(float) <= 160 * 1024, "k_fast_state2: one workgroup per CU");
-constexpr size_t kState2Lds = sizeof(SmemState2X) + 16;
-
+// The same for one whole segment by two groups of four waves (fast_state.h: state_two_groups).  grid (nseg, B*H), block 512,
+// one workgroup per CU.
 __global__ void __launch_bounds__(2 * NT) k_fast_state2(FastArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  SmemState2X& sm = *reinterpret_cast<SmemState2X*>(smem_raw);
-  float* dks = (float*)(smem_raw + sizeof(SmemState2X));
-  const int slot = blockIdx.x, bh = blockIdx.y;
-  const int grp = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), lane = threadIdx.x & 63, w = (threadIdx.x >> 6) & 3;
-  const int row_beg = slot * a.rows_per_seg, row_end = min(a.L, row_beg + a.rows_per_seg);
-  const int half = (chunks_of(row_end - row_beg) + 1) / 2, mid = min(row_end, row_beg + half * TC);
-  f32x4 T[4][NVT];
-  float dk;
-  state_rows(a, sm.s.s[grp], bh, grp ? mid : row_beg, grp ? row_end : mid, half, T, dk);
-  // (state_rows ends behind a barrier: its LDS is free)
-  if ((threadIdx.x & (NT - 1)) == 0) dks[grp] = dk;
-  auto put = [&](int t0) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int vt = 0; vt < NVT; ++vt) sm.x[grp][w][i][vt][lane] = T[t0 + i][vt];
-  };
-  if (grp) put(0);
-  else put(2);
-  __syncthreads();
-  const float dm = fmaxf(dks[0], dks[1]), other = dks[grp ^ 1];
-  // (a group without rows has a zero state and a shift of -inf)
-  const float f = dk == dm ? 1.f : fast_exp2(dk - dm), fo = other == dm ? 1.f : fast_exp2(other - dm);
-  float* out = a.Tpart + ((size_t)bh * a.nslot + slot) * M * DVP;
-  auto finish = [&](int t0) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int vt = 0; vt < NVT; ++vt) {
-        const f32x4 v = T[t0 + i][vt] * f + sm.x[grp ^ 1][w][i][vt][lane] * fo;
-        if (a.timg) {
-          *(f32x4*)(out + (size_t)((w * 4 + t0 + i) * NVT + vt) * 256 + 4 * lane) = v;
-        } else {
-#pragma unroll
-          for (int r = 0; r < 4; ++r) out[(size_t)(64 * w + 16 * (t0 + i) + 4 * (lane >> 4) + r) * DVP + 16 * vt + (lane & 15)] = v[r];
-        }
-      }
-  };
-  if (grp) finish(2);
-  else finish(0);
-  if (threadIdx.x == 0) a.cpart[(size_t)bh * a.nslot + slot] = dm;
+  const int slot = blockIdx.x, bh = blockIdx.y, row_beg = slot * a.rows_per_seg;
+  state_two_groups<STATE_KEYS>(a, smem_raw, bh, row_beg, min(a.L, row_beg + a.rows_per_seg), a.timg != 0,
+                               a.Tpart + ((size_t)bh * a.nslot + slot) * M * DVP, a.cpart + (size_t)bh * a.nslot + slot);
 }
 
 // The key shift of every sequence without the states (causal backward pass with one slot per sequence: its kernels
@@ -275,7 +223,7 @@ __global__ void __launch_bounds__(NT, 2) k_fast_bound(FastArgs a) {
   const int bh = blockIdx.x;
   f32x4 T[4][NVT];
   float dk;
-  state_rows<true>(a, *reinterpret_cast<SmemState*>(smem_raw), bh, 0, a.L, chunks_of(a.L), T, dk);
+  state_rows<STATE_BOUND>(a, *reinterpret_cast<SmemState*>(smem_raw), bh, 0, a.L, chunks_of(a.L), T, dk);
   if (threadIdx.x == 0) {
     a.cstar[bh] = dk;
     if (bh == 0 && a.flushed != nullptr) *a.flushed = 0u;
@@ -360,7 +308,7 @@ __global__ void k_fast_reduce(float* Tpart, const float* cpart, float* cstar, in
 // LDS: a thread takes the eight numbers of lane l for the tiles (2 fb, vt) and (2 fb + 1, vt) (accumulator images of
 // 16 features x 16 columns) and writes them as bf16 in the place of slot 0's first four, which nobody else reads.  The
 // state a query workgroup fetches is 40 kB that way instead of 80.  grid (ceil(M*DVP/2048), B*H), block 256.
-__global__ void __launch_bounds__(256) k_fast_total(float* Tpart, const float* cpart, int nslot, int nvalid, unsigned* flushed) {
+__global__ void __launch_bounds__(256) k_fast_total(float* Tpart, const float* cpart, float* cstar, int nslot, int nvalid, unsigned* flushed) {
   const int bh = blockIdx.y;
   if (flushed != nullptr && (blockIdx.x | blockIdx.y | threadIdx.x) == 0) *flushed = 0u;
   constexpr size_t per = (size_t)M * DVP;
@@ -368,10 +316,11 @@ __global__ void __launch_bounds__(256) k_fast_total(float* Tpart, const float* c
   const float* cp = cpart + (size_t)bh * nslot;
   float cs = -INFINITY;
   for (int s = 0; s < nvalid; ++s) cs = fmaxf(cs, cp[s]);
+  if (piece == 0 && cstar != nullptr) cstar[bh] = cs;
   if (piece >= (M / 32) * NVT * 64) return;
   float* p = Tpart + (size_t)bh * nslot * per + (size_t)(2 * fb * NVT + vt) * 256 + 4 * l;
   f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
-  constexpr int NB = 4;
+  constexpr int NB = 8;
   for (int s0 = 0; s0 < nvalid; s0 += NB) {
     f32x4 v[NB], u[NB];
 #pragma unroll
@@ -692,8 +641,7 @@ static int launch_fast_state_pass(const FastLaunch& f, FastArgs& a, hipStream_t 
     FS_LAUNCH_CHECK();
     if (prefix == 0) {
       // the sum of everything ends in range 0 of the scratch buffer: the query-side kernel reads it there
-      if (images) hipLaunchKernelGGL(k_fast_total, dim3((M * DVP / 8 + 255) / 256, BH), dim3(256), 0, st, f.rscr, f.cscr, Z, Zvalid, f.flushed);
-      else hipLaunchKernelGGL(k_fast_reduce, dim3(nblk, BH), dim3(256), 0, st, f.rscr, f.cscr, f.cstar, Z, Zvalid, 0, f.flushed);
+      launch_fast_total(f.rscr, f.cscr, f.cstar, Z, Zvalid, BH, f.flushed, st);
       FS_LAUNCH_CHECK();
       a.Tpart = f.rscr;
       a.nslot = Z;
@@ -707,8 +655,8 @@ static int launch_fast_state_pass(const FastLaunch& f, FastArgs& a, hipStream_t 
     }
     return 0;
   }
-  if (images && prefix == 0)
-    hipLaunchKernelGGL(k_fast_total, dim3((M * DVP / 8 + 255) / 256, BH), dim3(256), 0, st, f.Tpart, f.cpart, a.nslot, nstate, f.flushed);
+  if (prefix == 0)
+    launch_fast_total(f.Tpart, f.cpart, f.cstar, a.nslot, nstate, BH, f.flushed, st);
   else
     hipLaunchKernelGGL(k_fast_reduce, dim3(nblk, BH), dim3(256), 0, st, f.Tpart, f.cpart, f.cstar, a.nslot, nstate, prefix,
                        f.flushed);
@@ -724,10 +672,9 @@ int launch_fast_prepare(const float* theta, int groups, const float* Omega, int 
   return 0;
 }
 
-// Sum of `nslot` segment states per (b,h) into slot 0 (the reduction kernel of the forward pass on another buffer).
-void launch_fast_reduce_sum(float* part, const float* cpart, float* cstar, int nslot, int BH, hipStream_t st) {
-  hipLaunchKernelGGL(k_fast_reduce, dim3((M * DVP / 4 + 255) / 256, BH), dim3(256), 0, st, part, cpart, cstar, nslot, nslot, 0,
-                     (unsigned*)nullptr);
+// The operand image of the sum of `nvalid` of `nslot` states per (b,h), and its shift in cstar (optional).
+void launch_fast_total(float* part, const float* cpart, float* cstar, int nslot, int nvalid, int BH, unsigned* flushed, hipStream_t st) {
+  hipLaunchKernelGGL(k_fast_total, dim3((M * DVP / 8 + 255) / 256, BH), dim3(256), 0, st, part, cpart, cstar, nslot, nvalid, flushed);
 }
 
 // Non-causal calls that run one workgroup per sequence (k_fast_whole): enough sequences to fill most of the chip's
@@ -740,10 +687,12 @@ static bool fast_whole_sequences(int BH, int Lq, int Lk) {
 }
 
 // The same choice for the backward pass of a non-causal call (k_bwd_whole): six loops over the sequence in a row, so
-// the short-sequence bound is half the forward one (measured: B*H / 16 chunks, 4 .. 16).
+// the short-sequence bound is half the forward one (measured: B*H / 16 chunks, 4 .. 16), and with many sequences the
+// kernels that split the rows win as soon as the states are small beside the rows (us, whole / separate: 4096 x 128 500 /
+// 949, 1024 x 512 383 / 415, 384 x 512 186 / 183, 512 x 1024 369 / 346, 512 x 4096 1480 / 1140).
 static bool fast_whole_sequences_backward(int BH, int Lq, int Lk) {
   const int chunks = (Lq + TC - 1) / TC + (Lk + TC - 1) / TC;
-  return BH >= 384 || chunks <= std::min(16, std::max(4, BH / 16));
+  return chunks <= (BH >= 384 ? 24 : std::min(16, std::max(4, BH / 16)));
 }
 
 int launch_fast_attention(const FastLaunch& f, hipStream_t st, hipEvent_t ev_begin, hipEvent_t ev_end) {
@@ -787,7 +736,7 @@ int launch_fast_attention(const FastLaunch& f, hipStream_t st, hipEvent_t ev_beg
 
 // Backward pass of a non-causal call: the forward state pass, then the kernels of kernels_bf16_bwd.hip.
 int launch_fast_attention_backward(const FastLaunch& f, const TensorDev& dY, const TensorDev& dQ, const TensorDev& dK,
-                                   const TensorDev& dV, uint16_t* gh, float* Rpart, float* rcpart, float* rcstar,
+                                   const TensorDev& dV, uint16_t* gh, float* Rpart, float* rcpart,
                                    int rslots, int rows_per_rslot, hipStream_t st) {
   FastArgs a;
   if (f.causal) {
@@ -810,8 +759,8 @@ int launch_fast_attention_backward(const FastLaunch& f, const TensorDev& dY, con
       if (int rc = launch_fill_u32((uint32_t*)f.flushed, 0u, 1, st)) return rc;
     return launch_fast_backward_whole(f, a, dY, dQ, dK, dV, gh, st);
   }
-  if (int rc = launch_fast_state_pass(f, a, st)) return rc;
-  return launch_fast_backward(f, a, dY, dQ, dK, dV, gh, Rpart, rcpart, rcstar, rslots, rows_per_rslot, st);
+  if (int rc = launch_fast_state_pass(f, a, st, false, true)) return rc;
+  return launch_fast_backward(f, a, dY, dQ, dK, dV, gh, Rpart, rcpart, rslots, rows_per_rslot, st);
 }
 
 }  // namespace fs

@@ -161,6 +161,42 @@ def test_backward_bf16_path_whole_sequences_per_workgroup(fs, variant, B, H, Lq,
           f"worst row {worst[1]:.2e}")
 
 
+@pytest.mark.parametrize("variant", ["gerf", "saderf"])
+@pytest.mark.parametrize("H,Lq,Lk,f32", [(1, 1, 400, False), (3, 15, 700, True), (20, 129, 1000, False), (2, 2049, 1039, False),   # one row tile per wave
+                                         (33, 1999, 130, False), (70, 100, 1121, True), (65, 1041, 1025, False),                # two: queries, keys, both
+                                         (385, 800, 780, False)])                                                               # longest whole, then rows
+def test_backward_bf16_path_row_tiles(fs, variant, H, Lq, Lk, f32):
+    """The row-split gradient kernels in each of their row-tile widths, with remainders of tiles, steps and workgroups.
+    Reference: float64 chain rule on the same bf16 inputs and the kernels' bf16 projection matrices."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(H + Lq + Lk)
+    Q, K, V, dY = (torch.randn((1, H, L, 64), generator=gen, device="cuda") for L in (Lq, Lk, Lk, Lq))
+    Q, K, V = (x.bfloat16() for x in (Q, K, V))
+    dY = dY if f32 else dY.bfloat16()
+    Om = torch.randn((1, 256, 64), generator=gen, device="cuda")
+    rng = np.random.default_rng(7)
+    vec = util.theta_vec_from_oracle(orc.fit(variant, 0.35 * rng.standard_normal((400, 64)), 0.4 * rng.standard_normal((400, 64))))
+    th, s = util.oracle_theta_from_vec(vec, 64), 64 ** -0.25
+    grads = tuple(torch.full((1, H, L, 64), float("nan"), dtype=dY.dtype, device="cuda") for L in (Lq, Lk, Lk))
+    got = fs.attention_backward(torch.from_numpy(vec[None]).cuda(), Q, K, V, dY, s, Om, grads=grads)
+    log2e = float(np.log2(np.e))
+    W1, W2 = ((log2e * s * (Om[0] @ torch.from_numpy(Bm).float().cuda())).bfloat16().double() / log2e for Bm in (th.B1, th.B2))
+    bias = (Om[0].double() ** 2) @ torch.from_numpy(th.A).cuda()
+    C2 = s * s * torch.from_numpy(th.C2).cuda()
+    for h in sorted({0, H // 2, H - 1}):
+        q, k, v = (x[0, h].double().requires_grad_(True) for x in (Q, K, V))
+        E1, E2 = q @ W1.T + bias, k @ W2.T + bias + ((k @ C2) * k).sum(1, keepdim=True)
+        P = torch.exp(E1 - E1.detach().max(1, keepdim=True).values)
+        S = torch.exp(E2 - E2.detach().max())
+        Y = (P @ (S.T @ v)) / (P @ S.sum(0))[:, None]
+        ref = torch.autograd.grad((Y * dY[0, h].double()).sum(), (q, k, v))
+        # (one key: the gradients of Q and K vanish by construction; their rounding is measured against dY and V)
+        floor = 1e-3 * float(dY[0, h].double().norm() * V[0, h].double().norm(dim=1).max())
+        for g, r, name in zip(got, ref, ("dQ", "dK", "dV")):
+            fro, row = util.gradient_errors(g[0, h].double().cpu().numpy(), r.cpu().numpy(), floor)
+            assert fro <= 2e-2 and row <= 8e-2, (h, name, fro, row)
+
+
 def test_backward_whole_sequences_per_workgroup_is_bitwise_reproducible(fs):
     """The one-workgroup backward pass reuses one LDS region for six loops and a transposition, ordered by workgroup
     barriers only, and reads back rows of G1 that the same workgroup wrote to memory: a missing barrier would show up
