@@ -42,7 +42,7 @@ bool groups_ok(int g, int B, int H) { return g == 1 || g == H || g == B * H; }
 
 struct AttnPlan {
   int pgroups, ldt, nseg, rows_per_seg;
-  size_t off_W, off_Wbf, off_bias, off_kmax, off_rk, off_state, total;
+  size_t off_W, off_kpart, off_bias, off_kmax, off_rk, off_state, kcap, total;
 };
 
 // Every attention workspace starts with one 32-bit word (in a block of kAlign bytes): the number of output rows of the
@@ -61,7 +61,8 @@ void plan_contraction(int BH, int pgroups, int Lk, int d, int M, int nv1, int ca
   size_t off = kAlign;       // the counter word; the key maxima follow it so that one fill clears both
   p->off_kmax = off; off = align_up(off + (size_t)BH * sizeof(uint32_t));
   p->off_W = off;    off = align_up(off + (size_t)pgroups * 2 * M * d * sizeof(float));
-  p->off_Wbf = off;  off = align_up(off + (size_t)pgroups * 2 * M * d * sizeof(uint16_t));
+  p->kcap = (size_t)pgroups * M * d;
+  p->off_kpart = off; off = align_up(off + p->kcap * sizeof(float));      // partial key maxima
   p->off_bias = off; off = align_up(off + (size_t)pgroups * 2 * M * sizeof(float));
   p->off_rk = off;   off = align_up(off + (size_t)BH * Lk * sizeof(float));       // key row terms (general attention kernels)
   p->off_state = off; off = align_up(off + (size_t)BH * p->nseg * M * p->ldt * sizeof(float));
@@ -352,9 +353,8 @@ int favorsharp_features(const float* theta, int side, const fs_tensor* X, int n,
   plan_contraction(1, 1, 32, d, M, 1, 0, &p);
   char* ws = (char*)workspace;
   float* W = (float*)(ws + p.off_W);
-  uint16_t* Wbf = (uint16_t*)(ws + p.off_Wbf);
   float* bias = (float*)(ws + p.off_bias);
-  if (int rc = launch_prep(theta, 1, Omega, 1, 1, 1, 1, M, d, W, Wbf, bias, st)) return rc;
+  if (int rc = launch_prep(theta, 1, Omega, 1, 1, 1, 1, M, d, W, bias, nullptr, 0, st)) return rc;
   const size_t dd = (size_t)d * d;
   const long long c_off = FS_THETA_HEADER + d + 2 * dd + (side == 2 ? dd : 0);
   return launch_gen_features(dev(X), n, d, qk_scale, alpha, W + (side == 2 ? (size_t)M * d : 0),
@@ -535,20 +535,22 @@ int attention_impl(const float* theta, int groups, const fs_tensor* Q, const fs_
   hipStream_t st = (hipStream_t)stream;
   char* ws = (char*)workspace;
   float* W = (float*)(ws + p.off_W);
-  uint16_t* Wbf = (uint16_t*)(ws + p.off_Wbf);
   float* bias = (float*)(ws + p.off_bias);
   uint32_t* kmax = (uint32_t*)(ws + p.off_kmax);
   float* state = (float*)(ws + p.off_state);
   const size_t dd = (size_t)d * d;
   const long long tf = (long long)favorsharp_theta_floats(d);
 
-  if (int rc = launch_prep(theta, groups, Omega, omega_groups, pgroups, B, H, M, d, W, Wbf, bias, st)) return rc;
-  // the counter word and the key maxima behind it
+  // (it clears the counter word and the key maxima behind it)
   unsigned* flushed = (unsigned*)ws;
-  if (int rc = launch_fill_u32((uint32_t*)ws, 0u, p.off_kmax / sizeof(uint32_t) + BH, st)) return rc;
+  if (int rc = launch_prep(theta, groups, Omega, omega_groups, pgroups, B, H, M, d, W, bias, (uint32_t*)ws,
+                           (int)(p.off_kmax / sizeof(uint32_t)) + BH, st))
+    return rc;
   GenSide qs{dev(Q), qk_scale, 0.f, W, bias, theta, groups, pgroups, tf, (long long)(FS_THETA_HEADER + d + 2 * dd)};
   GenSide ks{dev(K), qk_scale, 0.f, W, bias, theta, groups, pgroups, tf, (long long)(FS_THETA_HEADER + d + 3 * dd)};
   ks.rk = (float*)(ws + p.off_rk);      // the key row terms are evaluated once (k_gen_kmax) and read by the kernels after it
+  ks.kpart = (float*)(ws + p.off_kpart);
+  ks.kcap = p.kcap;
   if (int rc = launch_gen_kmax(ks, Lk, BH, H, M, d, kmax, st)) return rc;
   if (int rc = launch_gen_state(ks, dev(V), Lk, BH, H, M, d, dv, 1, p.ldt, p.rows_per_seg, p.nseg, kmax, nullptr, state, st))
     return rc;
@@ -714,7 +716,6 @@ int attention_backward_impl(const float* theta, int groups, const fs_tensor* Q, 
   hipStream_t st = (hipStream_t)stream;
   char* ws = (char*)workspace;
   float* W = (float*)(ws + p.k.off_W);
-  uint16_t* Wbf = (uint16_t*)(ws + p.k.off_Wbf);
   float* bias = (float*)(ws + p.k.off_bias);
   uint32_t* kmax = (uint32_t*)(ws + p.k.off_kmax);
   float* state = (float*)(ws + p.k.off_state);
@@ -728,13 +729,16 @@ int attention_backward_impl(const float* theta, int groups, const fs_tensor* Q, 
 
   // forward quantities: segment states of S^T [V 1] (summed, or their exclusive prefix when causal), then Y, the
   // denominators and the query shifts
-  if (int rc = launch_prep(theta, groups, Omega, omega_groups, pgroups, B, H, M, d, W, Wbf, bias, st)) return rc;
-  // the counter word and the key maxima behind it
+  // (it clears the counter word and the key maxima behind it)
   unsigned* flushed = (unsigned*)ws;
-  if (int rc = launch_fill_u32((uint32_t*)ws, 0u, p.k.off_kmax / sizeof(uint32_t) + BH, st)) return rc;
+  if (int rc = launch_prep(theta, groups, Omega, omega_groups, pgroups, B, H, M, d, W, bias, (uint32_t*)ws,
+                           (int)(p.k.off_kmax / sizeof(uint32_t)) + BH, st))
+    return rc;
   GenSide qs{dev(Q), qk_scale, 0.f, W, bias, theta, groups, pgroups, tf, (long long)(FS_THETA_HEADER + d + 2 * dd)};
   GenSide ks{dev(K), qk_scale, 0.f, W, bias, theta, groups, pgroups, tf, (long long)(FS_THETA_HEADER + d + 3 * dd)};
   ks.rk = (float*)(ws + p.k.off_rk);      // the key row terms are evaluated once (k_gen_kmax) and read by the kernels after it
+  ks.kpart = (float*)(ws + p.k.off_kpart);
+  ks.kcap = p.k.kcap;
   if (int rc = launch_gen_kmax(ks, Lk, BH, H, M, d, kmax, st)) return rc;
   if (int rc = launch_gen_state(ks, dev(V), Lk, BH, H, M, d, dv, 1, ldt, p.k.rows_per_seg, p.k.nseg, kmax, nullptr, state, st))
     return rc;
@@ -829,17 +833,18 @@ int favorsharp_kernel_matvec(const float* theta, const fs_tensor* X, const fs_te
   hipStream_t st = (hipStream_t)stream;
   char* ws = (char*)workspace;
   float* W = (float*)(ws + p.off_W);
-  uint16_t* Wbf = (uint16_t*)(ws + p.off_Wbf);
   float* bias = (float*)(ws + p.off_bias);
   uint32_t* kmax = (uint32_t*)(ws + p.off_kmax);
   float* state = (float*)(ws + p.off_state);
   const size_t dd = (size_t)d * d;
   const long long tf = (long long)favorsharp_theta_floats(d);
-  if (int rc = launch_prep(theta, 1, Omega, 1, 1, 1, 1, M, d, W, Wbf, bias, st)) return rc;
-  if (int rc = launch_fill_u32(kmax, 0u, 1, st)) return rc;
+  if (int rc = launch_prep(theta, 1, Omega, 1, 1, 1, 1, M, d, W, bias, kmax, 1, st)) return rc;
   GenSide qs{dev(X), qk_scale, alpha, W, bias, theta, 1, 1, tf, (long long)(FS_THETA_HEADER + d + 2 * dd)};
   GenSide ks{dev(Y), qk_scale, alpha, W, bias, theta, 1, 1, tf, (long long)(FS_THETA_HEADER + d + 3 * dd)};
   qs.X.sb = qs.X.sh = ks.X.sb = ks.X.sh = 0;
+  ks.rk = (float*)(ws + p.off_rk);
+  ks.kpart = (float*)(ws + p.off_kpart);
+  ks.kcap = p.kcap;
   TensorDev Cv{C, FS_F32, 0, 0, n};
   TensorDev Ov{out, FS_F32, 0, 0, n};
   if (int rc = launch_gen_kmax(ks, Ny, 1, 1, M, d, kmax, st)) return rc;

@@ -25,6 +25,8 @@ struct GenSide {
   long long c_offset;   // offset of this side's C matrix inside a parameter set
   float* rk = nullptr;  // [B*H][rows] row terms of this side's rows (written by k_gen_kmax, read by the kernels after
                         // it instead of evaluating the quadratic form once per feature block); nullptr: none
+  float* kpart = nullptr; // room for kcap partial key maxima (k_gen_kmax leaves them, k_gen_state finds the maximum)
+  size_t kcap = 0;
 };
 
 size_t gen_lds_features(int d);
@@ -34,14 +36,14 @@ size_t gen_lds_causal(int d, int ldt);
 size_t gen_lds_stats(int d);
 
 int launch_prep(const float* theta, int groups, const float* Omega, int omega_groups, int pgroups, int B, int H,
-                int M, int d, float* W, uint16_t* Wbf, float* bias, hipStream_t st);
+                int M, int d, float* W, float* bias, uint32_t* clear, int nclear, hipStream_t st);   // clear[0 .. nclear) = 0
 int launch_fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t st);
 int launch_gen_features(const TensorDev& X, int n, int d, float scale, float alpha, const float* W, const float* bias,
                         const float* theta, long long c_offset, int M, float* out, float* row_logscale,
                         hipStream_t st);
 int launch_gen_kmax(const GenSide& ks, int Lk, int BH, int H, int M, int d, uint32_t* kmax_u, hipStream_t st);
 int launch_gen_state(const GenSide& ks, const TensorDev& V, int Lk, int BH, int H, int M, int d, int nv,
-                     int append_ones, int ldt, int rows_per_seg, int nseg, const uint32_t* kmax_u,
+                     int append_ones, int ldt, int rows_per_seg, int nseg, uint32_t* kmax_u,
                      const float* row_shift, float* Tpart, hipStream_t st);
 int launch_gen_reduce(float* Tpart, int BH, int nseg, size_t per_state, int prefix, hipStream_t st);
 int launch_gen_apply(const GenSide& qs, int Lq, int BH, int H, int M, int d, int nv, int ldt, const float* T,

@@ -1,0 +1,361 @@
+// General-shape kernels on fp32 matrix instructions (v_mfma_f32_16x16x4_f32) without data movement between the stages:
+// any d <= 128, any M, f32 or bf16 storage.  (The kernels that still stage every operand in LDS: kernels_generic.hip.)
+//
+// Lane l = (g, c) = (l / 16, l % 16) supplies A[i = c][k = g] and B[k = g][j = c] and owns D[i = 4 g + r][j = c] in register
+// r.  The order of the contraction index is free as long as both operands agree, and with k = g of step r standing for
+// index 4 g + r an accumulator register IS an operand: features (rows = tokens, columns = features) feed the state update
+// as they come from exp2, and so on.  Rows of 16 q + 4 g .. + 3 of a tensor are one 16-byte load per lane and four steps.  What
+// is left beside the matrix instructions (32 cycles each, 2048 flops) is a few per cent: these kernels are bound by the fp32
+// matrix rate.
+#include <type_traits>
+
+#include "fs_common.h"
+#include "kernels.h"
+
+namespace fs {
+namespace {
+
+__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+
+// Five widths: rows of at most 16 Q numbers, values of at most 16 VT columns.  Nothing in a kernel depends on the sizes within
+// a width (a uniform branch around a load is a wait for it: state of B2 H4 L4096 d64 M256 68 us with, 37 without): what lies past a row
+// or a value row is multiplied by zero.
+template <int Q> constexpr int VT_OF = Q == 1 ? 2 : Q == 2 ? 3 : Q == 4 ? 5 : Q == 6 ? 7 : 9;
+
+// BF: storage of a tensor.
+template <int BF>
+__device__ __forceinline__ float load1(const TensorDev& t, long long idx) {
+  return BF ? bf16_bits_to_f32(((const uint16_t*)t.ptr)[idx]) : ((const float*)t.ptr)[idx];
+}
+
+// Numbers 16 q + 4 g .. + 3 of a row of d at element `at`, as they lie in memory.  Rows start at multiples of 16 bytes, so that a
+// row of a multiple of four numbers is read four at a time and never past its end; groups past the end repeat the last.
+template <int BF, int Q> struct RawRow { typename std::conditional<BF, u32x2, u32x4>::type v[Q]; };
+// D4: d is a multiple of four.
+template <int D4, int BF, int Q>
+__device__ __forceinline__ void fetch_row(RawRow<BF, Q>& x, const TensorDev& t, long long at, int d, int g) {
+  typedef typename std::conditional<BF, u32x2, u32x4>::type Raw;
+  typedef typename std::conditional<BF, uint16_t, uint32_t>::type Elem;
+  const Elem* p = (const Elem*)t.ptr + at;
+  if constexpr (D4) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) x.v[q] = *(const Raw*)(p + min(16 * q + 4 * g, d - 4));
+  } else {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      uint32_t e[4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int col = 16 * q + 4 * g + s;
+        const uint32_t v = p[min(col, d - 1)];
+        e[s] = col < d ? v : 0u;
+      }
+      if constexpr (BF) x.v[q] = u32x2{e[0] | (e[1] << 16), e[2] | (e[3] << 16)};
+      else x.v[q] = u32x4{e[0], e[1], e[2], e[3]};
+    }
+  }
+}
+// scale[q]: what the numbers of group q are multiplied by, zero past the row (row_scales).
+template <int Q>
+__device__ __forceinline__ void row_scales(float (&sc)[Q], int d, float scale, int g) {
+#pragma unroll
+  for (int q = 0; q < Q; ++q) sc[q] = 16 * q + 4 * g < d ? scale : 0.f;
+}
+template <int BF, int Q>
+__device__ __forceinline__ f32x4 row_group(const RawRow<BF, Q>& x, int q, float sc) {
+  if constexpr (BF) {
+    const u32x2 p = x.v[q];
+    return f32x4{__uint_as_float(p[0] << 16), __uint_as_float(p[0] & 0xffff0000u), __uint_as_float(p[1] << 16), __uint_as_float(p[1] & 0xffff0000u)} * sc;
+  } else {
+    return __builtin_bit_cast(f32x4, x.v[q]) * sc;
+  }
+}
+
+// ---------------------------------------------------------------------------------------------------
+// Key-side maximum of the exponent per (b, h), max_{j,m} E2[j,m]: one partial maximum per workgroup, part[bh][block], or
+// where there is no room for them an atomic maximum into kmax[bh] (ordered-uint image; atomics of many workgroups on one
+// address queue up in memory, 15 ns each: 38 us of a 188 us call with one per wave); and the row terms of the keys (rk).  A workgroup takes four (wide rows: two) tiles of 16 tokens: every wave finds the row terms of one, then holds all of
+// them as operands and takes every fourth tile of 16 features through them.  grid (tokens, B*H), block 256.
+// ---------------------------------------------------------------------------------------------------
+template <int Q> constexpr int KMAX_T = Q >= 6 ? 2 : 4;      // token tiles per workgroup
+template <int Q, int XB, int D4>
+__global__ void __launch_bounds__(256, 2) k_gen_kmax(GenSide ks, int Lk, int H, int M, int d, uint32_t* kmax_u, float* part) {
+  constexpr int TT = KMAX_T<Q>;
+  __shared__ __align__(16) float rterm[16 * TT];
+  __shared__ float wmax[4];
+  const int bh = blockIdx.y, b = bh / H, h = bh % H, row0 = blockIdx.x * 16 * TT;
+  const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int pg = group_of(ks.pgroups, b, h, H);
+  const TensorDev W{ks.W + ((size_t)pg * 2 + 1) * M * d, 0, 0, 0, 0};
+  const float* bias = ks.bias + ((size_t)pg * 2 + 1) * M;
+  const float* th = ks.theta + (size_t)group_of(ks.groups, b, h, H) * ks.theta_stride;
+  const long long xbase = b * ks.X.sb + h * ks.X.sh;
+  float sc[Q], one[Q];
+  row_scales(sc, d, ks.scale, g);
+  row_scales(one, d, 1.f, g);
+  // everything the kernel starts from is requested at once
+  RawRow<XB, Q> raw[TT];
+#pragma unroll
+  for (int t = 0; t < TT; ++t) fetch_row<D4>(raw[t], ks.X, xbase + (long long)min(row0 + 16 * t + c, Lk - 1) * ks.X.sl, d, g);
+  RawRow<XB, Q> mine;
+  const int tw = w & (TT - 1), row = row0 + 16 * tw + c;
+  fetch_row<D4>(mine, ks.X, xbase + (long long)min(row, Lk - 1) * ks.X.sl, d, g);
+  const int nft = (M + 15) / 16;
+  RawRow<0, Q> wn;
+  fetch_row<D4>(wn, W, (long long)min(16 * w + c, M - 1) * d, d, g);
+  float bn = bias[min(16 * w + c, M - 1)];
+  {
+    float p = 0.f;
+    if (((int)th[2]) & 1) {
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const f32x4 x = row_group(mine, q, sc[q]);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) p += x[s] * x[s];
+      }
+      p *= ks.alpha - 0.5f;
+    } else {
+      // (C x)[a] for a = 16 t + 4 g + r of token c, times x[a], which the lane holds
+      const float* Cmat = th + ks.c_offset;
+#pragma unroll
+      for (int t = 0; t < Q; ++t) {
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        const int a = 16 * t + c;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+          const f32x4 x = row_group(mine, q, sc[q]);
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            const int col = 16 * q + 4 * g + s;
+            const float e = Cmat[(size_t)min(a, d - 1) * d + min(col, d - 1)];
+            acc = mfma4(a < d && col < d ? e : 0.f, x[s], acc);
+          }
+        }
+        const f32x4 xt = row_group(mine, t, sc[t]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) p += xt[r] * (acc[r] + ks.alpha * xt[r]);
+      }
+    }
+    p += __shfl_xor(p, 16);
+    p += __shfl_xor(p, 32);
+    if (g == 0) {
+      const float v = row < Lk ? kLog2e * p : -INFINITY;
+      rterm[16 * tw + c] = v;      // (two waves for a tile, where there are two tiles, agree)
+      if (row < Lk) ks.rk[(size_t)bh * Lk + row] = v;
+    }
+  }
+  f32x4 x[TT][Q];
+#pragma unroll
+  for (int t = 0; t < TT; ++t)
+#pragma unroll
+    for (int q = 0; q < Q; ++q) x[t][q] = row_group(raw[t], q, sc[q]);
+  __syncthreads();
+  f32x4 rt[TT];
+#pragma unroll
+  for (int t = 0; t < TT; ++t) rt[t] = *(const f32x4*)(&rterm[16 * t + 4 * g]);
+  float m = -INFINITY;
+  for (int ft = w; ft < nft; ft += 4) {
+    f32x4 acc[TT];
+#pragma unroll
+    for (int t = 0; t < TT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    f32x4 wr[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) wr[q] = row_group(wn, q, one[q]);
+    const float bf = 16 * ft + c < M ? bn : -INFINITY;
+    const int fn = min(16 * (ft + 4) + c, M - 1);       // the next tile's row travels meanwhile
+    fetch_row<D4>(wn, W, (long long)fn * d, d, g);
+    bn = bias[fn];
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int t = 0; t < TT; ++t) acc[t] = mfma4(x[t][q][s], wr[q][s], acc[t]);
+#pragma unroll
+    for (int t = 0; t < TT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) m = fmaxf(m, acc[t][r] + bf + rt[t][r]);
+  }
+#pragma unroll
+  for (int s = 1; s < 64; s <<= 1) m = fmaxf(m, __shfl_xor(m, s));
+  if (lane == 0) wmax[w] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    m = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
+    if (part != nullptr) part[(size_t)bh * gridDim.x + blockIdx.x] = m;
+    else atomicMax(&kmax_u[bh], float_to_ordered(m));
+  }
+}
+
+// ---------------------------------------------------------------------------------------------------
+// Partial states (Section 2.1, S^T C): Tpart[bh][seg][m][v] = sum_{j in seg} exp2(E2[j,m] - kmax) * V1[j,v].  With row_shift !=
+// nullptr the query side of the backward pass: features of side 0 with the per-row shifts of the forward pass (no row term),
+// "values" = rows of the output gradient.  A wave holds 16 FT features: their rows of W~ and their state stay in
+// registers, tokens pass by sixteen at a time straight from memory; no LDS, no barrier.  f32 B2 H4 L4096 d64 M256: 60 -> 37
+// us (18 at the matrix rate), bf16 B1 H16 L4096 d128 M512: 425 -> 310 (118).  grid (nseg, ceil(M / (16 FT
+// waves)), B*H), block 64 waves.
+// ---------------------------------------------------------------------------------------------------
+template <int Q> constexpr int STATE_FT = Q >= 6 ? 2 : 4;
+
+template <int Q, int XB, int VB, int D4>
+__global__ void __launch_bounds__(256, 2) k_gen_state(GenSide ks, TensorDev V, int Lk, int H, int M, int d, int nv, int append_ones,
+                                                      int ldt, int rows_per_seg, int nseg, uint32_t* kmax_u, const float* part,
+                                                      int npart, const float* row_shift, float* Tpart) {
+  constexpr int FT = STATE_FT<Q>, VT = VT_OF<Q>;
+  const int seg = blockIdx.x, bh = blockIdx.z, b = bh / H, h = bh % H;
+  const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int f0 = 16 * FT * (blockIdx.y * (blockDim.x >> 6) + w);
+  if (f0 >= M) return;
+  const int pg = group_of(ks.pgroups, b, h, H), side = row_shift == nullptr ? 1 : 0;
+  const TensorDev W{ks.W + ((size_t)pg * 2 + side) * M * d, 0, 0, 0, 0};
+  const float* bias = ks.bias + ((size_t)pg * 2 + side) * M;
+  float shift = 0.f;
+  if (row_shift == nullptr) {
+    if (part != nullptr) {
+      shift = -INFINITY;
+      for (int i = lane; i < npart; i += 64) shift = fmaxf(shift, part[(size_t)bh * npart + i]);
+#pragma unroll
+      for (int s = 1; s < 64; s <<= 1) shift = fmaxf(shift, __shfl_xor(shift, s));
+      if (seg == 0 && f0 == 0 && lane == 0) kmax_u[bh] = float_to_ordered(shift);      // for the kernels behind this one
+    } else {
+      shift = ordered_to_float(kmax_u[bh]);
+    }
+  }
+  const int row_beg = seg * rows_per_seg, row_end = min(Lk, row_beg + rows_per_seg);
+  const long long xbase = b * ks.X.sb + h * ks.X.sh, vbase = b * V.sb + h * V.sh;
+  const float* rterm = row_shift == nullptr ? ks.rk + (size_t)bh * Lk : row_shift + (size_t)bh * Lk;
+  const float rsign = row_shift == nullptr ? 1.f : -1.f;
+  typedef typename std::conditional<VB, uint16_t, uint32_t>::type VElem;
+
+  float sc[Q];
+  row_scales(sc, d, ks.scale, g);
+  int off[VT];                       // the columns of values the lane reads
+#pragma unroll
+  for (int vt = 0; vt < VT; ++vt) off[vt] = min(16 * vt + c, nv - 1);
+  const int ones_col = append_ones ? nv : -1;
+  RawRow<XB, Q> xn;
+  fetch_row<D4>(xn, ks.X, xbase + (long long)min(row_beg + c, row_end - 1) * ks.X.sl, d, g);
+  f32x4 wr[FT][Q], T[FT][VT];
+  float bf[FT];
+#pragma unroll
+  for (int ft = 0; ft < FT; ++ft) {
+    const int f = f0 + 16 * ft + c;
+    RawRow<0, Q> raw;
+    fetch_row<D4>(raw, W, (long long)min(f, M - 1) * d, d, g);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) wr[ft][q] = row_group(raw, q, 16 * q + 4 * g < d ? 1.f : 0.f);
+    bf[ft] = f < M ? bias[f] : -INFINITY;
+#pragma unroll
+    for (int vt = 0; vt < VT; ++vt) T[ft][vt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  for (int row0 = row_beg; row0 < row_end; row0 += 16) {
+    // values of tokens 4 g + r, column 16 vt + c, and the tokens' row terms: used after the projections
+    VElem vraw[VT][4];
+    float rt[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int rc = min(row0 + 4 * g + r, row_end - 1);
+      rt[r] = rterm[rc];
+      const VElem* p = (const VElem*)V.ptr + vbase + (long long)rc * V.sl;
+#pragma unroll
+      for (int vt = 0; vt < VT; ++vt) vraw[vt][r] = p[off[vt]];
+    }
+    f32x4 acc[FT];
+#pragma unroll
+    for (int ft = 0; ft < FT; ++ft) acc[ft] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const f32x4 x = row_group(xn, q, sc[q]);
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int ft = 0; ft < FT; ++ft) acc[ft] = mfma4(x[s], wr[ft][q][s], acc[ft]);
+    }
+    fetch_row<D4>(xn, ks.X, xbase + (long long)min(row0 + 16 + c, row_end - 1) * ks.X.sl, d, g);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const bool ok = row0 + 4 * g + r < row_end;
+      rt[r] = ok ? rsign * rt[r] - shift : -INFINITY;
+#pragma unroll
+      for (int ft = 0; ft < FT; ++ft) acc[ft][r] = fast_exp2(acc[ft][r] + (bf[ft] + rt[r]));
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const bool ok = row0 + 4 * g + r < row_end;
+#pragma unroll
+      for (int vt = 0; vt < VT; ++vt) {
+        float v = VB ? bf16_bits_to_f32((uint16_t)vraw[vt][r]) : __uint_as_float((uint32_t)vraw[vt][r]);
+        v = 16 * vt + c < nv ? v : (16 * vt + c == ones_col ? 1.f : 0.f);
+        v = ok ? v : 0.f;
+#pragma unroll
+        for (int ft = 0; ft < FT; ++ft) T[ft][vt] = mfma4(acc[ft][r], v, T[ft][vt]);
+      }
+    }
+  }
+  float* out = Tpart + (((size_t)bh * nseg + seg) * M) * ldt;
+#pragma unroll
+  for (int ft = 0; ft < FT; ++ft)
+#pragma unroll
+    for (int vt = 0; vt < VT; ++vt)
+      if (16 * vt < ldt) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int m = f0 + 16 * ft + 4 * g + r;
+          if (m < M) out[(size_t)m * ldt + 16 * vt + c] = T[ft][vt][r];
+        }
+      }
+}
+
+#define FS_LAUNCH_CHECK() do { if (hipGetLastError() != hipSuccess) return 5; } while (0)
+
+template <class F>
+int by_width(int d, int ldt, F launch) {
+  if (d <= 16 && ldt <= 32) return launch(std::integral_constant<int, 1>());
+  if (d <= 32 && ldt <= 48) return launch(std::integral_constant<int, 2>());
+  if (d <= 64 && ldt <= 80) return launch(std::integral_constant<int, 4>());
+  if (d <= 96 && ldt <= 112) return launch(std::integral_constant<int, 6>());
+  return launch(std::integral_constant<int, 8>());
+}
+
+}  // namespace
+
+// Rows of a workgroup of k_gen_kmax, and its partial maxima where they fit.
+static int kmax_rows(int d) {
+  return by_width(d, 0, [](auto q) { return 16 * KMAX_T<q()>; });
+}
+static float* kmax_part(const GenSide& ks, int Lk, int BH, int d) {
+  const int n = (Lk + kmax_rows(d) - 1) / kmax_rows(d);
+  return ks.kpart != nullptr && (size_t)BH * n <= ks.kcap ? ks.kpart : nullptr;
+}
+
+int launch_gen_kmax(const GenSide& ks, int Lk, int BH, int H, int M, int d, uint32_t* kmax_u, hipStream_t st) {
+  return by_width(d, 0, [&](auto width) -> int {
+    constexpr int Q = width(), TR = 16 * KMAX_T<Q>;
+    auto kernel = d % 4 ? (ks.X.dtype ? k_gen_kmax<Q, 1, 0> : k_gen_kmax<Q, 0, 0>) : (ks.X.dtype ? k_gen_kmax<Q, 1, 1> : k_gen_kmax<Q, 0, 1>);
+    hipLaunchKernelGGL(kernel, dim3((Lk + TR - 1) / TR, BH), dim3(256), 0, st, ks, Lk, H, M, d, kmax_u, kmax_part(ks, Lk, BH, d));
+    FS_LAUNCH_CHECK();
+    return 0;
+  });
+}
+
+int launch_gen_state(const GenSide& ks, const TensorDev& V, int Lk, int BH, int H, int M, int d, int nv, int append_ones, int ldt,
+                     int rows_per_seg, int nseg, uint32_t* kmax_u, const float* row_shift, float* Tpart, hipStream_t st) {
+  return by_width(d, ldt, [&](auto width) -> int {
+    constexpr int Q = width(), FT = STATE_FT<Q>;
+    const int groups = (M + 16 * FT - 1) / (16 * FT), waves = groups < 4 ? groups : 4;
+    auto pick = [&](auto d4) {
+      constexpr int D4 = d4();
+      return !ks.X.dtype ? k_gen_state<Q, 0, 0, D4> : V.dtype ? k_gen_state<Q, 1, 1, D4> : k_gen_state<Q, 1, 0, D4>;
+    };
+    auto kernel = d % 4 ? pick(std::integral_constant<int, 0>()) : pick(std::integral_constant<int, 1>());
+    hipLaunchKernelGGL(kernel, dim3(nseg, (groups + waves - 1) / waves, BH), dim3(64 * waves), 0, st, ks, V, Lk, H, M, d,
+                       nv, append_ones, ldt, rows_per_seg, nseg, kmax_u, kmax_part(ks, Lk, BH, d), (Lk + kmax_rows(d) - 1) / kmax_rows(d),
+                       row_shift, Tpart);
+    FS_LAUNCH_CHECK();
+    return 0;
+  });
+}
+
+}  // namespace fs

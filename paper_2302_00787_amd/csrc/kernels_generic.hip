@@ -331,7 +331,7 @@ __device__ void rowmax_pass2(uint32_t* rowmax_u, const float* Xs, float* Ws, flo
 // ---------------------------------------------------------------------------------------------------
 constexpr int PREP_F = 4;
 __global__ void __launch_bounds__(128) k_prep(const float* theta, int groups, const float* Omega, int omega_groups, int pgroups,
-                       int B, int H, int M, int d, float* W, uint16_t* Wbf, float* bias) {
+                       int B, int H, int M, int d, float* W, float* bias, uint32_t* clear, int nclear) {
   __shared__ float om[PREP_F][128];
   const int m0 = blockIdx.x * PREP_F, side = blockIdx.y, pg = blockIdx.z, nf = min(PREP_F, M - m0);
   int b = 0, h = 0;
@@ -343,6 +343,8 @@ __global__ void __launch_bounds__(128) k_prep(const float* theta, int groups, co
   const float* Bm = th + FS_THETA_HEADER_ + d + (side ? (size_t)d * d : 0);
   const size_t o = (((size_t)pg * 2 + side) * M + m0);
   const int c = threadIdx.x;
+  // the call's counter and key maxima start at zero (a launch of its own costs 4 us)
+  for (int i = ((blockIdx.z * 2 + blockIdx.y) * gridDim.x + blockIdx.x) * 128 + c; i < nclear; i += gridDim.x * 2 * gridDim.z * 128) clear[i] = 0u;
 #pragma unroll
   for (int f = 0; f < PREP_F; ++f) om[f][c] = (f < nf && c < d) ? omg[(size_t)f * d + c] : 0.f;
   __syncthreads();
@@ -370,7 +372,6 @@ __global__ void __launch_bounds__(128) k_prep(const float* theta, int groups, co
       if (f < nf) {
         const float v = acc[f] * kLog2e;
         W[(o + f) * d + c] = v;
-        Wbf[(o + f) * d + c] = f32_to_bf16_bits(v);
       }
   }
   if (c < nf) {
@@ -426,125 +427,6 @@ __global__ void __launch_bounds__(NT) k_gen_features(TensorDev X, int n, int d, 
       float e = acc[r] + bias_s[f];
       e = (row_logscale != nullptr) ? e - ordered_to_float(rowmax_u[row]) : e + rterm[row];
       if (row0 + row < n && m0 + f < M) out[(size_t)(row0 + row) * M + m0 + f] = fast_exp2(e);
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------------------------------
-// Key-side maximum of the exponent per (b, h): kmax[bh] = max_{j,m} E2[j,m] (ordered-uint image, atomicMax).
-// grid (ceil(Lk/32), B*H).
-// ---------------------------------------------------------------------------------------------------
-template <int WD>
-__global__ void __launch_bounds__(NT) k_gen_kmax(GenSide ks, int Lk, int H, int M, int d, uint32_t* kmax_u) {
-  extern __shared__ float smem[];
-  const int dpad = (d + 3) & ~3, ld = dpad + 1;
-  float* Xs = smem;
-  float* Ws = Xs + TR * ld;
-  float* bias_s = Ws + MB * ld;
-  float* rterm = bias_s + MB;
-  uint32_t* rowmax_u = (uint32_t*)(rterm + TR);
-  const int bh = blockIdx.y, b = bh / H, h = bh % H;
-  const int row0 = blockIdx.x * TR;
-  const int pg = group_of(ks.pgroups, b, h, H);
-  const float* W = ks.W + ((size_t)pg * 2 + 1) * M * d;
-  const float* bias = ks.bias + ((size_t)pg * 2 + 1) * M;
-  const float* Cmat = side_cmat(ks, b, h, H);
-
-  load_rows<WD>(Xs, ld, ks.X, b * ks.X.sb + h * ks.X.sh, row0, Lk, d, dpad, ks.scale);
-  __syncthreads();
-  row_terms(rterm, Xs, ld, d, Cmat, ks.alpha);
-  rowmax_pass<WD>(rowmax_u, Xs, Ws, bias_s, ld, W, bias, M, d, dpad);
-  if (threadIdx.x < 64) {
-    float v = (threadIdx.x < TR && row0 + threadIdx.x < Lk)
-                  ? ordered_to_float(rowmax_u[threadIdx.x]) + rterm[threadIdx.x] : -INFINITY;
-    for (int s = 1; s < 64; s <<= 1) v = fmaxf(v, __shfl_xor(v, s));
-    if (threadIdx.x == 0) atomicMax(&kmax_u[bh], float_to_ordered(v));
-    if (ks.rk != nullptr && threadIdx.x < TR && row0 + (int)threadIdx.x < Lk) ks.rk[(size_t)bh * Lk + row0 + threadIdx.x] = rterm[threadIdx.x];
-  }
-}
-
-// ---------------------------------------------------------------------------------------------------
-// Key-side partial states (Section 2.1, S^T C): Tpart[bh][seg][m][v] = sum_{j in seg} exp2(E2[j,m] - kmax) * V1[j,v].
-// grid (nseg, ceil(M/32), B*H).
-// ---------------------------------------------------------------------------------------------------
-// With row_shift != nullptr the kernel serves the backward pass on the query side: features of side 1 with the
-// per-row shifts the forward pass used (no row term in the exponent), "values" = the rows of the output gradient.
-template <int WD>
-__global__ void __launch_bounds__(NT) k_gen_state(GenSide ks, TensorDev V, int Lk, int H, int M, int d, int nv,
-                                                  int append_ones, int ldt, int rows_per_seg, int nseg,
-                                                  const uint32_t* kmax_u, const float* row_shift, float* Tpart) {
-  extern __shared__ float smem[];
-  const int dpad = (d + 3) & ~3, ld = dpad + 1, ldv = ldt + 1, lds = MB + 1;
-  float* Xs = smem;
-  float* Ws = Xs + TR * ld;
-  float* Vs = Ws + MB * ld;
-  float* Ss = Vs + TR * ldv;
-  float* bias_s = Ss + TR * lds;
-  float* rterm = bias_s + MB;
-  const int seg = blockIdx.x, m0 = blockIdx.y * MB, bh = blockIdx.z, b = bh / H, h = bh % H;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int pg = group_of(ks.pgroups, b, h, H);
-  const int side = row_shift == nullptr ? 1 : 0;
-  const float* W = ks.W + ((size_t)pg * 2 + side) * M * d;
-  const float* bias = ks.bias + ((size_t)pg * 2 + side) * M;
-  const float* Cmat = side_cmat(ks, b, h, H);
-  const float c = row_shift == nullptr ? ordered_to_float(kmax_u[bh]) : 0.f;
-  const int nvt = ldt / 16, ntiles = 2 * nvt;
-
-  load_wblock<WD>(Ws, bias_s, ld, W, bias, m0, M, d, dpad);
-  f32x4 acc[ACC_V<WD, 4>];
-#pragma unroll
-  for (int t = 0; t < ACC_V<WD, 4>; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  const int row_end = min(Lk, (seg + 1) * rows_per_seg);
-  const long long xbase = b * ks.X.sb + h * ks.X.sh, vbase = b * V.sb + h * V.sh;
-  // (the rows and values of the next step are fetched while the current one computes)
-  RowTile<WD, NT> xr;
-  ValTile<WD, NT> vr;
-  rows_fetch(xr, ks.X, xbase, seg * rows_per_seg, row_end, d);
-  values_fetch(vr, V, vbase, seg * rows_per_seg, row_end, nv);
-  for (int row0 = seg * rows_per_seg; row0 < row_end; row0 += TR) {
-    __syncthreads();
-    rows_put(xr, ks.X, Xs, ld, row0, row_end, d, dpad, ks.scale);
-    values_put(vr, V, Vs, ldv, row0, row_end, nv, ldt, append_ones);
-    __syncthreads();
-    if (row0 + TR < row_end) {
-      rows_fetch(xr, ks.X, xbase, row0 + TR, row_end, d);
-      values_fetch(vr, V, vbase, row0 + TR, row_end, nv);
-    }
-    if (row_shift == nullptr) row_terms_of(rterm, ks, bh, Lk, row0, row_end, Xs, ld, d, Cmat, ks.alpha);
-    else if (threadIdx.x < TR) rterm[threadIdx.x] = row0 + threadIdx.x < row_end ? -row_shift[(size_t)bh * Lk + row0 + threadIdx.x] : -INFINITY;
-    __syncthreads();
-    const f32x4 e = proj_tile(Xs, Ws, ld, dpad);
-    const int f = (w & 1) * 16 + (lane & 15);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int row = (w >> 1) * 16 + 4 * (lane >> 4) + r;
-      Ss[row * lds + f] = (m0 + f < M) ? fast_exp2(e[r] + bias_s[f] + rterm[row] - c) : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int tl = 0; tl < ACC_V<WD, 4>; ++tl) {
-      const int t = w + 4 * tl;
-      if (t < ntiles) {
-        const int mt = t & 1, vt = t >> 1;
-        const float* ap = Ss + (lane >> 4) * lds + mt * 16 + (lane & 15);      // A[i=m][k=j] = Ss[j][m]
-        const float* bp = Vs + (lane >> 4) * ldv + vt * 16 + (lane & 15);      // B[k=j][n=v] = Vs[j][v]
-        acc[tl] = mfma_chain(ap, lds, bp, ldv, TR, acc[tl]);
-      }
-    }
-  }
-  float* out = Tpart + (((size_t)bh * nseg + seg) * M) * ldt;
-#pragma unroll
-  for (int tl = 0; tl < ACC_V<WD, 4>; ++tl) {
-    const int t = w + 4 * tl;
-    if (t < ntiles) {
-      const int mt = t & 1, vt = t >> 1;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = m0 + mt * 16 + 4 * (lane >> 4) + r;
-        if (m < M) out[(size_t)m * ldt + vt * 16 + (lane & 15)] = acc[tl][r];
-      }
     }
   }
 }
@@ -1582,9 +1464,9 @@ static int by_width(int d, int ldt, F launch) {
 }
 
 int launch_prep(const float* theta, int groups, const float* Omega, int omega_groups, int pgroups, int B, int H,
-                int M, int d, float* W, uint16_t* Wbf, float* bias, hipStream_t st) {
+                int M, int d, float* W, float* bias, uint32_t* clear, int nclear, hipStream_t st) {
   hipLaunchKernelGGL(k_prep, dim3((M + PREP_F - 1) / PREP_F, 2, pgroups), dim3(128), 0, st, theta, groups, Omega, omega_groups, pgroups, B, H,
-                     M, d, W, Wbf, bias);
+                     M, d, W, bias, clear, nclear);
   FS_LAUNCH_CHECK();
   return 0;
 }
@@ -1605,31 +1487,6 @@ int launch_gen_features(const TensorDev& X, int n, int d, float scale, float alp
     if (int rc = set_lds((const void*)k_gen_features<WD>, lds)) return rc;
     hipLaunchKernelGGL((k_gen_features<WD>), dim3((n + TR - 1) / TR), dim3(NT), lds, st, X, n, d, scale, alpha, W, bias, theta,
                        c_offset, M, out, row_logscale);
-    FS_LAUNCH_CHECK();
-    return 0;
-  });
-}
-
-int launch_gen_kmax(const GenSide& ks, int Lk, int BH, int H, int M, int d, uint32_t* kmax_u, hipStream_t st) {
-  return by_width(d, 0, [&](auto width) -> int {
-    constexpr int WD = width();
-    const size_t lds = gen_lds_features(d);
-    if (int rc = set_lds((const void*)k_gen_kmax<WD>, lds)) return rc;
-    hipLaunchKernelGGL((k_gen_kmax<WD>), dim3((Lk + TR - 1) / TR, BH), dim3(NT), lds, st, ks, Lk, H, M, d, kmax_u);
-    FS_LAUNCH_CHECK();
-    return 0;
-  });
-}
-
-int launch_gen_state(const GenSide& ks, const TensorDev& V, int Lk, int BH, int H, int M, int d, int nv,
-                     int append_ones, int ldt, int rows_per_seg, int nseg, const uint32_t* kmax_u,
-                     const float* row_shift, float* Tpart, hipStream_t st) {
-  return by_width(d, ldt, [&](auto width) -> int {
-    constexpr int WD = width();
-    const size_t lds = gen_lds_state(d, ldt);
-    if (int rc = set_lds((const void*)k_gen_state<WD>, lds)) return rc;
-    hipLaunchKernelGGL((k_gen_state<WD>), dim3(nseg, (M + MB - 1) / MB, BH), dim3(NT), lds, st, ks, V, Lk, H, M, d, nv,
-                       append_ones, ldt, rows_per_seg, nseg, kmax_u, row_shift, Tpart);
     FS_LAUNCH_CHECK();
     return 0;
   });
