@@ -17,6 +17,7 @@ COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-
 SOURCES = {
     "favorsharp_api.hip": [],
     "kernels_generic.hip": [],
+    "kernels_gen_walk.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "kernels_gen_rows.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "kernels_bf16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-mllvm", "-amdgpu-atomic-optimizer-strategy=None"],
     "kernels_bf16_causal.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-mllvm", "-amdgpu-atomic-optimizer-strategy=None"],

@@ -558,7 +558,9 @@ int attention_impl(const float* theta, int groups, const fs_tensor* Q, const fs_
   if (int rc = launch_gen_reduce(state, BH, p.nseg, per_state, causal, st)) return rc;
   if (event_main_begin && hipEventRecord((hipEvent_t)event_main_begin, st) != hipSuccess) return FS_ERR_DEVICE;
   int rc;
-  if (causal)
+  if (causal && gen_walk_supported(d, dv, M))
+    rc = launch_gen_walk(qs, ks, dev(V), Lk, BH, H, M, d, dv, p.ldt, p.rows_per_seg, p.nseg, kmax, state, dev(Y), nullptr, nullptr, st, flushed);
+  else if (causal)
     rc = launch_gen_causal(qs, ks, dev(V), Lk, BH, H, M, d, dv, p.ldt, p.rows_per_seg, p.nseg, kmax, state, dev(Y), nullptr, nullptr, st, flushed);
   else
     rc = launch_gen_apply(qs, Lq, BH, H, M, d, dv, p.ldt, state, (size_t)p.nseg * per_state, kmax, 0, dev(Y), nullptr, nullptr, st, flushed);
@@ -744,7 +746,11 @@ int attention_backward_impl(const float* theta, int groups, const fs_tensor* Q, 
     return rc;
   if (int rc = launch_gen_reduce(state, BH, p.k.nseg, per_state, causal, st)) return rc;
   const TensorDev gbuf{ghat, 0, (long long)H * Lq * ldt, (long long)Lq * ldt, (long long)ldt};
-  if (causal) {
+  const bool walks = causal && gen_walk_supported(d, dv, M);
+  if (walks) {
+    if (int rc = launch_gen_walk(qs, ks, dev(V), Lk, BH, H, M, d, dv, ldt, p.k.rows_per_seg, p.k.nseg, kmax, state, gbuf, den, shift, st, flushed))
+      return rc;
+  } else if (causal) {
     // the forward kernel advances its copy of the prefix states; the backward query kernel needs them afresh
     if (hipMemcpyAsync(state2, state, (size_t)BH * p.k.nseg * per_state * sizeof(float), hipMemcpyDeviceToDevice, st) != hipSuccess)
       return FS_ERR_DEVICE;
@@ -761,6 +767,9 @@ int attention_backward_impl(const float* theta, int groups, const fs_tensor* Q, 
   if (int rc = launch_gen_state(qs, gbuf, Lq, BH, H, M, d, ldt, 0, ldt, p.q.rows_per_seg, p.q.nseg, kmax, shift, rstate, st))
     return rc;
   if (int rc = launch_gen_reduce(rstate, BH, p.q.nseg, per_state, causal ? 2 : 0, st)) return rc;
+  if (walks)
+    return launch_gen_bwd_walks(qs, ks, dev(V), ghat, Lk, BH, H, M, d, dv, ldt, p.k.rows_per_seg, p.k.nseg, kmax, shift, state, rstate,
+                                dev(dQ), dev(dK), dev(dV), st);
   if (causal)
     return launch_gen_bwd_causal(qs, ks, dev(V), ghat, Lk, BH, H, M, d, dv, ldt, p.k.rows_per_seg, p.k.nseg, kmax, shift,
                                  state2, rstate, dev(dQ), dev(dK), dev(dV), st);

@@ -65,6 +65,15 @@ int launch_gen_bwd_causal(const GenSide& qs, const GenSide& ks, const TensorDev&
                           int M, int d, int nv, int ldt, int rows_per_seg, int nseg, const uint32_t* kmax_u,
                           const float* row_shift, float* Tstate, float* Rstate, const TensorDev& dQ, const TensorDev& dK,
                           const TensorDev& dV, hipStream_t st);
+// The same on kernels that keep the state in registers (kernels_gen_walk.hip); they leave the states in memory as they are.
+bool gen_walk_supported(int d, int dv, int M);
+int launch_gen_walk(const GenSide& qs, const GenSide& ks, const TensorDev& V, int L, int BH, int H, int M, int d, int nv, int ldt,
+                    int rows_per_seg, int nseg, const uint32_t* kmax_u, const float* Tstate, const TensorDev& Y, float* den_out,
+                    float* shift_out, hipStream_t st, unsigned* flushed);
+int launch_gen_bwd_walks(const GenSide& qs, const GenSide& ks, const TensorDev& V, const float* ghat, int L, int BH, int H, int M, int d,
+                         int nv, int ldt, int rows_per_seg, int nseg, const uint32_t* kmax_u, const float* row_shift,
+                         const float* Tstate, const float* Rstate, const TensorDev& dQ, const TensorDev& dK, const TensorDev& dV,
+                         hipStream_t st);
 bool stats_bf16_supported(const TensorDev& X, const TensorDev& Y, int d);
 int launch_stats_bf16(const TensorDev& X, const TensorDev& Y, int BH, int H, int Lx, int Ly, float scale,
                       int rows_per_chunk, int nchunks, float* part, hipStream_t st);

@@ -93,6 +93,18 @@ def test_general_path_at_edges_of_widths_and_feature_blocks(fs, d, dv, M, L, cau
         assert max(e[0] for e in errs) <= 3e-4 and max(e[1] for e in errs) <= 1.2e-3, (h, errs)
 
 
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d,dv,M,L", [(16, 28, 64, 33), (16, 32, 65, 16), (20, 44, 128, 17), (32, 48, 129, 130), (36, 64, 256, 15),
+                                      (64, 76, 257, 150), (68, 96, 512, 31), (96, 108, 513, 20), (100, 112, 130, 129), (128, 128, 512, 161),
+                                      (16, 4, 16, 1), (4, 16, 250, 48), (18, 32, 64, 40), (32, 30, 64, 40)])
+def test_general_path_at_edges_of_register_tiles(fs, d, dv, M, L, causal):
+    """The kernels on register operands where their widths change (d 16 | 20, 32 | 36, 64 | 68, 96 | 100 and values with the
+    normaliser column of 32 | 48, 80 | 96, 112 | 128 columns), where the causal kernels change their split of the features (M
+    64 | 65, 128 | 129, 256 | 257) and where they give way to the kernels with the state in memory (M 513, d or dv not a multiple of
+    four), at chunks of sixteen tokens that end in every way."""
+    test_general_path_at_edges_of_widths_and_feature_blocks(fs, d, dv, M, L, causal)
+
+
 @pytest.mark.parametrize("what", ["attention", "backward", "operator"])
 @pytest.mark.parametrize("L", [31, 33, 64])
 def test_ragged_tiles_of_long_keys(fs, what, L):
