@@ -75,24 +75,30 @@ struct WalkSide {
 // column = token c; else rows = tokens 4 g + r, column = feature c.  The rows of W~ of the next 16-column group are requested
 // while one is used (a uniform base and 32-bit offsets, found anew for every chunk: addresses kept across chunks take
 // hundreds of registers).
-template <bool FEATURE_ROWS, int Q, int FT>
-__device__ __forceinline__ void project(f32x4 (&acc)[FT], const float* W, int f0, int M, int d, const float* Xs, int g, int c) {
-  f32x4 w[2][FT];
-  uint32_t row[FT];
+// The first group (first_group) is requested by the caller, ahead of whatever comes before the projection.
+__device__ __forceinline__ f32x4 load_wgroup(const float* W, int f, int q, int M, int d, int g) {
+  return *(const f32x4*)((const char*)W + (4u * (uint32_t)(min(f, M - 1) * d) + 4u * (uint32_t)min(16 * q + 4 * g, d - 4)));
+}
+template <int FT>
+__device__ __forceinline__ void first_group(f32x4 (&w)[FT], const float* W, int f0, int M, int d, int g, int c) {
 #pragma unroll
-  for (int ft = 0; ft < FT; ++ft) row[ft] = 4u * (uint32_t)(min(f0 + 16 * ft + c, M - 1) * d);
-  auto load = [&](int q, int ft) { return *(const f32x4*)((const char*)W + (row[ft] + 4u * (uint32_t)min(16 * q + 4 * g, d - 4))); };
+  for (int ft = 0; ft < FT; ++ft) w[ft] = load_wgroup(W, f0 + 16 * ft + c, 0, M, d, g);
+}
+template <bool FEATURE_ROWS, int Q, int FT>
+__device__ __forceinline__ void project(f32x4 (&acc)[FT], const f32x4 (&w0)[FT], const float* W, int f0, int M, int d, const float* Xs,
+                                        int g, int c) {
+  f32x4 w[2][FT];
 #pragma unroll
   for (int ft = 0; ft < FT; ++ft) {
     acc[ft] = f32x4{0.f, 0.f, 0.f, 0.f};
-    w[0][ft] = load(0, ft);
+    w[0][ft] = w0[ft];
   }
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
     __builtin_amdgcn_sched_barrier(0);             // (one group ahead and not all of them: registers)
     if (q + 1 < Q) {
 #pragma unroll
-      for (int ft = 0; ft < FT; ++ft) w[(q + 1) & 1][ft] = load(q + 1, ft);
+      for (int ft = 0; ft < FT; ++ft) w[(q + 1) & 1][ft] = load_wgroup(W, f0 + 16 * ft + c, q + 1, M, d, g);
     }
     const f32x4 x = *(const f32x4*)(Xs + c * LDX<Q> + 16 * q + 4 * g);
 #pragma unroll
@@ -200,11 +206,14 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_gen_walk(WalkArgs 
     const float* buf = smem + (ci & 1) * kBuf;
     const float addf = side_add(a, a.F, a.f_side, bh, row0 + c, row_end, kmax);
     const float adds = MODE ? side_add(a, a.S, a.s_side, bh, row0 + c, row_end, kmax) : 0.f;
+    f32x4 wf[FT];
+    first_group(wf, W1, f0, M, d, g, c);
     __syncthreads();
     // features of both sides: rows = features, column = token
     f32x4 sf[FT], p[FT];
-    project<true, Q, FT>(sf, W1, f0, M, d, buf, g, c);
-    project<true, Q, FT>(p, W2, f0, M, d, buf + TT * ldx, g, c);
+    project<true, Q, FT>(sf, wf, W1, f0, M, d, buf, g, c);
+    first_group(wf, W2, f0, M, d, g, c);
+    project<true, Q, FT>(p, wf, W2, f0, M, d, buf + TT * ldx, g, c);
     __builtin_amdgcn_sched_barrier(0);
     f32x4 br[FT];
 #pragma unroll
@@ -324,7 +333,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_gen_walk(WalkArgs 
 // grid (nseg, B*H), block 64 NW.
 // ---------------------------------------------------------------------------------------------------
 template <int Q, int FT, int NW> constexpr size_t gwalk_lds() {
-  return 4 * ((size_t)2 * (2 * TT * LDX<Q> + 2 * TT * LDV<Q>) + (size_t)NW * TT * (16 * Q + 1) + NW * TT + 16 * FT * NW);
+  return 4 * ((size_t)2 * (2 * TT * LDX<Q> + 2 * TT * LDV<Q>) + (size_t)NW * TT * (16 * Q + 1) + NW * TT + 16 * FT * NW + TT * LDX<Q>);
 }
 
 template <int Q, int FT, int NW, int MODE>
@@ -335,6 +344,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_gen_gwalk(WalkArgs
   float* xch = smem + 2 * kBuf;                    // [wave][token][coordinate]
   float* rsw = xch + NW * xch1;                    // [wave][token]: row sums of dE
   float* bl = rsw + NW * TT;                       // biases, -inf behind the last feature
+  float* cx = bl + 16 * FT * NW;                   // [token][coordinate]: x (C + C^T), where the kernel has a C
   const int seg = blockIdx.x, bh = blockIdx.y, b = bh / a.H, h = bh % a.H;
   const int lane = threadIdx.x & 63;
   int g = lane >> 4, c = lane & 15;
@@ -398,6 +408,8 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_gen_gwalk(WalkArgs
 #pragma unroll
     for (int r = 0; r < 4; ++r) addf[r] = side_add(a, a.F, a.f_side, bh, row0 + 4 * g + r, row_end, kmax);
     const float adds = side_add(a, a.S, a.s_side, bh, row0 + c, row_end, kmax);
+    f32x4 wf[FT];
+    first_group(wf, W1, f0, M, d, g, c);
     __syncthreads();
     // u_i . v_j (rows = first-side tokens 4 g + r, column = second-side token c), masked, and Z u
     f32x4 am = {0.f, 0.f, 0.f, 0.f}, df[FT];
@@ -419,7 +431,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_gen_gwalk(WalkArgs
     // first side's features, rows = tokens, column = feature: into dF and into the state
     __builtin_amdgcn_sched_barrier(0);
     f32x4 ff[FT];
-    project<false, Q, FT>(ff, W1, f0, M, d, buf, g, c);
+    project<false, Q, FT>(ff, wf, W1, f0, M, d, buf, g, c);
 #pragma unroll
     for (int ft = 0; ft < FT; ++ft)
 #pragma unroll
@@ -428,6 +440,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_gen_gwalk(WalkArgs
     for (int r = 0; r < 4; ++r)
 #pragma unroll
       for (int ft = 0; ft < FT; ++ft) df[ft] = mfma4(ff[ft][r], am[r], df[ft]);
+    first_group(wf, W2, f0, M, d, g, c);
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -439,7 +452,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_gen_gwalk(WalkArgs
       }
     // second side's features, rows = features, column = token; dE = F * dF
     f32x4 fs2[FT];
-    project<true, Q, FT>(fs2, W2, f0, M, d, buf + TT * ldx, g, c);
+    project<true, Q, FT>(fs2, wf, W2, f0, M, d, buf + TT * ldx, g, c);
     float rs = 0.f;
 #pragma unroll
     for (int ft = 0; ft < FT; ++ft) {
@@ -455,32 +468,62 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_gen_gwalk(WalkArgs
     if (g == 0) rsw[w * TT + c] = rs;
     // the next chunk's rows travel during the last products
     if (ci + 1 < nchunk) fetch_chunk(ci + 1);
-    // gradient rows of this wave's features: dE W~ (wide rows in two halves: registers)
-    constexpr int DT = Q >= 6 ? Q / 2 : Q;
+    // gradient rows of this wave's features: dE W~ (wide rows in two halves: registers), a tile's rows of W~ one ahead
+    constexpr int DT = Q >= 6 ? Q / 2 : Q, NS = FT * (Q / DT);
+    auto load_w = [&](float (&wv)[4][DT], int st) {
+      const int ft = st % FT, d0 = DT * (st / FT);
 #pragma unroll
-    for (int d0 = 0; d0 < Q; d0 += DT) {
-      f32x4 gr[DT];
+      for (int r = 0; r < 4; ++r) {
+        const uint32_t row = 4u * (uint32_t)(min(f0 + 16 * ft + 4 * g + r, M - 1) * d);
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt) gr[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int dt = 0; dt < DT; ++dt) wv[r][dt] = *(const float*)((const char*)W2 + (row + 4u * (uint32_t)min(16 * (d0 + dt) + c, d - 1)));
+      }
+    };
+    float wv[2][4][DT];
+    load_w(wv[0], 0);
+    f32x4 gr[DT];
 #pragma unroll
-      for (int ft = 0; ft < FT; ++ft) {
-        __builtin_amdgcn_sched_barrier(0);
-        float wv[4][DT];
+    for (int st = 0; st < NS; ++st) {
+      const int ft = st % FT, d0 = DT * (st / FT);
+      __builtin_amdgcn_sched_barrier(0);
+      if (st + 1 < NS) load_w(wv[(st + 1) & 1], st + 1);
+      if (ft == 0) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const uint32_t row = 4u * (uint32_t)(min(f0 + 16 * ft + 4 * g + r, M - 1) * d);
-#pragma unroll
-          for (int dt = 0; dt < DT; ++dt) wv[r][dt] = *(const float*)((const char*)W2 + (row + 4u * (uint32_t)min(16 * (d0 + dt) + c, d - 1)));
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int dt = 0; dt < DT; ++dt) gr[dt] = mfma4(df[ft][r], wv[r][dt], gr[dt]);
+        for (int dt = 0; dt < DT; ++dt) gr[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
+      for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) xch[w * xch1 + (4 * g + r) * ldo + 16 * (d0 + dt) + c] = gr[dt][r];
+        for (int dt = 0; dt < DT; ++dt) gr[dt] = mfma4(df[ft][r], wv[st & 1][r][dt], gr[dt]);
+      if (ft == FT - 1) {
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) xch[w * xch1 + (4 * g + r) * ldo + 16 * (d0 + dt) + c] = gr[dt][r];
+      }
+    }
+    // the row term's part, a tile of sixteen columns per wave.  (A thread's own dot products with rows and columns of C cost
+    // half as much as everything else: 1024 loads per thread and chunk at d = 128.  Causal backward f32 B2 H8 L1000 d128
+    // M256 with a dense C: 1383 -> 851 us.)
+    if (Cmat != nullptr) {
+      for (int ct = w; ct < Q; ct += NW) {
+        const float* xr = buf + TT * ldx + c * ldx + 4 * g;
+        const uint32_t col = (uint32_t)min(16 * ct + c, d - 1);
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+          if (q % 2 == 0) __builtin_amdgcn_sched_barrier(0);
+          const uint32_t e = (uint32_t)min(16 * q + 4 * g, d - 4);
+          f32x4 cm = *(const f32x4*)((const char*)Cmat + 4u * (col * (uint32_t)d + e));
+#pragma unroll
+          for (int s = 0; s < 4; ++s) cm[s] += *(const float*)((const char*)Cmat + 4u * ((e + s) * (uint32_t)d + col));
+          const f32x4 x = *(const f32x4*)(xr + 16 * q);
+#pragma unroll
+          for (int s = 0; s < 4; ++s) acc = mfma4(x[s], cm[s], acc);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) cx[(4 * g + r) * ldx + 16 * ct + c] = acc[r];
+      }
     }
     __builtin_amdgcn_sched_barrier(0);
     if (ci + 1 < nchunk) put_chunk(ci + 1);
@@ -497,21 +540,8 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_gen_gwalk(WalkArgs
           float v = 0.f;
 #pragma unroll
           for (int i = 0; i < NW; ++i) v += xch[i * xch1 + row * ldo + col];
-          float cx = -x[col];
-          if (Cmat != nullptr) {
-            float t0 = 0.f, t1 = 0.f, t2 = 0.f, t3 = 0.f;
-            const float* crow = Cmat + (size_t)col * d;
-            const float* ccol = Cmat + col;
-#pragma unroll 2
-            for (int e = 0; e < d; e += 4) {
-              t0 += (crow[e] + ccol[(size_t)e * d]) * x[e];
-              t1 += (crow[e + 1] + ccol[(size_t)(e + 1) * d]) * x[e + 1];
-              t2 += (crow[e + 2] + ccol[(size_t)(e + 2) * d]) * x[e + 2];
-              t3 += (crow[e + 3] + ccol[(size_t)(e + 3) * d]) * x[e + 3];
-            }
-            cx = (t0 + t1) + (t2 + t3);
-          }
-          store_elem(a.out, ob + col, a.S.scale * (v * kLn2 + rsum * cx));
+          const float rc = Cmat != nullptr ? cx[row * ldx + col] : -x[col];
+          store_elem(a.out, ob + col, a.S.scale * (v * kLn2 + rsum * rc));
         }
       }
     }
