@@ -74,14 +74,15 @@ __device__ __forceinline__ f32x4 row_group(const RawRow<BF, Q>& x, int q, float 
 // ---------------------------------------------------------------------------------------------------
 // Key-side maximum of the exponent per (b, h), max_{j,m} E2[j,m]: one partial maximum per workgroup, part[bh][block], or
 // where there is no room for them an atomic maximum into kmax[bh] (ordered-uint image; atomics of many workgroups on one
-// address queue up in memory, 15 ns each: 38 us of a 188 us call with one per wave); and the row terms of the keys (rk).  A workgroup takes four (wide rows: two) tiles of 16 tokens: every wave finds the row terms of one, then holds all of
-// them as operands and takes every fourth tile of 16 features through them.  grid (tokens, B*H), block 256.
+// address queue up in memory, 15 ns each: 38 us of a 188 us call with one per wave); and the row terms of the keys (rk).  A workgroup takes four (wide rows: two) tiles of 16 tokens, which every wave holds as operands: it takes
+// every fourth group of coordinates through C for the row terms (each tile's terms by one wave, C in single words: causal
+// f32 B8 H8 L300 d128 M200 dense 378 -> 258 us for the call), then every fourth tile of 16 features.  grid (tokens, B*H), block 256.
 // ---------------------------------------------------------------------------------------------------
 template <int Q> constexpr int KMAX_T = Q >= 6 ? 2 : 4;      // token tiles per workgroup
 template <int Q, int XB, int D4>
 __global__ void __launch_bounds__(256, 2) k_gen_kmax(GenSide ks, int Lk, int H, int M, int d, uint32_t* kmax_u, float* part) {
   constexpr int TT = KMAX_T<Q>;
-  __shared__ __align__(16) float rterm[16 * TT];
+  __shared__ __align__(16) float rpart[4][16 * TT];
   __shared__ float wmax[4];
   const int bh = blockIdx.y, b = bh / H, h = bh % H, row0 = blockIdx.x * 16 * TT;
   const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
@@ -98,62 +99,87 @@ __global__ void __launch_bounds__(256, 2) k_gen_kmax(GenSide ks, int Lk, int H, 
   RawRow<XB, Q> raw[TT];
 #pragma unroll
   for (int t = 0; t < TT; ++t) fetch_row<D4>(raw[t], ks.X, xbase + (long long)min(row0 + 16 * t + c, Lk - 1) * ks.X.sl, d, g);
-  RawRow<XB, Q> mine;
-  const int tw = w & (TT - 1), row = row0 + 16 * tw + c;
-  fetch_row<D4>(mine, ks.X, xbase + (long long)min(row, Lk - 1) * ks.X.sl, d, g);
   const int nft = (M + 15) / 16;
   RawRow<0, Q> wn;
   fetch_row<D4>(wn, W, (long long)min(16 * w + c, M - 1) * d, d, g);
   float bn = bias[min(16 * w + c, M - 1)];
-  {
-    float p = 0.f;
-    if (((int)th[2]) & 1) {
-#pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        const f32x4 x = row_group(mine, q, sc[q]);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) p += x[s] * x[s];
-      }
-      p *= ks.alpha - 0.5f;
-    } else {
-      // (C x)[a] for a = 16 t + 4 g + r of token c, times x[a], which the lane holds
-      const float* Cmat = th + ks.c_offset;
-#pragma unroll
-      for (int t = 0; t < Q; ++t) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        const int a = 16 * t + c;
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-          const f32x4 x = row_group(mine, q, sc[q]);
-#pragma unroll
-          for (int s = 0; s < 4; ++s) {
-            const int col = 16 * q + 4 * g + s;
-            const float e = Cmat[(size_t)min(a, d - 1) * d + min(col, d - 1)];
-            acc = mfma4(a < d && col < d ? e : 0.f, x[s], acc);
-          }
-        }
-        const f32x4 xt = row_group(mine, t, sc[t]);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) p += xt[r] * (acc[r] + ks.alpha * xt[r]);
-      }
-    }
-    p += __shfl_xor(p, 16);
-    p += __shfl_xor(p, 32);
-    if (g == 0) {
-      const float v = row < Lk ? kLog2e * p : -INFINITY;
-      rterm[16 * tw + c] = v;      // (two waves for a tile, where there are two tiles, agree)
-      if (row < Lk) ks.rk[(size_t)bh * Lk + row] = v;
-    }
-  }
   f32x4 x[TT][Q];
 #pragma unroll
   for (int t = 0; t < TT; ++t)
 #pragma unroll
     for (int q = 0; q < Q; ++q) x[t][q] = row_group(raw[t], q, sc[q]);
-  __syncthreads();
+  // row terms x C x + alpha |x|^2 of all the tokens, by way of LDS into accumulator order.  Isotropic: a tile per wave.
+  // Dense: every fourth group of sixteen coordinates per wave, (C x)[a] for a = 16 q + 4 g + r of token c times x[a],
+  // which the lane holds
   f32x4 rt[TT];
+  if (((int)th[2]) & 1) {
+    const int tw = w & (TT - 1), row = row0 + 16 * tw + c;
+    float p = 0.f;
 #pragma unroll
-  for (int t = 0; t < TT; ++t) rt[t] = *(const f32x4*)(&rterm[16 * t + 4 * g]);
+    for (int t = 0; t < TT; ++t)
+      if (t == tw)
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) p += x[t][q][r] * x[t][q][r];
+    p *= ks.alpha - 0.5f;
+    p += __shfl_xor(p, 16);
+    p += __shfl_xor(p, 32);
+    if (g == 0) {
+      rpart[0][16 * tw + c] = p;       // (two waves for a tile, where there are two tiles, agree)
+      if (row < Lk) ks.rk[(size_t)bh * Lk + row] = kLog2e * p;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < TT; ++t) rt[t] = *(const f32x4*)(&rpart[0][16 * t + 4 * g]);
+  } else {
+    const TensorDev Cm{th + ks.c_offset, 0, 0, 0, 0};
+    float p[TT];
+#pragma unroll
+    for (int t = 0; t < TT; ++t) p[t] = 0.f;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      if ((q & 3) != w) continue;
+      f32x4 cx[TT];
+#pragma unroll
+      for (int t = 0; t < TT; ++t) cx[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+      RawRow<0, Q> cr;
+      fetch_row<D4>(cr, Cm, (long long)min(16 * q + c, d - 1) * d, d, g);
+#pragma unroll
+      for (int k = 0; k < Q; ++k) {
+        const f32x4 ck = row_group(cr, k, one[k]);
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int t = 0; t < TT; ++t) cx[t] = mfma4(ck[s], x[t][k][s], cx[t]);
+      }
+#pragma unroll
+      for (int t = 0; t < TT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) p[t] += x[t][q][r] * (cx[t][r] + ks.alpha * x[t][q][r]);
+    }
+#pragma unroll
+    for (int t = 0; t < TT; ++t) {
+      p[t] += __shfl_xor(p[t], 16);
+      p[t] += __shfl_xor(p[t], 32);
+      if (g == 0) rpart[w][16 * t + c] = p[t];
+    }
+    __syncthreads();
+    const int tid = threadIdx.x;
+    if (tid < 16 * TT && row0 + tid < Lk)
+      ks.rk[(size_t)bh * Lk + row0 + tid] = kLog2e * ((rpart[0][tid] + rpart[1][tid]) + (rpart[2][tid] + rpart[3][tid]));
+#pragma unroll
+    for (int t = 0; t < TT; ++t)
+      rt[t] = (*(const f32x4*)(&rpart[0][16 * t + 4 * g]) + *(const f32x4*)(&rpart[1][16 * t + 4 * g])) +
+              (*(const f32x4*)(&rpart[2][16 * t + 4 * g]) + *(const f32x4*)(&rpart[3][16 * t + 4 * g]));
+  }
+#pragma unroll
+  for (int t = 0; t < TT; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = row0 + 16 * t + 4 * g + r;
+      rt[t][r] = row < Lk ? kLog2e * rt[t][r] : -INFINITY;
+    }
   float m = -INFINITY;
   for (int ft = w; ft < nft; ft += 4) {
     f32x4 acc[TT];

@@ -7,7 +7,7 @@
 // chunk: one when its rows have arrived, one when the waves' partial output rows are complete; rows of the next
 // chunk travel meanwhile.  What bounds them is the fp32 matrix rate (32 cycles per instruction) and the rows of W~, which come from L2
 // once per chunk, 13 bytes per cycle and CU.  Causal attention f32 B2 H4 L4096 d64 M256: 175 -> 89 us for this kernel, backward
-// pass bf16 B1 H16 L4096 d128 M512: 3300 -> 2830 us for its four.
+// pass bf16 B1 H16 L4096 d128 M512: 3300 -> 2560 us for its four.
 #include <type_traits>
 
 #include "fs_common.h"
