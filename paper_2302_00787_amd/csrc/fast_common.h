@@ -1,10 +1,11 @@
 // Device-side building blocks of the bf16 attention kernels (d = dv = 64, M = 256) for gfx950.
 //
-// Key-side state kernel and non-causal query-side kernel: one workgroup = 4 waves; wave w owns the 64 random
-// features [64w, 64w+64): its slice of the projection matrix W~ (bf16) and of the M x (d+1) state T (fp32 MFMA
-// accumulators) stay in registers for the whole kernel, so the feature matrices P, S are produced, used and
-// discarded in registers.  (The causal kernel splits the same dataflow over producer and consumer waves, see
-// kernels_bf16_causal.hip; operand layouts, exponents and shifts are the ones described here.)
+// Key-side state kernels: a group of 4 waves; wave w owns the 64 random features [64w, 64w+64): its slice of the
+// projection matrix W~ (bf16) and of the M x (d+1) state T (fp32 MFMA accumulators) stay in registers for the whole
+// kernel, so the features S are produced, used and discarded in registers (fast_state.h).  The causal kernel splits the
+// same dataflow over producer and consumer waves (kernels_bf16_causal.hip).  The non-causal query side and the gradients,
+// which need no running state, split the rows instead: a wave has all the features of its rows (fast_rows.h).  Operand
+// layouts, exponents and shifts are the ones described here.
 //
 //   E^T tile   = W~ (A operand) x tokens (B operand)      -> accumulator: lane <-> token, registers <-> feature
 //   S, P       = exp2(E^T)  (bias preloaded in the accumulator, per-token shift added before the exp2)
@@ -30,7 +31,7 @@ namespace fast {
 
 constexpr int D = 64;            // head dimension (= value dimension)
 constexpr int M = 256;           // random features
-constexpr int NW = 4;            // waves per workgroup, 64 features each
+constexpr int NW = 4;            // waves of a group that splits the features, 64 each
 constexpr int NT = NW * 64;
 constexpr int TC = 64;           // tokens per chunk
 constexpr int KS = D / 32;       // MFMA k-steps of a projection

@@ -1,6 +1,7 @@
 // General-shape FAVOR# kernels: fp32 arithmetic on fp32 MFMA tiles (v_mfma_f32_16x16x4_f32), any d <= 128,
 // any M, any sequence length, f32 or bf16 storage.  They serve the fp32 workloads and every shape the
-// bf16 fast path does not cover.  All exponents are kept in the log2 domain: the projection matrices and
+// bf16 fast path does not cover; key maxima and states are in kernels_gen_rows.hip, the causal kernels for d and dv
+// multiples of four and M <= 512 in kernels_gen_walk.hip.  All exponents are kept in the log2 domain: the projection matrices and
 // biases arrive pre-multiplied by log2(e), so a feature is exp2(E2 - shift).
 //
 // Tile shape everywhere: 32 rows (tokens) x 32 features per step, 256 threads = 4 waves.
@@ -17,16 +18,15 @@ constexpr int TR = 32;     // rows per tile
 constexpr int MB = 32;     // features per block
 constexpr int NT = 256;    // threads per workgroup (causal kernels: NTC)
 // The causal kernels have eight waves, two per SIMD: with 164 to 256 registers (d > 32) one workgroup fills a CU, and at
-// d = 128 it needs most of its LDS as well.  Four waves work on the query side while the other four work on the key
+// d = 128 it needs most of its LDS as well (they serve what the walks of kernels_gen_walk.hip do not).  Four waves work on the query side while the other four work on the key
 // side, both projection blocks in LDS (two barriers fewer per block).  Against four waves: causal attention B2 H4 L4096
 // d64 M256 f32 388 -> 320 us, causal backward pass B1 H16 L4096 d128 M512 5.63 -> 4.64 ms.
 constexpr int NTC = 512;
 
 // Every kernel comes in three widths W: rows of at most 32 W columns and values of at most 32 NV (W = 1: 64, 2: 96,
 // 4: 144).  Registers of a tile and accumulators are counted for the width: with those of W = 4 for every d, two or three
-// waves of k_gen_state, k_gen_apply and k_gen_bwd_side fitted a SIMD, now four or five at d <= 32 and three or four at
-// d <= 64.  f32: 2048 sequences of 128, d 8, M 32, attention 152 -> 106 us, causal 302 -> 175, their backward passes 425 ->
-// 258 and 873 -> 638; causal attention B2 H4 L4096 d64 M256 311 -> 278.
+// waves of k_gen_apply and k_gen_bwd_side fitted a SIMD, now four or five at d <= 32 and three or four at
+// d <= 64.  f32, 2048 sequences of 128, d 8, M 32, when this was done: attention 152 -> 106 us, backward pass 425 -> 258.
 template <int W> constexpr int NV = W == 4 ? 5 : W + 1;
 template <int W, int WAVES> constexpr int ACC_V = (4 * NV<W> + WAVES - 1) / WAVES;   // 16 x 16 tiles of 32 rows of values, per wave
 template <int W, int WAVES> constexpr int ACC_D = (4 * W + WAVES - 1) / WAVES;       // of 32 rows of a side
