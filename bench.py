@@ -46,8 +46,8 @@ MFMA_F32_PEAK_TFLOPS = 157.3
 # runs of this script (--only --calibrate-copy --workload <name>), each counter scaled by what it reads for the
 # 256 MiB copy; figures, factors and commands in the file named beside the values.
 MEASURED_TRAFFIC_BYTES = {
-    "c4": (294.1e6, 508e6, "profiles/hbm_traffic_c2_c3_c4_c5.md"),
-    "c3": (111.5e6, 270e6, "profiles/hbm_traffic_c2_c3_c4_c5.md"),
+    "c4": (291.5e6, 469e6, "profiles/hbm_traffic_c2_c3_c4_c5.md"),
+    "c3": (71.9e6, 185e6, "profiles/hbm_traffic_c2_c3_c4_c5.md"),
     "c5": (3.04e9, 3.71e9, "profiles/hbm_traffic_c2_c3_c4_c5.md"),
 }
 TOL = {"f32": 1e-4, "bf16": 2e-2}
