@@ -529,7 +529,7 @@ int attention_impl(const float* theta, int groups, const fs_tensor* Q, const fs_
   // beyond 32-bit offsets) recomputes them like favorsharp_attention
   AttnPlan p;
   plan_contraction(BH, pgroups, Lk, d, M, dv + 1, causal, &p);
-  const size_t lds_need = causal ? gen_lds_causal(d, p.ldt) : std::max(gen_lds_state(d, p.ldt), gen_lds_apply(d, p.ldt));
+  const size_t lds_need = causal ? gen_lds_causal(d, p.ldt) : gen_lds_apply(d, p.ldt);
   if ((int)lds_need > lds_limit) return FS_ERR_UNSUPPORTED;
 
   hipStream_t st = (hipStream_t)stream;
@@ -711,8 +711,8 @@ int attention_backward_impl(const float* theta, int groups, const fs_tensor* Q, 
   BwdPlan p;
   plan_backward(BH, pgroups, Lq, Lk, d, dv, M, causal, &p);
   const int ldt = p.k.ldt;
-  const size_t lds_need = causal ? std::max({gen_lds_state(d, ldt), gen_lds_causal(d, ldt), gen_lds_bwd_causal(d, ldt)})
-                                 : std::max({gen_lds_state(d, ldt), gen_lds_apply(d, ldt), gen_lds_bwd_side(d, ldt)});
+  const size_t lds_need = causal ? std::max(gen_lds_causal(d, ldt), gen_lds_bwd_causal(d, ldt))
+                                 : std::max(gen_lds_apply(d, ldt), gen_lds_bwd_side(d, ldt));
   if ((int)lds_need > device_lds_limit()) return FS_ERR_UNSUPPORTED;
 
   hipStream_t st = (hipStream_t)stream;
@@ -837,7 +837,7 @@ int favorsharp_kernel_matvec(const float* theta, const fs_tensor* X, const fs_te
   if (op_supported(X->dtype, Y->dtype, d, M, n))
     return launch_op_matvec(theta, dev(X), dev(Y), Nx, Ny, d, qk_scale, alpha, Omega, M, C, n, out, (float*)workspace,
                             (hipStream_t)stream);
-  if ((int)std::max(gen_lds_state(d, p.ldt), gen_lds_apply(d, p.ldt)) > device_lds_limit()) return FS_ERR_UNSUPPORTED;
+  if ((int)gen_lds_apply(d, p.ldt) > device_lds_limit()) return FS_ERR_UNSUPPORTED;
 
   hipStream_t st = (hipStream_t)stream;
   char* ws = (char*)workspace;

@@ -65,12 +65,6 @@ __device__ __forceinline__ void put(const Pieces<G, NW>& p, const RowSrc& s, flo
   }
 }
 
-// A side as a wave sees it: its rows of W~ and the rows' tensor.
-struct WalkSide {
-  const float* W;          // [M][d]
-  RowSrc x;
-};
-
 // acc[ft]: exponents (without bias) of 16 FT features against the sixteen rows at Xs.  FEATURE_ROWS: rows = features 4 g + r,
 // column = token c; else rows = tokens 4 g + r, column = feature c.  The rows of W~ of the next 16-column group are requested
 // while one is used (a uniform base and 32-bit offsets, found anew for every chunk: addresses kept across chunks take

@@ -1435,10 +1435,6 @@ __global__ void __launch_bounds__(NTC) k_gen_bwd_causal_k(GenSide qs, GenSide ks
 static size_t lds_floats_basic(int d) { const int ld = ((d + 3) & ~3) + 1; return (size_t)(TR + MB) * ld + MB + 2 * TR + TR; }
 
 size_t gen_lds_features(int d) { return lds_floats_basic(d) * 4; }
-size_t gen_lds_state(int d, int ldt) {
-  const int ld = ((d + 3) & ~3) + 1;
-  return ((size_t)(TR + MB) * ld + (size_t)TR * (ldt + 1) + (size_t)TR * (MB + 1) + MB + TR) * 4;
-}
 size_t gen_lds_apply(int d, int ldt) {
   const int ld = ((d + 3) & ~3) + 1;
   return ((size_t)(TR + MB) * ld + (size_t)MB * (ldt + 1) + (size_t)TR * (MB + 1) + MB + 3 * TR) * 4;

@@ -80,6 +80,20 @@ def test_backward_f32_small_ragged_different_lengths(fs, variant):
     _check_backward(fs, Q, K, V, dY, Om, d ** -0.25, variant, "f32", 3e-4)
 
 
+@pytest.mark.parametrize("variant,L,d,M", [("saderf", 1300, 16, 40), ("aderf", 1100, 20, 130), ("saderf", 200, 68, 257),
+                                           ("aderf", 210, 100, 60), ("saderf", 145, 128, 512)])
+@pytest.mark.parametrize("causal", [False, True])
+def test_backward_general_path_dense_quadratic_forms(fs, variant, L, d, M, causal):
+    """A dense C where it is split over the waves: fewer, as many and more groups of sixteen coordinates than waves (row
+    terms: four waves; gradient walks: four with M <= 64, else eight); 1100 and 1300 tokens are nine and eleven causal
+    segments, whose prefix is formed eight at a time.  The bar of this file for fp32."""
+    rng = np.random.default_rng(73 + d)
+    Q, K = ((0.6 * rng.standard_normal((1, 1, L, d))).astype(np.float32) for _ in range(2))
+    V, dY = (rng.standard_normal((1, 1, L, d)).astype(np.float32) for _ in range(2))
+    Om = rng.standard_normal((1, M, d)).astype(np.float32)
+    _check_backward(fs, Q, K, V, dY, Om, d ** -0.25, variant, "f32", 3e-4, causal=causal)
+
+
 @pytest.mark.parametrize("L,M,d,dv", [(1, 1, 4, 4), (33, 16, 8, 4), (64, 200, 128, 128)])
 def test_backward_degenerate_and_maximum_sizes(fs, L, M, d, dv):
     rng = np.random.default_rng(62)
