@@ -74,9 +74,10 @@ __device__ __forceinline__ f32x4 row_group(const RawRow<BF, Q>& x, int q, float 
 // ---------------------------------------------------------------------------------------------------
 // Key-side maximum of the exponent per (b, h), max_{j,m} E2[j,m]: one partial maximum per workgroup, part[bh][block], or
 // where there is no room for them an atomic maximum into kmax[bh] (ordered-uint image; atomics of many workgroups on one
-// address queue up in memory, 15 ns each: 38 us of a 188 us call with one per wave); and the row terms of the keys (rk).  A workgroup takes four (wide rows: two) tiles of 16 tokens, which every wave holds as operands: it takes
-// every fourth group of coordinates through C for the row terms (each tile's terms by one wave, C in single words: causal
-// f32 B8 H8 L300 d128 M200 dense 378 -> 258 us for the call), then every fourth tile of 16 features.  grid (tokens, B*H), block 256.
+// address queue up in memory, 15 ns each: 38 us of a 188 us call with one per wave); and the row terms of the keys (rk). A
+// workgroup takes four (wide rows: two) tiles of 16 tokens, which every wave holds as operands: it takes every fourth group
+// of coordinates through C for the row terms (each tile's terms by one wave, C in single words: causal f32 B8 H8 L300 d128
+// M200 dense 378 -> 258 us for the call), then every fourth tile of 16 features. grid (tokens, B*H), block 256.
 // ---------------------------------------------------------------------------------------------------
 template <int Q> constexpr int KMAX_T = Q >= 6 ? 2 : 4;      // token tiles per workgroup
 template <int Q, int XB, int D4>
