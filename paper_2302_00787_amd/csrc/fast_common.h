@@ -21,7 +21,10 @@
 // Exponents live in the log2 domain; W~ carries log2(e) and qk_scale.  Shifts: every query row has its own (it
 // cancels in the normalisation, Section 2.2); the key side needs a common one, kept as a running maximum of a
 // per-token bound with the state rescaled whenever it grows.  Both come from the Cauchy-Schwarz bound on the
-// projection (see row_shift), so nothing can overflow; rows whose bound exceeds about 2^250 may flush to zero.
+// projection (see row_shift), so no feature can overflow; rows whose bound exceeds about 2^250 may flush to zero.  A
+// product of a query's and a key's feature is at most 2^(half the sum of their bounds), which only rows along the same
+// longest row of W~ come near (random directions: 0.4 of a bound each, below the shifts): with such rows a sum over n
+// keys overflows once that half exceeds 127 - log2 n.
 #pragma once
 #include "fs_common.h"
 #include "kernels.h"
@@ -54,12 +57,6 @@ __device__ __forceinline__ bf16x8 pack8(f32x4 a, f32x4 b) {
 __device__ __forceinline__ f32x4 exp2v(f32x4 x) {
   return f32x4{fast_exp2(x[0]), fast_exp2(x[1]), fast_exp2(x[2]), fast_exp2(x[3])};
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int s = 1; s < 64; s <<= 1) v = fmaxf(v, __shfl_xor(v, s));
-  return v;
-}
-
 // Data-parallel-primitive moves inside a row of 16 lanes (no LDS round trip).  CTRL: 0xB1 = swap lanes within pairs,
 // 0x4E = swap pairs within quads, 0x141 = mirror within 8 lanes, 0x124 / 0x128 = rotate the row by 4 / 8 lanes.
 template <int CTRL>
@@ -84,6 +81,18 @@ __device__ __forceinline__ float max16(float v) {
   v = fmaxf(v, dpp_f<0x124>(v));
   v = fmaxf(v, dpp_f<0x128>(v));
   return v;
+}
+
+// Maximum over the wave; every lane gets it.
+__device__ __forceinline__ float wave_max(float v) {
+  v = max16(v);
+  v = fmaxf(v, __shfl_xor(v, 16));
+  return fmaxf(v, __shfl_xor(v, 32));
+}
+// Largest of m and the magnitudes of v (a chain of two-operand pairs: one instruction per two numbers).
+__device__ __forceinline__ float absmax4(float m, f32x4 v) {
+  m = fmaxf(fmaxf(m, fabsf(v[0])), fabsf(v[1]));
+  return fmaxf(fmaxf(m, fabsf(v[2])), fabsf(v[3]));
 }
 
 // Largest of 256 floats (16-byte aligned), as a wave-uniform value.

@@ -199,11 +199,26 @@ __device__ __forceinline__ void contract_rows(f32x4 (&y)[NVT][NTT], const SmemOp
   }
 }
 
-// The queries' per-row shifts: zero for all rows of the wave (and `false` returned) when no row's Cauchy-Schwarz bound
-// exceeds 2^80 (a factor per row cancels in the normalisation, and an unshifted feature of such a row is at most 2^80
-// where a shifted one may reach 2^120), else -row_shift of the lane's row.
+// The largest Cauchy-Schwarz bound at which a query row may go without its shift (a factor per row cancels in the
+// normalisation), given the largest magnitude `tmax` in the state that its features meet: a sum over the 256 features
+// is at most 2^(bound + 8) tmax, kept under 2^125 here, so that no row which is finite with its shift overflows without.
+// 2^80 at most, as far as a feature itself is concerned.  (The state of ordinary data reaches 2^20: every row up to
+// 2^80.  All rows shifted instead: B8 H8 L4096 59.6 -> 62.4 us, 64 x 12 x 197 59.5 -> 60.3.)
+__device__ __forceinline__ float noshift_bound(float tmax) { return fminf(80.f, 117.f - __builtin_amdgcn_logf(tmax)); }
+
+// The largest magnitude in a state that k_fast_total left in memory: one per wave of that kernel, in the unused half of
+// its piece.
+__device__ __forceinline__ float state_max(const float* T) {
+  constexpr int NPART = (M / 32) * NVT;
+  const int i = min((int)(threadIdx.x & 63), NPART - 1);
+  return wave_max(T[(size_t)((2 * (i / NVT) + 1) * NVT + i % NVT) * 256]);
+}
+static_assert((M / 32) * NVT <= 64, "one per lane");
+
+// The queries' per-row shifts: zero for all rows of the wave (and `false` returned) when no row's bound exceeds
+// `noshift`, else -row_shift of the lane's row.
 template <int NTT>
-__device__ __forceinline__ bool query_shifts(float (&add)[NTT], const bf16x8 (&x)[NTT][KS], float wmax, int nv, int lane) {
+__device__ __forceinline__ bool query_shifts(float (&add)[NTT], const bf16x8 (&x)[NTT][KS], float wmax, float noshift, int nv, int lane) {
   const int g = lane >> 4, c = lane & 15;
   float n2[NTT];
   bool large = false;
@@ -211,7 +226,7 @@ __device__ __forceinline__ bool query_shifts(float (&add)[NTT], const bf16x8 (&x
   for (int t = 0; t < NTT; ++t) {
     n2[t] = tile_row_norms(x[t][0], x[t][1], lane);
     add[t] = 0.f;
-    large |= g == (c >> 2) && 16 * t + c < nv && !(wmax * __builtin_amdgcn_sqrtf(n2[t]) <= 80.f);
+    large |= g == (c >> 2) && 16 * t + c < nv && !(wmax * __builtin_amdgcn_sqrtf(n2[t]) <= noshift);
   }
   if (__ballot(large) == 0) return false;
 #pragma unroll
@@ -220,11 +235,12 @@ __device__ __forceinline__ bool query_shifts(float (&add)[NTT], const bf16x8 (&x
 }
 
 // Rows [row_beg, row_end) of the queries of one (b,h), taken by NWV waves in turn: Y = (P T) normalised by its last column.
+// Rows whose bounds are all at most `noshift` go without their shifts.
 // `buf`: the wave's LDS buffer of 16 NTT rows when the rows of the next step travel during this one's work (PREF; the
 // caller has issued dma_rows for the first step), else unused.  Returns the number of rows this wave finished with a
 // zero normaliser.
 template <int NTT, int NWV, bool PREF>
-__device__ __forceinline__ int apply_rows(const FastArgs& a, const SmemOps& sm, uint16_t* buf, float wmax, int bh, int row_beg, int row_end) {
+__device__ __forceinline__ int apply_rows(const FastArgs& a, const SmemOps& sm, uint16_t* buf, float wmax, float noshift, int bh, int row_beg, int row_end) {
   const int b = bh / a.H, h = bh % a.H;
   const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -247,7 +263,7 @@ __device__ __forceinline__ int apply_rows(const FastArgs& a, const SmemOps& sm, 
     const int nv = row_end - row0;
     f32x4 y[NVT][NTT];
     float add[NTT];
-    if (query_shifts(add, x, wmax, nv, lane)) contract_rows<NTT, true>(y, sm, x, add, lane);
+    if (query_shifts(add, x, wmax, noshift, nv, lane)) contract_rows<NTT, true>(y, sm, x, add, lane);
     else contract_rows<NTT, false>(y, sm, x, add, lane);
 #pragma unroll
     for (int t = 0; t < NTT; ++t) {

@@ -309,7 +309,8 @@ __global__ void k_fast_reduce(float* Tpart, const float* cpart, float* cstar, in
 // The sum of the slots of a (b,h) on their largest shift as the operand image that the non-causal query kernel holds in
 // LDS: a thread takes the eight numbers of lane l for the tiles (2 fb, vt) and (2 fb + 1, vt) (accumulator images of
 // 16 features x 16 columns) and writes them as bf16 in the place of slot 0's first four, which nobody else reads.  The
-// state a query workgroup fetches is 40 kB that way instead of 80.  grid (ceil(M*DVP/2048), B*H), block 256.
+// state a query workgroup fetches is 40 kB that way instead of 80.  The place of lane 0's last four, which nobody else reads
+// either, gets the largest magnitude of the wave's part of the state (state_max).  grid (M*DVP/2048, B*H), block 256.
 __global__ void __launch_bounds__(256) k_fast_total(float* Tpart, const float* cpart, float* cstar, int nslot, int nvalid, unsigned* flushed) {
   const int bh = blockIdx.y;
   if (flushed != nullptr && (blockIdx.x | blockIdx.y | threadIdx.x) == 0) *flushed = 0u;
@@ -319,7 +320,7 @@ __global__ void __launch_bounds__(256) k_fast_total(float* Tpart, const float* c
   float cs = -INFINITY;
   for (int s = 0; s < nvalid; ++s) cs = fmaxf(cs, cp[s]);
   if (piece == 0 && cstar != nullptr) cstar[bh] = cs;
-  if (piece >= (M / 32) * NVT * 64) return;
+  static_assert((M / 32) * NVT * 64 % 256 == 0, "whole blocks");
   float* p = Tpart + (size_t)bh * nslot * per + (size_t)(2 * fb * NVT + vt) * 256 + 4 * l;
   f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
   constexpr int NB = 8;
@@ -340,6 +341,8 @@ __global__ void __launch_bounds__(256) k_fast_total(float* Tpart, const float* c
       }
   }
   *(bf16x8*)p = pack8(lo, hi);
+  const float m = wave_max(absmax4(absmax4(0.f, lo), hi));
+  if (l == 0) p[NVT * 256] = m;
 }
 
 // The same reduction for few sequences with many slots (one sequence of 262144 rows has 512 of them, and twenty
@@ -445,9 +448,10 @@ __global__ void __launch_bounds__(NTA) k_fast_apply(FastArgs a, int Lq, int rows
     rows::dma_rows<NTT>(buf, (const uint16_t*)a.Q.ptr + (bh / a.H) * a.Q.sb + (bh % a.H) * a.Q.sh + (long long)row0 * a.Q.sl, a.Q.sl,
                         row_end - row0, lane);
   rows::load_w_image<NTA>(sm, a.Wbf + ((size_t)pg * 2) * M * D, a.bias + ((size_t)pg * 2) * M, amax);
+  const float noshift = rows::noshift_bound(rows::state_max(a.Tpart + (size_t)bh * a.nslot * M * DVP));
   rows::dma_wait<0>();
   __syncthreads();
-  const int nzero = rows::apply_rows<NTT, NTA / 64, true>(a, sm, buf, wmax, bh, row_beg, row_end);
+  const int nzero = rows::apply_rows<NTT, NTA / 64, true>(a, sm, buf, wmax, noshift, bh, row_beg, row_end);
   report_zero_rows(a.flushed, nzero, threadIdx.x & 63);
 }
 
@@ -457,9 +461,12 @@ __global__ void __launch_bounds__(NTA) k_fast_apply(FastArgs a, int Lq, int rows
 // again, outweighs the rows themselves: a sequence of 128 tokens is 64 kB of Q, K, V, Y).  The shift of the state
 // cancels in the normalised rows.  grid (B*H), block 256, two workgroups per CU.
 // ---------------------------------------------------------------------------------------------------
-union SmemWhole {
-  SmemState s;
-  rows::SmemOps q;
+struct SmemWhole {
+  union {
+    SmemState s;
+    rows::SmemOps q;
+  };
+  __attribute__((aligned(16))) float tmax[NT / 16];   // per 16 lanes: largest magnitude in their part of the state
 };
 
 template <int NTT>
@@ -467,18 +474,30 @@ __global__ void __launch_bounds__(NT, 2) k_fast_whole(FastArgs a, int Lq) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int bh = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int pg = group_of(a.pgroups, bh / a.H, bh % a.H, a.H);
-  rows::SmemOps& sm = *reinterpret_cast<rows::SmemOps*>(smem_raw);
+  SmemWhole& whole = *reinterpret_cast<SmemWhole*>(smem_raw);
+  rows::SmemOps& sm = whole.q;
   {
     f32x4 T[4][NVT];
     float dk;
-    state_rows(a, *reinterpret_cast<SmemState*>(smem_raw), bh, 0, a.L, chunks_of(a.L), T, dk);
+    state_rows(a, whole.s, bh, 0, a.L, chunks_of(a.L), T, dk);
     rows::put_t_image(sm, T, w, lane);
+    float m[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+      for (int vt = 0; vt < NVT; ++vt) m[mt] = absmax4(m[mt], T[mt][vt]);
+    const float m16 = max16(fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3])));
+    if ((lane & 15) == 0) whole.tmax[threadIdx.x >> 4] = m16;
   }
   const float wmax = max256(a.wnorm + ((size_t)pg * 2) * M), amax = max256(a.bias + ((size_t)pg * 2) * M);
   rows::load_w_image<NT>(sm, a.Wbf + ((size_t)pg * 2) * M * D, a.bias + ((size_t)pg * 2) * M, amax);
   rows::dma_wait<0>();
   __syncthreads();
-  const int nzero = rows::apply_rows<NTT, NT / 64, false>(a, sm, nullptr, wmax, bh, 0, Lq);
+  float tmax = 0.f;
+#pragma unroll
+  for (int i = 0; i < NT / 16; i += 4) tmax = absmax4(tmax, *(const f32x4*)(&whole.tmax[i]));
+  const float noshift = rows::noshift_bound(tmax);
+  const int nzero = rows::apply_rows<NTT, NT / 64, false>(a, sm, nullptr, wmax, noshift, bh, 0, Lq);
   report_zero_rows(a.flushed, nzero, lane);
 }
 

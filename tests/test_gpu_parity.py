@@ -755,6 +755,56 @@ def test_bf16_path_non_causal_row_tiles(fs, H, Lq, Lk):
         assert fro <= TOL["bf16"] and row <= 4 * TOL["bf16"], (h, fro, row)
 
 
+def _aligned_rows_reference(q, k, v, W1, W2, bias, s, causal=False):
+    """float64 attention on the kernels' bf16 projection matrices (log2 domain), GERF parameters."""
+    import torch
+    log2e = float(np.log2(np.e))
+    E1, E2 = q @ W1.T + log2e * bias, k @ W2.T + log2e * (bias - 0.5 * s * s * (k * k).sum(1, keepdim=True))
+    P, S = torch.exp2(E1 - E1.max(1, keepdim=True).values), torch.exp2(E2 - E2.max())
+    A = P @ S.T
+    if causal:
+        A = torch.tril(A)
+    return (A @ v) / A.sum(1, keepdim=True)
+
+
+def _aligned_rows(H, Lq, Lk, qbound, kbound):
+    """Queries and keys along the longest row of W~, bounds up to the given ones (every second row, the others ordinary)."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(H + Lq + Lk + int(kbound))
+    Q, K, V = (torch.randn((1, H, L, 64), generator=gen, device="cuda") for L in (Lq, Lk, Lk))
+    Om = torch.randn((1, 256, 64), generator=gen, device="cuda")
+    th = orc.fit_gerf(0.35 * np.random.default_rng(1).standard_normal((64, 64)), 0.35 * np.random.default_rng(2).standard_normal((64, 64)))
+    vec = util.theta_vec_from_oracle(th)
+    th, s = util.oracle_theta_from_vec(vec, 64), 64 ** -0.25
+    log2e = float(np.log2(np.e))
+    W1, W2 = ((log2e * s * (Om[0] @ torch.from_numpy(Bm).float().cuda())).bfloat16().double() for Bm in (th.B1, th.B2))
+    bias = (Om[0].double() ** 2) @ torch.from_numpy(th.A).cuda()
+    for x, W, bound in ((Q, W1, qbound), (K, W2, kbound)):
+        n = W.norm(dim=1)
+        top = (W[n.argmax()] / n.max() ** 2).float()
+        far = x[:, :, ::2]
+        far[:] = bound * top * (0.97 + 0.02 * torch.rand(far.shape[:3] + (1,), generator=gen, device="cuda"))
+    Q, K, V = (x.bfloat16() for x in (Q, K, V))
+    return Q, K, V, Om, torch.from_numpy(vec[None]).cuda(), s, W1, W2, bias
+
+
+@pytest.mark.parametrize("H,Lq,Lk", [(1, 40, 300), (33, 1999, 130), (130, 1037, 193), (385, 129, 70), (388, 64, 100)])
+@pytest.mark.parametrize("qbound,kbound", [(79.0, 100.0), (79.0, 140.0), (60.0, 150.0), (39.0, 170.0), (110.0, 100.0), (20.0, 20.0)])
+def test_bf16_path_non_causal_queries_and_keys_along_one_feature(fs, H, Lq, Lk, qbound, kbound):
+    """A product of a query feature and a key feature is at most 2^(bounds), which only aligned rows reach: with the query
+    shifted by half of its bound fp32 holds every product here (39.5 + 70 and 12 more for the sum over the keys), without
+    a shift it does not hold the larger ones.  Both kernels (rows against a finished state; a sequence per workgroup),
+    each row-tile width."""
+    import torch
+    Q, K, V, Om, theta, s, W1, W2, bias = _aligned_rows(H, Lq, Lk, qbound, kbound)
+    Y = fs.attention(theta, Q, K, V, s, Om)
+    assert torch.isfinite(Y.float()).all()
+    for h in sorted({0, H // 2, H - 1}):
+        ref = _aligned_rows_reference(Q[0, h].double(), K[0, h].double(), V[0, h].double(), W1, W2, bias, s)
+        fro, row = util.attention_errors(Y[0, h].double().cpu().numpy(), ref.cpu().numpy(), V[0, h].double().cpu().numpy())
+        assert fro <= TOL["bf16"] and row <= 4 * TOL["bf16"], (h, fro, row)
+
+
 @pytest.mark.parametrize("variant,L", [("sderf", 128), ("aderf", 100), ("gerf", 333)])
 def test_bf16_path_causal_many_short_sequences(fs, variant, L):
     """Causal calls with 256 sequences or more are one segment per sequence: no state pass and no reduction run, the
