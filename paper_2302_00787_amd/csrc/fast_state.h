@@ -58,17 +58,17 @@ __device__ __forceinline__ void state_rows(const FastArgs& a, SmemState& sm, int
   const int nrows = row_end - row_beg;
 
   // staging: thread -> rows tid/8 and tid/8 + 32 of a chunk, bytes 16 (tid%8); rows past the end read as zero
-  // (a fresh descriptor per chunk: uniform base = the chunk's first row, 32-bit offsets inside the chunk)
+  // (a fresh descriptor per chunk: uniform base = the chunk's first row, 32-bit offsets and extent inside the chunk)
   const int srow = tid >> 3, spc = tid & 7;
   u32x4 kr[2], vr[QUERIES ? 3 : 2];
   auto load_k = [&](int r0) {
-    const __amdgpu_buffer_rsrc_t rk_ = pc::chunk_rsrc(Kb + (long long)r0 * X.sl, 2 * (int)X.sl, nrows - r0, 2 * D);
+    const __amdgpu_buffer_rsrc_t rk_ = pc::chunk_rsrc(Kb + (long long)r0 * X.sl, 2 * (int)X.sl, min(nrows - r0, TC), 2 * D);
 #pragma unroll
     for (int i = 0; i < 2; ++i) kr[i] = __builtin_amdgcn_raw_buffer_load_b128(rk_, 2 * ((srow + 32 * i) * (int)X.sl + spc * 8), 0, 0);
   };
   auto load_v = [&](int r0) {
     if (BOUND_ONLY) return;
-    const __amdgpu_buffer_rsrc_t rv_ = pc::chunk_rsrc(Vb + (long long)r0 * a.V.sl, 2 * (int)a.V.sl, nrows - r0, QUERIES ? 2 * DVP : 2 * D);
+    const __amdgpu_buffer_rsrc_t rv_ = pc::chunk_rsrc(Vb + (long long)r0 * a.V.sl, 2 * (int)a.V.sl, min(nrows - r0, TC), QUERIES ? 2 * DVP : 2 * D);
     if (QUERIES) {             // G1 rows: 160 bytes one after the other, a chunk is 640 pieces in a row
 #pragma unroll
       for (int i = 0; i < (QUERIES ? 3 : 2); ++i) vr[i] = __builtin_amdgcn_raw_buffer_load_b128(rv_, 16 * (tid + NT * i), 0, 0);

@@ -473,8 +473,7 @@ int attention_impl(const float* theta, int groups, const fs_tensor* Q, const fs_
     return FS_ERR_WORKSPACE_TOO_SMALL;
   if (Lq == 0) return launch_fill_u32((uint32_t*)workspace, 0u, 1, (hipStream_t)stream);     // no rows: the counter reads 0
   const int lds_limit = device_lds_limit();
-  // the bf16 kernels address the rows of a chunk with 32-bit offsets
-  const long long max_sl = 1ll << 23;
+  const long long max_sl = kMaxRowStride;
   const bool small_strides = Q->stride_l < max_sl && K->stride_l < max_sl && V->stride_l < max_sl && Y->stride_l < max_sl;
   if (fast_supported(Q->dtype, d, dv, M) && small_strides && (int)fast_lds_bytes() <= lds_limit) {
     FastPlan fp;
@@ -680,7 +679,7 @@ int attention_backward_impl(const float* theta, int groups, const fs_tensor* Q, 
   if (workspace_bytes < favorsharp_attention_backward_workspace_bytes(B, H, Lq, Lk, d, dv, M, causal, groups, omega_groups))
     return FS_ERR_WORKSPACE_TOO_SMALL;
   // bf16 kernels: d = dv = 64, M = 256, bf16 inputs (dY and the gradients: bf16 or fp32), rows addressable with 32 bits
-  const long long max_sl = 1ll << 23;
+  const long long max_sl = kMaxRowStride;
   if (fast_supported(Q->dtype, d, dv, M) && Q->stride_l < max_sl && K->stride_l < max_sl &&
       V->stride_l < max_sl && dY->stride_l < max_sl && dQ->stride_l < max_sl && dK->stride_l < max_sl &&
       dV->stride_l < max_sl &&

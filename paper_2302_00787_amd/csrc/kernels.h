@@ -11,6 +11,11 @@ namespace fs {
 
 constexpr int FS_THETA_HEADER_ = 8;
 
+// Row strides (in numbers) below which the bf16 kernels take a call: they address the rows of a chunk, 64 at most, by 32-bit
+// offsets into a buffer descriptor whose extent is a 32-bit number of bytes.
+constexpr long long kMaxRowStride = 1ll << 23;
+static_assert(63 * 4 * kMaxRowStride + 4 * 128 < 1ll << 31, "a chunk of fp32 rows");
+
 // One side (queries or keys) of a feature map as the general-shape kernels see it.
 struct GenSide {
   TensorDev X;          // rows to map

@@ -805,6 +805,34 @@ def test_bf16_path_non_causal_queries_and_keys_along_one_feature(fs, H, Lq, Lk, 
         assert fro <= TOL["bf16"] and row <= 4 * TOL["bf16"], (h, fro, row)
 
 
+@pytest.mark.parametrize("backward,Lq,Lk,far", [(False, 300, 300, "KV"), (False, 1800, 300, "KV"),      # whole sequences, state kernel
+                                                (True, 300, 300, "KV"), (True, 300, 900, "Q")])         # whole, sums of P^T G1
+def test_bf16_path_rows_more_than_4_gib_apart(fs, backward, Lq, Lk, far):
+    """One workgroup's rows span more than 2^32 bytes at the largest row stride that the bf16 kernels take (300 rows of
+    16 MiB): the results are those of the same rows side by side, to the last bit."""
+    import torch
+    H, sl = 256, (1 << 23) - 8
+    gen = torch.Generator(device="cuda").manual_seed(Lq + Lk)
+    X = {n: torch.randn((1, H, L, 64), generator=gen, device="cuda").bfloat16() for n, L in (("Q", Lq), ("K", Lk), ("V", Lk))}
+    dY = torch.randn((1, H, Lq, 64), generator=gen, device="cuda").bfloat16()
+    Om = torch.randn((1, 256, 64), generator=gen, device="cuda")
+    theta = fs.fit_params("sderf", X["Q"], X["K"], 64 ** -0.25)
+    base = torch.zeros(300 * sl, dtype=torch.bfloat16, device="cuda")
+    Z = dict(X)
+    for i, n in enumerate(far):
+        Z[n] = base.as_strided((1, H, 300, 64), (0, 64, sl, 1), i * H * 64)
+        Z[n].copy_(X[n])
+    outs = []
+    for t in (X, Z):
+        if backward:
+            outs.append(fs.attention_backward(theta, t["Q"], t["K"], t["V"], dY, 64 ** -0.25, Om))
+        else:
+            outs.append([fs.attention(theta, t["Q"], t["K"], t["V"], 64 ** -0.25, Om)])
+    for a, b in zip(*outs):
+        assert torch.isfinite(a.float()).all() and float(a.float().abs().max()) > 0
+        assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("variant,L", [("sderf", 128), ("aderf", 100), ("gerf", 333)])
 def test_bf16_path_causal_many_short_sequences(fs, variant, L):
     """Causal calls with 256 sequences or more are one segment per sequence: no state pass and no reduction run, the
