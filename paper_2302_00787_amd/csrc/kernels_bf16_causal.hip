@@ -34,10 +34,11 @@
 // the plain accesses (16 consecutive lanes = one g) and the transposing ones (one row of 16 lanes reads features
 // 4g' .. 4g'+3 of token quads 0..3) both touch 16 different 8-byte bank pairs.
 //
-// Shifts.  Keys: running maximum of a per-token bound, the state rebased when it grows (fast_common.h).  Queries:
-// when every row of the chunk has a Cauchy-Schwarz bound below 2^80 no shift is needed at all (the common case: the
-// per-row factor cancels in the normalisation) and the per-element addition is skipped; otherwise every row gets
-// its own shift as in the other kernels.
+// Shifts.  Keys: running maximum of a per-token bound, the state rebased when it grows (fast_common.h).  Queries: every
+// row its own.  (Chunks whose rows all have small bounds could do without, since the factor cancels in the normalisation,
+// but how small they have to be depends on the state, which the producers do not know: rows with bounds of 79 and keys
+// with bounds of 140 along the same feature overflow.  The additions cost 0.6 %, the maxima that the choice needs cost more:
+// B4 H8 L16384 170.7 us with the choice, 168.5 without.)
 //
 // The chunk is four steps of two token tiles (key tiles 0-1, 2-3, query tiles 0-1, 2-3), one workgroup barrier after
 // each; the producer works one step ahead of the consumer.  Both roles execute exactly the same number of barriers
@@ -48,9 +49,9 @@
 // reader of chunk c-1: the producers' tile reads end in interval 4c-1, the consumers' value reads in 4c) and are
 // first read in interval 4c+3 (row norms, and the prefetch of the next chunk's first key tiles; the key and query
 // rows were stored in steps 0 and 1); each part's registers are refilled at once with the same part of chunk c+2.
-// The per-token constants of chunk c+1 (row terms, query shifts) and the chunk's two maxima (largest key bound,
-// largest query shift: LDS float-maximum atomics from the lanes that hold a row norm) are written in interval 4c+3
-// and first read in interval 4c+4; the maxima of that parity were last read in interval 4c+1 and are reset in 4c+2.
+// The per-token constants of chunk c+1 (row terms, query shifts) and the chunk's largest key bound (LDS float-maximum
+// atomics from the lanes that hold a row norm) are written in interval 4c+3 and first read in interval 4c+4; the
+// maximum of that parity was last read in interval 4c+1 and is reset in 4c+2.
 #include <hip/hip_ext.h>
 
 #include "fast_pc.h"
@@ -66,7 +67,7 @@ struct SmemPC {
   uint16_t q[2][TC][LDR];          // query rows
   __attribute__((aligned(16))) uint16_t v[2][TC][LDV];   // value rows: columns 0..63, column 64 = 1, columns 65.. = 0
   __attribute__((aligned(16))) float kadd[2][TC];   // per key token t, at index t: row term log2e y^T C2 y (-inf past the end)
-  float kmax[2], qmax[2];                           // per chunk parity: largest key bound (row_shift + row term), largest query row_shift
+  float kmax[2];                                    // per chunk parity: largest key bound (row_shift + row term)
   __attribute__((aligned(16))) float qadd[2][TC];   // per query token t, at index 4 (t%16) + t/16: - row_shift
   // feature tiles of one step, two slots of 16 kB.  Key steps: [tile of the pair][producer][feature tile] blocks of
   // 64 units of 8 bytes (unit (g, c) at 8 sigma(g, c): feature c, tokens 4g .. 4g+3).  Query steps: [tile of the
@@ -162,23 +163,8 @@ __device__ __forceinline__ void row_constants(SmemPC& sm, int buf, const FastArg
     const float rt = isoC ? (valid ? -0.5f * kLog2e * a.scale * a.scale * nk2 : -INFINITY) : sm.kadd[buf][t];
     if (isoC) sm.kadd[buf][t] = rt;
     if (valid) lds_fmax(&sm.kmax[buf], row_shift(nk2, wmax2) + rt);
-    const float qs = row_shift(nq2, wmax1);
-    sm.qadd[buf][4 * c + j] = -qs;
-    lds_fmax(&sm.qmax[buf], qs);
+    sm.qadd[buf][4 * c + j] = -row_shift(nq2, wmax1);
   }
-}
-
-// Query feature tile without a row shift (every bound of the chunk is small: the per-row factor cancels later).
-__device__ __forceinline__ void feature_tile64_noshift(const W64& ws, const B64& qb, const XOp& x, bf16x8 img[2]) {
-  f32x4 acc[4];
-#pragma unroll
-  for (int mt = 0; mt < 4; ++mt) {
-    acc[mt] = mfma(ws.w[mt][0], x.b[0], qb.b[mt]);
-#pragma unroll
-    for (int ks = 1; ks < KS; ++ks) acc[mt] = mfma(ws.w[mt][ks], x.b[ks], acc[mt]);
-  }
-#pragma unroll
-  for (int blk = 0; blk < 2; ++blk) img[blk] = pack8(exp2v(acc[2 * blk]), exp2v(acc[2 * blk + 1]));
 }
 
 // Key features of one token tile and the pair's 64 features, feature-major, straight to LDS: for each feature tile
@@ -233,7 +219,7 @@ __device__ __forceinline__ void producer(const FastArgs& a, SmemPC& sm, const Se
   // output rows of the previous chunk (finished by the producers one chunk later)
   const long long ystep = (long long)TC * a.Y.sl * (a.Y.dtype == 1 ? 2 : 4);
   const char* yprev = (const char*)a.Y.ptr + (cx.ybase + (long long)cx.row_beg * a.Y.sl) * (a.Y.dtype == 1 ? 2 : 4) - ystep;
-  if (tid < 2) { sm.kmax[tid] = -INFINITY; sm.qmax[tid] = -INFINITY; }
+  if (tid < 2) sm.kmax[tid] = -INFINITY;
   FS_STEP_BARRIER();               // barrier 0: the first chunk's rows are in LDS
   row_constants(sm, 0, a, cx.isoC, cx.row_beg, cx.row_end, wmax1, wmax2, j, lane);
   FS_STEP_BARRIER();               // barrier 1: and their per-token constants
@@ -252,8 +238,6 @@ __device__ __forceinline__ void producer(const FastArgs& a, SmemPC& sm, const Se
     // running key shift (every wave reads the same number)
     dk = fmaxf(dk, sm.kmax[buf]);
     const f32x4 qadd4 = *(const f32x4*)(&sm.qadd[buf][4 * c_here]);
-    // no query shift at all when every row's shift is below 40 (Cauchy-Schwarz bound below 2^80)
-    const bool noshift = __builtin_amdgcn_readfirstlane((int)(sm.qmax[buf] < 40.f)) != 0;
     cp.q += qstep; cp.k += kstep; cp.v += vstep; cp.rk += TC;     // now the chunk after the next
     // running pointers stay loop-carried scalars (the compiler would otherwise rebuild each of them from the chunk
     // counter with a 64-bit multiplication per chunk)
@@ -283,13 +267,8 @@ __device__ __forceinline__ void producer(const FastArgs& a, SmemPC& sm, const Se
         }
       } else {
         bf16x8 img[2][2];
-        if (noshift) {
 #pragma unroll
-          for (int u = 0; u < 2; ++u) feature_tile64_noshift(wq, qb, xo[S & 1][u], img[u]);
-        } else {
-#pragma unroll
-          for (int u = 0; u < 2; ++u) feature_tile64<true>(wq, &qb, xo[S & 1][u], qadd4[2 * (S - 2) + u], img[u]);
-        }
+        for (int u = 0; u < 2; ++u) feature_tile64<true>(wq, &qb, xo[S & 1][u], qadd4[2 * (S - 2) + u], img[u]);
 #pragma unroll
         for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -302,8 +281,8 @@ __device__ __forceinline__ void producer(const FastArgs& a, SmemPC& sm, const Se
       // the previous chunk leaves: its partial tiles are summed in step 2 (before the consumers start to overwrite
       // them in interval 4c+3) and stored in step 3 (nothing is stored on the first pass: there is no previous chunk)
       if (S == 2) {
-        // the other parity's maxima were last read in interval 4c+1 and are gathered again in the next step
-        if (tid_here < 2) { if (tid_here == 0) sm.kmax[buf ^ 1] = -INFINITY; else sm.qmax[buf ^ 1] = -INFINITY; }
+        // the other parity's maximum was last read in interval 4c+1 and is gathered again in the next step
+        if (tid_here == 0) sm.kmax[buf ^ 1] = -INFINITY;
         finish_tiles(fsum, sm, j, 0, lane_here);
         finish_tiles(fsum, sm, j, 2, lane_here);
         unsigned zt;

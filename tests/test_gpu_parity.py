@@ -805,6 +805,20 @@ def test_bf16_path_non_causal_queries_and_keys_along_one_feature(fs, H, Lq, Lk, 
         assert fro <= TOL["bf16"] and row <= 4 * TOL["bf16"], (h, fro, row)
 
 
+@pytest.mark.parametrize("H,L", [(1, 300), (3, 1000), (257, 150)])
+@pytest.mark.parametrize("qbound,kbound", [(79.0, 100.0), (79.0, 140.0), (60.0, 150.0), (39.0, 170.0), (110.0, 100.0), (20.0, 20.0)])
+def test_bf16_path_causal_queries_and_keys_along_one_feature(fs, H, L, qbound, kbound):
+    """The same for the causal kernel, with several segments and with one."""
+    import torch
+    Q, K, V, Om, theta, s, W1, W2, bias = _aligned_rows(H, L, L, qbound, kbound)
+    Y = fs.attention(theta, Q, K, V, s, Om, causal=True)
+    assert torch.isfinite(Y.float()).all()
+    for h in sorted({0, H // 2, H - 1}):
+        ref = _aligned_rows_reference(Q[0, h].double(), K[0, h].double(), V[0, h].double(), W1, W2, bias, s, causal=True)
+        fro, row = util.attention_errors(Y[0, h].double().cpu().numpy(), ref.cpu().numpy(), V[0, h].double().cpu().numpy())
+        assert fro <= TOL["bf16"] and row <= 4 * TOL["bf16"], (h, fro, row)
+
+
 @pytest.mark.parametrize("backward,Lq,Lk,far", [(False, 300, 300, "KV"), (False, 1800, 300, "KV"),      # whole sequences, state kernel
                                                 (True, 300, 300, "KV"), (True, 300, 900, "Q")])         # whole, sums of P^T G1
 def test_bf16_path_rows_more_than_4_gib_apart(fs, backward, Lq, Lk, far):
