@@ -304,9 +304,11 @@ __global__ void __launch_bounds__(256, 2) k_gen_state(GenSide ks, TensorDev V, i
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const bool ok = row0 + 4 * g + r < row_end;
-      rt[r] = ok ? rsign * rt[r] - shift : -INFINITY;
+      rt[r] = ok ? rsign * rt[r] : -INFINITY;
+      // (in this order: row term less shift first, as far as 64-bit sums tell, leaves 1.04 times the error in non-causal
+      // attention over the range of d and M, up to 1.3 times at d = 8)
 #pragma unroll
-      for (int ft = 0; ft < FT; ++ft) acc[ft][r] = fast_exp2(acc[ft][r] + (bf[ft] + rt[r]));
+      for (int ft = 0; ft < FT; ++ft) acc[ft][r] = fast_exp2(((acc[ft][r] + bf[ft]) + rt[r]) - shift);
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {

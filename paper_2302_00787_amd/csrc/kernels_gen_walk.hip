@@ -104,7 +104,6 @@ __device__ __forceinline__ void project(f32x4 (&acc)[FT], const f32x4 (&w0)[FT],
 
 struct WalkArgs {
   GenSide F, S;            // first side (whose rows enter the state), second side (whose rows are the output's)
-  int f_side, s_side;      // 0 queries, 1 keys
   TensorDev V, U;          // values of the first side's rows; (gradient walk) left rows of the second side
   int vcols, vone, ucols, uone;
   int L, H, M, d, nv, ldt, rows_per_seg, nseg;
@@ -116,10 +115,16 @@ struct WalkArgs {
   unsigned* flushed;
 };
 
-// What is added to the exponents of a token of a side: - its shift (queries), row term - key maximum (keys), -inf past the end.
-__device__ __forceinline__ float side_add(const WalkArgs& a, const GenSide& sd, int side, int bh, int row, int row_end, float kmax) {
+// What a token of a side brings to its exponents: - its shift (queries), its row term (keys, whose shift is the key
+// maximum), -inf past the end; and an exponent of it, in the order of the other kernels (kernels_gen_rows.hip).
+template <bool KEYS>
+__device__ __forceinline__ float side_term(const WalkArgs& a, const GenSide& sd, int bh, int row, int row_end) {
   if (row >= row_end) return -INFINITY;
-  return side ? sd.rk[(size_t)bh * a.L + row] - kmax : -a.row_shift[(size_t)bh * a.L + row];
+  return KEYS ? sd.rk[(size_t)bh * a.L + row] : -a.row_shift[(size_t)bh * a.L + row];
+}
+template <bool KEYS>
+__device__ __forceinline__ float exponent(float e, float bias, float term, float kmax) {
+  return KEYS ? ((e + bias) + term) - kmax : (e + bias) + term;
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -146,8 +151,9 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_gen_walk(WalkArgs 
   int g = lane >> 4, c = lane & 15;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), f0 = 16 * FT * w;
   const int pg = group_of(a.F.pgroups, b, h, a.H), M = a.M, d = a.d;
-  const float* W1 = a.F.W + ((size_t)pg * 2 + a.f_side) * M * d;
-  const float* W2 = a.S.W + ((size_t)pg * 2 + a.s_side) * M * d;
+  constexpr bool F_KEYS = MODE == 0;
+  const float* W1 = a.F.W + ((size_t)pg * 2 + F_KEYS) * M * d;
+  const float* W2 = a.S.W + ((size_t)pg * 2 + !F_KEYS) * M * d;
   const float* bias = a.F.bias + ((size_t)pg * 2) * M;      // (the same on both sides)
   const float kmax = ordered_to_float(a.kmax_u[bh]);
   const int row_beg = seg * a.rows_per_seg, row_end = min(a.L, row_beg + a.rows_per_seg);
@@ -198,8 +204,8 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_gen_walk(WalkArgs 
     asm volatile("" : "+v"(g), "+v"(c));             // (nothing that follows from the lane is kept across chunks)
     const int row0 = row_of(ci);
     const float* buf = smem + (ci & 1) * kBuf;
-    const float addf = side_add(a, a.F, a.f_side, bh, row0 + c, row_end, kmax);
-    const float adds = MODE ? side_add(a, a.S, a.s_side, bh, row0 + c, row_end, kmax) : 0.f;
+    const float addf = side_term<F_KEYS>(a, a.F, bh, row0 + c, row_end);
+    const float adds = MODE ? side_term<true>(a, a.S, bh, row0 + c, row_end) : 0.f;
     f32x4 wf[FT];
     first_group(wf, W1, f0, M, d, g, c);
     __syncthreads();
@@ -215,12 +221,12 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_gen_walk(WalkArgs 
 #pragma unroll
     for (int ft = 0; ft < FT; ++ft)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) sf[ft][r] = fast_exp2(sf[ft][r] + (br[ft][r] + addf));
+      for (int r = 0; r < 4; ++r) sf[ft][r] = fast_exp2(exponent<F_KEYS>(sf[ft][r], br[ft][r], addf, kmax));
     if (MODE) {
 #pragma unroll
       for (int ft = 0; ft < FT; ++ft)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) p[ft][r] = fast_exp2(p[ft][r] + (br[ft][r] + adds));
+        for (int r = 0; r < 4; ++r) p[ft][r] = fast_exp2(exponent<true>(p[ft][r], br[ft][r], adds, kmax));
     } else {
       float m = -INFINITY;
 #pragma unroll
@@ -344,8 +350,9 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_gen_gwalk(WalkArgs
   int g = lane >> 4, c = lane & 15;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), f0 = 16 * FT * w;
   const int pg = group_of(a.F.pgroups, b, h, a.H), M = a.M, d = a.d;
-  const float* W1 = a.F.W + ((size_t)pg * 2 + a.f_side) * M * d;
-  const float* W2 = a.S.W + ((size_t)pg * 2 + a.s_side) * M * d;
+  constexpr bool F_KEYS = MODE == 0;
+  const float* W1 = a.F.W + ((size_t)pg * 2 + F_KEYS) * M * d;
+  const float* W2 = a.S.W + ((size_t)pg * 2 + !F_KEYS) * M * d;
   const float* bias = a.F.bias + ((size_t)pg * 2) * M;
   const float kmax = ordered_to_float(a.kmax_u[bh]);
   const int row_beg = seg * a.rows_per_seg, row_end = min(a.L, row_beg + a.rows_per_seg);
@@ -400,8 +407,8 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_gen_gwalk(WalkArgs
     const float* Us = Vs + TT * ldv;
     float addf[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) addf[r] = side_add(a, a.F, a.f_side, bh, row0 + 4 * g + r, row_end, kmax);
-    const float adds = side_add(a, a.S, a.s_side, bh, row0 + c, row_end, kmax);
+    for (int r = 0; r < 4; ++r) addf[r] = side_term<F_KEYS>(a, a.F, bh, row0 + 4 * g + r, row_end);
+    const float adds = side_term<!F_KEYS>(a, a.S, bh, row0 + c, row_end);
     f32x4 wf[FT];
     first_group(wf, W1, f0, M, d, g, c);
     __syncthreads();
@@ -429,7 +436,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_gen_gwalk(WalkArgs
 #pragma unroll
     for (int ft = 0; ft < FT; ++ft)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) ff[ft][r] = fast_exp2(ff[ft][r] + (bl[f0 + 16 * ft + c] + addf[r]));
+      for (int r = 0; r < 4; ++r) ff[ft][r] = fast_exp2(exponent<F_KEYS>(ff[ft][r], bl[f0 + 16 * ft + c], addf[r], kmax));
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -453,7 +460,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_gen_gwalk(WalkArgs
       const f32x4 br = *(const f32x4*)(bl + f0 + 16 * ft + 4 * g);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        df[ft][r] *= fast_exp2(fs2[ft][r] + (br[r] + adds));
+        df[ft][r] *= fast_exp2(exponent<!F_KEYS>(fs2[ft][r], br[r], adds, kmax));
         rs += df[ft][r];
       }
     }
@@ -592,7 +599,7 @@ bool gen_walk_supported(int d, int dv, int M) { return d % 4 == 0 && dv % 4 == 0
 int launch_gen_walk(const GenSide& qs, const GenSide& ks, const TensorDev& V, int L, int BH, int H, int M, int d, int nv, int ldt,
                     int rows_per_seg, int nseg, const uint32_t* kmax_u, const float* Tstate, const TensorDev& Y, float* den_out,
                     float* shift_out, hipStream_t st, unsigned* flushed) {
-  WalkArgs a{ks, qs, 1, 0, V, V, nv, 1, 0, 0, L, H, M, d, nv, ldt, rows_per_seg, nseg, kmax_u, nullptr, Tstate, Y, den_out, shift_out, flushed};
+  WalkArgs a{ks, qs, V, V, nv, 1, 0, 0, L, H, M, d, nv, ldt, rows_per_seg, nseg, kmax_u, nullptr, Tstate, Y, den_out, shift_out, flushed};
   return run_walk<0>(a, BH, st);
 }
 
@@ -601,9 +608,9 @@ int launch_gen_bwd_walks(const GenSide& qs, const GenSide& ks, const TensorDev& 
                          const float* Tstate, const float* Rstate, const TensorDev& dQ, const TensorDev& dK, const TensorDev& dV,
                          hipStream_t st) {
   const TensorDev G{ghat, 0, (long long)H * L * ldt, (long long)L * ldt, (long long)ldt};
-  WalkArgs a{ks, qs, 1, 0, V, G, nv, 1, ldt, 0, L, H, M, d, nv, ldt, rows_per_seg, nseg, kmax_u, row_shift, Tstate, dQ, nullptr, nullptr, nullptr};
+  WalkArgs a{ks, qs, V, G, nv, 1, ldt, 0, L, H, M, d, nv, ldt, rows_per_seg, nseg, kmax_u, row_shift, Tstate, dQ, nullptr, nullptr, nullptr};
   if (int rc = run_gwalk<0>(a, BH, st)) return rc;
-  WalkArgs r{qs, ks, 0, 1, G, V, ldt, 0, nv, 1, L, H, M, d, nv, ldt, rows_per_seg, nseg, kmax_u, row_shift, Rstate, dV, nullptr, nullptr, nullptr};
+  WalkArgs r{qs, ks, G, V, ldt, 0, nv, 1, L, H, M, d, nv, ldt, rows_per_seg, nseg, kmax_u, row_shift, Rstate, dV, nullptr, nullptr, nullptr};
   if (int rc = run_walk<1>(r, BH, st)) return rc;
   r.out = dK;
   return run_gwalk<1>(r, BH, st);
