@@ -551,7 +551,7 @@ int attention_impl(const float* theta, int groups, const fs_tensor* Q, const fs_
   ks.kpart = (float*)(ws + p.off_kpart);
   ks.kcap = p.kcap;
   if (int rc = launch_gen_kmax(ks, Lk, BH, H, M, d, kmax, st)) return rc;
-  if (int rc = launch_gen_state(ks, dev(V), Lk, BH, H, M, d, dv, 1, p.ldt, p.rows_per_seg, p.nseg, kmax, nullptr, state, st))
+  if (int rc = launch_gen_state(ks, dev(V), Lk, BH, H, M, d, dv, 1, p.ldt, p.rows_per_seg, p.nseg, kmax, nullptr, false, state, st))
     return rc;
   const size_t per_state = (size_t)M * p.ldt;
   if (int rc = launch_gen_reduce(state, BH, p.nseg, per_state, causal, st)) return rc;
@@ -740,12 +740,12 @@ int attention_backward_impl(const float* theta, int groups, const fs_tensor* Q, 
   ks.rk = (float*)(ws + p.k.off_rk);      // the key row terms are evaluated once (k_gen_kmax) and read by the kernels after it
   ks.kpart = (float*)(ws + p.k.off_kpart);
   ks.kcap = p.k.kcap;
+  const bool walks = causal && gen_walk_supported(d, dv, M);
   if (int rc = launch_gen_kmax(ks, Lk, BH, H, M, d, kmax, st)) return rc;
-  if (int rc = launch_gen_state(ks, dev(V), Lk, BH, H, M, d, dv, 1, ldt, p.k.rows_per_seg, p.k.nseg, kmax, nullptr, state, st))
+  if (int rc = launch_gen_state(ks, dev(V), Lk, BH, H, M, d, dv, 1, ldt, p.k.rows_per_seg, p.k.nseg, kmax, nullptr, !walks, state, st))
     return rc;
   if (int rc = launch_gen_reduce(state, BH, p.k.nseg, per_state, causal, st)) return rc;
   const TensorDev gbuf{ghat, 0, (long long)H * Lq * ldt, (long long)Lq * ldt, (long long)ldt};
-  const bool walks = causal && gen_walk_supported(d, dv, M);
   if (walks) {
     if (int rc = launch_gen_walk(qs, ks, dev(V), Lk, BH, H, M, d, dv, ldt, p.k.rows_per_seg, p.k.nseg, kmax, state, gbuf, den, shift, st, flushed))
       return rc;
@@ -763,7 +763,7 @@ int attention_backward_impl(const float* theta, int groups, const fs_tensor* Q, 
   }
   // G1 in place of Y, then the segment sums of P^T G1 (the query-side twin of the state pass)
   if (int rc = launch_bwd_ghat(dev(dY), ghat, den, Lq, BH, H, dv, ldt, st)) return rc;
-  if (int rc = launch_gen_state(qs, gbuf, Lq, BH, H, M, d, ldt, 0, ldt, p.q.rows_per_seg, p.q.nseg, kmax, shift, rstate, st))
+  if (int rc = launch_gen_state(qs, gbuf, Lq, BH, H, M, d, ldt, 0, ldt, p.q.rows_per_seg, p.q.nseg, kmax, shift, !walks, rstate, st))
     return rc;
   if (int rc = launch_gen_reduce(rstate, BH, p.q.nseg, per_state, causal ? 2 : 0, st)) return rc;
   if (walks)
@@ -856,7 +856,7 @@ int favorsharp_kernel_matvec(const float* theta, const fs_tensor* X, const fs_te
   TensorDev Cv{C, FS_F32, 0, 0, n};
   TensorDev Ov{out, FS_F32, 0, 0, n};
   if (int rc = launch_gen_kmax(ks, Ny, 1, 1, M, d, kmax, st)) return rc;
-  if (int rc = launch_gen_state(ks, Cv, Ny, 1, 1, M, d, n, 0, p.ldt, p.rows_per_seg, p.nseg, kmax, nullptr, state, st)) return rc;
+  if (int rc = launch_gen_state(ks, Cv, Ny, 1, 1, M, d, n, 0, p.ldt, p.rows_per_seg, p.nseg, kmax, nullptr, false, state, st)) return rc;
   const size_t per_state = (size_t)M * p.ldt;
   if (int rc = launch_gen_reduce(state, 1, p.nseg, per_state, 0, st)) return rc;
   return launch_gen_apply(qs, Nx, 1, 1, M, d, n, p.ldt, state, (size_t)p.nseg * per_state, kmax, 1, Ov, nullptr, nullptr, st);

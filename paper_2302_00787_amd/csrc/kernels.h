@@ -48,7 +48,7 @@ int launch_gen_features(const TensorDev& X, int n, int d, float scale, float alp
 int launch_gen_kmax(const GenSide& ks, int Lk, int BH, int H, int M, int d, uint32_t* kmax_u, hipStream_t st);
 int launch_gen_state(const GenSide& ks, const TensorDev& V, int Lk, int BH, int H, int M, int d, int nv,
                      int append_ones, int ldt, int rows_per_seg, int nseg, uint32_t* kmax_u,
-                     const float* row_shift, float* Tpart, hipStream_t st);
+                     const float* row_shift, bool tiles, float* Tpart, hipStream_t st);
 int launch_gen_reduce(float* Tpart, int BH, int nseg, size_t per_state, int prefix, hipStream_t st);
 int launch_gen_apply(const GenSide& qs, int Lq, int BH, int H, int M, int d, int nv, int ldt, const float* T,
                      size_t state_stride, const uint32_t* kmax_u, int matvec, const TensorDev& Y, float* den_out,

@@ -71,6 +71,15 @@ __device__ __forceinline__ f32x4 row_group(const RawRow<BF, Q>& x, int q, float 
   }
 }
 
+// Registers and rows of sixteen lanes exchanged: register j of row g <- register g of row j.  Of numbers 16 q + 4 g + r that makes
+// 16 q + 4 r + g: the order in which the kernels on LDS tiles (kernels_generic.hip) run through a row.
+__device__ __forceinline__ f32x4 lane_rows_transposed(f32x4 v) {
+  const u32x4 u = __builtin_bit_cast(u32x4, v);
+  const auto a = __builtin_amdgcn_permlane32_swap(u[0], u[2], false, false), b = __builtin_amdgcn_permlane32_swap(u[1], u[3], false, false);
+  const auto p = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false), q = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+  return __builtin_bit_cast(f32x4, u32x4{p[0], p[1], q[0], q[1]});
+}
+
 // ---------------------------------------------------------------------------------------------------
 // Key-side maximum of the exponent per (b, h), max_{j,m} E2[j,m]: one partial maximum per workgroup, part[bh][block], or
 // where there is no room for them an atomic maximum into kmax[bh] (ordered-uint image; atomics of many workgroups on one
@@ -218,14 +227,17 @@ __global__ void __launch_bounds__(256, 2) k_gen_kmax(GenSide ks, int Lk, int H, 
 // ---------------------------------------------------------------------------------------------------
 // Partial states (Section 2.1, S^T C): Tpart[bh][seg][m][v] = sum_{j in seg} exp2(E2[j,m] - kmax) * V1[j,v].  With row_shift !=
 // nullptr the query side of the backward pass: features of side 0 with the per-row shifts of the forward pass (no row term),
-// "values" = rows of the output gradient.  A wave holds 16 FT features: their rows of W~ and their state stay in
+// "values" = rows of the output gradient.  The gradients' kernels evaluate the features of both sides again, and what they and
+// this one round differently does not cancel in them against the normalisers: where they go through LDS tiles (TILES), the
+// projection runs through a row in their order, four lane swaps per four numbers (without: dV and dK of the non-causal
+// backward pass 1.1 times as far off on average, up to 1.6).  A wave holds 16 FT features: their rows of W~ and their state stay in
 // registers, tokens pass by sixteen at a time straight from memory; no LDS, no barrier.  f32 B2 H4 L4096 d64 M256: 60 -> 37
 // us (18 at the matrix rate), bf16 B1 H16 L4096 d128 M512: 425 -> 310 (118).  grid (nseg, ceil(M / (16 FT
 // waves)), B*H), block 64 waves.
 // ---------------------------------------------------------------------------------------------------
 template <int Q> constexpr int STATE_FT = Q >= 6 ? 2 : 4;
 
-template <int Q, int XB, int VB, int D4>
+template <int Q, int XB, int VB, int D4, int TILES>
 __global__ void __launch_bounds__(256, 2) k_gen_state(GenSide ks, TensorDev V, int Lk, int H, int M, int d, int nv, int append_ones,
                                                       int ldt, int rows_per_seg, int nseg, uint32_t* kmax_u, const float* part,
                                                       int npart, const float* row_shift, float* Tpart) {
@@ -272,7 +284,10 @@ __global__ void __launch_bounds__(256, 2) k_gen_state(GenSide ks, TensorDev V, i
     RawRow<0, Q> raw;
     fetch_row<D4>(raw, W, (long long)min(f, M - 1) * d, d, g);
 #pragma unroll
-    for (int q = 0; q < Q; ++q) wr[ft][q] = row_group(raw, q, 16 * q + 4 * g < d ? 1.f : 0.f);
+    for (int q = 0; q < Q; ++q) {
+      wr[ft][q] = row_group(raw, q, 16 * q + 4 * g < d ? 1.f : 0.f);
+      if (TILES) wr[ft][q] = lane_rows_transposed(wr[ft][q]);
+    }
     bf[ft] = f < M ? bias[f] : -INFINITY;
 #pragma unroll
     for (int vt = 0; vt < VT; ++vt) T[ft][vt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -294,7 +309,8 @@ __global__ void __launch_bounds__(256, 2) k_gen_state(GenSide ks, TensorDev V, i
     for (int ft = 0; ft < FT; ++ft) acc[ft] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      const f32x4 x = row_group(xn, q, sc[q]);
+      f32x4 x = row_group(xn, q, sc[q]);
+      if (TILES) x = lane_rows_transposed(x);
 #pragma unroll
       for (int s = 0; s < 4; ++s)
 #pragma unroll
@@ -370,13 +386,17 @@ int launch_gen_kmax(const GenSide& ks, int Lk, int BH, int H, int M, int d, uint
 }
 
 int launch_gen_state(const GenSide& ks, const TensorDev& V, int Lk, int BH, int H, int M, int d, int nv, int append_ones, int ldt,
-                     int rows_per_seg, int nseg, uint32_t* kmax_u, const float* row_shift, float* Tpart, hipStream_t st) {
+                     int rows_per_seg, int nseg, uint32_t* kmax_u, const float* row_shift, bool tiles, float* Tpart, hipStream_t st) {
   return by_width(d, ldt, [&](auto width) -> int {
     constexpr int Q = width(), FT = STATE_FT<Q>;
     const int groups = (M + 16 * FT - 1) / (16 * FT), waves = groups < 4 ? groups : 4;
     auto pick = [&](auto d4) {
       constexpr int D4 = d4();
-      return !ks.X.dtype ? k_gen_state<Q, 0, 0, D4> : V.dtype ? k_gen_state<Q, 1, 1, D4> : k_gen_state<Q, 1, 0, D4>;
+      auto pick2 = [&](auto tl) {
+        constexpr int TILES = tl();
+        return !ks.X.dtype ? k_gen_state<Q, 0, 0, D4, TILES> : V.dtype ? k_gen_state<Q, 1, 1, D4, TILES> : k_gen_state<Q, 1, 0, D4, TILES>;
+      };
+      return tiles ? pick2(std::integral_constant<int, 1>()) : pick2(std::integral_constant<int, 0>());
     };
     auto kernel = d % 4 ? pick(std::integral_constant<int, 0>()) : pick(std::integral_constant<int, 1>());
     hipLaunchKernelGGL(kernel, dim3(nseg, (groups + waves - 1) / waves, BH), dim3(64 * waves), 0, st, ks, V, Lk, H, M, d,

@@ -94,6 +94,40 @@ def test_backward_general_path_dense_quadratic_forms(fs, variant, L, d, M, causa
     _check_backward(fs, Q, K, V, dY, Om, d ** -0.25, variant, "f32", 3e-4, causal=causal)
 
 
+@pytest.mark.parametrize("d,M,causal", [(8, 40, False), (16, 16, False), (18, 40, False), (32, 70, False), (36, 40, False), (64, 33, False),
+                                        (80, 40, False), (128, 40, False), (16, 40, True), (64, 130, True), (18, 40, True), (24, 520, True)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_backward_general_path_weights_of_every_row_sum_to_one(fs, d, M, causal, dtype):
+    """The rows of K_hat over their normalisers sum to one, so sum_j dV_j = sum_i dY_i, but only as far as the features that the
+    gradient sums are those whose sum the normaliser is: with exponents of 2e5 a projection that is rounded in another order is
+    off by up to 2e-3.  All terms are positive: 2^-24 for each of at most 2 (L + M) additions in a row, and for the exponents' own
+    few roundings of the keys (below 16: 1e-6)."""
+    import torch
+    rng = np.random.default_rng(90 + d + M)
+    L = 300
+    Om = rng.standard_normal((1, M, d)).astype(np.float32)
+    Q = rng.standard_normal((1, 1, L, d))
+    Q *= 2e5 / (np.log2(np.e) * np.abs(Q[0, 0] @ Om[0].T.astype(np.float64)).max(1)[None, None, :, None])
+    K = 0.1 * rng.standard_normal((1, 1, L, d))
+    V = rng.standard_normal((1, 1, L, d))
+    dY = 0.5 + rng.random((1, 1, L, d))
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    width = (d + 7) // 8 * 8               # rows start at multiples of 16 bytes
+
+    def dev(x, t=dt):
+        y = torch.zeros((1, 1, L, width), dtype=t, device="cuda")
+        y[..., :d] = torch.from_numpy(x).to(t)
+        return y[..., :d]
+    th = orc.Theta(logD=0.0, A=np.zeros(d), B1=np.eye(d), B2=np.eye(d), C1=-0.5 * np.eye(d), C2=-0.5 * np.eye(d))
+    theta = torch.from_numpy(util.theta_vec_from_oracle(th)[None]).cuda()
+    dYd = dev(dY)
+    grads = tuple(dev(np.zeros((1, 1, L, d)), torch.float32) for _ in range(3))
+    fs.attention_backward(theta, dev(Q), dev(K), dev(V), dYd, 1.0, torch.from_numpy(Om).cuda(), causal=causal, grads=grads)
+    got, want = grads[2][0, 0].double().sum(0), dYd[0, 0].double().sum(0)
+    rel = float(((got - want).abs() / want).max())
+    assert rel <= 2 * (L + M) * 2.0 ** -24 + 1e-6, rel
+
+
 @pytest.mark.parametrize("L,M,d,dv", [(1, 1, 4, 4), (33, 16, 8, 4), (64, 200, 128, 128)])
 def test_backward_degenerate_and_maximum_sizes(fs, L, M, d, dv):
     rng = np.random.default_rng(62)
