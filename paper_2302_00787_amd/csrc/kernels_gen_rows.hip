@@ -230,18 +230,16 @@ __global__ void __launch_bounds__(256, 2) k_gen_kmax(GenSide ks, int Lk, int H, 
 // "values" = rows of the output gradient.  The gradients' kernels evaluate the features of both sides again, and what they and
 // this one round differently does not cancel in them against the normalisers: where they go through LDS tiles (TILES), the
 // projection runs through a row in their order, four lane swaps per four numbers (without: dV and dK of the non-causal
-// backward pass 1.1 times as far off on average, up to 1.6).  A wave holds 16 FT features: their rows of W~ and their state stay in
+// backward pass 1.1 times as far off on average, up to 1.6).  A wave holds 16 FT features (state_tiles): their rows of W~ and their state stay in
 // registers, tokens pass by sixteen at a time straight from memory; no LDS, no barrier.  f32 B2 H4 L4096 d64 M256: 60 -> 37
 // us (18 at the matrix rate), bf16 B1 H16 L4096 d128 M512: 425 -> 310 (118).  grid (nseg, ceil(M / (16 FT
 // waves)), B*H), block 64 waves.
 // ---------------------------------------------------------------------------------------------------
-template <int Q> constexpr int STATE_FT = Q >= 6 ? 2 : 4;
-
-template <int Q, int XB, int VB, int D4, int TILES>
+template <int Q, int XB, int VB, int D4, int TILES, int FT>
 __global__ void __launch_bounds__(256, 2) k_gen_state(GenSide ks, TensorDev V, int Lk, int H, int M, int d, int nv, int append_ones,
                                                       int ldt, int rows_per_seg, int nseg, uint32_t* kmax_u, const float* part,
                                                       int npart, const float* row_shift, float* Tpart) {
-  constexpr int FT = STATE_FT<Q>, VT = VT_OF<Q>;
+  constexpr int VT = VT_OF<Q>;
   const int seg = blockIdx.x, bh = blockIdx.z, b = bh / H, h = bh % H;
   const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -385,25 +383,48 @@ int launch_gen_kmax(const GenSide& ks, int Lk, int BH, int H, int M, int d, uint
   });
 }
 
+// Tiles of 16 features per wave of k_gen_state: few where the chip's 1024 SIMDs want waves or the last wave's tiles would be padding,
+// more where rows and values, which every wave fetches for itself, are what it waits for.  us per call with 1 / 2 / 4 of them:
+//   few waves       causal bf16 1 x 415 d 48 M 32  64.1 / 69.2 / 76.9;  f32 8 x 1472 d 64 M 256 backward  266.8 / 273.8 / 269.3 (736 waves of 4)
+//   M <= 64         causal f32 1024 x 512 d 48 M 64  574 / 610 / 605;  bf16 1024 x 128 d 8 M 16  44.1 / 47.3 / 52.0
+//   M <= 128        f32 4 x 16384 d 64 M 128  148 / 149 / 156;  causal f32 64 x 8192 d 16 M 128  404 / 395 / 403
+//   M larger        causal f32 128 x 2048 d 64 M 512  1811 / 1809 / 1672;  causal f32 8 x 4096 d 64 M 256  152 / 153 / 147
+//   wide rows       (four tiles do not fit)  f32 128 x 1024 d 128 M 256  1267 / 1064;  bf16 75 x 320 (segments of 96)  262 / 288
+//   the same in the order of the LDS tiles (f32: two spill 53 registers, not 26)  f32 128 x 1024 d 128 M 256 backward
+//                   2630 / 2893;  bf16 2600 / 2548
+static int state_tiles(int Q, bool tiles, int M, int BH, int nseg, int rows_per_seg, bool bf16) {
+  auto waves = [&](int ft) { return (long long)nseg * BH * ((M + 16 * ft - 1) / (16 * ft)); };
+  if (Q == 8 && tiles && !bf16) return 1;
+  if (Q >= 6) return waves(2) >= 1600 && (!bf16 || rows_per_seg >= 128) ? 2 : 1;
+  if (M > 128 && waves(4) >= 800) return 4;
+  return M > 64 && waves(2) >= 1600 ? 2 : 1;
+}
+
 int launch_gen_state(const GenSide& ks, const TensorDev& V, int Lk, int BH, int H, int M, int d, int nv, int append_ones, int ldt,
                      int rows_per_seg, int nseg, uint32_t* kmax_u, const float* row_shift, bool tiles, float* Tpart, hipStream_t st) {
   return by_width(d, ldt, [&](auto width) -> int {
-    constexpr int Q = width(), FT = STATE_FT<Q>;
-    const int groups = (M + 16 * FT - 1) / (16 * FT), waves = groups < 4 ? groups : 4;
-    auto pick = [&](auto d4) {
-      constexpr int D4 = d4();
-      auto pick2 = [&](auto tl) {
-        constexpr int TILES = tl();
-        return !ks.X.dtype ? k_gen_state<Q, 0, 0, D4, TILES> : V.dtype ? k_gen_state<Q, 1, 1, D4, TILES> : k_gen_state<Q, 1, 0, D4, TILES>;
+    constexpr int Q = width();
+    auto launch = [&](auto nft) -> int {
+      constexpr int FT = nft();
+      const int groups = (M + 16 * FT - 1) / (16 * FT), waves = groups < 4 ? groups : 4;
+      auto pick = [&](auto d4, auto tl) {
+        constexpr int D4 = d4(), TL = tl();
+        return !ks.X.dtype ? k_gen_state<Q, 0, 0, D4, TL, FT> : V.dtype ? k_gen_state<Q, 1, 1, D4, TL, FT> : k_gen_state<Q, 1, 0, D4, TL, FT>;
       };
-      return tiles ? pick2(std::integral_constant<int, 1>()) : pick2(std::integral_constant<int, 0>());
+      const std::integral_constant<int, 0> no;
+      const std::integral_constant<int, 1> yes;
+      auto kernel = d % 4 ? (tiles ? pick(no, yes) : pick(no, no)) : (tiles ? pick(yes, yes) : pick(yes, no));
+      hipLaunchKernelGGL(kernel, dim3(nseg, (groups + waves - 1) / waves, BH), dim3(64 * waves), 0, st, ks, V, Lk, H, M, d,
+                         nv, append_ones, ldt, rows_per_seg, nseg, kmax_u, kmax_part(ks, Lk, BH, d), (Lk + kmax_rows(d) - 1) / kmax_rows(d),
+                         row_shift, Tpart);
+      FS_LAUNCH_CHECK();
+      return 0;
     };
-    auto kernel = d % 4 ? pick(std::integral_constant<int, 0>()) : pick(std::integral_constant<int, 1>());
-    hipLaunchKernelGGL(kernel, dim3(nseg, (groups + waves - 1) / waves, BH), dim3(64 * waves), 0, st, ks, V, Lk, H, M, d,
-                       nv, append_ones, ldt, rows_per_seg, nseg, kmax_u, kmax_part(ks, Lk, BH, d), (Lk + kmax_rows(d) - 1) / kmax_rows(d),
-                       row_shift, Tpart);
-    FS_LAUNCH_CHECK();
-    return 0;
+    const int ft = state_tiles(Q, tiles, M, BH, nseg, rows_per_seg, ks.X.dtype != 0);
+    if (ft == 1) return launch(std::integral_constant<int, 1>());
+    if constexpr (Q < 6)
+      if (ft == 4) return launch(std::integral_constant<int, 4>());
+    return launch(std::integral_constant<int, 2>());
   });
 }
 

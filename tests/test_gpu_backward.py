@@ -94,6 +94,52 @@ def test_backward_general_path_dense_quadratic_forms(fs, variant, L, d, M, causa
     _check_backward(fs, Q, K, V, dY, Om, d ** -0.25, variant, "f32", 3e-4, causal=causal)
 
 
+@pytest.mark.parametrize("d,dv,M,B,L", [(8, 16, 250, 128, 500), (30, 30, 130, 64, 512), (64, 64, 150, 64, 300),       # four tiles of features per wave
+                                        (16, 16, 70, 128, 512), (32, 20, 100, 128, 300), (48, 64, 120, 128, 300),     # two
+                                        (66, 66, 40, 200, 300), (80, 96, 70, 128, 300), (128, 128, 100, 128, 300),     # two, rows of up to 96 and 128
+                                        (128, 8, 17, 300, 1100), (16, 128, 33, 130, 260)])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_general_states_of_many_waves(fs, d, dv, M, B, L, causal, dtype):
+    """Calls large enough for a wave of the state kernel to take two or four tiles of features, with remainders of tiles and of
+    segments: attention and its gradients of the first, a middle and the last sequence against float64 on the same inputs.  The
+    bars of this file: 1e-4 for the output, three times that for gradients."""
+    import torch
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    gen = torch.Generator(device="cuda").manual_seed(d + M + L)
+
+    def rows(n, scale=1.0):
+        x = scale * torch.randn((B, 1, L, (n + 7) // 8 * 8), generator=gen, device="cuda")
+        return x.to(dt)[..., :n]
+    Q, K, V, dY = rows(d, 0.7), rows(d, 0.7), rows(dv), rows(dv)
+    Om = torch.randn((1, M, d), generator=gen, device="cuda")
+    rng = np.random.default_rng(d)
+    theta = util.theta_vec_from_oracle(orc.fit("saderf", 0.5 * rng.standard_normal((400, d)), 0.4 * rng.standard_normal((400, d))))
+    th, s = util.oracle_theta_from_vec(theta, d), d ** -0.25
+    td = torch.from_numpy(theta[None]).cuda()
+
+    def out(n):
+        return torch.full((B, 1, L, (n + 7) // 8 * 8), float("nan"), device="cuda")[..., :n]
+    Y = fs.attention(td, Q, K, V, s, Om, causal=causal, out=out(dv))
+    grads = fs.attention_backward(td, Q, K, V, dY, s, Om, causal=causal, grads=(out(d), out(d), out(dv)))
+    om = Om[0].double()
+    A, B1, B2, C2 = (torch.from_numpy(np.asarray(x, dtype=np.float64)).cuda() for x in (th.A, th.B1, th.B2, th.C2))
+    for b in (0, B // 2, B - 1):
+        q, k, v = (x[b, 0].double().requires_grad_(True) for x in (Q, K, V))
+        bias = (om * om) @ A
+        E1, E2 = s * q @ (om @ B1).T + bias, s * k @ (om @ B2).T + bias + s * s * ((k @ C2) * k).sum(1, keepdim=True)
+        W = torch.exp(E1 - E1.detach().max(1, keepdim=True).values) @ torch.exp(E2 - E2.detach().max()).T
+        if causal:
+            W = torch.tril(W)
+        ref = (W @ v) / W.sum(1, keepdim=True)
+        gref = torch.autograd.grad((ref * dY[b, 0].double()).sum(), (q, k, v))
+        err = float((Y[b, 0].double() - ref.detach()).norm() / ref.detach().norm())
+        assert err <= 1e-4, (b, err)
+        for g, r, name in zip(grads, gref, ("dQ", "dK", "dV")):
+            fro, row = util.gradient_errors(g[b, 0].double().cpu().numpy(), r.cpu().numpy())
+            assert fro <= 3e-4 and row <= 1.2e-3, (b, name, fro, row)
+
+
 @pytest.mark.parametrize("d,M,causal", [(8, 40, False), (16, 16, False), (18, 40, False), (32, 70, False), (36, 40, False), (64, 33, False),
                                         (80, 40, False), (128, 40, False), (16, 40, True), (64, 130, True), (18, 40, True), (24, 520, True)])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
