@@ -49,12 +49,13 @@ struct AttnPlan {
 // last call whose normaliser came out as zero (favorsharp_attention_flushed_rows reads it).
 //
 // Shared by the workspace query and the call so that both agree.
-void plan_contraction(int BH, int pgroups, int Lk, int d, int M, int nv1, int causal, AttnPlan* p) {
+// short_segments: rows per segment of a causal call, 32 instead of 128, as long as that brings the segments up to one per CU.
+void plan_contraction(int BH, int pgroups, int Lk, int d, int M, int nv1, int causal, AttnPlan* p, bool short_segments = false) {
   p->pgroups = pgroups;
   p->ldt = ceil_div(nv1, 16) * 16;
   const int nmb = ceil_div(M, 32);
   int want;
-  if (causal) want = std::max(1, std::min(ceil_div(1024, BH), ceil_div(Lk, 128)));
+  if (causal) want = std::max(std::min(ceil_div(1024, BH), ceil_div(Lk, 128)), short_segments ? std::min(ceil_div(256, BH), ceil_div(Lk, 32)) : 1);
   else want = std::max(1, std::min(ceil_div(2048, BH * nmb), ceil_div(Lk, 32)));
   p->rows_per_seg = ceil_div(ceil_div(Lk, want), 32) * 32;
   p->nseg = ceil_div(Lk, p->rows_per_seg);
@@ -557,7 +558,7 @@ int attention_impl(const float* theta, int groups, const fs_tensor* Q, const fs_
   if (int rc = launch_gen_reduce(state, BH, p.nseg, per_state, causal, st)) return rc;
   if (event_main_begin && hipEventRecord((hipEvent_t)event_main_begin, st) != hipSuccess) return FS_ERR_DEVICE;
   int rc;
-  if (causal && gen_walk_supported(d, dv, M))
+  if (causal && gen_walk_attention(d, dv, M, (long long)BH * p.nseg > 256))
     rc = launch_gen_walk(qs, ks, dev(V), Lk, BH, H, M, d, dv, p.ldt, p.rows_per_seg, p.nseg, kmax, state, dev(Y), nullptr, nullptr, st, flushed);
   else if (causal)
     rc = launch_gen_causal(qs, ks, dev(V), Lk, BH, H, M, d, dv, p.ldt, p.rows_per_seg, p.nseg, kmax, state, dev(Y), nullptr, nullptr, st, flushed);
@@ -604,12 +605,17 @@ int favorsharp_attention_flushed_rows(const void* workspace, int* host_count, vo
 namespace {
 struct BwdPlan {
   AttnPlan k, q;           // key-side and query-side segmentations (the projection constants live in `k`)
+  bool walks;              // causal calls: on the kernels that keep the state in registers
   size_t off_ghat, off_den, off_shift, off_rstate, off_state2, total;
 };
 
 void plan_backward(int BH, int pgroups, int Lq, int Lk, int d, int dv, int M, int causal, BwdPlan* p) {
-  plan_contraction(BH, pgroups, Lk, d, M, dv + 1, causal, &p->k);
-  plan_contraction(BH, pgroups, Lq, d, M, dv + 1, causal, &p->q);
+  p->walks = causal && gen_walk_backward(d, dv, M, (long long)BH * ceil_div(Lk, 128) > 256);
+  // A walk of few features is four waves, half of them padding, and a chain of chunks: with few sequences its length is what
+  // the call waits for (us, 128 rows -> 32: f32 1 x 192 d80 M16 191 -> 96, 16 x 1024 261 -> 166; with the state in memory 171, 248).
+  const bool short_segments = p->walks && M <= 64;
+  plan_contraction(BH, pgroups, Lk, d, M, dv + 1, causal, &p->k, short_segments);
+  plan_contraction(BH, pgroups, Lq, d, M, dv + 1, causal, &p->q, short_segments);
   size_t off = p->k.total;
   p->off_ghat = off;   off = align_up(off + (size_t)BH * Lq * p->k.ldt * sizeof(float));
   p->off_den = off;    off = align_up(off + (size_t)BH * Lq * sizeof(float));
@@ -740,7 +746,7 @@ int attention_backward_impl(const float* theta, int groups, const fs_tensor* Q, 
   ks.rk = (float*)(ws + p.k.off_rk);      // the key row terms are evaluated once (k_gen_kmax) and read by the kernels after it
   ks.kpart = (float*)(ws + p.k.off_kpart);
   ks.kcap = p.k.kcap;
-  const bool walks = causal && gen_walk_supported(d, dv, M);
+  const bool walks = p.walks;
   if (int rc = launch_gen_kmax(ks, Lk, BH, H, M, d, kmax, st)) return rc;
   if (int rc = launch_gen_state(ks, dev(V), Lk, BH, H, M, d, dv, 1, ldt, p.k.rows_per_seg, p.k.nseg, kmax, nullptr, !walks, state, st))
     return rc;

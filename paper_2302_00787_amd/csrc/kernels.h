@@ -70,10 +70,10 @@ int launch_gen_bwd_causal(const GenSide& qs, const GenSide& ks, const TensorDev&
                           const float* row_shift, float* Tstate, float* Rstate, const TensorDev& dQ, const TensorDev& dK,
                           const TensorDev& dV, hipStream_t st);
 // The same on kernels that keep the state in registers (kernels_gen_walk.hip); they leave the states in memory as they are.
-// Rows and values are fetched four numbers at a time, and eight waves hold 64 features each: d, dv % 4 == 0 and M <= 512; there
-// they are the faster ones at every size measured (us per call, state in memory / in registers, f32 causal attention: B2 H4
-// L4096 d64 M256 279 / 147, B8 H8 L300 d128 M200 388 / 244, B2 H8 L1000 d48 M100 122 / 90; a part of it are the states).
-bool gen_walk_supported(int d, int dv, int M);
+// Which calls they take; us per call, state in memory / in registers, f32 causal attention: B2 H4 L4096 d64 M256 279 / 147,
+// B8 H8 L300 d128 M200 388 / 244, B2 H8 L1000 d48 M100 122 / 90; a part of it are the states.
+bool gen_walk_attention(int d, int dv, int M, bool many);
+bool gen_walk_backward(int d, int dv, int M, bool many);
 int launch_gen_walk(const GenSide& qs, const GenSide& ks, const TensorDev& V, int L, int BH, int H, int M, int d, int nv, int ldt,
                     int rows_per_seg, int nseg, const uint32_t* kmax_u, const float* Tstate, const TensorDev& Y, float* den_out,
                     float* shift_out, hipStream_t st, unsigned* flushed);

@@ -1,5 +1,6 @@
 // General-shape causal kernels with the state in registers: fp32 matrix instructions, d and dv multiples of four up to 128, M up to
-// 512 (other shapes: the causal kernels of kernels_generic.hip, whose state lies in memory).
+// 512 (other shapes, and those that would be mostly padding here: the causal kernels of kernels_generic.hip, whose state lies in
+// memory).
 //
 // A workgroup walks a segment of a sequence sixteen tokens at a time; a wave holds 16 FT features: its rows of the state stay in
 // accumulators from the first token to the last, and every operand of every product is either such an accumulator, a
@@ -594,7 +595,31 @@ int run_gwalk(const WalkArgs& a, int BH, hipStream_t st) {
 
 }  // namespace
 
-bool gen_walk_supported(int d, int dv, int M) { return d % 4 == 0 && dv % 4 == 0 && M <= 512; }
+// Rows and values are fetched four numbers at a time, and eight waves hold 64 features each.  A walk is made for the larger of the
+// widths of rows and values and for at least 64 features; where most of that is padding the kernels of kernels_generic.hip
+// remain, which go through blocks of 32 features and count columns.  (many: more segments than CUs, in the gradients before they
+// are shortened.)  Speed of a call on walks against one on those kernels, f32 and bf16:
+//   attention, widths even      1 x 192 to 128 x 512, d 8 to 128, M 16 to 512: 1.0 - 2.6 (bf16 d 128 M <= 32: 0.98 - 1.06)
+//   attention, uneven, M <= 32  d 8 dv 128  0.82 - 0.95;  d 8 dv 64 and d 64 dv 16  0.92 - 0.99, with many segments 1.1 - 1.3
+//   gradients                   few segments 1.1 - 3 (rows per segment: favorsharp_api.hip);  many, even widths 1.06 - 1.9, with a
+//                               dense C up to 3, wide rows at M <= 32 0.78 - 0.96 (dense 3);  many, d <= 64 beside dv 128,
+//                               M <= 64  0.6 - 0.9 (d 64 dense 1.15);  many, d 128 beside dv 8  0.63 - 0.9 (dense 3)
+static bool walk_possible(int d, int dv, int M) { return d % 4 == 0 && dv % 4 == 0 && M <= 512; }
+struct WalkWidths { int all; bool even; };
+static WalkWidths walk_widths(int d, int dv) {
+  const int ldt = (dv + 16) / 16 * 16;
+  auto w = [](int d_, int ldt_) { return by_width(d_, ldt_, [](auto q) { return (int)q(); }); };
+  const int all = w(d, ldt), rows = w(d, 0), values = w(0, ldt), lo = rows < values ? rows : values;
+  return {all, all >= 6 ? lo >= 6 : 2 * lo >= all};
+}
+bool gen_walk_attention(int d, int dv, int M, bool many) {
+  const WalkWidths x = walk_widths(d, dv);
+  return walk_possible(d, dv, M) && (M > 32 || x.even || (x.all < 6 && many));
+}
+bool gen_walk_backward(int d, int dv, int M, bool many) {
+  const WalkWidths x = walk_widths(d, dv);
+  return walk_possible(d, dv, M) && !(many && M <= 64 && !x.even && x.all >= 6 && d <= 64);
+}
 
 int launch_gen_walk(const GenSide& qs, const GenSide& ks, const TensorDev& V, int L, int BH, int H, int M, int d, int nv, int ldt,
                     int rows_per_seg, int nseg, const uint32_t* kmax_u, const float* Tstate, const TensorDev& Y, float* den_out,

@@ -97,12 +97,14 @@ def test_backward_general_path_dense_quadratic_forms(fs, variant, L, d, M, causa
 @pytest.mark.parametrize("d,dv,M,B,L", [(8, 16, 250, 128, 500), (30, 30, 130, 64, 512), (64, 64, 150, 64, 300),       # four tiles of features per wave
                                         (16, 16, 70, 128, 512), (32, 20, 100, 128, 300), (48, 64, 120, 128, 300),     # two
                                         (66, 66, 40, 200, 300), (80, 96, 70, 128, 300), (128, 128, 100, 128, 300),     # two, rows of up to 96 and 128
-                                        (128, 8, 17, 300, 1100), (16, 128, 33, 130, 260)])
+                                        (128, 8, 17, 300, 1100), (16, 128, 33, 130, 260),
+                                        (16, 16, 16, 300, 50), (64, 64, 20, 300, 40), (8, 64, 32, 300, 33), (24, 24, 64, 40, 300),   # causal walks with
+                                        (36, 64, 33, 3, 150), (12, 60, 64, 2, 140), (128, 100, 40, 5, 70)])                         # few features
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_general_states_of_many_waves(fs, d, dv, M, B, L, causal, dtype):
     """Calls large enough for a wave of the state kernel to take two or four tiles of features, with remainders of tiles and of
-    segments: attention and its gradients of the first, a middle and the last sequence against float64 on the same inputs.  The
+    segments, and calls on either side of the rules that choose the causal kernels: attention and its gradients of the first, a middle and the last sequence against float64 on the same inputs.  The
     bars of this file: 1e-4 for the output, three times that for gradients."""
     import torch
     dt = torch.float32 if dtype == "f32" else torch.bfloat16
