@@ -13,12 +13,30 @@
 // B8 H8 L4096 74.5 -> 64.4, 32 x 16384 117.7 -> 103.3, 1 x 262144 86.8 -> 72.3, 256 x 1000 69.8 -> 55.8, 16 x 300
 // 21.4 -> 19.5; one workgroup per sequence: 768 x 197 67.0 -> 61.6, 512 x 1024 98 -> 85.
 #pragma once
+#include <algorithm>
+
 #include "fast_pc.h"
 
 namespace fs {
 namespace rows {
 
 using namespace fast;
+
+// Parts into which each of BH sequences of `units` steps is cut for kernels with one workgroup per CU: as many as fit into one,
+// two, three or four passes over the chip, whichever takes the fewest steps (the last pass takes as long as a full one;
+// `fixed`: steps' worth of a workgroup's constants, images and results; at most `most` parts).  One workgroup per CU
+// rounded up instead leaves a second pass nearly empty: non-causal calls (us) 48 x 1024 44.2 -> 31.0, 24 x 2048 43.8 -> 31.2,
+// 12 x 4096 45.9 -> 32.5; gradients 48 x 1024 111.6 -> 71.5, 24 x 2048 103.4 -> 71.8.
+inline int parts_per_sequence(int BH, int units, int most, float fixed) {
+  int best = 1;
+  float least = 1e30f;
+  for (int pass = 1; pass <= 4; ++pass) {
+    const int n = std::max(1, std::min(most, 256 * pass / BH));
+    const float steps = (float)((n * BH + 255) / 256) * ((float)((units + n - 1) / n) + fixed);
+    if (steps < least) { least = steps; best = n; }
+  }
+  return best;
+}
 
 // Workgroups go to the eight XCDs in turn, each with an L2 of its own: the workgroup's place in an order in which an
 // XCD's workgroups are neighbours, so that those of one sequence fetch its state and constants through one L2.

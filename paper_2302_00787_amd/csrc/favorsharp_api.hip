@@ -630,7 +630,7 @@ namespace {
 // bf16 path of the non-causal backward pass: the forward plan plus G1 rows and the query-side segment sums.
 struct FastBwdPlan {
   FastPlan f;
-  int rslots, rows_per_rslot;
+  int rslots;
   size_t off_gh, off_rpart, off_rcpart, total;
 };
 
@@ -640,7 +640,6 @@ void plan_fast_backward(int BH, int pgroups, int Lq, int Lk, int causal, FastBwd
   fast_plan(BH, Lq, &nseg, &rows_per_seg, &sub);
   if (!causal) sub = 1;        // (half segments: the walks of the causal kernels)
   p->rslots = nseg * sub;
-  p->rows_per_rslot = rows_per_seg / sub;
   size_t off = p->f.total;
   p->off_gh = off;     off = align_up(off + (size_t)BH * Lq * 80 * sizeof(uint16_t));
   p->off_rpart = off;  off = align_up(off + (size_t)BH * p->rslots * 256 * 80 * sizeof(float));
@@ -711,7 +710,7 @@ int attention_backward_impl(const float* theta, int groups, const fs_tensor* Q, 
       f.pre_mode = dense_c2 ? 1 : 2;
     }
     return launch_fast_attention_backward(f, dev(dY), dev(dQ), dev(dK), dev(dV), (uint16_t*)(w8 + fp.off_gh),
-                                          (float*)(w8 + fp.off_rpart), (float*)(w8 + fp.off_rcpart), fp.rslots, fp.rows_per_rslot, (hipStream_t)stream);
+                                          (float*)(w8 + fp.off_rpart), (float*)(w8 + fp.off_rcpart), fp.rslots, (hipStream_t)stream);
   }
   BwdPlan p;
   plan_backward(BH, pgroups, Lq, Lk, d, dv, M, causal, &p);

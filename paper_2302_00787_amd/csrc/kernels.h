@@ -172,7 +172,7 @@ void fast_reduce_ranges(int BH, int nslot, int* Z, int* R);
 int launch_fast_attention(const FastLaunch& f, hipStream_t st, hipEvent_t ev_begin, hipEvent_t ev_end);
 int launch_fast_attention_backward(const FastLaunch& f, const TensorDev& dY, const TensorDev& dQ, const TensorDev& dK,
                                    const TensorDev& dV, uint16_t* gh, float* Rpart, float* rcpart,
-                                   int rslots, int rows_per_rslot, hipStream_t st);
+                                   int rslots, hipStream_t st);
 size_t fast_bwd_lds_bytes();
 size_t fast_bwd_causal_lds_bytes();
 

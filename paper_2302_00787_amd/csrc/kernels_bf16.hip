@@ -638,12 +638,18 @@ static int launch_fast_state_pass(const FastLaunch& f, FastArgs& a, hipStream_t 
   // whole segments, but for the causal backward pass, whose kernels run on the half segments
   const int sub = every_slot ? f.sub : 1;
   a.sub = sub;
-  a.nslot = f.nseg * sub;
+  if (!f.causal) {             // the segments are nobody else's: cut for the states (two chunks at a time), within the planned slots
+    const int chunks = (f.Lk + TC - 1) / TC;
+    const int want = rows::parts_per_sequence(BH, (chunks + 1) / 2, std::min(chunks, f.nseg * f.sub), 2.f);
+    a.rows_per_seg = (chunks + want - 1) / want * TC;
+    a.nseg = (f.Lk + a.rows_per_seg - 1) / a.rows_per_seg;
+  }
+  a.nslot = a.nseg * sub;
   // the last segment's states are never needed by the causal pass
-  const int nstate = (f.causal && !every_slot ? f.nseg - 1 : f.nseg) * sub;
+  const int nstate = (f.causal && !every_slot ? a.nseg - 1 : a.nseg) * sub;
   if (nstate > 0) {
     // two groups of waves need two chunks (sequences in segments of one: 1 x 4096 25.4 us with one group, 27.9 with two)
-    if (every_slot || f.rows_per_seg <= TC) {
+    if (every_slot || a.rows_per_seg <= TC) {
       hipLaunchKernelGGL(k_fast_state, dim3(nstate, BH), dim3(NT), sizeof(SmemState), st, a);
     } else {
       if (int rc = allow_lds((const void*)k_fast_state2, kState2Lds)) return rc;
@@ -748,7 +754,7 @@ int launch_fast_attention(const FastLaunch& f, hipStream_t st, hipEvent_t ev_beg
     const int ntt = tiles >= 4 * 2048 ? 4 : tiles >= 2 * 2048 ? 2 : 1;
     auto kernel = ntt == 4 ? k_fast_apply<4> : ntt == 2 ? k_fast_apply<2> : k_fast_apply<1>;
     const int step = 16 * ntt * (NTA / 64) / 2;      // at least four of the eight waves have a step
-    const int want = std::max(1, std::min((256 + BH - 1) / BH, (f.Lq + step - 1) / step));
+    const int want = rows::parts_per_sequence(BH, (f.Lq + 2 * step - 1) / (2 * step), (f.Lq + step - 1) / step, ntt == 4 ? 0.4f : 1.f);
     const int rows_per_blk = (((f.Lq + want - 1) / want) + step - 1) / step * step;
     const int nblk = (f.Lq + rows_per_blk - 1) / rows_per_blk;
     const size_t lds = apply_lds_bytes(ntt);
@@ -763,7 +769,7 @@ int launch_fast_attention(const FastLaunch& f, hipStream_t st, hipEvent_t ev_beg
 // Backward pass of a non-causal call: the forward state pass, then the kernels of kernels_bf16_bwd.hip.
 int launch_fast_attention_backward(const FastLaunch& f, const TensorDev& dY, const TensorDev& dQ, const TensorDev& dK,
                                    const TensorDev& dV, uint16_t* gh, float* Rpart, float* rcpart,
-                                   int rslots, int rows_per_rslot, hipStream_t st) {
+                                   int rslots, hipStream_t st) {
   FastArgs a;
   if (f.causal) {
     if (f.nseg == 1) {
@@ -785,7 +791,7 @@ int launch_fast_attention_backward(const FastLaunch& f, const TensorDev& dY, con
     return launch_fast_backward_whole(f, a, dY, dQ, dK, dV, gh, st);
   }
   if (int rc = launch_fast_state_pass(f, a, st, false, true)) return rc;
-  return launch_fast_backward(f, a, dY, dQ, dK, dV, gh, Rpart, rcpart, rslots, rows_per_rslot, st);
+  return launch_fast_backward(f, a, dY, dQ, dK, dV, gh, Rpart, rcpart, rslots, st);
 }
 
 }  // namespace fs

@@ -978,19 +978,24 @@ int launch_fast_backward_whole(const FastLaunch& f, const FastArgs& a, const Ten
 // One non-causal backward call after the forward state pass (f.Tpart slot 0 = total state, f.cstar = key shifts).
 int launch_fast_backward(const FastLaunch& f, const FastArgs& a, const TensorDev& dY, const TensorDev& dQ,
                          const TensorDev& dK, const TensorDev& dV, uint16_t* gh, float* Rpart, float* rcpart,
-                         int rslots, int rows_per_rslot, hipStream_t st) {
+                         int rslots, hipStream_t st) {
   BwdArgs ba;
   ba.f = a;
   ba.dY = dY; ba.dQ = dQ; ba.dK = dK; ba.dV = dV;
   ba.gh = gh; ba.Rpart = Rpart; ba.rcpart = rcpart;
-  ba.Lq = f.Lq; ba.Lk = f.Lk; ba.rslots = rslots; ba.rows_per_rslot = rows_per_rslot;
+  ba.Lq = f.Lq; ba.Lk = f.Lk;
   const int BH = f.B * f.H;
+  {       // the slots of R: cut like the forward states, within the planned ones
+    const int chunks = (f.Lq + TC - 1) / TC, want = rows::parts_per_sequence(BH, (chunks + 1) / 2, std::min(chunks, rslots), 2.f);
+    ba.rows_per_rslot = (chunks + want - 1) / want * TC;
+    ba.rslots = (f.Lq + ba.rows_per_rslot - 1) / ba.rows_per_rslot;
+  }
   // row tiles of 16 per wave: two where that leaves every wave of the chip a step; one workgroup per CU, whole steps each
   auto launch = [&](int side, int L) {
     const bool two = (long long)BH * ((L + 15) / 16) >= 2 * 2048;
     auto kernel = side ? (two ? k_bwd_rows<1, 2> : k_bwd_rows<1, 1>) : (two ? k_bwd_rows<0, 2> : k_bwd_rows<0, 1>);
     const int step = (two ? 32 : 16) * (NTR / 64) / 2;
-    const int want = std::max(1, std::min((256 + BH - 1) / BH, (L + step - 1) / step));
+    const int want = rows::parts_per_sequence(BH, (L + 2 * step - 1) / (2 * step), (L + step - 1) / step, 1.f);
     const int rows_per_blk = (((L + want - 1) / want) + step - 1) / step * step, nblk = (L + rows_per_blk - 1) / rows_per_blk;
     if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(SmemRows)) != hipSuccess) {
       (void)hipGetLastError();
@@ -1004,10 +1009,10 @@ int launch_fast_backward(const FastLaunch& f, const FastArgs& a, const TensorDev
     (void)hipGetLastError();
     return 2;
   }
-  if (rows_per_rslot > TC) hipLaunchKernelGGL(k_bwd_rstate2, dim3(rslots, BH), dim3(2 * NT), kState2Lds, st, ba);
-  else hipLaunchKernelGGL(k_bwd_rstate<true>, dim3(rslots, BH), dim3(NT), sizeof(SmemState), st, ba);
+  if (ba.rows_per_rslot > TC) hipLaunchKernelGGL(k_bwd_rstate2, dim3(ba.rslots, BH), dim3(2 * NT), kState2Lds, st, ba);
+  else hipLaunchKernelGGL(k_bwd_rstate<true>, dim3(ba.rslots, BH), dim3(NT), sizeof(SmemState), st, ba);
   FS_LAUNCH_CHECK();
-  launch_fast_total(Rpart, rcpart, nullptr, rslots, rslots, BH, nullptr, st);
+  launch_fast_total(Rpart, rcpart, nullptr, ba.rslots, ba.rslots, BH, nullptr, st);
   FS_LAUNCH_CHECK();
   if (int rc = launch(1, f.Lk)) return rc;
   return 0;
