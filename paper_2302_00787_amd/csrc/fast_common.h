@@ -95,12 +95,12 @@ __device__ __forceinline__ float absmax4(float m, f32x4 v) {
   return fmaxf(fmaxf(m, fabsf(v[2])), fabsf(v[3]));
 }
 
-// Largest of 256 floats (16-byte aligned), as a wave-uniform value.
-__device__ __forceinline__ float max256(const float* p) {
-  const f32x4 v = *(const f32x4*)(p + 4 * (threadIdx.x & 63));
+// Largest of 256 floats (16-byte aligned), as a wave-uniform value; lane l brings numbers 4 l .. 4 l + 3.
+__device__ __forceinline__ float max256(f32x4 v) {
   const float m = wave_max(fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])));
   return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, m)));
 }
+__device__ __forceinline__ float max256(const float* p) { return max256(*(const f32x4*)(p + 4 * (threadIdx.x & 63))); }
 
 // Per-token shift of the projection part W~_m . x of the exponent.  With cs = max_m |W~_m| |x| (Cauchy-Schwarz)
 // the projection never exceeds cs; random directions reach about 0.4 cs.  max(cs/2, cs - 120) keeps the largest

@@ -76,9 +76,9 @@ __device__ __forceinline__ void dma16(const DmaBase& d, uint32_t voff, const voi
 template <int N>
 __device__ __forceinline__ void dma_wait() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
 
-// Images of W~ (DMA) and the biases, for all threads of the workgroup; the caller waits and puts a barrier behind it.
+// Image of W~ (DMA), for all threads of the workgroup; the caller waits and puts a barrier behind it.
 template <int NTH>
-__device__ __forceinline__ void load_w_image(SmemOps& sm, const uint16_t* Wbf, const float* bias, float amax) {
+__device__ __forceinline__ void load_w_image(SmemOps& sm, const uint16_t* Wbf) {
   constexpr int NP = (M / 16) * KS * 64;
   const DmaBase src = dma_base(Wbf, M * D * 2);
 #pragma unroll
@@ -86,6 +86,11 @@ __device__ __forceinline__ void load_w_image(SmemOps& sm, const uint16_t* Wbf, c
     const int p = threadIdx.x + NTH * i, l = p & 63, ks = (p >> 6) % KS, ft = p / (64 * KS);
     dma16(src, 2 * ((16 * ft + (l & 15)) * D + 32 * ks + 8 * (l >> 4)), &sm.w[0][0][0][0] + 8 * (p & ~63));
   }
+}
+// The same and the biases.
+template <int NTH>
+__device__ __forceinline__ void load_w_image(SmemOps& sm, const uint16_t* Wbf, const float* bias, float amax) {
+  load_w_image<NTH>(sm, Wbf);
   if (threadIdx.x < M) sm.bias[threadIdx.x] = 2.f * (bias[threadIdx.x] - amax);
 }
 
@@ -255,10 +260,11 @@ __device__ __forceinline__ bool query_shifts(float (&add)[NTT], const bf16x8 (&x
 // Rows [row_beg, row_end) of the queries of one (b,h), taken by NWV waves in turn: Y = (P T) normalised by its last column.
 // Rows whose bounds are all at most `noshift` go without their shifts.
 // `buf`: the wave's LDS buffer of 16 NTT rows when the rows of the next step travel during this one's work (PREF; the
-// caller has issued dma_rows for the first step), else unused.  Returns the number of rows this wave finished with a
-// zero normaliser.
+// caller has issued dma_rows for the first step), else unused; `first`: else the operands of the first step, or nullptr.  Returns
+// the number of rows this wave finished with a zero normaliser.
 template <int NTT, int NWV, bool PREF>
-__device__ __forceinline__ int apply_rows(const FastArgs& a, const SmemOps& sm, uint16_t* buf, float wmax, float noshift, int bh, int row_beg, int row_end) {
+__device__ __forceinline__ int apply_rows(const FastArgs& a, const SmemOps& sm, uint16_t* buf, const bf16x8 (*first)[KS], float wmax,
+                                          float noshift, int bh, int row_beg, int row_end) {
   const int b = bh / a.H, h = bh % a.H;
   const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -275,6 +281,11 @@ __device__ __forceinline__ int apply_rows(const FastArgs& a, const SmemOps& sm, 
       read_rows(x, buf, lane);
       const int next = row0 + RT * NWV;
       if (next < row_end) dma_rows<NTT>(buf, Qb + (long long)next * a.Q.sl, a.Q.sl, row_end - next, lane);
+    } else if (first != nullptr && row0 == row_beg + RT * w) {
+#pragma unroll
+      for (int t = 0; t < NTT; ++t)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) x[t][ks] = first[t][ks];
     } else {
       load_row_ops(x, Qb + (long long)row0 * a.Q.sl, a.Q.sl, row_end - row0, lane);
     }

@@ -157,9 +157,9 @@ __device__ __forceinline__ void state_rows(const FastArgs& a, SmemState& sm, int
   // The second half of a chunk's state update is left for the next iteration, where its matrix instructions cover the
   // LDS reads behind the barrier; the exponentials of a token pair are interleaved with the matrix instructions beside
   // them (a wave issues in order: left to the compiler they came in runs of 32 and more).
-  // (Zero operands ahead of the first chunk: a test for it would make the compiler peel the loop, with registers for both.)
-  const bf16x8 zero8 = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
-  bf16x8 st1[4] = {zero8, zero8, zero8, zero8}, vop1[NVT] = {zero8, zero8, zero8, zero8, zero8};
+  // (The flag is opaque: the compiler would peel the first chunk off, with registers for both.)
+  bf16x8 st1[4], vop1[NVT];
+  int pending = 0;
   auto update1 = [&]() {
 #pragma unroll
     for (int vt = 0; vt < NVT; ++vt)
@@ -199,7 +199,9 @@ __device__ __forceinline__ void state_rows(const FastArgs& a, SmemState& sm, int
       }
       const bf16x8 xn0 = tile_op(knext, w, 0), xn1 = tile_op(knext, w, 1);     // token tile w of the next chunk
       __builtin_amdgcn_sched_barrier(0);
-      update1();
+      asm volatile("" : "+s"(pending));
+      if (pending) update1();
+      pending = 1;
       __builtin_amdgcn_sched_barrier(0);
       // ---- running key shift: the state is rebased when the chunk's largest bound exceeds the current shift
       if (!QUERIES && dnew > dk) {
@@ -260,7 +262,8 @@ __device__ __forceinline__ void state_rows(const FastArgs& a, SmemState& sm, int
     __syncthreads();
     const int t = kcur; kcur = knext; knext = kfree; kfree = t;
   }
-  if (!BOUND_ONLY) update1();
+  asm volatile("" : "+s"(pending));
+  if (!BOUND_ONLY && pending) update1();
 }
 
 // The state of the rows [row_beg, row_end) by two groups of four waves, whose states meet in LDS: one state per CU and launch goes

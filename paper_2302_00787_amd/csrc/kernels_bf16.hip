@@ -438,6 +438,7 @@ __global__ void __launch_bounds__(NTA) k_fast_apply(FastArgs a, int Lq, int rows
   const int id = rows::xcd_contiguous(blockIdx.x, gridDim.x), bh = id / nblk, blk = id - bh * nblk;
   const int pg = group_of(a.pgroups, bh / a.H, bh % a.H, a.H);
   const float wmax = max256(a.wnorm + ((size_t)pg * 2) * M), amax = max256(a.bias + ((size_t)pg * 2) * M);
+  const float noshift = rows::noshift_bound(rows::state_max(a.Tpart + (size_t)bh * a.nslot * M * DVP));
   const int row_beg = blk * rows_per_blk, row_end = min(Lq, row_beg + rows_per_blk);
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // everything the first step needs is requested at once
@@ -448,10 +449,9 @@ __global__ void __launch_bounds__(NTA) k_fast_apply(FastArgs a, int Lq, int rows
     rows::dma_rows<NTT>(buf, (const uint16_t*)a.Q.ptr + (bh / a.H) * a.Q.sb + (bh % a.H) * a.Q.sh + (long long)row0 * a.Q.sl, a.Q.sl,
                         row_end - row0, lane);
   rows::load_w_image<NTA>(sm, a.Wbf + ((size_t)pg * 2) * M * D, a.bias + ((size_t)pg * 2) * M, amax);
-  const float noshift = rows::noshift_bound(rows::state_max(a.Tpart + (size_t)bh * a.nslot * M * DVP));
   rows::dma_wait<0>();
   __syncthreads();
-  const int nzero = rows::apply_rows<NTT, NTA / 64, true>(a, sm, buf, wmax, noshift, bh, row_beg, row_end);
+  const int nzero = rows::apply_rows<NTT, NTA / 64, true>(a, sm, buf, nullptr, wmax, noshift, bh, row_beg, row_end);
   report_zero_rows(a.flushed, nzero, threadIdx.x & 63);
 }
 
@@ -476,10 +476,21 @@ __global__ void __launch_bounds__(NT, 2) k_fast_whole(FastArgs a, int Lq) {
   const int pg = group_of(a.pgroups, bh / a.H, bh % a.H, a.H);
   SmemWhole& whole = *reinterpret_cast<SmemWhole*>(smem_raw);
   rows::SmemOps& sm = whole.q;
+  constexpr bool FIRST = NTT <= 2;     // (the rows of the first step wait in registers, where there are enough of them)
+  bf16x8 x[NTT][KS];
+  float wmax;
   {
     f32x4 T[4][NVT];
     float dk;
     state_rows(a, whole.s, bh, 0, a.L, chunks_of(a.L), T, dk);
+    // what the queries start from is requested before the state goes to LDS
+    const float *wnorm = a.wnorm + ((size_t)pg * 2) * M, *bias = a.bias + ((size_t)pg * 2) * M;
+    const f32x4 wn = *(const f32x4*)(wnorm + 4 * lane), bs = *(const f32x4*)(bias + 4 * lane);
+    const float mine = bias[threadIdx.x];
+    static_assert(NT == M, "a bias per thread");
+    const int row0 = __builtin_amdgcn_readfirstlane(16 * NTT * w);
+    if (FIRST) rows::load_row_ops(x, (const uint16_t*)a.Q.ptr + (bh / a.H) * a.Q.sb + (bh % a.H) * a.Q.sh + (long long)row0 * a.Q.sl, a.Q.sl, Lq - row0, lane);
+    __builtin_amdgcn_sched_barrier(0);
     rows::put_t_image(sm, T, w, lane);
     float m[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -488,16 +499,17 @@ __global__ void __launch_bounds__(NT, 2) k_fast_whole(FastArgs a, int Lq) {
       for (int vt = 0; vt < NVT; ++vt) m[mt] = absmax4(m[mt], T[mt][vt]);
     const float m16 = max16(fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3])));
     if ((lane & 15) == 0) whole.tmax[threadIdx.x >> 4] = m16;
+    wmax = max256(wn);
+    sm.bias[threadIdx.x] = 2.f * (mine - max256(bs));
   }
-  const float wmax = max256(a.wnorm + ((size_t)pg * 2) * M), amax = max256(a.bias + ((size_t)pg * 2) * M);
-  rows::load_w_image<NT>(sm, a.Wbf + ((size_t)pg * 2) * M * D, a.bias + ((size_t)pg * 2) * M, amax);
+  rows::load_w_image<NT>(sm, a.Wbf + ((size_t)pg * 2) * M * D);
   rows::dma_wait<0>();
   __syncthreads();
   float tmax = 0.f;
 #pragma unroll
   for (int i = 0; i < NT / 16; i += 4) tmax = absmax4(tmax, *(const f32x4*)(&whole.tmax[i]));
   const float noshift = rows::noshift_bound(tmax);
-  const int nzero = rows::apply_rows<NTT, NT / 64, false>(a, sm, nullptr, wmax, noshift, bh, 0, Lq);
+  const int nzero = rows::apply_rows<NTT, NT / 64, false>(a, sm, nullptr, FIRST ? x : nullptr, wmax, noshift, bh, 0, Lq);
   report_zero_rows(a.flushed, nzero, lane);
 }
 
@@ -735,8 +747,9 @@ int launch_fast_attention(const FastLaunch& f, hipStream_t st, hipEvent_t ev_beg
     static_assert(2 * sizeof(SmemWhole) <= 160 * 1024, "k_fast_whole: two workgroups per CU");
     if (int rc = launch_fast_constants(f, a, st, false)) return rc;
     if (int rc = clear_counter(f, st)) return rc;
-    // four waves: two row tiles each as long as one step takes the whole sequence, else four
-    auto kernel = f.Lq <= 128 ? k_fast_whole<2> : k_fast_whole<4>;
+    // four waves: one row tile each, or two, as long as one step takes the whole sequence, else four (600 x 64 tokens: one 19.9
+    // us, two 21.7)
+    auto kernel = f.Lq <= 64 ? k_fast_whole<1> : f.Lq <= 128 ? k_fast_whole<2> : k_fast_whole<4>;
     if (int rc = allow_lds((const void*)kernel, sizeof(SmemWhole))) return rc;
     if (ev_begin || ev_end) hipExtLaunchKernelGGL(kernel, dim3(BH), dim3(NT), sizeof(SmemWhole), st, ev_begin, ev_end, 0, a, f.Lq);
     else hipLaunchKernelGGL(kernel, dim3(BH), dim3(NT), sizeof(SmemWhole), st, a, f.Lq);
