@@ -621,7 +621,8 @@ void plan_backward(int BH, int pgroups, int Lq, int Lk, int d, int dv, int M, in
   p->off_den = off;    off = align_up(off + (size_t)BH * Lq * sizeof(float));
   p->off_shift = off;  off = align_up(off + (size_t)BH * Lq * sizeof(float));
   p->off_rstate = off; off = align_up(off + (size_t)BH * p->q.nseg * M * p->k.ldt * sizeof(float));
-  p->off_state2 = off; off = align_up(off + (causal ? (size_t)BH * p->k.nseg * M * p->k.ldt * sizeof(float) : 0));
+  // the kernels with the state in memory need the prefix states twice
+  p->off_state2 = off; off = align_up(off + (causal && !p->walks ? (size_t)BH * p->k.nseg * M * p->k.ldt * sizeof(float) : 0));
   p->total = off;
 }
 }  // namespace

@@ -53,6 +53,18 @@ def test_host_only_queries(lib):
     assert lib.favorsharp_fit_workspace_bytes(4, 8, 16384, 16384, 64, 8) > 0
 
 
+def test_causal_backward_workspace_holds_a_second_copy_of_the_states_only_where_it_is_used(lib):
+    """The kernels that walk with the state in registers leave the prefix states alone; the others advance a copy."""
+    def size(M):
+        return lib.favorsharp_attention_backward_workspace_bytes(1, 16, 4096, 4096, 128, 128, M, 1, 1, 1)
+    def states(M):
+        return 16 * (4096 // 128) * M * 144 * 4        # segments of 128 rows, rows of 129 values padded to 144
+    rows = 16 * 4096 * (144 + 3) * 4                   # G1, normalisers, shifts, key row terms
+    slack = 2 * 2 * 516 * 129 * 4 + (1 << 16)          # projection matrices, biases, partial key maxima, alignment
+    assert size(512) <= 2 * states(512) + rows + slack
+    assert 3 * states(516) + rows <= size(516) <= 3 * states(516) + rows + slack
+
+
 def test_argument_errors_are_reported_before_any_device_work(lib):
     from paper_2302_00787_amd.binding import FsTensor
     t = FsTensor(None, 0, 0, 0, 64)
