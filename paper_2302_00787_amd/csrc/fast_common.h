@@ -222,18 +222,6 @@ __device__ __forceinline__ void store_rows_s(const RowRegs& r, uint16_t (*tile)[
   }
 }
 
-template <class S>
-__device__ __forceinline__ void store_query_rows(const RowRegs& r, S& sm, int buf, float wmax) {
-  float n2[2];
-  store_rows_s(r, sm.q[buf], n2);
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int q = threadIdx.x + NT * i;
-    if ((q & 7) == 0) sm.qadd[buf][q >> 3] = -row_shift(n2[i], wmax);
-  }
-}
-
-
 // Values: lane pairs (2t, 2t+1) exchange halves so that each lane writes whole dwords {token 2t, token 2t+1} of one
 // column: thread -> token tid%64, 16-byte pieces tid/64 and tid/64 + 4 of that token's row.
 __device__ __forceinline__ void load_vals_g(RowRegs& r, const uint16_t* base, long long sl, int row0, int row_end) {

@@ -28,8 +28,7 @@ struct GenSide {
   int pgroups;          // number of projection-constant sets
   long long theta_stride;
   long long c_offset;   // offset of this side's C matrix inside a parameter set
-  float* rk = nullptr;  // [B*H][rows] row terms of this side's rows (written by k_gen_kmax, read by the kernels after
-                        // it instead of evaluating the quadratic form once per feature block); nullptr: none
+  float* rk = nullptr;  // key side: [B*H][rows] row terms of its rows, written by k_gen_kmax and read by the kernels after it
   float* kpart = nullptr; // room for kcap partial key maxima (k_gen_kmax leaves them, k_gen_state finds the maximum)
   size_t kcap = 0;
 };

@@ -202,8 +202,8 @@ __device__ __forceinline__ float sym_row_dot(const float* Cmat, int d, int c, co
   return (t0 + t1) + (t2 + t3);
 }
 
-// rterm[r] = log2e * (x_r^T C x_r + alpha |x_r|^2), -inf for r >= live; Cmat == nullptr means C = -I/2.
-__device__ void row_terms(float* rterm, const float* Xs, int ld, int d, const float* Cmat, float alpha, int live = TR) {
+// rterm[r] = log2e * (x_r^T C x_r + alpha |x_r|^2); Cmat == nullptr means C = -I/2.
+__device__ void row_terms(float* rterm, const float* Xs, int ld, int d, const float* Cmat, float alpha) {
   if (threadIdx.x >= 8 * TR) return;         // eight threads a row
   const int r = threadIdx.x >> 3, part = threadIdx.x & 7;
   const float* x = Xs + r * ld;
@@ -231,19 +231,14 @@ __device__ void row_terms(float* rterm, const float* Xs, int ld, int d, const fl
   acc += __shfl_xor(acc, 1);
   acc += __shfl_xor(acc, 2);
   acc += __shfl_xor(acc, 4);
-  if (part == 0) rterm[r] = r < live ? kLog2e * acc : -INFINITY;
+  if (part == 0) rterm[r] = kLog2e * acc;
 }
 
-// Row terms of the 32-row tile at row0 of (b,h): from the side's table when the call keeps one, else computed.  Rows of
-// padding get -inf, so that their features are exactly zero: with 0 the exponent of a feature is its bias less the
-// sequence's key shift, which overflows where all keys are long.
-__device__ void row_terms_of(float* rterm, const GenSide& sd, int bh, int L, int row0, int row_end, const float* Xs,
-                             int ld, int d, const float* Cmat, float alpha) {
-  if (sd.rk != nullptr) {
-    if (threadIdx.x < TR) rterm[threadIdx.x] = row0 + (int)threadIdx.x < row_end ? sd.rk[(size_t)bh * L + row0 + threadIdx.x] : -INFINITY;
-  } else {
-    row_terms(rterm, Xs, ld, d, Cmat, alpha, row_end - row0);
-  }
+// Row terms of the 32-row tile at row0 of (b,h), as k_gen_kmax left them.  Rows of padding get -inf, so that their features
+// are exactly zero: with 0 the exponent of a feature is its bias less the sequence's key shift, which overflows where all
+// keys are long.
+__device__ __forceinline__ void row_terms_of(float* rterm, const GenSide& sd, int bh, int L, int row0, int row_end) {
+  if (threadIdx.x < TR) rterm[threadIdx.x] = row0 + (int)threadIdx.x < row_end ? sd.rk[(size_t)bh * L + row0 + threadIdx.x] : -INFINITY;
 }
 
 // Wave w (of four) computes the 16x16 tile (row tile w>>1, feature tile w&1) of Xs * Ws^T.
@@ -621,7 +616,6 @@ __global__ void __launch_bounds__(NTC, WD == 1 ? 4 : 2) k_gen_causal(GenSide qs,
   const float* bias1 = qs.bias + ((size_t)pgq * 2) * M;
   const float* W2 = ks.W + ((size_t)pgq * 2 + 1) * M * d;
   const float* bias2 = ks.bias + ((size_t)pgq * 2 + 1) * M;
-  const float* Cmat2 = side_cmat(ks, b, h, H);
   const float c = ordered_to_float(kmax_u[bh]);
   float* Tg = Tstate + ((size_t)bh * nseg + seg) * M * ldt;
   const int nvt = ldt / 16, ntiles = 2 * nvt;
@@ -634,7 +628,7 @@ __global__ void __launch_bounds__(NTC, WD == 1 ? 4 : 2) k_gen_causal(GenSide qs,
     load_rows<WD, NTC>(Ks, ld, ks.X, kbase, row0, row_end, d, dpad, ks.scale);
     load_values<WD, NTC>(Vs, ldv, V, b * V.sb + h * V.sh, row0, row_end, nv, ldt, 1);
     __syncthreads();
-    row_terms_of(rterm, ks, bh, L, row0, row_end, Ks, ld, d, Cmat2, 0.f);
+    row_terms_of(rterm, ks, bh, L, row0, row_end);
     rowmax_pass2<WD>(rowmax_u, Qs, Ws, Ws2, bias_s, bias2_s, ld, W1, bias1, M, d, dpad);
 
     f32x4 acc[ACC_V<WD, 8>];
@@ -893,7 +887,7 @@ __global__ void __launch_bounds__(NT) k_gen_bwd_side(GenSide sd, int side, Tenso
   load_values<WD>(As, ldts, A, b * A.sb + h * A.sh, row0, L, a_cols, ldt, append_ones);
   __syncthreads();
   if (side == 1) {
-    row_terms_of(rterm, sd, bh, L, row0, L, Xs, ld, d, Cmat, sd.alpha);
+    row_terms_of(rterm, sd, bh, L, row0, L);
     __syncthreads();
     if (threadIdx.x < TR) rterm[threadIdx.x] -= ordered_to_float(kmax_u[bh]);
   } else if (threadIdx.x < TR) {
@@ -1104,7 +1098,6 @@ __global__ void __launch_bounds__(NTC) k_gen_bwd_causal_q(GenSide qs, GenSide ks
   const float* W2 = ks.W + ((size_t)pg * 2 + 1) * M * d;
   const float* bias2 = ks.bias + ((size_t)pg * 2 + 1) * M;
   const float* Cmat1 = side_cmat(qs, b, h, H);
-  const float* Cmat2 = side_cmat(ks, b, h, H);
   const float c = ordered_to_float(kmax_u[bh]);
   float* Tg = Tstate + ((size_t)bh * nseg + seg) * M * ldt;
   const TensorDev G{ghat, 0, (long long)H * L * ldt, (long long)L * ldt, (long long)ldt};
@@ -1120,7 +1113,7 @@ __global__ void __launch_bounds__(NTC) k_gen_bwd_causal_q(GenSide qs, GenSide ks
     load_values<WD, NTC>(m.Gs, ldv, G, b * G.sb + h * G.sh, row0, row_end, ldt, ldt, 0);
     if (threadIdx.x < TR) m.qsh[threadIdx.x] = row0 + threadIdx.x < row_end ? -row_shift[(size_t)bh * L + row0 + threadIdx.x] : 0.f;
     __syncthreads();
-    row_terms_of(m.rterm, ks, bh, L, row0, row_end, m.Ks, ld, d, Cmat2, 0.f);
+    row_terms_of(m.rterm, ks, bh, L, row0, row_end);
     bwd_causal_amat(m.As, m.Gs, m.Vs, ldv, lds, ldt);
 
     f32x4 acc_g[ACC_D<WD, 8>];
@@ -1268,7 +1261,7 @@ __global__ void __launch_bounds__(NTC) k_gen_bwd_causal_k(GenSide qs, GenSide ks
     load_values<WD, NTC>(m.Gs, ldv, G, b * G.sb + h * G.sh, row0, row_end, ldt, ldt, 0);
     if (threadIdx.x < TR) m.qsh[threadIdx.x] = row0 + threadIdx.x < row_end ? -row_shift[(size_t)bh * L + row0 + threadIdx.x] : 0.f;
     __syncthreads();
-    row_terms_of(m.rterm, ks, bh, L, row0, row_end, m.Ks, ld, d, Cmat2, 0.f);
+    row_terms_of(m.rterm, ks, bh, L, row0, row_end);
     bwd_causal_amat(m.As, m.Gs, m.Vs, ldv, lds, ldt);
 
     f32x4 acc_o[ACC_V<WD, 8>], acc_g[ACC_D<WD, 8>];
