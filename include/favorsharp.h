@@ -23,7 +23,9 @@
  *     default stream).  favorsharp_fit_params additionally waits for the
  *     stream (its d x d closed form runs on the host in fp64); the others
  *     return as soon as their kernels are enqueued;
- *   - outputs are fully overwritten, inputs are never modified; the workspace
+ *   - outputs are fully overwritten, inputs are never modified; no output may overlap
+ *     an input, another output or the workspace (an input may be read again after
+ *     rows of an output have been written: dQ over Q, say, is not supported); the workspace
  *     content is undefined afterwards; calls that share a workspace must be
  *     ordered by the caller; there is no global mutable state apart from
  *     favorsharp_attention_noalloc's scratch array;
