@@ -4,23 +4,22 @@
 // Lane l = (g, c) = (l / 16, l % 16) supplies A[i = c][k = g] and B[k = g][j = c] and owns D[i = 4 g + r][j = c] in register
 // r.  The order of the contraction index is free as long as both operands agree, and with k = g of step r standing for
 // index 4 g + r an accumulator register IS an operand: features (rows = tokens, columns = features) feed the state update
-// as they come from exp2, and so on.  Rows of 16 q + 4 g .. + 3 of a tensor are one 16-byte load per lane and four steps.  What
-// is left beside the matrix instructions (32 cycles each, 2048 flops) is a few per cent: these kernels are bound by the fp32
-// matrix rate.
+// as they come from exp2, and so on.  Rows of 16 q + 4 g .. + 3 of a tensor are one 16-byte load per lane and four steps.
+// The matrix pipe (32 cycles an instruction, 2048 flops) is busy 52 % of the SIMD time in k_gen_kmax and 38 % in k_gen_state at d = 128,
+// M = 512: the rest is waiting for rows (half of a state wave's cycles: every wave fetches rows and values for itself) and the
+// exponentials.
 #include <type_traits>
 
-#include "fs_common.h"
+#include "gen_widths.h"
 #include "kernels.h"
 
 namespace fs {
 namespace {
 
-__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+using namespace gen;
 
-// Five widths: rows of at most 16 Q numbers, values of at most 16 VT columns.  Nothing in a kernel depends on the sizes within
-// a width (a uniform branch around a load is a wait for it: state of B2 H4 L4096 d64 M256 68 us with, 37 without): what lies past a row
-// or a value row is multiplied by zero.
-template <int Q> constexpr int VT_OF = Q == 1 ? 2 : Q == 2 ? 3 : Q == 4 ? 5 : Q == 6 ? 7 : 9;
+// Nothing in a kernel depends on the sizes within a width (a uniform branch around a load is a wait for it: state of B2 H4
+// L4096 d64 M256 68 us with, 37 without): what lies past a row or a value row is multiplied by zero.
 
 // BF: storage of a tensor.
 template <int BF>
@@ -84,9 +83,10 @@ __device__ __forceinline__ f32x4 lane_rows_transposed(f32x4 v) {
 // Key-side maximum of the exponent per (b, h), max_{j,m} E2[j,m]: one partial maximum per workgroup, part[bh][block], or
 // where there is no room for them an atomic maximum into kmax[bh] (ordered-uint image; atomics of many workgroups on one
 // address queue up in memory, 15 ns each: 38 us of a 188 us call with one per wave); and the row terms of the keys (rk). A
-// workgroup takes four (wide rows: two) tiles of 16 tokens, which every wave holds as operands: it takes every fourth group
-// of coordinates through C for the row terms (each tile's terms by one wave, C in single words: causal f32 B8 H8 L300 d128
-// M200 dense 378 -> 258 us for the call), then every fourth tile of 16 features. grid (tokens, B*H), block 256.
+// workgroup takes four (wide rows: two) tiles of 16 tokens, which every wave holds as operands.  Row terms: of an isotropic
+// set a tile per wave; of a dense one every wave takes every fourth group of sixteen coordinates of all the tiles through C, as
+// groups of four numbers, and the waves' parts are summed in LDS (each tile's terms by one wave, C in single words: causal f32
+// B8 H8 L300 d128 M200 378 us for the call, now 258).  Then every fourth tile of 16 features.  grid (tokens, B*H), block 256.
 // ---------------------------------------------------------------------------------------------------
 template <int Q> constexpr int KMAX_T = Q >= 6 ? 2 : 4;      // token tiles per workgroup
 template <int Q, int XB, int D4>
@@ -353,18 +353,10 @@ __global__ void __launch_bounds__(256, 2) k_gen_state(GenSide ks, TensorDev V, i
 
 #define FS_LAUNCH_CHECK() do { if (hipGetLastError() != hipSuccess) return 5; } while (0)
 
-template <class F>
-int by_width(int d, int ldt, F launch) {
-  if (d <= 16 && ldt <= 32) return launch(std::integral_constant<int, 1>());
-  if (d <= 32 && ldt <= 48) return launch(std::integral_constant<int, 2>());
-  if (d <= 64 && ldt <= 80) return launch(std::integral_constant<int, 4>());
-  if (d <= 96 && ldt <= 112) return launch(std::integral_constant<int, 6>());
-  return launch(std::integral_constant<int, 8>());
-}
-
 }  // namespace
 
-// Rows of a workgroup of k_gen_kmax, and its partial maxima where they fit.
+// Rows of a workgroup of k_gen_kmax, and its partial maxima where they fit.  (The room is that of one side's projection matrices:
+// with room for every call some workspaces would pass the fixed size of the scratch array that serves calls without one.)
 static int kmax_rows(int d) {
   return by_width(d, 0, [](auto q) { return 16 * KMAX_T<q()>; });
 }

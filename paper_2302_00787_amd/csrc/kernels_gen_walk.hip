@@ -11,14 +11,14 @@
 // pass bf16 B1 H16 L4096 d128 M512: 3300 -> 2560 us for its four.
 #include <type_traits>
 
-#include "fs_common.h"
+#include "gen_widths.h"
 #include "kernels.h"
 
 namespace fs {
 namespace {
 
-__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-template <int Q> constexpr int VT_OF = Q == 1 ? 2 : Q == 2 ? 3 : Q == 4 ? 5 : Q == 6 ? 7 : 9;
+using namespace gen;
+
 constexpr int TT = 16;                                   // tokens per chunk
 template <int Q> constexpr int LDX = 16 * Q + 4;         // strides of LDS rows: 16-byte reads of a column group and 4-byte
 template <int Q> constexpr int LDV = 16 * VT_OF<Q> + 4;  // reads of four rows 4 apart touch every bank once
@@ -550,14 +550,6 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_gen_gwalk(WalkArgs
   }
 }
 
-template <class F>
-int by_width(int d, int ldt, F launch) {
-  if (d <= 16 && ldt <= 32) return launch(std::integral_constant<int, 1>());
-  if (d <= 32 && ldt <= 48) return launch(std::integral_constant<int, 2>());
-  if (d <= 64 && ldt <= 80) return launch(std::integral_constant<int, 4>());
-  if (d <= 96 && ldt <= 112) return launch(std::integral_constant<int, 6>());
-  return launch(std::integral_constant<int, 8>());
-}
 // Features per wave and waves: two waves per SIMD where there are tiles for them (one's loads and exponentials beside the
 // other's matrix instructions: B2 H4 L4096 d64 M256 156 us against 168 with four waves of 64 features).
 template <class F>
