@@ -544,7 +544,8 @@ void fast_plan(int BH, int L, int* nseg, int* rows_per_seg, int* sub) {
   int want = std::max(1, std::min((256 + BH - 1) / BH, (L + TC - 1) / TC));
   *rows_per_seg = (((L + want - 1) / want) + TC - 1) / TC * TC;
   *nseg = (L + *rows_per_seg - 1) / *rows_per_seg;
-  // the key-side kernel runs two workgroups per CU: give it half-segments when they are whole chunks
+  // half segments, where they are whole chunks, for the causal gradients, whose walks run two workgroups per CU (other calls
+  // size their workspace with them)
   *sub = (*rows_per_seg % (2 * TC) == 0) ? 2 : 1;
 }
 

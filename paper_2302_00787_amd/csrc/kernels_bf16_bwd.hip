@@ -30,7 +30,8 @@ using namespace fast;
 namespace bwd {
 
 // ---------------------------------------------------------------------------------------------------------------
-// MODE 1 (queries): rows of G1.  MODE 2 (keys): dV = S R.  Structure of k_fast_apply.  grid (nblk, B*H).
+// Loops of k_bwd_whole.  A wave has 64 of the features for all rows of a chunk; the waves' partial tiles are summed through LDS.
+// MODE 1 (queries): rows of G1.  MODE 2 (keys): dV = S R.
 // ---------------------------------------------------------------------------------------------------------------
 // Rows [row_beg, row_end) of one (b,h) against the state image tb (state^T as A operand: row v = 16 vt + c, k <->
 // features 64w + 32 mb + 16 (e/4) + 4g + e%4); cs: the key shift of the sequence (MODE 2).  Returns the number of
@@ -199,7 +200,7 @@ __global__ void __launch_bounds__(2 * NT) k_bwd_rstate2(BwdArgs ba) {
 // state = R).  Per 16-token tile: F (feature tile), dF = state x (left rows)^T in the same accumulator layout
 // (rows = features, column = token), dE = F * dF, gradient tile = W~^T (A operand: rows = coordinates, k <->
 // features; a row of ones appended: row sum of dE) x dE.  The four waves' partial gradient tiles are summed through
-// LDS on the MFMA pipe.  grid (nblk, B*H); 74 kB of dynamic LDS: two workgroups per CU.
+// LDS on the MFMA pipe.  (Another loop of k_bwd_whole.)
 // ---------------------------------------------------------------------------------------------------------------
 struct SmemGrad {
   __attribute__((aligned(16))) uint16_t q[1][TC][LDR];            // rows of the chunk (one buffer)
@@ -858,16 +859,16 @@ __device__ __forceinline__ void rstate_rows(const BwdArgs& ba, Smem& sm, int bh,
 
 // ---------------------------------------------------------------------------------------------------------------
 // The whole backward pass of one (b,h) in one workgroup (non-causal calls with many or short sequences): the states T
-// and R never leave the workgroup.  In the kernels above each of them goes to memory once per slot, through a
-// reduction, and back twice, 80 kB a time, while a sequence of 128 tokens is 150 kB of rows altogether.  Phases, each
-// the loop of one of the kernels above over all rows of the sequence:
+// and R never leave the workgroup.  In the separate kernels each of them goes to memory once per slot, through a
+// reduction, and back, 80 kB a time, while a sequence of 128 tokens is 150 kB of rows altogether.  Phases, each a loop
+// over all rows of the sequence:
 //   keys:    T = S^T [V 1]                (state_rows)
 //   queries: G1 rows -> gh                (apply_rows_b<1>, T as operand image)
 //   queries: dQ                           (grad_rows<0>; T's image turned into the row operand through LDS)
 //   queries: R = P^T G1                   (rstate_rows; gh read back: written by this workgroup, behind a barrier)
 //   keys:    dV = S R                     (apply_rows_b<2>)
 //   keys:    dK                           (grad_rows<1>)
-// T is dead before R is built, so no phase holds more than its kernel does.  grid (B*H), block 256, two per CU.
+// T is dead before R is built.  grid (B*H), block 256, two per CU.
 // ---------------------------------------------------------------------------------------------------------------
 union SmemBwdWhole {
   SmemState s;

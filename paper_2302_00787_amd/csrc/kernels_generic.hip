@@ -1,7 +1,7 @@
 // General-shape FAVOR# kernels: fp32 arithmetic on fp32 MFMA tiles (v_mfma_f32_16x16x4_f32), any d <= 128,
 // any M, any sequence length, f32 or bf16 storage.  They serve the fp32 workloads and every shape the
-// bf16 fast path does not cover; key maxima and states are in kernels_gen_rows.hip, the causal kernels for d and dv
-// multiples of four and M <= 512 in kernels_gen_walk.hip.  All exponents are kept in the log2 domain: the projection matrices and
+// bf16 fast path does not cover; key maxima and states are in kernels_gen_rows.hip, the causal kernels of most shapes with d
+// and dv multiples of four and M <= 512 in kernels_gen_walk.hip (its gen_walk_attention and gen_walk_backward say which).  All exponents are kept in the log2 domain: the projection matrices and
 // biases arrive pre-multiplied by log2(e), so a feature is exp2(E2 - shift).
 //
 // Tile shape everywhere: 32 rows (tokens) x 32 features per step, 256 threads = 4 waves.
