@@ -183,7 +183,7 @@ int launch_key_row_terms(const float* theta, int groups, const TensorDev& K, int
 
 // Key-side state of one slot (fast_state.h: state_rows), written to Tpart with its shift in cpart.  grid (nslot, B*H),
 // block 256, two workgroups per CU: the slots of the causal backward pass, which needs the state of every half segment, and
-// segments of one chunk.
+// segments of at most six chunks.
 __global__ void __launch_bounds__(NT, 2) k_fast_state(FastArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int slot = blockIdx.x, bh = blockIdx.y;
@@ -661,8 +661,9 @@ static int launch_fast_state_pass(const FastLaunch& f, FastArgs& a, hipStream_t 
   // the last segment's states are never needed by the causal pass
   const int nstate = (f.causal && !every_slot ? a.nseg - 1 : a.nseg) * sub;
   if (nstate > 0) {
-    // two groups of waves need two chunks (sequences in segments of one: 1 x 4096 25.4 us with one group, 27.9 with two)
-    if (every_slot || a.rows_per_seg <= TC) {
+    // two groups of waves bring their states together through LDS: worth it from seven chunks a segment on.  Time of a call with
+    // two over one, by chunks: causal 2 1.034, 3 1.027, 4 1.014, 5 1.015, 6 1.002; non-causal 1.034, 1.047, 1.018, 1.025, 1.007
+    if (every_slot || a.rows_per_seg <= 6 * TC) {
       hipLaunchKernelGGL(k_fast_state, dim3(nstate, BH), dim3(NT), sizeof(SmemState), st, a);
     } else {
       if (int rc = allow_lds((const void*)k_fast_state2, kState2Lds)) return rc;

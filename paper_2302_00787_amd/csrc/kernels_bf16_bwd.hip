@@ -156,7 +156,7 @@ __device__ __forceinline__ int apply_rows_b(const BwdArgs& ba, SmemApply& sm, in
 
 // ---------------------------------------------------------------------------------------------------------------
 // Segment sums of P^T G1 (state_rows on the query side: features with their per-row shifts, "values" = rows of G1).
-// k_bwd_rstate: rows of a state per slot for the causal kernels, or (IMG) accumulator images for slots of one chunk.  grid
+// k_bwd_rstate: rows of a state per slot for the causal kernels, or (IMG) accumulator images for slots of few chunks.  grid
 // (rslots, B*H), block 256.
 // k_bwd_rstate2: two groups of waves per slot, accumulator images (k_fast_total sums them).  grid (rslots, B*H), block 512.
 // ---------------------------------------------------------------------------------------------------------------
@@ -1010,7 +1010,8 @@ int launch_fast_backward(const FastLaunch& f, const FastArgs& a, const TensorDev
     (void)hipGetLastError();
     return 2;
   }
-  if (ba.rows_per_rslot > TC) hipLaunchKernelGGL(k_bwd_rstate2, dim3(ba.rslots, BH), dim3(2 * NT), kState2Lds, st, ba);
+  // (time of a call with two groups over one: 1.02 at three chunks a slot, 1.00 at four)
+  if (ba.rows_per_rslot > 4 * TC) hipLaunchKernelGGL(k_bwd_rstate2, dim3(ba.rslots, BH), dim3(2 * NT), kState2Lds, st, ba);
   else hipLaunchKernelGGL(k_bwd_rstate<true>, dim3(ba.rslots, BH), dim3(NT), sizeof(SmemState), st, ba);
   FS_LAUNCH_CHECK();
   launch_fast_total(Rpart, rcpart, nullptr, ba.rslots, ba.rslots, BH, nullptr, st);

@@ -261,6 +261,7 @@ def test_backward_bf16_path_whole_sequences_per_workgroup(fs, variant, B, H, Lq,
 @pytest.mark.parametrize("H,Lq,Lk,f32", [(1, 1, 400, False), (3, 15, 700, True), (20, 129, 1000, False), (2, 2049, 1039, False),   # one row tile per wave
                                          (33, 1999, 130, False), (70, 100, 1121, True), (65, 1041, 1025, False),                # two: queries, keys, both
                                          (50, 1100, 1030, False), (104, 515, 520, False), (150, 3990, 3970, False),   # 2 or 5 parts in one pass, 3 in two
+                                         (64, 1000, 1500, False), (64, 1200, 1700, False),              # slots of 4 and of 5 chunks of queries, 6 and 7 of keys
                                          (385, 800, 780, False)])                                                               # longest whole, then rows
 def test_backward_bf16_path_row_tiles(fs, variant, H, Lq, Lk, f32):
     """The row-split gradient kernels in each of their row-tile widths, with remainders of tiles, steps and workgroups.

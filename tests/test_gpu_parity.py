@@ -759,6 +759,7 @@ def test_bf16_path_non_causal_whole_sequences_per_workgroup(fs, variant, B, H, L
                                      (33, 1999, 130), (70, 1121, 1030),                                          # two
                                      (130, 1037, 193), (40, 4099, 100),                                          # four
                                      (50, 1100, 1030), (104, 515, 520), (150, 3990, 3970),          # 2 or 5 parts in one pass, 3 in two
+                                     (64, 1000, 1500), (64, 1200, 1700),                            # slots of 6 and of 7 chunks
                                      (385, 128, 31), (385, 129, 70), (388, 1, 1)])                               # whole sequences
 def test_bf16_path_non_causal_row_tiles(fs, H, Lq, Lk):
     """The query side in each of its row-tile widths, with remainders of tiles, steps and workgroups; a few query rows
