@@ -26,7 +26,7 @@ using namespace fast;
 // two, three or four passes over the chip, whichever takes the fewest steps (the last pass takes as long as a full one;
 // `fixed`: steps' worth of a workgroup's constants, images and results; at most `most` parts).  One workgroup per CU
 // rounded up instead leaves a second pass nearly empty: non-causal calls (us) 48 x 1024 44.2 -> 31.0, 24 x 2048 43.8 -> 31.2,
-// 12 x 4096 45.9 -> 32.5; gradients 48 x 1024 111.6 -> 71.5, 24 x 2048 103.4 -> 71.8.
+// 12 x 4096 45.9 -> 32.5; gradients 48 x 1024 111.7 -> 69.8, 24 x 2048 103.4 -> 71.8.
 inline int parts_per_sequence(int BH, int units, int most, float fixed) {
   int best = 1;
   float least = 1e30f;
