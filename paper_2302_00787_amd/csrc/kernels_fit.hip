@@ -208,9 +208,9 @@ __device__ __forceinline__ void decompose_columns(double* g, int n, int k, FitSh
 // Symmetric eigenproblem by reduction to tridiagonal form, one workgroup, everything in fp64.
 //
 // What bounds it is latency (one workgroup per matrix, a few matrices per call), so the design counts dependent steps:
-// the reduction has two barriers per column against two barriers per rotation round of a Jacobi iteration, which
+// the reduction has one barrier per column against two barriers per rotation round of a Jacobi iteration, which
 // needs (n - 1) x 6 - 8 rounds; everything after the reduction has no barrier per step at all.  Measured against a
-// two-sided Jacobi iteration (8 matrices of 64: k_fit_device 686 -> 107 us; 16 matrices of 128: 7290 -> 319 us).
+// two-sided Jacobi iteration (8 matrices of 64: k_fit_device 686 -> 89 us; 16 matrices of 128: 7290 -> 313 us).
 // ---------------------------------------------------------------------------------------------------
 
 // Gap between neighbouring eigenvalues (in units of the norm) below which vectors from twisted factorisations are not
@@ -261,6 +261,15 @@ __device__ __forceinline__ double sum64(double v) {        // over the wave
   v += dpp64<kMirror16>(v);
   v = add_rows16(v, v);
   return add_halves32(v, v);
+}
+// The same through the matrix pipe: lane 16 k + 4 b + i of the first factor is entry (i, k) of block b, so that a product with ones is
+// the sum over the rows of lanes and a second one that over groups of four.  (Six steps of lane swaps and adds, each waiting
+// for the last, are 240 cycles.)
+__device__ __forceinline__ double wave_sum(double v) {
+  v = __builtin_amdgcn_mfma_f64_4x4x4f64(v, 1.0, 0.0, 0, 0, 0);
+  v = __builtin_amdgcn_mfma_f64_4x4x4f64(v, 1.0, 0.0, 0, 0, 0);
+  v += dpp64<kMirror8>(v);
+  return v + dpp64<kMirror16>(v);
 }
 __device__ __forceinline__ double max64(double v) {        // over the wave
   v = fmax(v, dpp64<kXor1>(v));
@@ -351,19 +360,20 @@ __device__ __forceinline__ void tridiagonal_qr(const f64x2* de, const double* es
 // LDS of `eig_tridiagonal` (doubles; NP = 32 RJ): reflectors [NP][NP], two vectors of NP, (diagonal, e^2) pairs, e,
 // eigenvalues, partial norms, partial minima with their rows (one per thread; the QR steps' matrices); for NP = 64 also the
 // multipliers of the twisted factorisations [2][NP][NP] (the QR steps' vectors; NP = 128: in place of the reflectors).
-constexpr size_t tri_lds_doubles(int NP) { return (size_t)(NP == 64 ? 3 : 1) * NP * NP + 8 * (size_t)NP + FIT_NT + FIT_NT / 2; }
+constexpr size_t tri_lds_doubles(int NP) { return (size_t)(NP == 64 ? 3 : 1) * NP * NP + 11 * (size_t)NP + FIT_NT + FIT_NT / 2; }
 
-// a: the matrix, entry (ti + 4 RJ ii, tj + 32 jj) in a[ii][jj] of thread (ti = t / 32, tj = t % 32) < 128 RJ, zero
-// outside n x n (destroyed).  Any symmetric matrix: the statistics' matrices are positive semidefinite only up to the
+constexpr int TRI_WAVES = 4;      // waves that hold the matrix of eig_tridiagonal, one per SIMD, every fourth column each
+
+// a: the matrix, entry (lane + 64 h, wave + 4 q) in a[q][h] of the first four waves, zero outside n x n
+// (destroyed).  Any symmetric matrix: the statistics' matrices are positive semidefinite only up to the
 // rounding of their fp32 sums, and where large means cancel that rounding is all there is.  Eigenvalues go to slot k of
-// the shared block with their order and the signs of the vectors, eigenvector j to column j of v (global, column-major
-// with stride ldv, component i in row sh.row[i]).  scr: 2 n n doubles of global scratch (NP = 128).  Statistics that are
+// the shared block with their order and the signs of the vectors, eigenvector j to column j of v (column-major with stride
+// ldv, component i in row sh.row[i]; may be the start of lds).  scr: 2 n n doubles of global scratch (NP = 128).  Statistics that are
 // not finite give parameters that are not finite.
 template <int RJ>
-__device__ __forceinline__ void eig_tridiagonal(double (&a)[8][RJ], int n, double* v, int ldv, double* scr, int k_slot,
+__device__ __forceinline__ void eig_tridiagonal(double (&a)[8 * RJ][RJ / 2], int n, double* v, int ldv, double* scr, int k_slot,
                                                 FitShared& sh, double* lds) {
-  constexpr int NP = 32 * RJ, RI = 8, HT = 128 * RJ, RS = 4 * RJ;      // HT threads hold the matrix, rows RS apart
-  auto IB = [](int jc) constexpr { return 32 * jc / RS; };             // first register row of column block jc
+  constexpr int NP = 32 * RJ, RH = NP / 64, TW = TRI_WAVES, NQ0 = NP / TW, QB = NQ0 / 4;
   constexpr bool kInLds = NP == 64;
   double* refl = lds;                                // reflector k: refl[k * NP + i], zero for i <= k
   double* col = refl + (size_t)NP * NP;
@@ -375,108 +385,158 @@ __device__ __forceinline__ void eig_tridiagonal(double (&a)[8][RJ], int n, doubl
   double* part_val = nsq + 2 * NP;
   int* part_arg = (int*)(part_val + FIT_NT);
   double* mul = part_val + FIT_NT + FIT_NT / 2;      // NP = 64: [2][n][n]
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, ti = t >> 5, tj = t & 31;
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
 
-  // ---- Householder reduction: A <- H A H with H = I - u u^T, |u|^2 = 2, column by column: u from column k (every wave
-  // forms it by itself: no barrier), p = A u, w = p - (u^T p / 2) u, A <- A - u w^T - w u^T.  The loop over blocks of 32
-  // columns is unrolled so that registers of finished rows and columns are skipped at compile time.  A wave issues one
-  // instruction per 6 cycles, two waves of a SIMD one fp64 instruction each per 8: with n <= 64 half the waves hold the
-  // whole matrix (2360 -> 2060 cycles per column on 4 instead of 8 waves), the others only meet the barriers.
+  // ---- Householder reduction: A <- H A H with H = I - tau v v^T, column by column: v = x - beta e (x: the entries of column k
+  // below the diagonal, e: unit vector k + 1, beta = -sign(x_0) |x|), tau = 1 / (|x| (|x| + |x_0|)), y = A v,
+  // A <- A - tau (v y^T + (y - tau (v^T y) v) v^T).  What bounds a step is the latency of its dependent fp64 operations and of
+  // its passes through LDS (a wave per SIMD).  A lane holds rows and a wave columns: A x takes no exchange between lanes, the
+  // numbers of a wave's columns (x_j, y_j) are broadcast reads of LDS.  The product is taken with the raw column, beside the chain of
+  // the norm: A v = A x - beta A e, A e being column k + 1, and v^T A v likewise from x^T A x.  From the parts of the product
+  // every wave has the next column for itself (column k + 1 after the update), so there is one barrier per column.  Column k + 1
+  // is finished then and goes without its share of beta; finished rows go on being rotated, their norms stay.  The loop over
+  // blocks of a quarter of the columns is unrolled so that finished columns are skipped at compile time.  Against a thread per 8 x 2
+  // entries with rows and columns both over lanes, u made before the product and two barriers a column: 2060 -> 1700 cycles per
+  // column at n = 64, 2700 -> 2600 at n = 128.
+  double* prt = lam;                                 // [2][4][NP] parts of A x, by wave and row (lam, nsq, part_val: not yet in use)
+  double* sw = prt + 8 * NP;                         // [2][4] x^T A x, a part per wave
+  double* xy = sw + 8 + 3 * NQ0 * wave;              // y, x of the wave's columns, [2] x
+  double x[RH], ax[RH] = {};                         // x, and the wave's part of A x
+  {
+    if (wave == 0)
 #pragma unroll
-  for (int jc = 0; jc < RJ; ++jc) {
-    for (int kk = 0; kk < 32; ++kk) {
-      const int k = 32 * jc + kk;
-      if (k > n - 3) break;
-      if (t < HT && tj == kk) {
+      for (int h = 0; h < RH; ++h) col[lane + 64 * h] = a[0][h];
+    if (wave == 1)
 #pragma unroll
-        for (int ii = 0; ii < RI; ++ii) {
-          const int i = ti + RS * ii;
-          col[i] = i > k ? a[ii][jc] : 0.0;
-          if (i == k) de[k].x = a[ii][jc];
-        }
+      for (int h = 0; h < RH; ++h) pv[lane + 64 * h] = a[0][h];
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < RH; ++h) {
+      const int i = lane + 64 * h;
+      x[h] = i > 0 ? col[i] : 0.0;
+      if (t == 0 && h == 0) de[0].x = col[0];
+    }
+    if (wave < TW) {
+#pragma unroll
+      for (int h = 0; h < RH; ++h)
+        if ((lane & (TW - 1)) == wave) xy[NQ0 + (lane + 64 * h) / TW] = x[h];
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+      for (int q = 0; q < NQ0 / 2; ++q) {
+        const f64x2 xj = ((const f64x2*)(xy + NQ0))[q];
+#pragma unroll
+        for (int h = 0; h < RH; ++h) ax[h] += a[2 * q][h] * xj.x + a[2 * q + 1][h] * xj.y;
       }
-      __syncthreads();
-      double xl[NP / 64], ui[RI], uj[RJ];
-      if (t < HT) {      // u = (x - beta e_0) / sqrt(|x| (|x| + |x_0|))
-        const double x0 = col[k + 1];
-        double n2 = 0.0;
+    }
+    __syncthreads();
+  }
+  auto columns = [&](auto Q0) {
+    constexpr int q0 = Q0();
+#pragma unroll 1
+    for (int k = TW * q0; k < min(n - 2, TW * (q0 + QB)); ++k) {
+      double* pk = prt + 4 * NP * (k & 1);
+      double* sk = sw + 4 * (k & 1);
+      double *xo = xy + NQ0 * (1 + (k & 1)), *xn = xy + NQ0 * (2 - (k & 1));      // x of this step and the next
+      double *c2p = k & 1 ? col : pv, *c2n = k & 1 ? pv : col;      // column k + 1, and k + 2 after this step
+      double beta = 0.0, tau = 0.0, x0 = 0.0;
+      if (wave < TW) {
+        double n2 = 0.0, xax = 0.0;
 #pragma unroll
-        for (int q = 0; q < NP / 64; ++q) { xl[q] = col[lane + 64 * q]; n2 += xl[q] * xl[q]; }
+        for (int h = 0; h < RH; ++h) n2 += x[h] * x[h];
+        n2 = wave_sum(n2);
 #pragma unroll
-        for (int ii = IB(jc); ii < RI; ++ii) ui[ii] = col[ti + RS * ii];
-#pragma unroll
-        for (int jj = jc; jj < RJ; ++jj) uj[jj] = col[tj + 32 * jj];
-        n2 = sum64(n2);
-        double beta = 0.0, f = 0.0;
+        for (int h = 0; h < RH; ++h) {
+          pk[NP * wave + lane + 64 * h] = ax[h];
+          xax += x[h] * ax[h];
+        }
+        xax = wave_sum(xax);
+        if (lane == 0) sk[wave] = xax;
+        const int l0 = (k + 1) & 63;                 // x_0 = x of row k + 1
+        double xs = x[0];
+        if constexpr (RH == 2) xs = k + 1 < 64 ? x[0] : x[RH - 1];
+        x0 = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(xs), l0), __builtin_amdgcn_readlane(__double2loint(xs), l0));
         if (n2 > 1e-290) {
           const double nrm = n2 * rsqrt64(n2);
           beta = -copysign(nrm, x0);
-          f = rsqrt64(nrm * (nrm + fabs(x0)));
+          tau = rcp64(fma(nrm, fabs(x0), n2));
         }
-        const double fb = f * beta;
-#pragma unroll
-        for (int ii = IB(jc); ii < RI; ++ii) ui[ii] = ui[ii] * f - (ti + RS * ii == k + 1 ? fb : 0.0);
-#pragma unroll
-        for (int jj = jc; jj < RJ; ++jj) uj[jj] = uj[jj] * f - (tj + 32 * jj == k + 1 ? fb : 0.0);
-#pragma unroll
-        for (int q = 0; q < NP / 64; ++q) xl[q] = xl[q] * f - (lane + 64 * q == k + 1 ? fb : 0.0);
-        if (wave == 0) {
-#pragma unroll
-          for (int q = 0; q < NP / 64; ++q) refl[(size_t)k * NP + lane + 64 * q] = xl[q];
-          if (lane == 0) es[k] = beta;
-        }
-        // p = A u: partial sums of a row over the 32 lanes of its half wave, folded so that every lane ends with one row
-        double s[RI];
-#pragma unroll
-        for (int ii = 0; ii < RI; ++ii) {
-          s[ii] = 0.0;
-          if (ii >= IB(jc)) {
-#pragma unroll
-            for (int jj = jc; jj < RJ; ++jj) s[ii] += a[ii][jj] * uj[jj];
-          }
-        }
-        const bool b3 = lane & 8, b2 = lane & 4;
-        double q4[4], q2[2];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) q4[q] = add_rows16(s[2 * q], s[2 * q + 1]);
-#pragma unroll
-        for (int q = 0; q < 2; ++q) q2[q] = (b3 ? q4[2 * q + 1] : q4[2 * q]) + dpp64<kMirror16>(b3 ? q4[2 * q] : q4[2 * q + 1]);
-        double r = (b2 ? q2[1] : q2[0]) + dpp64<kMirror8>(b2 ? q2[0] : q2[1]);
-        r += dpp64<kXor2>(r);
-        r += dpp64<kXor1>(r);
-        if ((lane & 3) == 0) pv[ti + RS * (4 * (b2 ? 1 : 0) + 2 * (b3 ? 1 : 0) + ((lane >> 4) & 1))] = r;
       }
       __syncthreads();
-      if (t < HT) {
-        double up = 0.0;
+      if (wave < TW) {
+        const f64x2 s01 = *(const f64x2*)sk, s23 = *(const f64x2*)(sk + 2);
+        const double a11 = c2p[k + 1];
+        const double ax0 = (pk[k + 1] + pk[NP + k + 1]) + (pk[2 * NP + k + 1] + pk[3 * NP + k + 1]);
+        const double y0 = ax0 - beta * a11, v0 = x0 - beta;          // y and v of row k + 1
+        const double c = tau * (((s01.x + s01.y) + (s23.x + s23.y)) - beta * (ax0 + y0));
+        double tv[RH], ty[RH];
 #pragma unroll
-        for (int q = 0; q < NP / 64; ++q) up += xl[q] * pv[lane + 64 * q];
-        double wi[RI], wj[RJ];
+        for (int h = 0; h < RH; ++h) {
+          const int i = lane + 64 * h;
+          const double c2 = c2p[i];
+          const double y = ((pk[i] + pk[NP + i]) + (pk[2 * NP + i] + pk[3 * NP + i])) - beta * c2;
+          const double v = i == k + 1 ? v0 : x[h];
+          if (wave == 0) refl[(size_t)k * NP + i] = i == k ? tau : v;
+          tv[h] = tau * v;
+          ty[h] = tau * (y - c * v);
+          const double full = c2 - ty[h] * v0 - tv[h] * y0;
+          if (wave == 0 && i == k + 1) {
+            de[k + 1].x = full;
+            es[k] = beta;
+          }
+          x[h] = i > k + 1 ? full : 0.0;
+          if ((lane & (TW - 1)) == wave) {
+            xn[i / TW] = x[h];
+            xy[i / TW] = y;
+          }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        double s[RH][2] = {};
 #pragma unroll
-        for (int ii = IB(jc); ii < RI; ++ii) wi[ii] = pv[ti + RS * ii];
+        for (int q = q0 / 2; q < NQ0 / 2; ++q) {     // the update, and the product with the next x
+          const f64x2 xj = ((const f64x2*)xo)[q], yj = ((const f64x2*)xy)[q], nj = ((const f64x2*)xn)[q];
 #pragma unroll
-        for (int jj = jc; jj < RJ; ++jj) wj[jj] = pv[tj + 32 * jj];
-        const double K = 0.5 * sum64(up);
+          for (int h = 0; h < RH; ++h) {
+            a[2 * q][h] = fma(-tv[h], yj.x, fma(-ty[h], xj.x, a[2 * q][h]));
+            a[2 * q + 1][h] = fma(-tv[h], yj.y, fma(-ty[h], xj.y, a[2 * q + 1][h]));
+            s[h][0] = fma(a[2 * q][h], nj.x, s[h][0]);
+            s[h][1] = fma(a[2 * q + 1][h], nj.y, s[h][1]);
+          }
+        }
 #pragma unroll
-        for (int ii = IB(jc); ii < RI; ++ii) wi[ii] -= K * ui[ii];
+        for (int h = 0; h < RH; ++h) ax[h] = s[h][0] + s[h][1];
+        if (wave == ((k + 2) & (TW - 1))) {
+          const int q = (k + 2) / TW - q0;           // at most the first column of the next block
+          auto pick = [&](double lo, double hi, int bit) { return q & bit ? hi : lo; };
 #pragma unroll
-        for (int jj = jc; jj < RJ; ++jj) wj[jj] -= K * uj[jj];
-#pragma unroll
-        for (int ii = IB(jc); ii < RI; ++ii)
-#pragma unroll
-          for (int jj = jc; jj < RJ; ++jj) a[ii][jj] -= ui[ii] * wj[jj] + wi[ii] * uj[jj];
+          for (int h = 0; h < RH; ++h) {
+            double r = pick(pick(a[q0][h], a[q0 + 1][h], 1), pick(a[q0 + 2][h], a[q0 + 3][h], 1), 2);
+            if constexpr (QB == 8)
+              r = pick(r, pick(pick(a[q0 + 4][h], a[q0 + 5][h], 1), pick(a[q0 + 6][h], a[q0 + 7][h], 1), 2), 4);
+            if constexpr (q0 + QB < NQ0) r = pick(r, a[q0 + QB][h], QB);
+            c2n[lane + 64 * h] = r;
+          }
+        }
       }
     }
+  };
+  columns(std::integral_constant<int, 0>());
+  columns(std::integral_constant<int, QB>());
+  columns(std::integral_constant<int, 2 * QB>());
+  columns(std::integral_constant<int, 3 * QB>());
+  __syncthreads();
+  if (n > 1 && t == n - 1) {                         // the last two columns
+    de[n - 1].x = (n & 1 ? col : pv)[n - 1];
+    es[n - 2] = t < 64 ? x[0] : x[RH - 1];
   }
+  for (int k = wave; k < n - 2; k += FIT_NT / 64) {  // reflectors as u = v sqrt(tau), |u|^2 = 2 (tau waits in entry k)
+    double* u = refl + (size_t)k * NP;
+    const double tau = u[k], f = tau > 0.0 ? tau * rsqrt64(tau) : 0.0;
 #pragma unroll
-  for (int ii = 0; ii < RI; ++ii)
-#pragma unroll
-    for (int jj = 0; jj < RJ; ++jj) {
-      const int i = ti + RS * ii, j = tj + 32 * jj;
-      if (t >= HT) continue;
-      if (i == j && i < n && i >= n - 2) de[i].x = a[ii][jj];
-      if (i == n - 1 && j == n - 2) es[n - 2] = a[ii][jj];
+    for (int h = 0; h < RH; ++h) {
+      const int i = lane + 64 * h;
+      u[i] = i == k ? 0.0 : f * u[i];
     }
+  }
   __syncthreads();
   // in units of the largest Gershgorin radius about zero (every wave finds it for itself), which no eigenvalue exceeds
   // in size; off-diagonal entries at least 1e-17 (far below the rounding of the reduction), so that no Sturm sequence and
@@ -506,7 +566,11 @@ __device__ __forceinline__ void eig_tridiagonal(double (&a)[8][RJ], int n, doubl
     __syncthreads();
   }
 
-  // ---- eigenvalues: 256 / NP lanes per eigenvalue split its interval into as many parts + 1.  The sequence of leading
+  // ---- eigenvalues: 256 / NP lanes per eigenvalue.  They split its interval into as many parts + 1 until it holds no other
+  // eigenvalue; then they stand about the zero of the secant through the characteristic polynomial at its ends, at distances that
+  // shrink with the secant's error (to the square of the interval).  Which part is kept is decided by the Sturm counts
+  // alone, and a step whose guess missed is followed by a split into equal parts.  (Equal parts throughout, 24 steps at n = 64 and 35
+  // at n = 128: 51 k and 139 k cycles, now 37 k and 98 k.)  The sequence of leading
   // minors in its three-term form: one dependent multiply-add per row, rescaled every 16 rows (a factor of at least
   // 1e-34 per two rows: no underflow before).  One wave per SIMD: with twice the lanes (and a quarter fewer steps) the
   // waves share the fp64 issue slots (50 k -> 60 k cycles at n = 64).
@@ -514,13 +578,27 @@ __device__ __forceinline__ void eig_tridiagonal(double (&a)[8][RJ], int n, doubl
     constexpr int S = 256 / NP;
     const int j = t / S, sec = t % S;
     const double frac = (double)(sec + 1) / (double)(S + 1);
-    double lo = -1.0 - 1e-9, hi = 1.0 + 1e-9;
-    const int steps = S == 4 ? 24 : 35;              // 5^24, 3^35 > 2^55
-    for (int it = 0; it < steps; ++it) {
-      const double x = fma(hi - lo, frac, lo);
+    constexpr double kFirst = 1.0 / 16.0;
+    // the ends of the interval, the polynomial m 2^e there, the eigenvalues below
+    double lo = -1.0 - 1e-9, hi = 1.0 + 1e-9, lo_m = 0.0, hi_m = 0.0;
+    int lo_e = 0, hi_e = 0, lo_cnt = 0, hi_cnt = n;
+    double eta = 0.0;                                // distance from the guess, in intervals; 0: equal parts
+    bool done = j >= n;
+    for (int it = 0; it < 60; ++it) {
+      const double w = hi - lo, third = fma(w, frac, lo);
+      double x = third, in = 0.0;
+      if (eta > 0.0) {
+        const double ratio = ldexp(fabs(hi_m), hi_e - lo_e) * rcp64(fabs(lo_m));
+        const double r = fma(w, rcp64(1.0 + ratio), lo), least = fma(fabs(r), 1.2e-16, 3e-17);
+        in = fmax((S == 4 ? eta * eta : eta) * w, least);
+        const double out = fmax(eta * w, 2.0 * in);
+        const double d = S == 4 && (sec == 0 || sec == 3) ? out : in;
+        x = sec < S / 2 ? r - d : r + d;
+        x = x > lo && x < hi ? x : third;        // (outside, or not a number)
+      }
       double p1 = 1.0, p2 = 0.0;
       unsigned bits = 0;
-      int cnt = 0;
+      int cnt = 0, ex_sum = 0;
       for (int i0 = 0; i0 < n; i0 += 16) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
@@ -534,16 +612,49 @@ __device__ __forceinline__ void eig_tridiagonal(double (&a)[8][RJ], int n, doubl
         const int ex = __builtin_amdgcn_frexp_exp(fmax(fabs(p1), fabs(p2)));
         p1 = ldexp(p1, -ex);
         p2 = ldexp(p2, -ex);
+        ex_sum += ex;
       }
-      double nlo = cnt <= j ? x : lo, nhi = cnt <= j ? hi : x;
-      nlo = fmax(nlo, dpp64<kXor1>(nlo));
-      nhi = fmin(nhi, dpp64<kXor1>(nhi));
-      if constexpr (S == 4) {
-        nlo = fmax(nlo, dpp64<kXor2>(nlo));
-        nhi = fmin(nhi, dpp64<kXor2>(nhi));
+      const bool up = cnt <= j && x > lo, down = cnt > j && x < hi;
+      double nlo = up ? x : lo, nhi = down ? x : hi, nlo_m = up ? p1 : lo_m, nhi_m = down ? p1 : hi_m;
+      int nlo_e = up ? ex_sum : lo_e, nhi_e = down ? ex_sum : hi_e, nlo_cnt = up ? cnt : lo_cnt, nhi_cnt = down ? cnt : hi_cnt;
+      auto over = [&](auto CTRL) {                   // the larger lower end, the smaller upper end of two lanes
+        constexpr int ctrl = CTRL();
+        const double ol = dpp64<ctrl>(nlo), oh = dpp64<ctrl>(nhi), olm = dpp64<ctrl>(nlo_m), ohm = dpp64<ctrl>(nhi_m);
+        const int ole = __builtin_amdgcn_update_dpp(0, nlo_e, ctrl, 0xf, 0xf, true);
+        const int ohe = __builtin_amdgcn_update_dpp(0, nhi_e, ctrl, 0xf, 0xf, true);
+        const int olc = __builtin_amdgcn_update_dpp(0, nlo_cnt, ctrl, 0xf, 0xf, true);
+        const int ohc = __builtin_amdgcn_update_dpp(0, nhi_cnt, ctrl, 0xf, 0xf, true);
+        const bool l = ol > nlo, h = oh < nhi;
+        nlo = l ? ol : nlo;
+        nlo_m = l ? olm : nlo_m;
+        nlo_e = l ? ole : nlo_e;
+        nlo_cnt = l ? olc : nlo_cnt;
+        nhi = h ? oh : nhi;
+        nhi_m = h ? ohm : nhi_m;
+        nhi_e = h ? ohe : nhi_e;
+        nhi_cnt = h ? ohc : nhi_cnt;
+      };
+      over(std::integral_constant<int, kXor1>());
+      if constexpr (S == 4) over(std::integral_constant<int, kXor2>());
+      if (!done) {
+        lo = nlo;
+        lo_m = nlo_m;
+        lo_e = nlo_e;
+        lo_cnt = nlo_cnt;
+        hi = nhi;
+        hi_m = nhi_m;
+        hi_e = nhi_e;
+        hi_cnt = nhi_cnt;
+        const double wn = hi - lo;
+        if (eta > 0.0) {                             // the guess is good to the square of eta, to eta, or not
+          if (wn <= 2.5 * in) eta = fmin(4.0 * eta * eta, kFirst);
+          else if (!(S == 4 && wn <= 2.5 * eta * w)) eta = 0.0;
+        } else if (lo_cnt == j && hi_cnt == j + 1) {
+          eta = kFirst;
+        }
+        done = wn <= fma(fmax(fabs(lo), fabs(hi)), 2.3e-16, 3e-17);
       }
-      lo = nlo;
-      hi = nhi;
+      if (!__any(!done)) break;
     }
     if (sec == 0) lam[j] = 0.5 * (lo + hi);
   }
@@ -553,11 +664,12 @@ __device__ __forceinline__ void eig_tridiagonal(double (&a)[8][RJ], int n, doubl
   __syncthreads();
   const bool close = sh.flag;
 
-  // what the last stage starts from: the components of the vectors that a thread holds there, eight lanes per RC vectors, a
-  // lane with rows 2 part + 16 q + {0, 1}
-  constexpr int RC = NP / 64, NQ = NP / 16;
-  const int part = t & 7, grp = t >> 3;
-  double z[RC][2 * NQ];
+  // what the last stage starts from: the components of the vector that a thread holds there, sixteen vectors a wave, four lanes
+  // (a row of lanes apart) per vector, each with rows 2 part + 8 q + {0, 1}
+  constexpr int NQ = NP / 8;
+  const int part = lane >> 4, vec = 16 * wave + (lane & 15);
+  const bool holds = 16 * wave < NP;
+  double z[2 * NQ];
   if (close) {
     double* Z = kInLds ? mul : refl;
     if (!kInLds) {                                   // (the reflectors wait in global memory)
@@ -577,9 +689,7 @@ __device__ __forceinline__ void eig_tridiagonal(double (&a)[8][RJ], int n, doubl
     __syncthreads();
     if (t < n) sh.twist[t] = descending_place(lam, n, t);
 #pragma unroll
-    for (int c = 0; c < RC; ++c)
-#pragma unroll
-      for (int q = 0; q < 2 * NQ; ++q) z[c][q] = Z[(grp + 64 * c) * NP + 2 * part + 16 * (q >> 1) + (q & 1)];
+    for (int q = 0; q < 2 * NQ; ++q) z[q] = Z[min(vec, NP - 1) * NP + 2 * part + 8 * (q >> 1) + (q & 1)];
     __syncthreads();
     if (!kInLds) {
       for (int e = t; e < n * NP; e += FIT_NT) refl[e] = e % NP < n ? scr[(size_t)(e / NP) * n + e % NP] : 0.0;
@@ -688,123 +798,142 @@ __device__ __forceinline__ void eig_tridiagonal(double (&a)[8][RJ], int n, doubl
     }
     if (t < NP) sh.twist[t] = rtw;
     __syncthreads();
-#pragma unroll
-    for (int c = 0; c < RC; ++c) {
-      const int j = grp + 64 * c, jc = min(j, n - 1), rt = sh.twist[jc];
-      const double sc = j < n ? rsqrt64(1.0 + nsq[jc] + nsq[NP + jc]) : 0.0;
+    if (holds) {
+      const int jc = min(vec, n - 1), rt = sh.twist[jc];
+      const double sc = vec < n ? rsqrt64(1.0 + nsq[jc] + nsq[NP + jc]) : 0.0;
 #pragma unroll
       for (int q = 0; q < 2 * NQ; ++q) {
-        const int i = 2 * part + 16 * (q >> 1) + (q & 1);
-        double x = 0.0;
-        if (i < n) x = i == rt ? 1.0 : (i < rt ? fl[(size_t)i * n + jc] : bu[(size_t)(i - 1) * n + jc]);
-        z[c][q] = x * sc;
+        const int i = 2 * part + 8 * (q >> 1) + (q & 1), ic = min(i, n - 1);
+        const double x = *(i < rt ? fl + (size_t)ic * n + jc : bu + (size_t)max(ic - 1, 0) * n + jc);
+        z[q] = i < n ? (i == rt ? sc : x * sc) : 0.0;
       }
     }
   }
 
-  // ---- the reflections applied to the vectors.
+  // ---- the reflections applied to the vectors, their products summed over the parts by the matrix pipe.
   // (sixteen reflectors per block, so that the rows above them are skipped at compile time; the next reflector is
   // requested while the current one is used)
+  if (holds) {
 #pragma unroll
-  for (int jb = NQ - 1; jb >= 0; --jb) {
-    const int ktop = min(n - 3, 16 * jb + 15);
-    if (ktop < 16 * jb) continue;
-    const f64x2* up = (const f64x2*)(refl + (size_t)ktop * NP) + part;
-    f64x2 u[NQ];
+    for (int jb = NP / 16 - 1; jb >= 0; --jb) {
+      const int ktop = min(n - 3, 16 * jb + 15);
+      if (ktop < 16 * jb) continue;
+      auto load = [&](f64x2 (&u)[NQ], int k) {
+        const f64x2* up = (const f64x2*)(refl + (size_t)max(k, 0) * NP) + part;
 #pragma unroll
-    for (int q = jb; q < NQ; ++q) u[q] = up[8 * q];
-    for (int k = ktop; k >= 16 * jb; --k) {
-      up -= k > 0 ? NP / 2 : 0;
-      f64x2 un[NQ];
+        for (int q = 2 * jb; q < NQ; ++q) u[q] = up[4 * q];
+      };
+      auto reflect = [&](const f64x2 (&u)[NQ]) {
+        double s[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int q = jb; q < NQ; ++q) un[q] = up[8 * q];
+        for (int q = 2 * jb; q < NQ; ++q) {
+          s[2 * (q & 1)] += u[q].x * z[2 * q];
+          s[2 * (q & 1) + 1] += u[q].y * z[2 * q + 1];
+        }
+        const double sm = -__builtin_amdgcn_mfma_f64_4x4x4f64(1.0, (s[0] + s[1]) + (s[2] + s[3]), 0.0, 0, 0, 0);
 #pragma unroll
-      for (int c = 0; c < RC; ++c) {
-        double s0 = 0.0, s1 = 0.0;
-#pragma unroll
-        for (int q = jb; q < NQ; ++q) { s0 += u[q].x * z[c][2 * q]; s1 += u[q].y * z[c][2 * q + 1]; }
-        const double sm = sum8(s0 + s1);
-#pragma unroll
-        for (int q = jb; q < NQ; ++q) { z[c][2 * q] -= u[q].x * sm; z[c][2 * q + 1] -= u[q].y * sm; }
+        for (int q = 2 * jb; q < NQ; ++q) {
+          z[2 * q] = fma(u[q].x, sm, z[2 * q]);
+          z[2 * q + 1] = fma(u[q].y, sm, z[2 * q + 1]);
+        }
+      };
+      f64x2 ua[NQ], ub[NQ];
+      load(ua, ktop);
+      int k = ktop;
+#pragma unroll 1
+      for (; k > 16 * jb; k -= 2) {
+        load(ub, k - 1);
+        reflect(ua);
+        load(ua, k - 2);
+        reflect(ub);
       }
-#pragma unroll
-      for (int q = jb; q < NQ; ++q) u[q] = un[q];
+      if (k == 16 * jb) reflect(ua);
     }
   }
+  __syncthreads();                                   // (v may be where the reflectors are)
   // results: vectors, and per vector the sign that makes its largest component positive (lowest index on ties)
-#pragma unroll
-  for (int c = 0; c < RC; ++c) {
-    const int j = grp + 64 * c;
+  if (holds) {
     double big = 0.0;
     int at = 0;
 #pragma unroll
     for (int q = 0; q < 2 * NQ; ++q) {
-      const int i = 2 * part + 16 * (q >> 1) + (q & 1);
-      if (j < n && i < n) v[(size_t)j * ldv + sh.row[i]] = z[c][q];
-      if (fabs(z[c][q]) > fabs(big)) { big = z[c][q]; at = i; }
+      const int i = 2 * part + 8 * (q >> 1) + (q & 1);
+      if (vec < n && i < n) v[(size_t)vec * ldv + sh.row[i]] = z[q];
+      if (fabs(z[q]) > fabs(big)) { big = z[q]; at = i; }
     }
-    for (int m = 1; m < 8; m <<= 1) {
+    for (int m = 16; m < 64; m <<= 1) {
       const double ob = __shfl_xor(big, m, 64);
       const int oa = __shfl_xor(at, m, 64);
       if (fabs(ob) > fabs(big) || (fabs(ob) == fabs(big) && oa < at)) { big = ob; at = oa; }
     }
-    if (part == 0 && j < n) {
-      sh.sgn[k_slot][j] = big < 0.0 ? -1.0 : 1.0;
-      sh.nrm[k_slot][j] = lam[j] * scale;
-      sh.ord[k_slot][close ? sh.twist[j] : n - 1 - j] = j;      // (bisection: in ascending order)
+    if (part == 0 && vec < n) {
+      sh.sgn[k_slot][vec] = big < 0.0 ? -1.0 : 1.0;
+      sh.nrm[k_slot][vec] = lam[vec] * scale;
+      sh.ord[k_slot][close ? sh.twist[vec] : n - 1 - vec] = vec;      // (bisection: in ascending order)
     }
   }
   __syncthreads();
 }
 
-// Eigen-decomposition of the symmetric matrix entry(i, j): into slot k and v (stride n) as above.  A row without
+// Eigen-decomposition of the symmetric matrix entry(i, j): into slot k as above, the vectors to the start of lds (stride n + 2:
+// vectors side by side in different banks).  A row without
 // off-diagonal entries (zero-padded dimensions) is left out of the eigenproblem: its diagonal entry is an eigenvalue, its
 // unit vector the eigenvector.  Several such rows would have equal eigenvalues and send the whole matrix through the QR
 // steps: fits with a quarter of the coordinates zero, 8 heads, d 16 / 64 / 128 take 78 / 145 / 378 us, with them 121 /
 // 723 / 2504.
 template <int RJ, class Entry>
-__device__ __forceinline__ void decompose_symmetric(Entry entry, double* v, double* scr, int n, int k, FitShared& sh, double* lds) {
-  const int t = threadIdx.x, lane = t & 63, ti = t >> 5, tj = t & 31;
-  double a[8][RJ];
-  // an m x m matrix; indices are clamped, not conditional, so that all loads are in flight (at n = 64 12 k -> 4 k cycles)
-  auto load = [&](int m, auto row_of) {
-    auto part = [&](auto II, auto JJ) {
+__device__ __forceinline__ void decompose_symmetric(Entry entry, double* scr, int n, int k, FitShared& sh, double* lds) {
+  double* v = lds;
+  constexpr int RH = RJ / 2, TW = TRI_WAVES, NQ = 8 * RJ;
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  double a[NQ][RH];
+  // The entries by way of LDS: all waves fetch, eight rows each in flight (by the four waves that hold the matrix, entry by entry: 25 k
+  // cycles at n = 128)
+  for (int r0 = wave; r0 < n; r0 += 8 * (FIT_NT / 64)) {
+    double e[8][RH];
 #pragma unroll
-      for (int ii = 0; ii < II; ++ii)
+    for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int jj = 0; jj < JJ; ++jj) a[ii][jj] = entry(row_of(min(ti + 4 * RJ * ii, m - 1)), row_of(min(tj + 32 * jj, m - 1)));
-    };
-    if (RJ == 4 || t < 128 * RJ) {
-      if (RJ == 4 || m > 16 * RJ) part(std::integral_constant<int, 8>(), std::integral_constant<int, RJ>());
-      else part(std::integral_constant<int, 4>(), std::integral_constant<int, RJ / 2>());
-    }
+      for (int h = 0; h < RH; ++h) e[i][h] = entry(min(r0 + (FIT_NT / 64) * i, n - 1), min(lane + 64 * h, n - 1));
 #pragma unroll
-    for (int ii = 0; ii < 8; ++ii)
+    for (int i = 0; i < 8; ++i)
 #pragma unroll
-      for (int jj = 0; jj < RJ; ++jj)
-        if (t >= 128 * RJ || ti + 4 * RJ * ii >= m || tj + 32 * jj >= m) a[ii][jj] = 0.0;
-  };
-  load(n, [](int i) { return i; });
-  unsigned rows = 0;                                 // bit ii: row ii of this thread has an off-diagonal entry
-#pragma unroll
-  for (int ii = 0; ii < 8; ++ii) {
-    unsigned bits = 0;
-#pragma unroll
-    for (int jj = 0; jj < RJ; ++jj) {
-      const unsigned b = ((unsigned)__double2hiint(a[ii][jj]) << 1) | (unsigned)__double2loint(a[ii][jj]);
-      bits |= ti + 4 * RJ * ii == tj + 32 * jj ? 0u : b;
-    }
-    rows |= bits != 0u ? 1u << ii : 0u;
+      for (int h = 0; h < RH; ++h) {
+        const int r = r0 + (FIT_NT / 64) * i, c = lane + 64 * h;
+        if (r < n && c < n) lds[(size_t)r * n + c] = e[i][h];
+      }
   }
-  // over the 32 lanes that share the rows
-  rows |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)rows, kXor1, 0xf, 0xf, true);
-  rows |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)rows, kXor2, 0xf, 0xf, true);
-  rows |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)rows, kMirror8, 0xf, 0xf, true);
-  rows |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)rows, kMirror16, 0xf, 0xf, true);
-  const auto halves = __builtin_amdgcn_permlane16_swap(rows, rows, false, false);
-  rows = halves[0] | halves[1];
-  if (t < 128 * RJ && tj < 8) sh.twist[ti + 4 * RJ * tj] = (rows >> tj) & 1;
-  if (t < n) sh.row[t] = t;
+  // rows and columns row_of(0 .. m - 1) of it
+  auto load = [&](int m, auto row_of) {
+    if (wave >= TW) return;
+#pragma unroll
+    for (int h = 0; h < RH; ++h) {
+      const double* at = lds + row_of(min(lane + 64 * h, m - 1));
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const double e = at[row_of(min(wave + TW * q, m - 1)) * n];
+        a[q][h] = wave + TW * q < m && lane + 64 * h < m ? e : 0.0;
+      }
+    }
+  };
+  if (t < n) {
+    sh.row[t] = t;
+    sh.twist[t] = 0;
+  }
+  __syncthreads();
+  load(n, [](int i) { return i; });
+  if (wave < TW) {                                   // rows with an off-diagonal entry
+#pragma unroll
+    for (int h = 0; h < RH; ++h) {
+      unsigned bits = 0;
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const unsigned b = ((unsigned)__double2hiint(a[q][h]) << 1) | (unsigned)__double2loint(a[q][h]);
+        bits |= wave + TW * q == lane + 64 * h ? 0u : b;
+      }
+      if (bits != 0u) sh.twist[lane + 64 * h] = 1;
+    }
+  }
   __syncthreads();
   unsigned long long off[RJ / 2];
   int coupled = 0;
@@ -822,12 +951,13 @@ __device__ __forceinline__ void decompose_symmetric(Entry entry, double* v, doub
     }
     __syncthreads();
     if (coupled > 0) load(coupled, [&](int i) { return sh.row[i]; });
+    __syncthreads();
   }
-  if (coupled > 0) eig_tridiagonal<RJ>(a, coupled, v, n, scr, k, sh, lds);
+  if (coupled > 0) eig_tridiagonal<RJ>(a, coupled, v, n + 2, scr, k, sh, lds);
   if (coupled < n) {
     for (int e = t; e < n * n; e += FIT_NT) {
       const int j = e / n, i = e % n;
-      if (j >= coupled || i >= coupled) v[(size_t)j * n + sh.row[i]] = i == j ? 1.0 : 0.0;
+      if (j >= coupled || i >= coupled) v[(size_t)j * (n + 2) + sh.row[i]] = i == j ? 1.0 : 0.0;
     }
     if (t >= coupled && t < n) {
       sh.nrm[k][t] = entry(sh.row[t], sh.row[t]);
@@ -872,16 +1002,19 @@ __global__ void __launch_bounds__(FIT_NT) k_fit_device(int variant, int d, const
 
   // traces and mu4 . mu5 (every wave sums them for itself: d <= 128 terms)
   double tr1 = 0.0, tr2 = 0.0, dot = 0.0;
-  for (int l = t & 63; l < d; l += 64) {
-    tr1 += M1[(size_t)l * d + l];
-    tr2 += M2[(size_t)l * d + l];
-    dot += mu4[l] * mu5[l];
-  }
-  tr1 = sum64(tr1);
-  tr2 = sum64(tr2);
-  dot = sum64(dot);
+  auto traces = [&]() {
+    for (int l = t & 63; l < d; l += 64) {
+      tr1 += M1[(size_t)l * d + l];
+      tr2 += M2[(size_t)l * d + l];
+      dot += mu4[l] * mu5[l];
+    }
+    tr1 = sum64(tr1);
+    tr2 = sum64(tr2);
+    dot = sum64(dot);
+  };
 
   if (variant <= 2) {                                   // PosRF, GERF, SADERF: A = a I, diagonal B and C
+    traces();
     // psi_l = (M2_ll / M1_ll)^(1/4) for SADERF, 1 otherwise
     bool bad = false;
     double s = variant == 2 ? 2.0 * dot : tr1 + tr2 + 2.0 * dot, sx = tr1, sy = tr2;
@@ -920,40 +1053,48 @@ __global__ void __launch_bounds__(FIT_NT) k_fit_device(int variant, int d, const
     return;
   }
 
+  const int lane = t & 63, wave = t >> 6;
   if (variant == 4) {                                   // SDERF: one eigendecomposition of N
-    double* V = w;
     decompose_symmetric<RJ>([=](int r, int c) {
       const size_t e = (size_t)r * d + c;
       return M1[e] + mu4[r] * mu5[c] + mu5[r] * mu4[c] + M2[e];
-    }, V, w + nn, n, 0, sh, lds);
-    // row scales: sqrt(1 - 4a), with the sign of the eigenvector
-    if (t < d) sh.red_row[t] = sqrt(1.0 - 4.0 * a_star(fmax(sh.nrm[0][t], 0.0))) * sh.sgn[0][t];
-    __syncthreads();
-    for (int e = t; e < nn; e += FIT_NT) {              // B = (I - 4A)^(1/2) Q3^T: row l is the scaled eigenvector l
-      const int l = e / d, c = e % d, src = sh.ord[0][l];
-      const float bv = (float)(sh.red_row[src] * V[(size_t)src * d + c]);
-      B1[e] = bv;
-      B2[e] = bv;
-      C1[e] = C2[e] = l == c ? -0.5f : 0.f;
-      if (c == 0) A[l] = (float)a_star(fmax(sh.nrm[0][src], 0.0));
-    }
-    // the per-eigenvalue terms of log D and of the objective in parallel (the logarithms are the expensive part),
-    // their sums in eigenvalue order by one thread
+    }, w, n, 0, sh, lds);
+    // row scales: sqrt(1 - 4a), with the sign of the eigenvector; the eigenvalues' terms of log D and of the objective
     if (t < d) {
-      const double lam = fmax(sh.nrm[0][sh.ord[0][t]], 0.0), a = a_star(lam);
+      const int src = sh.ord[0][t];
+      const double lam = fmax(sh.nrm[0][src], 0.0), a = a_star(lam);
+      A[t] = (float)a;
+      sh.red_row[src] = sqrt(1.0 - 4.0 * a) * sh.sgn[0][src];
       sh.nrm[1][t] = 0.25 * log(1.0 - 4.0 * a);
       sh.nrm[2][t] = log(1.0 - 4.0 * a) - 0.5 * log(1.0 - 8.0 * a) + (1.0 + 1.0 / (1.0 - 8.0 * a)) * lam;
     }
     __syncthreads();
-    if (t == 0) {
-      double logD = 0.0, lbar = -tr1 - tr2;
-      for (int l = 0; l < d; ++l) { logD += sh.nrm[1][l]; lbar += sh.nrm[2][l]; }
-      write_header(th, logD, lbar, 3, variant);
-      status[grp] = 0;
+    for (int l = wave; l < d; l += FIT_NT / 64) {       // B = (I - 4A)^(1/2) Q3^T: row l is the scaled eigenvector l
+      const int src = sh.ord[0][l];
+      const double sc = sh.red_row[src];
+      for (int c = lane; c < d; c += 64) {
+        const float bv = (float)(sc * lds[(size_t)src * (d + 2) + c]);
+        const size_t e = (size_t)l * d + c;
+        B1[e] = bv;
+        B2[e] = bv;
+        C1[e] = C2[e] = l == c ? -0.5f : 0.f;
+      }
+    }
+    if (wave == 0) {
+      traces();
+      double logD = 0.0, lbar = 0.0;
+      for (int l = lane; l < d; l += 64) { logD += sh.nrm[1][l]; lbar += sh.nrm[2][l]; }
+      logD = sum64(logD);
+      lbar = sum64(lbar) - tr1 - tr2;
+      if (lane == 0) {
+        write_header(th, logD, lbar, 3, variant);
+        status[grp] = 0;
+      }
     }
     return;
   }
 
+  traces();
   // ADERF: eig M1, eig M2, SVD of Z = L1^(1/2) Q1^T Q2 L2^(1/2)
   double* V1 = w;
   double* V2 = w + nn;
@@ -961,10 +1102,12 @@ __global__ void __launch_bounds__(FIT_NT) k_fit_device(int variant, int d, const
   double* b1 = w + 3 * (size_t)nn;     // row-major
   double* b2 = w + 4 * (size_t)nn;
   // (Z, b1 and b2 are not yet in use: scratch)
-  decompose_symmetric<RJ>([=](int r, int c) { return M1[(size_t)r * d + c] + (r == c ? ridge : 0.0); }, V1, Z, n, 0, sh,
-                          lds);
-  decompose_symmetric<RJ>([=](int r, int c) { return M2[(size_t)r * d + c] + (r == c ? ridge : 0.0); }, V2, Z, n, 1, sh,
-                          lds);
+  for (int m = 0; m < 2; ++m) {
+    const double* M = m ? M2 : M1;
+    decompose_symmetric<RJ>([=](int r, int c) { return M[(size_t)r * d + c] + (r == c ? ridge : 0.0); }, Z, n, m, sh, lds);
+    for (int e = t; e < nn; e += FIT_NT) (m ? V2 : V1)[e] = lds[(size_t)(e / d) * (d + 2) + e % d];
+    __syncthreads();
+  }
   {
     const double l1max = sh.nrm[0][sh.ord[0][0]], l1min = sh.nrm[0][sh.ord[0][d - 1]];
     const double l2max = sh.nrm[1][sh.ord[1][0]], l2min = sh.nrm[1][sh.ord[1][d - 1]];
