@@ -334,6 +334,35 @@ def test_kernel_matvec_on_the_operator_kernels(fs, variant, Nx, Ny, d, M, n):
         np.testing.assert_allclose(out, ref, rtol=1e-3, atol=1e-4 * np.abs(ref).max())
 
 
+@pytest.mark.parametrize("d,M,n", [(4, 16, 1), (28, 48, 3), (32, 272, 16), (36, 16, 16), (60, 144, 2), (64, 80, 7)])
+@pytest.mark.parametrize("length", [0.02, 1.0, 6.0])
+def test_kernel_matvec_operator_kernels_edges(fs, d, M, n, length):
+    """Rows with something else behind them, odd numbers of feature tiles, d with and without room for
+    bias and row term in the projection, exponents near zero and (rows of norm 6) far beyond those that go without a shift.
+    The exponents' roundings are what the tolerance allows: 2^-24 of the largest exponent each, a handful of them."""
+    import torch
+    rng = np.random.default_rng(d * M + n)
+    Nx, Ny = 67, 130
+
+    def rows(N):
+        X = rng.standard_normal((N, d))
+        return (length * X / np.linalg.norm(X, axis=1, keepdims=True)).astype(np.float32)
+
+    X, Yp = rows(Nx), rows(Ny)
+    C = rng.standard_normal((Ny, n)).astype(np.float32)
+    Om = rng.standard_normal((M, d)).astype(np.float32)
+    vec = util.theta_vec_from_oracle(orc.fit("gerf", X.astype(np.float64), Yp.astype(np.float64)))
+    th = util.oracle_theta_from_vec(vec, d)
+
+    ref = orc.kernel_matvec(th, Om, X, Yp, C, 0.0)
+    tol = 1e-4 + 20 * 2.0 ** -24 * np.log(np.abs(ref).max() + 1.0)
+    Xd, Yd = (torch.from_numpy(np.pad(a, ((0, 0), (0, 4)), constant_values=np.nan)).cuda()[:, :d] for a in (X, Yp))
+    out = util.to_host(fs.kernel_matvec(torch.from_numpy(vec).cuda(), Xd, Yd, 1.0, 0.0, torch.from_numpy(Om).cuda(),
+                                        torch.from_numpy(C).cuda()))
+    assert np.isfinite(out).all()
+    assert np.linalg.norm(out - ref) <= tol * np.linalg.norm(ref)
+
+
 # ----------------------------------------------------------------------------- fit
 def _fit(fs, entry, variant, Qd, Kd, s, groups):
     """theta [groups, floats] on the host from either fit entry point."""
