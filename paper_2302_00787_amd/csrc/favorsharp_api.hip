@@ -42,7 +42,7 @@ bool groups_ok(int g, int B, int H) { return g == 1 || g == H || g == B * H; }
 
 struct AttnPlan {
   int pgroups, ldt, nseg, rows_per_seg;
-  size_t off_W, off_kpart, off_bias, off_kmax, off_rk, off_state, kcap, total;
+  size_t off_W, off_kpart, off_bias, off_kmax, off_rk, off_state, off_img, img_bytes, off_part, kcap, total;
 };
 
 // Every attention workspace starts with one 32-bit word (in a block of kAlign bytes): the number of output rows of the
@@ -68,6 +68,44 @@ void plan_contraction(int BH, int pgroups, int Lk, int d, int M, int nv1, int ca
   p->off_rk = off;   off = align_up(off + (size_t)BH * Lk * sizeof(float));       // key row terms (general attention kernels)
   p->off_state = off; off = align_up(off + (size_t)BH * p->nseg * M * p->ldt * sizeof(float));
   p->total = off;
+}
+
+// Causal calls on the bf16 matrix instructions (kernels_gen_split.hip): segments of their own, operand images of W~ (`copies`: 1, 2 for
+// gradients), rows between two launches.  `base` is the plan of the other kernels: no call that fits the scratch array with
+// that one stops fitting it.
+bool plan_split(int BH, int pgroups, int L, int d, int dv, int M, int dtype, int copies, const AttnPlan& base, AttnPlan* p) {
+  if (!(copies > 1 ? gen_split_backward(d, dv, M, dtype) : gen_split_attention(d, dv, M, dtype))) return false;
+  *p = base;
+  const GenSplitShape s = gen_split_shape(d, dv, M);
+  // one workgroup of eight waves per CU; the fewest chunks in sequence over one to four passes, a workgroup's start being two
+  const int slots = 256 * 8 / s.waves;
+  int best = 0;
+  for (int passes = 1; passes <= 4; ++passes) {
+    const int want = std::min(std::max(1, slots * passes / BH), ceil_div(L, 64));
+    const int rows = ceil_div(ceil_div(L, want), 32) * 32, nseg = ceil_div(L, rows);
+    const int steps = ceil_div(BH * nseg, slots) * (rows / 32 + 2);
+    if (passes == 1 || steps < best) {
+      best = steps;
+      p->rows_per_seg = rows;
+      p->nseg = nseg;
+    }
+  }
+  p->off_img = align_up(p->off_state + (size_t)BH * p->nseg * M * p->ldt * sizeof(float));
+  p->img_bytes = (size_t)pgroups * 2 * s.tiles * s.steps * 3 * 512 * sizeof(uint16_t);
+  p->off_part = align_up(p->off_img + copies * p->img_bytes);
+  p->total = align_up(p->off_part + (s.part ? (size_t)BH * L * gen_split_part_row(d, dv) * sizeof(float) : 0));
+  return copies > 1 || base.total > FS_NOALLOC_SCRATCH_BYTES || p->total <= FS_NOALLOC_SCRATCH_BYTES;
+}
+GenSplit split_of(const AttnPlan& p, char* ws, int d, int dv, int M, float scale, bool gradients) {
+  const GenSplitShape s = gen_split_shape(d, dv, M);
+  GenSplit g;
+  g.img = (uint16_t*)(ws + p.off_img);
+  if (gradients) g.img_t = (uint16_t*)(ws + p.off_img + p.img_bytes);
+  if (s.part) g.part = (float*)(ws + p.off_part);
+  g.tiles = s.tiles;
+  g.steps = s.steps;
+  g.scale = scale;
+  return g;
 }
 
 struct FitPlan {
@@ -370,6 +408,10 @@ size_t favorsharp_attention_workspace_bytes(int B, int H, int Lq, int Lk, int d,
   AttnPlan p;
   plan_contraction(B * H, std::max(groups, omega_groups), Lk, d, M, dv + 1, causal, &p);
   size_t total = p.total;
+  for (int dtype : {FS_F32, FS_BF16}) {
+    AttnPlan sp;
+    if (causal && plan_split(B * H, std::max(groups, omega_groups), Lk, d, dv, M, dtype, 1, p, &sp)) total = std::max(total, sp.total);
+  }
   if (fast_supported(FS_BF16, d, dv, M)) {      // the query does not know the dtype: cover both paths
     FastPlan fp;
     plan_fast(B * H, std::max(groups, omega_groups), Lk, &fp);
@@ -529,6 +571,9 @@ int attention_impl(const float* theta, int groups, const fs_tensor* Q, const fs_
   // beyond 32-bit offsets) recomputes them like favorsharp_attention
   AttnPlan p;
   plan_contraction(BH, pgroups, Lk, d, M, dv + 1, causal, &p);
+  AttnPlan sp;
+  const bool on_split = causal && plan_split(BH, pgroups, Lk, d, dv, M, Q->dtype, 1, p, &sp);
+  if (on_split) p = sp;
   const size_t lds_need = causal ? gen_lds_causal(d, p.ldt) : gen_lds_apply(d, p.ldt);
   if ((int)lds_need > lds_limit) return FS_ERR_UNSUPPORTED;
 
@@ -543,8 +588,9 @@ int attention_impl(const float* theta, int groups, const fs_tensor* Q, const fs_
 
   // (it clears the counter word and the key maxima behind it)
   unsigned* flushed = (unsigned*)ws;
+  const GenSplit split = on_split ? split_of(p, ws, d, dv, M, qk_scale, false) : GenSplit();
   if (int rc = launch_prep(theta, groups, Omega, omega_groups, pgroups, B, H, M, d, W, bias, (uint32_t*)ws,
-                           (int)(p.off_kmax / sizeof(uint32_t)) + BH, st))
+                           (int)(p.off_kmax / sizeof(uint32_t)) + BH, st, split))
     return rc;
   GenSide qs{dev(Q), qk_scale, 0.f, W, bias, theta, groups, pgroups, tf, (long long)(FS_THETA_HEADER + d + 2 * dd)};
   GenSide ks{dev(K), qk_scale, 0.f, W, bias, theta, groups, pgroups, tf, (long long)(FS_THETA_HEADER + d + 3 * dd)};
@@ -552,13 +598,19 @@ int attention_impl(const float* theta, int groups, const fs_tensor* Q, const fs_
   ks.kpart = (float*)(ws + p.off_kpart);
   ks.kcap = p.kcap;
   if (int rc = launch_gen_kmax(ks, Lk, BH, H, M, d, kmax, st)) return rc;
-  if (int rc = launch_gen_state(ks, dev(V), Lk, BH, H, M, d, dv, 1, p.ldt, p.rows_per_seg, p.nseg, kmax, nullptr, false, state, st))
+  int npart = 0;
+  const float* part = gen_kmax_part(ks, Lk, BH, d, &npart);
+  if (int rc = split.img ? launch_split_state(ks, split, true, dev(V), Lk, BH, H, M, d, dv, p.ldt, p.rows_per_seg, p.nseg, kmax, part, npart,
+                                              nullptr, state, st)
+                         : launch_gen_state(ks, dev(V), Lk, BH, H, M, d, dv, 1, p.ldt, p.rows_per_seg, p.nseg, kmax, nullptr, false, state, st))
     return rc;
   const size_t per_state = (size_t)M * p.ldt;
   if (int rc = launch_gen_reduce(state, BH, p.nseg, per_state, causal, st)) return rc;
   if (event_main_begin && hipEventRecord((hipEvent_t)event_main_begin, st) != hipSuccess) return FS_ERR_DEVICE;
   int rc;
-  if (causal && gen_walk_attention(d, dv, M, (long long)BH * p.nseg > 256))
+  if (split.img)
+    rc = launch_split_walk(qs, ks, split, dev(V), Lk, BH, H, M, d, dv, p.ldt, p.rows_per_seg, p.nseg, kmax, state, dev(Y), nullptr, nullptr, st, flushed);
+  else if (causal && gen_walk_attention(d, dv, M, (long long)BH * p.nseg > 256))
     rc = launch_gen_walk(qs, ks, dev(V), Lk, BH, H, M, d, dv, p.ldt, p.rows_per_seg, p.nseg, kmax, state, dev(Y), nullptr, nullptr, st, flushed);
   else if (causal)
     rc = launch_gen_causal(qs, ks, dev(V), Lk, BH, H, M, d, dv, p.ldt, p.rows_per_seg, p.nseg, kmax, state, dev(Y), nullptr, nullptr, st, flushed);
@@ -606,23 +658,27 @@ namespace {
 struct BwdPlan {
   AttnPlan k, q;           // key-side and query-side segmentations (the projection constants live in `k`)
   bool walks;              // causal calls: on the kernels that keep the state in registers
+  bool split;              // causal calls: on the bf16 matrix instructions
   size_t off_ghat, off_den, off_shift, off_rstate, off_state2, total;
 };
 
-void plan_backward(int BH, int pgroups, int Lq, int Lk, int d, int dv, int M, int causal, BwdPlan* p) {
+void plan_backward(int BH, int pgroups, int Lq, int Lk, int d, int dv, int M, int causal, int dtype, BwdPlan* p) {
   p->walks = causal && gen_walk_backward(d, dv, M, (long long)BH * ceil_div(Lk, 128) > 256);
   // A walk of few features is four waves, half of them padding, and a chain of chunks: with few sequences its length is what
   // the call waits for (us, 128 rows -> 32: f32 1 x 192 d80 M16 191 -> 96, 16 x 1024 261 -> 166; with the state in memory 171, 248).
   const bool short_segments = p->walks && M <= 64;
   plan_contraction(BH, pgroups, Lk, d, M, dv + 1, causal, &p->k, short_segments);
   plan_contraction(BH, pgroups, Lq, d, M, dv + 1, causal, &p->q, short_segments);
+  AttnPlan sp;
+  p->split = causal && plan_split(BH, pgroups, Lk, d, dv, M, dtype, 2, p->k, &sp);
+  if (p->split) p->k = p->q = sp;
   size_t off = p->k.total;
   p->off_ghat = off;   off = align_up(off + (size_t)BH * Lq * p->k.ldt * sizeof(float));
   p->off_den = off;    off = align_up(off + (size_t)BH * Lq * sizeof(float));
   p->off_shift = off;  off = align_up(off + (size_t)BH * Lq * sizeof(float));
   p->off_rstate = off; off = align_up(off + (size_t)BH * p->q.nseg * M * p->k.ldt * sizeof(float));
   // the kernels with the state in memory need the prefix states twice
-  p->off_state2 = off; off = align_up(off + (causal && !p->walks ? (size_t)BH * p->k.nseg * M * p->k.ldt * sizeof(float) : 0));
+  p->off_state2 = off; off = align_up(off + (causal && !p->walks && !p->split ? (size_t)BH * p->k.nseg * M * p->k.ldt * sizeof(float) : 0));
   p->total = off;
 }
 }  // namespace
@@ -655,9 +711,12 @@ size_t favorsharp_attention_backward_workspace_bytes(int B, int H, int Lq, int L
   if ((causal != 0 && causal != 1) || (causal && Lq != Lk)) return 0;
   if (!groups_ok(groups, B, H) || !groups_ok(omega_groups, B, H)) return 0;
   BwdPlan p;
-  plan_backward(B * H, std::max(groups, omega_groups), Lq, Lk, d, dv, M, causal, &p);
-  size_t total = p.total;
-  if (fast_supported(FS_BF16, d, dv, M)) {      // the query does not know the dtype: cover both paths
+  size_t total = 0;      // the query does not know the dtype: cover all paths
+  for (int dtype : {FS_F32, FS_BF16}) {
+    plan_backward(B * H, std::max(groups, omega_groups), Lq, Lk, d, dv, M, causal, dtype, &p);
+    total = std::max(total, p.total);
+  }
+  if (fast_supported(FS_BF16, d, dv, M)) {
     FastBwdPlan fp;
     plan_fast_backward(B * H, std::max(groups, omega_groups), Lq, Lk, causal, &fp);
     total = std::max(total, fp.total);
@@ -714,7 +773,7 @@ int attention_backward_impl(const float* theta, int groups, const fs_tensor* Q, 
                                           (float*)(w8 + fp.off_rpart), (float*)(w8 + fp.off_rcpart), fp.rslots, (hipStream_t)stream);
   }
   BwdPlan p;
-  plan_backward(BH, pgroups, Lq, Lk, d, dv, M, causal, &p);
+  plan_backward(BH, pgroups, Lq, Lk, d, dv, M, causal, Q->dtype, &p);
   const int ldt = p.k.ldt;
   const size_t lds_need = causal ? std::max(gen_lds_causal(d, ldt), gen_lds_bwd_causal(d, ldt))
                                  : std::max(gen_lds_apply(d, ldt), gen_lds_bwd_side(d, ldt));
@@ -738,21 +797,29 @@ int attention_backward_impl(const float* theta, int groups, const fs_tensor* Q, 
   // denominators and the query shifts
   // (it clears the counter word and the key maxima behind it)
   unsigned* flushed = (unsigned*)ws;
+  const GenSplit split = p.split ? split_of(p.k, ws, d, dv, M, qk_scale, true) : GenSplit();
   if (int rc = launch_prep(theta, groups, Omega, omega_groups, pgroups, B, H, M, d, W, bias, (uint32_t*)ws,
-                           (int)(p.k.off_kmax / sizeof(uint32_t)) + BH, st))
+                           (int)(p.k.off_kmax / sizeof(uint32_t)) + BH, st, split))
     return rc;
   GenSide qs{dev(Q), qk_scale, 0.f, W, bias, theta, groups, pgroups, tf, (long long)(FS_THETA_HEADER + d + 2 * dd)};
   GenSide ks{dev(K), qk_scale, 0.f, W, bias, theta, groups, pgroups, tf, (long long)(FS_THETA_HEADER + d + 3 * dd)};
   ks.rk = (float*)(ws + p.k.off_rk);      // the key row terms are evaluated once (k_gen_kmax) and read by the kernels after it
   ks.kpart = (float*)(ws + p.k.off_kpart);
   ks.kcap = p.k.kcap;
-  const bool walks = p.walks;
+  const bool walks = p.walks && !split.img;
+  int npart = 0;
+  const float* part = gen_kmax_part(ks, Lk, BH, d, &npart);
   if (int rc = launch_gen_kmax(ks, Lk, BH, H, M, d, kmax, st)) return rc;
-  if (int rc = launch_gen_state(ks, dev(V), Lk, BH, H, M, d, dv, 1, ldt, p.k.rows_per_seg, p.k.nseg, kmax, nullptr, !walks, state, st))
+  if (int rc = split.img ? launch_split_state(ks, split, true, dev(V), Lk, BH, H, M, d, dv, ldt, p.k.rows_per_seg, p.k.nseg, kmax, part, npart,
+                                              nullptr, state, st)
+                         : launch_gen_state(ks, dev(V), Lk, BH, H, M, d, dv, 1, ldt, p.k.rows_per_seg, p.k.nseg, kmax, nullptr, !walks, state, st))
     return rc;
   if (int rc = launch_gen_reduce(state, BH, p.k.nseg, per_state, causal, st)) return rc;
   const TensorDev gbuf{ghat, 0, (long long)H * Lq * ldt, (long long)Lq * ldt, (long long)ldt};
-  if (walks) {
+  if (split.img) {
+    if (int rc = launch_split_walk(qs, ks, split, dev(V), Lk, BH, H, M, d, dv, ldt, p.k.rows_per_seg, p.k.nseg, kmax, state, gbuf, den, shift, st, flushed))
+      return rc;
+  } else if (walks) {
     if (int rc = launch_gen_walk(qs, ks, dev(V), Lk, BH, H, M, d, dv, ldt, p.k.rows_per_seg, p.k.nseg, kmax, state, gbuf, den, shift, st, flushed))
       return rc;
   } else if (causal) {
@@ -769,9 +836,14 @@ int attention_backward_impl(const float* theta, int groups, const fs_tensor* Q, 
   }
   // G1 in place of Y, then the segment sums of P^T G1 (the query-side twin of the state pass)
   if (int rc = launch_bwd_ghat(dev(dY), ghat, den, Lq, BH, H, dv, ldt, st)) return rc;
-  if (int rc = launch_gen_state(qs, gbuf, Lq, BH, H, M, d, ldt, 0, ldt, p.q.rows_per_seg, p.q.nseg, kmax, shift, !walks, rstate, st))
+  if (int rc = split.img ? launch_split_state(qs, split, false, gbuf, Lq, BH, H, M, d, dv, ldt, p.q.rows_per_seg, p.q.nseg, kmax, nullptr, 0, shift,
+                                              rstate, st)
+                         : launch_gen_state(qs, gbuf, Lq, BH, H, M, d, ldt, 0, ldt, p.q.rows_per_seg, p.q.nseg, kmax, shift, !walks, rstate, st))
     return rc;
   if (int rc = launch_gen_reduce(rstate, BH, p.q.nseg, per_state, causal ? 2 : 0, st)) return rc;
+  if (split.img)
+    return launch_split_bwd_walks(qs, ks, split, dev(V), ghat, Lk, BH, H, M, d, dv, ldt, p.k.rows_per_seg, p.k.nseg, kmax, shift, state, rstate,
+                                  dev(dQ), dev(dK), dev(dV), st);
   if (walks)
     return launch_gen_bwd_walks(qs, ks, dev(V), ghat, Lk, BH, H, M, d, dv, ldt, p.k.rows_per_seg, p.k.nseg, kmax, shift, state, rstate,
                                 dev(dQ), dev(dK), dev(dV), st);

@@ -38,8 +38,18 @@ size_t gen_lds_apply(int d, int ldt);
 size_t gen_lds_causal(int d, int ldt);
 size_t gen_lds_stats(int d);
 
+// Operand images of the projection matrices in bf16 pieces (kernels_gen_split.hip): W~ times qk_scale for `tiles` tiles of 16
+// features and `steps` steps of 32 coordinates; img_t, for the gradients only, by coordinate.
+struct GenSplit {
+  uint16_t* img = nullptr;
+  uint16_t* img_t = nullptr;
+  float* part = nullptr;   // [B*H][rows][gen_split_part_row] of the first of two launches
+  int tiles = 0, steps = 0;
+  float scale = 1.f;
+};
+// clear[0 .. nclear) = 0
 int launch_prep(const float* theta, int groups, const float* Omega, int omega_groups, int pgroups, int B, int H,
-                int M, int d, float* W, float* bias, uint32_t* clear, int nclear, hipStream_t st);   // clear[0 .. nclear) = 0
+                int M, int d, float* W, float* bias, uint32_t* clear, int nclear, hipStream_t st, const GenSplit& split = GenSplit());
 int launch_fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t st);
 int launch_gen_features(const TensorDev& X, int n, int d, float scale, float alpha, const float* W, const float* bias,
                         const float* theta, long long c_offset, int M, float* out, float* row_logscale,
@@ -80,6 +90,23 @@ int launch_gen_bwd_walks(const GenSide& qs, const GenSide& ks, const TensorDev& 
                          int nv, int ldt, int rows_per_seg, int nseg, const uint32_t* kmax_u, const float* row_shift,
                          const float* Tstate, const float* Rstate, const TensorDev& dQ, const TensorDev& dK, const TensorDev& dV,
                          hipStream_t st);
+// Causal calls on bf16 matrix instructions with fp32 accuracy (kernels_gen_split.hip).
+struct GenSplitShape { int tiles, steps; bool part; int waves; };
+int gen_split_part_row(int d, int dv);
+bool gen_split_attention(int d, int dv, int M, int dtype);
+bool gen_split_backward(int d, int dv, int M, int dtype);
+GenSplitShape gen_split_shape(int d, int dv, int M);
+int launch_split_state(const GenSide& side, const GenSplit& sp, bool keys, const TensorDev& V, int L, int BH, int H, int M, int d, int nv,
+                       int ldt, int rows_per_seg, int nseg, uint32_t* kmax_u, const float* part, int npart, const float* row_shift,
+                       float* state, hipStream_t st);
+int launch_split_walk(const GenSide& qs, const GenSide& ks, const GenSplit& sp, const TensorDev& V, int L, int BH, int H, int M, int d,
+                      int nv, int ldt, int rows_per_seg, int nseg, uint32_t* kmax_u, float* Tstate, const TensorDev& Y, float* den_out,
+                      float* shift_out, hipStream_t st, unsigned* flushed);
+int launch_split_bwd_walks(const GenSide& qs, const GenSide& ks, const GenSplit& sp, const TensorDev& V, const float* ghat, int L, int BH,
+                           int H, int M, int d, int nv, int ldt, int rows_per_seg, int nseg, uint32_t* kmax_u, const float* row_shift,
+                           float* Tstate, float* Rstate, const TensorDev& dQ, const TensorDev& dK, const TensorDev& dV, hipStream_t st);
+// Partial key maxima that k_gen_kmax leaves: where (nullptr: the maximum itself in kmax_u) and how many per sequence.
+const float* gen_kmax_part(const GenSide& ks, int Lk, int BH, int d, int* npart);
 bool stats_bf16_supported(const TensorDev& X, const TensorDev& Y, int d);
 int launch_stats_bf16(const TensorDev& X, const TensorDev& Y, int BH, int H, int Lx, int Ly, float scale,
                       int rows_per_chunk, int nchunks, float* part, hipStream_t st);

@@ -365,6 +365,11 @@ static float* kmax_part(const GenSide& ks, int Lk, int BH, int d) {
   return ks.kpart != nullptr && (size_t)BH * n <= ks.kcap ? ks.kpart : nullptr;
 }
 
+const float* gen_kmax_part(const GenSide& ks, int Lk, int BH, int d, int* npart) {
+  *npart = (Lk + kmax_rows(d) - 1) / kmax_rows(d);
+  return kmax_part(ks, Lk, BH, d);
+}
+
 int launch_gen_kmax(const GenSide& ks, int Lk, int BH, int H, int M, int d, uint32_t* kmax_u, hipStream_t st) {
   return by_width(d, 0, [&](auto width) -> int {
     constexpr int Q = width(), TR = 16 * KMAX_T<Q>;

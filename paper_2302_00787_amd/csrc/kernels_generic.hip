@@ -11,6 +11,7 @@
 
 #include "fs_common.h"
 #include "kernels.h"
+#include "split3.h"
 
 namespace fs {
 
@@ -326,7 +327,7 @@ __device__ void rowmax_pass2(uint32_t* rowmax_u, const float* Xs, float* Ws, flo
 // ---------------------------------------------------------------------------------------------------
 constexpr int PREP_F = 4;
 __global__ void __launch_bounds__(128) k_prep(const float* theta, int groups, const float* Omega, int omega_groups, int pgroups,
-                       int B, int H, int M, int d, float* W, float* bias, uint32_t* clear, int nclear) {
+                       int B, int H, int M, int d, float* W, float* bias, uint32_t* clear, int nclear, GenSplit split) {
   __shared__ float om[PREP_F][128];
   const int m0 = blockIdx.x * PREP_F, side = blockIdx.y, pg = blockIdx.z, nf = min(PREP_F, M - m0);
   int b = 0, h = 0;
@@ -343,10 +344,10 @@ __global__ void __launch_bounds__(128) k_prep(const float* theta, int groups, co
 #pragma unroll
   for (int f = 0; f < PREP_F; ++f) om[f][c] = (f < nf && c < d) ? omg[(size_t)f * d + c] : 0.f;
   __syncthreads();
-  if (c < d) {
-    float acc[PREP_F];
+  float acc[PREP_F];
 #pragma unroll
-    for (int f = 0; f < PREP_F; ++f) acc[f] = 0.f;
+  for (int f = 0; f < PREP_F; ++f) acc[f] = 0.f;
+  if (c < d) {
     int l = 0;
     for (; l + 8 <= d; l += 8) {
       float bv[8];
@@ -368,6 +369,18 @@ __global__ void __launch_bounds__(128) k_prep(const float* theta, int groups, co
         const float v = acc[f] * kLog2e;
         W[(o + f) * d + c] = v;
       }
+  }
+  if (split.img != nullptr && c < 32 * split.steps) {      // (zero past the features and past the row)
+    const size_t base = ((size_t)pg * 2 + side) * split.tiles * split.steps * 3 * 512;
+#pragma unroll
+    for (int f = 0; f < PREP_F; ++f) {
+      const int m = m0 + f, tile = m >> 4, i = m & 15;
+      const float v = acc[f] * kLog2e * split.scale;
+      split3_store(split.img + base + ((size_t)tile * split.steps + (c >> 5)) * 3 * 512 + ((c & 31) / 8 * 16 + i) * 8 + (c & 7), 512, v);
+      if (split.img_t != nullptr)
+        split3_store(split.img_t + base + ((size_t)(tile >> 1) * 2 * split.steps + (c >> 4)) * 3 * 512 + (i / 4 * 16 + (c & 15)) * 8 +
+                         4 * (tile & 1) + (i & 3), 512, v);
+    }
   }
   if (c < nf) {
     const float* A = th + FS_THETA_HEADER_;
@@ -1465,9 +1478,10 @@ static int by_width(int d, int ldt, F launch) {
 }
 
 int launch_prep(const float* theta, int groups, const float* Omega, int omega_groups, int pgroups, int B, int H,
-                int M, int d, float* W, float* bias, uint32_t* clear, int nclear, hipStream_t st) {
-  hipLaunchKernelGGL(k_prep, dim3((M + PREP_F - 1) / PREP_F, 2, pgroups), dim3(128), 0, st, theta, groups, Omega, omega_groups, pgroups, B, H,
-                     M, d, W, bias, clear, nclear);
+                int M, int d, float* W, float* bias, uint32_t* clear, int nclear, hipStream_t st, const GenSplit& split) {
+  const int features = split.img != nullptr ? 16 * split.tiles : M;
+  hipLaunchKernelGGL(k_prep, dim3((features + PREP_F - 1) / PREP_F, 2, pgroups), dim3(128), 0, st, theta, groups, Omega, omega_groups, pgroups, B, H,
+                     M, d, W, bias, clear, nclear, split);
   FS_LAUNCH_CHECK();
   return 0;
 }

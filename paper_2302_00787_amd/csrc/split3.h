@@ -35,6 +35,16 @@ __device__ __forceinline__ f32x4 mfma3(const Split3& a, const Split3& b, f32x4 c
   return mfma_bf16(a.h, b.h, c);
 }
 
+// The same for the transposed product: the pieces in the order of mfma3(b, a, .), so that both round alike.
+__device__ __forceinline__ f32x4 mfma3_t(const Split3& a, const Split3& b, f32x4 c) {
+  c = mfma_bf16(a.h, b.l, c);
+  c = mfma_bf16(a.l, b.h, c);
+  c = mfma_bf16(a.m, b.m, c);
+  c = mfma_bf16(a.h, b.m, c);
+  c = mfma_bf16(a.m, b.h, c);
+  return mfma_bf16(a.h, b.h, c);
+}
+
 // Piece p (0, 1, 2) of a number, for operand images written number by number.
 __device__ __forceinline__ void split3_store(uint16_t* at, size_t piece_stride, float v) {
   const uint16_t h = f32_to_bf16_bits(v);
