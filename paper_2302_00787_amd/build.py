@@ -18,6 +18,7 @@ SOURCES = {
     "favorsharp_api.hip": [],
     "kernels_generic.hip": [],
     "kernels_gen_walk.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+    "kernels_gen_small.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "kernels_gen_split.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "kernels_gen_rows.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "kernels_bf16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-mllvm", "-amdgpu-atomic-optimizer-strategy=None"],

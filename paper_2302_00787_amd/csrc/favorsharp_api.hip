@@ -586,8 +586,15 @@ int attention_impl(const float* theta, int groups, const fs_tensor* Q, const fs_
   const size_t dd = (size_t)d * d;
   const long long tf = (long long)favorsharp_theta_floats(d);
 
-  // (it clears the counter word and the key maxima behind it)
   unsigned* flushed = (unsigned*)ws;
+  if (!causal && gen_small_supported(BH, Lk, d, dv, M)) {
+    if (event_main_begin && hipEventRecord((hipEvent_t)event_main_begin, st) != hipSuccess) return FS_ERR_DEVICE;
+    if (int rc = launch_gen_small(dev(Q), dev(K), dev(V), dev(Y), theta, groups, Omega, omega_groups, BH, H, Lq, Lk, d, dv, M, qk_scale, flushed, st))
+      return rc;
+    if (event_main_end && hipEventRecord((hipEvent_t)event_main_end, st) != hipSuccess) return FS_ERR_DEVICE;
+    return FS_OK;
+  }
+  // (it clears the counter word and the key maxima behind it)
   const GenSplit split = on_split ? split_of(p, ws, d, dv, M, qk_scale, false) : GenSplit();
   if (int rc = launch_prep(theta, groups, Omega, omega_groups, pgroups, B, H, M, d, W, bias, (uint32_t*)ws,
                            (int)(p.off_kmax / sizeof(uint32_t)) + BH, st, split))

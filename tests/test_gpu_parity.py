@@ -289,6 +289,37 @@ def test_attention_empty_query_set_and_error_paths(fs):
     assert e.value.status == 4
 
 
+@pytest.mark.parametrize("d,dv,M,Lq,Lk,B,H", [(4, 4, 1, 1, 1, 1, 1), (8, 31, 17, 130, 255, 1, 1), (16, 16, 64, 300, 256, 2, 3), (20, 47, 33, 15, 17, 3, 1),
+                                              (32, 32, 64, 256, 240, 1, 2), (28, 5, 48, 129, 128, 2, 2), (16, 24, 32, 16, 16, 1, 1)])
+@pytest.mark.parametrize("dtype,variant", [("f32", "saderf"), ("f32", "gerf"), ("bf16", "saderf")])
+def test_attention_of_short_sequences_in_one_launch(fs, d, dv, M, Lq, Lk, B, H, dtype, variant):
+    """Non-causal calls that one workgroup per sequence takes: remainders of tokens, coordinates, value columns and features, from
+    one key to the most there can be, more queries than keys and fewer, one sequence (which writes the counter of zero
+    normalisers itself) and several.  1e-4, the file's bar, on the same inputs in float64."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(d + M + Lk)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+
+    def rows(L, n, scale):
+        return (scale * torch.randn((B, H, L, (n + 7) // 8 * 8), generator=gen, device="cuda")).to(dt)[..., :n]
+    Q, K, V = rows(Lq, d, 0.7), rows(Lk, d, 0.7), rows(Lk, dv, 1.0)
+    Om = torch.randn((H, M, d), generator=gen, device="cuda")
+    rng = np.random.default_rng(d)
+    theta = util.theta_vec_from_oracle(orc.fit(variant, 0.5 * rng.standard_normal((400, d)), 0.4 * rng.standard_normal((400, d))))
+    th, s = util.oracle_theta_from_vec(theta, d), d ** -0.25
+    Y = torch.full((B, H, Lq, (dv + 7) // 8 * 8), float("nan"), device="cuda")[..., :dv]
+    ws = torch.full((fs.attention_workspace_bytes(B, H, Lq, Lk, d, dv, M, False, 1, H),), 255, dtype=torch.uint8, device="cuda")
+    fs.attention(torch.from_numpy(theta[None]).cuda(), Q, K, V, s, Om, out=Y, workspace=ws)
+    A, B1, B2, C2 = (torch.from_numpy(np.asarray(x, dtype=np.float64)).cuda() for x in (th.A, th.B1, th.B2, th.C2))
+    q, k, v, om = s * Q.double(), s * K.double(), V.double(), Om.double()
+    bias = ((om * om) @ A)[None, :, None]
+    E1, E2 = q @ (om @ B1).transpose(1, 2) + bias, k @ (om @ B2).transpose(1, 2) + bias + ((k @ C2) * k).sum(-1, keepdim=True)
+    W = torch.exp(E1 - E1.amax(-1, keepdim=True)) @ torch.exp(E2 - E2.amax((2, 3), keepdim=True)).transpose(2, 3)
+    ref = (W @ v) / W.sum(-1, keepdim=True)
+    assert float((Y.double() - ref).norm() / ref.norm()) <= 1e-4
+    assert int(ws[:4].view(torch.int32)) == 0
+
+
 # ----------------------------------------------------------------------------- kernel operator
 @pytest.mark.parametrize("variant", ["sderf", "aderf"])
 def test_kernel_matvec_small(fs, variant):
