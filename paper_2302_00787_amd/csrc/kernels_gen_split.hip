@@ -114,7 +114,7 @@ template <int COLS, int NW, int P> struct Fetch {
       } else {
         f32x4 x = __builtin_bit_cast(f32x4, v[i]);
         x = in ? x : f32x4{one ? 1.f : 0.f, 0.f, 0.f, 0.f};
-        const Split3 q = split3(x, x);
+        const Split3 q = split3_each(x, x);
         const u32x4 h = __builtin_bit_cast(u32x4, q.h), m = __builtin_bit_cast(u32x4, q.m), l = __builtin_bit_cast(u32x4, q.l);
         *(u32x2*)at = u32x2{h[0], h[1]};
         *(u32x2*)(at + PLANE) = u32x2{m[0], m[1]};

@@ -13,7 +13,38 @@ typedef __attribute__((ext_vector_type(8))) float f32x8_t;
 
 struct Split3 { bf16x8 h, m, l; };
 
+typedef __attribute__((ext_vector_type(2))) float f32x2_t;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
+
+// x less its first piece, for two numbers: the dot product of their pieces with (-1, 0) or (0, -1), which is exact.  (Seven instructions
+// for the pieces of two numbers where shifts and subtractions take eleven.  A number that is not finite makes its neighbour NaN:
+// for numbers that are summed anyway.  The pairs are kept in registers: as an inline constant of the instruction the first one is
+// read as the second.)
+__device__ __forceinline__ f32x2_t less_piece(f32x2_t x, bf16x2_t h) {
+  uint32_t low = 0xbf80u, high = 0xbf800000u;
+  asm("" : "+s"(low));
+  asm("" : "+s"(high));
+  return f32x2_t{__builtin_amdgcn_fdot2_f32_bf16(h, __builtin_bit_cast(bf16x2_t, low), x[0], false),
+                 __builtin_amdgcn_fdot2_f32_bf16(h, __builtin_bit_cast(bf16x2_t, high), x[1], false)};
+}
 __device__ __forceinline__ Split3 split3(f32x4 a, f32x4 b) {
+  const f32x2_t x[4] = {{a[0], a[1]}, {a[2], a[3]}, {b[0], b[1]}, {b[2], b[3]}};
+  bf16x2_t h[4], m[4], l[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    h[i] = __builtin_convertvector(x[i], bf16x2_t);
+    const f32x2_t r = less_piece(x[i], h[i]);
+    m[i] = __builtin_convertvector(r, bf16x2_t);
+    l[i] = __builtin_convertvector(less_piece(r, m[i]), bf16x2_t);
+  }
+  auto join = [](const bf16x2_t (&v)[4]) {
+    return __builtin_bit_cast(bf16x8, u32x4{__builtin_bit_cast(uint32_t, v[0]), __builtin_bit_cast(uint32_t, v[1]), __builtin_bit_cast(uint32_t, v[2]),
+                                            __builtin_bit_cast(uint32_t, v[3])});
+  };
+  return {join(h), join(m), join(l)};
+}
+// The same number by number (numbers of different rows or columns of a result).
+__device__ __forceinline__ Split3 split3_each(f32x4 a, f32x4 b) {
   const f32x8_t x = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
   Split3 s;
   s.h = __builtin_convertvector(x, bf16x8);
