@@ -604,7 +604,7 @@ int attention_impl(const float* theta, int groups, const fs_tensor* Q, const fs_
   ks.rk = (float*)(ws + p.off_rk);      // the key row terms are evaluated once (k_gen_kmax) and read by the kernels after it
   ks.kpart = (float*)(ws + p.off_kpart);
   ks.kcap = p.kcap;
-  if (int rc = launch_gen_kmax(ks, Lk, BH, H, M, d, kmax, st)) return rc;
+  if (int rc = launch_gen_kmax(ks, Lk, BH, H, M, d, kmax, st, split)) return rc;
   int npart = 0;
   const float* part = gen_kmax_part(ks, Lk, BH, d, &npart);
   if (int rc = split.img ? launch_split_state(ks, split, true, dev(V), Lk, BH, H, M, d, dv, p.ldt, p.rows_per_seg, p.nseg, kmax, part, npart,
@@ -816,7 +816,7 @@ int attention_backward_impl(const float* theta, int groups, const fs_tensor* Q, 
   const bool walks = p.walks && !split.img;
   int npart = 0;
   const float* part = gen_kmax_part(ks, Lk, BH, d, &npart);
-  if (int rc = launch_gen_kmax(ks, Lk, BH, H, M, d, kmax, st)) return rc;
+  if (int rc = launch_gen_kmax(ks, Lk, BH, H, M, d, kmax, st, split)) return rc;
   if (int rc = split.img ? launch_split_state(ks, split, true, dev(V), Lk, BH, H, M, d, dv, ldt, p.k.rows_per_seg, p.k.nseg, kmax, part, npart,
                                               nullptr, state, st)
                          : launch_gen_state(ks, dev(V), Lk, BH, H, M, d, dv, 1, ldt, p.k.rows_per_seg, p.k.nseg, kmax, nullptr, !walks, state, st))

@@ -54,7 +54,7 @@ int launch_fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t st);
 int launch_gen_features(const TensorDev& X, int n, int d, float scale, float alpha, const float* W, const float* bias,
                         const float* theta, long long c_offset, int M, float* out, float* row_logscale,
                         hipStream_t st);
-int launch_gen_kmax(const GenSide& ks, int Lk, int BH, int H, int M, int d, uint32_t* kmax_u, hipStream_t st);
+int launch_gen_kmax(const GenSide& ks, int Lk, int BH, int H, int M, int d, uint32_t* kmax_u, hipStream_t st, const GenSplit& split = GenSplit());
 int launch_gen_state(const GenSide& ks, const TensorDev& V, int Lk, int BH, int H, int M, int d, int nv,
                      int append_ones, int ldt, int rows_per_seg, int nseg, uint32_t* kmax_u,
                      const float* row_shift, bool tiles, float* Tpart, hipStream_t st);

@@ -12,6 +12,7 @@
 
 #include "gen_widths.h"
 #include "kernels.h"
+#include "split3.h"
 
 namespace fs {
 namespace {
@@ -89,8 +90,10 @@ __device__ __forceinline__ f32x4 lane_rows_transposed(f32x4 v) {
 // B8 H8 L300 d128 M200 378 us for the call, now 258).  Then every fourth tile of 16 features.  grid (tokens, B*H), block 256.
 // ---------------------------------------------------------------------------------------------------
 template <int Q> constexpr int KMAX_T = Q >= 6 ? 2 : 4;      // token tiles per workgroup
-template <int Q, int XB, int D4>
-__global__ void __launch_bounds__(256, 2) k_gen_kmax(GenSide ks, int Lk, int H, int M, int d, uint32_t* kmax_u, float* part) {
+// SP: the projection on bf16 pieces (split3.h), W~ from the images of the kernels behind (bf16 B1 H16 L4096 d128 M512 92 -> 66 us, f32
+// B2 H4 L4096 d64 M256 17.2 -> 14.7).
+template <int Q, int XB, int D4, int SP>
+__global__ void __launch_bounds__(256, 2) k_gen_kmax(GenSide ks, int Lk, int H, int M, int d, uint32_t* kmax_u, float* part, GenSplit split) {
   constexpr int TT = KMAX_T<Q>;
   __shared__ __align__(16) float rpart[4][16 * TT];
   __shared__ float wmax[4];
@@ -111,7 +114,7 @@ __global__ void __launch_bounds__(256, 2) k_gen_kmax(GenSide ks, int Lk, int H, 
   for (int t = 0; t < TT; ++t) fetch_row<D4>(raw[t], ks.X, xbase + (long long)min(row0 + 16 * t + c, Lk - 1) * ks.X.sl, d, g);
   const int nft = (M + 15) / 16;
   RawRow<0, Q> wn;
-  fetch_row<D4>(wn, W, (long long)min(16 * w + c, M - 1) * d, d, g);
+  if (!SP) fetch_row<D4>(wn, W, (long long)min(16 * w + c, M - 1) * d, d, g);
   float bn = bias[min(16 * w + c, M - 1)];
   f32x4 x[TT][Q];
 #pragma unroll
@@ -191,27 +194,85 @@ __global__ void __launch_bounds__(256, 2) k_gen_kmax(GenSide ks, int Lk, int H, 
       rt[t][r] = row < Lk ? kLog2e * rt[t][r] : -INFINITY;
     }
   float m = -INFINITY;
-  for (int ft = w; ft < nft; ft += 4) {
-    f32x4 acc[TT];
+  if constexpr (SP) {
+    constexpr int KS = (Q + 1) / 2;
+    typedef typename std::conditional<XB, bf16x8, Split3>::type XOp;
+    XOp xo[TT][KS];
 #pragma unroll
-    for (int t = 0; t < TT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    f32x4 wr[Q];
+    for (int t = 0; t < TT; ++t) {
+      const long long at = xbase + (long long)min(row0 + 16 * t + c, Lk - 1) * ks.X.sl;
 #pragma unroll
-    for (int q = 0; q < Q; ++q) wr[q] = row_group(wn, q, one[q]);
-    const float bf = 16 * ft + c < M ? bn : -INFINITY;
-    const int fn = min(16 * (ft + 4) + c, M - 1);       // the next tile's row travels meanwhile
-    fetch_row<D4>(wn, W, (long long)fn * d, d, g);
-    bn = bias[fn];
+      for (int k = 0; k < KS; ++k) {         // (past the row W~ is zero)
+        const int c0 = min(32 * k + 8 * g, d - 4), c1 = min(32 * k + 8 * g + 4, d - 4);
+        if constexpr (XB) {
+          const u32x2 lo = *(const u32x2*)((const uint16_t*)ks.X.ptr + at + c0), hi = *(const u32x2*)((const uint16_t*)ks.X.ptr + at + c1);
+          xo[t][k] = __builtin_bit_cast(bf16x8, u32x4{lo[0], lo[1], hi[0], hi[1]});
+        } else {
+          xo[t][k] = split3(*(const f32x4*)((const float*)ks.X.ptr + at + c0), *(const f32x4*)((const float*)ks.X.ptr + at + c1));
+        }
+      }
+    }
+    const uint16_t* img = split.img + ((size_t)pg * 2 + 1) * split.tiles * split.steps * 3 * 512 + 8 * lane;
+    auto image = [&](Split3 (&o)[KS], int ft) {
 #pragma unroll
-    for (int q = 0; q < Q; ++q)
+      for (int k = 0; k < KS; ++k) {
+        const uint16_t* p = img + ((size_t)ft * split.steps + k) * 3 * 512;
+        o[k] = {*(const bf16x8*)p, *(const bf16x8*)(p + 512), *(const bf16x8*)(p + 1024)};
+      }
+    };
+    Split3 wn[KS];
+    image(wn, min(w, nft - 1));
+    for (int ft = w; ft < nft; ft += 4) {
+      f32x4 acc[TT];
 #pragma unroll
-      for (int s = 0; s < 4; ++s)
+      for (int t = 0; t < TT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+      Split3 wr[KS];
 #pragma unroll
-        for (int t = 0; t < TT; ++t) acc[t] = mfma4(x[t][q][s], wr[q][s], acc[t]);
+      for (int k = 0; k < KS; ++k) wr[k] = wn[k];
+      const float bf = 16 * ft + c < M ? bn : -INFINITY;
+      const int fn = min(ft + 4, nft - 1);   // the next tile's operands travel meanwhile
+      image(wn, fn);
+      bn = bias[min(16 * fn + c, M - 1)];
 #pragma unroll
-    for (int t = 0; t < TT; ++t)
+      for (int k = 0; k < KS; ++k)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) m = fmaxf(m, acc[t][r] + bf + rt[t][r]);
+        for (int t = 0; t < TT; ++t) {
+          if constexpr (XB) {
+            acc[t] = mfma_bf16(xo[t][k], wr[k].l, acc[t]);
+            acc[t] = mfma_bf16(xo[t][k], wr[k].m, acc[t]);
+            acc[t] = mfma_bf16(xo[t][k], wr[k].h, acc[t]);
+          } else {
+            acc[t] = mfma3_t(xo[t][k], wr[k], acc[t]);
+          }
+        }
+#pragma unroll
+      for (int t = 0; t < TT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) m = fmaxf(m, acc[t][r] + bf + rt[t][r]);
+    }
+  } else {
+    for (int ft = w; ft < nft; ft += 4) {
+      f32x4 acc[TT];
+#pragma unroll
+      for (int t = 0; t < TT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+      f32x4 wr[Q];
+#pragma unroll
+      for (int q = 0; q < Q; ++q) wr[q] = row_group(wn, q, one[q]);
+      const float bf = 16 * ft + c < M ? bn : -INFINITY;
+      const int fn = min(16 * (ft + 4) + c, M - 1);       // the next tile's row travels meanwhile
+      fetch_row<D4>(wn, W, (long long)fn * d, d, g);
+      bn = bias[fn];
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int t = 0; t < TT; ++t) acc[t] = mfma4(x[t][q][s], wr[q][s], acc[t]);
+#pragma unroll
+      for (int t = 0; t < TT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) m = fmaxf(m, acc[t][r] + bf + rt[t][r]);
+    }
   }
 #pragma unroll
   for (int s = 1; s < 64; s <<= 1) m = fmaxf(m, __shfl_xor(m, s));
@@ -370,11 +431,15 @@ const float* gen_kmax_part(const GenSide& ks, int Lk, int BH, int d, int* npart)
   return kmax_part(ks, Lk, BH, d);
 }
 
-int launch_gen_kmax(const GenSide& ks, int Lk, int BH, int H, int M, int d, uint32_t* kmax_u, hipStream_t st) {
+int launch_gen_kmax(const GenSide& ks, int Lk, int BH, int H, int M, int d, uint32_t* kmax_u, hipStream_t st, const GenSplit& split) {
   return by_width(d, 0, [&](auto width) -> int {
     constexpr int Q = width(), TR = 16 * KMAX_T<Q>;
-    auto kernel = d % 4 ? (ks.X.dtype ? k_gen_kmax<Q, 1, 0> : k_gen_kmax<Q, 0, 0>) : (ks.X.dtype ? k_gen_kmax<Q, 1, 1> : k_gen_kmax<Q, 0, 1>);
-    hipLaunchKernelGGL(kernel, dim3((Lk + TR - 1) / TR, BH), dim3(256), 0, st, ks, Lk, H, M, d, kmax_u, kmax_part(ks, Lk, BH, d));
+    auto kernel = d % 4 ? (ks.X.dtype ? k_gen_kmax<Q, 1, 0, 0> : k_gen_kmax<Q, 0, 0, 0>) : (ks.X.dtype ? k_gen_kmax<Q, 1, 1, 0> : k_gen_kmax<Q, 0, 1, 0>);
+    if (split.img != nullptr) {
+      if (ks.X.dtype) kernel = k_gen_kmax<Q, 1, 1, 1>;
+      else if constexpr (Q < 6) kernel = k_gen_kmax<Q, 0, 1, 1>;
+    }
+    hipLaunchKernelGGL(kernel, dim3((Lk + TR - 1) / TR, BH), dim3(256), 0, st, ks, Lk, H, M, d, kmax_u, kmax_part(ks, Lk, BH, d), split);
     FS_LAUNCH_CHECK();
     return 0;
   });
