@@ -9,9 +9,9 @@
 // and value rows are read in that order with the transposing LDS read.
 //
 // What bounds it: the matrix pipe needs 96 cycles for 16 x 16 x 32 numbers (48 against bf16 tensors; fp32 instructions 256), splitting an
-// accumulator pair 44 vector instructions; W~ is 6 bytes per feature and coordinate and chunk from L2.  Two waves per SIMD overlap the two
-// pipes about half.  Against fp32 instructions: causal attention f32 B2 H4 L4096 d64 M256 147 -> 108 us (walk 87 -> 61, states 38 -> 24),
-// gradients bf16 B1 H16 L4096 d128 M512 3510 -> 1680 (four walks 2570 -> 1320 in eight launches, two states 680 -> 180), results
+// accumulator pair 28 vector instructions; W~ is 6 bytes per feature and coordinate and chunk from L2.  Two waves per SIMD overlap the two
+// pipes about half.  Against fp32 instructions: causal attention f32 B2 H4 L4096 d64 M256 147 -> 106 us (walk 87 -> 61, states 38 -> 24),
+// gradients bf16 B1 H16 L4096 d128 M512 3510 -> 1630 (four walks 2570 -> 1340 in eight launches, two states 680 -> 183), results
 // of 20 f32 calls 0.9 times as far from 64 bits.
 #include <type_traits>
 

@@ -1,6 +1,6 @@
 // General-shape causal kernels with the state in registers: fp32 matrix instructions, d and dv multiples of four up to 128, M up to
 // 512 (other shapes, and those that would be mostly padding here: the causal kernels of kernels_generic.hip, whose state lies in
-// memory).
+// memory; with many features and rows that are not narrow: kernels_gen_split.hip).
 //
 // A workgroup walks a segment of a sequence sixteen tokens at a time; a wave holds 16 FT features: its rows of the state stay in
 // accumulators from the first token to the last, and every operand of every product is either such an accumulator, a
@@ -8,7 +8,7 @@
 // chunk: one when its rows have arrived, one when the waves' partial output rows are complete; rows of the next
 // chunk travel meanwhile.  What bounds them is the fp32 matrix rate (32 cycles per instruction) and the rows of W~, which come from L2
 // once per chunk, 13 bytes per cycle and CU.  Causal attention f32 B2 H4 L4096 d64 M256: 175 -> 89 us for this kernel, backward
-// pass bf16 B1 H16 L4096 d128 M512: 3300 -> 2560 us for its four.
+// pass bf16 B1 H16 L4096 d128 M512: 3300 -> 2560 us for its four (sizes that kernels_gen_split.hip has taken over since).
 #include <type_traits>
 
 #include "gen_widths.h"
