@@ -93,7 +93,7 @@ bool plan_split(int BH, int pgroups, int L, int d, int dv, int M, int dtype, int
   p->off_img = align_up(p->off_state + (size_t)BH * p->nseg * M * p->ldt * sizeof(float));
   p->img_bytes = (size_t)pgroups * 2 * s.tiles * s.steps * 3 * 512 * sizeof(uint16_t);
   p->off_part = align_up(p->off_img + copies * p->img_bytes);
-  p->total = align_up(p->off_part + (s.part ? (size_t)BH * L * gen_split_part_row(d, dv) * sizeof(float) : 0));
+  p->total = align_up(p->off_part + (s.part ? (size_t)gen_split_part_sequences(BH, L, d, dv) * L * gen_split_part_row(d, dv) * sizeof(float) : 0));
   return copies > 1 || base.total > FS_NOALLOC_SCRATCH_BYTES || p->total <= FS_NOALLOC_SCRATCH_BYTES;
 }
 GenSplit split_of(const AttnPlan& p, char* ws, int d, int dv, int M, float scale, bool gradients) {

@@ -43,7 +43,7 @@ size_t gen_lds_stats(int d);
 struct GenSplit {
   uint16_t* img = nullptr;
   uint16_t* img_t = nullptr;
-  float* part = nullptr;   // [B*H][rows][gen_split_part_row] of the first of two launches
+  float* part = nullptr;   // [gen_split_part_sequences][rows][gen_split_part_row] of the first of two launches
   int tiles = 0, steps = 0;
   float scale = 1.f;
 };
@@ -93,6 +93,7 @@ int launch_gen_bwd_walks(const GenSide& qs, const GenSide& ks, const TensorDev& 
 // Causal calls on bf16 matrix instructions with fp32 accuracy (kernels_gen_split.hip).
 struct GenSplitShape { int tiles, steps; bool part; int waves; };
 int gen_split_part_row(int d, int dv);
+int gen_split_part_sequences(int BH, int L, int d, int dv);
 bool gen_split_attention(int d, int dv, int M, int dtype);
 bool gen_split_backward(int d, int dv, int M, int dtype);
 GenSplitShape gen_split_shape(int d, int dv, int M);

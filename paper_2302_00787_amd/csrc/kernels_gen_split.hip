@@ -140,7 +140,8 @@ struct SplitArgs {
   float *den_out, *shift_out;
   unsigned* flushed;
   int tile0;               // the launch's first tile of features
-  float *part_out, *part_in;   // [BH][L][ldp] rows of a launch that is not the last, of the one before it
+  int bh0, nbh;            // its first sequence, sequences
+  float *part_out, *part_in;   // [nbh][L][ldp] rows of a launch that is not the last, of the one before it
   int ldp;
 };
 
@@ -162,11 +163,12 @@ __device__ __forceinline__ const uint16_t* side_image(const SplitArgs& a, const 
 
 // Segment and sequence of a workgroup.  Workgroups go to the eight XCDs in turn; the segments of a sequence go to one XCD, one after
 // the other, so that its L2 holds the images they all read (16 heads, d 128, M 512: 6 MB for an XCD that serves all of them).
-__device__ __forceinline__ void segment_of(int& seg, int& bh) {
+__device__ __forceinline__ void segment_of(int& seg, int& bh, int bh0) {
   const unsigned total = gridDim.x * gridDim.y, id = blockIdx.x + gridDim.x * blockIdx.y, xcd = id % 8, per = total / 8, rest = total % 8;
   const unsigned at = xcd * per + min(xcd, rest) + id / 8;
-  bh = at / gridDim.x;
-  seg = at - bh * gridDim.x;
+  const int at_bh = at / gridDim.x;
+  seg = at - at_bh * gridDim.x;
+  bh = bh0 + at_bh;
 }
 
 // Exponents (without bias) of N tiles of 16 features, from f0 / 16 on, against the chunk's rows at Xs.  FEATURE_ROWS: rows = features
@@ -220,7 +222,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_state(SplitA
   constexpr int VT = VT_OF<Q>, XC = 32 * KS<Q>, VC = 16 * VT, LDV = LDR(VC), VPLANE = TT * LDV;
   uint16_t *Xs = lds16, *Vs = Xs + XP * TT * LDR(XC);
   int seg, bh;
-  segment_of(seg, bh);
+  segment_of(seg, bh, a.bh0);
   const int b = bh / a.H, h = bh % a.H;
   const int lane = threadIdx.x & 63;
   int g = lane >> 4, c = lane & 15;
@@ -324,7 +326,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_walk(SplitAr
   float* mw = xch + NW * XCH<Q>;                   // [wave][token]: row maxima
   float* bl = mw + NW * TT;                        // biases, -inf behind the last feature
   int seg, bh;
-  segment_of(seg, bh);
+  segment_of(seg, bh, a.bh0);
   const int b = bh / a.H, h = bh % a.H;
   const int lane = threadIdx.x & 63;
   int g = lane >> 4, c = lane & 15;
@@ -504,7 +506,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_walk(SplitAr
     // the waves' rows summed, 2 NW threads per row
     const int row = threadIdx.x / (2 * NW), l = threadIdx.x % (2 * NW);
     const bool live = row0 + row < row_end;
-    const size_t rec = (size_t)bh * a.L + row0 + row;
+    const size_t rec = (size_t)bh * a.L + row0 + row, prec = (size_t)(bh - a.bh0) * a.L + row0 + row;
     float wgt[NW], wpart = 0.f, mm = -INFINITY, den = 1.f;
 #pragma unroll
     for (int vb = (VT - 1) / VB<Q> * VB<Q>; vb >= 0; vb -= VB<Q>) {
@@ -524,7 +526,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_walk(SplitAr
 #pragma unroll
         for (int i = 0; i < NW; ++i) mm = fmaxf(mm, mw[i * TT + row]);
         float before = -INFINITY;
-        if (a.part_in != nullptr && live) before = a.part_in[rec * a.ldp + a.ldt];
+        if (a.part_in != nullptr && live) before = a.part_in[prec * a.ldp + a.ldt];
         mm = fmaxf(mm, before);
         wpart = before == -INFINITY ? 0.f : fast_exp2(before - mm);
         den = 0.f;
@@ -534,11 +536,11 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_walk(SplitAr
           wgt[i] = mi == mm ? 1.f : fast_exp2(mi - mm);
           den += wgt[i] * at[i * XCH<Q> + a.nv - base];
         }
-        if (a.part_in != nullptr && live) den += wpart * a.part_in[rec * a.ldp + a.nv];
+        if (a.part_in != nullptr && live) den += wpart * a.part_in[prec * a.ldp + a.nv];
         if (live && l == 0) {
           if (a.part_out != nullptr) {
-            a.part_out[rec * a.ldp + a.nv] = den;
-            a.part_out[rec * a.ldp + a.ldt] = mm;
+            a.part_out[prec * a.ldp + a.nv] = den;
+            a.part_out[prec * a.ldp + a.ldt] = mm;
           } else {
             if (a.flushed != nullptr && !(den > 0.f)) atomicAdd(a.flushed, 1u);
             if (a.den_out != nullptr) {
@@ -554,9 +556,9 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_walk(SplitAr
           float v = 0.f;
 #pragma unroll
           for (int i = 0; i < NW; ++i) v += (MODE ? 1.f : wgt[i]) * at[i * XCH<Q> + col];
-          if (a.part_in != nullptr) v += (MODE ? 1.f : wpart) * a.part_in[rec * a.ldp + base + col];
+          if (a.part_in != nullptr) v += (MODE ? 1.f : wpart) * a.part_in[prec * a.ldp + base + col];
           if (a.part_out != nullptr) {
-            a.part_out[rec * a.ldp + base + col] = v;
+            a.part_out[prec * a.ldp + base + col] = v;
           } else {
             if (!MODE) v = den > 0.f ? v / den : 0.f;
             store_elem(a.out, ob + base + col, v);
@@ -594,7 +596,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_gwalk(SplitA
   float* bl = rsw + NW * TT;                       // biases, -inf behind the last feature
   float* cx = bl + 16 * FT * NW;                   // [token][coordinate]: x (C + C^T), where the kernel has a C
   int seg, bh;
-  segment_of(seg, bh);
+  segment_of(seg, bh, a.bh0);
   const int b = bh / a.H, h = bh % a.H;
   const int lane = threadIdx.x & 63;
   int g = lane >> 4, c = lane & 15;
@@ -821,7 +823,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_gwalk(SplitA
 #pragma unroll
         for (int i = 0; i < NW; ++i) rsum += rsw[i * TT + row];
         if (row0 + row < row_end) {
-          const size_t rec = (size_t)bh * a.L + row0 + row;
+          const size_t rec = (size_t)(bh - a.bh0) * a.L + row0 + row;
           if (a.part_in != nullptr) rsum += a.part_in[rec * a.ldp + d];
           if (a.part_out != nullptr && d0 == 0 && l == 0) a.part_out[rec * a.ldp + d] = rsum;
           const long long ob = b * a.out.sb + h * a.out.sh + (long long)(row0 + row) * a.out.sl;
@@ -893,37 +895,40 @@ int run_state(const SplitArgs& a, int BH, hipStream_t st) {
     });
   });
 }
-// launch(args) once or twice, the rows of the first launch on their way through `part`
+// launch(args) once, or twice for as many sequences at a time as `part` has room for the rows of the first launch
 template <class F>
-int in_launches(SplitArgs a, F launch) {
-  const int n = launches_of(a.M);
+int in_launches(SplitArgs a, int BH, F launch) {
+  const int n = launches_of(a.M), batch = n > 1 ? gen_split_part_sequences(BH, a.L, a.d, a.nv) : BH;
   float* part = a.part_out;
-  for (int i = 0; i < n; ++i) {
-    a.tile0 = 16 * i;
-    a.part_out = i + 1 < n ? part : nullptr;
-    a.part_in = i > 0 ? part : nullptr;
-    if (int rc = launch(a)) return rc;
+  for (a.bh0 = 0; a.bh0 < BH; a.bh0 += batch) {
+    a.nbh = BH - a.bh0 < batch ? BH - a.bh0 : batch;
+    for (int i = 0; i < n; ++i) {
+      a.tile0 = 16 * i;
+      a.part_out = i + 1 < n ? part : nullptr;
+      a.part_in = i > 0 ? part : nullptr;
+      if (int rc = launch(a)) return rc;
+    }
   }
   return 0;
 }
 template <int MODE>
 int run_walk(const SplitArgs& args, int BH, hipStream_t st) {
-  return in_launches(args, [&](const SplitArgs& a) {
+  return in_launches(args, BH, [&](const SplitArgs& a) {
     return by_rows(a.d, a.ldt, a.F.X.dtype, [&](auto q, auto xp) {
       return by_features<xp() == 1>(a.M, [&](auto nw) {
         constexpr int VP = MODE ? 3 : xp();
-        return run(k_split_walk<q(), nw(), xp(), VP, MODE>, a, dim3(a.nseg, BH), 64 * nw(), walk_lds<q(), nw(), xp(), VP>(), st);
+        return run(k_split_walk<q(), nw(), xp(), VP, MODE>, a, dim3(a.nseg, a.nbh), 64 * nw(), walk_lds<q(), nw(), xp(), VP>(), st);
       });
     });
   });
 }
 template <int MODE>
 int run_gwalk(const SplitArgs& args, int BH, hipStream_t st) {
-  return in_launches(args, [&](const SplitArgs& a) {
+  return in_launches(args, BH, [&](const SplitArgs& a) {
     return by_rows(a.d, a.ldt, a.F.X.dtype, [&](auto q, auto xp) {
       return by_features<xp() == 1>(a.M, [&](auto nw) {
         constexpr int VP = MODE ? 3 : xp(), UP = MODE ? xp() : 3;
-        return run(k_split_gwalk<q(), nw(), xp(), MODE>, a, dim3(a.nseg, BH), 64 * nw(), gwalk_lds<q(), nw(), xp(), VP, UP>(), st);
+        return run(k_split_gwalk<q(), nw(), xp(), MODE>, a, dim3(a.nseg, a.nbh), 64 * nw(), gwalk_lds<q(), nw(), xp(), VP, UP>(), st);
       });
     });
   });
@@ -955,6 +960,11 @@ bool gen_split_backward(int d, int dv, int M, int dtype) {
   return split_rows(d, dv, dtype) && M > (!dtype || (d > 64 && d <= 96) ? 128 : 64) && M <= 512;
 }
 int gen_split_part_row(int d, int dv) { return (d > dv ? d : dv) + 20; }
+// Sequences whose partial rows are there at a time: 256 MB of them, one at least.
+int gen_split_part_sequences(int BH, int L, int d, int dv) {
+  const size_t one = sizeof(float) * (size_t)L * gen_split_part_row(d, dv), n = ((size_t)256 << 20) / one;
+  return n < 1 ? 1 : n < (size_t)BH ? (int)n : BH;
+}
 GenSplitShape gen_split_shape(int d, int dv, int M) {
   const int q = width_of(d, (dv + 16) / 16 * 16);
   return {tiles_of(M), q == 2 ? 1 : q == 4 ? 2 : 4, launches_of(M) > 1, M <= 128 ? 4 : 8};

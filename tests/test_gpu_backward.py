@@ -142,13 +142,15 @@ def test_general_states_of_many_waves(fs, d, dv, M, B, L, causal, dtype):
             assert fro <= 3e-4 and row <= 1.2e-3, (b, name, fro, row)
 
 
-@pytest.mark.parametrize("d,dv,M,L", [(20, 28, 129, 31), (32, 44, 256, 65), (64, 60, 140, 40), (36, 64, 257, 97), (60, 36, 512, 130),
-                                      (32, 20, 65, 70), (128, 124, 70, 33), (100, 128, 130, 64), (96, 68, 300, 100), (128, 80, 511, 160)])
+@pytest.mark.parametrize("d,dv,M,L,B", [(20, 28, 129, 31, 3), (32, 44, 256, 65, 3), (64, 60, 140, 40, 3), (36, 64, 257, 97, 3),
+                                        (60, 36, 512, 130, 3), (32, 20, 65, 70, 3), (128, 124, 70, 33, 3), (100, 128, 130, 64, 3),
+                                        (96, 68, 300, 100, 3), (128, 80, 511, 160, 3), (20, 28, 257, 100, 16000)])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_general_causal_calls_on_bf16_matrix_instructions(fs, d, dv, M, L, dtype):
+def test_general_causal_calls_on_bf16_matrix_instructions(fs, d, dv, M, L, B, dtype):
     """Causal calls whose fp32 products run on bf16 pieces: remainders of tokens, coordinates, value columns (one and two blocks of
-    them, with the normaliser in either) and features (one and two launches)."""
-    test_general_states_of_many_waves(fs, d, dv, M, 3, L, True, dtype)
+    them, with the normaliser in either) and features (one and two launches; 16000 sequences: in two parts, as partial rows take
+    at most 256 MB)."""
+    test_general_states_of_many_waves(fs, d, dv, M, B, L, True, dtype)
 
 
 @pytest.mark.parametrize("d,M,causal", [(8, 40, False), (16, 16, False), (18, 40, False), (32, 70, False), (36, 40, False), (64, 33, False),
