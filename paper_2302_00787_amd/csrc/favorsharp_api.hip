@@ -587,7 +587,7 @@ int attention_impl(const float* theta, int groups, const fs_tensor* Q, const fs_
   const long long tf = (long long)favorsharp_theta_floats(d);
 
   unsigned* flushed = (unsigned*)ws;
-  if (!causal && gen_small_supported(BH, Lk, d, dv, M)) {
+  if (!causal && gen_small_supported(BH, Lq, Lk, d, dv, M)) {
     if (event_main_begin && hipEventRecord((hipEvent_t)event_main_begin, st) != hipSuccess) return FS_ERR_DEVICE;
     if (int rc = launch_gen_small(dev(Q), dev(K), dev(V), dev(Y), theta, groups, Omega, omega_groups, BH, H, Lq, Lk, d, dv, M, qk_scale, flushed, st))
       return rc;

@@ -107,7 +107,7 @@ int launch_split_bwd_walks(const GenSide& qs, const GenSide& ks, const GenSplit&
                            int H, int M, int d, int nv, int ldt, int rows_per_seg, int nseg, uint32_t* kmax_u, const float* row_shift,
                            float* Tstate, float* Rstate, const TensorDev& dQ, const TensorDev& dK, const TensorDev& dV, hipStream_t st);
 // Non-causal attention of short sequences in one launch (kernels_gen_small.hip).
-bool gen_small_supported(int BH, int Lk, int d, int dv, int M);
+bool gen_small_supported(int BH, int Lq, int Lk, int d, int dv, int M);
 int launch_gen_small(const TensorDev& Q, const TensorDev& K, const TensorDev& V, const TensorDev& Y, const float* theta, int groups,
                      const float* Omega, int omega_groups, int BH, int H, int Lq, int Lk, int d, int nv, int M, float scale,
                      unsigned* flushed, hipStream_t st);

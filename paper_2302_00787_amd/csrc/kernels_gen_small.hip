@@ -1,5 +1,5 @@
 // Non-causal attention of short sequences in one launch: constants, key maximum, state and outputs of a sequence by one workgroup.
-// d up to 32 in fours, up to 256 keys, few features (gen_small_supported); fp32 arithmetic on v_mfma_f32_16x16x4_f32.
+// d up to 32 in fours, up to 256 keys, few features, queries and sequences as gen_small_supported says; fp32 arithmetic on v_mfma_f32_16x16x4_f32.
 //
 // Such a call is a chain of launches and memory latencies (f32 L 256 d 16 M 64: five launches of 3 - 9 us, 23 us, for 0.1 us of
 // work at the card's rates).  Here rows, values and parameters are requested at once at the start, everything else stays in
@@ -310,12 +310,27 @@ int by_small(int d, int M, int dtype, F launch) {
 
 }  // namespace
 
-// Which calls: us, the five launches / this one (f32): 1 x 256 d16 M64 24.9 / 14.3, 512 x 256 d16 M32 57.6 / 19.8, 2048 x 256 d32 M64 358 /
-// 199, 320 x 200 d32 M48 dense C 73.9 / 53.8.  Thousands of sequences of a few tiles leave most of its waves without keys:
-// 4096 x 64 d16 M64 175 / 164 (bf16 177 / 183), 16384 x 48 592 / 625 (582 / 723).
-bool gen_small_supported(int BH, int Lk, int d, int dv, int M) {
-  if (d % 4 || Lk > 16 * SW * KT || (BH > 2048 && Lk < 96)) return false;
-  return M <= 64 && (d <= 16 ? dv < 32 : d <= 32 && dv < 48);      // (the waves' parts of the state fit in LDS)
+// Which calls.  Times as five launches / this one, us.
+// Rows of 32 numbers, 64 features and 256 keys are what LDS holds of the waves' parts of the state (eight waves, two tiles of keys each,
+// their exponents in registers until the maximum is known).
+// Queries: a workgroup takes all queries of its sequence, 128 at a time, where the five launches spread them over the chip.  From 96
+// sequences on it is faster for any number of them (16384 queries: f32 d16 M64 416 / 310, bf16 d32 M64 554 / 509; 80 sequences 354 /
+// 310, 469 / 508).  With fewer it may take only so many passes:
+//   1 sequence    d32 M64 256 queries 28.7 / 25.5, 512 28.5 / 32.7;  d16 M64 512 30 / 21, 1024 31 / 30 (bf16 28 / 33), 65536 39 / 1203;
+//                 d16 M32 1024 28 / 22, 2048 28 / 34
+//   48 sequences  d32 M64 256 32 / 28, 512 33.7 / 35.3;  d16 M64 1024 36 / 32, 2048 48 / 51;  d16 M32 2048 37 / 36, 4096 53 / 61
+// Tokens: sequences of a few tiles leave most of its waves without any, which counts once the sequences are several times the CUs
+// (bf16, as many queries as keys):
+//   1024 sequences  d8 M64 32 keys 39 / 49, 48 keys 50 / 49
+//   2048 sequences  d32 M64 64 keys 137 / 154, 80 keys 171 / 171;  d32 M24 32 keys 67 / 71, 48 keys 83 / 72
+//   8192 sequences  d8 M64 96 keys 361 / 405, 128 keys 445 / 405 (one query: 265 / 345);  d32 M24 96 keys 362 / 309
+// 256 x 256 d16 M64 53 / 20, 2048 x 256 d32 M64 358 / 200.
+bool gen_small_supported(int BH, int Lq, int Lk, int d, int dv, int M) {
+  if (d % 4 || Lk > 16 * SW * KT || M > 64 || !(d <= 16 ? dv < 32 : d <= 32 && dv < 48)) return false;
+  const int passes = (Lq + 16 * SW - 1) / (16 * SW), few = d > 16 ? 2 : M > 32 ? 4 : 8;
+  if (BH < 96 && (long long)passes * (112 - BH) > 112 * few) return false;
+  const int least = M > 32 ? (BH > 2048 ? 128 : BH > 1024 ? 80 : BH > 512 ? 48 : 1) : (BH > 2048 ? 96 : BH > 1024 && d > 16 ? 48 : 1);
+  return (long long)Lq + Lk >= 2 * least;
 }
 
 int launch_gen_small(const TensorDev& Q, const TensorDev& K, const TensorDev& V, const TensorDev& Y, const float* theta, int groups,

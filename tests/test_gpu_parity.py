@@ -320,6 +320,35 @@ def test_attention_of_short_sequences_in_one_launch(fs, d, dv, M, Lq, Lk, B, H, 
     assert int(ws[:4].view(torch.int32)) == 0
 
 
+@pytest.mark.parametrize("BH,Lq,Lk,d,M,spread", [(1, 65536, 256, 16, 64, True), (8, 16384, 64, 32, 48, True), (1, 1025, 128, 12, 32, True),
+                                                 (1, 1024, 128, 12, 32, False), (95, 17, 40, 32, 64, False), (96, 5000, 33, 8, 40, False),
+                                                 (2048, 16, 16, 32, 64, True), (520, 48, 47, 8, 33, True), (2100, 1, 250, 8, 64, True),
+                                                 (1100, 48, 49, 20, 16, False)])
+def test_short_keys_and_many_queries_or_sequences(fs, BH, Lq, Lk, d, M, spread):
+    """Few keys beside many queries, or thousands of sequences of a few keys: one workgroup per sequence would hold the call up, so
+    it is spread over the chip, which shows in the workspace (the one-launch kernel leaves all but the counter's block alone).
+    Both sides of that rule against float64, at the file's bar."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(BH + Lq)
+    Q, K, V = (0.7 * torch.randn((1, BH, L, d), generator=gen, device="cuda") for L in (Lq, Lk, Lk))
+    Om = torch.randn((1, M, d), generator=gen, device="cuda")
+    rng = np.random.default_rng(d)
+    theta = util.theta_vec_from_oracle(orc.fit("saderf", 0.5 * rng.standard_normal((400, d)), 0.4 * rng.standard_normal((400, d))))
+    th, s = util.oracle_theta_from_vec(theta, d), d ** -0.25
+    ws = torch.full((fs.attention_workspace_bytes(1, BH, Lq, Lk, d, d, M, False, 1, 1),), 0xa5, dtype=torch.uint8, device="cuda")
+    Y = fs.attention(torch.from_numpy(theta[None]).cuda(), Q, K, V, s, Om, workspace=ws)
+    assert bool((ws[256:] != 0xa5).any()) == spread
+    A, B1, B2, C2 = (torch.from_numpy(np.asarray(x, dtype=np.float64)).cuda() for x in (th.A, th.B1, th.B2, th.C2))
+    om = Om[0].double()
+    for h in sorted({0, BH // 2, BH - 1}):
+        q, k, v = s * Q[0, h].double(), s * K[0, h].double(), V[0, h].double()
+        E1, E2 = q @ (om @ B1).T + (om * om) @ A, k @ (om @ B2).T + (om * om) @ A + ((k @ C2) * k).sum(-1, keepdim=True)
+        P, S = torch.exp(E1 - E1.amax(-1, keepdim=True)), torch.exp(E2 - E2.max())
+        ref = (P @ (S.T @ v)) / (P @ S.sum(0))[:, None]
+        assert float((Y[0, h].double() - ref).norm() / ref.norm()) <= 1e-4, h
+    assert int(ws[:4].view(torch.int32)) == 0
+
+
 # ----------------------------------------------------------------------------- kernel operator
 @pytest.mark.parametrize("variant", ["sderf", "aderf"])
 def test_kernel_matvec_small(fs, variant):
