@@ -30,6 +30,15 @@ template <int Q> constexpr int KS = (Q + 1) / 2;         // steps of 32 coordina
 template <int Q> constexpr int VTP = (VT_OF<Q> + 1) / 2 * 2;
 constexpr int LDR(int cols) { return cols + 8; }         // stride of LDS rows (bf16 numbers)
 constexpr int IMG = 512;                                 // numbers of an operand image
+// Features are lifted before they are split: they lie in 2^-126 .. 1 (a causal row may see only keys whose features are that far
+// below the largest of the sequence), and pieces of numbers below 2^-109 lose bits.  Lifted, one of 2^-126 is off by 2^-20 of itself, less
+// than by the rounding of its exponent, 2^-18.  Sums carry the factors: the keys' states kLift, output rows and normalisers kLift^2
+// (a quotient loses them); G1 is made from normalisers kLift too large, so that the queries' states and every sum with one feature of
+// each side and G1 have none; dV alone is taken back.  (Keys 2^-121 below the largest: outputs 1.1e-5 - 1.8e-5 off without it, gradients
+// 5e-4, now 1e-7 - 3e-7 and 6e-6, as with fp32 instructions; causal f32 B2 H4 L4096 d64 M256 105.9 -> 107.5 us, the gradients of
+// B1 H16 L4096 d128 M512 1631 -> 1632.)
+constexpr float kLift = 4096.f;
+constexpr float kLeastSum = 0x1p-125f;                   // kLift^2 times the least fp32 number: below it a normaliser counts as zero
 
 typedef __attribute__((ext_vector_type(4))) short s16x4_t;
 __device__ __forceinline__ u32x2 read_tr(const uint16_t* p) {
@@ -280,7 +289,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_state(SplitA
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) s[0][t][r] = fast_exp2(exponent<KEYS>(s[0][t][r], bf[ft], add[t][r], kmax));
+        for (int r = 0; r < 4; ++r) s[0][t][r] = kLift * fast_exp2(exponent<KEYS>(s[0][t][r], bf[ft], add[t][r], kmax));
       const Split3 so = split3(s[0][0], s[0][1]);
 #pragma unroll
       for (int vt = 0; vt < VT; ++vt) {
@@ -403,9 +412,9 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_walk(SplitAr
       for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          sf[ft][t][r] = fast_exp2(exponent<F_KEYS>(sf[ft][t][r], br[r], addf[t], kmax));
+          sf[ft][t][r] = kLift * fast_exp2(exponent<F_KEYS>(sf[ft][t][r], br[r], addf[t], kmax));
           if (MODE) {
-            p[ft][t][r] = fast_exp2(exponent<true>(p[ft][t][r], br[r], adds[t], kmax));
+            p[ft][t][r] = kLift * fast_exp2(exponent<true>(p[ft][t][r], br[r], adds[t], kmax));
           } else {
             p[ft][t][r] += br[r];
             m[t] = fmaxf(m[t], p[ft][t][r]);
@@ -422,7 +431,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_walk(SplitAr
 #pragma unroll
         for (int ft = 0; ft < FT; ++ft)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) p[ft][t][r] = fast_exp2(p[ft][t][r] - ms);
+          for (int r = 0; r < 4; ++r) p[ft][t][r] = kLift * fast_exp2(p[ft][t][r] - ms);
       }
     }
     f32x4 sc[2][2], y[2][VT];      // scores (rows = first-side tokens, column = second-side token), output rows
@@ -542,9 +551,9 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_walk(SplitAr
             a.part_out[prec * a.ldp + a.nv] = den;
             a.part_out[prec * a.ldp + a.ldt] = mm;
           } else {
-            if (a.flushed != nullptr && !(den > 0.f)) atomicAdd(a.flushed, 1u);
+            if (a.flushed != nullptr && !(den > kLeastSum)) atomicAdd(a.flushed, 1u);
             if (a.den_out != nullptr) {
-              a.den_out[rec] = den;
+              a.den_out[rec] = den > kLeastSum ? den * (1.f / kLift) : 0.f;
               a.shift_out[rec] = mm;
             }
           }
@@ -560,7 +569,8 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_walk(SplitAr
           if (a.part_out != nullptr) {
             a.part_out[prec * a.ldp + base + col] = v;
           } else {
-            if (!MODE) v = den > 0.f ? v / den : 0.f;
+            if (!MODE) v = den > kLeastSum ? v / den : 0.f;
+            else v *= 1.f / kLift;
             store_elem(a.out, ob + base + col, v);
           }
         }
@@ -722,7 +732,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_gwalk(SplitA
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) ff[0][t][r] = fast_exp2(exponent<F_KEYS>(ff[0][t][r], bf, addf[t][r], kmax));
+        for (int r = 0; r < 4; ++r) ff[0][t][r] = kLift * fast_exp2(exponent<F_KEYS>(ff[0][t][r], bf, addf[t][r], kmax));
       const Split3 fo = split3(ff[0][0], ff[0][1]);
 #pragma unroll
       for (int t = 0; t < 2; ++t) df[ft][t] = mfma3(fo, split3(am[0][t], am[1][t]), df[ft][t]);

@@ -153,6 +153,69 @@ def test_general_causal_calls_on_bf16_matrix_instructions(fs, d, dv, M, L, B, dt
     test_general_states_of_many_waves(fs, d, dv, M, B, L, True, dtype)
 
 
+@pytest.mark.parametrize("below", [96, 110, 121])
+@pytest.mark.parametrize("d,M,dtype", [(32, 160, "f32"), (64, 300, "f32"), (48, 100, "bf16"), (128, 300, "bf16")])
+def test_general_causal_rows_whose_keys_lie_far_below_the_largest(fs, d, M, dtype, below):
+    """The first 40 keys have all their features 2^-`below` times those of the others (a coordinate of their own in C2 that no
+    projection sees), down to 2^-125 of the largest: with one shift per sequence fp32 holds them to the rounding of their exponents,
+    2^-18 for numbers between 64 and 128.  Four of those (projection, row term, sum, shift) are 1.1e-5 of a feature; outputs of the
+    first rows divide two sums of them, gradients multiply another two."""
+    import torch
+    L, n, s = 100, 40, d ** -0.25
+    gen = torch.Generator(device="cuda").manual_seed(d + M + below)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    Q, K, V, dY = (f * torch.randn((1, 1, L, d), generator=gen, device="cuda") for f in (0.1, 0.1, 1.0, 1.0))
+    Q[..., 0] = K[..., 0] = 0.0
+    K[:, :, :n, 0] = 1.0
+    Q, K, V, dY = (x.to(dt) for x in (Q, K, V, dY))
+    Om = torch.randn((1, M, d), generator=gen, device="cuda")
+    B, C2 = np.eye(d), np.zeros((d, d))
+    B[0, 0], C2[0, 0] = 0.0, -below * np.log(2.0) / s ** 2
+    th = orc.Theta(logD=0.0, A=np.zeros(d), B1=B, B2=B, C1=-0.5 * np.eye(d), C2=C2)
+    td = torch.from_numpy(util.theta_vec_from_oracle(th)[None]).cuda()
+    Y = fs.attention(td, Q, K, V, s, Om, causal=True, out_dtype=torch.float32)
+    grads = fs.attention_backward(td, Q, K, V, dY, s, Om, causal=True, grad_dtype=torch.float32)
+    q, k, v = (x[0, 0].double().requires_grad_(True) for x in (Q, K, V))
+    om, c2 = Om[0].double(), float(td[0, 8 + d + 3 * d * d])
+    om[:, 0] = 0.0
+    W = torch.tril(torch.exp(s * q @ om.T) @ torch.exp(s * k @ om.T + s * s * c2 * k[:, :1] ** 2).T)
+    ref = (W @ v) / W.sum(1, keepdim=True)
+    gref = torch.autograd.grad((ref * dY[0, 0].double()).sum(), (q, k, v))
+    errs = [float((a[0, 0, :n].double() - r[:n]).norm() / r[:n].norm()) for a, r in zip((Y, *grads), (ref.detach(), *gref))]
+    print(d, M, dtype, below, " ".join("%.2e" % e for e in errs))
+    assert errs[0] <= 2.2e-5 and max(errs[1:]) <= 4.4e-5, errs
+
+
+@pytest.mark.parametrize("d,M,dtype", [(32, 160, "f32"), (48, 100, "bf16"), (128, 300, "bf16")])
+def test_general_causal_rows_that_see_no_key_are_zero_and_counted(fs, d, M, dtype):
+    """Keys 2^-170 below the largest: none of their features is a number of fp32.  Rows that see only them get zeros, outputs and
+    gradients, and are counted; the others are as without those keys."""
+    import torch
+    L, n, s = 100, 40, d ** -0.25
+    gen = torch.Generator(device="cuda").manual_seed(d + M)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    Q, K, V, dY = (f * torch.randn((2, 1, L, d), generator=gen, device="cuda") for f in (0.1, 0.1, 1.0, 1.0))
+    Q[..., 0] = K[..., 0] = 0.0
+    K[:, :, :n, 0] = 1.0
+    Q, K, V, dY = (x.to(dt) for x in (Q, K, V, dY))
+    Om = torch.randn((1, M, d), generator=gen, device="cuda")
+    B, C2 = np.eye(d), np.zeros((d, d))
+    B[0, 0], C2[0, 0] = 0.0, -170.0 * np.log(2.0) / s ** 2
+    td = torch.from_numpy(util.theta_vec_from_oracle(orc.Theta(logD=0.0, A=np.zeros(d), B1=B, B2=B, C1=-0.5 * np.eye(d), C2=C2))[None]).cuda()
+    ws = torch.empty(fs.attention_backward_workspace_bytes(2, 1, L, L, d, d, M, True, 1, 1), dtype=torch.uint8, device="cuda")
+    Y = fs.attention(td, Q, K, V, s, Om, causal=True, workspace=ws)
+    assert fs.attention_flushed_rows(ws) == 2 * n
+    grads = fs.attention_backward(td, Q, K, V, dY, s, Om, causal=True, workspace=ws)
+    assert fs.attention_flushed_rows(ws) == 2 * n
+    assert all(bool((x[:, :, :n] == 0).all()) and bool(torch.isfinite(x).all()) for x in (Y, *grads))
+    Qr, Kr, Vr, dYr = (x[:, :, n:] for x in (Q, K, V, dY))
+    tail = (fs.attention(td, Qr, Kr, Vr, s, Om, causal=True), *fs.attention_backward(td, Qr, Kr, Vr, dYr, s, Om, causal=True))
+    # (sums of other chunks: fp32 rounding, and that of the outputs' type)
+    tol = 1e-5 if dtype == "f32" else 4e-3
+    for x, y in zip((Y, *grads), tail):
+        assert float((x[:, :, n:].double() - y.double()).norm()) <= tol * float(y.double().norm())
+
+
 @pytest.mark.parametrize("d,M,causal", [(8, 40, False), (16, 16, False), (18, 40, False), (32, 70, False), (36, 40, False), (64, 33, False),
                                         (80, 40, False), (128, 40, False), (16, 40, True), (64, 130, True), (18, 40, True), (24, 520, True)])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
