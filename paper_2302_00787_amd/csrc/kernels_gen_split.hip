@@ -69,10 +69,11 @@ __device__ __forceinline__ Op<P> column_op(const uint16_t* s, int ld, int plane)
   for (int i = 0; i < P; ++i) o.p[i] = join(read_tr(s + i * plane), read_tr(s + i * plane + 16 * ld));
   return o;
 }
+template <int PART = ALL>
 __device__ __forceinline__ f32x4 times(const Split3& a, const Op<1>& b, f32x4 c) {
-  c = mfma_bf16(a.l, b.p[0], c);
-  c = mfma_bf16(a.m, b.p[0], c);
-  return mfma_bf16(a.h, b.p[0], c);
+  c = mfma_bf16<PART>(a.l, b.p[0], c);
+  c = mfma_bf16<PART>(a.m, b.p[0], c);
+  return mfma_bf16<PART>(a.h, b.p[0], c);
 }
 __device__ __forceinline__ f32x4 times(const Op<1>& a, const Split3& b, f32x4 c) {
   c = mfma_bf16(a.p[0], b.l, c);
@@ -80,7 +81,8 @@ __device__ __forceinline__ f32x4 times(const Op<1>& a, const Split3& b, f32x4 c)
   return mfma_bf16(a.p[0], b.h, c);
 }
 __device__ __forceinline__ Split3 as_split(const Op<3>& a) { return {a.p[0], a.p[1], a.p[2]}; }
-__device__ __forceinline__ f32x4 times(const Split3& a, const Op<3>& b, f32x4 c) { return mfma3(a, as_split(b), c); }
+template <int PART = ALL>
+__device__ __forceinline__ f32x4 times(const Split3& a, const Op<3>& b, f32x4 c) { return mfma3<PART>(a, as_split(b), c); }
 __device__ __forceinline__ f32x4 times(const Op<3>& a, const Split3& b, f32x4 c) { return mfma3_t(as_split(a), b, c); }
 __device__ __forceinline__ f32x4 times(const Op<1>& a, const Op<1>& b, f32x4 c) { return mfma_bf16(a.p[0], b.p[0], c); }
 __device__ __forceinline__ f32x4 times(const Op<1>& a, const Op<3>& b, f32x4 c) { return times(a, as_split(b), c); }
@@ -507,8 +509,8 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_walk(SplitAr
       for (int vt = 0; vt < VT; ++vt) {
         __builtin_amdgcn_sched_barrier(0);
         const Op<VP> v = column_op<VP>(vcol + 16 * vt, LDV, VPLANE);
-        y[0][vt] = times(so[0], v, y[0][vt]);
-        y[1][vt] = times(so[1], v, y[1][vt]);
+        y[0][vt] = times<MODE ? ALL : LOW>(so[0], v, y[0][vt]);
+        y[1][vt] = times<MODE ? HIGH : ALL>(so[1], v, y[1][vt]);
       }
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -734,8 +736,8 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_gwalk(SplitA
 #pragma unroll
         for (int r = 0; r < 4; ++r) ff[0][t][r] = kLift * fast_exp2(exponent<F_KEYS>(ff[0][t][r], bf, addf[t][r], kmax));
       const Split3 fo = split3(ff[0][0], ff[0][1]);
-#pragma unroll
-      for (int t = 0; t < 2; ++t) df[ft][t] = mfma3(fo, split3(am[0][t], am[1][t]), df[ft][t]);
+      df[ft][0] = mfma3<MODE ? ALL : LOW>(fo, split3(am[0][0], am[1][0]), df[ft][0]);
+      df[ft][1] = mfma3<MODE ? HIGH : ALL>(fo, split3(am[0][1], am[1][1]), df[ft][1]);
 #pragma unroll
       for (int vt = 0; vt < VT; ++vt) {
         if (vt % 2 == 0) __builtin_amdgcn_sched_barrier(0);

@@ -54,16 +54,32 @@ __device__ __forceinline__ Split3 split3_each(f32x4 a, f32x4 b) {
   return s;
 }
 
-__device__ __forceinline__ f32x4 mfma_bf16(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+// PART: which numbers of an operand are summed over, all eight of a lane or the four of its low or high half (the others need not be
+// finite then).
+enum { ALL = 0, LOW = 1, HIGH = 2 };
+template <int PART = ALL>
+__device__ __forceinline__ f32x4 mfma_bf16(bf16x8 a, bf16x8 b, f32x4 c) {
+  typedef __attribute__((ext_vector_type(4))) short s16x4;
+  if constexpr (PART == ALL) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+  } else {
+    auto half = [](bf16x8 v) {
+      const u32x4 u = __builtin_bit_cast(u32x4, v);
+      return __builtin_bit_cast(s16x4, PART == LOW ? u32x2{u[0], u[1]} : u32x2{u[2], u[3]});
+    };
+    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(half(a), half(b), c, 0, 0, 0);
+  }
+}
 
 // c + a b, small products first.
+template <int PART = ALL>
 __device__ __forceinline__ f32x4 mfma3(const Split3& a, const Split3& b, f32x4 c) {
-  c = mfma_bf16(a.l, b.h, c);
-  c = mfma_bf16(a.h, b.l, c);
-  c = mfma_bf16(a.m, b.m, c);
-  c = mfma_bf16(a.m, b.h, c);
-  c = mfma_bf16(a.h, b.m, c);
-  return mfma_bf16(a.h, b.h, c);
+  c = mfma_bf16<PART>(a.l, b.h, c);
+  c = mfma_bf16<PART>(a.h, b.l, c);
+  c = mfma_bf16<PART>(a.m, b.m, c);
+  c = mfma_bf16<PART>(a.m, b.h, c);
+  c = mfma_bf16<PART>(a.h, b.m, c);
+  return mfma_bf16<PART>(a.h, b.h, c);
 }
 
 // The same for the transposed product: the pieces in the order of mfma3(b, a, .), so that both round alike.

@@ -216,6 +216,41 @@ def test_general_causal_rows_that_see_no_key_are_zero_and_counted(fs, d, M, dtyp
         assert float((x[:, :, n:].double() - y.double()).norm()) <= tol * float(y.double().norm())
 
 
+@pytest.mark.parametrize("row", [42, 58])
+@pytest.mark.parametrize("d,M,dtype", [(32, 160, "f32"), (64, 300, "f32"), (48, 100, "bf16"), (128, 300, "bf16")])
+def test_general_causal_rows_that_are_not_finite_stay_in_their_tile(fs, d, M, dtype, row):
+    """A row of V that is not finite leaves the outputs and the gradients of Q as they are in all tiles of sixteen rows before
+    its own, one of dY or Q the gradients of K and V in those behind it: masked scores are zeros, but zeros times such a number are
+    not."""
+    import torch
+    L, s, tile = 100, d ** -0.25, row // 16 * 16
+    gen = torch.Generator(device="cuda").manual_seed(d + M)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    Q, K, V, dY = ((f * torch.randn((1, 1, L, d), generator=gen, device="cuda")).to(dt) for f in (0.5, 0.5, 1.0, 1.0))
+    Om = torch.randn((1, M, d), generator=gen, device="cuda")
+    td = torch.from_numpy(util.theta_vec_from_oracle(orc.fit_posrf(d))[None]).cuda()
+
+    def call(*args):
+        return (fs.attention(td, *args[:3], s, Om, causal=True), *fs.attention_backward(td, *args, s, Om, causal=True))
+    Y, dQ, dK, dV = call(Q, K, V, dY)
+    for value in (float("inf"), float("nan")):
+        V2, dY2 = V.clone(), dY.clone()
+        V2[:, :, row, 3] = dY2[:, :, row, 3] = value
+        got = call(Q, K, V2, dY)
+        assert torch.equal(got[0][:, :, :tile], Y[:, :, :tile]) and torch.equal(got[1][:, :, :tile], dQ[:, :, :tile])
+        assert not bool(torch.isfinite(got[0][:, :, row:, 3]).any())
+        assert torch.equal(got[0][..., :3], Y[..., :3]) and torch.equal(got[0][..., 4:], Y[..., 4:])
+        got = call(Q, K, V, dY2)
+        assert torch.equal(got[0], Y)
+        assert torch.equal(got[2][:, :, tile + 16:], dK[:, :, tile + 16:]) and torch.equal(got[3][:, :, tile + 16:], dV[:, :, tile + 16:])
+        assert not bool(torch.isfinite(got[3][:, :, :row + 1, 3]).any())
+    Q2 = Q.clone()
+    Q2[:, :, row] = float("nan")
+    got = call(Q2, K, V, dY)
+    assert torch.equal(got[0][:, :, :tile], Y[:, :, :tile]) and torch.equal(got[0][:, :, tile + 16:], Y[:, :, tile + 16:])
+    assert torch.equal(got[2][:, :, tile + 16:], dK[:, :, tile + 16:]) and torch.equal(got[3][:, :, tile + 16:], dV[:, :, tile + 16:])
+
+
 @pytest.mark.parametrize("d,M,causal", [(8, 40, False), (16, 16, False), (18, 40, False), (32, 70, False), (36, 40, False), (64, 33, False),
                                         (80, 40, False), (128, 40, False), (16, 40, True), (64, 130, True), (18, 40, True), (24, 520, True)])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
