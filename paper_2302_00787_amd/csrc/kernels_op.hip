@@ -18,6 +18,10 @@
 // Exponents live in the log2 domain.  Shifts, where there have to be any, are largest exponents of what a wave has in its registers
 // anyway, so no factor can overflow and none that matters can vanish, and they are applied back at the end through the exponent field: a sum of shifts
 // may leave the fp32 exponent range although the result does not.
+// Pieces of numbers below 2^-109 lose bits (split3.h), so no operand is left there: right-hand sides are split relative to the largest of
+// their column among the workgroup's rows, the state relative to the largest of the column (powers of two, taken back through the
+// exponent field), and features are lifted by kLift.  (All of C near 2^-110 / 2^-115 / 2^-120: results up to 8e-4 / 3e-2 / 0.8 off
+// without that, with fp32 instructions 4e-6 .. 2e-4, now as for C near one, up to 4e-6.)
 //
 // What bounds it: matrix pipe, exponentials and splits are 3 - 4 us of each of the two main kernels (256 workgroups of c2), the rest is
 // the launch and the chain rows -> operands -> first tile.  With fp32 instructions and Cauchy-Schwarz bounds over all features as
@@ -37,6 +41,9 @@ constexpr int NWV = NTH / 64;
 constexpr int NC = 16;          // right-hand-side columns (padded)
 constexpr int DMAX = 64;
 constexpr int IMG = 512;        // numbers of an operand image: 64 lanes x 8
+constexpr int LIFT = 12;        // binary exponent of the factor on the features of either side
+constexpr float kLift = 1 << LIFT;
+constexpr int NONE = -1000;     // exponent of a column of zeros
 // (the kernels are instantiated for KS = 1 and 2 contraction steps of a projection: d <= 32 and d <= 64; numbers past d are zero)
 
 struct OpArgs {
@@ -47,6 +54,8 @@ struct OpArgs {
   const float* C;         // [Ny][n]
   float* Tpart;           // [nwg][M][NC]
   float* tshift;          // [M/16][nwg]
+  int* cexp;              // [nwg][NC]: binary exponents of the columns of C, in the workgroup's rows
+  const int* cstar;       // [NC]: the largest of them
   const uint16_t* T;      // [pairs of tiles][3][IMG]: pieces of the state
   const float* tstar;     // [M/16]
   float* out;             // [Nx][n]
@@ -215,6 +224,19 @@ __global__ void __launch_bounds__(NTH, 2) k_op_state(OpArgs a) {
     }
   Split3 x[KS][4], cs[2];
   stage_rows<KS>(sm, a, 1, row0, x);
+  float big = 0.f;
+#pragma unroll
+  for (int tt = 0; tt < 4; ++tt)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) big = fmaxf(big, fabsf(cv[tt][r]));
+  big = fmaxf(big, __shfl_xor(big, 16));
+  big = fmaxf(big, __shfl_xor(big, 32));
+  const int ce = big > 0.f ? __builtin_amdgcn_frexp_expf(big) : NONE;
+#pragma unroll
+  for (int tt = 0; tt < 4; ++tt)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) cv[tt][r] = ldexpf(cv[tt][r], -ce);
+  if (w == 0 && g == 0) a.cexp[blockIdx.x * NC + c] = ce;
   cs[0] = split3(cv[0], cv[1]);
   cs[1] = split3(cv[2], cv[3]);
   f32x4 add[4];
@@ -243,26 +265,32 @@ __global__ void __launch_bounds__(NTH, 2) k_op_state(OpArgs a) {
 #pragma unroll
     for (int tt = 0; tt < 4; ++tt)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) e[tt][r] = fast_exp2(e[tt][r] - shift);
+      for (int r = 0; r < 4; ++r) e[tt][r] = kLift * fast_exp2(e[tt][r] - shift);
     f32x4 t = mfma3(split3(e[0], e[1]), cs[0], f32x4{0.f, 0.f, 0.f, 0.f});
     t = mfma3(split3(e[2], e[3]), cs[1], t);
     float* out = a.Tpart + ((size_t)blockIdx.x * a.M + 16 * ft + 4 * g) * NC + c;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) out[(size_t)r * NC] = t[r];
+    for (int r = 0; r < 4; ++r) out[(size_t)r * NC] = ldexpf(t[r], ce);
     if (lane == 0) a.tshift[(size_t)ft * a.nwg + blockIdx.x] = shift;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) wr[ks] = wn[ks];
   }
 }
 
-// T = sum_wg Tpart[wg] 2^(t_wg - t*), t* = max t_wg of the tile.  grid M / 4, block 1024: four features per workgroup, the
+// T = 2^-c* sum_wg Tpart[wg] 2^(t_wg - t*), t* = max t_wg of the tile.  grid M / 4, block 1024: four features per workgroup, the
 // workgroups' partial states dealt to the sixteen waves.  (A last tile without a partner gets one of zeros.)
-__global__ void __launch_bounds__(1024) k_op_reduce(const float* Tpart, const float* tshift, uint16_t* T, float* tstar, int nwg, int M) {
+__global__ void __launch_bounds__(1024) k_op_reduce(const float* Tpart, const float* tshift, const int* cexp, uint16_t* T, float* tstar, int* cstar,
+                                                    int nwg, int M) {
   __shared__ float red[16], part[16][64];
+  __shared__ int cred[16][NC];
   const int ft = blockIdx.x >> 2, q = threadIdx.x >> 6, l = threadIdx.x & 63;
   const float* sh = tshift + (size_t)ft * nwg;
   const float* p = Tpart + (size_t)blockIdx.x * 64 + l;
   const size_t total = (size_t)M * NC;
+  int cs = NONE;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) cs = max(cs, cexp[min((int)threadIdx.x + 1024 * u, nwg * NC - NC + (l & 15))]);
+  for (int i = threadIdx.x + 4096; i < nwg * NC; i += 1024) cs = max(cs, cexp[i]);
   // the first sixteen parts of a wave are requested ahead of the shifts
   float v[16], s16[16];
 #pragma unroll
@@ -275,6 +303,9 @@ __global__ void __launch_bounds__(1024) k_op_reduce(const float* Tpart, const fl
   for (int i = threadIdx.x; i < nwg; i += 1024) ts = fmaxf(ts, sh[i]);
   ts = fast::wave_max(ts);
   if (l == 0) red[q] = ts;
+  cs = max(cs, __shfl_xor(cs, 16));
+  cs = max(cs, __shfl_xor(cs, 32));
+  if (l < NC) cred[q][l] = cs;
   __syncthreads();
   ts = red[0];
 #pragma unroll
@@ -288,7 +319,12 @@ __global__ void __launch_bounds__(1024) k_op_reduce(const float* Tpart, const fl
   __syncthreads();
   if (q == 0) {
 #pragma unroll
-    for (int i = 1; i < 16; ++i) acc += part[i][l];
+    for (int i = 1; i < 16; ++i) {
+      acc += part[i][l];
+      cs = max(cs, cred[i][l & 15]);
+    }
+    acc = ldexpf(acc, -cs);
+    if (blockIdx.x == 0 && l < NC) cstar[l] = cs;
     const int f = (blockIdx.x & 3) * 4 + (l >> 4), n = l & 15;        // feature of the tile, column
     uint16_t* at = T + (size_t)(ft >> 1) * 3 * IMG + ((f >> 2) * 16 + n) * 8 + (f & 3);
     split3_store(at + 4 * (ft & 1), IMG, acc);
@@ -358,7 +394,7 @@ __global__ void __launch_bounds__(NTH, 2) k_op_apply(OpArgs a) {
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) e[i][tt][r] = fast_exp2(e[i][tt][r] - sn);
+        for (int r = 0; r < 4; ++r) e[i][tt][r] = kLift * fast_exp2(e[i][tt][r] - sn);
       o[tt] = mfma3(T, split3(e[0][tt], e[1][tt]), o[tt]);
     }
   }
@@ -383,7 +419,7 @@ __global__ void __launch_bounds__(NTH, 2) k_op_apply(OpArgs a) {
         v += sm.o.xo[wv][r][col] * (sw == m ? 1.f : fast_exp2(sw - m));
       }
       const float whole = floorf(m);
-      a.out[(size_t)(row0 + r) * a.n + col] = ldexpf(v * fast_exp2(m - whole), (int)fminf(fmaxf(whole, -1000.f), 1000.f));
+      a.out[(size_t)(row0 + r) * a.n + col] = ldexpf(v * fast_exp2(m - whole), (int)fminf(fmaxf(whole, -1000.f), 1000.f) + a.cstar[col] - 2 * LIFT);
     }
   }
 }
@@ -394,11 +430,11 @@ bool op_supported(int dtype_x, int dtype_y, int d, int M, int n) {
   return dtype_x == 0 && dtype_y == 0 && d % 4 == 0 && d <= op::DMAX && M % 16 == 0 && n <= op::NC;
 }
 
-// Floats of workspace: pieces of W~ (both sides), partial states, pieces of the state, biases and shifts.
+// Floats of workspace: pieces of W~ (both sides), partial states, pieces of the state, biases, shifts and exponents.
 static int op_steps(int d) { return d <= 32 ? 1 : 2; }
 size_t op_workspace_floats(int Ny, int d, int M) {
   const size_t nwg = (Ny + op::RW - 1) / op::RW, ntile = M >> 4;
-  return 2 * ntile * op_steps(d) * 3 * op::IMG / 2 + nwg * M * op::NC + (ntile + 1) / 2 * 3 * op::IMG / 2 + M + nwg * ntile + ntile + 64;
+  return 2 * ntile * op_steps(d) * 3 * op::IMG / 2 + nwg * M * op::NC + (ntile + 1) / 2 * 3 * op::IMG / 2 + M + nwg * ntile + ntile + (nwg + 1) * op::NC + 64;
 }
 
 #define FS_LAUNCH_CHECK() do { if (hipGetLastError() != hipSuccess) return 5; } while (0)
@@ -415,15 +451,17 @@ static int launch(const float* theta, const TensorDev& X, const TensorDev& Y, in
   float* bias = Tpart + (size_t)nwg * M * NC;
   float* tshift = bias + M;
   float* tstar = tshift + (size_t)nwg * ntile;
+  int* cexp = (int*)(tstar + ntile);
+  int* cstar = cexp + (size_t)nwg * NC;
   hipLaunchKernelGGL(k_op_pre<KS>, dim3(M / 4, 2), dim3(256), 0, st, theta, Omega, M, d, W, bias);
   FS_LAUNCH_CHECK();
   OpArgs a;
-  a.theta = theta; a.bias = bias; a.C = C; a.Tpart = Tpart; a.tshift = tshift; a.T = T;
-  a.tstar = tstar; a.out = out; a.d = d; a.M = M; a.n = n; a.nwg = nwg; a.scale = scale; a.alpha = alpha;
+  a.theta = theta; a.bias = bias; a.C = C; a.Tpart = Tpart; a.tshift = tshift; a.cexp = cexp; a.T = T;
+  a.tstar = tstar; a.cstar = cstar; a.out = out; a.d = d; a.M = M; a.n = n; a.nwg = nwg; a.scale = scale; a.alpha = alpha;
   a.X = Y; a.N = Ny; a.W = W + side;
   hipLaunchKernelGGL(k_op_state<KS>, dim3(nwg), dim3(NTH), 0, st, a);
   FS_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_op_reduce, dim3(M / 4), dim3(1024), 0, st, Tpart, tshift, T, tstar, nwg, M);
+  hipLaunchKernelGGL(k_op_reduce, dim3(M / 4), dim3(1024), 0, st, Tpart, tshift, cexp, T, tstar, cstar, nwg, M);
   FS_LAUNCH_CHECK();
   a.X = X; a.N = Nx; a.W = W;
   hipLaunchKernelGGL(k_op_apply<KS>, dim3((Nx + RW - 1) / RW), dim3(NTH), 0, st, a);

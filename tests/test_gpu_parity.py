@@ -423,6 +423,59 @@ def test_kernel_matvec_operator_kernels_edges(fs, d, M, n, length):
     assert np.linalg.norm(out - ref) <= tol * np.linalg.norm(ref)
 
 
+@pytest.mark.parametrize("d,M,n", [(32, 512, 8), (8, 64, 3), (64, 256, 16)])
+@pytest.mark.parametrize("below", [0, 60])
+def test_kernel_matvec_columns_of_any_size(fs, d, M, n, below):
+    """Columns of C near 2^-120, 2^-100, 1, 2^40 and of zeros beside each other, one of which is zero but in the last rows; with
+    `below`, only rows count whose features all are 2^-`below` of the others' (a coordinate of their own in C2): results relative to
+    their own column.  An exponent below 128 is rounded to 2^-18; four such roundings are 1.1e-5 of a feature."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(d + below)
+    Nx, Ny = 100, 200
+    X, Y = (0.3 * torch.randn((N, d), generator=gen, device="cuda") for N in (Nx, Ny))
+    X[:, 0] = Y[:, 0] = 0.0
+    Y[::2, 0] = 1.0 if below else 0.0
+    C = torch.randn((Ny, n), generator=gen, device="cuda")
+    C[1::2] *= 0.0 if below else 1.0
+    scale = torch.tensor([2.0 ** e for e in ((-120, -100, 0, 40) if not below else (-60, 0, 40, 90))] * 4, device="cuda")[:n]
+    C *= scale
+    C[:150, 0] = 0.0
+    C[:, n - 1] = 0.0
+    Om = torch.randn((M, d), generator=gen, device="cuda")
+    B, C2 = np.eye(d), np.zeros((d, d))
+    B[0, 0], C2[0, 0] = 0.0, -below * np.log(2.0)
+    td = torch.from_numpy(util.theta_vec_from_oracle(orc.Theta(logD=0.0, A=np.zeros(d), B1=B, B2=B, C1=np.zeros((d, d)), C2=C2))).cuda()
+    out = fs.kernel_matvec(td, X, Y, 1.0, 0.0, Om, C)
+    om, c2 = Om.double(), float(td[8 + d + 3 * d * d])
+    om[:, 0] = 0.0
+    ref = torch.exp(X.double() @ om.T) @ (torch.exp(Y.double() @ om.T + c2 * Y[:, :1].double() ** 2).T @ C.double()) / M
+    for i in range(n - 1):
+        assert float((out[:, i].double() - ref[:, i]).norm() / ref[:, i].norm()) <= 1.1e-5, i
+    assert bool((out[:, n - 1] == 0).all())
+
+
+@pytest.mark.parametrize("below", [100, 118])
+def test_kernel_matvec_features_near_the_least(fs, below):
+    """As above, features down to 2^-124 and C near one: 64 features, whose 1/8 is all that comes off the exponents."""
+    import torch
+    d, M, n = 8, 64, 3
+    gen = torch.Generator(device="cuda").manual_seed(below)
+    X, Y = (0.05 * torch.randn((N, d), generator=gen, device="cuda") for N in (100, 200))
+    X[:, 0] = Y[:, 0] = 0.0
+    Y[::2, 0] = 1.0
+    C = torch.randn((200, n), generator=gen, device="cuda")
+    C[1::2] = 0.0
+    Om = torch.randn((M, d), generator=gen, device="cuda")
+    B, C2 = np.eye(d), np.zeros((d, d))
+    B[0, 0], C2[0, 0] = 0.0, -below * np.log(2.0)
+    td = torch.from_numpy(util.theta_vec_from_oracle(orc.Theta(logD=0.0, A=np.zeros(d), B1=B, B2=B, C1=np.zeros((d, d)), C2=C2))).cuda()
+    out = fs.kernel_matvec(td, X, Y, 1.0, 0.0, Om, C)
+    om, c2 = Om.double(), float(td[8 + d + 3 * d * d])
+    om[:, 0] = 0.0
+    ref = torch.exp(X.double() @ om.T) @ (torch.exp(Y.double() @ om.T + c2 * Y[:, :1].double() ** 2).T @ C.double()) / M
+    assert float((out.double() - ref).norm() / ref.norm()) <= 1.1e-5
+
+
 # ----------------------------------------------------------------------------- fit
 def _fit(fs, entry, variant, Qd, Kd, s, groups):
     """theta [groups, floats] on the host from either fit entry point."""
