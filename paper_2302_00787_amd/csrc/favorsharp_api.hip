@@ -42,7 +42,7 @@ bool groups_ok(int g, int B, int H) { return g == 1 || g == H || g == B * H; }
 
 struct AttnPlan {
   int pgroups, ldt, nseg, rows_per_seg;
-  size_t off_W, off_kpart, off_bias, off_kmax, off_rk, off_state, off_img, img_bytes, off_part, kcap, total;
+  size_t off_W, off_kpart, off_bias, off_kmax, off_rk, off_state, off_img, img_bytes, off_part, off_vmax, off_dmax, off_exps, kcap, total;
 };
 
 // Every attention workspace starts with one 32-bit word (in a block of kAlign bytes): the number of output rows of the
@@ -92,15 +92,27 @@ bool plan_split(int BH, int pgroups, int L, int d, int dv, int M, int dtype, int
   }
   p->off_img = align_up(p->off_state + (size_t)BH * p->nseg * M * p->ldt * sizeof(float));
   p->img_bytes = (size_t)pgroups * 2 * s.tiles * s.steps * 3 * 512 * sizeof(uint16_t);
-  p->off_part = align_up(p->off_img + copies * p->img_bytes);
+  const size_t maxima = (size_t)BH * gen_kmax_parts(L, d) * sizeof(float);
+  p->off_vmax = align_up(p->off_img + copies * p->img_bytes);
+  p->off_dmax = align_up(p->off_vmax + maxima);
+  p->off_exps = align_up(p->off_dmax + (copies > 1 ? maxima : 0));
+  p->off_part = align_up(p->off_exps + (size_t)copies * BH * sizeof(int));
   p->total = align_up(p->off_part + (s.part ? (size_t)gen_split_part_sequences(BH, L, d, dv) * L * gen_split_part_row(d, dv) * sizeof(float) : 0));
   return copies > 1 || base.total > FS_NOALLOC_SCRATCH_BYTES || p->total <= FS_NOALLOC_SCRATCH_BYTES;
 }
-GenSplit split_of(const AttnPlan& p, char* ws, int d, int dv, int M, float scale, bool gradients) {
+GenSplit split_of(const AttnPlan& p, char* ws, int d, int dv, int M, float scale, const fs_tensor* V, const fs_tensor* dY) {
   const GenSplitShape s = gen_split_shape(d, dv, M);
   GenSplit g;
   g.img = (uint16_t*)(ws + p.off_img);
-  if (gradients) g.img_t = (uint16_t*)(ws + p.off_img + p.img_bytes);
+  g.V = dev(V);
+  g.nv = dv;
+  g.vmax = (float*)(ws + p.off_vmax);
+  g.exps = (int*)(ws + p.off_exps);
+  if (dY != nullptr) {
+    g.img_t = (uint16_t*)(ws + p.off_img + p.img_bytes);
+    g.dY = dev(dY);
+    g.dmax = (float*)(ws + p.off_dmax);
+  }
   if (s.part) g.part = (float*)(ws + p.off_part);
   g.tiles = s.tiles;
   g.steps = s.steps;
@@ -595,7 +607,7 @@ int attention_impl(const float* theta, int groups, const fs_tensor* Q, const fs_
     return FS_OK;
   }
   // (it clears the counter word and the key maxima behind it)
-  const GenSplit split = on_split ? split_of(p, ws, d, dv, M, qk_scale, false) : GenSplit();
+  const GenSplit split = on_split ? split_of(p, ws, d, dv, M, qk_scale, V, nullptr) : GenSplit();
   if (int rc = launch_prep(theta, groups, Omega, omega_groups, pgroups, B, H, M, d, W, bias, (uint32_t*)ws,
                            (int)(p.off_kmax / sizeof(uint32_t)) + BH, st, split))
     return rc;
@@ -804,7 +816,7 @@ int attention_backward_impl(const float* theta, int groups, const fs_tensor* Q, 
   // denominators and the query shifts
   // (it clears the counter word and the key maxima behind it)
   unsigned* flushed = (unsigned*)ws;
-  const GenSplit split = p.split ? split_of(p.k, ws, d, dv, M, qk_scale, true) : GenSplit();
+  const GenSplit split = p.split ? split_of(p.k, ws, d, dv, M, qk_scale, V, dY) : GenSplit();
   if (int rc = launch_prep(theta, groups, Omega, omega_groups, pgroups, B, H, M, d, W, bias, (uint32_t*)ws,
                            (int)(p.k.off_kmax / sizeof(uint32_t)) + BH, st, split))
     return rc;
@@ -842,7 +854,7 @@ int attention_backward_impl(const float* theta, int groups, const fs_tensor* Q, 
       return rc;
   }
   // G1 in place of Y, then the segment sums of P^T G1 (the query-side twin of the state pass)
-  if (int rc = launch_bwd_ghat(dev(dY), ghat, den, Lq, BH, H, dv, ldt, st)) return rc;
+  if (int rc = launch_bwd_ghat(dev(dY), ghat, den, split.img ? split.exps + BH : nullptr, Lq, BH, H, dv, ldt, st)) return rc;
   if (int rc = split.img ? launch_split_state(qs, split, false, gbuf, Lq, BH, H, M, d, dv, ldt, p.q.rows_per_seg, p.q.nseg, kmax, nullptr, 0, shift,
                                               rstate, st)
                          : launch_gen_state(qs, gbuf, Lq, BH, H, M, d, ldt, 0, ldt, p.q.rows_per_seg, p.q.nseg, kmax, shift, !walks, rstate, st))

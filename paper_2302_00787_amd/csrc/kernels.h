@@ -43,6 +43,10 @@ size_t gen_lds_stats(int d);
 struct GenSplit {
   uint16_t* img = nullptr;
   uint16_t* img_t = nullptr;
+  TensorDev V{}, dY{};     // values and (gradients) the gradient of the output, whose largest numbers k_gen_kmax finds: partial ones to vmax, dmax
+  int nv = 0;
+  float *vmax = nullptr, *dmax = nullptr;
+  int* exps = nullptr;     // [2][B*H] binary exponents that values and gradient are divided by
   float* part = nullptr;   // [gen_split_part_sequences][rows][gen_split_part_row] of the first of two launches
   int tiles = 0, steps = 0;
   float scale = 1.f;
@@ -64,7 +68,7 @@ int launch_gen_apply(const GenSide& qs, int Lq, int BH, int H, int M, int d, int
                      float* shift_out, hipStream_t st, unsigned* flushed = nullptr);
 // Backward pass of non-causal attention (general-shape kernels).
 size_t gen_lds_bwd_side(int d, int ldt);
-int launch_bwd_ghat(const TensorDev& dY, float* buf, const float* den, int L, int BH, int H, int nv, int ldt,
+int launch_bwd_ghat(const TensorDev& dY, float* buf, const float* den, const int* exps, int L, int BH, int H, int nv, int ldt,
                     hipStream_t st);
 int launch_gen_bwd_side(const GenSide& sd, int side, const TensorDev& A, int a_cols, int append_ones, int L, int BH,
                         int H, int M, int d, int nv, int ldt, const float* St, size_t state_stride,
@@ -112,6 +116,7 @@ int launch_gen_small(const TensorDev& Q, const TensorDev& K, const TensorDev& V,
                      const float* Omega, int omega_groups, int BH, int H, int Lq, int Lk, int d, int nv, int M, float scale,
                      unsigned* flushed, hipStream_t st);
 // Partial key maxima that k_gen_kmax leaves: where (nullptr: the maximum itself in kmax_u) and how many per sequence.
+int gen_kmax_parts(int Lk, int d);
 const float* gen_kmax_part(const GenSide& ks, int Lk, int BH, int d, int* npart);
 bool stats_bf16_supported(const TensorDev& X, const TensorDev& Y, int d);
 int launch_stats_bf16(const TensorDev& X, const TensorDev& Y, int BH, int H, int Lx, int Ly, float scale,

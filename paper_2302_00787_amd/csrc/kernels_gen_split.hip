@@ -30,14 +30,17 @@ template <int Q> constexpr int KS = (Q + 1) / 2;         // steps of 32 coordina
 template <int Q> constexpr int VTP = (VT_OF<Q> + 1) / 2 * 2;
 constexpr int LDR(int cols) { return cols + 8; }         // stride of LDS rows (bf16 numbers)
 constexpr int IMG = 512;                                 // numbers of an operand image
-// Features are lifted before they are split: they lie in 2^-126 .. 1 (a causal row may see only keys whose features are that far
-// below the largest of the sequence), and pieces of numbers below 2^-109 lose bits.  Lifted, one of 2^-126 is off by 2^-20 of itself, less
-// than by the rounding of its exponent, 2^-18.  Sums carry the factors: the keys' states kLift, output rows and normalisers kLift^2
-// (a quotient loses them); G1 is made from normalisers kLift too large, so that the queries' states and every sum with one feature of
-// each side and G1 have none; dV alone is taken back.  (Keys 2^-121 below the largest: outputs 1.1e-5 - 1.8e-5 off without it, gradients
-// 5e-4, now 1e-7 - 3e-7 and 6e-6, as with fp32 instructions; causal f32 B2 H4 L4096 d64 M256 105.9 -> 107.5 us, the gradients of
-// B1 H16 L4096 d128 M512 1631 -> 1632.)
-constexpr float kLift = 4096.f;
+// Pieces of numbers below 2^-109 lose bits, so no operand is left there.  Features lie in 2^-126 .. 1 (a causal row may see only keys
+// whose features are that far below the largest of the sequence); they are lifted by 2^12 before they are split: one of 2^-126 is then off
+// by 2^-20 of itself, less than by the rounding of its exponent, 2^-18.  Values and the gradient of the output are divided by the power
+// of two of the largest of their sequence where that is far from one (k_gen_kmax finds it beside the key maxima), so that the lift
+// leaves room above.  Sums carry the factors.  Output rows and their normalisers have 2^24: the quotient loses it, and G1, made from
+// those normalisers, is 2^24 too small; a sum with one feature of each side and G1 (dV) is as it should be, one with a feature of one
+// side (R, dQ, dK) 2^12 too small.  (Keys 2^-121 below the largest: outputs up to 1.8e-5 off without it, gradients 5e-4, now 3e-7 and
+// 6e-6, as with fp32 instructions; V or dY near 2^-110 / 2^-120: gradients up to 8e-6 / 8e-3 off, now 2e-7 - 8e-7.  causal f32 B2 H4 L4096
+// d64 M256 107.7 -> 111.5 us, of which the maxima of V 1.7; gradients bf16 B1 H16 L4096 d128 M512 1622 -> 1644.)
+constexpr int LIFT = 12;
+constexpr float kLift = 1 << LIFT;
 constexpr float kLeastSum = 0x1p-125f;                   // kLift^2 times the least fp32 number: below it a normaliser counts as zero
 
 typedef __attribute__((ext_vector_type(4))) short s16x4_t;
@@ -112,7 +115,8 @@ template <int COLS, int NW, int P> struct Fetch {
       else v[i] = *(const u32x4*)((const float*)s.ptr + at);
     }
   }
-  __device__ __forceinline__ void put(const RowSrc& s, uint16_t* dst, int row0, int row_end, int tid) {
+  // exponent: the numbers are divided by 2^exponent
+  __device__ __forceinline__ void put(const RowSrc& s, uint16_t* dst, int row0, int row_end, int tid, int exponent = 0) {
     constexpr int LD = LDR(COLS), PLANE = TT * LD;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
@@ -121,9 +125,18 @@ template <int COLS, int NW, int P> struct Fetch {
       const bool live = row0 + row < row_end, in = live && col < s.ncols, one = live && s.one && col == s.ncols;
       uint16_t* at = dst + row * LD + col;
       if constexpr (P == 1) {
-        *(u32x2*)at = in ? v[i] : u32x2{one ? 0x3f80u : 0u, 0u};
+        u32x2 x = v[i];
+        if (__builtin_amdgcn_readfirstlane(exponent) != 0) {                 // (exact but for numbers that leave the exponent range)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            x[j] = __float_as_uint(ldexpf(__uint_as_float(x[j] << 16), -exponent)) >> 16 |
+                   (__float_as_uint(ldexpf(__uint_as_float(x[j] & 0xffff0000u), -exponent)) & 0xffff0000u);
+        }
+        *(u32x2*)at = in ? x : u32x2{one ? 0x3f80u : 0u, 0u};
       } else {
         f32x4 x = __builtin_bit_cast(f32x4, v[i]);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[j] = ldexpf(x[j], -exponent);
         x = in ? x : f32x4{one ? 1.f : 0.f, 0.f, 0.f, 0.f};
         const Split3 q = split3_each(x, x);
         const u32x4 h = __builtin_bit_cast(u32x4, q.h), m = __builtin_bit_cast(u32x4, q.m), l = __builtin_bit_cast(u32x4, q.l);
@@ -135,16 +148,24 @@ template <int COLS, int NW, int P> struct Fetch {
   }
 };
 
+// The binary exponent of the largest number of a tensor's rows, where it is far from one (then they are divided by it).
+__device__ __forceinline__ int far_exponent(float largest) {
+  const int e = __builtin_amdgcn_frexp_expf(largest);      // (0 for what is not finite)
+  return e < -16 || e > 16 ? e : 0;
+}
+
 struct SplitArgs {
   GenSide F, S;            // first side (whose rows enter the state), second side (whose rows are the output's)
   TensorDev V, U;          // values of the first side's rows; (gradient walk) left rows of the second side
   int vcols, vone, ucols, uone;
-  int L, H, M, d, nv, ldt, rows_per_seg, nseg, ntile;
+  int L, BH, H, M, d, nv, ldt, rows_per_seg, nseg, ntile;
   const uint16_t* img;     // [pgroups][2][ntile][KS][3][IMG]: W~ times qk_scale, a lane's feature against eight coordinates
   const uint16_t* img_t;   // [pgroups][2][ntile / 2][2 KS][3][IMG]: a lane's coordinate against eight features
   uint32_t* kmax_u;
   const float* part;       // partial key maxima (k_gen_kmax) or nullptr: kmax_u has the maximum
   int npart;
+  const float *vmax, *dmax;    // partial maxima of |V|, |dY|
+  int* exps;               // [2][BH] exponents of V and dY
   const float* row_shift;  // [BH][L] shifts of the queries
   float* state;            // [BH][nseg][M][ldt]: sums of the segments (written), exclusive prefix or suffix (read)
   TensorDev out;
@@ -249,15 +270,27 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_state(SplitA
   px.get(xf, row_beg, row_end, threadIdx.x);
   pv.get(vf, row_beg, row_end, threadIdx.x);
   float kmax = 0.f;
+  int ve = 0;
   if (KEYS) {
-    if (a.part != nullptr) {
-      kmax = -INFINITY;
-      for (int i = lane; i < a.npart; i += 64) kmax = fmaxf(kmax, a.part[(size_t)bh * a.npart + i]);
+    float km = -INFINITY, vm = 0.f, dm = 0.f;
+    for (int i = lane; i < a.npart; i += 64) {
+      const size_t at = (size_t)bh * a.npart + i;
+      if (a.part != nullptr) km = fmaxf(km, a.part[at]);
+      if (a.dmax != nullptr) dm = fmaxf(dm, a.dmax[at]);
+      vm = fmaxf(vm, a.vmax[at]);
+    }
 #pragma unroll
-      for (int s = 1; s < 64; s <<= 1) kmax = fmaxf(kmax, __shfl_xor(kmax, s));
-      if (seg == 0 && threadIdx.x == 0 && blockIdx.z == 0) a.kmax_u[bh] = float_to_ordered(kmax);      // for the kernels behind this one
-    } else {
-      kmax = ordered_to_float(a.kmax_u[bh]);
+    for (int s = 1; s < 64; s <<= 1) {
+      km = fmaxf(km, __shfl_xor(km, s));
+      vm = fmaxf(vm, __shfl_xor(vm, s));
+      dm = fmaxf(dm, __shfl_xor(dm, s));
+    }
+    kmax = a.part != nullptr ? km : ordered_to_float(a.kmax_u[bh]);
+    ve = far_exponent(vm);
+    if (seg == 0 && threadIdx.x == 0 && blockIdx.z == 0) {      // for the kernels behind this one
+      if (a.part != nullptr) a.kmax_u[bh] = float_to_ordered(km);
+      a.exps[bh] = ve;
+      if (a.dmax != nullptr) a.exps[a.BH + bh] = far_exponent(dm);
     }
   }
   float bf[FT];
@@ -273,7 +306,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_state(SplitA
     asm volatile("" : "+v"(g), "+v"(c));             // (nothing that follows from the lane is kept across chunks)
     __syncthreads();
     px.put(xf, Xs, row0, row_end, threadIdx.x);
-    pv.put(vf, Vs, row0, row_end, threadIdx.x);
+    pv.put(vf, Vs, row0, row_end, threadIdx.x, ve);
     __syncthreads();
     if (row0 + TT < row_end) {
       px.get(xf, row0 + TT, row_end, threadIdx.x);
@@ -349,6 +382,8 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_walk(SplitAr
   const uint16_t* W2 = side_image<Q>(a, a.img, pg, !F_KEYS) + wave_w;
   const float* bias = a.F.bias + (size_t)pg * 2 * M;        // (the same on both sides)
   const float kmax = ordered_to_float(a.kmax_u[bh]);
+  int ve = a.exps[bh], back = MODE ? a.exps[a.BH + bh] : a.den_out == nullptr ? ve : 0;      // of the values, of the output
+  asm("" : "+v"(ve), "+v"(back));                    // (scalar registers are what runs out)
   const int row_beg = seg * a.rows_per_seg, row_end = min(a.L, row_beg + a.rows_per_seg);
   const int nchunk = (row_end - row_beg + TT - 1) / TT;
   const RowSrc xf = row_src(a.F.X, b, h, 0, a.d, 0), xs = row_src(a.S.X, b, h, 0, a.d, 0), vf = row_src(a.V, b, h, 0, a.vcols, a.vone);
@@ -370,7 +405,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_walk(SplitAr
     const int r0 = row_of(ci);
     pf.put(xf, Xf, r0, row_end, tid);
     ps.put(xs, Xs, r0, row_end, tid);
-    pv.put(vf, Vs, r0, row_end, tid);
+    pv.put(vf, Vs, r0, row_end, tid, MODE ? 0 : ve);
   };
   fetch_chunk(0);
   for (int f = threadIdx.x; f < 16 * FT * NW; f += 64 * NW) bl[f] = 16 * a.tile0 + f < M ? bias[16 * a.tile0 + f] : -INFINITY;
@@ -555,7 +590,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_walk(SplitAr
           } else {
             if (a.flushed != nullptr && !(den > kLeastSum)) atomicAdd(a.flushed, 1u);
             if (a.den_out != nullptr) {
-              a.den_out[rec] = den > kLeastSum ? den * (1.f / kLift) : 0.f;
+              a.den_out[rec] = den > kLeastSum ? den : 0.f;
               a.shift_out[rec] = mm;
             }
           }
@@ -571,8 +606,8 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_walk(SplitAr
           if (a.part_out != nullptr) {
             a.part_out[prec * a.ldp + base + col] = v;
           } else {
-            if (!MODE) v = den > kLeastSum ? v / den : 0.f;
-            else v *= 1.f / kLift;
+            if (!MODE) v = den > kLeastSum ? ldexpf(v / den, back) : 0.f;
+            else v = ldexpf(v, back);
             store_elem(a.out, ob + base + col, v);
           }
         }
@@ -621,6 +656,8 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_gwalk(SplitA
   const uint16_t* Wt = side_image<Q>(a, a.img_t, pg, !F_KEYS) + wave_w;
   const float* bias = a.F.bias + (size_t)pg * 2 * M;
   const float kmax = ordered_to_float(a.kmax_u[bh]), scale = a.S.scale;
+  int ve = a.exps[bh], back = ve + a.exps[a.BH + bh] + LIFT;
+  asm("" : "+v"(ve), "+v"(back));
   const int row_beg = seg * a.rows_per_seg, row_end = min(a.L, row_beg + a.rows_per_seg);
   const int nchunk = (row_end - row_beg + TT - 1) / TT;
   const RowSrc xf = row_src(a.F.X, b, h, 0, d, 0), xs = row_src(a.S.X, b, h, 0, d, 0);
@@ -647,8 +684,8 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_gwalk(SplitA
     const int r0 = row_of(ci);
     pf.put(xf, Xf, r0, row_end, tid);
     ps.put(xs, Xs, r0, row_end, tid);
-    pv.put(vf, Vs, r0, row_end, tid);
-    pu.put(uf, Us, r0, row_end, tid);
+    pv.put(vf, Vs, r0, row_end, tid, MODE ? 0 : ve);
+    pu.put(uf, Us, r0, row_end, tid, MODE ? ve : 0);
   };
   // four numbers of a second-side row as they are
   auto x_four = [&](int row, int col) {
@@ -857,7 +894,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_gwalk(SplitA
               for (int i = XP - 1; i >= 0; --i) rc -= bf16_bits_to_f32(Xs[i * XPLANE + row * LDX + d0 + col]);
               rc *= scale;
             }
-            store_elem(a.out, ob + d0 + col, v * kLn2 + scale * (rsum * rc));
+            store_elem(a.out, ob + d0 + col, ldexpf(v * kLn2 + scale * (rsum * rc), back));
           }
         }
       }
@@ -945,11 +982,12 @@ int run_gwalk(const SplitArgs& args, int BH, hipStream_t st) {
     });
   });
 }
-SplitArgs split_args(const GenSide& f, const GenSide& s, const GenSplit& sp, int L, int H, int M, int d, int nv, int ldt, int rows_per_seg,
+SplitArgs split_args(const GenSide& f, const GenSide& s, const GenSplit& sp, int L, int BH, int H, int M, int d, int nv, int ldt, int rows_per_seg,
                      int nseg, uint32_t* kmax_u, const float* row_shift, float* state) {
   SplitArgs a{};
   a.F = f; a.S = s;
-  a.L = L; a.H = H; a.M = M; a.d = d; a.nv = nv; a.ldt = ldt; a.rows_per_seg = rows_per_seg; a.nseg = nseg; a.ntile = tiles_of(M);
+  a.L = L; a.BH = BH; a.H = H; a.M = M; a.d = d; a.nv = nv; a.ldt = ldt; a.rows_per_seg = rows_per_seg; a.nseg = nseg; a.ntile = tiles_of(M);
+  a.vmax = sp.vmax; a.dmax = sp.dmax; a.exps = sp.exps;
   a.img = sp.img; a.img_t = sp.img_t; a.part_out = sp.part; a.ldp = gen_split_part_row(d, nv);
   a.kmax_u = kmax_u; a.row_shift = row_shift; a.state = state;
   return a;
@@ -985,7 +1023,7 @@ GenSplitShape gen_split_shape(int d, int dv, int M) {
 int launch_split_state(const GenSide& side, const GenSplit& sp, bool keys, const TensorDev& V, int L, int BH, int H, int M, int d, int nv,
                        int ldt, int rows_per_seg, int nseg, uint32_t* kmax_u, const float* part, int npart, const float* row_shift,
                        float* state, hipStream_t st) {
-  SplitArgs a = split_args(side, side, sp, L, H, M, d, nv, ldt, rows_per_seg, nseg, kmax_u, row_shift, state);
+  SplitArgs a = split_args(side, side, sp, L, BH, H, M, d, nv, ldt, rows_per_seg, nseg, kmax_u, row_shift, state);
   a.V = V; a.vcols = keys ? nv : ldt; a.vone = keys; a.part = part; a.npart = npart;
   return keys ? run_state<true>(a, BH, st) : run_state<false>(a, BH, st);
 }
@@ -993,7 +1031,7 @@ int launch_split_state(const GenSide& side, const GenSplit& sp, bool keys, const
 int launch_split_walk(const GenSide& qs, const GenSide& ks, const GenSplit& sp, const TensorDev& V, int L, int BH, int H, int M, int d,
                       int nv, int ldt, int rows_per_seg, int nseg, uint32_t* kmax_u, float* Tstate, const TensorDev& Y, float* den_out,
                       float* shift_out, hipStream_t st, unsigned* flushed) {
-  SplitArgs a = split_args(ks, qs, sp, L, H, M, d, nv, ldt, rows_per_seg, nseg, kmax_u, nullptr, Tstate);
+  SplitArgs a = split_args(ks, qs, sp, L, BH, H, M, d, nv, ldt, rows_per_seg, nseg, kmax_u, nullptr, Tstate);
   a.V = V; a.vcols = nv; a.vone = 1; a.out = Y; a.den_out = den_out; a.shift_out = shift_out; a.flushed = flushed;
   return run_walk<0>(a, BH, st);
 }
@@ -1002,10 +1040,10 @@ int launch_split_bwd_walks(const GenSide& qs, const GenSide& ks, const GenSplit&
                            int H, int M, int d, int nv, int ldt, int rows_per_seg, int nseg, uint32_t* kmax_u, const float* row_shift,
                            float* Tstate, float* Rstate, const TensorDev& dQ, const TensorDev& dK, const TensorDev& dV, hipStream_t st) {
   const TensorDev G{ghat, 0, (long long)H * L * ldt, (long long)L * ldt, (long long)ldt};
-  SplitArgs a = split_args(ks, qs, sp, L, H, M, d, nv, ldt, rows_per_seg, nseg, kmax_u, row_shift, Tstate);
+  SplitArgs a = split_args(ks, qs, sp, L, BH, H, M, d, nv, ldt, rows_per_seg, nseg, kmax_u, row_shift, Tstate);
   a.V = V; a.vcols = nv; a.vone = 1; a.U = G; a.ucols = ldt; a.out = dQ;
   if (int rc = run_gwalk<0>(a, BH, st)) return rc;
-  SplitArgs r = split_args(qs, ks, sp, L, H, M, d, nv, ldt, rows_per_seg, nseg, kmax_u, row_shift, Rstate);
+  SplitArgs r = split_args(qs, ks, sp, L, BH, H, M, d, nv, ldt, rows_per_seg, nseg, kmax_u, row_shift, Rstate);
   r.V = G; r.vcols = ldt; r.U = V; r.ucols = nv; r.uone = 1; r.out = dV;
   if (int rc = run_walk<1>(r, BH, st)) return rc;
   r.out = dK;

@@ -851,7 +851,7 @@ __global__ void k_stats_final(const float* part, int B, int H, int nchunks, int 
 
 // In place: row i of `buf` ([bh][L][ldt], holding Y_i in its first nv columns) becomes G1_i (zero padded).
 // Sixteen lanes per row (consecutive columns: coalesced), 16 rows per workgroup of 256 threads.
-__global__ void k_bwd_ghat(TensorDev dY, float* buf, const float* den, int L, int H, int nv, int ldt, size_t rows) {
+__global__ void k_bwd_ghat(TensorDev dY, float* buf, const float* den, const int* exps, int L, int H, int nv, int ldt, size_t rows) {
   const size_t i = (size_t)blockIdx.x * 16 + (threadIdx.x >> 4);
   const int l = threadIdx.x & 15;
   const bool live = i < rows;
@@ -859,16 +859,16 @@ __global__ void k_bwd_ghat(TensorDev dY, float* buf, const float* den, int L, in
   const int bh = (int)(ii / L), row = (int)(ii - (size_t)bh * L), b = bh / H, h = bh % H;
   float* g = buf + ii * ldt;
   const float dn = den[ii];
-  const float inv = dn > 0.f ? 1.f / dn : 0.f;
+  const float inv = dn > 0.f ? 1.f / dn : 0.f, scale = exps != nullptr ? ldexpf(1.f, -exps[bh]) : 1.f;
   const long long base = b * dY.sb + h * dY.sh + (long long)row * dY.sl;
   float dot = 0.f;
-  for (int c = l; c < nv; c += 16) dot += load_elem(dY, base + c) * g[c];
+  for (int c = l; c < nv; c += 16) dot += load_elem(dY, base + c) * scale * g[c];
   dot += __shfl_xor(dot, 1);
   dot += __shfl_xor(dot, 2);
   dot += __shfl_xor(dot, 4);
   dot += __shfl_xor(dot, 8);
   if (!live) return;
-  for (int c = l; c < ldt; c += 16) g[c] = c < nv ? load_elem(dY, base + c) * inv : (c == nv ? -dot * inv : 0.f);
+  for (int c = l; c < ldt; c += 16) g[c] = c < nv ? load_elem(dY, base + c) * scale * inv : (c == nv ? -dot * inv : 0.f);
 }
 
 // One side of the backward pass for a tile of 32 rows.  F = this side's features (query side: per-row shifts from
@@ -1538,10 +1538,10 @@ size_t gen_lds_bwd_side(int d, int ldt) {
   return ((size_t)(TR + MB) * ld + (size_t)(TR + MB) * (ldt + 1) + (size_t)2 * TR * (MB + 1) + MB + 2 * TR) * 4;
 }
 
-int launch_bwd_ghat(const TensorDev& dY, float* buf, const float* den, int L, int BH, int H, int nv, int ldt,
+int launch_bwd_ghat(const TensorDev& dY, float* buf, const float* den, const int* exps, int L, int BH, int H, int nv, int ldt,
                     hipStream_t st) {
   const size_t rows = (size_t)BH * L;
-  hipLaunchKernelGGL(k_bwd_ghat, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, st, dY, buf, den, L, H, nv, ldt, rows);
+  hipLaunchKernelGGL(k_bwd_ghat, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, st, dY, buf, den, exps, L, H, nv, ldt, rows);
   FS_LAUNCH_CHECK();
   return 0;
 }

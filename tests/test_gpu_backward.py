@@ -216,6 +216,36 @@ def test_general_causal_rows_that_see_no_key_are_zero_and_counted(fs, d, M, dtyp
         assert float((x[:, :, n:].double() - y.double()).norm()) <= tol * float(y.double().norm())
 
 
+@pytest.mark.parametrize("kv,kd", [(-120, 0), (-110, 20), (0, -118), (-60, -60), (105, 0), (0, 100), (60, 40)])
+@pytest.mark.parametrize("d,M,dtype", [(32, 160, "f32"), (64, 300, "f32"), (48, 100, "bf16"), (128, 300, "bf16")])
+def test_general_causal_values_of_any_size(fs, d, M, dtype, kv, kd):
+    """V and dY of one sequence near 2^kv and 2^kd, of its neighbours near one (the last: its first 40 rows of V and last 40 of dY
+    2^-80 of the others): outputs and gradients as near to float64 as fp32 sums are, each sequence by itself."""
+    import torch
+    L, n, s = 100, 40, d ** -0.25
+    gen = torch.Generator(device="cuda").manual_seed(d + M)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    Q, K, V, dY = (f * torch.randn((3, 1, L, d), generator=gen, device="cuda") for f in (0.5, 0.5, 1.0, 1.0))
+    V[1] *= 2.0 ** kv
+    dY[1] *= 2.0 ** kd
+    V[2, :, :n] *= 2.0 ** -80
+    dY[2, :, -n:] *= 2.0 ** -80
+    Q, K, V, dY = (x.to(dt) for x in (Q, K, V, dY))
+    Om = torch.randn((1, M, d), generator=gen, device="cuda")
+    td = torch.from_numpy(util.theta_vec_from_oracle(orc.fit_posrf(d))[None]).cuda()
+    Y = fs.attention(td, Q, K, V, s, Om, causal=True, out_dtype=torch.float32)
+    grads = fs.attention_backward(td, Q, K, V, dY, s, Om, causal=True, grad_dtype=torch.float32)
+    om = Om[0].double()
+    for b in range(3):
+        q, k, v = (x[b, 0].double().requires_grad_(True) for x in (Q, K, V))
+        W = torch.tril(torch.exp(s * q @ om.T) @ torch.exp(s * k @ om.T - 0.5 * s * s * (k * k).sum(1, keepdim=True)).T)
+        ref = (W @ v) / W.sum(1, keepdim=True)
+        gref = torch.autograd.grad((ref * dY[b, 0].double()).sum(), (q, k, v))
+        for x, r, name in zip((Y, *grads), (ref.detach(), *gref), "YQKV"):
+            for part in ((slice(0, n), slice(n, L - n), slice(L - n, L)) if b == 2 and name in "YV" else (slice(0, L),)):
+                assert float((x[b, 0, part].double() - r[part]).norm() / r[part].norm()) <= 1.2e-5, (b, name, part)
+
+
 @pytest.mark.parametrize("row", [42, 58])
 @pytest.mark.parametrize("d,M,dtype", [(32, 160, "f32"), (64, 300, "f32"), (48, 100, "bf16"), (128, 300, "bf16")])
 def test_general_causal_rows_that_are_not_finite_stay_in_their_tile(fs, d, M, dtype, row):
