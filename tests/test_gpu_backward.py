@@ -216,6 +216,41 @@ def test_general_causal_rows_that_see_no_key_are_zero_and_counted(fs, d, M, dtyp
         assert float((x[:, :, n:].double() - y.double()).norm()) <= tol * float(y.double().norm())
 
 
+@pytest.mark.parametrize("tg,og", [("H", "H"), ("BH", "1"), ("1", "BH"), ("BH", "H")])
+@pytest.mark.parametrize("variant", ["sderf", "saderf", "aderf"])
+@pytest.mark.parametrize("d,M,dtype", [(64, 256, "f32"), (28, 300, "f32"), (128, 300, "bf16"), (64, 100, "bf16")])
+def test_general_causal_calls_with_parameters_per_head_and_sequence(fs, d, M, dtype, variant, tg, og):
+    """Parameter sets and omegas of their own for heads and sequences, in every combination, isotropic and dense families, one launch
+    and two: attention and gradients of every sequence against float64, at this file's bars."""
+    import torch
+    B, H, L, s = 2, 3, 90, d ** -0.25
+    gen = torch.Generator(device="cuda").manual_seed(d + M)
+    rng = np.random.default_rng(d)
+    count = {"1": 1, "H": H, "BH": B * H}
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    Q, K, V, dY = ((f * torch.randn((B, H, L, d), generator=gen, device="cuda")).to(dt) for f in (0.7, 0.7, 1.0, 1.0))
+    Om = torch.randn((count[og], M, d), generator=gen, device="cuda")
+    ths = [orc.fit(variant, (0.3 + 0.1 * i) * rng.standard_normal((4 * d, d)), 0.4 * rng.standard_normal((4 * d, d))) for i in range(count[tg])]
+    td = torch.from_numpy(np.stack([util.theta_vec_from_oracle(t) for t in ths])).cuda()
+    Y = fs.attention(td, Q, K, V, s, Om, causal=True, out_dtype=torch.float32)
+    grads = fs.attention_backward(td, Q, K, V, dY, s, Om, causal=True, grad_dtype=torch.float32)
+    for b in range(B):
+        for h in range(H):
+            at = {"1": 0, "H": h, "BH": b * H + h}
+            th, om = util.oracle_theta_from_vec(td[at[tg]].cpu().numpy(), d), Om[at[og]].double()
+            A, B1, B2, C2 = (torch.from_numpy(np.asarray(x, dtype=np.float64)).cuda() for x in (th.A, th.B1, th.B2, th.C2))
+            q, k, v = (x[b, h].double().requires_grad_(True) for x in (Q, K, V))
+            bias = (om * om) @ A
+            E1, E2 = s * q @ (om @ B1).T + bias, s * k @ (om @ B2).T + bias + s * s * ((k @ C2) * k).sum(1, keepdim=True)
+            W = torch.tril(torch.exp(E1 - E1.detach().max(1, keepdim=True).values) @ torch.exp(E2 - E2.detach().max()).T)
+            ref = (W @ v) / W.sum(1, keepdim=True)
+            gref = torch.autograd.grad((ref * dY[b, h].double()).sum(), (q, k, v))
+            assert float((Y[b, h].double() - ref.detach()).norm() / ref.detach().norm()) <= 1e-4, (b, h)
+            for g, r, name in zip(grads, gref, ("dQ", "dK", "dV")):
+                fro, row = util.gradient_errors(g[b, h].double().cpu().numpy(), r.cpu().numpy())
+                assert fro <= 3e-4 and row <= 1.2e-3, (b, h, name, fro, row)
+
+
 @pytest.mark.parametrize("kv,kd", [(-120, 0), (-110, 20), (0, -118), (-60, -60), (105, 0), (0, 100), (60, 40)])
 @pytest.mark.parametrize("d,M,dtype", [(32, 160, "f32"), (64, 300, "f32"), (48, 100, "bf16"), (128, 300, "bf16")])
 def test_general_causal_values_of_any_size(fs, d, M, dtype, kv, kd):

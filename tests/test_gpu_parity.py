@@ -320,6 +320,43 @@ def test_attention_of_short_sequences_in_one_launch(fs, d, dv, M, Lq, Lk, B, H, 
     assert int(ws[:4].view(torch.int32)) == 0
 
 
+@pytest.mark.parametrize("B,H", [(1, 1), (2, 3)])
+@pytest.mark.parametrize("Lq,Lk,d,M,dtype", [(70, 40, 16, 64, "f32"), (300, 256, 16, 64, "f32"), (33, 100, 32, 17, "f32"), (150, 60, 12, 32, "bf16")])
+def test_attention_of_short_sequences_counts_zero_normalisers(fs, B, H, Lq, Lk, d, M, dtype):
+    """Every third query has its large features where all keys have theirs 2^-140 below the others, and the other way round (a coordinate
+    whose projection has one sign for queries and the other for keys): no product is left of such a row.  It is zero and counted,
+    whether one workgroup writes the count (one sequence) or several add to it; the rest is as in float64, at the file's bar."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(Lq + d)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    Q, K, V = (0.5 * torch.randn((B, H, L, (d + 7) // 8 * 8), generator=gen, device="cuda") for L in (Lq, Lk, Lk))
+    Q[..., 0], K[..., 0] = 0.0, 1.0
+    Q[:, :, ::3, 0] = 1.0
+    Q, K, V = (x.to(dt)[..., :d] for x in (Q, K, V))
+    Om = torch.randn((1, M, d), generator=gen, device="cuda")
+    Om[0, :, 0] = torch.where(torch.arange(M, device="cuda") % 2 == 0, 70.0, -70.0)
+    B1 = np.eye(d)
+    B1[0, 0] = np.log(2.0)
+    B2 = B1.copy()
+    B2[0, 0] = -np.log(2.0)
+    th = orc.Theta(logD=0.0, A=np.zeros(d), B1=B1, B2=B2, C1=-0.5 * np.eye(d), C2=-0.5 * np.eye(d))
+    ws = torch.full((fs.attention_workspace_bytes(B, H, Lq, Lk, d, d, M, False, 1, 1),), 255, dtype=torch.uint8, device="cuda")
+    Y = fs.attention(torch.from_numpy(util.theta_vec_from_oracle(th)[None]).cuda(), Q, K, V, 1.0, Om, workspace=ws, out_dtype=torch.float32)
+    gone = torch.zeros(Lq, dtype=torch.bool, device="cuda")
+    gone[::3] = True
+    assert fs.attention_flushed_rows(ws) == B * H * int(gone.sum())
+    assert bool((Y[:, :, gone] == 0).all())
+    om = Om[0].double()
+    for b in range(B):
+        for h in range(H):
+            q, k, v = (x[b, h].double() for x in (Q, K, V))
+            q = q[~gone]
+            E1, E2 = q @ (om @ torch.from_numpy(B1).cuda()).T, k @ (om @ torch.from_numpy(B2).cuda()).T - 0.5 * (k * k).sum(1, keepdim=True)
+            P, S = torch.exp(E1 - E1.amax(1, keepdim=True)), torch.exp(E2 - E2.max())
+            ref = (P @ (S.T @ v)) / (P @ S.sum(0))[:, None]
+            assert float((Y[b, h, ~gone].double() - ref).norm() / ref.norm()) <= 1e-4
+
+
 @pytest.mark.parametrize("BH,Lq,Lk,d,M,spread", [(1, 65536, 256, 16, 64, True), (8, 16384, 64, 32, 48, True), (1, 1025, 128, 12, 32, True),
                                                  (1, 1024, 128, 12, 32, False), (95, 17, 40, 32, 64, False), (96, 5000, 33, 8, 40, False),
                                                  (2048, 16, 16, 32, 64, True), (520, 48, 47, 8, 33, True), (2100, 1, 250, 8, 64, True),

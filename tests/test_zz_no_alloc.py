@@ -42,6 +42,24 @@ def test_noalloc_attention_two_calls_in_a_row_second_smaller(fs):
     _case(fs, "c1", True)
 
 
+@pytest.mark.parametrize("d,M,dtype,L", [(64, 256, "f32", 700), (24, 130, "f32", 33), (96, 300, "bf16", 500), (64, 100, "bf16", 1000)])
+def test_noalloc_attention_general_causal_kernels_on_pieces(fs, d, M, dtype, L):
+    """The general causal kernels that keep operand images and (more than 256 features) rows of a first launch in the workspace: the
+    bits of the call with a workspace of its own, and those of the call before on other rows left in the array do not matter."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(d + M)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    Om = torch.randn((2, M, d), generator=gen, device="cuda")
+    for scale in (1.0, 2.0 ** 40):
+        Q, K, V = ((f * torch.randn((1, 2, L, d), generator=gen, device="cuda")).to(dt) for f in (0.5, 0.5, scale))
+        theta = fs.fit_params("saderf", Q, K, d ** -0.25, groups=2)
+        want = fs.attention(theta, Q, K, V, d ** -0.25, Om, causal=True)
+        got = torch.full_like(want, float("nan"))
+        fs.attention_noalloc(theta, Q, K, V, d ** -0.25, Om, got, causal=True)
+        torch.cuda.synchronize()
+        assert torch.isfinite(want.float()).all().item() and torch.equal(got, want)
+
+
 def test_noalloc_attention_counts_zero_normalisers_in_its_own_array(fs):
     """The counter of rows with a zero normaliser is the first word of the scratch array for these calls: four query
     rows 40 times longer than the data's flush on the bf16 kernels and are counted; the next, ordinary call puts the
