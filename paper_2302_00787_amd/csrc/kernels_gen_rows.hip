@@ -479,10 +479,11 @@ int launch_gen_kmax(const GenSide& ks, int Lk, int BH, int H, int M, int d, uint
   return by_width(d, 0, [&](auto width) -> int {
     constexpr int Q = width(), TR = 16 * KMAX_T<Q>;
     auto kernel = d % 4 ? (ks.X.dtype ? k_gen_kmax<Q, 1, 0, 0> : k_gen_kmax<Q, 0, 0, 0>) : (ks.X.dtype ? k_gen_kmax<Q, 1, 1, 0> : k_gen_kmax<Q, 0, 1, 0>);
-    if (split.img != nullptr) {
-      if (ks.X.dtype) kernel = k_gen_kmax<Q, 1, 1, 1>;
-      else if constexpr (Q < 6) kernel = k_gen_kmax<Q, 0, 1, 1>;
-    }
+    if constexpr (Q > 1)         // (the kernels behind begin beyond rows of 16 numbers)
+      if (split.img != nullptr) {
+        if (ks.X.dtype) kernel = k_gen_kmax<Q, 1, 1, 1>;
+        else if constexpr (Q < 6) kernel = k_gen_kmax<Q, 0, 1, 1>;
+      }
     hipLaunchKernelGGL(kernel, dim3((Lk + TR - 1) / TR, BH), dim3(256), 0, st, ks, Lk, H, M, d, kmax_u, kmax_part(ks, Lk, BH, d), split);
     FS_LAUNCH_CHECK();
     return 0;

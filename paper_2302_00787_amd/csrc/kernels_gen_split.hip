@@ -87,7 +87,6 @@ __device__ __forceinline__ Split3 as_split(const Op<3>& a) { return {a.p[0], a.p
 template <int PART = ALL>
 __device__ __forceinline__ f32x4 times(const Split3& a, const Op<3>& b, f32x4 c) { return mfma3<PART>(a, as_split(b), c); }
 __device__ __forceinline__ f32x4 times(const Op<3>& a, const Split3& b, f32x4 c) { return mfma3_t(as_split(a), b, c); }
-__device__ __forceinline__ f32x4 times(const Op<1>& a, const Op<1>& b, f32x4 c) { return mfma_bf16(a.p[0], b.p[0], c); }
 __device__ __forceinline__ f32x4 times(const Op<1>& a, const Op<3>& b, f32x4 c) { return times(a, as_split(b), c); }
 __device__ __forceinline__ f32x4 times(const Op<3>& a, const Op<1>& b, f32x4 c) { return times(as_split(a), b, c); }
 __device__ __forceinline__ f32x4 times(const Op<3>& a, const Op<3>& b, f32x4 c) { return mfma3(as_split(a), as_split(b), c); }

@@ -884,6 +884,45 @@ def test_backward_call_replays_from_a_hip_graph(fs, name, over, prepared):
         _ = torch.randn(1 << 20, device="cuda").sum().item()
 
 
+@pytest.mark.parametrize("d,M,dtype", [(64, 256, "f32"), (128, 300, "bf16")])
+def test_general_causal_calls_replay_on_other_values(fs, d, M, dtype):
+    """Attention and gradients captured once and replayed on inputs of other sizes (the powers of two that values and dY are divided by
+    are found by every replay): the bits of eager calls on the same inputs."""
+    import torch
+    L, s = 300, d ** -0.25
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    Q, K, V, dY = ((f * torch.randn((1, 2, L, d), generator=gen, device="cuda")).to(dt) for f in (0.5, 0.5, 1.0, 1.0))
+    Om = torch.randn((2, M, d), generator=gen, device="cuda")
+    theta = fs.fit_params("saderf", Q, K, s, groups=2)
+    ws = torch.empty(fs.attention_backward_workspace_bytes(1, 2, L, L, d, d, M, True, 2, 2), dtype=torch.uint8, device="cuda")
+    Y, grads = torch.empty_like(V), tuple(torch.empty_like(x) for x in (Q, K, V))
+
+    def call():
+        fs.attention(theta, Q, K, V, s, Om, causal=True, workspace=ws, out=Y)
+        fs.attention_backward(theta, Q, K, V, dY, s, Om, causal=True, workspace=ws, grads=grads)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        call()
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for kv, kd in ((0, 0), (60, -50), (-100, 0), (0, 30)):
+        V.copy_(V.float() * 2.0 ** kv)
+        dY.copy_(dY.float() * 2.0 ** kd)
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [x.clone() for x in (Y, *grads)]
+        call()
+        torch.cuda.synchronize()
+        assert all(torch.isfinite(x.float()).all().item() and torch.equal(x, y) for x, y in zip(got, (Y, *grads))), (kv, kd)
+        V.copy_(V.float() * 2.0 ** -kv)
+        dY.copy_(dY.float() * 2.0 ** -kd)
+
+
 def test_backward_error_paths(fs):
     import torch
     Q = torch.zeros((1, 1, 8, 8), device="cuda")
