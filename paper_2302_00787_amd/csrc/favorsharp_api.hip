@@ -92,7 +92,7 @@ bool plan_split(int BH, int pgroups, int L, int d, int dv, int M, int dtype, int
   }
   p->off_img = align_up(p->off_state + (size_t)BH * p->nseg * M * p->ldt * sizeof(float));
   p->img_bytes = (size_t)pgroups * 2 * s.tiles * s.steps * 3 * 512 * sizeof(uint16_t);
-  const size_t maxima = (size_t)BH * gen_kmax_parts(L, d) * sizeof(float);
+  const size_t maxima = (size_t)BH * ceil_div(L, VMAX_ROWS) * sizeof(float);
   p->off_vmax = align_up(p->off_img + copies * p->img_bytes);
   p->off_dmax = align_up(p->off_vmax + maxima);
   p->off_exps = align_up(p->off_dmax + (copies > 1 ? maxima : 0));
@@ -100,12 +100,14 @@ bool plan_split(int BH, int pgroups, int L, int d, int dv, int M, int dtype, int
   p->total = align_up(p->off_part + (s.part ? (size_t)gen_split_part_sequences(BH, L, d, dv) * L * gen_split_part_row(d, dv) * sizeof(float) : 0));
   return copies > 1 || base.total > FS_NOALLOC_SCRATCH_BYTES || p->total <= FS_NOALLOC_SCRATCH_BYTES;
 }
-GenSplit split_of(const AttnPlan& p, char* ws, int d, int dv, int M, float scale, const fs_tensor* V, const fs_tensor* dY) {
+GenSplit split_of(const AttnPlan& p, char* ws, int BH, int L, int d, int dv, int M, float scale, const fs_tensor* V, const fs_tensor* dY) {
   const GenSplitShape s = gen_split_shape(d, dv, M);
   GenSplit g;
   g.img = (uint16_t*)(ws + p.off_img);
   g.V = dev(V);
   g.nv = dv;
+  g.L = L;
+  g.BH = BH;
   g.vmax = (float*)(ws + p.off_vmax);
   g.exps = (int*)(ws + p.off_exps);
   if (dY != nullptr) {
@@ -607,7 +609,7 @@ int attention_impl(const float* theta, int groups, const fs_tensor* Q, const fs_
     return FS_OK;
   }
   // (it clears the counter word and the key maxima behind it)
-  const GenSplit split = on_split ? split_of(p, ws, d, dv, M, qk_scale, V, nullptr) : GenSplit();
+  const GenSplit split = on_split ? split_of(p, ws, BH, Lk, d, dv, M, qk_scale, V, nullptr) : GenSplit();
   if (int rc = launch_prep(theta, groups, Omega, omega_groups, pgroups, B, H, M, d, W, bias, (uint32_t*)ws,
                            (int)(p.off_kmax / sizeof(uint32_t)) + BH, st, split))
     return rc;
@@ -816,7 +818,7 @@ int attention_backward_impl(const float* theta, int groups, const fs_tensor* Q, 
   // denominators and the query shifts
   // (it clears the counter word and the key maxima behind it)
   unsigned* flushed = (unsigned*)ws;
-  const GenSplit split = p.split ? split_of(p.k, ws, d, dv, M, qk_scale, V, dY) : GenSplit();
+  const GenSplit split = p.split ? split_of(p.k, ws, BH, Lk, d, dv, M, qk_scale, V, dY) : GenSplit();
   if (int rc = launch_prep(theta, groups, Omega, omega_groups, pgroups, B, H, M, d, W, bias, (uint32_t*)ws,
                            (int)(p.k.off_kmax / sizeof(uint32_t)) + BH, st, split))
     return rc;

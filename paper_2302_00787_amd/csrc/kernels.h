@@ -40,12 +40,13 @@ size_t gen_lds_stats(int d);
 
 // Operand images of the projection matrices in bf16 pieces (kernels_gen_split.hip): W~ times qk_scale for `tiles` tiles of 16
 // features and `steps` steps of 32 coordinates; img_t, for the gradients only, by coordinate.
+constexpr int VMAX_ROWS = 64;
 struct GenSplit {
   uint16_t* img = nullptr;
   uint16_t* img_t = nullptr;
-  TensorDev V{}, dY{};     // values and (gradients) the gradient of the output, whose largest numbers k_gen_kmax finds: partial ones to vmax, dmax
-  int nv = 0;
-  float *vmax = nullptr, *dmax = nullptr;
+  TensorDev V{}, dY{};     // values and (gradients) the gradient of the output; k_prep leaves the largest numbers of VMAX_ROWS rows each:
+  int nv = 0, L = 0, BH = 0;
+  float *vmax = nullptr, *dmax = nullptr;      // [BH][ceil(L / VMAX_ROWS)]
   int* exps = nullptr;     // [2][B*H] binary exponents that values and gradient are divided by
   float* part = nullptr;   // [gen_split_part_sequences][rows][gen_split_part_row] of the first of two launches
   int tiles = 0, steps = 0;
@@ -116,7 +117,6 @@ int launch_gen_small(const TensorDev& Q, const TensorDev& K, const TensorDev& V,
                      const float* Omega, int omega_groups, int BH, int H, int Lq, int Lk, int d, int nv, int M, float scale,
                      unsigned* flushed, hipStream_t st);
 // Partial key maxima that k_gen_kmax leaves: where (nullptr: the maximum itself in kmax_u) and how many per sequence.
-int gen_kmax_parts(int Lk, int d);
 const float* gen_kmax_part(const GenSide& ks, int Lk, int BH, int d, int* npart);
 bool stats_bf16_supported(const TensorDev& X, const TensorDev& Y, int d);
 int launch_stats_bf16(const TensorDev& X, const TensorDev& Y, int BH, int H, int Lx, int Ly, float scale,

@@ -92,32 +92,11 @@ __device__ __forceinline__ f32x4 lane_rows_transposed(f32x4 v) {
 template <int Q> constexpr int KMAX_T = Q >= 6 ? 2 : 4;      // token tiles per workgroup
 // SP: the projection on bf16 pieces (split3.h), W~ from the images of the kernels behind (bf16 B1 H16 L4096 d128 M512 92 -> 66 us, f32
 // B2 H4 L4096 d64 M256 17.2 -> 14.7).
-// The largest number of a workgroup's rows of a tensor, a part per thread: N times four numbers, requested at once.
-template <int BF, int N>
-__device__ __forceinline__ float largest_of(const TensorDev& t, long long base, int row0, int rows, int cols) {
-  typename std::conditional<BF, u32x2, f32x4>::type v[N];
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    const int e = min((int)threadIdx.x + 256 * i, rows * cols - 1), row = e / cols;
-    const long long at = base + (long long)(row0 + row) * t.sl + 4 * (e - row * cols);
-    if constexpr (BF) v[i] = *(const u32x2*)((const uint16_t*)t.ptr + at);
-    else v[i] = *(const f32x4*)((const float*)t.ptr + at);
-  }
-  float m = 0.f;
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    f32x4 x;
-    if constexpr (BF) x = f32x4{__uint_as_float(v[i][0] << 16), __uint_as_float(v[i][0] & 0xffff0000u), __uint_as_float(v[i][1] << 16), __uint_as_float(v[i][1] & 0xffff0000u)};
-    else x = v[i];
-    m = fmaxf(fmaxf(m, fmaxf(fabsf(x[0]), fabsf(x[1]))), fmaxf(fabsf(x[2]), fabsf(x[3])));
-  }
-  return m;
-}
 template <int Q, int XB, int D4, int SP>
 __global__ void __launch_bounds__(256, 2) k_gen_kmax(GenSide ks, int Lk, int H, int M, int d, uint32_t* kmax_u, float* part, GenSplit split) {
   constexpr int TT = KMAX_T<Q>;
   __shared__ __align__(16) float rpart[4][16 * TT];
-  __shared__ float wmax[4], vmax[4], dmax[4];
+  __shared__ float wmax[4];
   const int bh = blockIdx.y, b = bh / H, h = bh % H, row0 = blockIdx.x * 16 * TT;
   const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -133,14 +112,6 @@ __global__ void __launch_bounds__(256, 2) k_gen_kmax(GenSide ks, int Lk, int H, 
   RawRow<XB, Q> raw[TT];
 #pragma unroll
   for (int t = 0; t < TT; ++t) fetch_row<D4>(raw[t], ks.X, xbase + (long long)min(row0 + 16 * t + c, Lk - 1) * ks.X.sl, d, g);
-  float vm = 0.f, dm = 0.f;
-  if (SP) {
-    constexpr int N = (16 * TT * (Q < 4 ? 11 : Q < 6 ? 19 : 32) + 255) / 256;      // (columns in fours beside rows of that width)
-    const int cols = split.nv / 4, rows = min(16 * TT, Lk - row0);
-    const long long db = b * split.dY.sb + h * split.dY.sh;
-    vm = largest_of<XB, N>(split.V, b * split.V.sb + h * split.V.sh, row0, rows, cols);
-    if (split.dmax != nullptr) dm = split.dY.dtype ? largest_of<1, N>(split.dY, db, row0, rows, cols) : largest_of<0, N>(split.dY, db, row0, rows, cols);
-  }
   const int nft = (M + 15) / 16;
   RawRow<0, Q> wn;
   if (!SP) fetch_row<D4>(wn, W, (long long)min(16 * w + c, M - 1) * d, d, g);
@@ -304,24 +275,9 @@ __global__ void __launch_bounds__(256, 2) k_gen_kmax(GenSide ks, int Lk, int H, 
     }
   }
 #pragma unroll
-  for (int s = 1; s < 64; s <<= 1) {
-    m = fmaxf(m, __shfl_xor(m, s));
-    if (SP) {
-      vm = fmaxf(vm, __shfl_xor(vm, s));
-      dm = fmaxf(dm, __shfl_xor(dm, s));
-    }
-  }
-  if (lane == 0) {
-    wmax[w] = m;
-    vmax[w] = vm;
-    dmax[w] = dm;
-  }
+  for (int s = 1; s < 64; s <<= 1) m = fmaxf(m, __shfl_xor(m, s));
+  if (lane == 0) wmax[w] = m;
   __syncthreads();
-  if (SP && threadIdx.x == 64) {
-    const size_t at = (size_t)bh * gridDim.x + blockIdx.x;
-    split.vmax[at] = fmaxf(fmaxf(vmax[0], vmax[1]), fmaxf(vmax[2], vmax[3]));
-    if (split.dmax != nullptr) split.dmax[at] = fmaxf(fmaxf(dmax[0], dmax[1]), fmaxf(dmax[2], dmax[3]));
-  }
   if (threadIdx.x == 0) {
     m = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
     if (part != nullptr) part[(size_t)bh * gridDim.x + blockIdx.x] = m;
@@ -465,13 +421,13 @@ __global__ void __launch_bounds__(256, 2) k_gen_state(GenSide ks, TensorDev V, i
 static int kmax_rows(int d) {
   return by_width(d, 0, [](auto q) { return 16 * KMAX_T<q()>; });
 }
-int gen_kmax_parts(int Lk, int d) { return (Lk + kmax_rows(d) - 1) / kmax_rows(d); }
 static float* kmax_part(const GenSide& ks, int Lk, int BH, int d) {
-  return ks.kpart != nullptr && (size_t)BH * gen_kmax_parts(Lk, d) <= ks.kcap ? ks.kpart : nullptr;
+  const int n = (Lk + kmax_rows(d) - 1) / kmax_rows(d);
+  return ks.kpart != nullptr && (size_t)BH * n <= ks.kcap ? ks.kpart : nullptr;
 }
 
 const float* gen_kmax_part(const GenSide& ks, int Lk, int BH, int d, int* npart) {
-  *npart = gen_kmax_parts(Lk, d);
+  *npart = (Lk + kmax_rows(d) - 1) / kmax_rows(d);
   return kmax_part(ks, Lk, BH, d);
 }
 

@@ -33,12 +33,12 @@ constexpr int IMG = 512;                                 // numbers of an operan
 // Pieces of numbers below 2^-109 lose bits, so no operand is left there.  Features lie in 2^-126 .. 1 (a causal row may see only keys
 // whose features are that far below the largest of the sequence); they are lifted by 2^12 before they are split: one of 2^-126 is then off
 // by 2^-20 of itself, less than by the rounding of its exponent, 2^-18.  Values and the gradient of the output are divided by the power
-// of two of the largest of their sequence where that is far from one (k_gen_kmax finds it beside the key maxima), so that the lift
+// of two of the largest of their sequence where that is far from one (k_prep finds it beside the constants), so that the lift
 // leaves room above.  Sums carry the factors.  Output rows and their normalisers have 2^24: the quotient loses it, and G1, made from
 // those normalisers, is 2^24 too small; a sum with one feature of each side and G1 (dV) is as it should be, one with a feature of one
 // side (R, dQ, dK) 2^12 too small.  (Keys 2^-121 below the largest: outputs up to 1.8e-5 off without it, gradients 5e-4, now 3e-7 and
 // 6e-6, as with fp32 instructions; V or dY near 2^-110 / 2^-120: gradients up to 8e-6 / 8e-3 off, now 2e-7 - 8e-7.  causal f32 B2 H4 L4096
-// d64 M256 107.7 -> 111.5 us, of which the maxima of V 1.7; gradients bf16 B1 H16 L4096 d128 M512 1622 -> 1644.)
+// d64 M256 106.5 -> 108.3 us; gradients bf16 B1 H16 L4096 d128 M512 1622 -> 1653, of which the maxima 10.)
 constexpr int LIFT = 12;
 constexpr float kLift = 1 << LIFT;
 constexpr float kLeastSum = 0x1p-125f;                   // kLift^2 times the least fp32 number: below it a normaliser counts as zero
@@ -163,7 +163,8 @@ struct SplitArgs {
   uint32_t* kmax_u;
   const float* part;       // partial key maxima (k_gen_kmax) or nullptr: kmax_u has the maximum
   int npart;
-  const float *vmax, *dmax;    // partial maxima of |V|, |dY|
+  const float *vmax, *dmax;    // [BH][nvmax] partial maxima of |V|, |dY|
+  int nvmax;
   int* exps;               // [2][BH] exponents of V and dY
   const float* row_shift;  // [BH][L] shifts of the queries
   float* state;            // [BH][nseg][M][ldt]: sums of the segments (written), exclusive prefix or suffix (read)
@@ -272,11 +273,11 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_state(SplitA
   int ve = 0;
   if (KEYS) {
     float km = -INFINITY, vm = 0.f, dm = 0.f;
-    for (int i = lane; i < a.npart; i += 64) {
-      const size_t at = (size_t)bh * a.npart + i;
-      if (a.part != nullptr) km = fmaxf(km, a.part[at]);
-      if (a.dmax != nullptr) dm = fmaxf(dm, a.dmax[at]);
-      vm = fmaxf(vm, a.vmax[at]);
+    if (a.part != nullptr)
+      for (int i = lane; i < a.npart; i += 64) km = fmaxf(km, a.part[(size_t)bh * a.npart + i]);
+    for (int i = lane; i < a.nvmax; i += 64) {
+      vm = fmaxf(vm, a.vmax[(size_t)bh * a.nvmax + i]);
+      if (a.dmax != nullptr) dm = fmaxf(dm, a.dmax[(size_t)bh * a.nvmax + i]);
     }
 #pragma unroll
     for (int s = 1; s < 64; s <<= 1) {
@@ -986,7 +987,7 @@ SplitArgs split_args(const GenSide& f, const GenSide& s, const GenSplit& sp, int
   SplitArgs a{};
   a.F = f; a.S = s;
   a.L = L; a.BH = BH; a.H = H; a.M = M; a.d = d; a.nv = nv; a.ldt = ldt; a.rows_per_seg = rows_per_seg; a.nseg = nseg; a.ntile = tiles_of(M);
-  a.vmax = sp.vmax; a.dmax = sp.dmax; a.exps = sp.exps;
+  a.vmax = sp.vmax; a.dmax = sp.dmax; a.nvmax = (L + VMAX_ROWS - 1) / VMAX_ROWS; a.exps = sp.exps;
   a.img = sp.img; a.img_t = sp.img_t; a.part_out = sp.part; a.ldp = gen_split_part_row(d, nv);
   a.kmax_u = kmax_u; a.row_shift = row_shift; a.state = state;
   return a;

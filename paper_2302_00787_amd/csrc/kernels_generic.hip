@@ -323,12 +323,58 @@ __device__ void rowmax_pass2(uint32_t* rowmax_u, const float* Xs, float* Ws, flo
 // (omega_m^T A omega_m + log D - 1/2 log M).  grid (ceil(M/4), 2 sides, pgroups), block 128: thread c carries column c
 // of four features, so that a row of B is read once for the four, eight rows at a time in flight (one feature per
 // workgroup and one load at a time: 231 us for 16 heads of d 128, M 512 and 24 us for 4 of d 64, M 256; now 28 and 8).  Four and not
-// more: with few features the launch would leave most of the chip idle.
+// more: with few features the launch would leave most of the chip idle.  Further layers of the grid's second axis: value_maxima.
 // ---------------------------------------------------------------------------------------------------
 constexpr int PREP_F = 4;
+
+// The largest of rows row0 .. row0 + rows - 1 of a tensor, 4 cols numbers each, by 128 threads.
+__device__ __forceinline__ float largest_of(const TensorDev& t, long long base, int row0, int rows, int cols, float* red) {
+  float m = 0.f;
+  for (int e0 = threadIdx.x; e0 < rows * cols; e0 += 8 * 128) {
+    f32x4 v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int e = min(e0 + 128 * i, rows * cols - 1), row = e / cols;
+      const long long at = base + (long long)(row0 + row) * t.sl + 4 * (e - row * cols);
+      if (t.dtype) {
+        const u32x2 p = *(const u32x2*)((const uint16_t*)t.ptr + at);
+        v[i] = f32x4{__uint_as_float(p[0] << 16), __uint_as_float(p[0] & 0xffff0000u), __uint_as_float(p[1] << 16), __uint_as_float(p[1] & 0xffff0000u)};
+      } else {
+        v[i] = *(const f32x4*)((const float*)t.ptr + at);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) m = fmaxf(fmaxf(m, fmaxf(fabsf(v[i][0]), fabsf(v[i][1]))), fmaxf(fabsf(v[i][2]), fabsf(v[i][3])));
+  }
+#pragma unroll
+  for (int s = 1; s < 64; s <<= 1) m = fmaxf(m, __shfl_xor(m, s));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  __syncthreads();
+  m = fmaxf(red[0], red[1]);
+  __syncthreads();
+  return m;
+}
+// Partial maxima of values and gradient, on the compute units that the constants leave idle (causal f32 B2 H4 L4096 d64 M256: 0.8 us,
+// in k_gen_kmax, whose rows they are, 1.7).
+__device__ __forceinline__ void value_maxima(const GenSplit& sp, int H, int first, int step, float* red) {
+  const int parts = (sp.L + VMAX_ROWS - 1) / VMAX_ROWS, cols = sp.nv / 4;
+  for (int p = first; p < sp.BH * parts; p += step) {
+    const int bh = p / parts, b = bh / H, h = bh % H, row0 = (p - bh * parts) * VMAX_ROWS, rows = min(VMAX_ROWS, sp.L - row0);
+    const float v = largest_of(sp.V, b * sp.V.sb + h * sp.V.sh, row0, rows, cols, red);
+    const float g = sp.dmax != nullptr ? largest_of(sp.dY, b * sp.dY.sb + h * sp.dY.sh, row0, rows, cols, red) : 0.f;
+    if (threadIdx.x == 0) {
+      sp.vmax[p] = v;
+      if (sp.dmax != nullptr) sp.dmax[p] = g;
+    }
+  }
+}
 __global__ void __launch_bounds__(128) k_prep(const float* theta, int groups, const float* Omega, int omega_groups, int pgroups,
                        int B, int H, int M, int d, float* W, float* bias, uint32_t* clear, int nclear, GenSplit split) {
   __shared__ float om[PREP_F][128];
+  if (blockIdx.y >= 2) {
+    value_maxima(split, H, ((blockIdx.y - 2) * gridDim.z + blockIdx.z) * gridDim.x + blockIdx.x, (gridDim.y - 2) * gridDim.z * gridDim.x, om[0]);
+    return;
+  }
   const int m0 = blockIdx.x * PREP_F, side = blockIdx.y, pg = blockIdx.z, nf = min(PREP_F, M - m0);
   int b = 0, h = 0;
   if (pgroups == H && pgroups != 1) h = pg;
@@ -1480,7 +1526,10 @@ static int by_width(int d, int ldt, F launch) {
 int launch_prep(const float* theta, int groups, const float* Omega, int omega_groups, int pgroups, int B, int H,
                 int M, int d, float* W, float* bias, uint32_t* clear, int nclear, hipStream_t st, const GenSplit& split) {
   const int features = split.img != nullptr ? 16 * split.tiles : M;
-  hipLaunchKernelGGL(k_prep, dim3((features + PREP_F - 1) / PREP_F, 2, pgroups), dim3(128), 0, st, theta, groups, Omega, omega_groups, pgroups, B, H,
+  const int nx = (features + PREP_F - 1) / PREP_F;
+  const long long parts = split.img != nullptr ? (long long)split.BH * ((split.L + VMAX_ROWS - 1) / VMAX_ROWS) : 0;
+  const long long layers = (parts + (long long)nx * pgroups - 1) / ((long long)nx * pgroups);      // (of the grid, for value_maxima)
+  hipLaunchKernelGGL(k_prep, dim3(nx, 2 + (unsigned)(layers < 1024 ? layers : 1024), pgroups), dim3(128), 0, st, theta, groups, Omega, omega_groups, pgroups, B, H,
                      M, d, W, bias, clear, nclear, split);
   FS_LAUNCH_CHECK();
   return 0;
