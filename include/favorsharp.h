@@ -29,6 +29,9 @@
  *     content is undefined afterwards; calls that share a workspace must be
  *     ordered by the caller; there is no global mutable state apart from
  *     favorsharp_attention_noalloc's scratch array;
+ *   - inputs are not checked for numbers that are not finite: what depends on one may come out as an infinity, as NaN
+ *     or as a row of zeros that is counted (favorsharp_attention_flushed_rows), in causal calls also rows of the same
+ *     block of up to 64 tokens;
  *   - tensors are row-major; an fs_tensor carries element strides for the
  *     batch, head and row axes, the innermost (feature) axis has stride 1 and
  *     row starts must be 16-byte aligned (stride_l a multiple of 8 for bf16, of 4 for f32);

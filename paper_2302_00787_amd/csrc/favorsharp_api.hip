@@ -77,7 +77,8 @@ bool plan_split(int BH, int pgroups, int L, int d, int dv, int M, int dtype, int
   if (!(copies > 1 ? gen_split_backward(d, dv, M, dtype) : gen_split_attention(d, dv, M, dtype))) return false;
   *p = base;
   const GenSplitShape s = gen_split_shape(d, dv, M);
-  // one workgroup of eight waves per CU; the fewest chunks in sequence over one to four passes, a workgroup's start being two
+  // one workgroup of eight waves per CU, or two of four (rows beyond 64 take the LDS of a CU with four waves too: their segments are cut
+  // for more places than there are); the fewest chunks in sequence over one to four passes, a workgroup's start being two
   const int slots = 256 * 8 / s.waves;
   int best = 0;
   for (int passes = 1; passes <= 4; ++passes) {

@@ -10,9 +10,9 @@
 //
 // What bounds it: the matrix pipe needs 96 cycles for 16 x 16 x 32 numbers (48 against bf16 tensors; fp32 instructions 256), splitting an
 // accumulator pair 28 vector instructions; W~ is 6 bytes per feature and coordinate and chunk from L2.  Two waves per SIMD overlap the two
-// pipes about half.  Against fp32 instructions: causal attention f32 B2 H4 L4096 d64 M256 147 -> 106 us (walk 87 -> 61, states 38 -> 24),
-// gradients bf16 B1 H16 L4096 d128 M512 3510 -> 1630 (four walks 2570 -> 1340 in eight launches, two states 680 -> 183), results
-// of 20 f32 calls 0.9 times as far from 64 bits.
+// pipes about half.  Against fp32 instructions: causal attention f32 B2 H4 L4096 d64 M256 147 -> 107 us (walk 87 -> 61, states 38 -> 26),
+// gradients bf16 B1 H16 L4096 d128 M512 3510 -> 1655 (four walks 2570 -> 1320 in eight launches, two states 680 -> 188), results
+// of 60 drawn calls 0.93 times as far from 64 bits.
 #include <type_traits>
 
 #include "gen_widths.h"
@@ -1001,6 +1001,9 @@ SplitArgs split_args(const GenSide& f, const GenSide& s, const GenSplit& sp, int
 //              bf16  M <= 64 0.81 - 1.06;  M >= 100: d 8, 16 0.96 - 1.13, d 24 .. 128 1.04 - 1.48
 //   gradients  f32   M <= 64 0.72 - 0.82;  M 100, 128 0.86 - 1.08;  M 200, 256: d 8, 16 0.91 - 0.97, d 24 .. 64 1.10 - 1.40
 //              bf16  M <= 64 0.69 - 0.99;  M >= 100: d 8, 16 1.04 - 1.07, d 24 .. 128 1.15 - 1.50 (d 80 M 100, 128 0.96 - 1.04)
+// and, as features pad to 128, 256 or 512, over numbers between those (2 x 700, 16 x 1024 and 32 x 2048 head-tokens, d 24 .. 128)
+//   attention  f32   M 129 .. 256 1.18 - 1.67, 257 .. 512 1.19 - 1.70;  bf16  65 .. 128 1.33 - 1.89, 129 .. 256 1.39 - 2.07, 257 .. 512 1.33 - 1.96
+//   gradients  f32   M 129 .. 256 1.17 - 2.04, 257 .. 512 1.14 - 1.93;  bf16  65 .. 128 1.42 - 2.04, 129 .. 256 1.34 - 2.45, 257 .. 512 1.22 - 2.56
 static bool split_rows(int d, int dv, int dtype) {
   const int ldt = (dv + 16) / 16 * 16;
   return d % 4 == 0 && dv % 4 == 0 && d > 16 && width_of(d, 0) == width_of(0, ldt) && (dtype || width_of(d, ldt) < 8);

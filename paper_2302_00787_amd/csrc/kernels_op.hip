@@ -25,8 +25,8 @@
 //
 // What bounds it: matrix pipe, exponentials and splits are 3 - 4 us of each of the two main kernels (256 workgroups of c2), the rest is
 // the launch and the chain rows -> operands -> first tile.  With fp32 instructions and Cauchy-Schwarz bounds over all features as
-// shifts (N 16384, d 32, M 512, n 8): k_op_state 25.3 us, now 15.1, k_op_apply
-// 20.7 and 10.3, the call 52.9 and 29.9; 40 calls of N 256 .. 32768, d 8 .. 64: results 0.65 times as far from 64 bits.
+// shifts (N 16384, d 32, M 512, n 8): k_op_state 25.3 us, now 15.0, k_op_apply
+// 20.7 and 9.8, the call 52.3 and 29.2; 40 calls of N 256 .. 32768, d 8 .. 64: results 0.56 times as far from 64 bits.
 #include <algorithm>
 
 #include "fast_common.h"

@@ -2,8 +2,9 @@
 // left: 24 bits), a product of two numbers six products of pieces; those left out are below 2^-24 of it.  Six
 // v_mfma_f32_16x16x32_bf16 take 96 cycles where eight v_mfma_f32_16x16x4_f32 take 256.  The pieces' products are exact and 32 of
 // them are summed at once, so a sum over K numbers is nearer to 64 bits than the chain of fp32 instructions: error of K = 128 /
-// 1024 / 16384 random products 0.7 / 0.8 / 0.9 of it, of positive ones 0.5 / 0.5 / 0.6.  A number that is not finite gives NaN;
-// below 2^-109 the last pieces leave the exponent range.
+// 1024 / 16384 random products 0.7 / 0.8 / 0.9 of it, of positive ones 0.5 / 0.5 / 0.6.  A number that is not finite gives NaN.  Below
+// 2^-109 the last pieces leave the exponent range (subnormal pieces count: a number is then off by up to 2^-134): the kernels scale what
+// they split so that nothing that matters is left there.
 #pragma once
 #include "fs_common.h"
 
