@@ -74,7 +74,7 @@ void plan_contraction(int BH, int pgroups, int Lk, int d, int M, int nv1, int ca
 // gradients), rows between two launches.  `base` is the plan of the other kernels: no call that fits the scratch array with
 // that one stops fitting it.
 bool plan_split(int BH, int pgroups, int L, int d, int dv, int M, int dtype, int copies, const AttnPlan& base, AttnPlan* p) {
-  if (!(copies > 1 ? gen_split_backward(d, dv, M, dtype) : gen_split_attention(d, dv, M, dtype))) return false;
+  if (!(copies > 1 ? gen_split_backward(d, dv, M, dtype) : gen_split_attention(d, dv, M, dtype)) || !gen_split_length(BH, L, d, M, dtype)) return false;
   *p = base;
   const GenSplitShape s = gen_split_shape(d, dv, M);
   // one workgroup of eight waves per CU, or two of four (rows beyond 64 take the LDS of a CU with four waves too: their segments are cut

@@ -97,6 +97,7 @@ int launch_gen_bwd_walks(const GenSide& qs, const GenSide& ks, const TensorDev& 
                          hipStream_t st);
 // Causal calls on bf16 matrix instructions with fp32 accuracy (kernels_gen_split.hip).
 struct GenSplitShape { int tiles, steps; bool part; int waves; };
+bool gen_split_length(int BH, int L, int d, int M, int dtype);
 int gen_split_part_row(int d, int dv);
 int gen_split_part_sequences(int BH, int L, int d, int dv);
 bool gen_split_attention(int d, int dv, int M, int dtype);

@@ -1012,6 +1012,19 @@ bool gen_split_attention(int d, int dv, int M, int dtype) { return split_rows(d,
 bool gen_split_backward(int d, int dv, int M, int dtype) {
   return split_rows(d, dv, dtype) && M > (!dtype || (d > 64 && d <= 96) ? 128 : 64) && M <= 512;
 }
+// Sequences of a chunk or two: half of a chunk of 32 tokens is padding where a chunk of 16 has none, and the start of a workgroup counts.
+// Speed against the same kernels, 1 - 1024 sequences, M 129 - 512 (bf16 from 70; the lower figures of bf16 are those of M 70):
+//   tokens       8, 16        17 .. 32      48           64           80           96
+//   f32   d 24   0.70 - 0.85  0.92 - 1.06   0.83 - 0.92  0.96 - 1.08  0.95 - 1.06  1.06 - 1.18
+//         d 64   0.73 - 0.90  1.02 - 1.12   0.89 - 1.00  1.06 - 1.18  0.98 - 1.15  1.10 - 1.33
+//   bf16  d 24   0.76 - 0.90  0.96 - 1.10   0.93 - 1.01  1.05 - 1.20  1.02 - 1.20  1.15 - 1.33
+//         d 128  0.74 - 0.95  0.96 - 1.30   0.95 - 1.19  1.10 - 1.45  1.22 - 1.48  1.08 - 1.67
+// (80 tokens of f32 d 24: below one only from 256 sequences on; bf16 d 128 M 129 .. at 48 tokens 1.01 and more)
+bool gen_split_length(int BH, int L, int d, int M, int dtype) {
+  if (L > 80) return true;
+  if (dtype) return L > 48 || (M > 128 && L > 16 && (L <= 32 || d > 32));
+  return d > 32 ? L > 48 || (L > 16 && L <= 32) : L > 48 && BH < 256;
+}
 int gen_split_part_row(int d, int dv) { return (d > dv ? d : dv) + 20; }
 // Sequences whose partial rows are there at a time: 256 MB of them, one at least.
 int gen_split_part_sequences(int BH, int L, int d, int dv) {

@@ -167,3 +167,14 @@ def test_orthogonal_omega_matches_the_oracle_and_reports_rank_deficiency():
         raise AssertionError("rank deficiency not reported")
     except fs.FavorSharpError as e:
         assert "NOT_PD" in str(e).upper() or "singular" in str(e).lower(), str(e)
+
+
+def test_workspace_of_causal_sequences_of_a_chunk_or_two_has_no_images(lib):
+    """Sequences that do not fill the chunks of 32 tokens run without the operand images of the longer ones, which are six bytes for
+    each number of W~ (here 64 and 32 coordinates of 256 features)."""
+    def bytes_of(d, L):
+        return lib.favorsharp_attention_workspace_bytes(1, 4, L, L, d, d, 256, 1, 1, 1)
+    for d, images, without, with_ in ((64, 2 * 256 * 64 * 6, (8, 16), (17, 32, 49)), (24, 2 * 256 * 32 * 6, (8, 16, 33, 48), (17, 49, 81))):
+        few = max(bytes_of(d, L) for L in without)
+        for L in with_:
+            assert bytes_of(d, L) - few >= images, (d, L)

@@ -144,7 +144,9 @@ def test_general_states_of_many_waves(fs, d, dv, M, B, L, causal, dtype):
 
 @pytest.mark.parametrize("d,dv,M,L,B", [(20, 28, 129, 31, 3), (32, 44, 256, 65, 3), (64, 60, 140, 40, 3), (36, 64, 257, 97, 3),
                                         (60, 36, 512, 130, 3), (32, 20, 65, 70, 3), (128, 124, 70, 33, 3), (100, 128, 130, 64, 3),
-                                        (96, 68, 300, 100, 3), (128, 80, 511, 160, 3), (20, 28, 257, 100, 16000)])
+                                        (96, 68, 300, 100, 3), (128, 80, 511, 160, 3), (20, 28, 257, 100, 16000),
+                                        (20, 28, 129, 63, 3), (32, 44, 256, 81, 300), (64, 60, 140, 17, 3), (60, 76, 200, 50, 3), (32, 20, 65, 49, 3),
+                                        (128, 124, 70, 55, 3), (100, 128, 130, 33, 3), (24, 40, 200, 17, 3), (64, 60, 140, 16, 3), (32, 44, 256, 48, 300)])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_general_causal_calls_on_bf16_matrix_instructions(fs, d, dv, M, L, B, dtype):
     """Causal calls whose fp32 products run on bf16 pieces: remainders of tokens, coordinates, value columns (one and two blocks of
