@@ -77,14 +77,15 @@ bool plan_split(int BH, int pgroups, int L, int d, int dv, int M, int dtype, int
   if (!(copies > 1 ? gen_split_backward(d, dv, M, dtype) : gen_split_attention(d, dv, M, dtype)) || !gen_split_length(BH, L, d, M, dtype)) return false;
   *p = base;
   const GenSplitShape s = gen_split_shape(d, dv, M);
-  // one workgroup of eight waves per CU, or two of four (rows beyond 64 take the LDS of a CU with four waves too: their segments are cut
-  // for more places than there are); the fewest chunks in sequence over one to four passes, a workgroup's start being two
-  const int slots = 256 * 8 / s.waves;
+  // one workgroup of eight waves per CU, or two of four: but of the walks of the gradients, beyond rows of 64, the LDS of a CU fits one (bf16
+  // 256 x 80 d 128 M 100: 378 us with two counted there too, 314 with one; 200 x 300: 759 with one counted everywhere, 728); the
+  // fewest chunks in sequence over one to four passes, a workgroup's start being two
+  const int two = 256 * 8 / s.waves, one = copies > 1 && s.steps == 4 ? 256 : two;
   int best = 0;
-  for (int passes = 1; passes <= 4; ++passes) {
-    const int want = std::min(std::max(1, slots * passes / BH), ceil_div(L, 64));
+  for (int passes = 1; passes <= 4 * two / one; ++passes) {
+    const int want = std::min(std::max(1, one * passes / BH), ceil_div(L, 64));
     const int rows = ceil_div(ceil_div(L, want), 32) * 32, nseg = ceil_div(L, rows);
-    const int steps = ceil_div(BH * nseg, slots) * (rows / 32 + 2);
+    const int steps = (ceil_div(BH * nseg, two) + ceil_div(BH * nseg, one)) * (rows / 32 + 2);
     if (passes == 1 || steps < best) {
       best = steps;
       p->rows_per_seg = rows;
