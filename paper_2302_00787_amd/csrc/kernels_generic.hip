@@ -864,23 +864,45 @@ __global__ void k_stats_final(const float* part, int B, int H, int nchunks, int 
   const int first = groups == 1 ? 0 : g, step = groups == 1 ? 1 : H, count = groups == 1 ? B * H : (groups == H ? B : 1);
   const float* p = part + ((size_t)which * B * H + first) * nchunks * per + e;
   const long long rows = (long long)count * (which ? Ly : Lx);
-  // Sixteen parts' loads are in flight together: a thread is one chain of memory latencies, which is what this kernel takes
-  // (8 heads of 8 sequences, d = 64: 11.1 -> 8.6 us against four chunks at a time within a sequence; of 128: bytes, 14 - 15 us).
+  // Sixteen parts' loads are in flight together: a thread is one chain of memory latencies, which is what this kernel takes,
+  // with the scalar work between the requests beside it: a clamp, a select and a 64-bit product per part took longer than the
+  // loads.  So the pointer only advances, parts that lie next to each other (one group, or one per sequence) by constants, and
+  // the last, shorter pass alone is clamped.  us, four chunks of one sequence at a time -> sixteen with a product each -> this:
+  // 8 heads of 8 sequences, d = 64: 11.3 -> 8.7 -> 5.9; d = 128: 15.4 -> 16.6 -> 13.1; one group, d = 128: 50.5 -> 53.3 -> 19.5;
+  // one sequence of 20000, d = 128: 28.0 -> 34.5 -> 13.4; eight of 1000, d = 8: 8.2 -> 4.4 -> 3.4.
   const int total = count * nchunks;
   double s4[4] = {0.0, 0.0, 0.0, 0.0};
-  int c = 0;
-  size_t at = 0;
-  for (int i = 0; i < total; i += 16) {
+  const size_t skip = count == 1 ? 0 : (size_t)(step - 1) * nchunks * per;  // between two of the group's sequences
+  int done = 0, c = 0;
+  for (; done + 16 <= total; done += 16) {
+    float v[16];
+    if (skip == 0) {
+#pragma unroll
+      for (int u = 0; u < 16; ++u) v[u] = p[u * per];
+      p += 16 * per;
+    } else {
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        v[u] = *p;
+        const bool wrap = ++c == nchunks;
+        p += wrap ? per + skip : per;
+        c = wrap ? 0 : c;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 16; ++u) s4[u & 3] += (double)v[u];
+  }
+  if (done < total) {
     float v[16];
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
-      v[u] = p[at * per];
-      const bool more = i + u + 1 < total, wrap = c + 1 == nchunks;
-      at += more ? (wrap ? (size_t)(step - 1) * nchunks + 1 : 1) : 0;
-      c = wrap ? 0 : c + 1;
+      v[u] = *p;
+      const bool wrap = ++c == nchunks;
+      p += done + u + 1 < total ? (wrap ? per + skip : per) : 0;
+      c = wrap ? 0 : c;
     }
 #pragma unroll
-    for (int u = 0; u < 16; ++u) s4[u & 3] += i + u < total ? (double)v[u] : 0.0;
+    for (int u = 0; u < 16; ++u) s4[u & 3] += done + u < total ? (double)v[u] : 0.0;
   }
   const double s = (s4[0] + s4[1]) + (s4[2] + s4[3]);
   stats[i] = s / (double)rows;

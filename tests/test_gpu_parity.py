@@ -586,6 +586,30 @@ def test_fit_params_sets_of_different_sizes(fs, variant, entry):
         assert orc.lbar_bruteforce(got, X[:150], Yk[:200]) == pytest.approx(orc.lbar_bruteforce(ref, X[:150], Yk[:200]), abs=2e-4)
 
 
+@pytest.mark.parametrize("groups", ["one", "heads", "sequences"])
+@pytest.mark.parametrize("L", [20, 256, 300])
+def test_statistics_of_every_kind_of_group(fs, L, groups):
+    """The final sums over a group's partial sums, which lie next to each other (one group, or one per sequence) or a head
+    stride apart: fewer of them than one pass takes (sixteen), just as many, and several passes with a remainder, where a
+    sequence ends within a pass.  Tolerances: those of the fits above."""
+    rng = np.random.default_rng(47)
+    B, H, d = 2, 3, 16
+    sc = np.linspace(0.4, 1.3, d)
+    Q = (rng.standard_normal((B, H, L, d)) * sc + 0.15 + 0.2 * np.arange(B * H).reshape(B, H, 1, 1)).astype(np.float32)
+    K = (rng.standard_normal((B, H, L, d)) * sc[::-1] - 0.1 * np.arange(B * H).reshape(B, H, 1, 1)).astype(np.float32)
+    n = {"one": 1, "heads": H, "sequences": B * H}[groups]
+    s = d ** -0.25
+    theta = _fit(fs, "device", "saderf", util.to_device(Q, "f32"), util.to_device(K, "f32"), s, n)
+    for g in range(n):
+        pick = lambda A: (A if n == 1 else A[:, g] if n == H else A.reshape(B * H, L, d)[g]).reshape(-1, d).astype(np.float64)
+        ref = orc.fit("saderf", s * pick(Q), s * pick(K))
+        got = util.oracle_theta_from_vec(theta[g], d)
+        np.testing.assert_allclose(np.sort(got.A), np.sort(ref.A), atol=2e-5)
+        assert got.logD == pytest.approx(ref.logD, abs=1e-4)
+        np.testing.assert_allclose(got.B1.T @ got.B1, ref.B1.T @ ref.B1, atol=3e-4)
+        np.testing.assert_allclose(got.C1, ref.C1, atol=3e-4)
+
+
 @pytest.mark.parametrize("variant", ["sderf", "aderf"])
 @pytest.mark.parametrize("d", [9, 64, 128])
 def test_device_fit_dense_families_at_other_sizes(fs, variant, d):
