@@ -97,8 +97,8 @@ bool plan_split(int BH, int pgroups, int L, int d, int dv, int M, int dtype, int
   const size_t maxima = (size_t)BH * ceil_div(L, VMAX_ROWS) * sizeof(float);
   p->off_vmax = align_up(p->off_img + copies * p->img_bytes);
   p->off_dmax = align_up(p->off_vmax + maxima);
-  p->off_exps = align_up(p->off_dmax + (copies > 1 ? maxima : 0));
-  p->off_part = align_up(p->off_exps + (size_t)copies * BH * sizeof(int));
+  p->off_exps = align_up(p->off_dmax + (copies > 1 ? (size_t)BH * ceil_div(L, GMAX_ROWS) * sizeof(float) : 0));
+  p->off_part = align_up(p->off_exps + (size_t)(copies > 1 ? 3 : 1) * BH * sizeof(int));
   p->total = align_up(p->off_part + (s.part ? (size_t)gen_split_part_sequences(BH, L, d, dv) * L * gen_split_part_row(d, dv) * sizeof(float) : 0));
   return copies > 1 || base.total > FS_NOALLOC_SCRATCH_BYTES || p->total <= FS_NOALLOC_SCRATCH_BYTES;
 }
@@ -858,7 +858,7 @@ int attention_backward_impl(const float* theta, int groups, const fs_tensor* Q, 
       return rc;
   }
   // G1 in place of Y, then the segment sums of P^T G1 (the query-side twin of the state pass)
-  if (int rc = launch_bwd_ghat(dev(dY), ghat, den, split.img ? split.exps + BH : nullptr, Lq, BH, H, dv, ldt, st)) return rc;
+  if (int rc = launch_bwd_ghat(dev(dY), ghat, den, split.img ? split.exps + BH : nullptr, split.dmax, Lq, BH, H, dv, ldt, st)) return rc;
   if (int rc = split.img ? launch_split_state(qs, split, false, gbuf, Lq, BH, H, M, d, dv, ldt, p.q.rows_per_seg, p.q.nseg, kmax, nullptr, 0, shift,
                                               rstate, st)
                          : launch_gen_state(qs, gbuf, Lq, BH, H, M, d, ldt, 0, ldt, p.q.rows_per_seg, p.q.nseg, kmax, shift, !walks, rstate, st))

@@ -40,14 +40,14 @@ size_t gen_lds_stats(int d);
 
 // Operand images of the projection matrices in bf16 pieces (kernels_gen_split.hip): W~ times qk_scale for `tiles` tiles of 16
 // features and `steps` steps of 32 coordinates; img_t, for the gradients only, by coordinate.
-constexpr int VMAX_ROWS = 64;
+constexpr int VMAX_ROWS = 64, GMAX_ROWS = 16;
 struct GenSplit {
   uint16_t* img = nullptr;
   uint16_t* img_t = nullptr;
   TensorDev V{}, dY{};     // values and (gradients) the gradient of the output; k_prep leaves the largest numbers of VMAX_ROWS rows each:
   int nv = 0, L = 0, BH = 0;
-  float *vmax = nullptr, *dmax = nullptr;      // [BH][ceil(L / VMAX_ROWS)]
-  int* exps = nullptr;     // [2][B*H] binary exponents that values and gradient are divided by
+  float *vmax = nullptr, *dmax = nullptr;      // [BH][ceil(L / VMAX_ROWS)]; k_bwd_ghat leaves those of G1 in dmax, [BH][ceil(L / GMAX_ROWS)]
+  int* exps = nullptr;     // [B*H] binary exponents that values, (gradients) [3][B*H] that dY and G1 are divided by
   float* part = nullptr;   // [gen_split_part_sequences][rows][gen_split_part_row] of the first of two launches
   int tiles = 0, steps = 0;
   float scale = 1.f;
@@ -69,7 +69,7 @@ int launch_gen_apply(const GenSide& qs, int Lq, int BH, int H, int M, int d, int
                      float* shift_out, hipStream_t st, unsigned* flushed = nullptr);
 // Backward pass of non-causal attention (general-shape kernels).
 size_t gen_lds_bwd_side(int d, int ldt);
-int launch_bwd_ghat(const TensorDev& dY, float* buf, const float* den, const int* exps, int L, int BH, int H, int nv, int ldt,
+int launch_bwd_ghat(const TensorDev& dY, float* buf, const float* den, const int* exps, float* largest, int L, int BH, int H, int nv, int ldt,
                     hipStream_t st);
 int launch_gen_bwd_side(const GenSide& sd, int side, const TensorDev& A, int a_cols, int append_ones, int L, int BH,
                         int H, int M, int d, int nv, int ldt, const float* St, size_t state_stride,

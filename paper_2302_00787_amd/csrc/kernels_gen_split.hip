@@ -32,13 +32,18 @@ constexpr int LDR(int cols) { return cols + 8; }         // stride of LDS rows (
 constexpr int IMG = 512;                                 // numbers of an operand image
 // Pieces of numbers below 2^-109 lose bits, so no operand is left there.  Features lie in 2^-126 .. 1 (a causal row may see only keys
 // whose features are that far below the largest of the sequence); they are lifted by 2^12 before they are split: one of 2^-126 is then off
-// by 2^-20 of itself, less than by the rounding of its exponent, 2^-18.  Values and the gradient of the output are divided by the power
-// of two of the largest of their sequence where that is far from one (k_prep finds it beside the constants), so that the lift
-// leaves room above.  Sums carry the factors.  Output rows and their normalisers have 2^24: the quotient loses it, and G1, made from
-// those normalisers, is 2^24 too small; a sum with one feature of each side and G1 (dV) is as it should be, one with a feature of one
-// side (R, dQ, dK) 2^12 too small.  (Keys 2^-121 below the largest: outputs up to 1.8e-5 off without it, gradients 5e-4, now 3e-7 and
-// 6e-6, as with fp32 instructions; V or dY near 2^-110 / 2^-120: gradients up to 8e-6 / 8e-3 off, now 2e-7 - 8e-7.  causal f32 B2 H4 L4096
-// d64 M256 106.5 -> 108.3 us; gradients bf16 B1 H16 L4096 d128 M512 1622 -> 1653, of which the maxima 10.)
+// by 2^-20 of itself, less than by the rounding of its exponent, 2^-18.  Output rows and their normalisers have 2^24, which the quotient
+// loses; a sum with one feature of either side (dV) has 2^24, one with a feature of one side (R, dQ, dK) 2^12.
+// Values, dY and G1 are divided by powers of two, found for each sequence beside the constants (k_prep) and the G1 rows (k_bwd_ghat):
+//   V     its largest number is left where it is from 2^-16 to 2^48, brought to one below and to 2^48 above, so that it does not leave the
+//         range with the lift, nor with the sums over a million tokens;
+//   dY    its largest number is brought to one, so that G1, a normaliser's size off, is neither subnormal nor infinite;
+//   G1    its largest number is brought to 2^64 (a product with a value is at most about that: the last column is such a product,
+//         summed), so that rows far below the largest have all pieces, down to 2^-125 of it and less.
+// (Keys 2^-121 below the largest: outputs up to 1.8e-5 off without the lift, gradients 5e-4, now 3e-7 and 6e-6, as with fp32
+// instructions; V or dY near 2^-120, or rows of dY 2^-105 and of V 2^-100 below the largest: up to 1 off where numbers are
+// divided by the largest of V and dY alone, 8e-3 undivided, now 2e-7 - 8e-7.  Causal f32 B2 H4 L4096 d64 M256 106.5 -> 108.3 us; gradients
+// bf16 B1 H16 L4096 d128 M512 1622 -> 1658, of which the maxima 10.)
 constexpr int LIFT = 12;
 constexpr float kLift = 1 << LIFT;
 constexpr float kLeastSum = 0x1p-125f;                   // kLift^2 times the least fp32 number: below it a normaliser counts as zero
@@ -147,11 +152,12 @@ template <int COLS, int NW, int P> struct Fetch {
   }
 };
 
-// The binary exponent of the largest number of a tensor's rows, where it is far from one (then they are divided by it).
-__device__ __forceinline__ int far_exponent(float largest) {
-  const int e = __builtin_amdgcn_frexp_expf(largest);      // (0 for what is not finite)
-  return e < -16 || e > 16 ? e : 0;
+// The exponents that V and G1 are divided by, of their largest numbers.
+__device__ __forceinline__ int value_exponent(float largest) {
+  const int e = __builtin_amdgcn_frexp_expf(largest);
+  return e < -16 ? e : max(e - 48, 0);
 }
+__device__ __forceinline__ int left_exponent(float largest) { return __builtin_amdgcn_frexp_expf(largest) - 64; }
 
 struct SplitArgs {
   GenSide F, S;            // first side (whose rows enter the state), second side (whose rows are the output's)
@@ -163,9 +169,9 @@ struct SplitArgs {
   uint32_t* kmax_u;
   const float* part;       // partial key maxima (k_gen_kmax) or nullptr: kmax_u has the maximum
   int npart;
-  const float *vmax, *dmax;    // [BH][nvmax] partial maxima of |V|, |dY|
+  const float *vmax, *dmax;    // [BH][nvmax] partial maxima of |V|, |dY|; behind k_bwd_ghat dmax has those of |G1|, of GMAX_ROWS rows
   int nvmax;
-  int* exps;               // [2][BH] exponents of V and dY
+  int* exps;               // [BH] exponents that V is divided by; (gradients) [3][BH], those of dY and G1 behind them
   const float* row_shift;  // [BH][L] shifts of the queries
   float* state;            // [BH][nseg][M][ldt]: sums of the segments (written), exclusive prefix or suffix (read)
   TensorDev out;
@@ -267,31 +273,37 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_state(SplitA
   const RowSrc xf = row_src(a.F.X, b, h, 0, a.d, 0), vf = row_src(a.V, b, h, 0, a.vcols, a.vone);
   Fetch<XC, NW, XP> px;
   Fetch<VC, NW, VP> pv;
+  // (the first partial maxima of each lane are requested ahead of the rows: their reduction waits for no more than them)
+  const bool first = seg == 0 && blockIdx.z == 0;             // leaves what was found for the kernels behind this one
+  const int nmax = KEYS ? a.nvmax : (a.L + GMAX_ROWS - 1) / GMAX_ROWS;
+  const float *vmax = (KEYS ? a.vmax : a.dmax) + (size_t)bh * nmax, *kpart = a.part + (size_t)bh * a.npart;
+  float vm = vmax[min(lane, nmax - 1)], km = KEYS && a.part != nullptr ? kpart[min(lane, a.npart - 1)] : 0.f, kmax = 0.f;
   px.get(xf, row_beg, row_end, threadIdx.x);
   pv.get(vf, row_beg, row_end, threadIdx.x);
-  float kmax = 0.f;
-  int ve = 0;
-  if (KEYS) {
-    float km = -INFINITY, vm = 0.f, dm = 0.f;
-    if (a.part != nullptr)
-      for (int i = lane; i < a.npart; i += 64) km = fmaxf(km, a.part[(size_t)bh * a.npart + i]);
-    for (int i = lane; i < a.nvmax; i += 64) {
-      vm = fmaxf(vm, a.vmax[(size_t)bh * a.nvmax + i]);
-      if (a.dmax != nullptr) dm = fmaxf(dm, a.dmax[(size_t)bh * a.nvmax + i]);
-    }
+  for (int i = lane + 64; i < nmax; i += 64) vm = fmaxf(vm, vmax[i]);
+  if (KEYS && a.part != nullptr)
+    for (int i = lane + 64; i < a.npart; i += 64) km = fmaxf(km, kpart[i]);
 #pragma unroll
-    for (int s = 1; s < 64; s <<= 1) {
-      km = fmaxf(km, __shfl_xor(km, s));
-      vm = fmaxf(vm, __shfl_xor(vm, s));
-      dm = fmaxf(dm, __shfl_xor(dm, s));
-    }
+  for (int s = 1; s < 64; s <<= 1) {
+    if (KEYS) km = fmaxf(km, __shfl_xor(km, s));
+    vm = fmaxf(vm, __shfl_xor(vm, s));
+  }
+  const int ve = KEYS ? value_exponent(vm) : left_exponent(vm);
+  if (KEYS) {
     kmax = a.part != nullptr ? km : ordered_to_float(a.kmax_u[bh]);
-    ve = far_exponent(vm);
-    if (seg == 0 && threadIdx.x == 0 && blockIdx.z == 0) {      // for the kernels behind this one
+    if (first && a.dmax != nullptr) {
+      float dm = 0.f;
+      for (int i = lane; i < nmax; i += 64) dm = fmaxf(dm, a.dmax[(size_t)bh * nmax + i]);
+#pragma unroll
+      for (int s = 1; s < 64; s <<= 1) dm = fmaxf(dm, __shfl_xor(dm, s));
+      if (threadIdx.x == 0) a.exps[a.BH + bh] = __builtin_amdgcn_frexp_expf(dm);
+    }
+    if (first && threadIdx.x == 0) {
       if (a.part != nullptr) a.kmax_u[bh] = float_to_ordered(km);
       a.exps[bh] = ve;
-      if (a.dmax != nullptr) a.exps[a.BH + bh] = far_exponent(dm);
     }
+  } else if (first && threadIdx.x == 0) {
+    a.exps[2 * a.BH + bh] = ve;
   }
   float bf[FT];
   f32x4 T[FT][VT];
@@ -382,7 +394,8 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_walk(SplitAr
   const uint16_t* W2 = side_image<Q>(a, a.img, pg, !F_KEYS) + wave_w;
   const float* bias = a.F.bias + (size_t)pg * 2 * M;        // (the same on both sides)
   const float kmax = ordered_to_float(a.kmax_u[bh]);
-  int ve = a.exps[bh], back = MODE ? a.exps[a.BH + bh] : a.den_out == nullptr ? ve : 0;      // of the values, of the output
+  int ve = MODE ? a.exps[2 * a.BH + bh] : a.exps[bh];                                    // of the values, of the output
+  int back = MODE ? ve + a.exps[a.BH + bh] - 2 * LIFT : a.den_out == nullptr ? ve : 0;
   asm("" : "+v"(ve), "+v"(back));                    // (scalar registers are what runs out)
   const int row_beg = seg * a.rows_per_seg, row_end = min(a.L, row_beg + a.rows_per_seg);
   const int nchunk = (row_end - row_beg + TT - 1) / TT;
@@ -405,7 +418,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_walk(SplitAr
     const int r0 = row_of(ci);
     pf.put(xf, Xf, r0, row_end, tid);
     ps.put(xs, Xs, r0, row_end, tid);
-    pv.put(vf, Vs, r0, row_end, tid, MODE ? 0 : ve);
+    pv.put(vf, Vs, r0, row_end, tid, ve);
   };
   fetch_chunk(0);
   for (int f = threadIdx.x; f < 16 * FT * NW; f += 64 * NW) bl[f] = 16 * a.tile0 + f < M ? bias[16 * a.tile0 + f] : -INFINITY;
@@ -656,8 +669,8 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_gwalk(SplitA
   const uint16_t* Wt = side_image<Q>(a, a.img_t, pg, !F_KEYS) + wave_w;
   const float* bias = a.F.bias + (size_t)pg * 2 * M;
   const float kmax = ordered_to_float(a.kmax_u[bh]), scale = a.S.scale;
-  int ve = a.exps[bh], back = ve + a.exps[a.BH + bh] + LIFT;
-  asm("" : "+v"(ve), "+v"(back));
+  int ve = a.exps[bh], ge = a.exps[2 * a.BH + bh], back = ve + ge + a.exps[a.BH + bh] - LIFT;
+  asm("" : "+v"(ve), "+v"(ge), "+v"(back));
   const int row_beg = seg * a.rows_per_seg, row_end = min(a.L, row_beg + a.rows_per_seg);
   const int nchunk = (row_end - row_beg + TT - 1) / TT;
   const RowSrc xf = row_src(a.F.X, b, h, 0, d, 0), xs = row_src(a.S.X, b, h, 0, d, 0);
@@ -684,8 +697,8 @@ __global__ void __launch_bounds__(64 * NW, NW == 8 ? 2 : 1) k_split_gwalk(SplitA
     const int r0 = row_of(ci);
     pf.put(xf, Xf, r0, row_end, tid);
     ps.put(xs, Xs, r0, row_end, tid);
-    pv.put(vf, Vs, r0, row_end, tid, MODE ? 0 : ve);
-    pu.put(uf, Us, r0, row_end, tid, MODE ? ve : 0);
+    pv.put(vf, Vs, r0, row_end, tid, MODE ? ge : ve);
+    pu.put(uf, Us, r0, row_end, tid, MODE ? ve : ge);
   };
   // four numbers of a second-side row as they are
   auto x_four = [&](int row, int col) {

@@ -327,7 +327,7 @@ __device__ void rowmax_pass2(uint32_t* rowmax_u, const float* Xs, float* Ws, flo
 // ---------------------------------------------------------------------------------------------------
 constexpr int PREP_F = 4;
 
-// The largest of rows row0 .. row0 + rows - 1 of a tensor, 4 cols numbers each, by 128 threads.
+// The largest finite number of rows row0 .. row0 + rows - 1 of a tensor, 4 cols numbers each, by 128 threads.
 __device__ __forceinline__ float largest_of(const TensorDev& t, long long base, int row0, int rows, int cols, float* red) {
   float m = 0.f;
   for (int e0 = threadIdx.x; e0 < rows * cols; e0 += 8 * 128) {
@@ -344,7 +344,9 @@ __device__ __forceinline__ float largest_of(const TensorDev& t, long long base, 
       }
     }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) m = fmaxf(fmaxf(m, fmaxf(fabsf(v[i][0]), fabsf(v[i][1]))), fmaxf(fabsf(v[i][2]), fabsf(v[i][3])));
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) m = fmaxf(m, fabsf(v[i][j]) < INFINITY ? fabsf(v[i][j]) : 0.f);
   }
 #pragma unroll
   for (int s = 1; s < 64; s <<= 1) m = fmaxf(m, __shfl_xor(m, s));
@@ -919,24 +921,47 @@ __global__ void k_stats_final(const float* part, int B, int H, int nchunks, int 
 
 // In place: row i of `buf` ([bh][L][ldt], holding Y_i in its first nv columns) becomes G1_i (zero padded).
 // Sixteen lanes per row (consecutive columns: coalesced), 16 rows per workgroup of 256 threads.
-__global__ void k_bwd_ghat(TensorDev dY, float* buf, const float* den, const int* exps, int L, int H, int nv, int ldt, size_t rows) {
+// SPLIT (behind k_split_walk): dY is divided by 2^exps, normalisers have a factor 2^24, which is taken out here, and the largest |G1| of the
+// workgroup's rows is left in `largest`; grid (ceil(L / GMAX_ROWS), B H).  Else grid ceil(rows / 16).
+template <bool SPLIT>
+__global__ void __launch_bounds__(256) k_bwd_ghat(TensorDev dY, float* buf, const float* den, const int* exps, float* largest, int L, int H, int nv,
+                                                  int ldt, size_t rows) {
   const size_t i = (size_t)blockIdx.x * 16 + (threadIdx.x >> 4);
   const int l = threadIdx.x & 15;
   const bool live = i < rows;
-  const size_t ii = live ? i : 0;
+  const size_t ii = (live ? i : 0) + (SPLIT ? (size_t)blockIdx.y * L : 0);
   const int bh = (int)(ii / L), row = (int)(ii - (size_t)bh * L), b = bh / H, h = bh % H;
   float* g = buf + ii * ldt;
   const float dn = den[ii];
-  const float inv = dn > 0.f ? 1.f / dn : 0.f, scale = exps != nullptr ? ldexpf(1.f, -exps[bh]) : 1.f;
+  const int e = SPLIT ? -exps[bh] : 0, late = SPLIT && dn < 1.f ? 24 : 0;
+  const float inv = dn > 0.f ? ldexpf(1.f / dn, SPLIT ? 24 - late : 0) : 0.f;      // (neither it nor its product with dY vanishes)
   const long long base = b * dY.sb + h * dY.sh + (long long)row * dY.sl;
+  const auto dy = [&](int c) { return SPLIT ? ldexpf(load_elem(dY, base + c), e) : load_elem(dY, base + c); };
   float dot = 0.f;
-  for (int c = l; c < nv; c += 16) dot += load_elem(dY, base + c) * scale * g[c];
+  for (int c = l; c < nv; c += 16) dot += dy(c) * g[c];
   dot += __shfl_xor(dot, 1);
   dot += __shfl_xor(dot, 2);
   dot += __shfl_xor(dot, 4);
   dot += __shfl_xor(dot, 8);
-  if (!live) return;
-  for (int c = l; c < ldt; c += 16) g[c] = c < nv ? load_elem(dY, base + c) * scale * inv : (c == nv ? -dot * inv : 0.f);
+  if (!SPLIT && !live) return;
+  float most = 0.f;
+  if (live)
+    for (int c = l; c < ldt; c += 16) {
+      float v = c < nv ? dy(c) * inv : (c == nv ? -dot * inv : 0.f);
+      if (SPLIT) {
+        v = ldexpf(v, late);
+        if (fabsf(v) < INFINITY) most = fmaxf(most, fabsf(v));
+      }
+      g[c] = v;
+    }
+  if constexpr (SPLIT) {
+    __shared__ float red[4];
+#pragma unroll
+    for (int s = 1; s < 64; s <<= 1) most = fmaxf(most, __shfl_xor(most, s));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = most;
+    __syncthreads();
+    if (threadIdx.x == 0) largest[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+  }
 }
 
 // One side of the backward pass for a tile of 32 rows.  F = this side's features (query side: per-row shifts from
@@ -1609,10 +1634,13 @@ size_t gen_lds_bwd_side(int d, int ldt) {
   return ((size_t)(TR + MB) * ld + (size_t)(TR + MB) * (ldt + 1) + (size_t)2 * TR * (MB + 1) + MB + 2 * TR) * 4;
 }
 
-int launch_bwd_ghat(const TensorDev& dY, float* buf, const float* den, const int* exps, int L, int BH, int H, int nv, int ldt,
+int launch_bwd_ghat(const TensorDev& dY, float* buf, const float* den, const int* exps, float* largest, int L, int BH, int H, int nv, int ldt,
                     hipStream_t st) {
   const size_t rows = (size_t)BH * L;
-  hipLaunchKernelGGL(k_bwd_ghat, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, st, dY, buf, den, exps, L, H, nv, ldt, rows);
+  if (largest != nullptr)
+    hipLaunchKernelGGL(k_bwd_ghat<true>, dim3((L + GMAX_ROWS - 1) / GMAX_ROWS, BH), dim3(256), 0, st, dY, buf, den, exps, largest, L, H, nv, ldt, (size_t)L);
+  else
+    hipLaunchKernelGGL(k_bwd_ghat<false>, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, st, dY, buf, den, exps, largest, L, H, nv, ldt, rows);
   FS_LAUNCH_CHECK();
   return 0;
 }

@@ -283,6 +283,42 @@ def test_general_causal_values_of_any_size(fs, d, M, dtype, kv, kd):
                 assert float((x[b, 0, part].double() - r[part]).norm() / r[part].norm()) <= 1.2e-5, (b, name, part)
 
 
+@pytest.mark.parametrize("values,lefts", [((-100, 20), (0, 0)), ((-60, 60), (60, 0)), ((-20, 100), (0, 0)), ((0, 0), (0, -105)),
+                                          ((0, 0), (20, -90)), ((0, 60), (60, -60)), ((-90, 30), (30, -80))])
+@pytest.mark.parametrize("d,M,dtype", [(32, 160, "f32"), (64, 300, "f32"), (48, 100, "bf16"), (128, 300, "bf16")])
+def test_general_causal_rows_of_every_size_in_one_sequence(fs, d, M, dtype, values, lefts):
+    """The first 40 rows of V near 2^values[0], the others near 2^values[1]; dY near 2^lefts[0] but for its last 40 rows, 2^lefts[1];
+    with an infinity among the last, which none of the first rows sees.  Rows of both ends as near to float64 as fp32 sums are."""
+    import torch
+    L, n, s = 100, 40, d ** -0.25
+    gen = torch.Generator(device="cuda").manual_seed(d + M)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    Q, K, V, dY = (f * torch.randn((1, 1, L, d), generator=gen, device="cuda") for f in (0.5, 0.5, 1.0, 1.0))
+    V[:, :, :n] *= 2.0 ** values[0]
+    V[:, :, n:] *= 2.0 ** values[1]
+    dY[:, :, :-n] *= 2.0 ** lefts[0]
+    dY[:, :, -n:] *= 2.0 ** lefts[1]
+    Q, K, V, dY = (x.to(dt) for x in (Q, K, V, dY))
+    Om = torch.randn((1, M, d), generator=gen, device="cuda")
+    td = torch.from_numpy(util.theta_vec_from_oracle(orc.fit_posrf(d))[None]).cuda()
+    om = Om[0].double()
+    q, k, v = (x[0, 0].double().requires_grad_(True) for x in (Q, K, V))
+    W = torch.tril(torch.exp(s * q @ om.T) @ torch.exp(s * k @ om.T - 0.5 * s * s * (k * k).sum(1, keepdim=True)).T)
+    ref = (W @ v) / W.sum(1, keepdim=True)
+    gref = torch.autograd.grad((ref * dY[0, 0].double()).sum(), (q, k, v))
+    for infinite in (False, True):
+        if infinite:
+            V = V.clone()
+            V[:, :, -1, 0] = float("inf")
+        got = (fs.attention(td, Q, K, V, s, Om, causal=True, out_dtype=torch.float32),
+               *fs.attention_backward(td, Q, K, V, dY, s, Om, causal=True, grad_dtype=torch.float32))
+        for x, r, name in zip(got, (ref.detach(), *gref), "YQKV"):
+            if infinite and name == "K":
+                continue
+            for part in (slice(0, n), slice(n, L - n), slice(L - n, L))[:1 if infinite else 3]:
+                assert float((x[0, 0, part].double() - r[part]).norm() / r[part].norm()) <= 1.2e-5, (infinite, name, part)
+
+
 @pytest.mark.parametrize("row", [42, 58])
 @pytest.mark.parametrize("d,M,dtype", [(32, 160, "f32"), (64, 300, "f32"), (48, 100, "bf16"), (128, 300, "bf16")])
 def test_general_causal_rows_that_are_not_finite_stay_in_their_tile(fs, d, M, dtype, row):
