@@ -43,6 +43,7 @@ constexpr int DMAX = 64;
 constexpr int IMG = 512;        // numbers of an operand image: 64 lanes x 8
 constexpr int LIFT = 12;        // binary exponent of the factor on the features of either side
 constexpr float kLift = 1 << LIFT;
+constexpr int FAR = 64;         // parts of the state from larger right-hand sides are stored at 2^-LIFT, not 2^LIFT (sums near the largest number)
 constexpr int NONE = -1000;     // exponent of a column of zeros
 // (the kernels are instantiated for KS = 1 and 2 contraction steps of a projection: d <= 32 and d <= 64; numbers past d are zero)
 
@@ -270,7 +271,7 @@ __global__ void __launch_bounds__(NTH, 2) k_op_state(OpArgs a) {
     t = mfma3(split3(e[2], e[3]), cs[1], t);
     float* out = a.Tpart + ((size_t)blockIdx.x * a.M + 16 * ft + 4 * g) * NC + c;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) out[(size_t)r * NC] = ldexpf(t[r], ce);
+    for (int r = 0; r < 4; ++r) out[(size_t)r * NC] = ldexpf(t[r], ce - (ce > FAR ? 2 * LIFT : 0));
     if (lane == 0) a.tshift[(size_t)ft * a.nwg + blockIdx.x] = shift;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) wr[ks] = wn[ks];
@@ -281,7 +282,7 @@ __global__ void __launch_bounds__(NTH, 2) k_op_state(OpArgs a) {
 // workgroups' partial states dealt to the sixteen waves.  (A last tile without a partner gets one of zeros.)
 __global__ void __launch_bounds__(1024) k_op_reduce(const float* Tpart, const float* tshift, const int* cexp, uint16_t* T, float* tstar, int* cstar,
                                                     int nwg, int M) {
-  __shared__ float red[16], part[16][64];
+  __shared__ float red[16][2], part[16][64];
   __shared__ int cred[16][NC];
   const int ft = blockIdx.x >> 2, q = threadIdx.x >> 6, l = threadIdx.x & 63;
   const float* sh = tshift + (size_t)ft * nwg;
@@ -302,19 +303,37 @@ __global__ void __launch_bounds__(1024) k_op_reduce(const float* Tpart, const fl
   float ts = -INFINITY;
   for (int i = threadIdx.x; i < nwg; i += 1024) ts = fmaxf(ts, sh[i]);
   ts = fast::wave_max(ts);
-  if (l == 0) red[q] = ts;
   cs = max(cs, __shfl_xor(cs, 16));
   cs = max(cs, __shfl_xor(cs, 32));
   if (l < NC) cred[q][l] = cs;
+  const float any = __any(cs > FAR) ? 1.f : 0.f;
+  if (l == 0) {
+    red[q][0] = ts;
+    red[q][1] = any;
+  }
   __syncthreads();
-  ts = red[0];
+  ts = red[0][0];
+  float far = red[0][1];
 #pragma unroll
-  for (int i = 1; i < 16; ++i) ts = fmaxf(ts, red[i]);
+  for (int i = 1; i < 16; ++i) {
+    ts = fmaxf(ts, red[i][0]);
+    far = fmaxf(far, red[i][1]);
+  }
   float acc = 0.f;
 #pragma unroll
   for (int u = 0; u < 16; ++u) acc += q + 16 * u < nwg ? v[u] * fast_exp2(s16[u] - ts) : 0.f;
 #pragma unroll 4
   for (int i = q + 256; i < nwg; i += 16) acc += p[i * total] * fast_exp2(sh[i] - ts);
+  int down = 0;
+  if (far > 0.f) {                                   // (there are parts at 2^-LIFT: those at 2^LIFT are brought down)
+    cs = NONE;
+    for (int i = 0; i < 16; ++i) cs = max(cs, cred[i][l & 15]);
+    if (cs > FAR) {
+      down = 2 * LIFT;
+      acc = 0.f;
+      for (int i = q; i < nwg; i += 16) acc += ldexpf(p[i * total], cexp[i * NC + (l & 15)] > FAR ? 0 : -down) * fast_exp2(sh[i] - ts);
+    }
+  }
   part[q][l] = acc;
   __syncthreads();
   if (q == 0) {
@@ -323,7 +342,7 @@ __global__ void __launch_bounds__(1024) k_op_reduce(const float* Tpart, const fl
       acc += part[i][l];
       cs = max(cs, cred[i][l & 15]);
     }
-    acc = ldexpf(acc, -cs);
+    acc = ldexpf(acc, down - cs);
     if (blockIdx.x == 0 && l < NC) cstar[l] = cs;
     const int f = (blockIdx.x & 3) * 4 + (l >> 4), n = l & 15;        // feature of the tile, column
     uint16_t* at = T + (size_t)(ft >> 1) * 3 * IMG + ((f >> 2) * 16 + n) * 8 + (f & 3);

@@ -491,6 +491,31 @@ def test_kernel_matvec_columns_of_any_size(fs, d, M, n, below):
     assert bool((out[:, n - 1] == 0).all())
 
 
+@pytest.mark.parametrize("Ny,d,M", [(200, 32, 512), (5000, 8, 64), (20000, 64, 32)])
+def test_kernel_matvec_large_right_hand_sides(fs, Ny, d, M):
+    """Columns of C whose sums are near the largest number, in all rows or in few (the others near 2^60, and near one), beside one
+    of zeros and one near one; workgroups of 64 rows with and without large numbers.  The bar of the test above."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(Ny)
+    X, Y = (0.2 * torch.randn((N, d), generator=gen, device="cuda") for N in (100, Ny))
+    C = torch.randn((Ny, 5), generator=gen, device="cuda")
+    C[:, 0] *= 2.0 ** 126 / Ny
+    C[:, 1] *= 2.0 ** 60
+    C[::150, 1] *= 2.0 ** 58
+    C[7, 2] *= 2.0 ** 120
+    C[:, 3] = 0.0
+    Om = torch.randn((M, d), generator=gen, device="cuda")
+    td = torch.from_numpy(util.theta_vec_from_oracle(orc.fit_posrf(d))).cuda()
+    out = fs.kernel_matvec(td, X, Y, 1.0, 0.0, Om, C)
+    om = Om.double()
+    f = lambda Z: torch.exp(Z.double() @ om.T - 0.5 * (Z.double() ** 2).sum(1, keepdim=True))
+    ref = f(X) @ (f(Y).T @ C.double()) / M
+    assert float(ref.abs().max()) < 2.0 ** 127
+    for i in (0, 1, 2, 4):
+        assert float((out[:, i].double() - ref[:, i]).norm() / ref[:, i].norm()) <= 1.1e-5, i
+    assert bool((out[:, 3] == 0).all())
+
+
 @pytest.mark.parametrize("below", [100, 118])
 def test_kernel_matvec_features_near_the_least(fs, below):
     """As above, features down to 2^-124 and C near one: 64 features, whose 1/8 is all that comes off the exponents."""
