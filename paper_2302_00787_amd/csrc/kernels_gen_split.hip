@@ -10,8 +10,8 @@
 //
 // What bounds it: the matrix pipe needs 96 cycles for 16 x 16 x 32 numbers (48 against bf16 tensors; fp32 instructions 256), splitting an
 // accumulator pair 28 vector instructions; W~ is 6 bytes per feature and coordinate and chunk from L2.  Two waves per SIMD overlap the two
-// pipes about half.  Against fp32 instructions: causal attention f32 B2 H4 L4096 d64 M256 147 -> 107 us (walk 87 -> 61, states 38 -> 26),
-// gradients bf16 B1 H16 L4096 d128 M512 3510 -> 1655 (four walks 2570 -> 1320 in eight launches, two states 680 -> 188), results
+// pipes about half.  Against fp32 instructions: causal attention f32 B2 H4 L4096 d64 M256 147 -> 107 us (walk 87 -> 61, states 38 -> 25),
+// gradients bf16 B1 H16 L4096 d128 M512 3510 -> 1660 (four walks 2570 -> 1325 in eight launches, two states 680 -> 190), results
 // of 60 drawn calls 0.93 times as far from 64 bits.
 #include <type_traits>
 
